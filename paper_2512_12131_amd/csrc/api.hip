@@ -55,10 +55,15 @@ void gemm(Ctx& c, GemmOp op) {
     LAUNCH(c, gemm_f32(op, c.st));
     return;
   }
-  if (gemm_bf16_kmajor_ok(op)) {   // weight gradient: both operands k-major, read in place
+  // read in place: a weight gradient's two k-major operands, and a k-major weight under the smaller tiles (a size
+  // query leaves room for the copy: it does not know the epilogue of the call, which the choice of tile looks at)
+  if (gemm_bf16_kmajor_ok(op) || (!c.dry && gemm_bf16_mixed_ok(op))) {
     LAUNCH(c, gemm_bf16(op, c.st));
     return;
   }
+  // everything below runs k-contiguous on the 256-row tiles; the choice was made with the k-major form in view
+  // and its row partials are laid out for it
+  if (op.transA || op.transB) op.tile = GEMM_T256;
   const size_t m = c.mark();
   if (op.transA) {
     // only un-batched k-major A operands occur (weight gradients)
@@ -85,17 +90,51 @@ void gemm(Ctx& c, GemmOp op) {
 }
 
 // dw[Mw, Nw] (+)= colscale * sum_t Aact[t, Mw] * Bact[t, Nw]    (reduction over tokens, split-K)
+// n > 1: n such products, operands sA / sB elements apart, gradients stacked [n][Mw][Nw].
 void wgrad(Ctx& c, const void* Aact, int64_t lda, int Mw, const void* Bact, int64_t ldb, int Nw, int64_t T, void* dw,
-           const void* colscale, const void* w_for_dgamma, float* dgamma_part, int accumulate) {
+           const void* colscale, const void* w_for_dgamma, float* dgamma_part, int accumulate, int n = 1, int64_t sA = 0,
+           int64_t sB = 0) {
   const size_t m = c.mark();
   GemmOp op;
-  op.A = Aact; op.lda = lda; op.transA = 1;
-  op.B = Bact; op.ldb = ldb; op.transB = 1;
-  op.M = Mw; op.N = Nw; op.K = (int)T;
-  op.splitk = gemm_bf16_pick_splitk(Mw, Nw, (int)T, 1);
+  op.A = Aact; op.lda = lda; op.transA = 1; op.sA = sA;
+  op.B = Bact; op.ldb = ldb; op.transB = 1; op.sB = sB;
+  op.M = Mw; op.N = Nw; op.K = (int)T; op.batch = n;
+  op.epi.kind = EPI_PARTIAL;
+  const bool kmajor = c.dt == LR_F32 || gemm_bf16_kmajor_ok(op);
+  auto plan = [&](int batch, bool direct) {
+    if (c.dt == LR_F32) return WgradPlan{GEMM_TILE_AUTO, gemm_f32_pick_splitk(Mw, Nw, (int)T, batch)};
+    return gemm_bf16_plan_wgrad(Mw, Nw, (int)T, batch, direct);
+  };
+  if (c.dry) {   // a size query knows neither `accumulate` nor what else is folded in: room for every form of the call
+    int splits = 0;
+    for (int batch : {1, n})
+      for (bool direct : {false, true}) {
+        const int s = plan(batch, direct).splitk;
+        if (!(direct && kmajor && s == 1) && s > splits) splits = s;
+      }
+    c.take((size_t)splits * Mw * Nw * sizeof(float));
+    gemm(c, op);
+    c.release(m);
+    return;
+  }
+  // nothing to scale, add to or sum up: an un-split product is the gradient itself, in either output type
+  const bool direct = !colscale && !w_for_dgamma && !accumulate && kmajor;
+  const WgradPlan pl = plan(n, direct);
+  op.tile = pl.tile; op.splitk = pl.splitk;
+  if (direct && op.splitk == 1) {
+    op.C = dw; op.ldc = Nw; op.sC = (int64_t)Mw * Nw;
+    if (c.gdt == LR_BF16) op.epi.kind = EPI_STORE;   // EPI_PARTIAL stores fp32
+    gemm(c, op);
+    return;
+  }
+  if (n > 1) {   // the finishing pass takes one product at a time
+    for (int i = 0; i < n; i++)
+      wgrad(c, (const char*)Aact + (size_t)i * sA * esize(c.dt), lda, Mw, (const char*)Bact + (size_t)i * sB * esize(c.dt), ldb,
+            Nw, T, (char*)dw + (size_t)i * Mw * Nw * esize(c.gdt), colscale, w_for_dgamma, dgamma_part, accumulate);
+    return;
+  }
   float* part = (float*)c.take((size_t)op.splitk * Mw * Nw * sizeof(float));
   op.C = part; op.ldc = Nw;
-  op.epi.kind = EPI_PARTIAL;
   gemm(c, op);
   LAUNCH(c, k_wgrad_finish(part, op.splitk, Mw, Nw, dw, colscale, w_for_dgamma, dgamma_part, accumulate, c.dt, c.gdt, c.st));
   c.release(m);
@@ -281,25 +320,23 @@ void group_bwd_seq(Ctx& c, const GrpArgs& a, const void* act) {
   GrpRun run[2];
   const int nrun = group_runs(a, run);
   // dW_up[g] = dy_g^T . sigma(z_g)
-  for (int i = 0; i < nrun; i++)
-    for (int j = 0; j < run[i].n; j++) {
-      const GrpRun& u = run[i];
-      wgrad(c, (const char*)a.dy_stack + (size_t)(u.dy_off + j * u.dy_bs) * es, u.lddy, (int)u.d_out,
-            (const char*)act + (size_t)(u.g0 + j) * a.r * es, GR, (int)a.r, a.T,
-            (char*)a.dw_up_stack + (size_t)(u.w_off + j * u.d_out * a.r) * esize(c.gdt), nullptr, nullptr, nullptr,
-            a.accumulate);
-    }
+  for (int i = 0; i < nrun; i++) {
+    const GrpRun& u = run[i];
+    wgrad(c, (const char*)a.dy_stack + (size_t)u.dy_off * es, u.lddy, (int)u.d_out, (const char*)act + (size_t)u.g0 * a.r * es,
+          GR, (int)a.r, a.T, (char*)a.dw_up_stack + (size_t)u.w_off * esize(c.gdt), nullptr, nullptr, nullptr,
+          a.accumulate, u.n, u.dy_bs, a.r);
+  }
   // dp_g = rho * (dy_g . W_up_g) * sigma'(z_g), batched over g, written into the columns of dp_cat;
   // cdot[t] = sum_n dp[t,n] z[t,n] is the RMSNorm-backward statistic, taken at rank r.
   void* dp = c.take((size_t)a.T * GR * es);
   float* cdot = normed ? (float*)c.take((size_t)a.T * sizeof(float)) : nullptr;
   // one launch per run of equally wide members (one launch in all unless the key / value members are narrower)
-  const int slabs1 = (normed && c.dt == LR_BF16) ? gemm_bf16_rowpart_slabs((int)a.r) : 0;   // row-partial columns per member
-  float* parts = slabs1 ? (float*)c.take((size_t)a.T * slabs1 * a.G * sizeof(float)) : nullptr;
   auto at = [&](const void* p, int g0) -> const void* { return p ? (const char*)p + (size_t)g0 * a.r * es : nullptr; };
+  GemmOp das[2];
+  RowParts rp{0, 0, 0};                         // row partials of one member: as wide in every run, so one tile for all
   for (int i = 0; i < nrun; i++) {
     const GrpRun& u = run[i];
-    GemmOp da;
+    GemmOp& da = das[i];
     da.A = (const char*)a.dy_stack + (size_t)u.dy_off * es; da.lda = u.lddy; da.sA = u.dy_bs;
     da.B = (const char*)a.w_up_stack + (size_t)u.w_off * es; da.ldb = a.r; da.sB = u.d_out * a.r; da.transB = 1;
     da.C = (char*)dp + (size_t)u.g0 * a.r * es; da.ldc = GR; da.sC = a.r;
@@ -312,14 +349,23 @@ void group_bwd_seq(Ctx& c, const GrpArgs& a, const void* act) {
     }
     if (normed) {
       da.epi.use_rho = 1; da.epi.rowa = a.statc; da.epi.inv_d = 1.f / (float)a.d_in; da.epi.eps = a.eps;
+      if (c.dt == LR_BF16) {
+        da.tile = i == 0 ? gemm_bf16_tile(da) : das[0].tile;
+        rp = gemm_bf16_rowparts(da);
+      }
     }
-    if (parts) {
-      da.epi.rowpart = parts; da.epi.rowpart_ld = slabs1 * a.G; da.epi.rowpart_off = u.g0 * slabs1;
-    }
-    gemm(c, da);
   }
-  if (parts) {
-    LAUNCH(c, k_rowsum_parts(parts, slabs1 * a.G, slabs1 * a.G, cdot, a.T, c.st));
+  if (c.dry && rp.slabs) rp.slabs = (int)((a.r + 63) / 64 * 2);   // size query: the narrowest tile's partials
+  const int nparts = rp.slabs * a.G;
+  float* parts = nparts ? (float*)c.take((size_t)a.T * nparts * sizeof(float)) : nullptr;
+  for (int i = 0; i < nrun; i++) {
+    if (nparts) {
+      das[i].epi.rowpart = parts; das[i].epi.rowpart_ld = nparts; das[i].epi.rowpart_off = run[i].g0 * rp.slabs;
+    }
+    gemm(c, das[i]);
+  }
+  if (nparts) {
+    LAUNCH(c, k_rowsum_parts(parts, nparts, a.G, rp, cdot, a.T, c.st));
   } else if (normed) {
     LAUNCH(c, k_rowdot(dp, GR, a.zc, GR, cdot, a.T, GR, c.dt, c.st));
   }
@@ -474,12 +520,13 @@ void single_up(Ctx& c, const Blk& b, const void* act, const void* w_up, int64_t 
   up.epi.kind = EPI_UP; up.epi.R = resid; up.epi.ldr = N;
   if (resid32) { up.epi.kind = EPI_UP_I32; up.epi.R = resid32; }
   else if (out32) { up.epi.kind = EPI_UP_O32; up.epi.C32 = out32; up.epi.ldc32 = N; }
-  if (sumsq) {
-    const int slabs = gemm_bf16_rowpart_slabs((int)N);
-    float* parts = (float*)c.take((size_t)b.T * slabs * sizeof(float));
-    up.epi.rowpart = parts; up.epi.rowpart_ld = slabs;
+  if (sumsq || c.dry) {
+    RowParts rp = gemm_bf16_rowparts(up);
+    if (c.dry) rp.slabs = (int)((N + 63) / 64 * 2);   // size query: the narrowest tile's partials
+    float* parts = (float*)c.take((size_t)b.T * rp.slabs * sizeof(float));
+    up.epi.rowpart = parts; up.epi.rowpart_ld = rp.slabs;
     gemm(c, up);
-    LAUNCH(c, k_rowsum_parts(parts, slabs, slabs, sumsq, b.T, c.st));
+    LAUNCH(c, k_rowsum_parts(parts, rp.slabs, 1, rp, sumsq, b.T, c.st));
   } else {
     gemm(c, up);
   }

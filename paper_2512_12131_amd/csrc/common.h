@@ -81,19 +81,35 @@ struct GemmOp {
   // k-major bf16 form only: the rows m0.. of a row tile use k < m0 + (tile height) only, i.e. A is
   // known to be zero where k > m (the causal structure of an attention gradient)
   int causal_k = 0;
+  int tile = 0;                // GemmTile: GEMM_TILE_AUTO lets gemm_bf16 choose
   Epilogue epi;
 };
+// Output tiles of the bf16 kernels (gemm_bf16.hip: 256 rows, 256 or, two k-major operands only, 128 columns;
+// gemm_ring.h: the others)
+enum GemmTile : int { GEMM_TILE_AUTO = 0, GEMM_T256 = 1, GEMM_T256X128 = 2, GEMM_R64 = 3, GEMM_R64X128 = 4, GEMM_R128 = 5 };
 
-// Number of n-slabs the bf16 kernel emits row partials for (rowpart_ld must be >= this * batch).
-int gemm_bf16_rowpart_slabs(int N);
-// Chooses a split-K factor for a weight-gradient GEMM with K = T.
-int gemm_bf16_pick_splitk(int M, int N, int K, int batch);
+// The tile gemm_bf16 runs `op` with (op.tile if set, else by estimated time; see gemm_bf16.hip).
+int gemm_bf16_tile(const GemmOp& op);
+// Row partials the bf16 kernel emits with `op`, per batch member: `slabs` columns (rowpart_ld must be >= slabs *
+// batch), each the sum over 128 / per128 output columns; n128 = 128-column groups that hold any.
+struct RowParts { int slabs, per128, n128; };
+RowParts gemm_bf16_rowparts(const GemmOp& op);
+// Tile and split-K factor for a weight gradient (both operands k-major, K = T).  direct: the output needs no
+// finishing pass when it is not split.
+struct WgradPlan { int tile, splitk; };
+WgradPlan gemm_bf16_plan_wgrad(int M, int N, int K, int batch, bool direct);
+hipError_t gemm_ring64(const GemmOp& op, hipStream_t st);
+hipError_t gemm_ring64x128(const GemmOp& op, hipStream_t st);
+hipError_t gemm_ring128(const GemmOp& op, hipStream_t st);
+// true when gemm_bf16 reads a k-major B operand beside a k-contiguous A in place (no transposed copy)
+bool gemm_bf16_mixed_ok(const GemmOp& op);
 hipError_t gemm_bf16(const GemmOp& op, hipStream_t st);
 // the same launch, never counted by the benchmark timer below (launches that are not projection GEMMs)
 hipError_t gemm_bf16_untimed(const GemmOp& op, hipStream_t st);
 // true when gemm_bf16 can run `op` with both operands k-major (no transposed copies needed)
 bool gemm_bf16_kmajor_ok(const GemmOp& op);
 hipError_t gemm_f32(const GemmOp& op, hipStream_t st);
+int gemm_f32_pick_splitk(int M, int N, int K, int batch);   // weight gradients in fp32: K = T
 // Benchmark aid: launches bracketed by HIP events on their stream (every gemm_bf16 launch, tagged with
 // its epilogue kind, and whatever the sequencing code opens and closes itself, tags >= LR_TAG_ATTN_FWD).
 int launch_timer_begin(int max_launches);
@@ -127,8 +143,8 @@ hipError_t k_swiglu_bwd(const void* g, const void* u, const void* dm, void* dg, 
 // out[r, c] = in[c, r] for in[rows, cols] (ld_in) -> out[cols, rows] (ld_out)
 hipError_t k_transpose(const void* in, int64_t ld_in, void* out, int64_t ld_out, int64_t rows,
                        int64_t cols, int dt, hipStream_t);
-// out[m] = sum_p part[m, p], p < nparts
-hipError_t k_rowsum_parts(const float* part, int64_t ld, int nparts, float* out, int64_t M, hipStream_t);
+// out[m] = sum of the row partials of `members` batch members (each rp.slabs columns of part[m, :])
+hipError_t k_rowsum_parts(const float* part, int64_t ld, int members, const RowParts& rp, float* out, int64_t M, hipStream_t);
 // out[m] = sum_n a[m,n] * b[m,n]
 hipError_t k_rowdot(const void* a, int64_t lda, const void* b, int64_t ldb, float* out, int64_t M,
                     int64_t N, int dt, hipStream_t);

@@ -18,18 +18,15 @@
 // auxiliary tiles it reads, the secondary output) is a row-contiguous 16-byte vector through a per-tile
 // buffer resource, without branches.  Workgroups map to tiles XCD by XCD in compact panels and all walk k front to back, so that
 // the tiles resident in one XCD share operand slices in its L2.
-#include <type_traits>
 #include <vector>
 
-#include "epilogue.h"
+#include "gemm_tile.h"
 
 namespace lrb {
 namespace {
 
-constexpr int BK = 64;          // k elements per LDS stage: 128-byte rows, i.e. whole cache lines per request
 constexpr int NSA = 3;          // LDS slots of the A operand's slices: loads get two slices of lead
 constexpr int NSB = 2;          // LDS slots of the B operand's slices: loads get one slice of lead
-constexpr int NXCD = 8;
 
 template <int BM_, int BN_, int WM_, int WN_>
 struct Tile {
@@ -53,72 +50,6 @@ struct Tile {
   static_assert(BM / 8 % NW == 0 && BN / 8 % NW == 0 && FM >= 1 && FN >= 1 && BM <= NT,
                 "tile / wavefront layout mismatch");
 };
-
-// Compile-time loop: the body receives std::integral_constant indices, so register arrays indexed
-// by them never turn into scratch memory, whatever the unroller decides.
-template <int N, class F, int I = 0>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<N, F, I + 1>(static_cast<F&&>(f));
-  }
-}
-
-__device__ __forceinline__ float sumsq8(const uint4& q) {
-  float v[8];
-  unpack8(q, v);
-  float s = 0.f;
-#pragma unroll
-  for (int i = 0; i < 8; i++) s = fmaf(v[i], v[i], s);
-  return s;
-}
-
-// s_waitcnt vmcnt(N) with the other counters left alone (gfx9 encoding: vmcnt in bits 3:0 and 15:14).
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0f70);
-}
-__device__ __forceinline__ void wait_lgkmcnt0() { __builtin_amdgcn_s_waitcnt(0xc07f); }
-
-// Sum over aligned groups of N = 8 or 16 consecutive lanes, every lane receiving the total, with
-// data-parallel-primitive moves (register file only): neighbours inside a quad, then the mirror image
-// inside 8 lanes, then inside 16.  (A butterfly of __shfl_xor goes through the LDS crossbar: four
-// dependent round trips per row partial.)
-template <int N>
-__device__ __forceinline__ float lane_group_sum(float x) {
-  static_assert(N == 8 || N == 16, "lane group size");
-  auto dpp = [](float v, auto CTRL) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(CTRL)::value, 0xf, 0xf, false));
-  };
-  x += dpp(x, std::integral_constant<int, 0xB1>{});    // quad_perm [1,0,3,2]
-  x += dpp(x, std::integral_constant<int, 0x4E>{});    // quad_perm [2,3,0,1]
-  x += dpp(x, std::integral_constant<int, 0x141>{});   // row_half_mirror: lane i <-> 7 - i
-  if constexpr (N == 16) x += dpp(x, std::integral_constant<int, 0x140>{});   // row_mirror: lane i <-> 15 - i
-  return x;
-}
-
-// Maps the linear workgroup id to an output tile so that (a) the workgroups that the hardware
-// deals round-robin to one XCD form a contiguous range of tiles, and (b) consecutive tiles of that
-// range form compact panels (PM tiles tall), keeping the A rows and B rows they share in that
-// XCD's L2.
-// The range runs over the whole launch, (batch member, k split) slowest: an XCD then works on tiles of
-// one batch member and one k range at a time, which is what lets its workgroups share operand slices.
-__device__ __forceinline__ void tile_of_block(int bid, int total, int tiles_m, int tiles_n, int& tm, int& tn, int& bz) {
-  const int xcd = bid % NXCD, loc = bid / NXCD;
-  const int base = total / NXCD, rem = total % NXCD;
-  const int nid = xcd * base + (xcd < rem ? xcd : rem) + loc;
-  const int tiles = tiles_m * tiles_n;
-  bz = nid / tiles;
-  const int tid_ = nid % tiles;
-  constexpr int PM = 8;
-  const int per_panel = PM * tiles_n;
-  const int panel = tid_ / per_panel, within = tid_ % per_panel;
-  const int pm_eff = min(PM, tiles_m - panel * PM);
-  tn = within / pm_eff;
-  tm = panel * PM + within % pm_eff;
-}
-
-#define LRB_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
 
 // KM = false: operands k-contiguous, A[m][k], B[n][k].
 // KM = true:  operands k-major,      A[k][m], B[k][n]  (weight gradients: k runs over tokens).  The
@@ -316,13 +247,15 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, i
       for (int j = 0; j < T::FN; j++)
         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[buf][j], af[buf][i], acc[i][j], 0, 0, 0);
   };
-  float ssq = 0.f;   // STAT_A: thread t accumulates the sum of squares of tile row t from the LDS copy
+  // STAT_A: thread t accumulates the sum of squares of tile row t from the LDS copy, one sum per 32 bytes of the
+  // 128-byte slice rows (the ring kernels share a row among threads at that grain: same order, same bits)
+  float ssq[4] = {0.f, 0.f, 0.f, 0.f};
   auto stat_row = [&](int kt, int half) {
     if constexpr (STAT_A) {
       if (tid < T::BM) {
         const unsigned char* sr = a_slot(kt) + tid * 128 + half * 64;
 #pragma unroll
-        for (int c = 0; c < 4; c++) ssq += sumsq8(*reinterpret_cast<const uint4*>(sr + c * 16));
+        for (int c = 0; c < 4; c++) ssq[half * 2 + c / 2] += sumsq8(*reinterpret_cast<const uint4*>(sr + c * 16));
       }
     }
   };
@@ -409,191 +342,10 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, i
   // ---- per-row sum of squares gathered from the A slices ---------------------------------------
   __syncthreads();  // main-loop LDS is dead from here on
   if constexpr (STAT_A) {
-    if (tid < T::BM) sStat[tid] = ssq;
+    if (tid < T::BM) sStat[tid] = (ssq[0] + ssq[1]) + (ssq[2] + ssq[3]);
     __syncthreads();
   }
-
-  // ---- epilogue: accumulators -> LDS (per-wave region) -> row-contiguous 8-wide vectors ---------
-  // The wavefront's sub-tile leaves in FM x (32/RPP) passes of RPP rows.  Everything the passes touch
-  // in global memory goes through buffer resources that start at the tile's first row and end after
-  // its last valid row: rows past M (and, by an out-of-range offset, columns past N) read as zeros and
-  // are dropped on store, an absent auxiliary tile is a resource of size zero.  The pass code is
-  // therefore free of branches, which is what lets the compiler count the loads in flight exactly: the
-  // auxiliary tiles an epilogue reads (residual, z, x, g, u) are fetched PF passes ahead into a small
-  // register ring, and each pass waits only for its own.
-  const Epilogue& e = op.epi;
-  float* sC = reinterpret_cast<float*>(smem) + wave * (32 * T::CS);
-  constexpr int LPR = T::TN / 8;            // lanes per output row
-  constexpr int RPP = 64 / LPR;             // rows per pass
-  constexpr int PPB = 32 / RPP;             // passes per 32-row block
-  constexpr int NQ = T::FM * PPB;           // passes per wavefront
-  // which auxiliary tiles a kind can read at all, and the prefetch distance in passes: kinds with one
-  // auxiliary tile keep eight of its 16-byte vectors in flight per lane, kinds with two keep four of each
-  // BASE: the formula; R_F32: the R tile is fp32 (two 16-byte vectors per lane and pass); O32: the primary
-  // output is also written un-rounded, as fp32, into C32
-  constexpr int BASE = epi_base(KIND);
-  constexpr bool R_F32 = epi_r_is_f32(KIND), O32 = epi_writes_f32(KIND);
-  constexpr bool HAS_R = BASE == EPI_UP || BASE == EPI_ACTGRAD || BASE == EPI_NORMBWD || BASE == EPI_SWIGLU_BWD ||
-                         BASE == EPI_SWIGLU_FWD || BASE == EPI_DOWN_LAX || BASE == EPI_LAXGRAD;
-  constexpr bool HAS_R2 = BASE == EPI_NORMBWD || BASE == EPI_SWIGLU_BWD || BASE == EPI_LAXGRAD;
-  constexpr int PF = (HAS_R2 || R_F32) ? 4 : 8;
-  constexpr uint32_t EOOB = 0x80000000u;
-  const int cg = lane % LPR, rsub = lane / LPR;
-  const int rows_valid = min(T::BM, op.M - m0);
-  const int coln = n0 + wn * T::TN + cg * 8;                         // first of this lane's 8 columns
-  const bool col_ok = coln < op.N;
-  auto tile_rsrc = [&](const void* base, int64_t batch_off, int64_t ld, int esz) {
-    const char* p = base ? (const char*)base + (batch_off + (int64_t)m0 * ld) * esz : nullptr;
-    return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, base ? (uint32_t)rows_valid * (uint32_t)ld * (uint32_t)esz : 0u,
-                                             0x00020000);
-  };
-  auto row_rsrc = [&](const float* base) {   // per-row fp32 scalars of the tile's rows
-    return __builtin_amdgcn_make_buffer_rsrc((void*)(base ? base + m0 : nullptr), 0, base ? (uint32_t)rows_valid * 4u : 0u,
-                                             0x00020000);
-  };
-  constexpr bool PARTIAL = KIND == EPI_PARTIAL;
-  // C: bf16 [batch][M][ldc]; fp32 split-K partials: [batch * split][M][N]
-  const __amdgpu_buffer_rsrc_t rsC = PARTIAL
-      ? __builtin_amdgcn_make_buffer_rsrc((void*)((char*)op.C + ((int64_t)bz * op.M + m0) * op.N * 4), 0,
-                                          (uint32_t)rows_valid * (uint32_t)op.N * 4u, 0x00020000)
-      : tile_rsrc(op.C, (int64_t)bi * op.sC + (int64_t)bo * op.sCo, op.ldc, 2);
-  const __amdgpu_buffer_rsrc_t rsC2 = tile_rsrc(PARTIAL ? nullptr : e.C2, (int64_t)b * e.sC2, e.ldc2, 2);
-  const bool use_r = !PARTIAL && epi_reads_r<BASE>(e), use_r2 = !PARTIAL && epi_reads_r2<BASE>(e);
-  const __amdgpu_buffer_rsrc_t rsR = tile_rsrc(use_r ? e.R : nullptr, (int64_t)b * e.sR, e.ldr, R_F32 ? 4 : 2);
-  const __amdgpu_buffer_rsrc_t rsC32 = tile_rsrc(O32 ? e.C32 : nullptr, 0, e.ldc32, 4);
-  const __amdgpu_buffer_rsrc_t rsR2 = tile_rsrc(use_r2 ? e.R2 : nullptr, (int64_t)b * e.sR2, e.ldr2, 2);
-  const __amdgpu_buffer_rsrc_t rsRowA = row_rsrc((!PARTIAL && e.use_rho && !STAT_A) ? e.rowa : nullptr);
-  const __amdgpu_buffer_rsrc_t rsRowB = row_rsrc(!PARTIAL ? e.rowb : nullptr);
-  const int ldC = PARTIAL ? op.N * 4 : (int)op.ldc * 2;               // row pitches in bytes
-  const int ldC2 = (int)e.ldc2 * 2, ldR = (int)e.ldr * (R_F32 ? 4 : 2), ldR2 = (int)e.ldr2 * 2, ldC32 = (int)e.ldc32 * 4;
-  const uint32_t colC = col_ok ? (uint32_t)coln * (PARTIAL ? 4u : 2u) : EOOB, col2 = col_ok ? (uint32_t)coln * 2u : EOOB;
-  const uint32_t col4 = col_ok ? (uint32_t)coln * 4u : EOOB;      // this lane's columns in an fp32 tile
-  const bool want2 = KIND == EPI_SWIGLU_BWD || KIND == EPI_SWIGLU_FWD || KIND == EPI_DOWN_LAX || KIND == EPI_LAXGRAD ||
-                     (KIND == EPI_DOWN && e.C2 != nullptr);
-  const bool use_rho = !PARTIAL && e.use_rho;
-  const bool rho_sqrt = e.rho_sqrt != 0;
-  // row partials [M, rowpart_ld] and the statistic [M]: one lane per row writes, the others (and rows
-  // past M) are given an out-of-range offset
-  constexpr bool ROWPART = BASE == EPI_UP || BASE == EPI_ACTGRAD || BASE == EPI_LAXGRAD;
-  const __amdgpu_buffer_rsrc_t rsPart = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)((ROWPART && e.rowpart) ? e.rowpart + (int64_t)m0 * e.rowpart_ld : nullptr), 0,
-      (ROWPART && e.rowpart) ? (uint32_t)rows_valid * (uint32_t)e.rowpart_ld * 4u : 0u, 0x00020000);
-  const int ldPart = ROWPART ? (int)e.rowpart_ld * 4 : 0;
-  const uint32_t colPart = cg == 0 ? (uint32_t)(e.rowpart_off + b * (tiles_n * T::WN) + tn * T::WN + wn) * 4u : EOOB;
-  const bool write_stat = STAT_A && e.stat_out && tn == 0 && wn == 0 && b == 0;
-  const __amdgpu_buffer_rsrc_t rsStat = row_rsrc(write_stat ? e.stat_out : nullptr);
-  const uint32_t colStat = cg == 0 ? 0u : EOOB;
-  const int act = e.act;
-  const float inv_d = e.inv_d, eps = e.eps;
-  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-  u32x4 auxr[PF], auxr2[PF], auxr3[R_F32 ? PF : 1];   // auxr3: columns 4..7 of an fp32 R tile
-  auto row_of = [&](int q) { return wm * T::TM + (q / PPB) * 32 + (q % PPB) * RPP + rsub; };   // row inside the tile
-  auto fetch = [&](int q, u32x4& ar, u32x4& ar2, u32x4& ar3) {
-    const int lm = row_of(q);
-    if constexpr (R_F32) {
-      ar = __builtin_amdgcn_raw_buffer_load_b128(rsR, (int)((uint32_t)(lm * ldR) + col4), 0, 0);
-      ar3 = __builtin_amdgcn_raw_buffer_load_b128(rsR, (int)((uint32_t)(lm * ldR) + col4 + 16u), 0, 0);
-    } else if constexpr (HAS_R) {
-      ar = __builtin_amdgcn_raw_buffer_load_b128(rsR, (int)((uint32_t)(lm * ldR) + col2), 0, 0);
-    }
-    if constexpr (HAS_R2) ar2 = __builtin_amdgcn_raw_buffer_load_b128(rsR2, (int)((uint32_t)(lm * ldR2) + col2), 0, 0);
-  };
-  static_for<PF>([&](auto Q) {
-    constexpr int q = decltype(Q)::value;
-    auxr[q] = u32x4{0u, 0u, 0u, 0u};
-    auxr2[q] = u32x4{0u, 0u, 0u, 0u};
-    if constexpr (R_F32) auxr3[q] = u32x4{0u, 0u, 0u, 0u};
-    if constexpr (q < NQ) fetch(q, auxr[q], auxr2[q], auxr3[R_F32 ? q : 0]);
-  });
-  // per-row scalars of all passes, requested before the first pass
-  float ssv[NQ], rbv[NQ];
-  static_for<NQ>([&](auto Q) {
-    constexpr int q = decltype(Q)::value;
-    ssv[q] = 0.f;
-    rbv[q] = 0.f;
-    if constexpr (!PARTIAL && !STAT_A) {
-      if (use_rho) ssv[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsRowA, row_of(q) * 4, 0, 0));
-    }
-    if constexpr (BASE == EPI_NORMBWD)
-      rbv[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsRowB, row_of(q) * 4, 0, 0));
-  });
-  static_for<NQ>([&](auto Q) {
-    constexpr int q = decltype(Q)::value;
-    constexpr int i = q / PPB, p = q % PPB;
-    if constexpr (p == 0) {
-      static_for<T::FN>([&](auto J) {
-        constexpr int j = decltype(J)::value;
-        // the accumulators hold the transposed 32x32 block (the MFMA is issued with its operands
-        // exchanged): lane -> row lane%32, registers 4g..4g+3 -> columns 8g + 4*(lane/32) + 0..3, so a lane
-        // stages four consecutive columns with one 16-byte write
-#pragma unroll
-        for (int g = 0; g < 4; g++)
-          *reinterpret_cast<float4*>(sC + (lane & 31) * T::CS + j * 32 + 8 * g + 4 * (lane >> 5)) =
-              make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
-      });
-      // No barrier: the staging region belongs to this wavefront alone and a wavefront's LDS
-      // operations complete in order.
-    }
-    const int rl = p * RPP + rsub;
-    const int lm = wm * T::TM + i * 32 + rl;      // row inside the block tile
-    float v[8];
-    {
-      const float4 lo = *reinterpret_cast<const float4*>(sC + rl * T::CS + cg * 8);
-      const float4 hi = *reinterpret_cast<const float4*>(sC + rl * T::CS + cg * 8 + 4);
-      v[0] = lo.x; v[1] = lo.y; v[2] = lo.z; v[3] = lo.w;
-      v[4] = hi.x; v[5] = hi.y; v[6] = hi.z; v[7] = hi.w;
-    }
-    if constexpr (PARTIAL) {
-      const uint32_t off = (uint32_t)(lm * ldC) + colC;
-      const u32x4 lo = {__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])};
-      const u32x4 hi = {__float_as_uint(v[4]), __float_as_uint(v[5]), __float_as_uint(v[6]), __float_as_uint(v[7])};
-      __builtin_amdgcn_raw_buffer_store_b128(lo, rsC, (int)off, 0, 0);
-      __builtin_amdgcn_raw_buffer_store_b128(hi, rsC, (int)(off + 16u), 0, 0);
-    } else {
-      float rho = 1.f, rowb = 0.f;
-      if (use_rho) {
-        float ss;
-        if constexpr (STAT_A) ss = sStat[lm];
-        else ss = ssv[q];
-        rho = rho_sqrt ? sqrtf(ss * inv_d + eps) : rsqrtf(ss * inv_d + eps);
-      }
-      if constexpr (BASE == EPI_NORMBWD) rowb = rbv[q];
-      float r[8], r2[8], v2[8];
-      if constexpr (R_F32) {
-        const u32x4 a0 = auxr[q % PF], a1 = auxr3[q % PF];
-        r[0] = __uint_as_float(a0.x); r[1] = __uint_as_float(a0.y); r[2] = __uint_as_float(a0.z); r[3] = __uint_as_float(a0.w);
-        r[4] = __uint_as_float(a1.x); r[5] = __uint_as_float(a1.y); r[6] = __uint_as_float(a1.z); r[7] = __uint_as_float(a1.w);
-      } else {
-        unpack8(make_uint4(auxr[q % PF].x, auxr[q % PF].y, auxr[q % PF].z, auxr[q % PF].w), r);
-      }
-      unpack8(make_uint4(auxr2[q % PF].x, auxr2[q % PF].y, auxr2[q % PF].z, auxr2[q % PF].w), r2);
-      float part = epi_math<8, BASE, true>(act, inv_d, want2, v, v2, rho, rowb, r, r2);
-      if constexpr (O32) {
-        const u32x4 lo = {__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])};
-        const u32x4 hi = {__float_as_uint(v[4]), __float_as_uint(v[5]), __float_as_uint(v[6]), __float_as_uint(v[7])};
-        const uint32_t off = (uint32_t)(lm * ldC32) + col4;
-        __builtin_amdgcn_raw_buffer_store_b128(lo, rsC32, (int)off, 0, 0);
-        __builtin_amdgcn_raw_buffer_store_b128(hi, rsC32, (int)(off + 16u), 0, 0);
-      }
-      {
-        const uint4 o = pack8(v);
-        const u32x4 ov = {o.x, o.y, o.z, o.w};
-        __builtin_amdgcn_raw_buffer_store_b128(ov, rsC, (int)((uint32_t)(lm * ldC) + colC), 0, 0);
-      }
-      if (want2) {
-        const uint4 o = pack8(v2);
-        const u32x4 ov = {o.x, o.y, o.z, o.w};
-        __builtin_amdgcn_raw_buffer_store_b128(ov, rsC2, (int)((uint32_t)(lm * ldC2) + col2), 0, 0);
-      }
-      if constexpr (q + PF < NQ) fetch(q + PF, auxr[q % PF], auxr2[q % PF], auxr3[R_F32 ? q % PF : 0]);
-      if constexpr (ROWPART) {
-        part = lane_group_sum<LPR>(part);
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(part), rsPart, (int)((uint32_t)(lm * ldPart) + colPart), 0, 0);
-      }
-      if constexpr (STAT_A)
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(sStat[lm]), rsStat, (int)((uint32_t)(lm * 4) + colStat), 0, 0);
-    }
-  });
+  gemm_epilogue<T, KIND, STAT_A>(op, acc, smem, sStat, wave, lane, m0, n0, tn, tiles_n, b, bi, bo, bz);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -614,7 +366,7 @@ hipError_t launch(const GemmOp& op, hipStream_t st) {
 }
 
 using TileBig = Tile<256, 256, 4, 2>;   // 8 waves, 64x128 per wave
-using TileMid = Tile<256, 128, 2, 2>;   // 4 waves, 128x64 per wave (narrow N, weight gradients)
+using TileMid = Tile<256, 128, 2, 2>;   // 4 waves, 128x64 per wave (two k-major operands, N = 128)
 
 template <class T>
 hipError_t dispatch(const GemmOp& op, hipStream_t st) {
@@ -640,34 +392,115 @@ hipError_t dispatch(const GemmOp& op, hipStream_t st) {
   }
 }
 
-// (A 128x128 tile of four wavefronts needs 80 KB of LDS, so two workgroups share a CU and one's epilogue
-// could run under the other's main loop.  Measured on the 7B block it loses everywhere, 6-30 % per launch
-// class, the classes with tile-reading epilogues included: it moves twice the operand bytes per FLOP
-// through L2 and LDS, and that costs more than the overlap returns.)
-bool use_big_tile(int N) { return N > 128 && (N % 256 == 0 || N > 512); }
+// ---- which tile runs a launch --------------------------------------------------------------------
+// Estimated microseconds of a launch.  A tile kind runs `slots` workgroups at a time; a round of them takes a
+// fixed time f (pipeline fill), the epilogue g * e + h * e and nk 64-wide k slices of s0 + s1 each, where s1 and g
+// are what the slices and the epilogue lose to each other when every slot is busy (they scale with the share
+// of slots in use) and e is the traffic of the epilogue in units of one bf16 output.  The coefficients are fits to
+// 1770 measured launches (M 64 .. 16384, N 64 .. 11008, K 64 .. 11008, nine epilogue kinds, k-contiguous operands),
+// which they reproduce to 7-11 % rms; always taking the estimated best loses 1 % (geometric mean) against the
+// measured best, where the 256-row tiles alone took 1.93 times as long.  What the lines amount to, with both sides measured (us):
+//   few tiles, the loads' latency decides          777 x 1024 x 4096:   T256 68.0   R64    16.1
+//   half the CUs idle under T256                 16384 x 512 x 2048:   T256 45.6   R128   37.6
+//   N = 128 leaves T256 half its columns         16384 x 128 x 4096:   T256 72.1   R64x128 29.9
+//   short k, the epilogue decides: two resident workgroups overlap it with each other's main loop
+//                                                16384 x 4096 x 256:   T256 70.8   R128   54.6
+//   the chip full and k long                     16384 x 4096 x 2048:  T256 225.8  R128   274.4
+struct TileCost {
+  int bm, bn, slots;
+  float a, f, s0, s1, g, h;
+};
+constexpr TileCost kTileCost[] = {
+    {0, 0, 0, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f},
+    {256, 256, 256, 0.82f, 3.82f, 0.876f, 0.591f, 4.68f, 0.703f},   // GEMM_T256
+    {256, 128, 256, 3.02f, 2.24f, 0.689f, 0.231f, 1.98f, 0.f},      // GEMM_T256X128
+    {64, 64, 256, 1.89f, 1.80f, 0.169f, 0.029f, 0.22f, 0.141f},     // GEMM_R64
+    {64, 128, 512, 2.08f, 1.38f, 0.231f, 0.306f, 1.05f, 0.095f},    // GEMM_R64X128
+    {128, 128, 512, 2.48f, 0.80f, 0.479f, 0.451f, 2.42f, 0.142f},   // GEMM_R128
+};
+// bf16-output equivalents an epilogue moves (reads and writes, secondary outputs included)
+float epi_traffic(int kind) {
+  switch (kind) {
+    case EPI_STORE: return 1.f;
+    case EPI_DOWN: case EPI_UP: case EPI_ACTGRAD: case EPI_PARTIAL: return 2.f;
+    case EPI_UP_I32: case EPI_NORMBWD: case EPI_SWIGLU_FWD: case EPI_DOWN_LAX: return 3.f;
+    case EPI_UP_O32: case EPI_NORMBWD_I32: case EPI_SWIGLU_BWD: case EPI_LAXGRAD: return 4.f;
+    default: return 5.f;   // EPI_NORMBWD_O32
+  }
+}
+// nk: k slices of one workgroup; members: batch members times k splits; slice: factor on the slice time
+float tile_time(int tile, int M, int N, int nk, int members, float e, float slice = 1.f) {
+  const TileCost& c = kTileCost[tile];
+  const long wgs = (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn) * members;
+  const long full = wgs / c.slots;
+  const float u = (float)(wgs % c.slots) / (float)c.slots;
+  float t = c.a + (float)full * (c.f + (c.g + c.h) * e + (float)nk * slice * (c.s0 + c.s1));
+  if (u > 0.f) t += c.f + (c.g * u + c.h) * e + (float)nk * slice * (c.s0 + c.s1 * u);
+  return t;
+}
+// The smaller tiles have to be estimated 7.5 % faster than T256 before they are taken: the estimate's own error.
+constexpr float kRingMargin = 1.075f;
+// What a slice costs more with two k-major operands.  The 256-row kernels pay for their transpose reads.  The ring
+// tiles read 128 or 256 bytes per k row where those read 512, which shows when the rows come from HBM (2048 x 512
+// over 16384 tokens: R64x128 in 4 splits 60 us, T256 in 16 splits 45 us plus 6 us more in the finishing pass).
+constexpr float kKMajorSlice[] = {0.f, 1.13f, 1.05f, 1.5f, 1.5f, 1.3f};
 
 }  // namespace
 
-int gemm_bf16_rowpart_slabs(int N) {
-  if (use_big_tile(N)) return (N + TileBig::BN - 1) / TileBig::BN * TileBig::WN;
-  return (N + TileMid::BN - 1) / TileMid::BN * TileMid::WN;
+bool gemm_bf16_mixed_ok(const GemmOp& op) {
+  return !op.transA && op.transB && op.splitk == 1 && gemm_bf16_tile(op) >= GEMM_R64;
 }
 
-int gemm_bf16_pick_splitk(int M, int N, int K, int batch) {
-  // One workgroup per CU is resident at a time (LDS), so a launch runs in ceil(workgroups / 256)
-  // rounds, each as long as one workgroup: its k-slices plus a fixed cost (pipeline fill, the fp32
-  // partial tile it writes, its share of the fold) worth about 8 slices.  Pick the split count with
-  // the smallest estimate; ties go to fewer splits (less partial traffic).
-  const int bm = 256, bn = use_big_tile(N) ? 256 : 128;
-  const long tiles = (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * batch;
+int gemm_bf16_tile(const GemmOp& op) {
+  if (op.tile != GEMM_TILE_AUTO) return op.tile;
+  if (op.splitk > 1 || op.epi.kind == EPI_PARTIAL) return GEMM_T256;   // weight gradients come with a plan
+  // a k-major weight is read in place in whole 8-column chunks, within the 2 GB a buffer resource addresses
+  if (op.transB && !op.transA && (op.N % 8 || op.K % 8 || (int64_t)op.K * op.ldb * 2 >= 0x7fffffffLL)) return GEMM_T256;
+  const int nk = (op.K + BK - 1) / BK;
+  const float e = epi_traffic(op.epi.kind);
+  const bool km = op.transA && op.transB;
+  float best = tile_time(GEMM_T256, op.M, op.N, nk, op.batch, e, km ? kKMajorSlice[GEMM_T256] : 1.f);
+  // T256 with a k-major weight first writes a transposed copy: one launch per batch member
+  if (op.transB && !op.transA) best += (float)op.batch * (2.5f + (float)op.N * (float)op.K * (4.f / 4e6f));
+  int tile = GEMM_T256;
+  if (km) {
+    const float c = tile_time(GEMM_T256X128, op.M, op.N, nk, op.batch, e, kKMajorSlice[GEMM_T256X128]);
+    if (c < best) {
+      best = c;
+      tile = GEMM_T256X128;
+    }
+  }
+  for (int t = GEMM_R64; t <= GEMM_R128; t++) {
+    const float c = tile_time(t, op.M, op.N, nk, op.batch, e, km ? kKMajorSlice[t] : 1.f);
+    if (c * (tile < GEMM_R64 ? kRingMargin : 1.f) < best) {
+      best = c;
+      tile = t;
+    }
+  }
+  return tile;
+}
+
+RowParts gemm_bf16_rowparts(const GemmOp& op) {
+  const int tile = gemm_bf16_tile(op), bn = kTileCost[tile].bn;   // every tile has two wavefronts across
+  return RowParts{(op.N + bn - 1) / bn * 2, 256 / bn, (op.N + 127) / 128};
+}
+
+WgradPlan gemm_bf16_plan_wgrad(int M, int N, int K, int batch, bool direct) {
+  // Every split adds its fp32 partial tile to what the workgroups write and the finishing pass reads (7 TB/s);
+  // without a split and with nothing else to fold in, the GEMM writes the gradient itself.
   const int nk = (K + BK - 1) / BK;
-  const int maxs = nk >= 16 ? (nk / 8 < 64 ? nk / 8 : 64) : 1;   // at least 8 slices per split
-  int best = 1;
-  long best_cost = -1;
-  for (int s = 1; s <= maxs; s++) {
-    const long rounds = (tiles * s + 255) / 256;
-    const long cost = rounds * ((nk + s - 1) / s + 8) * 16 + s;   // "+ s": the tie-break
-    if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = s; }
+  WgradPlan best{GEMM_T256, 1};
+  float best_t = -1.f;
+  for (int tile = GEMM_T256; tile <= GEMM_R128; tile++) {
+    for (int s : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 24, 32, 48, 64}) {
+      if (s > 1 && nk / s < (tile < GEMM_R64 ? 8 : 4)) break;
+      float t = tile_time(tile, M, N, (nk + s - 1) / s, batch * s, 2.f, kKMajorSlice[tile]);
+      if (s > 1 || !direct) t += (float)batch * (2.f + (float)(s + 1) * (float)M * (float)N * (4.f / 7e6f));
+      if (best_t < 0.f || t < best_t) {
+        best_t = t;
+        best = WgradPlan{tile, s};
+      }
+    }
   }
   return best;
 }
@@ -750,28 +583,31 @@ hipError_t gemm_bf16(const GemmOp& op, hipStream_t st) {
 }
 
 bool gemm_bf16_kmajor_ok(const GemmOp& op) {
-  // both operands k-major, fp32 partial output, offsets within the 2 GB a buffer resource addresses
-  const bool wgrad = op.batch == 1 && op.epi.kind == EPI_PARTIAL;
+  // both operands k-major, offsets within the 2 GB a buffer resource addresses.  M need not be a multiple of 8
+  // (rows of A then run on into the padding of its leading dimension); N, the vector width of the stores, does.
+  const bool wgrad = op.epi.kind == EPI_PARTIAL;
   const bool plain = op.splitk == 1 && op.epi.kind == EPI_STORE;
-  return op.transA && op.transB && (wgrad || plain) && op.M % 8 == 0 && op.N % 8 == 0 &&
+  return op.transA && op.transB && (wgrad || plain) && op.lda % 8 == 0 && op.N % 8 == 0 && op.lda >= (op.M + 7) / 8 * 8 &&
          (int64_t)op.K * op.lda * 2 < 0x7fffffffLL && (int64_t)op.K * op.ldb * 2 < 0x7fffffffLL;
 }
 
 hipError_t gemm_bf16_untimed(const GemmOp& op, hipStream_t st) {
   if (op.M <= 0 || op.N <= 0 || op.batch <= 0) return hipSuccess;
-  if (op.transA && op.transB) {
-    if (!gemm_bf16_kmajor_ok(op)) return hipErrorInvalidValue;
-    if (op.epi.kind == EPI_STORE && op.splitk == 1) {
-      if (use_big_tile(op.N)) return launch<TileBig, EPI_STORE, false, true>(op, st);
-      return launch<TileMid, EPI_STORE, false, true>(op, st);
-    }
-    if (use_big_tile(op.N)) return launch<TileBig, EPI_PARTIAL, false, true>(op, st);
-    return launch<TileMid, EPI_PARTIAL, false, true>(op, st);
-  }
-  if (op.transA || op.transB) return hipErrorInvalidValue;
+  const bool km = op.transA && op.transB;
+  if (km && !gemm_bf16_kmajor_ok(op)) return hipErrorInvalidValue;
+  if (op.transA != op.transB && !gemm_bf16_mixed_ok(op)) return hipErrorInvalidValue;
   if (op.epi.stat_from_a && op.splitk > 1) return hipErrorInvalidValue;
-  if (use_big_tile(op.N)) return dispatch<TileBig>(op, st);
-  return dispatch<TileMid>(op, st);
+  switch (gemm_bf16_tile(op)) {
+    case GEMM_R64: return gemm_ring64(op, st);
+    case GEMM_R64X128: return gemm_ring64x128(op, st);
+    case GEMM_R128: return gemm_ring128(op, st);
+    default: break;
+  }
+  if (!km) return dispatch<TileBig>(op, st);
+  const bool store = op.epi.kind == EPI_STORE && op.splitk == 1;
+  if (gemm_bf16_tile(op) == GEMM_T256X128)
+    return store ? launch<TileMid, EPI_STORE, false, true>(op, st) : launch<TileMid, EPI_PARTIAL, false, true>(op, st);
+  return store ? launch<TileBig, EPI_STORE, false, true>(op, st) : launch<TileBig, EPI_PARTIAL, false, true>(op, st);
 }
 
 }  // namespace lrb

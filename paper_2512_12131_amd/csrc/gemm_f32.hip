@@ -85,6 +85,13 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmOp op, int kper) {
 
 }  // namespace
 
+int gemm_f32_pick_splitk(int M, int N, int K, int batch) {
+  const long tiles = (long)((M + TBM - 1) / TBM) * ((N + TBN - 1) / TBN) * batch;
+  long s = 1;
+  while (s < 32 && tiles * s < 256 && K / (s * 2) >= 64) s *= 2;
+  return (int)s;
+}
+
 hipError_t gemm_f32(const GemmOp& op, hipStream_t st) {
   if (op.M <= 0 || op.N <= 0 || op.batch <= 0) return hipSuccess;
   dim3 grid((op.N + TBN - 1) / TBN, (op.M + TBM - 1) / TBM, op.batch * op.splitk);

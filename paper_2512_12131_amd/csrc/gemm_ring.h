@@ -1,0 +1,294 @@
+// bf16 MFMA GEMM for launches that the 256-row tiles of gemm_bf16.hip cannot spread over the chip:
+// C[M,N] = epi( sum_k A[m,k] * B[n,k] ), fp32 accumulate, every epilogue of that kernel.
+//
+// Bound: with few output tiles per CU the time of a launch is the time one workgroup takes to walk k, and
+// that is set by the latency of its global->LDS loads, not by the matrix pipes.  So the tiles are small (the
+// output spreads over more CUs) and the loads run far ahead: a ring of NS LDS stages, NS - 1 of them in
+// flight, one barrier per stage.  The small tiles read each operand element more often than the 256 x 256
+// tile does, which is why that one keeps the launches that fill the chip (gemm_bf16_route).
+//
+// Every output element is summed by the same MFMA instruction in the same k order, and from the same k slots,
+// as in the 256-row kernel's k-contiguous form: which of the two kernels runs a product does not change its
+// bits, so a token's result does not depend on how many tokens share the call.  The row statistics keep to that
+// too: k_rowsum_parts adds the narrower row partials of these tiles up in the order a 128-column wavefront does.
+//
+// Measured (us, this kernel's best tile against the 256-row kernel): 777 x 1024 x 11008 37 / 172, 1031 x 256 x 1024
+// 6.5 / 22, 16384 x 128 x 4096 30 / 72, 512 x 256 x 64 4.2 / 7.2.  A 64 x 64 tile takes 0.21 us per 64-wide slice: a
+// wavefront's 32 x 32 block reads 2 KB of LDS per MFMA, so the LDS port (128 B per cycle) is busy for twice the
+// matrix time, and the loads (one 1 KB load per ~17 cycles and CU) for as long again.  Reading all operands of a
+// stage before issuing the next loads took 12 % off that; 32 x 64 tiles and a ring of ten 16 KB stages were slower.
+//
+// Operand forms: k-contiguous (p[i*ld + k]) or k-major (p[k*ld + i]) for A and B independently; the k-major
+// side is read through the LDS transpose read, so a data-gradient product needs no transposed weight copy.
+#pragma once
+#include "gemm_tile.h"
+
+namespace lrb {
+namespace {
+
+template <int BM_, int BN_, int WM_, int WN_, int SUB_, int NS_>
+struct RingTile {
+  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_;
+  static constexpr int SUB = SUB_;                     // 64-wide k slices per LDS stage (one barrier per stage)
+  static constexpr int NS = NS_;                       // stages in the ring
+  static constexpr int NW = WM * WN, NT = NW * 64;
+  static constexpr int TM = BM / WM, TN = BN / WN;
+  static constexpr int FM = TM / 32, FN = TN / 32;
+  static constexpr int A_BYTES = BM * 128, B_BYTES = BN * 128, SLICE = A_BYTES + B_BYTES, STAGE = SUB * SLICE;
+  static constexpr int LA = BM / 8 / NW, LB = BN / 8 / NW;   // 1 KB wavefront loads per wavefront and slice
+  static constexpr int LPS = (LA + LB) * SUB;                // ... and stage
+  static constexpr int CS = TN + 4;                          // fp32 row stride of the epilogue staging tile
+  static constexpr int EPI_BYTES = NW * 32 * CS * 4;
+  static constexpr int STAT_OFF = EPI_BYTES;
+  static constexpr int MAIN_BYTES = NS * STAGE;
+  static constexpr int LDS_BYTES = MAIN_BYTES > EPI_BYTES + BM * 4 ? MAIN_BYTES : EPI_BYTES + BM * 4;
+  static_assert(BM / 8 % NW == 0 && BN / 8 % NW == 0 && FM >= 1 && FN >= 1, "tile / wavefront layout mismatch");
+  static_assert(NS >= 2 && (NS - 2) * LPS < 64, "vmcnt is a 6-bit counter");
+  static_assert(LDS_BYTES <= 160 * 1024, "LDS of a CU");
+  // main-loop statistics: NT / BM threads share a row, each takes a 16-byte chunk run of every slice
+  static constexpr int TPR = NT / BM;
+  static_assert(TPR == 2 || TPR == 4, "threads per tile row");
+};
+
+typedef uint32_t rsrc_words __attribute__((ext_vector_type(4)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+
+// One 1 KB global -> LDS load of a wavefront: lane L's 16 bytes land at lds + 16 L.  Inline assembly, because
+// through the builtin the compiler makes later LDS reads wait for every load in flight; completion is counted
+// by hand (wait_vmcnt before the barrier that publishes a stage).  No output register is written.
+__device__ __forceinline__ void dma16(rsrc_words rs, uint32_t lds, uint32_t voff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(rs) : "memory");
+}
+__device__ __forceinline__ rsrc_words operand_rsrc(const void* base) {
+  const uint64_t a = (uint64_t)(uintptr_t)base;
+  const rsrc_words r = {(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a),
+                        (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(a >> 32) & 0xffffu)), 0x7fffffffu, 0x00020000u};
+  return r;
+}
+
+// Swizzle of a k-major stage ([k][W columns], 2 W bytes per k row): the term XORed into the 16-byte chunk index
+// of row k.  A transpose read takes 64 bytes out of each of four consecutive rows per half wavefront; with this
+// term the four land on different 64-byte quarters of the 256 bytes of banks.  It repeats every four rows, so
+// the second read of an operand (k + 4) differs from the first by a constant offset.
+template <int W>
+__device__ __forceinline__ int kmajor_swz(int k) {
+  return W >= 128 ? (k & 3) << 2 : ((k >> 1) & 1) << 2;
+}
+
+template <class T, int KIND, bool STAT_A, bool AKM, bool BKM>
+__global__ __launch_bounds__(T::NT) void gemm_ring_kernel(GemmOp op, int kper, int tiles_m, int tiles_n) {
+  static_assert(!(STAT_A && AKM), "row statistics are gathered from k-contiguous rows");
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / T::WN, wn = wave % T::WN;
+  int tm, tn, bz;
+  tile_of_block(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y, tiles_m, tiles_n, tm, tn, bz);
+  const int m0 = tm * T::BM, n0 = tn * T::BN;
+  const int b = bz / op.splitk, ks = bz % op.splitk;
+  const int kbeg = ks * kper;
+  int kend = min(op.K, kbeg + kper);
+  if (AKM && BKM && op.causal_k) kend = min(kend, m0 + T::BM);
+  const int bo = op.batch_inner > 0 ? b / op.batch_inner : 0, bi = op.batch_inner > 0 ? b % op.batch_inner : b;
+  const int klen = kend > kbeg ? kend - kbeg : 0;
+  constexpr int KST = T::SUB * BK, KSTEPS = T::SUB * 4;  // k elements and k16 steps per stage
+  const int nit = (klen + KST - 1) / KST;
+
+  const uint16_t* A = (const uint16_t*)op.A + (int64_t)bi * op.sA + (int64_t)bo * op.sAo;
+  const uint16_t* B = (const uint16_t*)op.B + (int64_t)bi * op.sB + (int64_t)bo * op.sBo;
+  constexpr uint32_t OOB = 0x80000000u;                  // beyond every resource: the load delivers zeros
+  const rsrc_words rsA = operand_rsrc(AKM ? A + (int64_t)kbeg * op.lda + m0 : A + (int64_t)m0 * op.lda + kbeg);
+  const rsrc_words rsB = operand_rsrc(BKM ? B + (int64_t)kbeg * op.ldb + n0 : B + (int64_t)n0 * op.ldb + kbeg);
+  const uint32_t sbase = (uint32_t)(uintptr_t)LRB_LDS_PTR(smem);
+
+  // A wavefront's loads of one slice of an operand: group g = wave + NW * i covers 8 rows x 128 B
+  // (k-contiguous; chunk index XORed by (row / 2) % 8) or 512 / W k rows x 2 W bytes (k-major).
+  uint32_t offA[T::LA], offB[T::LB];
+  int kA = 0, kB = 0;        // this lane's first k inside the slice: of its chunk (k-contiguous) or its row (k-major)
+  auto lane_offsets = [&](auto KM, auto Wc, auto& off, int& k_of_lane, int64_t ld, int i0, int lim) {
+    constexpr bool km = decltype(KM)::value;
+    constexpr int W = decltype(Wc)::value, NL = W / 8 / T::NW;
+#pragma unroll
+    for (int i = 0; i < NL; i++) {
+      const int g = wave + T::NW * i;
+      if constexpr (!km) {
+        const int row = g * 8 + (lane >> 3);
+        const int lc = (lane & 7) ^ ((row >> 1) & 7);
+        if (i == 0) k_of_lane = lc * 8;                  // the same for every i: NW * 8 rows apart, NW even
+        off[i] = (i0 + row) < lim ? (uint32_t)(row * (int)ld + lc * 8) * 2u : OOB;
+      } else {
+        constexpr int CPR = W / 8, RPL = 64 / CPR;
+        const int krow = g * RPL + lane / CPR;
+        const int lc = (lane % CPR) ^ kmajor_swz<W>(krow);
+        if (i == 0) k_of_lane = krow;                    // load i: NW * RPL rows further
+        off[i] = (i0 + lc * 8) < lim ? (uint32_t)(krow * (int)ld + lc * 8) * 2u : OOB;
+      }
+    }
+  };
+  using WA = std::integral_constant<int, T::BM>;
+  using WB = std::integral_constant<int, T::BN>;
+  lane_offsets(std::integral_constant<bool, AKM>{}, WA{}, offA, kA, op.lda, m0, op.M);
+  lane_offsets(std::integral_constant<bool, BKM>{}, WB{}, offB, kB, op.ldb, n0, op.N);
+
+  // Load I (compile-time, 0 .. LPS - 1) of stage `it` into ring slot `slot`.  k past the end of the range (also
+  // whole stages past it) reads as zeros, so the loop needs no tail code and the counts of loads in flight are
+  // constants.
+  auto issue_one = [&](int it, int slot, auto I) {
+    constexpr int s = decltype(I)::value / (T::LA + T::LB), j = decltype(I)::value % (T::LA + T::LB);
+    constexpr bool is_a = j < T::LA, km = is_a ? AKM : BKM;
+    constexpr int i = is_a ? j : j - T::LA, W = is_a ? T::BM : T::BN, RPL = 512 / W;
+    const int k0 = it * KST + s * BK;
+    const uint32_t adv = (uint32_t)k0 * (km ? (uint32_t)(is_a ? op.lda : op.ldb) : 1u) * 2u;
+    const bool in = (k0 + (is_a ? kA : kB) + (km ? i * T::NW * RPL : 0)) < klen;
+    const uint32_t dst = sbase + (uint32_t)(slot * T::STAGE + s * T::SLICE + (is_a ? 0 : T::A_BYTES)) +
+                         (uint32_t)(wave + T::NW * i) * 1024u;
+    dma16(is_a ? rsA : rsB, dst, in ? (is_a ? offA[is_a ? i : 0] : offB[is_a ? 0 : i]) + adv : OOB);   // OOB + adv stays past the resource
+  };
+
+  // MFMA operands: 32 rows (lane % 32) x 8 consecutive k (k16 step kk, half lane / 32) from either layout
+  const int frow = lane & 31, fhalf = lane >> 5, fsw = (frow >> 1) & 7;
+  auto frag = [&](auto KM, auto Wc, const unsigned char* base, int r0, int kk) -> bf16x8 {
+    constexpr bool km = decltype(KM)::value;
+    constexpr int W = decltype(Wc)::value;
+    if constexpr (!km) {
+      return *reinterpret_cast<const bf16x8*>(base + (r0 + frow) * 128 + (((kk * 2 + fhalf) ^ fsw) << 4));
+    } else {
+      // inside 16 lanes, lane s supplies the address of 4 columns of k row s / 4 and receives column s
+      const int g = lane >> 4, s = lane & 15;
+      const int krow = fhalf * 8 + (s >> 2);
+      const int col = r0 + (g & 1) * 16 + (s & 3) * 4;
+      const unsigned char* p = base + (kk * 16 + krow) * (2 * W) + (((col >> 3) ^ kmajor_swz<W>(krow)) << 4) + (col & 7) * 2;
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p));
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p + 4 * 2 * W));
+      const s16x8 r = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+      return __builtin_bit_cast(bf16x8, r);
+    }
+  };
+
+  f32x16 acc[T::FM][T::FN];
+#pragma unroll
+  for (int i = 0; i < T::FM; i++)
+#pragma unroll
+    for (int j = 0; j < T::FN; j++)
+#pragma unroll
+      for (int v = 0; v < 16; v++) acc[i][j][v] = 0.f;
+  // STAT_A: sums of squares of tile row tid / TPR, one per 32 bytes of the slice rows, 4 / TPR of them per thread
+  float ssq[4 / T::TPR] = {};
+
+#pragma unroll
+  for (int s = 0; s < T::NS - 1; s++) static_for<T::LPS>([&](auto I) { issue_one(s, s, I); });
+  int rd = 0, wr = T::NS - 1;                            // slots read from and written to
+  for (int it = 0; it < nit; it++) {
+    // this wavefront's loads of stage `it` have landed (loads retire in order), and its reads of the stage
+    // before are done; after the barrier that holds for all of them
+    asm volatile("" ::: "memory");
+    wait_vmcnt<(T::NS - 2) * T::LPS>();
+    wait_lgkmcnt0();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    // all operand reads of the stage first, then the next stage's loads among the MFMAs: a CU accepts one 1 KB
+    // load per ~17 cycles and a wavefront issues in order, so loads in front of the reads would delay them
+    bf16x8 af[KSTEPS][T::FM], bf[KSTEPS][T::FN];
+#pragma unroll
+    for (int kk = 0; kk < KSTEPS; kk++) {
+      const unsigned char* sa = smem + rd * T::STAGE + (kk / 4) * T::SLICE;
+#pragma unroll
+      for (int i = 0; i < T::FM; i++) af[kk][i] = frag(std::integral_constant<bool, AKM>{}, WA{}, sa, wm * T::TM + i * 32, kk % 4);
+#pragma unroll
+      for (int j = 0; j < T::FN; j++)
+        bf[kk][j] = frag(std::integral_constant<bool, BKM>{}, WB{}, sa + T::A_BYTES, wn * T::TN + j * 32, kk % 4);
+    }
+    if constexpr (STAT_A) {
+#pragma unroll
+      for (int s = 0; s < T::SUB; s++) {
+        const unsigned char* sr = smem + rd * T::STAGE + s * T::SLICE + (tid / T::TPR) * 128 + (tid % T::TPR) * (128 / T::TPR);
+#pragma unroll
+        for (int c = 0; c < 8 / T::TPR; c++) ssq[c / 2] += sumsq8(*reinterpret_cast<const uint4*>(sr + c * 16));
+      }
+    }
+    asm volatile("" ::: "memory");
+    static_for<KSTEPS>([&](auto KK) {
+      constexpr int kk = decltype(KK)::value;
+      constexpr int l0 = kk * T::LPS / KSTEPS, l1 = (kk + 1) * T::LPS / KSTEPS;
+      static_for<l1 - l0>([&](auto L) { issue_one(it + T::NS - 1, wr, std::integral_constant<int, l0 + decltype(L)::value>{}); });
+#pragma unroll
+      for (int i = 0; i < T::FM; i++)
+#pragma unroll
+        for (int j = 0; j < T::FN; j++)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[kk][j], af[kk][i], acc[i][j], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    rd = rd + 1 == T::NS ? 0 : rd + 1;
+    wr = wr + 1 == T::NS ? 0 : wr + 1;
+  }
+  wait_vmcnt<0>();
+  __syncthreads();           // the ring is dead from here on
+  float* sStat = reinterpret_cast<float*>(smem + T::STAT_OFF);
+  if constexpr (STAT_A) {
+    float s = ssq[0];
+    if constexpr (T::TPR == 2) s += ssq[1];
+    s += __shfl_xor(s, 1);
+    if constexpr (T::TPR == 4) s += __shfl_xor(s, 2);
+    if (tid % T::TPR == 0) sStat[tid / T::TPR] = s;
+    __syncthreads();
+  }
+  gemm_epilogue<T, KIND, STAT_A>(op, acc, smem, sStat, wave, lane, m0, n0, tn, tiles_n, b, bi, bo, bz);
+}
+
+template <class T, int KIND, bool STAT_A, bool AKM, bool BKM>
+hipError_t launch_ring(const GemmOp& op, hipStream_t st) {
+  auto kern = gemm_ring_kernel<T, KIND, STAT_A, AKM, BKM>;
+  // one-time opt-in to more than 64 KB of dynamic LDS (thread-safe function-local static)
+  static const hipError_t attr_err =
+      hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
+  if (attr_err != hipSuccess) return attr_err;
+  const int tiles_m = (op.M + T::BM - 1) / T::BM, tiles_n = (op.N + T::BN - 1) / T::BN;
+  int kper = (op.K + op.splitk - 1) / op.splitk;
+  kper = (kper + BK - 1) / BK * BK;    // a split ends on a slice boundary; a ragged last stage reads zeros
+  hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n, op.batch * op.splitk), dim3(T::NT), T::LDS_BYTES, st, op, kper, tiles_m, tiles_n);
+  return hipGetLastError();
+}
+
+// Every (epilogue, operand form) the sequencing code issues: forward products have both operands k-contiguous,
+// data gradients a k-major weight, weight gradients and the attention's query gradient two k-major operands.
+template <class T>
+hipError_t dispatch_ring(const GemmOp& op, hipStream_t st) {
+  const int kind = op.splitk > 1 ? (int)EPI_PARTIAL : op.epi.kind;
+  const bool stat = op.epi.stat_from_a != 0;
+  if (op.transA && op.transB) {
+    switch (kind) {
+      case EPI_PARTIAL: return launch_ring<T, EPI_PARTIAL, false, true, true>(op, st);
+      case EPI_STORE: return launch_ring<T, EPI_STORE, false, true, true>(op, st);
+      default: return hipErrorInvalidValue;
+    }
+  }
+  if (op.transB) {
+    switch (kind) {
+      case EPI_STORE: return launch_ring<T, EPI_STORE, false, false, true>(op, st);
+      case EPI_UP: return launch_ring<T, EPI_UP, false, false, true>(op, st);
+      case EPI_ACTGRAD: return launch_ring<T, EPI_ACTGRAD, false, false, true>(op, st);
+      case EPI_LAXGRAD: return launch_ring<T, EPI_LAXGRAD, false, false, true>(op, st);
+      case EPI_NORMBWD: return launch_ring<T, EPI_NORMBWD, false, false, true>(op, st);
+      case EPI_NORMBWD_O32: return launch_ring<T, EPI_NORMBWD_O32, false, false, true>(op, st);
+      case EPI_NORMBWD_I32: return launch_ring<T, EPI_NORMBWD_I32, false, false, true>(op, st);
+      case EPI_SWIGLU_BWD: return launch_ring<T, EPI_SWIGLU_BWD, false, false, true>(op, st);
+      default: return hipErrorInvalidValue;
+    }
+  }
+  switch (kind) {
+    case EPI_STORE: return launch_ring<T, EPI_STORE, false, false, false>(op, st);
+    case EPI_DOWN:
+      return stat ? launch_ring<T, EPI_DOWN, true, false, false>(op, st) : launch_ring<T, EPI_DOWN, false, false, false>(op, st);
+    case EPI_DOWN_LAX:
+      return stat ? launch_ring<T, EPI_DOWN_LAX, true, false, false>(op, st)
+                  : launch_ring<T, EPI_DOWN_LAX, false, false, false>(op, st);
+    case EPI_UP: return launch_ring<T, EPI_UP, false, false, false>(op, st);
+    case EPI_UP_O32: return launch_ring<T, EPI_UP_O32, false, false, false>(op, st);
+    case EPI_UP_I32: return launch_ring<T, EPI_UP_I32, false, false, false>(op, st);
+    case EPI_SWIGLU_FWD: return launch_ring<T, EPI_SWIGLU_FWD, false, false, false>(op, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace
+}  // namespace lrb

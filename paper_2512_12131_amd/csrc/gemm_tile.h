@@ -1,0 +1,274 @@
+// What the bf16 MFMA GEMM kernels share: compile-time loops, wait counts, the workgroup -> tile map and the
+// epilogue that carries an accumulator tile through LDS into row-contiguous global vectors.
+#pragma once
+#include <type_traits>
+
+#include "epilogue.h"
+
+namespace lrb {
+namespace {
+
+constexpr int BK = 64;          // k elements per LDS stage: 128-byte rows, i.e. whole cache lines per request
+constexpr int NXCD = 8;
+
+// Compile-time loop: the body receives std::integral_constant indices, so register arrays indexed
+// by them never turn into scratch memory, whatever the unroller decides.
+template <int N, class F, int I = 0>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, F, I + 1>(static_cast<F&&>(f));
+  }
+}
+
+__device__ __forceinline__ float sumsq8(const uint4& q) {
+  float v[8];
+  unpack8(q, v);
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < 8; i++) s = fmaf(v[i], v[i], s);
+  return s;
+}
+
+// s_waitcnt vmcnt(N) with the other counters left alone (gfx9 encoding: vmcnt in bits 3:0 and 15:14).
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0f70);
+}
+__device__ __forceinline__ void wait_lgkmcnt0() { __builtin_amdgcn_s_waitcnt(0xc07f); }
+
+// Sum over aligned groups of N = 4, 8 or 16 consecutive lanes, every lane receiving the total, with
+// data-parallel-primitive moves (register file only): neighbours inside a quad, then the mirror image
+// inside 8 lanes, then inside 16.  (A butterfly of __shfl_xor goes through the LDS crossbar: four
+// dependent round trips per row partial.)
+template <int N>
+__device__ __forceinline__ float lane_group_sum(float x) {
+  static_assert(N == 4 || N == 8 || N == 16, "lane group size");
+  auto dpp = [](float v, auto CTRL) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(CTRL)::value, 0xf, 0xf, false));
+  };
+  x += dpp(x, std::integral_constant<int, 0xB1>{});    // quad_perm [1,0,3,2]
+  x += dpp(x, std::integral_constant<int, 0x4E>{});    // quad_perm [2,3,0,1]
+  if constexpr (N >= 8) x += dpp(x, std::integral_constant<int, 0x141>{});   // row_half_mirror: lane i <-> 7 - i
+  if constexpr (N == 16) x += dpp(x, std::integral_constant<int, 0x140>{});   // row_mirror: lane i <-> 15 - i
+  return x;
+}
+
+// Maps the linear workgroup id to an output tile so that (a) the workgroups that the hardware
+// deals round-robin to one XCD form a contiguous range of tiles, and (b) consecutive tiles of that
+// range form compact panels (PM tiles tall), keeping the A rows and B rows they share in that
+// XCD's L2.
+// The range runs over the whole launch, (batch member, k split) slowest: an XCD then works on tiles of
+// one batch member and one k range at a time, which is what lets its workgroups share operand slices.
+__device__ __forceinline__ void tile_of_block(int bid, int total, int tiles_m, int tiles_n, int& tm, int& tn, int& bz) {
+  const int xcd = bid % NXCD, loc = bid / NXCD;
+  const int base = total / NXCD, rem = total % NXCD;
+  const int nid = xcd * base + (xcd < rem ? xcd : rem) + loc;
+  const int tiles = tiles_m * tiles_n;
+  bz = nid / tiles;
+  const int tid_ = nid % tiles;
+  constexpr int PM = 8;
+  const int per_panel = PM * tiles_n;
+  const int panel = tid_ / per_panel, within = tid_ % per_panel;
+  const int pm_eff = min(PM, tiles_m - panel * PM);
+  tn = within / pm_eff;
+  tm = panel * PM + within % pm_eff;
+}
+
+#define LRB_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
+
+// ---- epilogue ---------------------------------------------------------------------------------
+// Called by every wavefront of a workgroup once its accumulators are final and the main loop's LDS is dead.
+// Tile type T: BM rows; WN wavefronts across, each with an FM x FN arrangement of 32x32 MFMA blocks (TM x TN);
+// CS = fp32 row stride of the staging tile.  (m0, n0): first row / column of the output tile, tn its column
+// index, b / (bi, bo) / bz: batch member, its two-level split, batch member times k split.  sStat: the row
+// statistics gathered in the main loop (STAT_A).
+template <class T, int KIND, bool STAT_A>
+__device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T::FM][T::FN], unsigned char* smem,
+                                              const float* sStat, int wave, int lane, int m0, int n0, int tn,
+                                              int tiles_n, int b, int bi, int bo, int bz) {
+  const int wm = wave / T::WN, wn = wave % T::WN;
+  // The wavefront's sub-tile leaves in FM x (32/RPP) passes of RPP rows.  Everything the passes touch
+  // in global memory goes through buffer resources that start at the tile's first row and end after
+  // its last valid row: rows past M (and, by an out-of-range offset, columns past N) read as zeros and
+  // are dropped on store, an absent auxiliary tile is a resource of size zero.  The pass code is
+  // therefore free of branches, which is what lets the compiler count the loads in flight exactly: the
+  // auxiliary tiles an epilogue reads (residual, z, x, g, u) are fetched PF passes ahead into a small
+  // register ring, and each pass waits only for its own.
+  const Epilogue& e = op.epi;
+  float* sC = reinterpret_cast<float*>(smem) + wave * (32 * T::CS);
+  constexpr int LPR = T::TN / 8;            // lanes per output row
+  constexpr int RPP = 64 / LPR;             // rows per pass
+  constexpr int PPB = 32 / RPP;             // passes per 32-row block
+  constexpr int NQ = T::FM * PPB;           // passes per wavefront
+  // which auxiliary tiles a kind can read at all, and the prefetch distance in passes: kinds with one
+  // auxiliary tile keep eight of its 16-byte vectors in flight per lane, kinds with two keep four of each
+  // BASE: the formula; R_F32: the R tile is fp32 (two 16-byte vectors per lane and pass); O32: the primary
+  // output is also written un-rounded, as fp32, into C32
+  constexpr int BASE = epi_base(KIND);
+  constexpr bool R_F32 = epi_r_is_f32(KIND), O32 = epi_writes_f32(KIND);
+  constexpr bool HAS_R = BASE == EPI_UP || BASE == EPI_ACTGRAD || BASE == EPI_NORMBWD || BASE == EPI_SWIGLU_BWD ||
+                         BASE == EPI_SWIGLU_FWD || BASE == EPI_DOWN_LAX || BASE == EPI_LAXGRAD;
+  constexpr bool HAS_R2 = BASE == EPI_NORMBWD || BASE == EPI_SWIGLU_BWD || BASE == EPI_LAXGRAD;
+  constexpr int PF = (HAS_R2 || R_F32) ? 4 : 8;
+  constexpr uint32_t EOOB = 0x80000000u;
+  const int cg = lane % LPR, rsub = lane / LPR;
+  const int rows_valid = min(T::BM, op.M - m0);
+  const int coln = n0 + wn * T::TN + cg * 8;                         // first of this lane's 8 columns
+  const bool col_ok = coln < op.N;
+  auto tile_rsrc = [&](const void* base, int64_t batch_off, int64_t ld, int esz) {
+    const char* p = base ? (const char*)base + (batch_off + (int64_t)m0 * ld) * esz : nullptr;
+    return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, base ? (uint32_t)rows_valid * (uint32_t)ld * (uint32_t)esz : 0u,
+                                             0x00020000);
+  };
+  auto row_rsrc = [&](const float* base) {   // per-row fp32 scalars of the tile's rows
+    return __builtin_amdgcn_make_buffer_rsrc((void*)(base ? base + m0 : nullptr), 0, base ? (uint32_t)rows_valid * 4u : 0u,
+                                             0x00020000);
+  };
+  constexpr bool PARTIAL = KIND == EPI_PARTIAL;
+  // C: bf16 [batch][M][ldc]; fp32 split-K partials: [batch * split][M][N]
+  const __amdgpu_buffer_rsrc_t rsC = PARTIAL
+      ? __builtin_amdgcn_make_buffer_rsrc((void*)((char*)op.C + ((int64_t)bz * op.M + m0) * op.N * 4), 0,
+                                          (uint32_t)rows_valid * (uint32_t)op.N * 4u, 0x00020000)
+      : tile_rsrc(op.C, (int64_t)bi * op.sC + (int64_t)bo * op.sCo, op.ldc, 2);
+  const __amdgpu_buffer_rsrc_t rsC2 = tile_rsrc(PARTIAL ? nullptr : e.C2, (int64_t)b * e.sC2, e.ldc2, 2);
+  const bool use_r = !PARTIAL && epi_reads_r<BASE>(e), use_r2 = !PARTIAL && epi_reads_r2<BASE>(e);
+  const __amdgpu_buffer_rsrc_t rsR = tile_rsrc(use_r ? e.R : nullptr, (int64_t)b * e.sR, e.ldr, R_F32 ? 4 : 2);
+  const __amdgpu_buffer_rsrc_t rsC32 = tile_rsrc(O32 ? e.C32 : nullptr, 0, e.ldc32, 4);
+  const __amdgpu_buffer_rsrc_t rsR2 = tile_rsrc(use_r2 ? e.R2 : nullptr, (int64_t)b * e.sR2, e.ldr2, 2);
+  const __amdgpu_buffer_rsrc_t rsRowA = row_rsrc((!PARTIAL && e.use_rho && !STAT_A) ? e.rowa : nullptr);
+  const __amdgpu_buffer_rsrc_t rsRowB = row_rsrc(!PARTIAL ? e.rowb : nullptr);
+  const int ldC = PARTIAL ? op.N * 4 : (int)op.ldc * 2;               // row pitches in bytes
+  const int ldC2 = (int)e.ldc2 * 2, ldR = (int)e.ldr * (R_F32 ? 4 : 2), ldR2 = (int)e.ldr2 * 2, ldC32 = (int)e.ldc32 * 4;
+  const uint32_t colC = col_ok ? (uint32_t)coln * (PARTIAL ? 4u : 2u) : EOOB, col2 = col_ok ? (uint32_t)coln * 2u : EOOB;
+  const uint32_t col4 = col_ok ? (uint32_t)coln * 4u : EOOB;      // this lane's columns in an fp32 tile
+  const bool want2 = KIND == EPI_SWIGLU_BWD || KIND == EPI_SWIGLU_FWD || KIND == EPI_DOWN_LAX || KIND == EPI_LAXGRAD ||
+                     (KIND == EPI_DOWN && e.C2 != nullptr);
+  const bool use_rho = !PARTIAL && e.use_rho;
+  const bool rho_sqrt = e.rho_sqrt != 0;
+  // row partials [M, rowpart_ld] and the statistic [M]: one lane per row writes, the others (and rows
+  // past M) are given an out-of-range offset
+  constexpr bool ROWPART = BASE == EPI_UP || BASE == EPI_ACTGRAD || BASE == EPI_LAXGRAD;
+  const __amdgpu_buffer_rsrc_t rsPart = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)((ROWPART && e.rowpart) ? e.rowpart + (int64_t)m0 * e.rowpart_ld : nullptr), 0,
+      (ROWPART && e.rowpart) ? (uint32_t)rows_valid * (uint32_t)e.rowpart_ld * 4u : 0u, 0x00020000);
+  const int ldPart = ROWPART ? (int)e.rowpart_ld * 4 : 0;
+  const uint32_t colPart = cg == 0 ? (uint32_t)(e.rowpart_off + b * (tiles_n * T::WN) + tn * T::WN + wn) * 4u : EOOB;
+  const bool write_stat = STAT_A && e.stat_out && tn == 0 && wn == 0 && b == 0;
+  const __amdgpu_buffer_rsrc_t rsStat = row_rsrc(write_stat ? e.stat_out : nullptr);
+  const uint32_t colStat = cg == 0 ? 0u : EOOB;
+  const int act = e.act;
+  const float inv_d = e.inv_d, eps = e.eps;
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  u32x4 auxr[PF], auxr2[PF], auxr3[R_F32 ? PF : 1];   // auxr3: columns 4..7 of an fp32 R tile
+  auto row_of = [&](int q) { return wm * T::TM + (q / PPB) * 32 + (q % PPB) * RPP + rsub; };   // row inside the tile
+  auto fetch = [&](int q, u32x4& ar, u32x4& ar2, u32x4& ar3) {
+    const int lm = row_of(q);
+    if constexpr (R_F32) {
+      ar = __builtin_amdgcn_raw_buffer_load_b128(rsR, (int)((uint32_t)(lm * ldR) + col4), 0, 0);
+      ar3 = __builtin_amdgcn_raw_buffer_load_b128(rsR, (int)((uint32_t)(lm * ldR) + col4 + 16u), 0, 0);
+    } else if constexpr (HAS_R) {
+      ar = __builtin_amdgcn_raw_buffer_load_b128(rsR, (int)((uint32_t)(lm * ldR) + col2), 0, 0);
+    }
+    if constexpr (HAS_R2) ar2 = __builtin_amdgcn_raw_buffer_load_b128(rsR2, (int)((uint32_t)(lm * ldR2) + col2), 0, 0);
+  };
+  static_for<PF>([&](auto Q) {
+    constexpr int q = decltype(Q)::value;
+    auxr[q] = u32x4{0u, 0u, 0u, 0u};
+    auxr2[q] = u32x4{0u, 0u, 0u, 0u};
+    if constexpr (R_F32) auxr3[q] = u32x4{0u, 0u, 0u, 0u};
+    if constexpr (q < NQ) fetch(q, auxr[q], auxr2[q], auxr3[R_F32 ? q : 0]);
+  });
+  // per-row scalars of all passes, requested before the first pass
+  float ssv[NQ], rbv[NQ];
+  static_for<NQ>([&](auto Q) {
+    constexpr int q = decltype(Q)::value;
+    ssv[q] = 0.f;
+    rbv[q] = 0.f;
+    if constexpr (!PARTIAL && !STAT_A) {
+      if (use_rho) ssv[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsRowA, row_of(q) * 4, 0, 0));
+    }
+    if constexpr (BASE == EPI_NORMBWD)
+      rbv[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsRowB, row_of(q) * 4, 0, 0));
+  });
+  static_for<NQ>([&](auto Q) {
+    constexpr int q = decltype(Q)::value;
+    constexpr int i = q / PPB, p = q % PPB;
+    if constexpr (p == 0) {
+      static_for<T::FN>([&](auto J) {
+        constexpr int j = decltype(J)::value;
+        // the accumulators hold the transposed 32x32 block (the MFMA is issued with its operands
+        // exchanged): lane -> row lane%32, registers 4g..4g+3 -> columns 8g + 4*(lane/32) + 0..3, so a lane
+        // stages four consecutive columns with one 16-byte write
+#pragma unroll
+        for (int g = 0; g < 4; g++)
+          *reinterpret_cast<float4*>(sC + (lane & 31) * T::CS + j * 32 + 8 * g + 4 * (lane >> 5)) =
+              make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
+      });
+      // No barrier: the staging region belongs to this wavefront alone and a wavefront's LDS
+      // operations complete in order.
+    }
+    const int rl = p * RPP + rsub;
+    const int lm = wm * T::TM + i * 32 + rl;      // row inside the block tile
+    float v[8];
+    {
+      const float4 lo = *reinterpret_cast<const float4*>(sC + rl * T::CS + cg * 8);
+      const float4 hi = *reinterpret_cast<const float4*>(sC + rl * T::CS + cg * 8 + 4);
+      v[0] = lo.x; v[1] = lo.y; v[2] = lo.z; v[3] = lo.w;
+      v[4] = hi.x; v[5] = hi.y; v[6] = hi.z; v[7] = hi.w;
+    }
+    if constexpr (PARTIAL) {
+      const uint32_t off = (uint32_t)(lm * ldC) + colC;
+      const u32x4 lo = {__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])};
+      const u32x4 hi = {__float_as_uint(v[4]), __float_as_uint(v[5]), __float_as_uint(v[6]), __float_as_uint(v[7])};
+      __builtin_amdgcn_raw_buffer_store_b128(lo, rsC, (int)off, 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b128(hi, rsC, (int)(off + 16u), 0, 0);
+    } else {
+      float rho = 1.f, rowb = 0.f;
+      if (use_rho) {
+        float ss;
+        if constexpr (STAT_A) ss = sStat[lm];
+        else ss = ssv[q];
+        rho = rho_sqrt ? sqrtf(ss * inv_d + eps) : rsqrtf(ss * inv_d + eps);
+      }
+      if constexpr (BASE == EPI_NORMBWD) rowb = rbv[q];
+      float r[8], r2[8], v2[8];
+      if constexpr (R_F32) {
+        const u32x4 a0 = auxr[q % PF], a1 = auxr3[q % PF];
+        r[0] = __uint_as_float(a0.x); r[1] = __uint_as_float(a0.y); r[2] = __uint_as_float(a0.z); r[3] = __uint_as_float(a0.w);
+        r[4] = __uint_as_float(a1.x); r[5] = __uint_as_float(a1.y); r[6] = __uint_as_float(a1.z); r[7] = __uint_as_float(a1.w);
+      } else {
+        unpack8(make_uint4(auxr[q % PF].x, auxr[q % PF].y, auxr[q % PF].z, auxr[q % PF].w), r);
+      }
+      unpack8(make_uint4(auxr2[q % PF].x, auxr2[q % PF].y, auxr2[q % PF].z, auxr2[q % PF].w), r2);
+      float part = epi_math<8, BASE, true>(act, inv_d, want2, v, v2, rho, rowb, r, r2);
+      if constexpr (O32) {
+        const u32x4 lo = {__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])};
+        const u32x4 hi = {__float_as_uint(v[4]), __float_as_uint(v[5]), __float_as_uint(v[6]), __float_as_uint(v[7])};
+        const uint32_t off = (uint32_t)(lm * ldC32) + col4;
+        __builtin_amdgcn_raw_buffer_store_b128(lo, rsC32, (int)off, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(hi, rsC32, (int)(off + 16u), 0, 0);
+      }
+      {
+        const uint4 o = pack8(v);
+        const u32x4 ov = {o.x, o.y, o.z, o.w};
+        __builtin_amdgcn_raw_buffer_store_b128(ov, rsC, (int)((uint32_t)(lm * ldC) + colC), 0, 0);
+      }
+      if (want2) {
+        const uint4 o = pack8(v2);
+        const u32x4 ov = {o.x, o.y, o.z, o.w};
+        __builtin_amdgcn_raw_buffer_store_b128(ov, rsC2, (int)((uint32_t)(lm * ldC2) + col2), 0, 0);
+      }
+      if constexpr (q + PF < NQ) fetch(q + PF, auxr[q % PF], auxr2[q % PF], auxr3[R_F32 ? q % PF : 0]);
+      if constexpr (ROWPART) {
+        part = lane_group_sum<LPR>(part);
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(part), rsPart, (int)((uint32_t)(lm * ldPart) + colPart), 0, 0);
+      }
+      if constexpr (STAT_A)
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(sStat[lm]), rsStat, (int)((uint32_t)(lm * 4) + colStat), 0, 0);
+    }
+  });
+}
+
+}  // namespace
+}  // namespace lrb

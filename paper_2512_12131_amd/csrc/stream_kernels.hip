@@ -567,13 +567,28 @@ __global__ __launch_bounds__(256) void transpose16_vec_kernel(const uint16_t* in
   }
 }
 
-__global__ __launch_bounds__(256) void rowsum_parts_kernel(const float* part, int64_t ld, int nparts, float* out,
-                                                           int64_t M) {
-  const int64_t m = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (m >= M) return;
+// Row partials -> row sums: eight lanes per row, lane l takes the 128-column groups l, l + 8, ...  A group that
+// arrives as two or four partials is added up pairwise first, the order in which a wavefront that owns 128
+// columns adds its quads of lanes: the sum has the same bits whichever tile wrote the partials.  Bound by
+// launch and latency (8 MB at most); one thread per row left most CUs without a wavefront (4.8 us at 16384
+// rows x 8 partials).
+__global__ __launch_bounds__(256) void rowsum_parts_kernel(const float* part, int64_t ld, int members, int slabs, int per128,
+                                                           int n128, float* out, int64_t M) {
+  const int l = threadIdx.x & 7;
+  const int64_t m = (int64_t)blockIdx.x * 32 + (threadIdx.x >> 3);
   float s = 0.f;
-  for (int p = 0; p < nparts; p++) s += part[m * ld + p];
-  out[m] = s;
+  if (m < M) {
+    for (int i = l; i < members * n128; i += 8) {
+      const int g = i / n128, c0 = (i % n128) * per128;
+      const float* p = part + m * ld + g * slabs + c0;
+      auto at = [&](int j) { return j < per128 && c0 + j < slabs ? p[j] : 0.f; };
+      s += (at(0) + at(1)) + (at(2) + at(3));
+    }
+  }
+  s += __shfl_xor(s, 1);
+  s += __shfl_xor(s, 2);
+  s += __shfl_xor(s, 4);
+  if (m < M && l == 0) out[m] = s;
 }
 
 template <int DT>
@@ -839,9 +854,11 @@ hipError_t k_transpose(const void* in, int64_t ld_in, void* out, int64_t ld_out,
                        ld_out, rows, cols, pad_to);
   return hipGetLastError();
 }
-hipError_t k_rowsum_parts(const float* part, int64_t ld, int nparts, float* out, int64_t M, hipStream_t st) {
+hipError_t k_rowsum_parts(const float* part, int64_t ld, int members, const RowParts& rp, float* out, int64_t M,
+                          hipStream_t st) {
   if (M <= 0) return hipSuccess;
-  hipLaunchKernelGGL(rowsum_parts_kernel, dim3((M + 255) / 256), dim3(256), 0, st, part, ld, nparts, out, M);
+  hipLaunchKernelGGL(rowsum_parts_kernel, dim3((M + 31) / 32), dim3(256), 0, st, part, ld, members, rp.slabs, rp.per128, rp.n128,
+                     out, M);
   return hipGetLastError();
 }
 hipError_t k_rowdot(const void* a, int64_t lda, const void* b, int64_t ldb, float* out, int64_t M, int64_t N, int dt,

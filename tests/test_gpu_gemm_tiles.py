@@ -1,0 +1,98 @@
+"""The bf16 products run on one of several output tiles, chosen by size.  The choice must not show in the result,
+every tile must be right at its edges, and no call may use more workspace than the size query asks for."""
+import pytest
+import torch
+
+import synth_inputs as si
+from oracle import lowrank_oracle as orc
+from paper_2512_12131_amd import binding as B
+from parity import check, l2_and_slope, relerr
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("norm", [B.LR_NORM_NONE, B.LR_NORM_ONLINE_GATHER])
+def test_rows_do_not_depend_on_the_tile(norm):
+    # 16384 tokens run on the 256-row tiles, fewer on the smaller ones, with other numbers of column tiles and,
+    # in the gathered norm, other threads adding up a row: every row has to keep its bits
+    d, r, T = 1024, 512, 16384
+    g = torch.Generator(device=DEV).manual_seed(3)
+    x = torch.randn((T, d), generator=g, device=DEV).bfloat16()
+    gamma = (1 + 0.1 * torch.randn((d,), generator=g, device=DEV)).bfloat16()
+    wd = (torch.randn((2 * r, d), generator=g, device=DEV) * d ** -0.5).bfloat16()
+    wu = (torch.randn((2, d, r), generator=g, device=DEV) * r ** -0.5).bfloat16()
+    z, s, y = B.lr_group_fwd(x, gamma, 1e-5, norm, wd, wu)
+    for t in (1, 63, 65, 129, 777, 2048, 5000):
+        print(f"rows t={t} norm={norm}", flush=True)
+        z1, s1, y1 = B.lr_group_fwd(x[:t].contiguous(), gamma, 1e-5, norm, wd, wu)
+        torch.cuda.synchronize()
+        assert torch.equal(z1, z[:t]) and torch.equal(y1, y[:, :t])
+        assert norm == B.LR_NORM_NONE or torch.equal(s1, s[:t])
+
+
+# one tile exactly, one row / column chunk more, remainders in every dimension, k shorter than a slice, several
+# splits of the token reduction, wide and narrow outputs
+EDGES = [(64, 64, 64, 64), (65, 72, 8, 136), (129, 264, 120, 520), (255, 1032, 200, 328), (2, 2048, 64, 2048),
+         (777, 128, 32, 4096), (3000, 264, 72, 200)]
+
+
+def _bf(a):
+    return torch.from_numpy(a).to(torch.bfloat16).to(torch.float64).numpy()
+
+
+def _ideal_bf16_linear(X, WD, WU, DY):
+    """The layer in fp64 with one rounding to bf16 wherever a tensor is stored as bf16 (z, sigma(z), dz, the bf16
+    outputs): with a rank of 8 those roundings hardly average out, and an ideal implementation is past the flat bar
+    too.  Its error is the bound a tensor may use instead (parity.check, rule 3)."""
+    z = _bf(X @ WD.T)
+    sg = 1 / (1 + torch.exp(-torch.from_numpy(z))).numpy()
+    a = _bf(z * sg)
+    dz = _bf((DY @ WU) * sg * (1 + z * (1 - sg)))
+    return {"z": z, "y": _bf(a @ WU.T), "dx": _bf(dz @ WD), "dw_down": dz.T @ X, "dw_up": DY.T @ a}
+
+
+@pytest.mark.parametrize("T,d_in,r,d_out", EDGES)
+def test_linear_at_tile_edges(T, d_in, r, d_out):
+    print(f"linear T={T} d_in={d_in} r={r} d_out={d_out}", flush=True)
+    c = si.linear_case(T, d_in, r, d_out, dtype=torch.bfloat16, seed=2)
+    x, wd, wu, dy = (c[k].to(DEV) for k in ("x", "w_down", "w_up", "dy"))
+    z, y = B.lr_linear_fwd(x, wd, wu)
+    dx, dwd, dwu = B.lr_linear_bwd(x, wd, wu, z, dy)
+    acc = (dwd.clone(), dwu.clone())
+    B.lr_linear_bwd(x, wd, wu, z, dy, grads=acc)
+    torch.cuda.synchronize()
+    X, WD, WU, DY = (si.f64(c[k]) for k in ("x", "w_down", "w_up", "dy"))
+    z_ref, _, y_ref = orc.lr_linear_fwd(X, WD, WU, B.LR_ACT_SILU)
+    refs = orc.lr_linear_bwd(X, WD, WU, DY, B.LR_ACT_SILU)
+    ideal = _ideal_bf16_linear(X, WD, WU, DY)
+    for n, got, ref in (("z", z, z_ref), ("y", y, y_ref), ("dx", dx, refs[0]), ("dw_down", dwd, refs[1]), ("dw_up", dwu, refs[2])):
+        check(n, got, ref, torch.bfloat16, (relerr(ideal[n], ref), l2_and_slope(ideal[n], ref)[0]))
+    # the accumulating form adds the same sum, in another split, to what is there: fp32 sums of T terms
+    for a, b in zip(acc, (dwd, dwu)):
+        assert float((a - 2 * b).norm() / b.norm()) < 1e-5
+
+
+@pytest.mark.parametrize("accumulate,grad_dt", [(False, B.LR_F32), (True, B.LR_F32), (False, B.LR_BF16), (True, B.LR_BF16)])
+def test_block_keeps_to_the_workspace_it_asks_for(accumulate, grad_dt):
+    Bn, S, H, f, r = 3, 192, 6, 2303, 120
+    print(f"block B={Bn} S={S} H={H} f={f} r={r} accumulate={accumulate} grad_dt={grad_dt}", flush=True)
+    d, f_ld = 128 * H, si.pad_ld(f, 8)
+    case = si.block_case(Bn, S, d, H, 128, f, r, seed=0)
+    desc = B.make_block_desc(Bn, S, d, H, 128, f, f_ld, r, grad_dt=grad_dt)
+    packed = {k: v.to(DEV) for k, v in si.pack_block_params(case["params"], f, f_ld).items()}
+    x, dy = case["x"].to(DEV), case["dy"].to(DEV)
+    guard = 64 << 20      # more than any buffer of the call: an overrun lands in it
+
+    def workspace(backward):
+        n = B.lr_block_workspace_bytes(desc, backward)
+        return n, torch.full((n + guard,), 0x5A, dtype=torch.uint8, device=DEV)
+
+    nf, wf = workspace(0)
+    nb, wb = workspace(1)
+    y, ck = B.lr_block_fwd(desc, packed, x, ws=wf)
+    grads = {n: torch.zeros_like(packed[n], dtype=torch.float32 if grad_dt == B.LR_F32 else torch.bfloat16)
+             for n in B.PARAM_NAMES}
+    B.lr_block_bwd(desc, packed, x, dy, ck, grads=grads, accumulate=accumulate, ws=wb)
+    torch.cuda.synchronize()
+    assert bool((wf[nf:] == 0x5A).all()) and bool((wb[nb:] == 0x5A).all())
