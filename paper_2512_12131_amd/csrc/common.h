@@ -153,12 +153,12 @@ hipError_t k_scale_cols(const void* w, const void* gamma, void* wout, int64_t ro
                         hipStream_t);
 // Sum `nsplit` fp32 partials [nsplit][count] (batch-major outside) and write / accumulate into dw.
 //   dw[i] (+)= colscale[i % cols] * sum_s part[s][i]      (colscale optional)
-// With wg_for_dgamma (the un-scaled weight) also emits dgamma_part[row_block][cols] partial sums of
+// With wg_for_dgamma (the un-scaled weight) also emits dgamma_part[k_wgrad_dgamma_parts()][cols] partial sums of
 // w * sum_s part (dgamma = sum over all rows).
 hipError_t k_wgrad_finish(const float* part, int nsplit, int64_t rows, int64_t cols, void* dw,
                           const void* colscale, const void* w_for_dgamma, float* dgamma_part,
                           int accumulate, int dt, int out_dt, hipStream_t);
-int64_t k_wgrad_dgamma_parts(int64_t rows);
+int64_t k_wgrad_dgamma_parts(int64_t rows, int64_t cols, int dt);
 // out[c] (+)= sum_p part[p, c]; out has dtype out_dt
 hipError_t k_colsum_parts(const float* part, int64_t nparts, int64_t cols, void* out, int accumulate,
                           int out_dt, hipStream_t);

@@ -630,16 +630,21 @@ __global__ __launch_bounds__(256) void scale_cols_kernel(const void* w, const vo
 
 // ---- finish a split-K weight gradient ------------------------------------------------------------
 // One thread per 8-column (bf16) / 1-column (fp32) vector of one row: sums the nsplit fp32 partials,
-// scales, accumulates, stores.  When dgamma partials are wanted a workgroup covers WF_RB rows of a
+// scales, accumulates, stores.  When dgamma partials are wanted a workgroup covers `rb` rows of a
 // 64-vector column strip: its 4 wavefronts take rows r, r+4, ... and add their column sums through LDS.
-constexpr int WF_RB = 32;  // rows per dgamma partial
+// rows per dgamma partial: 32, or 8 where 32 would leave CUs without two workgroups (3072 x 512, five
+// splits: 96 workgroups took 20 us; 3072 x 4096: 768 workgroups read at 5.4 TB/s)
+inline int wf_row_block(int64_t rows, int64_t cols, int dt) {
+  const int64_t strips = (cols / (dt == LR_BF16 ? 8 : 1) + 63) / 64;
+  return strips * ((rows + 31) / 32) < 512 ? 8 : 32;
+}
 
 // NS > 0: the number of split-K partials is known at compile time, so their loads are issued
 // together instead of one dependent round trip per partial; NS = 0 takes any count.
 template <int DT, typename OT, bool DG, int NS>
 __global__ __launch_bounds__(256) void wgrad_finish_kernel(const float* part, int nsplit, int64_t rows, int64_t cols,
                                                            void* dw, const void* colscale, const void* wdg,
-                                                           float* dgpart, int accumulate) {
+                                                           float* dgpart, int accumulate, int rb) {
   using S = St<DT>;
   using IO = VecIO<typename S::T, S::NV>;
   using OIO = VecIO<OT, S::NV>;
@@ -699,7 +704,7 @@ __global__ __launch_bounds__(256) void wgrad_finish_kernel(const float* part, in
     const int64_t c = ((int64_t)blockIdx.x * 64 + lane) * NV;
     const bool cok = c < cols;
     if (cok && colscale) IO::load(colscale, c, cs);
-    const int64_t rbeg = (int64_t)blockIdx.y * WF_RB, rend = min(rows, rbeg + WF_RB);
+    const int64_t rbeg = (int64_t)blockIdx.y * rb, rend = min(rows, rbeg + rb);
     if (cok)
       for (int64_t r = rbeg + wave; r < rend; r += 4) one(r, c);
 #pragma unroll
@@ -714,14 +719,27 @@ __global__ __launch_bounds__(256) void wgrad_finish_kernel(const float* part, in
   }
 }
 
+// Column sums of a few hundred partial rows: 16 columns (a 64-byte run) per workgroup, 16 threads per column that
+// take every 16th row.  Bound by the latency of the loads: a thread per column walked all rows one after the
+// other from a handful of workgroups (96 x 4096: 26 us).
 template <typename OT>
 __global__ __launch_bounds__(256) void colsum_parts_kernel(const float* part, int64_t nparts, int64_t cols, void* out,
                                                            int accumulate) {
   using IO = VecIO<OT, 1>;
-  const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (c >= cols) return;
+  __shared__ float red[16][17];
+  const int ci = threadIdx.x & 15, pi = threadIdx.x >> 4;
+  const int64_t c = (int64_t)blockIdx.x * 16 + ci;
   float s = 0.f;
-  for (int64_t p = 0; p < nparts; p++) s += part[p * cols + c];
+  if (c < cols) {
+#pragma unroll 8
+    for (int64_t p = pi; p < nparts; p += 16) s += part[p * cols + c];
+  }
+  red[pi][ci] = s;
+  __syncthreads();
+  if (pi != 0 || c >= cols) return;
+  s = 0.f;
+#pragma unroll
+  for (int i = 0; i < 16; i++) s += red[i][ci];
   if (accumulate) {
     float o;
     IO::load(out, c, &o);
@@ -872,23 +890,27 @@ hipError_t k_scale_cols(const void* w, const void* gamma, void* wout, int64_t ro
   const int nv = dt == LR_BF16 ? 8 : 1;
   DISPATCH_DT(dt, scale_cols_kernel, dim3(grid1d(rows * (cols / nv))), dim3(256), st, w, gamma, wout, rows, cols);
 }
-int64_t k_wgrad_dgamma_parts(int64_t rows) { return (rows + WF_RB - 1) / WF_RB; }
+int64_t k_wgrad_dgamma_parts(int64_t rows, int64_t cols, int dt) {
+  const int rb = wf_row_block(rows, cols, dt);
+  return (rows + rb - 1) / rb;
+}
 hipError_t k_wgrad_finish(const float* part, int nsplit, int64_t rows, int64_t cols, void* dw, const void* colscale,
                           const void* w_for_dgamma, float* dgamma_part, int accumulate, int dt, int out_dt,
                           hipStream_t st) {
   if (rows <= 0 || cols <= 0) return hipSuccess;
   const int nv = dt == LR_BF16 ? 8 : 1;
   const bool dg = w_for_dgamma != nullptr && dgamma_part != nullptr;
-  dim3 grid = dg ? dim3((unsigned)((cols / nv + 63) / 64), (unsigned)((rows + WF_RB - 1) / WF_RB))
+  const int rb = wf_row_block(rows, cols, dt);
+  dim3 grid = dg ? dim3((unsigned)((cols / nv + 63) / 64), (unsigned)((rows + rb - 1) / rb))
                  : dim3((unsigned)((rows * (cols / nv) + 255) / 256));
 #define LRB_WF2(DT_, OT_, NS_)                                                                                   \
   do {                                                                                                           \
     if (dg)                                                                                                      \
       hipLaunchKernelGGL((wgrad_finish_kernel<DT_, OT_, true, NS_>), grid, dim3(256), 0, st, part, nsplit, rows, cols, dw, \
-                         colscale, w_for_dgamma, dgamma_part, accumulate);                                      \
+                         colscale, w_for_dgamma, dgamma_part, accumulate, rb);                                  \
     else                                                                                                         \
       hipLaunchKernelGGL((wgrad_finish_kernel<DT_, OT_, false, NS_>), grid, dim3(256), 0, st, part, nsplit, rows, cols, dw, \
-                         colscale, w_for_dgamma, dgamma_part, accumulate);                                      \
+                         colscale, w_for_dgamma, dgamma_part, accumulate, rb);                                  \
   } while (0)
 #define LRB_WF(DT_, OT_)                                                                                         \
   do {                                                                                                           \
@@ -911,10 +933,10 @@ hipError_t k_colsum_parts(const float* part, int64_t nparts, int64_t cols, void*
                           hipStream_t st) {
   if (cols <= 0) return hipSuccess;
   if (out_dt == LR_F32)
-    hipLaunchKernelGGL(colsum_parts_kernel<float>, dim3((cols + 255) / 256), dim3(256), 0, st, part, nparts, cols, out,
+    hipLaunchKernelGGL(colsum_parts_kernel<float>, dim3((cols + 15) / 16), dim3(256), 0, st, part, nparts, cols, out,
                        accumulate);
   else
-    hipLaunchKernelGGL(colsum_parts_kernel<bf16_t>, dim3((cols + 255) / 256), dim3(256), 0, st, part, nparts, cols,
+    hipLaunchKernelGGL(colsum_parts_kernel<bf16_t>, dim3((cols + 15) / 16), dim3(256), 0, st, part, nparts, cols,
                        out, accumulate);
   return hipGetLastError();
 }
