@@ -266,10 +266,12 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(const uint16_t* __rest
   // Causal work grows linearly with the query block index.  Every workgroup takes one block from the
   // late end and its mirror image from the early end, so that all workgroups of the launch do the
   // same amount of work (the hardware deals workgroups to the XCDs in strict rotation: unequal
-  // workgroups leave most of the chip waiting for the XCD that drew the heavy ones).
+  // workgroups leave most of the chip waiting for the XCD that drew the heavy ones).  A launch that gives
+  // every block a CU of its own is not paired (grid.x = the number of blocks).
   for (int pass = 0; pass < 2; pass++) {
   const int qblk = pass == 0 ? nqb - 1 - wg.x : wg.x;
-  if (pass == 1 && qblk >= nqb - 1 - wg.x) break;   // odd block count: the middle block has no mirror
+  // unpaired launch, or odd block count: the middle block has no mirror
+  if (pass == 1 && ((int)gridDim.x == nqb || qblk >= nqb - 1 - wg.x)) break;
   const int q0 = qblk * BQ;
   const int qw0 = q0 + wave * MB * 32;                   // first query of this wavefront
 
@@ -654,7 +656,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(const uint16_t* __res
 
   for (int pass = 0; pass < 2; pass++) {
   const int kblk = pass == 0 ? wg.x : nkb - 1 - wg.x;
-  if (pass == 1 && kblk <= wg.x) break;
+  if (pass == 1 && ((int)gridDim.x == nkb || kblk <= wg.x)) break;   // (unpaired launch: see the forward)
   const int n0 = kblk * BN;
   const int nw0 = n0 + wave * NB * 32;
   if constexpr (WRITE_DS) {
@@ -846,7 +848,10 @@ hipError_t attention_gqa_fwd_bf16(const void* q, const void* k, const void* v, v
   static const hipError_t attr_err = set_lds(attn_fwd_kernel<MB>, FWD_LDS);
   if (attr_err != hipSuccess) return attr_err;
   const int nqb = (S + BQ - 1) / BQ;
-  dim3 grid((nqb + 1) / 2, H, B);                        // each workgroup: one query block and its mirror
+  // Each workgroup: one query block and its mirror; or one block, where each finds a CU free: the launch then takes
+  // as long as its longest block instead of a pair (2 x 256 tokens, 2 heads: 18.3 -> 12.3 us).  With two
+  // unpaired workgroups per CU the late blocks meet on some CUs (4 x 4096 tokens, 4 heads: 110 -> 135 us).
+  dim3 grid((int64_t)nqb * H * B <= 256 ? nqb : (nqb + 1) / 2, H, B);
   hipLaunchKernelGGL(attn_fwd_kernel<MB>, grid, dim3(256), FWD_LDS, st, (const uint16_t*)q, (const uint16_t*)k,
                      (const uint16_t*)v, (uint16_t*)o, lse, ld, ldkv, grp, S, H, 1.f / sqrtf((float)hd));
   return hipGetLastError();
@@ -900,7 +905,8 @@ hipError_t attention_gqa_bwd_bf16(const void* q, const void* k, const void* v, c
   hipLaunchKernelGGL(attn_dot_kernel, dim3((unsigned)((items * 16 + 255) / 256)), dim3(256), 0, st,
                      (const uint16_t*)dout, (const uint16_t*)o, lse, D, lse2, ld, S, H, items);
   const float scale = 1.f / sqrtf((float)hd);
-  const dim3 kv_grid(((S + DKV_NB * 128 - 1) / (DKV_NB * 128) + 1) / 2, H, B);
+  const int nkb = (S + DKV_NB * 128 - 1) / (DKV_NB * 128);   // paired or not as in the forward (29.6 -> 18.6 us)
+  const dim3 kv_grid((int64_t)nkb * H * B <= 256 ? nkb : (nkb + 1) / 2, H, B);
   const size_t small = (2 * (size_t)items * sizeof(float) + 255) / 256 * 256;
   // where the dK / dV kernel writes: the outputs themselves, or (fewer key / value heads than query
   // heads) one contribution per query head, added up at the end
@@ -924,28 +930,18 @@ hipError_t attention_gqa_bwd_bf16(const void* q, const void* k, const void* v, c
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     // dQ[q, :] = sum_key (scale dS^T)[key, q] * K[key, :], per (batch, head): both operands k-major, the
-    // key range of a row tile cut at its last query
+    // key range of a row tile cut at its last query; one launch, batch index = (batch element, head), the
+    // heads of a group on the same K
     GemmOp op;
     op.lda = S; op.transA = 1; op.ldb = ldkv; op.transB = 1; op.ldc = ld;
     op.M = S; op.N = HD; op.K = S; op.causal_k = 1;
     op.epi.kind = EPI_STORE;
-    if (grp == 1) {   // one launch: batch index = (batch element, head)
-      op.A = dst; op.sA = (int64_t)S * S; op.sAo = (int64_t)H * S * S;
-      op.B = k; op.sB = HD; op.sBo = (int64_t)S * ldkv;
-      op.C = dq; op.sC = HD; op.sCo = (int64_t)S * ld;
-      op.batch = B * H; op.batch_inner = H;
-      return gemm_bf16_untimed(op, st);
-    }
-    // one launch per batch element: batch index = (key / value head, query head inside its group)
-    for (int b = 0; b < B; b++) {
-      op.A = dst + (int64_t)b * H * S * S; op.sA = (int64_t)S * S; op.sAo = (int64_t)grp * S * S;
-      op.B = (const uint16_t*)k + (int64_t)b * S * ldkv; op.sB = 0; op.sBo = HD;
-      op.C = (uint16_t*)dq + (int64_t)b * S * ld; op.sC = HD; op.sCo = (int64_t)grp * HD;
-      op.batch = H; op.batch_inner = grp;
-      e = gemm_bf16_untimed(op, st);
-      if (e != hipSuccess) return e;
-    }
-    return group_sum();
+    op.A = dst; op.sA = (int64_t)S * S; op.sAo = (int64_t)H * S * S;
+    op.B = k; op.sB = HD; op.sBo = (int64_t)S * ldkv; op.b_group = grp;
+    op.C = dq; op.sC = HD; op.sCo = (int64_t)S * ld;
+    op.batch = B * H; op.batch_inner = H;
+    e = gemm_bf16_untimed(op, st);
+    return e != hipSuccess ? e : group_sum();
   }
   hipLaunchKernelGGL(attn_bwd_dq_kernel<DQ_MB>, dim3(((S + DQ_MB * 128 - 1) / (DQ_MB * 128) + 1) / 2, H, B), dim3(256), DQ_LDS, st, (const uint16_t*)q,
                      (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout, lse2, D, (uint16_t*)dq, ld, ldkv, grp,

@@ -78,6 +78,7 @@ struct GemmOp {
   // operand of that entry starts at outer * s?o + inner * s?.  batch_inner = 0: one level.
   int batch_inner = 0;
   int64_t sAo = 0, sBo = 0, sCo = 0;
+  int b_group = 1;             // consecutive (inner) members that share a B operand: sB counts groups
   // k-major bf16 form only: the rows m0.. of a row tile use k < m0 + (tile height) only, i.e. A is
   // known to be zero where k > m (the causal structure of an attention gradient)
   int causal_k = 0;

@@ -66,6 +66,7 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, i
   const int wm = wave / T::WN, wn = wave % T::WN;
   int tm, tn, bz;
   tile_of_block(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y, tiles_m, tiles_n, tm, tn, bz);
+  if (KM && op.causal_k) tm = tiles_m - 1 - tm;   // the longest k ranges of a batch member first
   const int m0 = tm * T::BM, n0 = tn * T::BN;
   const int b = bz / op.splitk, ks = bz % op.splitk;
   const int kbeg = ks * kper;
@@ -76,7 +77,7 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, i
   const int nk = kend > kbeg ? (kend - kbeg + BK - 1) / BK : 0;
 
   const uint16_t* A = (const uint16_t*)op.A + (int64_t)bi * op.sA + (int64_t)bo * op.sAo;
-  const uint16_t* B = (const uint16_t*)op.B + (int64_t)bi * op.sB + (int64_t)bo * op.sBo;
+  const uint16_t* B = (const uint16_t*)op.B + (int64_t)(bi / op.b_group) * op.sB + (int64_t)bo * op.sBo;
 
   // ---- global -> LDS, without passing through registers ---------------------------------------
   // One buffer_load_dwordx4 ... lds per wavefront moves 8 tile rows x 128 bytes (1 KB, eight whole

@@ -84,6 +84,7 @@ __global__ __launch_bounds__(T::NT) void gemm_ring_kernel(GemmOp op, int kper, i
   const int wm = wave / T::WN, wn = wave % T::WN;
   int tm, tn, bz;
   tile_of_block(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y, tiles_m, tiles_n, tm, tn, bz);
+  if (AKM && BKM && op.causal_k) tm = tiles_m - 1 - tm;   // the longest k ranges of a batch member first
   const int m0 = tm * T::BM, n0 = tn * T::BN;
   const int b = bz / op.splitk, ks = bz % op.splitk;
   const int kbeg = ks * kper;
@@ -95,7 +96,7 @@ __global__ __launch_bounds__(T::NT) void gemm_ring_kernel(GemmOp op, int kper, i
   const int nit = (klen + KST - 1) / KST;
 
   const uint16_t* A = (const uint16_t*)op.A + (int64_t)bi * op.sA + (int64_t)bo * op.sAo;
-  const uint16_t* B = (const uint16_t*)op.B + (int64_t)bi * op.sB + (int64_t)bo * op.sBo;
+  const uint16_t* B = (const uint16_t*)op.B + (int64_t)(bi / op.b_group) * op.sB + (int64_t)bo * op.sBo;
   constexpr uint32_t OOB = 0x80000000u;                  // beyond every resource: the load delivers zeros
   const rsrc_words rsA = operand_rsrc(AKM ? A + (int64_t)kbeg * op.lda + m0 : A + (int64_t)m0 * op.lda + kbeg);
   const rsrc_words rsB = operand_rsrc(BKM ? B + (int64_t)kbeg * op.ldb + n0 : B + (int64_t)n0 * op.ldb + kbeg);

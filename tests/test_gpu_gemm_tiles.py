@@ -73,6 +73,23 @@ def test_linear_at_tile_edges(T, d_in, r, d_out):
         assert float((a - 2 * b).norm() / b.norm()) < 1e-5
 
 
+# fp32: odd sizes and leading dimensions (no 16-byte loads), k tails of 1 to 3, four and sixteen wavefronts per
+# tile, a token reduction long enough to be split
+@pytest.mark.parametrize("T,d_in,r,d_out", [(33, 41, 13, 55), (1000, 999, 77, 333), (4200, 30, 9, 31), (5, 131, 130, 3)])
+def test_linear_f32_at_tile_edges(T, d_in, r, d_out):
+    print(f"linear fp32 T={T} d_in={d_in} r={r} d_out={d_out}", flush=True)
+    c = si.linear_case(T, d_in, r, d_out, dtype=torch.float32, seed=4)
+    x, wd, wu, dy = (c[k].to(DEV) for k in ("x", "w_down", "w_up", "dy"))
+    z, y = B.lr_linear_fwd(x, wd, wu)
+    dx, dwd, dwu = B.lr_linear_bwd(x, wd, wu, z, dy)
+    torch.cuda.synchronize()
+    X, WD, WU, DY = (si.f64(c[k]) for k in ("x", "w_down", "w_up", "dy"))
+    z_ref, _, y_ref = orc.lr_linear_fwd(X, WD, WU, B.LR_ACT_SILU)
+    refs = orc.lr_linear_bwd(X, WD, WU, DY, B.LR_ACT_SILU)
+    for n, got, ref in (("z", z, z_ref), ("y", y, y_ref), ("dx", dx, refs[0]), ("dw_down", dwd, refs[1]), ("dw_up", dwu, refs[2])):
+        check(n, got, ref, torch.float32)
+
+
 @pytest.mark.parametrize("accumulate,grad_dt", [(False, B.LR_F32), (True, B.LR_F32), (False, B.LR_BF16), (True, B.LR_BF16)])
 def test_block_keeps_to_the_workspace_it_asks_for(accumulate, grad_dt):
     Bn, S, H, f, r = 3, 192, 6, 2303, 120
