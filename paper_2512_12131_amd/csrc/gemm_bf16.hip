@@ -401,7 +401,8 @@ hipError_t dispatch(const GemmOp& op, hipStream_t st) {
 // 1770 measured launches (M 64 .. 16384, N 64 .. 11008, K 64 .. 11008, nine epilogue kinds, k-contiguous operands),
 // which they reproduce to 7-11 % rms; always taking the estimated best loses 1 % (geometric mean) against the
 // measured best, where the 256-row tiles alone took 1.93 times as long.  What the lines amount to, with both sides measured (us):
-//   few tiles, the loads' latency decides          777 x 1024 x 4096:   T256 68.0   R64    16.1
+//   a handful of rows: one chain of k per CU        16 x 1024 x 4096:   T256 67.6   R64    15.0   R32 9.4
+//   few tiles, the loads' latency decides          777 x 1024 x 4096:   T256 68.0   R64    16.1   R32 25.9
 //   half the CUs idle under T256                 16384 x 512 x 2048:   T256 45.6   R128   37.6
 //   N = 128 leaves T256 half its columns         16384 x 128 x 4096:   T256 72.1   R64x128 29.9
 //   short k, the epilogue decides: two resident workgroups overlap it with each other's main loop
@@ -418,6 +419,7 @@ constexpr TileCost kTileCost[] = {
     {64, 64, 256, 1.89f, 1.80f, 0.169f, 0.029f, 0.22f, 0.141f},     // GEMM_R64
     {64, 128, 512, 2.08f, 1.38f, 0.231f, 0.306f, 1.05f, 0.095f},    // GEMM_R64X128
     {128, 128, 512, 2.48f, 0.80f, 0.479f, 0.451f, 2.42f, 0.142f},   // GEMM_R128
+    {32, 32, 512, 2.00f, 1.00f, 0.095f, 0.080f, 0.30f, 0.140f},     // GEMM_R32
 };
 // bf16-output equivalents an epilogue moves (reads and writes, secondary outputs included)
 float epi_traffic(int kind) {
@@ -444,7 +446,7 @@ constexpr float kRingMargin = 1.075f;
 // What a slice costs more with two k-major operands.  The 256-row kernels pay for their transpose reads.  The ring
 // tiles read 128 or 256 bytes per k row where those read 512, which shows when the rows come from HBM (2048 x 512
 // over 16384 tokens: R64x128 in 4 splits 60 us, T256 in 16 splits 45 us plus 6 us more in the finishing pass).
-constexpr float kKMajorSlice[] = {0.f, 1.13f, 1.05f, 1.5f, 1.5f, 1.3f};
+constexpr float kKMajorSlice[] = {0.f, 1.13f, 1.05f, 1.5f, 1.5f, 1.3f, 1.5f};
 
 }  // namespace
 
@@ -471,7 +473,7 @@ int gemm_bf16_tile(const GemmOp& op) {
       tile = GEMM_T256X128;
     }
   }
-  for (int t = GEMM_R64; t <= GEMM_R128; t++) {
+  for (int t = GEMM_R64; t <= GEMM_R32; t++) {
     const float c = tile_time(t, op.M, op.N, nk, op.batch, e, km ? kKMajorSlice[t] : 1.f);
     if (c * (tile < GEMM_R64 ? kRingMargin : 1.f) < best) {
       best = c;
@@ -482,8 +484,9 @@ int gemm_bf16_tile(const GemmOp& op) {
 }
 
 RowParts gemm_bf16_rowparts(const GemmOp& op) {
-  const int tile = gemm_bf16_tile(op), bn = kTileCost[tile].bn;   // every tile has two wavefronts across
-  return RowParts{(op.N + bn - 1) / bn * 2, 256 / bn, (op.N + 127) / 128};
+  const int tile = gemm_bf16_tile(op), bn = kTileCost[tile].bn;   // two wavefronts across, but for the narrowest
+  const int wn = tile == GEMM_R32 ? 1 : 2;
+  return RowParts{(op.N + bn - 1) / bn * wn, 128 * wn / bn, (op.N + 127) / 128};
 }
 
 WgradPlan gemm_bf16_plan_wgrad(int M, int N, int K, int batch, bool direct) {
@@ -492,7 +495,7 @@ WgradPlan gemm_bf16_plan_wgrad(int M, int N, int K, int batch, bool direct) {
   const int nk = (K + BK - 1) / BK;
   WgradPlan best{GEMM_T256, 1};
   float best_t = -1.f;
-  for (int tile = GEMM_T256; tile <= GEMM_R128; tile++) {
+  for (int tile = GEMM_T256; tile <= GEMM_R32; tile++) {
     for (int s : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 24, 32, 48, 64}) {
       if (s > 1 && nk / s < (tile < GEMM_R64 ? 8 : 4)) break;
       float t = tile_time(tile, M, N, (nk + s - 1) / s, batch * s, 2.f, kKMajorSlice[tile]);
@@ -602,6 +605,7 @@ hipError_t gemm_bf16_untimed(const GemmOp& op, hipStream_t st) {
     case GEMM_R64: return gemm_ring64(op, st);
     case GEMM_R64X128: return gemm_ring64x128(op, st);
     case GEMM_R128: return gemm_ring128(op, st);
+    case GEMM_R32: return gemm_ring32(op, st);
     default: break;
   }
   if (!km) return dispatch<TileBig>(op, st);

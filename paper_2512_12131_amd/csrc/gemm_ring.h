@@ -16,7 +16,10 @@
 // 6.5 / 22, 16384 x 128 x 4096 30 / 72, 512 x 256 x 64 4.2 / 7.2.  A 64 x 64 tile takes 0.21 us per 64-wide slice: a
 // wavefront's 32 x 32 block reads 2 KB of LDS per MFMA, so the LDS port (128 B per cycle) is busy for twice the
 // matrix time, and the loads (one 1 KB load per ~17 cycles and CU) for as long again.  Reading all operands of a
-// stage before issuing the next loads took 12 % off that; 32 x 64 tiles and a ring of ten 16 KB stages were slower.
+// stage before issuing the next loads took 12 % off that; a ring of ten 16 KB stages was slower.
+// A handful of rows (16 x 1024 x 4096) leaves one chain of 256 MFMAs per 32 x 32 block, 3.4 us of matrix time in
+// the order that keeps a row's bits: there the 32 x 32 tile gives the chain a wavefront of its own and the loads
+// to four others, 0.095 us per slice (15.0 -> 9.4 us; 16 x 4096 x 1024 6.6 -> 5.5; the same split at 64 x 64: 13.3).
 //
 // Operand forms: k-contiguous (p[i*ld + k]) or k-major (p[k*ld + i]) for A and B independently; the k-major
 // side is read through the LDS transpose read, so a data-gradient product needs no transposed weight copy.
@@ -26,27 +29,31 @@
 namespace lrb {
 namespace {
 
-template <int BM_, int BN_, int WM_, int WN_, int SUB_, int NS_>
+// NL = 0: every wavefront loads its share of a stage and multiplies.  NL > 0: NL further wavefronts do nothing but
+// load, the WM x WN others nothing but multiply.
+template <int BM_, int BN_, int WM_, int WN_, int SUB_, int NS_, int NL_ = 0>
 struct RingTile {
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_;
   static constexpr int SUB = SUB_;                     // 64-wide k slices per LDS stage (one barrier per stage)
   static constexpr int NS = NS_;                       // stages in the ring
-  static constexpr int NW = WM * WN, NT = NW * 64;
+  static constexpr int NL = NL_;
+  static constexpr int NW = WM * WN, NT = (NW + NL) * 64;
+  static constexpr int NWL = NL > 0 ? NL : NW;         // wavefronts that load
   static constexpr int TM = BM / WM, TN = BN / WN;
   static constexpr int FM = TM / 32, FN = TN / 32;
   static constexpr int A_BYTES = BM * 128, B_BYTES = BN * 128, SLICE = A_BYTES + B_BYTES, STAGE = SUB * SLICE;
-  static constexpr int LA = BM / 8 / NW, LB = BN / 8 / NW;   // 1 KB wavefront loads per wavefront and slice
+  static constexpr int LA = BM / 8 / NWL, LB = BN / 8 / NWL;   // 1 KB wavefront loads per wavefront and slice
   static constexpr int LPS = (LA + LB) * SUB;                // ... and stage
   static constexpr int CS = TN + 4;                          // fp32 row stride of the epilogue staging tile
   static constexpr int EPI_BYTES = NW * 32 * CS * 4;
   static constexpr int STAT_OFF = EPI_BYTES;
   static constexpr int MAIN_BYTES = NS * STAGE;
   static constexpr int LDS_BYTES = MAIN_BYTES > EPI_BYTES + BM * 4 ? MAIN_BYTES : EPI_BYTES + BM * 4;
-  static_assert(BM / 8 % NW == 0 && BN / 8 % NW == 0 && FM >= 1 && FN >= 1, "tile / wavefront layout mismatch");
+  static_assert(BM / 8 % NWL == 0 && BN / 8 % NWL == 0 && NWL % 2 == 0 && FM >= 1 && FN >= 1, "tile / wavefront layout mismatch");
   static_assert(NS >= 2 && (NS - 2) * LPS < 64, "vmcnt is a 6-bit counter");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS of a CU");
-  // main-loop statistics: NT / BM threads share a row, each takes a 16-byte chunk run of every slice
-  static constexpr int TPR = NT / BM;
+  // main-loop statistics: TPR threads share a row, each takes a 16-byte chunk run of every slice
+  static constexpr int TPR = NT / BM < 4 ? NT / BM : 4;
   static_assert(TPR == 2 || TPR == 4, "threads per tile row");
 };
 
@@ -73,7 +80,7 @@ __device__ __forceinline__ rsrc_words operand_rsrc(const void* base) {
 // the second read of an operand (k + 4) differs from the first by a constant offset.
 template <int W>
 __device__ __forceinline__ int kmajor_swz(int k) {
-  return W >= 128 ? (k & 3) << 2 : ((k >> 1) & 1) << 2;
+  return W >= 128 ? (k & 3) << 2 : W == 64 ? ((k >> 1) & 1) << 2 : 0;
 }
 
 template <class T, int KIND, bool STAT_A, bool AKM, bool BKM>
@@ -81,7 +88,8 @@ __global__ __launch_bounds__(T::NT) void gemm_ring_kernel(GemmOp op, int kper, i
   static_assert(!(STAT_A && AKM), "row statistics are gathered from k-contiguous rows");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / T::WN, wn = wave % T::WN;
+  const int wm = wave / T::WN, wn = wave % T::WN;        // (of a multiplying wavefront)
+  const int lw = T::NL > 0 ? wave - T::NW : wave;        // index among the loading wavefronts (below 0: not one)
   int tm, tn, bz;
   tile_of_block(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y, tiles_m, tiles_n, tm, tn, bz);
   if (AKM && BKM && op.causal_k) tm = tiles_m - 1 - tm;   // the longest k ranges of a batch member first
@@ -102,26 +110,26 @@ __global__ __launch_bounds__(T::NT) void gemm_ring_kernel(GemmOp op, int kper, i
   const rsrc_words rsB = operand_rsrc(BKM ? B + (int64_t)kbeg * op.ldb + n0 : B + (int64_t)n0 * op.ldb + kbeg);
   const uint32_t sbase = (uint32_t)(uintptr_t)LRB_LDS_PTR(smem);
 
-  // A wavefront's loads of one slice of an operand: group g = wave + NW * i covers 8 rows x 128 B
+  // A wavefront's loads of one slice of an operand: group g = lw + NWL * i covers 8 rows x 128 B
   // (k-contiguous; chunk index XORed by (row / 2) % 8) or 512 / W k rows x 2 W bytes (k-major).
   uint32_t offA[T::LA], offB[T::LB];
   int kA = 0, kB = 0;        // this lane's first k inside the slice: of its chunk (k-contiguous) or its row (k-major)
   auto lane_offsets = [&](auto KM, auto Wc, auto& off, int& k_of_lane, int64_t ld, int i0, int lim) {
     constexpr bool km = decltype(KM)::value;
-    constexpr int W = decltype(Wc)::value, NL = W / 8 / T::NW;
+    constexpr int W = decltype(Wc)::value, NI = W / 8 / T::NWL;
 #pragma unroll
-    for (int i = 0; i < NL; i++) {
-      const int g = wave + T::NW * i;
+    for (int i = 0; i < NI; i++) {
+      const int g = lw + T::NWL * i;
       if constexpr (!km) {
         const int row = g * 8 + (lane >> 3);
         const int lc = (lane & 7) ^ ((row >> 1) & 7);
-        if (i == 0) k_of_lane = lc * 8;                  // the same for every i: NW * 8 rows apart, NW even
+        if (i == 0) k_of_lane = lc * 8;                  // the same for every i: NWL * 8 rows apart, NWL even
         off[i] = (i0 + row) < lim ? (uint32_t)(row * (int)ld + lc * 8) * 2u : OOB;
       } else {
         constexpr int CPR = W / 8, RPL = 64 / CPR;
         const int krow = g * RPL + lane / CPR;
         const int lc = (lane % CPR) ^ kmajor_swz<W>(krow);
-        if (i == 0) k_of_lane = krow;                    // load i: NW * RPL rows further
+        if (i == 0) k_of_lane = krow;                    // load i: NWL * RPL rows further
         off[i] = (i0 + lc * 8) < lim ? (uint32_t)(krow * (int)ld + lc * 8) * 2u : OOB;
       }
     }
@@ -140,9 +148,9 @@ __global__ __launch_bounds__(T::NT) void gemm_ring_kernel(GemmOp op, int kper, i
     constexpr int i = is_a ? j : j - T::LA, W = is_a ? T::BM : T::BN, RPL = 512 / W;
     const int k0 = it * KST + s * BK;
     const uint32_t adv = (uint32_t)k0 * (km ? (uint32_t)(is_a ? op.lda : op.ldb) : 1u) * 2u;
-    const bool in = (k0 + (is_a ? kA : kB) + (km ? i * T::NW * RPL : 0)) < klen;
+    const bool in = (k0 + (is_a ? kA : kB) + (km ? i * T::NWL * RPL : 0)) < klen;
     const uint32_t dst = sbase + (uint32_t)(slot * T::STAGE + s * T::SLICE + (is_a ? 0 : T::A_BYTES)) +
-                         (uint32_t)(wave + T::NW * i) * 1024u;
+                         (uint32_t)(lw + T::NWL * i) * 1024u;
     dma16(is_a ? rsA : rsB, dst, in ? (is_a ? offA[is_a ? i : 0] : offB[is_a ? 0 : i]) + adv : OOB);   // OOB + adv stays past the resource
   };
 
@@ -177,7 +185,8 @@ __global__ __launch_bounds__(T::NT) void gemm_ring_kernel(GemmOp op, int kper, i
   float ssq[4 / T::TPR] = {};
 
 #pragma unroll
-  for (int s = 0; s < T::NS - 1; s++) static_for<T::LPS>([&](auto I) { issue_one(s, s, I); });
+  for (int s = 0; s < T::NS - 1; s++)
+    if (lw >= 0) static_for<T::LPS>([&](auto I) { issue_one(s, s, I); });
   int rd = 0, wr = T::NS - 1;                            // slots read from and written to
   for (int it = 0; it < nit; it++) {
     // this wavefront's loads of stage `it` have landed (loads retire in order), and its reads of the stage
@@ -187,38 +196,44 @@ __global__ __launch_bounds__(T::NT) void gemm_ring_kernel(GemmOp op, int kper, i
     wait_lgkmcnt0();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    // all operand reads of the stage first, then the next stage's loads among the MFMAs: a CU accepts one 1 KB
-    // load per ~17 cycles and a wavefront issues in order, so loads in front of the reads would delay them
-    bf16x8 af[KSTEPS][T::FM], bf[KSTEPS][T::FN];
+    if constexpr (T::NL > 0) {
+      if (lw >= 0) static_for<T::LPS>([&](auto I) { issue_one(it + T::NS - 1, wr, I); });
+    }
+    if (T::NL == 0 || lw < 0) {
+      // all operand reads of the stage first, then the next stage's loads among the MFMAs: a CU accepts one 1 KB
+      // load per ~17 cycles and a wavefront issues in order, so loads in front of the reads would delay them
+      bf16x8 af[KSTEPS][T::FM], bf[KSTEPS][T::FN];
 #pragma unroll
-    for (int kk = 0; kk < KSTEPS; kk++) {
-      const unsigned char* sa = smem + rd * T::STAGE + (kk / 4) * T::SLICE;
+      for (int kk = 0; kk < KSTEPS; kk++) {
+        const unsigned char* sa = smem + rd * T::STAGE + (kk / 4) * T::SLICE;
 #pragma unroll
-      for (int i = 0; i < T::FM; i++) af[kk][i] = frag(std::integral_constant<bool, AKM>{}, WA{}, sa, wm * T::TM + i * 32, kk % 4);
+        for (int i = 0; i < T::FM; i++) af[kk][i] = frag(std::integral_constant<bool, AKM>{}, WA{}, sa, wm * T::TM + i * 32, kk % 4);
 #pragma unroll
-      for (int j = 0; j < T::FN; j++)
-        bf[kk][j] = frag(std::integral_constant<bool, BKM>{}, WB{}, sa + T::A_BYTES, wn * T::TN + j * 32, kk % 4);
+        for (int j = 0; j < T::FN; j++)
+          bf[kk][j] = frag(std::integral_constant<bool, BKM>{}, WB{}, sa + T::A_BYTES, wn * T::TN + j * 32, kk % 4);
+      }
+      asm volatile("" ::: "memory");
+      static_for<KSTEPS>([&](auto KK) {
+        constexpr int kk = decltype(KK)::value;
+        constexpr int l0 = kk * T::LPS / KSTEPS, l1 = (kk + 1) * T::LPS / KSTEPS;
+        if constexpr (T::NL == 0) static_for<l1 - l0>([&](auto L) { issue_one(it + T::NS - 1, wr, std::integral_constant<int, l0 + decltype(L)::value>{}); });
+#pragma unroll
+        for (int i = 0; i < T::FM; i++)
+#pragma unroll
+          for (int j = 0; j < T::FN; j++)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[kk][j], af[kk][i], acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      });
     }
     if constexpr (STAT_A) {
 #pragma unroll
       for (int s = 0; s < T::SUB; s++) {
+        if (tid >= T::BM * T::TPR) continue;
         const unsigned char* sr = smem + rd * T::STAGE + s * T::SLICE + (tid / T::TPR) * 128 + (tid % T::TPR) * (128 / T::TPR);
 #pragma unroll
         for (int c = 0; c < 8 / T::TPR; c++) ssq[c / 2] += sumsq8(*reinterpret_cast<const uint4*>(sr + c * 16));
       }
     }
-    asm volatile("" ::: "memory");
-    static_for<KSTEPS>([&](auto KK) {
-      constexpr int kk = decltype(KK)::value;
-      constexpr int l0 = kk * T::LPS / KSTEPS, l1 = (kk + 1) * T::LPS / KSTEPS;
-      static_for<l1 - l0>([&](auto L) { issue_one(it + T::NS - 1, wr, std::integral_constant<int, l0 + decltype(L)::value>{}); });
-#pragma unroll
-      for (int i = 0; i < T::FM; i++)
-#pragma unroll
-        for (int j = 0; j < T::FN; j++)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[kk][j], af[kk][i], acc[i][j], 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-    });
     rd = rd + 1 == T::NS ? 0 : rd + 1;
     wr = wr + 1 == T::NS ? 0 : wr + 1;
   }
@@ -230,9 +245,10 @@ __global__ __launch_bounds__(T::NT) void gemm_ring_kernel(GemmOp op, int kper, i
     if constexpr (T::TPR == 2) s += ssq[1];
     s += __shfl_xor(s, 1);
     if constexpr (T::TPR == 4) s += __shfl_xor(s, 2);
-    if (tid % T::TPR == 0) sStat[tid / T::TPR] = s;
+    if (tid < T::BM * T::TPR && tid % T::TPR == 0) sStat[tid / T::TPR] = s;
     __syncthreads();
   }
+  if (T::NL > 0 && lw >= 0) return;
   gemm_epilogue<T, KIND, STAT_A>(op, acc, smem, sStat, wave, lane, m0, n0, tn, tiles_n, b, bi, bo, bz);
 }
 
