@@ -88,7 +88,7 @@ struct GemmOp {
 // Output tiles of the bf16 kernels (gemm_bf16.hip: 256 rows, 256 or, two k-major operands only, 128 columns;
 // gemm_ring.h: the others)
 enum GemmTile : int { GEMM_TILE_AUTO = 0, GEMM_T256 = 1, GEMM_T256X128 = 2, GEMM_R64 = 3, GEMM_R64X128 = 4, GEMM_R128 = 5,
-                      GEMM_R32 = 6 };
+                      GEMM_R32 = 6, GEMM_R128W = 7 };
 
 // The tile gemm_bf16 runs `op` with (op.tile if set, else by estimated time; see gemm_bf16.hip).
 int gemm_bf16_tile(const GemmOp& op);
@@ -104,6 +104,7 @@ hipError_t gemm_ring32(const GemmOp& op, hipStream_t st);
 hipError_t gemm_ring64(const GemmOp& op, hipStream_t st);
 hipError_t gemm_ring64x128(const GemmOp& op, hipStream_t st);
 hipError_t gemm_ring128(const GemmOp& op, hipStream_t st);
+hipError_t gemm_ring128w(const GemmOp& op, hipStream_t st);   // two k-major operands, plain store
 // true when gemm_bf16 reads a k-major B operand beside a k-contiguous A in place (no transposed copy)
 bool gemm_bf16_mixed_ok(const GemmOp& op);
 hipError_t gemm_bf16(const GemmOp& op, hipStream_t st);

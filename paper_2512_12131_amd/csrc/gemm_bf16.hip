@@ -367,7 +367,7 @@ hipError_t launch(const GemmOp& op, hipStream_t st) {
 }
 
 using TileBig = Tile<256, 256, 4, 2>;   // 8 waves, 64x128 per wave
-using TileMid = Tile<256, 128, 2, 2>;   // 4 waves, 128x64 per wave (two k-major operands, N = 128)
+using TileMid = Tile<256, 128, 2, 2>;   // 4 waves, 128x64 per wave (two k-major operands)
 
 template <class T>
 hipError_t dispatch(const GemmOp& op, hipStream_t st) {
@@ -420,6 +420,7 @@ constexpr TileCost kTileCost[] = {
     {64, 128, 512, 2.08f, 1.38f, 0.231f, 0.306f, 1.05f, 0.095f},    // GEMM_R64X128
     {128, 128, 512, 2.48f, 0.80f, 0.479f, 0.451f, 2.42f, 0.142f},   // GEMM_R128
     {32, 32, 512, 2.00f, 1.00f, 0.095f, 0.080f, 0.30f, 0.140f},     // GEMM_R32
+    {128, 128, 256, 2.27f, 1.88f, 0.361f, 0.156f, 0.78f, 0.f},      // GEMM_R128W (causal products only)
 };
 // bf16-output equivalents an epilogue moves (reads and writes, secondary outputs included)
 float epi_traffic(int kind) {
@@ -446,7 +447,7 @@ constexpr float kRingMargin = 1.075f;
 // What a slice costs more with two k-major operands.  The 256-row kernels pay for their transpose reads.  The ring
 // tiles read 128 or 256 bytes per k row where those read 512, which shows when the rows come from HBM (2048 x 512
 // over 16384 tokens: R64x128 in 4 splits 60 us, T256 in 16 splits 45 us plus 6 us more in the finishing pass).
-constexpr float kKMajorSlice[] = {0.f, 1.13f, 1.05f, 1.5f, 1.5f, 1.3f, 1.5f};
+constexpr float kKMajorSlice[] = {0.f, 1.13f, 1.05f, 1.5f, 1.5f, 1.3f, 1.5f, 1.f};
 
 }  // namespace
 
@@ -459,6 +460,15 @@ int gemm_bf16_tile(const GemmOp& op) {
   if (op.splitk > 1 || op.epi.kind == EPI_PARTIAL) return GEMM_T256;   // weight gradients come with a plan
   // a k-major weight is read in place in whole 8-column chunks, within the 2 GB a buffer resource addresses
   if (op.transB && !op.transA && (op.N % 8 || op.K % 8 || (int64_t)op.K * op.ldb * 2 >= 0x7fffffffLL)) return GEMM_T256;
+  // Causal k ranges: tiles of unequal length, for which the estimate has no term.  Where the 256-row tiles give less
+  // than two rounds their longest decides, and finer ones even them out (attention backward of 4 x 4096 tokens, 4
+  // heads: 83 us on T256X128, 71 on R128W; 1 x 1024 tokens, 32 heads: 18.8 / 13.4); with more rounds the larger
+  // tile reads less (4 x 4096 tokens, 32 heads: 553 / 583).  Fewer tiles than half the CUs: as any product.
+  if (op.causal_k) {
+    const int64_t members = (int64_t)((op.N + 127) / 128) * op.batch;
+    if ((op.M + 255) / 256 * members >= 512) return GEMM_T256X128;
+    if ((op.M + 127) / 128 * members >= 128) return GEMM_R128W;
+  }
   const int nk = (op.K + BK - 1) / BK;
   const float e = epi_traffic(op.epi.kind);
   const bool km = op.transA && op.transB;
@@ -606,6 +616,7 @@ hipError_t gemm_bf16_untimed(const GemmOp& op, hipStream_t st) {
     case GEMM_R64X128: return gemm_ring64x128(op, st);
     case GEMM_R128: return gemm_ring128(op, st);
     case GEMM_R32: return gemm_ring32(op, st);
+    case GEMM_R128W: return gemm_ring128w(op, st);
     default: break;
   }
   if (!km) return dispatch<TileBig>(op, st);
