@@ -205,6 +205,7 @@ struct GrpArgs {
   const float* dres32;       // the same residual gradient as an fp32 [T, d_in] tensor (takes precedence)
   float* dx32;               // optional: dx also un-rounded, fp32 [T, d_in] (the residual of a later sum)
   void* act_out;             // optional: where sigma(z_cat) goes (else workspace)
+  const void* w_scaled;      // optional: w_down_cat with gamma already folded into its columns
   // LaX variant (identity gate): h_prev [T, G*r] is added to z_cat before the up-projections; in the
   // backward dz_next [T, G*r] is the layer above's gradient w.r.t. z_cat and dh_prev [T, G*r] receives
   // the gradient w.r.t. h_prev.  `lax` selects the variant; each pointer may still be null (= zeros / unused).
@@ -239,6 +240,15 @@ int group_runs(const GrpArgs& a, GrpRun (&run)[2]) {
   return 2;
 }
 
+// w_down_cat with gamma folded into its columns
+const void* scaled_weight(Ctx& c, const GrpArgs& a) {
+  if (a.w_scaled) return a.w_scaled;
+  const int64_t GR = (int64_t)a.G * a.r;
+  void* wg = c.take((size_t)GR * a.d_in * esize(c.dt));
+  LAUNCH(c, k_scale_cols(a.w_down_cat, a.gamma, wg, GR, a.d_in, c.dt, c.st));
+  return wg;
+}
+
 // z_cat = RMSNorm(x) . w_down_cat^T (+ sigma(z_cat) into `act`)
 void group_down_seq(Ctx& c, const GrpArgs& a, void* act) {
   const size_t es = esize(c.dt);
@@ -249,9 +259,7 @@ void group_down_seq(Ctx& c, const GrpArgs& a, void* act) {
   dn.epi.kind = EPI_DOWN; dn.epi.act = a.act; dn.epi.C2 = act; dn.epi.ldc2 = GR;
   if (a.lax) { dn.epi.kind = EPI_DOWN_LAX; dn.epi.R = a.h_prev; dn.epi.ldr = GR; }
   if (a.norm == LR_NORM_ONLINE || a.norm == LR_NORM_ONLINE_GATHER) {
-    void* wg = c.take((size_t)GR * a.d_in * es);   // w_down_cat with gamma folded into its columns
-    LAUNCH(c, k_scale_cols(a.w_down_cat, a.gamma, wg, GR, a.d_in, c.dt, c.st));
-    dn.B = wg;
+    dn.B = scaled_weight(c, a);
     dn.epi.use_rho = 1; dn.epi.inv_d = 1.f / (float)a.d_in; dn.epi.eps = a.eps;
     if (a.stat_ready) {
       dn.epi.rowa = a.stat;
@@ -377,9 +385,7 @@ void group_bwd_seq(Ctx& c, const GrpArgs& a, const void* act) {
     float* dgp = (float*)c.take((size_t)nparts * a.d_in * sizeof(float));
     wgrad(c, dp, GR, (int)GR, a.x, a.ldx, (int)a.d_in, a.T, a.dw_down_cat, a.gamma, a.w_down_cat, dgp, a.accumulate);
     LAUNCH(c, k_colsum_parts(dgp, nparts, a.d_in, a.dgamma, a.accumulate, c.gdt, c.st));
-    void* wg = c.take((size_t)GR * a.d_in * es);
-    LAUNCH(c, k_scale_cols(a.w_down_cat, a.gamma, wg, GR, a.d_in, c.dt, c.st));
-    wB = wg;
+    wB = scaled_weight(c, a);
   } else {
     wgrad(c, dp, GR, (int)GR, a.x, a.ldx, (int)a.d_in, a.T, a.dw_down_cat, nullptr, nullptr, nullptr, a.accumulate);
   }
@@ -586,10 +592,12 @@ GrpArgs group_args(const Blk& b, int G, int64_t d_out) {
   return g;
 }
 
-// rank-r activation of a layer for the backward: sigma(z), or z + h_prev in the LaX variant
-void rebuild_act(Ctx& c, const Blk& b, const void* z, const void* h_prev, void* act, int64_t n, int lax) {
-  if (lax && h_prev) LAUNCH(c, k_add2_bf16(z, h_prev, act, b.T, n, c.st));
-  else LAUNCH(c, k_act_fwd(z, n, act, n, b.T, n, lax ? (int)LR_ACT_IDENTITY : b.act, LR_BF16, c.st));
+// the down-projection weights of both norms' groups with gamma folded in: qkv [3r, d], then gate / up [2r, d]
+void* scaled_weights(Ctx& c, const Blk& b, const lr_block_params* p) {
+  void* w = c.take((size_t)5 * b.r * b.d * 2);
+  LAUNCH(c, k_scale_cols2(p->w_dn_qkv, p->gamma1, w, 3 * b.r, p->w_dn_gu, p->gamma2, (char*)w + (size_t)3 * b.r * b.d * 2, 2 * b.r,
+                          b.d, LR_BF16, c.st));
+  return w;
 }
 
 void rope_qk(Ctx& c, const Blk& b, void* qkv, int inverse) {
@@ -625,6 +633,8 @@ void block_fwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   a.z_cat = ck ? ck->z_qkv : nullptr; a.stat = ck ? ck->s1 : nullptr; a.y_stack = qkv; a.act_out = act;
   a.stat_ready = b.stat_x_ready;
   a.lax = lax; a.h_prev = lax ? lx->h_prev_qkv : nullptr;
+  const void* w_scaled = b.norm == LR_NORM_TWO_PASS ? nullptr : scaled_weights(c, b, p);
+  a.w_scaled = w_scaled;
   group_fwd_seq(c, a);
   if (b.rope_cos) rope_qk(c, b, qkv, 0);
   {
@@ -640,6 +650,7 @@ void block_fwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   m.x = h1; m.gamma = p->gamma2; m.w_down_cat = p->w_dn_gu; m.w_up_stack = p->w_up_gu;
   m.z_cat = ck ? ck->z_gu : nullptr; m.stat = ck ? ck->s2 : nullptr; m.stat_ready = 1; m.act_out = act;
   m.lax = lax; m.h_prev = lax ? lx->h_prev_gu : nullptr;
+  m.w_scaled = w_scaled ? (const char*)w_scaled + (size_t)3 * r * d * es : nullptr;
   group_down_seq(c, m, act);
   mlp_up_swiglu(c, b, p->w_up_gu, act, gg, uu, mm);
   single_down(c, b, mm, f, p->w_dn_d, ck ? ck->z_d : nullptr, act, lax, lax ? lx->h_prev_d : nullptr);
@@ -663,7 +674,8 @@ void block_bwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   if (!ck) ck = &nck;
   void* act_d = c.take((size_t)T * r * es);
   void* act_o = c.take((size_t)T * r * es);
-  void* act_g = c.take((size_t)T * 3 * r * es);   // sigma(z_gu), later sigma(z_qkv)
+  void* act_g = c.take((size_t)T * 2 * r * es);   // sigma(z_gu)
+  void* act_q = c.take((size_t)T * 3 * r * es);   // sigma(z_qkv)
   void* dz1 = c.take((size_t)T * r * es);         // dz_d, later dz_o
   void* h1 = sv ? sv->h1 : c.take((size_t)T * d * es);
   void* dh1 = c.take((size_t)T * d * es);
@@ -692,13 +704,21 @@ void block_bwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
     dout = (char*)mm + (size_t)T * d * es;
   }
 
+  // rank-r activations of all layers (z + h_prev in the LaX variant), and the weights with gamma folded in
+  {
+    const int64_t row = T * r * (int64_t)es;
+    const bool lh = lax != 0;
+    const ActLayers al{{ck->z_d, ck->z_o, ck->z_gu, ck->z_qkv},
+                       {lh ? lx->h_prev_d : nullptr, lh ? lx->h_prev_o : nullptr, lh ? lx->h_prev_gu : nullptr, lh ? lx->h_prev_qkv : nullptr},
+                       {act_d, act_o, act_g, act_q}, {row, row, 2 * row, 3 * row}, {}, 4};
+    LAUNCH(c, k_act_layers_bf16(al, lax ? (int)LR_ACT_IDENTITY : b.act, c.st));
+  }
+  const char* w_scaled = (const char*)scaled_weights(c, b, p);
+
   // ---- MLP side ----
-  rebuild_act(c, b, ck->z_d, lx->h_prev_d, act_d, r, lax);
   single_up_bwd(c, b, dy, d, act_d, ck->z_d, p->w_up_d, g->w_up_d, dz1, accumulate, lax, lx->dz_next_d, lx->dh_prev_d);
   // re-forward from the rank-r checkpoints: h1, then g, u, m
-  rebuild_act(c, b, ck->z_o, lx->h_prev_o, act_o, r, lax);
   if (!sv) single_up(c, b, act_o, p->w_up_o, d, x, h1, nullptr);
-  rebuild_act(c, b, ck->z_gu, lx->h_prev_gu, act_g, 2 * r, lax);
   GrpArgs m = group_args(b, 2, f);
   m.x = h1; m.gamma = p->gamma2; m.w_down_cat = p->w_dn_gu; m.w_up_stack = p->w_up_gu; m.y_stack = big;
   if (!sv) mlp_up_swiglu(c, b, p->w_up_gu, act_g, big, (char*)big + (size_t)T * f * es, mm);
@@ -716,15 +736,15 @@ void block_bwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   m.zc = ck->z_gu; m.statc = ck->s2; m.dy_stack = big2; m.dx = dh1; m.dx32 = dh1f; m.dres = dy; m.dgamma = g->gamma2;
   m.dw_down_cat = g->w_dn_gu; m.dw_up_stack = g->w_up_gu; m.accumulate = accumulate;
   m.lax = lax; m.dz_next = lx->dz_next_gu; m.dh_prev = lx->dh_prev_gu;
+  m.w_scaled = w_scaled ? w_scaled + (size_t)3 * r * d * es : nullptr;
   group_bwd_seq(c, m, act_g);
 
   // ---- attention side ----
   single_up_bwd(c, b, dh1, d, act_o, ck->z_o, p->w_up_o, g->w_up_o, dz1, accumulate, lax, lx->dz_next_o, lx->dh_prev_o);
   // re-forward q, k, v, o
-  rebuild_act(c, b, ck->z_qkv, lx->h_prev_qkv, act_g, 3 * r, lax);
   GrpArgs a = qkv_group_args(b);
   a.x = x; a.gamma = p->gamma1; a.w_down_cat = p->w_dn_qkv; a.w_up_stack = p->w_up_qkv; a.y_stack = qkv;
-  if (!sv) group_up_seq(c, a, act_g);
+  if (!sv) group_up_seq(c, a, act_q);
   if (!sv && b.rope_cos) rope_qk(c, b, qkv, 0);
   const void* q_ = qkv; const void* k_ = (char*)qkv + (size_t)T * d * es; const void* v_ = (char*)qkv + (size_t)T * (d + dkv) * es;
   if (!sv) {
@@ -758,7 +778,8 @@ void block_bwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   a.zc = ck->z_qkv; a.statc = ck->s1; a.dy_stack = dqkv; a.dx = dx; a.dres = dh1; a.dres32 = dh1f; a.dgamma = g->gamma1;
   a.dw_down_cat = g->w_dn_qkv; a.dw_up_stack = g->w_up_qkv; a.accumulate = accumulate;
   a.lax = lax; a.dz_next = lx->dz_next_qkv; a.dh_prev = lx->dh_prev_qkv;
-  group_bwd_seq(c, a, act_g);
+  a.w_scaled = w_scaled;
+  group_bwd_seq(c, a, act_q);
 }
 
 }  // namespace

@@ -140,8 +140,15 @@ hipError_t k_swiglu_fwd(const void* g, const void* u, void* m, int64_t ld, int64
 // cos / sin tables [S, 64] fp32; inverse = the transposed rotation
 hipError_t k_rope128_bf16(void* x, int64_t ld, const float* cos_tab, const float* sin_tab, int64_t rows, int S, int H,
                           int inverse, hipStream_t);
-// out = a + b, dense bf16 [T, n] (n a multiple of 8)
-hipError_t k_add2_bf16(const void* a, const void* b, void* out, int64_t T, int64_t n, hipStream_t);
+// a[i] = act(z[i]), or z[i] + h[i] where h[i] is given: up to four dense bf16 tensors of bytes[i] (a multiple of 16)
+struct ActLayers {
+  const void *z[4], *h[4];
+  void* a[4];
+  int64_t bytes[4];
+  int first[4];      // filled in by the launch
+  int n;
+};
+hipError_t k_act_layers_bf16(ActLayers p, int act, hipStream_t);
 hipError_t k_swiglu_bwd(const void* g, const void* u, const void* dm, void* dg, void* du, int64_t ld,
                         int64_t T, int64_t f, int dt, hipStream_t);
 // out[r, c] = in[c, r] for in[rows, cols] (ld_in) -> out[cols, rows] (ld_out)
@@ -155,6 +162,9 @@ hipError_t k_rowdot(const void* a, int64_t lda, const void* b, int64_t ldb, floa
 // wout[n, k] = w[n, k] * gamma[k]
 hipError_t k_scale_cols(const void* w, const void* gamma, void* wout, int64_t rows, int64_t cols, int dt,
                         hipStream_t);
+// the same for two matrices of equal width
+hipError_t k_scale_cols2(const void* w0, const void* gamma0, void* out0, int64_t rows0, const void* w1, const void* gamma1,
+                         void* out1, int64_t rows1, int64_t cols, int dt, hipStream_t);
 // Sum `nsplit` fp32 partials [nsplit][count] (batch-major outside) and write / accumulate into dw.
 //   dw[i] (+)= colscale[i % cols] * sum_s part[s][i]      (colscale optional)
 // With wg_for_dgamma (the un-scaled weight) also emits dgamma_part[k_wgrad_dgamma_parts()][cols] partial sums of

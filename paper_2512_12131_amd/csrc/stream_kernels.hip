@@ -398,27 +398,40 @@ __global__ __launch_bounds__(256) void act_fwd_dense_kernel(const void* z, void*
   }
 }
 
-// out = a + b: the LaX variant's rank-r activation h_i + h_{i-1}, rebuilt in the backward
+// The rank-r activations of a block's layers, rebuilt from the checkpoints in one launch (a launch per layer is
+// what a small block waits for: four of 2.4 us at 512 tokens): sigma(z), or z + h_{i-1} where the LaX variant
+// hands an h.  Workgroups [first[i], first[i + 1]) take segment i.
 template <int U>
-__global__ __launch_bounds__(256) void add2_dense_kernel(const void* a, const void* b, void* out, int64_t total_bytes) {
+__global__ __launch_bounds__(256) void act_layers_kernel(ActLayers p, int act) {
   constexpr int64_t CHUNK = 256 * U * 16;
-  const __amdgpu_buffer_rsrc_t ra = chunk_rsrc(a, total_bytes, CHUNK), rb = chunk_rsrc(b, total_bytes, CHUNK),
-                               ro = chunk_rsrc(out, total_bytes, CHUNK);
-  u32x4_t aq[U], bq[U];
+  int i = 0;
+  while (i + 1 < p.n && (int)blockIdx.x >= p.first[i + 1]) i++;
+  const int64_t start = (int64_t)((int)blockIdx.x - p.first[i]) * CHUNK, left = p.bytes[i] - start;
+  const uint32_t size = (uint32_t)(left < CHUNK ? left : CHUNK);
+  auto rsrc = [&](const void* q) { return __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)q + start), 0, size, 0x00020000); };
+  const __amdgpu_buffer_rsrc_t rz = rsrc(p.z[i]), ra = rsrc(p.a[i]);
+  u32x4_t q[U], hq[U];
 #pragma unroll
-  for (int j = 0; j < U; j++) {
-    const int off = (j * 256 + (int)threadIdx.x) * 16;
-    aq[j] = __builtin_amdgcn_raw_buffer_load_b128(ra, off, 0, NT_POLICY);
-    bq[j] = __builtin_amdgcn_raw_buffer_load_b128(rb, off, 0, NT_POLICY);
+  for (int j = 0; j < U; j++) q[j] = __builtin_amdgcn_raw_buffer_load_b128(rz, (j * 256 + (int)threadIdx.x) * 16, 0, NT_POLICY);
+  const bool add = p.h[i] != nullptr;
+  if (add) {
+    const __amdgpu_buffer_rsrc_t rh = rsrc(p.h[i]);
+#pragma unroll
+    for (int j = 0; j < U; j++) hq[j] = __builtin_amdgcn_raw_buffer_load_b128(rh, (j * 256 + (int)threadIdx.x) * 16, 0, NT_POLICY);
   }
 #pragma unroll
   for (int j = 0; j < U; j++) {
-    float av[8], bv[8];
-    unpack8v(aq[j], av);
-    unpack8v(bq[j], bv);
+    float v[8], h[8];
+    unpack8v(q[j], v);
+    if (add) {
+      unpack8v(hq[j], h);
 #pragma unroll
-    for (int k = 0; k < 8; k++) av[k] += bv[k];
-    __builtin_amdgcn_raw_buffer_store_b128(pack8v(av), ro, (j * 256 + (int)threadIdx.x) * 16, 0, NT_POLICY);
+      for (int k = 0; k < 8; k++) v[k] += h[k];
+    } else {
+#pragma unroll
+      for (int k = 0; k < 8; k++) v[k] = act_f(v[k], act);
+    }
+    __builtin_amdgcn_raw_buffer_store_b128(pack8v(v), ra, (j * 256 + (int)threadIdx.x) * 16, 0, NT_POLICY);
   }
 }
 
@@ -611,20 +624,23 @@ __global__ __launch_bounds__(256) void rowdot_kernel(const void* a, int64_t lda,
   if (lane == 0) out[row] = s;
 }
 
+// One or two matrices of equal width (rows1 = 0: one): a block folds both of its norms' gammas in one launch.
 template <int DT>
-__global__ __launch_bounds__(256) void scale_cols_kernel(const void* w, const void* gamma, void* wout, int64_t rows,
-                                                         int64_t cols) {
+__global__ __launch_bounds__(256) void scale_cols_kernel(const void* w0, const void* gamma0, void* out0, int64_t rows0, const void* w1,
+                                                         const void* gamma1, void* out1, int64_t rows1, int64_t cols) {
   using S = St<DT>;
   using IO = VecIO<typename S::T, S::NV>;
-  const int64_t cpr = cols / S::NV, total = rows * cpr;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
+  const int64_t cpr = cols / S::NV, total0 = rows0 * cpr, total = total0 + rows1 * cpr;
+  for (int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x; j < total; j += (int64_t)gridDim.x * 256) {
+    const bool second = j >= total0;
+    const int64_t i = second ? j - total0 : j;
     const int64_t c = (i % cpr) * S::NV, off = (i / cpr) * cols + c;
     float wv[S::NV], gv[S::NV];
-    IO::load(w, off, wv);
-    IO::load(gamma, c, gv);
+    IO::load(second ? w1 : w0, off, wv);
+    IO::load(second ? gamma1 : gamma0, c, gv);
 #pragma unroll
     for (int k = 0; k < S::NV; k++) wv[k] *= gv[k];
-    IO::store(wout, off, wv);
+    IO::store(second ? out1 : out0, off, wv);
   }
 }
 
@@ -827,10 +843,14 @@ hipError_t k_rope128_bf16(void* x, int64_t ld, const float* cos_tab, const float
                      sin_tab, rows, S, H, inverse ? -1.f : 1.f);
   return hipGetLastError();
 }
-hipError_t k_add2_bf16(const void* a, const void* b, void* out, int64_t T, int64_t n, hipStream_t st) {
-  if (T <= 0 || n <= 0) return hipSuccess;
-  const int64_t bytes = T * n * 2;
-  hipLaunchKernelGGL(add2_dense_kernel<DENSE_U>, dim3(grid_chunks(bytes / 16, 256 * DENSE_U)), dim3(256), 0, st, a, b, out, bytes);
+hipError_t k_act_layers_bf16(ActLayers p, int act, hipStream_t st) {
+  unsigned grid = 0;
+  for (int i = 0; i < p.n; i++) {
+    p.first[i] = (int)grid;
+    grid += grid_chunks(p.bytes[i] / 16, 256 * DENSE_U);
+  }
+  if (grid == 0) return hipSuccess;
+  hipLaunchKernelGGL(act_layers_kernel<DENSE_U>, dim3(grid), dim3(256), 0, st, p, act);
   return hipGetLastError();
 }
 hipError_t k_swiglu_fwd(const void* g, const void* u, void* m, int64_t ld, int64_t T, int64_t f, int dt,
@@ -886,9 +906,14 @@ hipError_t k_rowdot(const void* a, int64_t lda, const void* b, int64_t ldb, floa
 }
 hipError_t k_scale_cols(const void* w, const void* gamma, void* wout, int64_t rows, int64_t cols, int dt,
                         hipStream_t st) {
-  if (rows <= 0 || cols <= 0) return hipSuccess;
+  return k_scale_cols2(w, gamma, wout, rows, nullptr, nullptr, nullptr, 0, cols, dt, st);
+}
+hipError_t k_scale_cols2(const void* w0, const void* gamma0, void* out0, int64_t rows0, const void* w1, const void* gamma1,
+                         void* out1, int64_t rows1, int64_t cols, int dt, hipStream_t st) {
+  if (rows0 + rows1 <= 0 || cols <= 0) return hipSuccess;
   const int nv = dt == LR_BF16 ? 8 : 1;
-  DISPATCH_DT(dt, scale_cols_kernel, dim3(grid1d(rows * (cols / nv))), dim3(256), st, w, gamma, wout, rows, cols);
+  DISPATCH_DT(dt, scale_cols_kernel, dim3(grid1d((rows0 + rows1) * (cols / nv))), dim3(256), st, w0, gamma0, out0, rows0, w1, gamma1,
+              out1, rows1, cols);
 }
 int64_t k_wgrad_dgamma_parts(int64_t rows, int64_t cols, int dt) {
   const int rb = wf_row_block(rows, cols, dt);
