@@ -605,8 +605,9 @@ void rope_qk(Ctx& c, const Blk& b, void* qkv, int inverse) {
     LAUNCH(c, k_rope128_bf16(qkv, b.d, b.rope_cos, b.rope_sin, 2 * b.T, (int)b.S, (int)b.H, inverse, c.st));
     return;
   }
-  LAUNCH(c, k_rope128_pair_bf16(qkv, b.d, (int)b.H, (char*)qkv + (size_t)b.T * b.d * 2, b.dkv, (int)b.Hkv, b.rope_cos, b.rope_sin,
-                                b.T, (int)b.S, inverse, c.st));
+  LAUNCH(c, k_rope128_bf16(qkv, b.d, b.rope_cos, b.rope_sin, b.T, (int)b.S, (int)b.H, inverse, c.st));
+  LAUNCH(c, k_rope128_bf16((char*)qkv + (size_t)b.T * b.d * 2, b.dkv, b.rope_cos, b.rope_sin, b.T, (int)b.S, (int)b.Hkv,
+                           inverse, c.st));
 }
 
 // sv: optional; the wide activations then land in the caller's buffers (to be kept for a backward that

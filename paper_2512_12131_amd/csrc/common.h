@@ -140,9 +140,6 @@ hipError_t k_swiglu_fwd(const void* g, const void* u, void* m, int64_t ld, int64
 // cos / sin tables [S, 64] fp32; inverse = the transposed rotation
 hipError_t k_rope128_bf16(void* x, int64_t ld, const float* cos_tab, const float* sin_tab, int64_t rows, int S, int H,
                           int inverse, hipStream_t);
-// the same for two tensors of equal rows, H0 and H1 heads
-hipError_t k_rope128_pair_bf16(void* x0, int64_t ld0, int H0, void* x1, int64_t ld1, int H1, const float* cos_tab,
-                               const float* sin_tab, int64_t rows, int S, int inverse, hipStream_t);
 // a[i] = act(z[i]), or z[i] + h[i] where h[i] is given: up to four dense bf16 tensors of bytes[i] (a multiple of 16)
 struct ActLayers {
   const void *z[4], *h[4];

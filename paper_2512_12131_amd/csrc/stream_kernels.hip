@@ -494,12 +494,9 @@ __global__ __launch_bounds__(256) void swiglu_bwd_dense_kernel(const void* g, co
 // x[rows, ld], head h in columns 128 h ..; the pair (v[i], v[i + 64]) of the row at position p = row % S
 // is turned by the angle whose cosine and sine the caller tabulated as cs[p, i], sn[p, i] ([S, 64] fp32).
 // One lane owns 8 consecutive i of one head: two 16-byte loads, two 16-byte stores.  sgn = -1 applies the
-// transpose (the backward of the rotation).  x1 (H1 heads, rows of ld1; H1 = 0: none) takes the heads past H: the
-// narrower keys beside the queries in the same launch.
-__global__ __launch_bounds__(256) void rope128_kernel(uint16_t* x, int64_t ld, uint16_t* x1, int64_t ld1,
-                                                      const float* __restrict__ cs, const float* __restrict__ sn,
-                                                      int64_t rows, int S, int H0, int H1, float sgn) {
-  const int H = H0 + H1;
+// transpose (the backward of the rotation).
+__global__ __launch_bounds__(256) void rope128_kernel(uint16_t* x, int64_t ld, const float* __restrict__ cs,
+                                                      const float* __restrict__ sn, int64_t rows, int S, int H, float sgn) {
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (idx >= rows * H * 8) return;
   const int c8 = (int)(idx & 7) * 8;
@@ -507,7 +504,7 @@ __global__ __launch_bounds__(256) void rope128_kernel(uint16_t* x, int64_t ld, u
   const int h = (int)(rh % H);
   const int64_t row = rh / H;
   const int p = (int)(row % S);
-  uint16_t* ptr = (h < H0 ? x + row * ld + (int64_t)h * 128 : x1 + row * ld1 + (int64_t)(h - H0) * 128) + c8;
+  uint16_t* ptr = x + row * ld + (int64_t)h * 128 + c8;
   float lo[8], hi[8], c[8], s[8];
   unpack8(*reinterpret_cast<const uint4*>(ptr), lo);
   unpack8(*reinterpret_cast<const uint4*>(ptr + 64), hi);
@@ -840,14 +837,10 @@ hipError_t k_act_fwd(const void* z, int64_t ldz, void* a, int64_t lda, int64_t T
 }
 hipError_t k_rope128_bf16(void* x, int64_t ld, const float* cos_tab, const float* sin_tab, int64_t rows, int S, int H,
                           int inverse, hipStream_t st) {
-  return k_rope128_pair_bf16(x, ld, H, nullptr, 0, 0, cos_tab, sin_tab, rows, S, inverse, st);
-}
-hipError_t k_rope128_pair_bf16(void* x0, int64_t ld0, int H0, void* x1, int64_t ld1, int H1, const float* cos_tab,
-                               const float* sin_tab, int64_t rows, int S, int inverse, hipStream_t st) {
-  if (rows <= 0 || H0 + H1 <= 0) return hipSuccess;
-  const int64_t items = rows * (H0 + H1) * 8;
-  hipLaunchKernelGGL(rope128_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, (uint16_t*)x0, ld0, (uint16_t*)x1,
-                     ld1, cos_tab, sin_tab, rows, S, H0, H1, inverse ? -1.f : 1.f);
+  if (rows <= 0 || H <= 0) return hipSuccess;
+  const int64_t items = rows * H * 8;
+  hipLaunchKernelGGL(rope128_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, (uint16_t*)x, ld, cos_tab,
+                     sin_tab, rows, S, H, inverse ? -1.f : 1.f);
   return hipGetLastError();
 }
 hipError_t k_act_layers_bf16(ActLayers p, int act, hipStream_t st) {
