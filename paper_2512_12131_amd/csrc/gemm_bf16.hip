@@ -597,11 +597,10 @@ hipError_t gemm_bf16(const GemmOp& op, hipStream_t st) {
 }
 
 bool gemm_bf16_kmajor_ok(const GemmOp& op) {
-  // both operands k-major, offsets within the 2 GB a buffer resource addresses.  M need not be a multiple of 8
-  // (rows of A then run on into the padding of its leading dimension); N, the vector width of the stores, does.
+  // both operands k-major, whole 8-column chunks, offsets within the 2 GB a buffer resource addresses
   const bool wgrad = op.epi.kind == EPI_PARTIAL;
   const bool plain = op.splitk == 1 && op.epi.kind == EPI_STORE;
-  return op.transA && op.transB && (wgrad || plain) && op.lda % 8 == 0 && op.N % 8 == 0 && op.lda >= (op.M + 7) / 8 * 8 &&
+  return op.transA && op.transB && (wgrad || plain) && op.M % 8 == 0 && op.N % 8 == 0 &&
          (int64_t)op.K * op.lda * 2 < 0x7fffffffLL && (int64_t)op.K * op.ldb * 2 < 0x7fffffffLL;
 }
 
