@@ -8,7 +8,7 @@
 // tile does, which is why that one keeps the launches that fill the chip (gemm_bf16_route).
 //
 // Every output element is summed by the same MFMA instruction in the same k order, and from the same k slots,
-// as in the 256-row kernel's k-contiguous form: which of the two kernels runs a product does not change its
+// as in the 256-row kernel: which of the two kernels runs a product does not change its
 // bits, so a token's result does not depend on how many tokens share the call.  The row statistics keep to that
 // too: k_rowsum_parts adds the narrower row partials of these tiles up in the order a 128-column wavefront does.
 //
@@ -162,13 +162,17 @@ __global__ __launch_bounds__(T::NT) void gemm_ring_kernel(GemmOp op, int kper, i
     if constexpr (!km) {
       return *reinterpret_cast<const bf16x8*>(base + (r0 + frow) * 128 + (((kk * 2 + fhalf) ^ fsw) << 4));
     } else {
-      // inside 16 lanes, lane s supplies the address of 4 columns of k row s / 4 and receives column s
+      // Inside 16 lanes, lane s supplies the address of 4 columns of k row s / 4 and receives column s.  Beside a
+      // k-contiguous operand the lane's slots are its half's 8 consecutive k.  With two k-major operands they are
+      // the two runs of four of the 256-row kernel's k-major form (k = (e / 4) * 8 + half * 4 + e % 4): the order of
+      // the sum, and so the bits of the attention's query gradient, must not depend on which of the two runs.
+      constexpr bool both = AKM && BKM;
       const int g = lane >> 4, s = lane & 15;
-      const int krow = fhalf * 8 + (s >> 2);
+      const int krow = fhalf * (both ? 4 : 8) + (s >> 2);
       const int col = r0 + (g & 1) * 16 + (s & 3) * 4;
       const unsigned char* p = base + (kk * 16 + krow) * (2 * W) + (((col >> 3) ^ kmajor_swz<W>(krow)) << 4) + (col & 7) * 2;
       const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p));
-      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p + 4 * 2 * W));
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p + (both ? 8 : 4) * 2 * W));
       const s16x8 r = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
       return __builtin_bit_cast(bf16x8, r);
     }

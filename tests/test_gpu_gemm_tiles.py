@@ -31,6 +31,22 @@ def test_rows_do_not_depend_on_the_tile(norm):
         assert norm == B.LR_NORM_NONE or torch.equal(s1, s[:t])
 
 
+def test_query_gradient_does_not_depend_on_the_tile():
+    # 16, 4 and 1 sequences of 512 tokens, 16 heads: three tiles of the dQ product
+    S, H = 512, 16
+    g = torch.Generator(device=DEV).manual_seed(5)
+    q, k, v, do = (torch.randn((16 * S, H * 128), generator=g, device=DEV).bfloat16() for _ in range(4))
+    o, lse = B.lr_attention_fwd(q, k, v, 16, S, H, 128)
+    full = B.lr_attention_bwd(q, k, v, o, do, lse, 16, S, H, 128)
+    for n in (4, 1):
+        print(f"dQ of {n} sequences", flush=True)
+        t = n * S
+        part = B.lr_attention_bwd(q[:t], k[:t], v[:t], o[:t], do[:t], lse[:n].contiguous(), n, S, H, 128)
+        torch.cuda.synchronize()
+        for a, b in zip(part, full):
+            assert torch.equal(a, b[:t])
+
+
 # one tile exactly, one row / column chunk more, remainders in every dimension, k shorter than a slice, several
 # splits of the token reduction, wide and narrow outputs
 EDGES = [(64, 64, 64, 64), (65, 72, 8, 136), (129, 264, 120, 520), (255, 1032, 200, 328), (2, 2048, 64, 2048),
