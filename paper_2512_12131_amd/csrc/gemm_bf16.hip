@@ -248,15 +248,15 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, i
       for (int j = 0; j < T::FN; j++)
         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[buf][j], af[buf][i], acc[i][j], 0, 0, 0);
   };
-  // STAT_A: thread t accumulates the sum of squares of tile row t from the LDS copy, one sum per 32 bytes of the
-  // 128-byte slice rows (the ring kernels share a row among threads at that grain: same order, same bits)
-  float ssq[4] = {0.f, 0.f, 0.f, 0.f};
+  // STAT_A: thread t accumulates the sum of squares of tile row t from the LDS copy, chunk by chunk as they lie there
+  // (the ring kernels share a row among threads and add its chunks up in this order)
+  float ssq = 0.f;
   auto stat_row = [&](int kt, int half) {
     if constexpr (STAT_A) {
       if (tid < T::BM) {
         const unsigned char* sr = a_slot(kt) + tid * 128 + half * 64;
 #pragma unroll
-        for (int c = 0; c < 4; c++) ssq[half * 2 + c / 2] += sumsq8(*reinterpret_cast<const uint4*>(sr + c * 16));
+        for (int c = 0; c < 4; c++) ssq += sumsq8(*reinterpret_cast<const uint4*>(sr + c * 16));
       }
     }
   };
@@ -343,7 +343,7 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, i
   // ---- per-row sum of squares gathered from the A slices ---------------------------------------
   __syncthreads();  // main-loop LDS is dead from here on
   if constexpr (STAT_A) {
-    if (tid < T::BM) sStat[tid] = (ssq[0] + ssq[1]) + (ssq[2] + ssq[3]);
+    if (tid < T::BM) sStat[tid] = ssq;
     __syncthreads();
   }
   gemm_epilogue<T, KIND, STAT_A>(op, acc, smem, sStat, wave, lane, m0, n0, tn, tiles_n, b, bi, bo, bz);

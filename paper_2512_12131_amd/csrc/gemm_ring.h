@@ -52,7 +52,7 @@ struct RingTile {
   static_assert(BM / 8 % NWL == 0 && BN / 8 % NWL == 0 && NWL % 2 == 0 && FM >= 1 && FN >= 1, "tile / wavefront layout mismatch");
   static_assert(NS >= 2 && (NS - 2) * LPS < 64, "vmcnt is a 6-bit counter");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS of a CU");
-  // main-loop statistics: TPR threads share a row, each takes a 16-byte chunk run of every slice
+  // main-loop statistics: TPR threads (of one quad of lanes) share a row, each takes 8 / TPR chunks of every slice
   static constexpr int TPR = NT / BM < 4 ? NT / BM : 4;
   static_assert(TPR == 2 || TPR == 4, "threads per tile row");
 };
@@ -185,8 +185,7 @@ __global__ __launch_bounds__(T::NT) void gemm_ring_kernel(GemmOp op, int kper, i
     for (int j = 0; j < T::FN; j++)
 #pragma unroll
       for (int v = 0; v < 16; v++) acc[i][j][v] = 0.f;
-  // STAT_A: sums of squares of tile row tid / TPR, one per 32 bytes of the slice rows, 4 / TPR of them per thread
-  float ssq[4 / T::TPR] = {};
+  float ssq = 0.f;           // STAT_A: sum of squares of tile row tid / TPR, the same in its TPR threads
 
 #pragma unroll
   for (int s = 0; s < T::NS - 1; s++)
@@ -230,12 +229,21 @@ __global__ __launch_bounds__(T::NT) void gemm_ring_kernel(GemmOp op, int kper, i
       });
     }
     if constexpr (STAT_A) {
+      // Each of a row's threads squares its 8 / TPR chunks of a slice; all of them then add the eight chunk sums in the
+      // order they lie in LDS, as the one thread per row of the 256-row kernel does: same bits whichever tile runs.
+      constexpr int CPT = 8 / T::TPR;
 #pragma unroll
       for (int s = 0; s < T::SUB; s++) {
         if (tid >= T::BM * T::TPR) continue;
-        const unsigned char* sr = smem + rd * T::STAGE + s * T::SLICE + (tid / T::TPR) * 128 + (tid % T::TPR) * (128 / T::TPR);
+        const unsigned char* sr = smem + rd * T::STAGE + s * T::SLICE + (tid / T::TPR) * 128 + (tid % T::TPR) * (CPT * 16);
+        float cs[CPT];
 #pragma unroll
-        for (int c = 0; c < 8 / T::TPR; c++) ssq[c / 2] += sumsq8(*reinterpret_cast<const uint4*>(sr + c * 16));
+        for (int c = 0; c < CPT; c++) cs[c] = sumsq8(*reinterpret_cast<const uint4*>(sr + c * 16));
+        static_for<8>([&](auto C) {
+          constexpr int j = decltype(C)::value / CPT;    // the thread of the row that holds this chunk
+          constexpr int ctrl = T::TPR == 4 ? j * 0x55 : j == 0 ? 0xA0 : 0xF5;   // quad_perm [j,j,j,j] / [j,j,2+j,2+j]
+          ssq += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(cs[decltype(C)::value % CPT]), ctrl, 0xf, 0xf, false));
+        });
       }
     }
     rd = rd + 1 == T::NS ? 0 : rd + 1;
@@ -245,11 +253,7 @@ __global__ __launch_bounds__(T::NT) void gemm_ring_kernel(GemmOp op, int kper, i
   __syncthreads();           // the ring is dead from here on
   float* sStat = reinterpret_cast<float*>(smem + T::STAT_OFF);
   if constexpr (STAT_A) {
-    float s = ssq[0];
-    if constexpr (T::TPR == 2) s += ssq[1];
-    s += __shfl_xor(s, 1);
-    if constexpr (T::TPR == 4) s += __shfl_xor(s, 2);
-    if (tid < T::BM * T::TPR && tid % T::TPR == 0) sStat[tid / T::TPR] = s;
+    if (tid < T::BM * T::TPR && tid % T::TPR == 0) sStat[tid / T::TPR] = ssq;
     __syncthreads();
   }
   if (T::NL > 0 && lw >= 0) return;

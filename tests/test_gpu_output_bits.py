@@ -1,0 +1,118 @@
+"""Which output tile runs a product, how its workgroups share k and how partial sums are folded are choices of speed: none
+of them may show in a result.  The orders in which the fp32 sums of the bf16 path are added are therefore fixed, and the
+bits that follow from them are pinned here for calls whose sizes reach the different folds (CRC-32 of every output, in
+tests/golden/output_bits.txt, recorded when every product ran on 256-row tiles)."""
+import os
+import zlib
+
+import pytest
+import torch
+
+import synth_inputs as si
+from paper_2512_12131_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+EPS = 1e-5
+GOLDEN = os.path.join(os.path.dirname(__file__), "golden", "output_bits.txt")
+
+# group: members' width and rank on either side of the column folds (ranks up to 128 and 256 < rank <= 512 that are no
+# multiple of 256 fold 64 columns at a time, the others 128), token counts that split the token reduction or not.
+# block: the same through the residual sums (width 256, 384, 640), grouped heads, the LaX form, both gradient types.
+CASES = {
+    "group_r72": dict(kind="group", T=1031, d=264, r=72, n=264, G=3, norm=B.LR_NORM_ONLINE, grad=B.LR_F32),
+    "group_r152": dict(kind="group", T=700, d=600, r=152, n=600, G=2, norm=B.LR_NORM_TWO_PASS, grad=B.LR_BF16),
+    "group_r512": dict(kind="group", T=2500, d=512, r=512, n=1032, G=2, norm=B.LR_NORM_ONLINE, grad=B.LR_F32),
+    "group_r536": dict(kind="group", T=300, d=1024, r=536, n=768, G=2, norm=B.LR_NORM_ONLINE_GATHER, grad=B.LR_F32),
+    "linear": dict(kind="linear", T=3000, d=1024, r=256, n=768),
+    "block_d256": dict(kind="block", Bn=2, S=256, H=2, Hkv=2, f=344, r=64, grad=B.LR_F32, lax=False),
+    "block_d384": dict(kind="block", Bn=2, S=1100, H=3, Hkv=1, f=1003, r=152, grad=B.LR_BF16, lax=False),
+    "block_d640": dict(kind="block", Bn=1, S=700, H=5, Hkv=5, f=1720, r=200, grad=B.LR_F32, lax=True),
+}
+
+
+def outputs(c):
+    if c["kind"] == "linear":
+        k = si.linear_case(c["T"], c["d"], c["r"], c["n"], dtype=torch.bfloat16, seed=11)
+        x, wd, wu, dy = (k[n].to(DEV) for n in ("x", "w_down", "w_up", "dy"))
+        z, y = B.lr_linear_fwd(x, wd, wu)
+        dx, dwd, dwu = B.lr_linear_bwd(x, wd, wu, z, dy)
+        return {"z": z, "y": y, "dx": dx, "dw_down": dwd, "dw_up": dwu}
+    if c["kind"] == "group":
+        k = si.group_case(c["T"], c["d"], c["r"], c["n"], c["G"], seed=12)
+        wd, wu = (t.to(DEV) for t in si.pack_group(k))
+        x, gamma, dy = k["x"].to(DEV), k["gamma"].to(DEV), torch.stack(k["dy"]).to(DEV)
+        z, stat, y = B.lr_group_fwd(x, gamma, EPS, c["norm"], wd, wu)
+        dx, dgamma, dwd, dwu = B.lr_group_bwd(x, gamma, EPS, c["norm"], wd, wu, z, stat, dy, grad_dt=c["grad"])
+        return {"z": z, "stat": stat, "y": y, "dx": dx, "dgamma": dgamma, "dw_down": dwd, "dw_up": dwu}
+    Bn, S, H, f, r = c["Bn"], c["S"], c["H"], c["f"], c["r"]
+    d, f_ld, T = 128 * H, si.pad_ld(f, 8), Bn * S
+    case = si.block_case(Bn, S, d, H, 128, f, r, seed=13, Hkv=c["Hkv"])
+    stat_y = torch.empty((T,), dtype=torch.float32, device=DEV)
+    desc = B.make_block_desc(Bn, S, d, H, 128, f, f_ld, r, eps=EPS, grad_dt=c["grad"], n_kv_heads=c["Hkv"], stat_y_out=stat_y,
+                             act=B.LR_ACT_IDENTITY if c["lax"] else B.LR_ACT_SILU)
+    p = {k: v.to(DEV) for k, v in si.pack_block_params(case["params"], f, f_ld).items()}
+    x, dy = case["x"].to(DEV), case["dy"].to(DEV)
+    if c["lax"]:
+        wide = {"qkv": 3, "o": 1, "gu": 2, "d": 1}
+        h, dz = ({n: si.gaussian(13, t + n, (T, w * r), std=0.5, dtype=torch.bfloat16).to(DEV) for n, w in wide.items()}
+                 for t in ("h_prev", "dz_next"))
+        y, ck = B.lr_block_lax_fwd(desc, p, x, h_prev=h)
+        dx, grads, dh = B.lr_block_lax_bwd(desc, p, x, dy, ck, h_prev=h, dz_next=dz)
+    else:
+        y, ck = B.lr_block_fwd(desc, p, x)
+        dx, grads = B.lr_block_bwd(desc, p, x, dy, ck)
+        dh = {}
+    return {"y": y, "stat_y": stat_y, "dx": dx, **{"ck." + n: t for n, t in ck.items()},
+            **{"grad." + n: t for n, t in grads.items()}, **{"dh." + n: t for n, t in dh.items()}}
+
+
+def crc(t):
+    return zlib.crc32(t.detach().contiguous().view(torch.uint8).cpu().numpy().tobytes())
+
+
+def pinned():
+    with open(GOLDEN) as fh:
+        rows = [ln.split("#", 1)[0].split() for ln in fh]
+    return {(r[0], r[1]): int(r[2], 16) for r in rows if r}
+
+
+@pytest.mark.parametrize("name", sorted({case for case, _ in pinned()}))
+def test_outputs_keep_their_bits(name):
+    print(f"output bits of {name}: {CASES[name]}", flush=True)
+    want = {out: v for (case, out), v in pinned().items() if case == name}
+    got = outputs(CASES[name])
+    torch.cuda.synchronize()
+    off = [out for out, v in want.items() if crc(got[out]) != v]
+    assert not off, f"{name}: other bits in {', '.join(off)}"
+
+
+def _stat_in_order(x):
+    """Sum of squares of each row of x [T, d] in the order of the gathered norm statistic: along 64-wide slices, inside a
+    slice eight chunks of 8 values in the order in which the slice's row lies in LDS (chunk c of row t holds columns
+    8 (c ^ (t / 2) % 8) ..), each chunk summed from its first value on.  A square of a bf16 value is exact in fp32."""
+    T, d = x.shape
+    x = torch.nn.functional.pad(x.float(), (0, -d % 64)).view(T, -1, 8, 8)
+    chunk = torch.zeros(x.shape[:3], device=x.device)
+    for i in range(8):
+        chunk = chunk + x[..., i] * x[..., i]
+    t = torch.arange(T, device=x.device)
+    s = torch.zeros(T, device=x.device)
+    for sl in range(x.shape[1]):
+        for c in range(8):
+            s = s + chunk[t, sl, c ^ ((t >> 1) & 7)]
+    return s
+
+
+# one row to several row tiles on each of the tiles a gathering product can run on: 32, 64, 64 x 128, 128 and 256 rows
+@pytest.mark.parametrize("T,d,r,G", [(1, 72, 8, 1), (33, 1024, 128, 3), (777, 1032, 64, 2), (3000, 512, 168, 3), (16384, 256, 128, 1),
+                                     (16383, 2048, 256, 2)])
+def test_gathered_statistic_is_added_in_one_order(T, d, r, G):
+    print(f"gathered statistic T={T} d={d} r={r} G={G}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(9)
+    x = torch.randn((T, d), generator=g, device=DEV).bfloat16()
+    wd = (torch.randn((G * r, d), generator=g, device=DEV) * d ** -0.5).bfloat16()
+    wu = torch.randn((G, 8, r), generator=g, device=DEV).bfloat16()
+    _, stat, _ = B.lr_group_fwd(x, torch.ones((d,), device=DEV).bfloat16(), EPS, B.LR_NORM_ONLINE_GATHER, wd, wu)
+    torch.cuda.synchronize()
+    assert torch.equal(stat, _stat_in_order(x))
