@@ -363,7 +363,7 @@ void group_bwd_seq(Ctx& c, const GrpArgs& a, const void* act) {
       }
     }
   }
-  if (c.dry && rp.slabs) rp.slabs = (int)((a.r + 63) / 64 * 2);   // size query: the narrowest tile's partials
+  if (c.dry && rp.slabs) rp.slabs = gemm_bf16_rowpart_slabs_max((int)a.r);   // (it does not know the epilogue)
   const int nparts = rp.slabs * a.G;
   float* parts = nparts ? (float*)c.take((size_t)a.T * nparts * sizeof(float)) : nullptr;
   for (int i = 0; i < nrun; i++) {
@@ -528,7 +528,7 @@ void single_up(Ctx& c, const Blk& b, const void* act, const void* w_up, int64_t 
   else if (out32) { up.epi.kind = EPI_UP_O32; up.epi.C32 = out32; up.epi.ldc32 = N; }
   if (sumsq || c.dry) {
     RowParts rp = gemm_bf16_rowparts(up);
-    if (c.dry) rp.slabs = (int)((N + 63) / 64 * 2);   // size query: the narrowest tile's partials
+    if (c.dry) rp.slabs = gemm_bf16_rowpart_slabs_max((int)N);   // (it does not know the epilogue)
     float* parts = (float*)c.take((size_t)b.T * rp.slabs * sizeof(float));
     up.epi.rowpart = parts; up.epi.rowpart_ld = rp.slabs;
     gemm(c, up);

@@ -93,9 +93,12 @@ enum GemmTile : int { GEMM_TILE_AUTO = 0, GEMM_T256 = 1, GEMM_T256X128 = 2, GEMM
 // The tile gemm_bf16 runs `op` with (op.tile if set, else by estimated time; see gemm_bf16.hip).
 int gemm_bf16_tile(const GemmOp& op);
 // Row partials the bf16 kernel emits with `op`, per batch member: `slabs` columns (rowpart_ld must be >= slabs *
-// batch), each the sum over 128 / per128 output columns; n128 = 128-column groups that hold any.
-struct RowParts { int slabs, per128, n128; };
+// batch), each the sum over 64 or 32 output columns.  A row's sum is formed from `units` runs of `per_unit` consecutive
+// partials: what a unit is depends on op.N alone, not on the tile.
+struct RowParts { int slabs, per_unit, units; };
 RowParts gemm_bf16_rowparts(const GemmOp& op);
+// the most slabs a product of N columns has on any tile (size queries)
+int gemm_bf16_rowpart_slabs_max(int N);
 // Tile and split-K factor for a weight gradient (both operands k-major, K = T).  direct: the output needs no
 // finishing pass when it is not split.
 struct WgradPlan { int tile, splitk; };

@@ -494,9 +494,24 @@ int gemm_bf16_tile(const GemmOp& op) {
 }
 
 RowParts gemm_bf16_rowparts(const GemmOp& op) {
-  const int tile = gemm_bf16_tile(op), bn = kTileCost[tile].bn;   // two wavefronts across, but for the narrowest
-  const int wn = tile == GEMM_R32 ? 1 : 2;
-  return RowParts{(op.N + bn - 1) / bn * wn, 128 * wn / bn, (op.N + 127) / 128};
+  const int tile = gemm_bf16_tile(op), bn = kTileCost[tile].bn;
+  const int width = bn <= 64 ? 32 : 64;                            // columns per partial (gemm_tile.h)
+  // The order in which a row's columns are added may not depend on the tile, so it is fixed by N: units of 128
+  // columns, or of 64 for a narrow N that does not fill 256-column tiles.
+  const int unit = op.N > 128 && (op.N % 256 == 0 || op.N > 512) ? 128 : 64;
+  return RowParts{(op.N + bn - 1) / bn * (bn / width), unit / width, (op.N + unit - 1) / unit};
+}
+
+int gemm_bf16_rowpart_slabs_max(int N) {
+  int most = 0;
+  for (int tile = GEMM_T256; tile <= GEMM_R32; tile++) {
+    if (tile == GEMM_T256X128) continue;                           // two k-major operands only: no row partials
+    GemmOp op;
+    op.N = N; op.tile = tile;
+    const int s = gemm_bf16_rowparts(op).slabs;
+    if (s > most) most = s;
+  }
+  return most;
 }
 
 WgradPlan gemm_bf16_plan_wgrad(int M, int N, int K, int batch, bool direct) {

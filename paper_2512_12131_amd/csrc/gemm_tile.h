@@ -37,20 +37,19 @@ __device__ __forceinline__ void wait_vmcnt() {
 }
 __device__ __forceinline__ void wait_lgkmcnt0() { __builtin_amdgcn_s_waitcnt(0xc07f); }
 
-// Sum over aligned groups of N = 4, 8 or 16 consecutive lanes, every lane receiving the total, with
+// Sum over aligned groups of N = 4 or 8 consecutive lanes, every lane receiving the total, with
 // data-parallel-primitive moves (register file only): neighbours inside a quad, then the mirror image
-// inside 8 lanes, then inside 16.  (A butterfly of __shfl_xor goes through the LDS crossbar: four
+// inside 8 lanes.  (A butterfly of __shfl_xor goes through the LDS crossbar: three
 // dependent round trips per row partial.)
 template <int N>
 __device__ __forceinline__ float lane_group_sum(float x) {
-  static_assert(N == 4 || N == 8 || N == 16, "lane group size");
+  static_assert(N == 4 || N == 8, "lane group size");
   auto dpp = [](float v, auto CTRL) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(CTRL)::value, 0xf, 0xf, false));
   };
   x += dpp(x, std::integral_constant<int, 0xB1>{});    // quad_perm [1,0,3,2]
   x += dpp(x, std::integral_constant<int, 0x4E>{});    // quad_perm [2,3,0,1]
-  if constexpr (N >= 8) x += dpp(x, std::integral_constant<int, 0x141>{});   // row_half_mirror: lane i <-> 7 - i
-  if constexpr (N == 16) x += dpp(x, std::integral_constant<int, 0x140>{});   // row_mirror: lane i <-> 15 - i
+  if constexpr (N == 8) x += dpp(x, std::integral_constant<int, 0x141>{});   // row_half_mirror: lane i <-> 7 - i
   return x;
 }
 
@@ -153,7 +152,10 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T:
       (void*)((ROWPART && e.rowpart) ? e.rowpart + (int64_t)m0 * e.rowpart_ld : nullptr), 0,
       (ROWPART && e.rowpart) ? (uint32_t)rows_valid * (uint32_t)e.rowpart_ld * 4u : 0u, 0x00020000);
   const int ldPart = ROWPART ? (int)e.rowpart_ld * 4 : 0;
-  const uint32_t colPart = cg == 0 ? (uint32_t)(e.rowpart_off + b * (tiles_n * T::WN) + tn * T::WN + wn) * 4u : EOOB;
+  // one partial per 64 columns (32 where the wavefront's sub-tile has no more): SPW of them per wavefront and row
+  constexpr int LPP = T::TN < 64 ? T::TN / 8 : 8, SPW = LPR / LPP;
+  const uint32_t colPart =
+      cg % LPP == 0 ? (uint32_t)(e.rowpart_off + ((b * tiles_n + tn) * T::WN + wn) * SPW + cg / LPP) * 4u : EOOB;
   const bool write_stat = STAT_A && e.stat_out && tn == 0 && wn == 0 && b == 0;
   const __amdgpu_buffer_rsrc_t rsStat = row_rsrc(write_stat ? e.stat_out : nullptr);
   const uint32_t colStat = cg == 0 ? 0u : EOOB;
@@ -261,7 +263,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T:
       }
       if constexpr (q + PF < NQ) fetch(q + PF, auxr[q % PF], auxr2[q % PF], auxr3[R_F32 ? q % PF : 0]);
       if constexpr (ROWPART) {
-        part = lane_group_sum<LPR>(part);
+        part = lane_group_sum<LPP>(part);
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(part), rsPart, (int)((uint32_t)(lm * ldPart) + colPart), 0, 0);
       }
       if constexpr (STAT_A)

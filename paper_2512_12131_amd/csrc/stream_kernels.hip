@@ -580,27 +580,28 @@ __global__ __launch_bounds__(256) void transpose16_vec_kernel(const uint16_t* in
   }
 }
 
-// Row partials -> row sums: eight lanes per row, lane l takes the 128-column groups l, l + 8, ...  A group that
-// arrives as two or four partials is added up pairwise first, the order in which a wavefront that owns 128
-// columns adds its quads of lanes: the sum has the same bits whichever tile wrote the partials.  Bound by
-// launch and latency (8 MB at most); one thread per row left most CUs without a wavefront (4.8 us at 16384
-// rows x 8 partials).
-__global__ __launch_bounds__(256) void rowsum_parts_kernel(const float* part, int64_t ld, int members, int slabs, int per128,
-                                                           int n128, float* out, int64_t M) {
+// Row partials -> row sums: eight lanes per row, lane l loads the units l, l + 8, ...  A unit that arrives as two or
+// four partials is added up pairwise first, the order in which a wavefront that owns all its columns adds its
+// quads of lanes; the units are then added front to back, each lane taking the others' from their registers.
+// The sum has the same bits whichever tile wrote the partials.  Bound by launch and latency (8 MB at
+// most); one thread per row left most CUs without a wavefront (4.8 us at 16384 rows x 8 partials).
+__global__ __launch_bounds__(256) void rowsum_parts_kernel(const float* part, int64_t ld, int members, int slabs,
+                                                           int per_unit, int units, float* out, int64_t M) {
   const int l = threadIdx.x & 7;
   const int64_t m = (int64_t)blockIdx.x * 32 + (threadIdx.x >> 3);
   float s = 0.f;
-  if (m < M) {
-    for (int i = l; i < members * n128; i += 8) {
-      const int g = i / n128, c0 = (i % n128) * per128;
+  for (int i0 = 0; i0 < members * units; i0 += 8) {
+    const int i = i0 + l;
+    float u = 0.f;
+    if (m < M && i < members * units) {
+      const int g = i / units, c0 = (i % units) * per_unit;
       const float* p = part + m * ld + g * slabs + c0;
-      auto at = [&](int j) { return j < per128 && c0 + j < slabs ? p[j] : 0.f; };
-      s += (at(0) + at(1)) + (at(2) + at(3));
+      auto at = [&](int j) { return j < per_unit && c0 + j < slabs ? p[j] : 0.f; };
+      u = (at(0) + at(1)) + (at(2) + at(3));
     }
+#pragma unroll
+    for (int j = 0; j < 8; j++) s += __shfl(u, j, 8);
   }
-  s += __shfl_xor(s, 1);
-  s += __shfl_xor(s, 2);
-  s += __shfl_xor(s, 4);
   if (m < M && l == 0) out[m] = s;
 }
 
@@ -895,7 +896,7 @@ hipError_t k_transpose(const void* in, int64_t ld_in, void* out, int64_t ld_out,
 hipError_t k_rowsum_parts(const float* part, int64_t ld, int members, const RowParts& rp, float* out, int64_t M,
                           hipStream_t st) {
   if (M <= 0) return hipSuccess;
-  hipLaunchKernelGGL(rowsum_parts_kernel, dim3((M + 31) / 32), dim3(256), 0, st, part, ld, members, rp.slabs, rp.per128, rp.n128,
+  hipLaunchKernelGGL(rowsum_parts_kernel, dim3((M + 31) / 32), dim3(256), 0, st, part, ld, members, rp.slabs, rp.per_unit, rp.units,
                      out, M);
   return hipGetLastError();
 }
