@@ -381,7 +381,7 @@ void group_bwd_seq(Ctx& c, const GrpArgs& a, const void* act) {
   // pass scales it by gamma and also produces dgamma[k] = sum_n w[n,k] * dW'[n,k].
   const void* wB = a.w_down_cat;
   if (normed) {
-    const int64_t nparts = k_wgrad_dgamma_parts(GR, a.d_in, c.dt);
+    const int64_t nparts = k_wgrad_dgamma_parts(GR);
     float* dgp = (float*)c.take((size_t)nparts * a.d_in * sizeof(float));
     wgrad(c, dp, GR, (int)GR, a.x, a.ldx, (int)a.d_in, a.T, a.dw_down_cat, a.gamma, a.w_down_cat, dgp, a.accumulate);
     LAUNCH(c, k_colsum_parts(dgp, nparts, a.d_in, a.dgamma, a.accumulate, c.gdt, c.st));

@@ -175,7 +175,7 @@ hipError_t k_scale_cols2(const void* w0, const void* gamma0, void* out0, int64_t
 hipError_t k_wgrad_finish(const float* part, int nsplit, int64_t rows, int64_t cols, void* dw,
                           const void* colscale, const void* w_for_dgamma, float* dgamma_part,
                           int accumulate, int dt, int out_dt, hipStream_t);
-int64_t k_wgrad_dgamma_parts(int64_t rows, int64_t cols, int dt);
+int64_t k_wgrad_dgamma_parts(int64_t rows);
 // out[c] (+)= sum_p part[p, c]; out has dtype out_dt
 hipError_t k_colsum_parts(const float* part, int64_t nparts, int64_t cols, void* out, int accumulate,
                           int out_dt, hipStream_t);

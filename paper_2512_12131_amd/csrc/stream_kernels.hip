@@ -646,84 +646,81 @@ __global__ __launch_bounds__(256) void scale_cols_kernel(const void* w0, const v
 }
 
 // ---- finish a split-K weight gradient ------------------------------------------------------------
-// One thread per 8-column (bf16) / 1-column (fp32) vector of one row: sums the nsplit fp32 partials,
-// scales, accumulates, stores.  When dgamma partials are wanted a workgroup covers `rb` rows of a
-// 64-vector column strip: its 4 wavefronts take rows r, r+4, ... and add their column sums through LDS.
-// rows per dgamma partial: 32, or 8 where 32 would leave CUs without two workgroups (3072 x 512, five
-// splits: 96 workgroups took 20 us; 3072 x 4096: 768 workgroups read at 5.4 TB/s)
-inline int wf_row_block(int64_t rows, int64_t cols, int dt) {
-  const int64_t strips = (cols / (dt == LR_BF16 ? 8 : 1) + 63) / 64;
-  return strips * ((rows + 31) / 32) < 512 ? 8 : 32;
+// Sums the nsplit fp32 partials of one 8-column (bf16) / 1-column (fp32) vector of the gradient, scales, accumulates, stores;
+// s[] is the sum.  NS > 0: the number of split-K partials is known at compile time, so their loads are issued
+// together instead of one dependent round trip per partial; NS = 0 takes any count.
+template <int DT, typename OT, int NS>
+__device__ __forceinline__ void finish_vector(const float* part, int nsplit, int64_t count, int64_t off, const float* cs, void* dw,
+                                              int accumulate, float* s) {
+  constexpr int NV = St<DT>::NV;
+  using OIO = VecIO<OT, NV>;
+  using PIO = VecIO<float, NV>;
+  if constexpr (NS > 0) {
+    float t[NS][NV];
+#pragma unroll
+    for (int sp = 0; sp < NS; sp++) PIO::load(part, (int64_t)sp * count + off, t[sp]);
+#pragma unroll
+    for (int i = 0; i < NV; i++) s[i] = t[0][i];
+#pragma unroll
+    for (int sp = 1; sp < NS; sp++)
+#pragma unroll
+      for (int i = 0; i < NV; i++) s[i] += t[sp][i];
+  } else {
+    PIO::load(part, off, s);
+    for (int sp = 1; sp < nsplit; sp++) {
+      float t[NV];
+      PIO::load(part, (int64_t)sp * count + off, t);
+#pragma unroll
+      for (int i = 0; i < NV; i++) s[i] += t[i];
+    }
+  }
+  float o[NV];
+#pragma unroll
+  for (int i = 0; i < NV; i++) o[i] = s[i] * cs[i];
+  if (accumulate) {
+    float old[NV];
+    OIO::load(dw, off, old);
+#pragma unroll
+    for (int i = 0; i < NV; i++) o[i] += old[i];
+  }
+  OIO::store(dw, off, o);
 }
 
-// NS > 0: the number of split-K partials is known at compile time, so their loads are issued
-// together instead of one dependent round trip per partial; NS = 0 takes any count.
+// One thread per vector of one row.  When dgamma partials are wanted a workgroup covers 32 rows of a
+// 64-vector column strip: its 4 wavefronts take rows r, r+4, ... and add their column sums through LDS.
+constexpr int WF_RB = 32;  // rows per dgamma partial
 template <int DT, typename OT, bool DG, int NS>
 __global__ __launch_bounds__(256) void wgrad_finish_kernel(const float* part, int nsplit, int64_t rows, int64_t cols,
                                                            void* dw, const void* colscale, const void* wdg,
-                                                           float* dgpart, int accumulate, int rb) {
-  using S = St<DT>;
-  using IO = VecIO<typename S::T, S::NV>;
-  using OIO = VecIO<OT, S::NV>;
-  using PIO = VecIO<float, S::NV>;
-  constexpr int NV = S::NV;
+                                                           float* dgpart, int accumulate) {
+  constexpr int NV = St<DT>::NV;
+  using IO = VecIO<typename St<DT>::T, NV>;
   __shared__ float sred[DG ? 4 * 64 * NV : 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t count = rows * cols;
-  float cs[NV], dg[NV];
+  float cs[NV], dg[NV], s[NV];
 #pragma unroll
   for (int i = 0; i < NV; i++) { cs[i] = 1.f; dg[i] = 0.f; }
-  auto one = [&](int64_t r, int64_t c) {
-    float s[NV];
-    if constexpr (NS > 0) {
-      float t[NS][NV];
-#pragma unroll
-      for (int sp = 0; sp < NS; sp++) PIO::load(part, (int64_t)sp * count + r * cols + c, t[sp]);
-#pragma unroll
-      for (int i = 0; i < NV; i++) s[i] = t[0][i];
-#pragma unroll
-      for (int sp = 1; sp < NS; sp++)
-#pragma unroll
-        for (int i = 0; i < NV; i++) s[i] += t[sp][i];
-    } else {
-      PIO::load(part, r * cols + c, s);
-      for (int sp = 1; sp < nsplit; sp++) {
-        float t[NV];
-        PIO::load(part, (int64_t)sp * count + r * cols + c, t);
-#pragma unroll
-        for (int i = 0; i < NV; i++) s[i] += t[i];
-      }
-    }
-    if constexpr (DG) {
-      float wv[NV];
-      IO::load(wdg, r * cols + c, wv);
-#pragma unroll
-      for (int i = 0; i < NV; i++) dg[i] = fmaf(wv[i], s[i], dg[i]);
-    }
-#pragma unroll
-    for (int i = 0; i < NV; i++) s[i] *= cs[i];
-    if (accumulate) {
-      float old[NV];
-      OIO::load(dw, r * cols + c, old);
-#pragma unroll
-      for (int i = 0; i < NV; i++) s[i] += old[i];
-    }
-    OIO::store(dw, r * cols + c, s);
-  };
   if constexpr (!DG) {
     const int64_t vpr = cols / NV;                               // vectors per row
     const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (v >= rows * vpr) return;
     const int64_t r = v / vpr, c = (v % vpr) * NV;
     if (colscale) IO::load(colscale, c, cs);
-    one(r, c);
+    finish_vector<DT, OT, NS>(part, nsplit, count, r * cols + c, cs, dw, accumulate, s);
   } else {
     const int64_t c = ((int64_t)blockIdx.x * 64 + lane) * NV;
     const bool cok = c < cols;
     if (cok && colscale) IO::load(colscale, c, cs);
-    const int64_t rbeg = (int64_t)blockIdx.y * rb, rend = min(rows, rbeg + rb);
+    const int64_t rbeg = (int64_t)blockIdx.y * WF_RB, rend = min(rows, rbeg + WF_RB);
     if (cok)
-      for (int64_t r = rbeg + wave; r < rend; r += 4) one(r, c);
+      for (int64_t r = rbeg + wave; r < rend; r += 4) {
+        float wv[NV];
+        IO::load(wdg, r * cols + c, wv);
+        finish_vector<DT, OT, NS>(part, nsplit, count, r * cols + c, cs, dw, accumulate, s);
+#pragma unroll
+        for (int i = 0; i < NV; i++) dg[i] = fmaf(wv[i], s[i], dg[i]);
+      }
 #pragma unroll
     for (int i = 0; i < NV; i++) sred[(wave * 64 + lane) * NV + i] = dg[i];
     __syncthreads();
@@ -736,27 +733,79 @@ __global__ __launch_bounds__(256) void wgrad_finish_kernel(const float* part, in
   }
 }
 
-// Column sums of a few hundred partial rows: 16 columns (a 64-byte run) per workgroup, 16 threads per column that
-// take every 16th row.  Bound by the latency of the loads: a thread per column walked all rows one after the
-// other from a handful of workgroups (96 x 4096: 26 us).
+// The same with dgamma partials where few strips leave CUs idle: 32 rows x 16 vectors per workgroup, every vector on a
+// thread of its own instead of eight rows in turn, the column sums afterwards from LDS.  They are added in the
+// wide kernel's order (four classes of rows r, r+4, ..., then the classes), so the choice does not show in dgamma.
+constexpr int WF_NS = 16;  // vectors per strip
+template <int DT, typename OT, int NS>
+__global__ __launch_bounds__(256) void wgrad_finish_narrow_kernel(const float* part, int nsplit, int64_t rows, int64_t cols,
+                                                                  void* dw, const void* colscale, const void* wdg,
+                                                                  float* dgpart, int accumulate) {
+  constexpr int NV = St<DT>::NV, W = WF_NS * NV;
+  using IO = VecIO<typename St<DT>::T, NV>;
+  __shared__ float ssum[WF_RB * W], sw[WF_RB * W], sclass[4 * W];
+  const int tid = threadIdx.x, v = tid % WF_NS;
+  const int64_t count = rows * cols, c0 = (int64_t)blockIdx.x * W, c = c0 + v * NV;
+  const int64_t rbeg = (int64_t)blockIdx.y * WF_RB;
+  const int nrows = (int)min((int64_t)WF_RB, rows - rbeg);
+  float cs[NV];
+#pragma unroll
+  for (int i = 0; i < NV; i++) cs[i] = 1.f;
+  if (c < cols) {
+    if (colscale) IO::load(colscale, c, cs);
+#pragma unroll
+    for (int rr = tid / WF_NS; rr < WF_RB; rr += 256 / WF_NS) {
+      if (rr >= nrows) continue;
+      const int64_t off = (rbeg + rr) * cols + c;
+      float s[NV], wv[NV];
+      IO::load(wdg, off, wv);
+      finish_vector<DT, OT, NS>(part, nsplit, count, off, cs, dw, accumulate, s);
+#pragma unroll
+      for (int i = 0; i < NV; i++) {
+        ssum[rr * W + v * NV + i] = s[i];
+        sw[rr * W + v * NV + i] = wv[i];
+      }
+    }
+  }
+  __syncthreads();
+  for (int i = tid; i < 4 * W; i += 256) {
+    const int q = i / W, col = i % W;
+    float dg = 0.f;
+    if (c0 + col < cols)
+      for (int rr = q; rr < nrows; rr += 4) dg = fmaf(sw[rr * W + col], ssum[rr * W + col], dg);
+    sclass[i] = dg;
+  }
+  __syncthreads();
+  if (tid < W && c0 + tid < cols)
+    dgpart[(int64_t)blockIdx.y * cols + c0 + tid] = sclass[tid] + sclass[W + tid] + sclass[2 * W + tid] + sclass[3 * W + tid];
+}
+
+// Column sums of a few hundred partial rows, front to back: 16 columns (a 64-byte run) per workgroup, 16 threads per
+// column that bring every 16th row into LDS, from where one of them adds the column up.  Bound by the latency of
+// the loads: a thread per column walked all rows one after the other from a handful of workgroups (96 x 4096: 26 us).
 template <typename OT>
 __global__ __launch_bounds__(256) void colsum_parts_kernel(const float* part, int64_t nparts, int64_t cols, void* out,
                                                            int accumulate) {
   using IO = VecIO<OT, 1>;
-  __shared__ float red[16][17];
+  constexpr int NR = 128;
+  __shared__ float rowsv[NR][17];
   const int ci = threadIdx.x & 15, pi = threadIdx.x >> 4;
   const int64_t c = (int64_t)blockIdx.x * 16 + ci;
   float s = 0.f;
-  if (c < cols) {
-#pragma unroll 8
-    for (int64_t p = pi; p < nparts; p += 16) s += part[p * cols + c];
-  }
-  red[pi][ci] = s;
-  __syncthreads();
-  if (pi != 0 || c >= cols) return;
-  s = 0.f;
+  for (int64_t p0 = 0; p0 < nparts; p0 += NR) {
 #pragma unroll
-  for (int i = 0; i < 16; i++) s += red[i][ci];
+    for (int i = 0; i < NR / 16; i++) {
+      const int64_t p = p0 + pi + i * 16;
+      rowsv[pi + i * 16][ci] = c < cols && p < nparts ? part[p * cols + c] : 0.f;
+    }
+    __syncthreads();
+    if (pi == 0) {
+#pragma unroll 16
+      for (int i = 0; i < NR; i++) s += rowsv[i][ci];   // (rows past the end are zeros)
+    }
+    __syncthreads();
+  }
+  if (pi != 0 || c >= cols) return;
   if (accumulate) {
     float o;
     IO::load(out, c, &o);
@@ -916,27 +965,31 @@ hipError_t k_scale_cols2(const void* w0, const void* gamma0, void* out0, int64_t
   DISPATCH_DT(dt, scale_cols_kernel, dim3(grid1d((rows0 + rows1) * (cols / nv))), dim3(256), st, w0, gamma0, out0, rows0, w1, gamma1,
               out1, rows1, cols);
 }
-int64_t k_wgrad_dgamma_parts(int64_t rows, int64_t cols, int dt) {
-  const int rb = wf_row_block(rows, cols, dt);
-  return (rows + rb - 1) / rb;
-}
+int64_t k_wgrad_dgamma_parts(int64_t rows) { return (rows + WF_RB - 1) / WF_RB; }
 hipError_t k_wgrad_finish(const float* part, int nsplit, int64_t rows, int64_t cols, void* dw, const void* colscale,
                           const void* w_for_dgamma, float* dgamma_part, int accumulate, int dt, int out_dt,
                           hipStream_t st) {
   if (rows <= 0 || cols <= 0) return hipSuccess;
   const int nv = dt == LR_BF16 ? 8 : 1;
   const bool dg = w_for_dgamma != nullptr && dgamma_part != nullptr;
-  const int rb = wf_row_block(rows, cols, dt);
-  dim3 grid = dg ? dim3((unsigned)((cols / nv + 63) / 64), (unsigned)((rows + rb - 1) / rb))
-                 : dim3((unsigned)((rows * (cols / nv) + 255) / 256));
+  const int64_t blocks = (rows + WF_RB - 1) / WF_RB;
+  // narrow strips where 64-vector ones would leave CUs without two workgroups (3072 x 512, five splits: 96 workgroups
+  // took 20 us; 3072 x 4096: 768 workgroups read at 5.4 TB/s)
+  const bool narrow = dg && (cols / nv + 63) / 64 * blocks < 512;
+  dim3 grid = narrow ? dim3((unsigned)((cols / nv + WF_NS - 1) / WF_NS), (unsigned)blocks)
+              : dg   ? dim3((unsigned)((cols / nv + 63) / 64), (unsigned)blocks)
+                     : dim3((unsigned)((rows * (cols / nv) + 255) / 256));
 #define LRB_WF2(DT_, OT_, NS_)                                                                                   \
   do {                                                                                                           \
-    if (dg)                                                                                                      \
+    if (narrow)                                                                                                  \
+      hipLaunchKernelGGL((wgrad_finish_narrow_kernel<DT_, OT_, NS_>), grid, dim3(256), 0, st, part, nsplit, rows, cols, dw, \
+                         colscale, w_for_dgamma, dgamma_part, accumulate);                                      \
+    else if (dg)                                                                                                 \
       hipLaunchKernelGGL((wgrad_finish_kernel<DT_, OT_, true, NS_>), grid, dim3(256), 0, st, part, nsplit, rows, cols, dw, \
-                         colscale, w_for_dgamma, dgamma_part, accumulate, rb);                                  \
+                         colscale, w_for_dgamma, dgamma_part, accumulate);                                      \
     else                                                                                                         \
       hipLaunchKernelGGL((wgrad_finish_kernel<DT_, OT_, false, NS_>), grid, dim3(256), 0, st, part, nsplit, rows, cols, dw, \
-                         colscale, w_for_dgamma, dgamma_part, accumulate, rb);                                  \
+                         colscale, w_for_dgamma, dgamma_part, accumulate);                                      \
   } while (0)
 #define LRB_WF(DT_, OT_)                                                                                         \
   do {                                                                                                           \
