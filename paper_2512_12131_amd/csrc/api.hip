@@ -101,36 +101,27 @@ void wgrad(Ctx& c, const void* Aact, int64_t lda, int Mw, const void* Bact, int6
   op.M = Mw; op.N = Nw; op.K = (int)T; op.batch = n;
   op.epi.kind = EPI_PARTIAL;
   const bool kmajor = c.dt == LR_F32 || gemm_bf16_kmajor_ok(op);
-  auto plan = [&](int batch, bool direct) {
-    if (c.dt == LR_F32) return WgradPlan{GEMM_TILE_AUTO, gemm_f32_pick_splitk(Mw, Nw, (int)T, batch)};
-    return gemm_bf16_plan_wgrad(Mw, Nw, (int)T, batch, direct);
-  };
-  if (c.dry) {   // a size query knows neither `accumulate` nor what else is folded in: room for every form of the call
-    int splits = 0;
-    for (int batch : {1, n})
-      for (bool direct : {false, true}) {
-        const int s = plan(batch, direct).splitk;
-        if (!(direct && kmajor && s == 1) && s > splits) splits = s;
-      }
-    c.take((size_t)splits * Mw * Nw * sizeof(float));
-    gemm(c, op);
-    c.release(m);
-    return;
-  }
   // nothing to scale, add to or sum up: an un-split product is the gradient itself, in either output type
-  const bool direct = !colscale && !w_for_dgamma && !accumulate && kmajor;
-  const WgradPlan pl = plan(n, direct);
-  op.tile = pl.tile; op.splitk = pl.splitk;
-  if (direct && op.splitk == 1) {
-    op.C = dw; op.ldc = Nw; op.sC = (int64_t)Mw * Nw;
-    if (c.gdt == LR_BF16) op.epi.kind = EPI_STORE;   // EPI_PARTIAL stores fp32
-    gemm(c, op);
-    return;
+  const bool plain = !colscale && !w_for_dgamma && !accumulate && kmajor;
+  if (c.dt == LR_F32) {
+    op.splitk = gemm_f32_pick_splitk(Mw, Nw, (int)T);
+  } else if (kmajor && !c.dry) {
+    const WgradPlan pl = gemm_bf16_plan_wgrad(Mw, Nw, (int)T, n, plain);
+    op.tile = pl.tile; op.splitk = pl.splitk; op.k_parts = pl.k_parts;
+  } else {   // (a size query knows neither `accumulate` nor what else is folded in: it leaves room for every split)
+    op.splitk = gemm_bf16_wgrad_splits(Mw, Nw, (int)T);
   }
-  if (n > 1) {   // the finishing pass takes one product at a time
+  const bool direct = !c.dry && plain && op.splitk == 1;
+  if (!direct && n > 1) {   // the finishing pass takes one product at a time
     for (int i = 0; i < n; i++)
       wgrad(c, (const char*)Aact + (size_t)i * sA * esize(c.dt), lda, Mw, (const char*)Bact + (size_t)i * sB * esize(c.dt), ldb,
             Nw, T, (char*)dw + (size_t)i * Mw * Nw * esize(c.gdt), colscale, w_for_dgamma, dgamma_part, accumulate);
+    return;
+  }
+  if (direct) {
+    op.C = dw; op.ldc = Nw; op.sC = (int64_t)Mw * Nw;
+    if (c.gdt == LR_BF16) op.epi.kind = EPI_STORE;   // EPI_PARTIAL stores fp32
+    gemm(c, op);
     return;
   }
   float* part = (float*)c.take((size_t)op.splitk * Mw * Nw * sizeof(float));

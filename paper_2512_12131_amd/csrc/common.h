@@ -82,6 +82,8 @@ struct GemmOp {
   // k-major bf16 form only: the rows m0.. of a row tile use k < m0 + (tile height) only, i.e. A is
   // known to be zero where k > m (the causal structure of an attention gradient)
   int causal_k = 0;
+  // ring tiles (not 128 x 128) with two k-major operands, un-split: the sum over k is formed as a split into this many parts would form it
+  int k_parts = 1;
   int tile = 0;                // GemmTile: GEMM_TILE_AUTO lets gemm_bf16 choose
   Epilogue epi;
 };
@@ -99,9 +101,11 @@ struct RowParts { int slabs, per_unit, units; };
 RowParts gemm_bf16_rowparts(const GemmOp& op);
 // the most slabs a product of N columns has on any tile (size queries)
 int gemm_bf16_rowpart_slabs_max(int N);
-// Tile and split-K factor for a weight gradient (both operands k-major, K = T).  direct: the output needs no
-// finishing pass when it is not split.
-struct WgradPlan { int tile, splitk; };
+// How `batch` weight gradients (both operands k-major, K = T) run.  Their sum over k is that of gemm_bf16_wgrad_splits()
+// parts, added up by the finishing pass (splitk) or inside the GEMM (k_parts); the other of the two is 1.
+// direct: the output needs no finishing pass when it is not split.
+int gemm_bf16_wgrad_splits(int M, int N, int K);
+struct WgradPlan { int tile, splitk, k_parts; };
 WgradPlan gemm_bf16_plan_wgrad(int M, int N, int K, int batch, bool direct);
 hipError_t gemm_ring32(const GemmOp& op, hipStream_t st);
 hipError_t gemm_ring64(const GemmOp& op, hipStream_t st);
@@ -116,7 +120,7 @@ hipError_t gemm_bf16_untimed(const GemmOp& op, hipStream_t st);
 // true when gemm_bf16 can run `op` with both operands k-major (no transposed copies needed)
 bool gemm_bf16_kmajor_ok(const GemmOp& op);
 hipError_t gemm_f32(const GemmOp& op, hipStream_t st);
-int gemm_f32_pick_splitk(int M, int N, int K, int batch);   // weight gradients in fp32: K = T
+int gemm_f32_pick_splitk(int M, int N, int K);   // weight gradients in fp32: K = T
 // Benchmark aid: launches bracketed by HIP events on their stream (every gemm_bf16 launch, tagged with
 // its epilogue kind, and whatever the sequencing code opens and closes itself, tags >= LR_TAG_ATTN_FWD).
 int launch_timer_begin(int max_launches);

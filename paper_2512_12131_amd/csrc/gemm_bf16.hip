@@ -514,23 +514,43 @@ int gemm_bf16_rowpart_slabs_max(int N) {
   return most;
 }
 
-WgradPlan gemm_bf16_plan_wgrad(int M, int N, int K, int batch, bool direct) {
-  // Every split adds its fp32 partial tile to what the workgroups write and the finishing pass reads (7 TB/s);
-  // without a split and with nothing else to fold in, the GEMM writes the gradient itself.
+int gemm_bf16_wgrad_splits(int M, int N, int K) {
+  // The splits are part of the result: the fp32 sum over the tokens is their sums added up.  So they follow from the shape
+  // alone, whatever tile runs them, whether the gradient is added to and how many equal ones share a launch.
+  // With one 256-row tile per CU a launch runs in ceil(workgroups / 256) rounds, each as long as one workgroup: its
+  // k slices plus a fixed cost (pipeline fill, the fp32 partial tile it writes, its share of the fold) worth
+  // about 8 slices.  The split count with the smallest estimate; ties go to fewer splits (less partial traffic).
+  const int bm = 256, bn = N > 128 && (N % 256 == 0 || N > 512) ? 256 : 128;
+  const long tiles = (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
   const int nk = (K + BK - 1) / BK;
-  WgradPlan best{GEMM_T256, 1};
+  const int maxs = nk >= 16 ? (nk / 8 < 64 ? nk / 8 : 64) : 1;   // at least 8 slices per split
+  int best = 1;
+  long best_cost = -1;
+  for (int s = 1; s <= maxs; s++) {
+    const long rounds = (tiles * s + 255) / 256;
+    const long cost = rounds * ((nk + s - 1) / s + 8) * 16 + s;   // "+ s": the tie-break
+    if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = s; }
+  }
+  return best;
+}
+
+WgradPlan gemm_bf16_plan_wgrad(int M, int N, int K, int batch, bool direct) {
+  // A split launch writes an fp32 partial per split, which the finishing pass reads (7 TB/s).  The ring tiles can instead add
+  // the parts up in registers, where the shape spreads over the chip without a split (256 x 1024 over 1031 tokens, two
+  // parts: 6.6 us against 7.0 + 2.7); what is left is at most a finishing pass over one partial.
+  const int nk = (K + BK - 1) / BK, splits = gemm_bf16_wgrad_splits(M, N, K);
+  WgradPlan best{GEMM_T256, splits, 1};
   float best_t = -1.f;
-  for (int tile = GEMM_T256; tile <= GEMM_R32; tile++) {
-    for (int s : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 24, 32, 48, 64}) {
-      if (s > 1 && nk / s < (tile < GEMM_R64 ? 8 : 4)) break;
+  for (int tile = GEMM_T256; tile <= GEMM_R32; tile++)
+    for (int s : {splits, 1}) {
+      if (s < splits && (tile < GEMM_R64 || tile == GEMM_R128)) continue;   // (gemm_ring.h)
       float t = tile_time(tile, M, N, (nk + s - 1) / s, batch * s, 2.f, kKMajorSlice[tile]);
       if (s > 1 || !direct) t += (float)batch * (2.f + (float)(s + 1) * (float)M * (float)N * (4.f / 7e6f));
       if (best_t < 0.f || t < best_t) {
         best_t = t;
-        best = WgradPlan{tile, s};
+        best = WgradPlan{tile, s, splits / s};
       }
     }
-  }
   return best;
 }
 
@@ -625,6 +645,7 @@ hipError_t gemm_bf16_untimed(const GemmOp& op, hipStream_t st) {
   if (km && !gemm_bf16_kmajor_ok(op)) return hipErrorInvalidValue;
   if (op.transA != op.transB && !gemm_bf16_mixed_ok(op)) return hipErrorInvalidValue;
   if (op.epi.stat_from_a && op.splitk > 1) return hipErrorInvalidValue;
+  if (op.k_parts > 1 && gemm_bf16_tile(op) < GEMM_R64) return hipErrorInvalidValue;
   switch (gemm_bf16_tile(op)) {
     case GEMM_R64: return gemm_ring64(op, st);
     case GEMM_R64X128: return gemm_ring64x128(op, st);

@@ -100,8 +100,8 @@ long tiles_of(int M, int N, int batch) { return (long)((M + TB - 1) / TB) * ((N 
 
 // Weight gradients (K = T): a workgroup's wavefronts already share k, so a split, which costs the finishing launch,
 // only pays once each of its parts is long and the tiles alone leave most CUs idle.
-int gemm_f32_pick_splitk(int M, int N, int K, int batch) {
-  const long tiles = tiles_of(M, N, batch);
+int gemm_f32_pick_splitk(int M, int N, int K) {
+  const long tiles = tiles_of(M, N, 1);
   long s = 1;
   while (s < 32 && tiles * s < 256 && K / (s * 2) >= 2048) s *= 2;
   return (int)s;

@@ -83,7 +83,8 @@ __device__ __forceinline__ int kmajor_swz(int k) {
   return W >= 128 ? (k & 3) << 2 : W == 64 ? ((k >> 1) & 1) << 2 : 0;
 }
 
-template <class T, int KIND, bool STAT_A, bool AKM, bool BKM>
+// PARTS: k runs in op.k_parts parts that are summed one by one, as split-K partials are.
+template <class T, int KIND, bool STAT_A, bool AKM, bool BKM, bool PARTS>
 __global__ __launch_bounds__(T::NT) void gemm_ring_kernel(GemmOp op, int kper, int tiles_m, int tiles_n) {
   static_assert(!(STAT_A && AKM), "row statistics are gathered from k-contiguous rows");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -185,6 +186,16 @@ __global__ __launch_bounds__(T::NT) void gemm_ring_kernel(GemmOp op, int kper, i
     for (int j = 0; j < T::FN; j++)
 #pragma unroll
       for (int v = 0; v < 16; v++) acc[i][j][v] = 0.f;
+  // PARTS: sum of the finished parts; a part ends on a slice boundary
+  f32x16 tot[PARTS ? T::FM : 1][PARTS ? T::FN : 1];
+  const int part_slices = PARTS ? ((op.K + op.k_parts - 1) / op.k_parts + BK - 1) / BK : 0;
+  int part_end = part_slices;
+  if constexpr (PARTS) {
+#pragma unroll
+    for (int i = 0; i < T::FM; i++)
+#pragma unroll
+      for (int j = 0; j < T::FN; j++) tot[i][j] = acc[i][j];
+  }
   float ssq = 0.f;           // STAT_A: sum of squares of tile row tid / TPR, the same in its TPR threads
 
 #pragma unroll
@@ -218,6 +229,20 @@ __global__ __launch_bounds__(T::NT) void gemm_ring_kernel(GemmOp op, int kper, i
       asm volatile("" ::: "memory");
       static_for<KSTEPS>([&](auto KK) {
         constexpr int kk = decltype(KK)::value;
+        if constexpr (PARTS && kk % 4 == 0) {
+          if (it * T::SUB + kk / 4 == part_end) {
+            part_end += part_slices;
+#pragma unroll
+            for (int i = 0; i < T::FM; i++)
+#pragma unroll
+              for (int j = 0; j < T::FN; j++)
+#pragma unroll
+                for (int v = 0; v < 16; v++) {
+                  tot[i][j][v] += acc[i][j][v];
+                  acc[i][j][v] = 0.f;
+                }
+          }
+        }
         constexpr int l0 = kk * T::LPS / KSTEPS, l1 = (kk + 1) * T::LPS / KSTEPS;
         if constexpr (T::NL == 0) static_for<l1 - l0>([&](auto L) { issue_one(it + T::NS - 1, wr, std::integral_constant<int, l0 + decltype(L)::value>{}); });
 #pragma unroll
@@ -257,12 +282,21 @@ __global__ __launch_bounds__(T::NT) void gemm_ring_kernel(GemmOp op, int kper, i
     __syncthreads();
   }
   if (T::NL > 0 && lw >= 0) return;
+  if constexpr (PARTS) {
+#pragma unroll
+    for (int i = 0; i < T::FM; i++)
+#pragma unroll
+      for (int j = 0; j < T::FN; j++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) acc[i][j][v] += tot[i][j][v];
+  }
   gemm_epilogue<T, KIND, STAT_A>(op, acc, smem, sStat, wave, lane, m0, n0, tn, tiles_n, b, bi, bo, bz);
 }
 
-template <class T, int KIND, bool STAT_A, bool AKM, bool BKM>
+template <class T, int KIND, bool STAT_A, bool AKM, bool BKM, bool PARTS = false>
 hipError_t launch_ring(const GemmOp& op, hipStream_t st) {
-  auto kern = gemm_ring_kernel<T, KIND, STAT_A, AKM, BKM>;
+  if (!PARTS && op.k_parts != 1) return hipErrorInvalidValue;
+  auto kern = gemm_ring_kernel<T, KIND, STAT_A, AKM, BKM, PARTS>;
   // one-time opt-in to more than 64 KB of dynamic LDS (thread-safe function-local static)
   static const hipError_t attr_err =
       hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
@@ -280,6 +314,14 @@ template <class T>
 hipError_t dispatch_ring(const GemmOp& op, hipStream_t st) {
   const int kind = op.splitk > 1 ? (int)EPI_PARTIAL : op.epi.kind;
   const bool stat = op.epi.stat_from_a != 0;
+  if (op.transA && op.transB && op.k_parts > 1) {
+    // (with 64 x 64 per wavefront the second set of accumulators leaves one workgroup per CU)
+    if constexpr (T::FM * T::FN < 4) {
+      if (op.splitk == 1 && kind == EPI_PARTIAL) return launch_ring<T, EPI_PARTIAL, false, true, true, true>(op, st);
+      if (op.splitk == 1 && kind == EPI_STORE) return launch_ring<T, EPI_STORE, false, true, true, true>(op, st);
+    }
+    return hipErrorInvalidValue;
+  }
   if (op.transA && op.transB) {
     switch (kind) {
       case EPI_PARTIAL: return launch_ring<T, EPI_PARTIAL, false, true, true>(op, st);

@@ -647,32 +647,41 @@ __global__ __launch_bounds__(256) void scale_cols_kernel(const void* w0, const v
 
 // ---- finish a split-K weight gradient ------------------------------------------------------------
 // Sums the nsplit fp32 partials of one 8-column (bf16) / 1-column (fp32) vector of the gradient, scales, accumulates, stores;
-// s[] is the sum.  NS > 0: the number of split-K partials is known at compile time, so their loads are issued
-// together instead of one dependent round trip per partial; NS = 0 takes any count.
+// s[] is the sum, front to back.  The loads of up to eight partials are issued together instead of one dependent round trip per
+// partial (16 partials of 2048 x 512 in the narrow kernel below: 16.6 -> 14.0 us).  NS > 0: the number of partials is known at compile time; NS = 0 takes any count.
 template <int DT, typename OT, int NS>
 __device__ __forceinline__ void finish_vector(const float* part, int nsplit, int64_t count, int64_t off, const float* cs, void* dw,
                                               int accumulate, float* s) {
   constexpr int NV = St<DT>::NV;
   using OIO = VecIO<OT, NV>;
   using PIO = VecIO<float, NV>;
-  if constexpr (NS > 0) {
-    float t[NS][NV];
+  // partials sp0 .. sp0 + G - 1, added to s (FIRST: the first of them starts it)
+  auto take = [&](auto Gc, auto FIRST, int sp0) {
+    constexpr int G = decltype(Gc)::value, first = decltype(FIRST)::value;
+    float t[G][NV];
 #pragma unroll
-    for (int sp = 0; sp < NS; sp++) PIO::load(part, (int64_t)sp * count + off, t[sp]);
+    for (int g = 0; g < G; g++) PIO::load(part, (int64_t)(sp0 + g) * count + off, t[g]);
+    if constexpr (first) {
 #pragma unroll
-    for (int i = 0; i < NV; i++) s[i] = t[0][i];
-#pragma unroll
-    for (int sp = 1; sp < NS; sp++)
-#pragma unroll
-      for (int i = 0; i < NV; i++) s[i] += t[sp][i];
-  } else {
-    PIO::load(part, off, s);
-    for (int sp = 1; sp < nsplit; sp++) {
-      float t[NV];
-      PIO::load(part, (int64_t)sp * count + off, t);
-#pragma unroll
-      for (int i = 0; i < NV; i++) s[i] += t[i];
+      for (int i = 0; i < NV; i++) s[i] = t[0][i];
     }
+#pragma unroll
+    for (int g = first; g < G; g++)
+#pragma unroll
+      for (int i = 0; i < NV; i++) s[i] += t[g][i];
+  };
+  using std::integral_constant;
+  if constexpr (NS > 0) {
+    take(integral_constant<int, NS>{}, integral_constant<int, 1>{}, 0);
+  } else {
+    constexpr integral_constant<int, 0> more{};
+    int sp = nsplit >= 8 ? 8 : 1;
+    if (nsplit >= 8) take(integral_constant<int, 8>{}, integral_constant<int, 1>{}, 0);
+    else take(integral_constant<int, 1>{}, integral_constant<int, 1>{}, 0);
+    for (; sp + 8 <= nsplit; sp += 8) take(integral_constant<int, 8>{}, more, sp);
+    if (nsplit - sp >= 4) { take(integral_constant<int, 4>{}, more, sp); sp += 4; }
+    if (nsplit - sp >= 2) { take(integral_constant<int, 2>{}, more, sp); sp += 2; }
+    if (nsplit - sp >= 1) take(integral_constant<int, 1>{}, more, sp);
   }
   float o[NV];
 #pragma unroll
@@ -800,8 +809,10 @@ __global__ __launch_bounds__(256) void colsum_parts_kernel(const float* part, in
     }
     __syncthreads();
     if (pi == 0) {
-#pragma unroll 16
-      for (int i = 0; i < NR; i++) s += rowsv[i][ci];   // (rows past the end are zeros)
+      const int n16 = (int)min((int64_t)NR, nparts - p0 + 15) / 16;
+      for (int j = 0; j < n16; j++)
+#pragma unroll
+        for (int i = 0; i < 16; i++) s += rowsv[j * 16 + i][ci];   // (rows past the end are zeros)
     }
     __syncthreads();
   }
@@ -994,6 +1005,7 @@ hipError_t k_wgrad_finish(const float* part, int nsplit, int64_t rows, int64_t c
 #define LRB_WF(DT_, OT_)                                                                                         \
   do {                                                                                                           \
     switch (nsplit) {                                                                                            \
+      case 1: LRB_WF2(DT_, OT_, 1); break;                                                                       \
       case 2: LRB_WF2(DT_, OT_, 2); break;                                                                       \
       case 3: LRB_WF2(DT_, OT_, 3); break;                                                                       \
       case 4: LRB_WF2(DT_, OT_, 4); break;                                                                       \

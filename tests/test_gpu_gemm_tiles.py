@@ -84,7 +84,7 @@ def test_linear_at_tile_edges(T, d_in, r, d_out):
     ideal = _ideal_bf16_linear(X, WD, WU, DY)
     for n, got, ref in (("z", z, z_ref), ("y", y, y_ref), ("dx", dx, refs[0]), ("dw_down", dwd, refs[1]), ("dw_up", dwu, refs[2])):
         check(n, got, ref, torch.bfloat16, (relerr(ideal[n], ref), l2_and_slope(ideal[n], ref)[0]))
-    # the accumulating form adds the same sum, in another split, to what is there: fp32 sums of T terms
+    # the accumulating form adds the same sum to what is there
     for a, b in zip(acc, (dwd, dwu)):
         assert float((a - 2 * b).norm() / b.norm()) < 1e-5
 

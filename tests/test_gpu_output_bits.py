@@ -87,6 +87,27 @@ def test_outputs_keep_their_bits(name):
     assert not off, f"{name}: other bits in {', '.join(off)}"
 
 
+# un-split gradients that the GEMM writes itself, split ones, and parts that a small tile adds up itself (T = 1031, 3000)
+@pytest.mark.parametrize("grad_dt", [B.LR_F32, B.LR_BF16])
+@pytest.mark.parametrize("T,d,r,n,G", [(500, 256, 64, 344, 2), (1031, 1024, 256, 768, 1), (3000, 264, 72, 200, 3), (16384, 512, 128, 1032, 2)])
+def test_accumulating_onto_zeros_gives_the_overwriting_bits(T, d, r, n, G, grad_dt):
+    print(f"accumulate onto zeros T={T} d={d} r={r} n={n} G={G} grad_dt={grad_dt}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(21)
+    x, z = (torch.randn(s, generator=g, device=DEV).bfloat16() for s in ((T, d), (T, G * r)))
+    wd = (torch.randn((G * r, d), generator=g, device=DEV) * d ** -0.5).bfloat16()
+    wu = (torch.randn((G, n, r), generator=g, device=DEV) * r ** -0.5).bfloat16()
+    dy = torch.randn((G, T, n), generator=g, device=DEV).bfloat16()
+    gamma, stat = torch.ones((d,), device=DEV).bfloat16(), x.float().square().sum(1)
+    for norm in (B.LR_NORM_NONE, B.LR_NORM_ONLINE):
+        over = B.lr_group_bwd(x, gamma, EPS, norm, wd, wu, z, stat, dy, grad_dt=grad_dt)
+        zeros = tuple(torch.zeros_like(t) for t in over[1:])
+        B.lr_group_bwd(x, gamma, EPS, norm, wd, wu, z, stat, dy, grads=zeros, grad_dt=grad_dt)
+        torch.cuda.synchronize()
+        for name, a, b in zip(("dgamma", "dw_down", "dw_up"), zeros, over[1:]):
+            if norm != B.LR_NORM_NONE or name != "dgamma":
+                assert torch.equal(a, b), f"{name}, norm {norm}"
+
+
 def _stat_in_order(x):
     """Sum of squares of each row of x [T, d] in the order of the gathered norm statistic: along 64-wide slices, inside a
     slice eight chunks of 8 values in the order in which the slice's row lies in LDS (chunk c of row t holds columns
