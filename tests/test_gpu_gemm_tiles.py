@@ -90,8 +90,9 @@ def test_linear_at_tile_edges(T, d_in, r, d_out):
 
 
 # fp32: odd sizes and leading dimensions (no 16-byte loads), k tails of 1 to 3, four and sixteen wavefronts per
-# tile, a token reduction long enough to be split
-@pytest.mark.parametrize("T,d_in,r,d_out", [(33, 41, 13, 55), (1000, 999, 77, 333), (4200, 30, 9, 31), (5, 131, 130, 3)])
+# tile, a token reduction long enough to be split, 64 x 64 tiles with and without 16-byte loads
+@pytest.mark.parametrize("T,d_in,r,d_out", [(33, 41, 13, 55), (1000, 999, 77, 333), (4200, 30, 9, 31), (5, 131, 130, 3), (16423, 201, 70, 130),
+                                            (16400, 264, 68, 196)])
 def test_linear_f32_at_tile_edges(T, d_in, r, d_out):
     print(f"linear fp32 T={T} d_in={d_in} r={r} d_out={d_out}", flush=True)
     c = si.linear_case(T, d_in, r, d_out, dtype=torch.float32, seed=4)

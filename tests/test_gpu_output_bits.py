@@ -137,3 +137,23 @@ def test_gathered_statistic_is_added_in_one_order(T, d, r, G):
     _, stat, _ = B.lr_group_fwd(x, torch.ones((d,), device=DEV).bfloat16(), EPS, B.LR_NORM_ONLINE_GATHER, wd, wu)
     torch.cuda.synchronize()
     assert torch.equal(stat, _stat_in_order(x))
+
+
+# fp32: k shorter than a range, one run per range, several with a ragged last one; few tokens leave 32 x 32 tiles, many
+# 64 x 64 ones, with edges in every dimension
+@pytest.mark.parametrize("d,r,n", [(97, 20, 130), (512, 64, 256), (999, 77, 333), (2048, 130, 1028)])
+def test_fp32_rows_do_not_depend_on_the_number_of_tokens(d, r, n):
+    T = 16500
+    print(f"fp32 rows d={d} r={r} n={n}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(31)
+    x, dy = (torch.randn((T, w), generator=g, device=DEV) for w in (d, n))
+    wd = torch.randn((r, d), generator=g, device=DEV) * d ** -0.5
+    wu = torch.randn((n, r), generator=g, device=DEV) * r ** -0.5
+    z, y = B.lr_linear_fwd(x, wd, wu)
+    dx = B.lr_linear_bwd(x, wd, wu, z, dy)[0]
+    for t in (1, 33, 700, 5000):
+        x1, dy1 = x[:t].contiguous(), dy[:t].contiguous()
+        z1, y1 = B.lr_linear_fwd(x1, wd, wu)
+        dx1 = B.lr_linear_bwd(x1, wd, wu, z1, dy1)[0]
+        torch.cuda.synchronize()
+        assert torch.equal(z1, z[:t]) and torch.equal(y1, y[:t]) and torch.equal(dx1, dx[:t]), f"{t} tokens"
