@@ -196,7 +196,8 @@ struct GrpArgs {
   const float* dres32;       // the same residual gradient as an fp32 [T, d_in] tensor (takes precedence)
   float* dx32;               // optional: dx also un-rounded, fp32 [T, d_in] (the residual of a later sum)
   void* act_out;             // optional: where sigma(z_cat) goes (else workspace)
-  const void* w_scaled;      // optional: w_down_cat with gamma already folded into its columns
+  int w_scaled_given;        // w_scaled is w_down_cat with gamma already folded into its columns (null in a size query)
+  const void* w_scaled;
   // LaX variant (identity gate): h_prev [T, G*r] is added to z_cat before the up-projections; in the
   // backward dz_next [T, G*r] is the layer above's gradient w.r.t. z_cat and dh_prev [T, G*r] receives
   // the gradient w.r.t. h_prev.  `lax` selects the variant; each pointer may still be null (= zeros / unused).
@@ -233,7 +234,7 @@ int group_runs(const GrpArgs& a, GrpRun (&run)[2]) {
 
 // w_down_cat with gamma folded into its columns
 const void* scaled_weight(Ctx& c, const GrpArgs& a) {
-  if (a.w_scaled) return a.w_scaled;
+  if (a.w_scaled_given) return a.w_scaled;
   const int64_t GR = (int64_t)a.G * a.r;
   void* wg = c.take((size_t)GR * a.d_in * esize(c.dt));
   LAUNCH(c, k_scale_cols(a.w_down_cat, a.gamma, wg, GR, a.d_in, c.dt, c.st));
@@ -354,7 +355,7 @@ void group_bwd_seq(Ctx& c, const GrpArgs& a, const void* act) {
       }
     }
   }
-  if (c.dry && rp.slabs) rp.slabs = gemm_bf16_rowpart_slabs_max((int)a.r);   // (it does not know the epilogue)
+  if (c.dry && rp.slabs) rp.slabs = gemm_bf16_rowpart_slabs_max(das[0], {EPI_ACTGRAD, EPI_LAXGRAD});
   const int nparts = rp.slabs * a.G;
   float* parts = nparts ? (float*)c.take((size_t)a.T * nparts * sizeof(float)) : nullptr;
   for (int i = 0; i < nrun; i++) {
@@ -519,7 +520,7 @@ void single_up(Ctx& c, const Blk& b, const void* act, const void* w_up, int64_t 
   else if (out32) { up.epi.kind = EPI_UP_O32; up.epi.C32 = out32; up.epi.ldc32 = N; }
   if (sumsq || c.dry) {
     RowParts rp = gemm_bf16_rowparts(up);
-    if (c.dry) rp.slabs = gemm_bf16_rowpart_slabs_max((int)N);   // (it does not know the epilogue)
+    if (c.dry) rp.slabs = gemm_bf16_rowpart_slabs_max(up, {EPI_UP, EPI_UP_O32, EPI_UP_I32});
     float* parts = (float*)c.take((size_t)b.T * rp.slabs * sizeof(float));
     up.epi.rowpart = parts; up.epi.rowpart_ld = rp.slabs;
     gemm(c, up);
@@ -624,8 +625,9 @@ void block_fwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   a.z_cat = ck ? ck->z_qkv : nullptr; a.stat = ck ? ck->s1 : nullptr; a.y_stack = qkv; a.act_out = act;
   a.stat_ready = b.stat_x_ready;
   a.lax = lax; a.h_prev = lax ? lx->h_prev_qkv : nullptr;
-  const void* w_scaled = b.norm == LR_NORM_TWO_PASS ? nullptr : scaled_weights(c, b, p);
-  a.w_scaled = w_scaled;
+  const bool scaled = b.norm != LR_NORM_TWO_PASS;
+  const char* w_scaled = scaled ? (const char*)scaled_weights(c, b, p) : nullptr;
+  a.w_scaled_given = scaled; a.w_scaled = w_scaled;
   group_fwd_seq(c, a);
   if (b.rope_cos) rope_qk(c, b, qkv, 0);
   {
@@ -641,7 +643,7 @@ void block_fwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   m.x = h1; m.gamma = p->gamma2; m.w_down_cat = p->w_dn_gu; m.w_up_stack = p->w_up_gu;
   m.z_cat = ck ? ck->z_gu : nullptr; m.stat = ck ? ck->s2 : nullptr; m.stat_ready = 1; m.act_out = act;
   m.lax = lax; m.h_prev = lax ? lx->h_prev_gu : nullptr;
-  m.w_scaled = w_scaled ? (const char*)w_scaled + (size_t)3 * r * d * es : nullptr;
+  m.w_scaled_given = scaled; m.w_scaled = w_scaled ? w_scaled + (size_t)3 * r * d * es : nullptr;
   group_down_seq(c, m, act);
   mlp_up_swiglu(c, b, p->w_up_gu, act, gg, uu, mm);
   single_down(c, b, mm, f, p->w_dn_d, ck ? ck->z_d : nullptr, act, lax, lax ? lx->h_prev_d : nullptr);
@@ -665,8 +667,12 @@ void block_bwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   if (!ck) ck = &nck;
   void* act_d = c.take((size_t)T * r * es);
   void* act_o = c.take((size_t)T * r * es);
-  void* act_g = c.take((size_t)T * 2 * r * es);   // sigma(z_gu)
-  void* act_q = c.take((size_t)T * 3 * r * es);   // sigma(z_qkv)
+  // What small blocks wait for are launches, so theirs rebuild all layers' activations in one and fold both norms' gammas in
+  // one (8 launches of 2.4 us less at 512 tokens).  Large ones keep to the buffers that the two sides share (67 MB of
+  // activations and 25 MB of weights at 16384 tokens of the 7B shape, where a launch is 12 us and more of work).
+  const bool act_once = 7 * T * r * (int64_t)es <= (16 << 20), fold_once = 5 * r * d * (int64_t)es <= (16 << 20);
+  void* act_g = c.take((size_t)T * (act_once ? 2 : 3) * r * es);            // sigma(z_gu)
+  void* act_q = act_once ? c.take((size_t)T * 3 * r * es) : act_g;          // sigma(z_qkv)
   void* dz1 = c.take((size_t)T * r * es);         // dz_d, later dz_o
   void* h1 = sv ? sv->h1 : c.take((size_t)T * d * es);
   void* dh1 = c.take((size_t)T * d * es);
@@ -695,16 +701,13 @@ void block_bwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
     dout = (char*)mm + (size_t)T * d * es;
   }
 
-  // rank-r activations of all layers (z + h_prev in the LaX variant), and the weights with gamma folded in
-  {
-    const int64_t row = T * r * (int64_t)es;
-    const bool lh = lax != 0;
-    const ActLayers al{{ck->z_d, ck->z_o, ck->z_gu, ck->z_qkv},
-                       {lh ? lx->h_prev_d : nullptr, lh ? lx->h_prev_o : nullptr, lh ? lx->h_prev_gu : nullptr, lh ? lx->h_prev_qkv : nullptr},
-                       {act_d, act_o, act_g, act_q}, {row, row, 2 * row, 3 * row}, {}, 4};
-    LAUNCH(c, k_act_layers_bf16(al, lax ? (int)LR_ACT_IDENTITY : b.act, c.st));
-  }
-  const char* w_scaled = (const char*)scaled_weights(c, b, p);
+  // rank-r activations of the layers (z + h_prev in the LaX variant), and the weights with gamma folded in
+  const int64_t row = T * r * (int64_t)es;
+  const int act_kind = lax ? (int)LR_ACT_IDENTITY : b.act;
+  const ActLayers al{{ck->z_d, ck->z_o, ck->z_gu, ck->z_qkv}, {lx->h_prev_d, lx->h_prev_o, lx->h_prev_gu, lx->h_prev_qkv},
+                     {act_d, act_o, act_g, act_q}, {row, row, 2 * row, 3 * row}, {}, act_once ? 4 : 3};
+  LAUNCH(c, k_act_layers_bf16(al, act_kind, c.st));
+  const char* w_scaled = fold_once ? (const char*)scaled_weights(c, b, p) : nullptr;
 
   // ---- MLP side ----
   single_up_bwd(c, b, dy, d, act_d, ck->z_d, p->w_up_d, g->w_up_d, dz1, accumulate, lax, lx->dz_next_d, lx->dh_prev_d);
@@ -727,12 +730,16 @@ void block_bwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   m.zc = ck->z_gu; m.statc = ck->s2; m.dy_stack = big2; m.dx = dh1; m.dx32 = dh1f; m.dres = dy; m.dgamma = g->gamma2;
   m.dw_down_cat = g->w_dn_gu; m.dw_up_stack = g->w_up_gu; m.accumulate = accumulate;
   m.lax = lax; m.dz_next = lx->dz_next_gu; m.dh_prev = lx->dh_prev_gu;
-  m.w_scaled = w_scaled ? w_scaled + (size_t)3 * r * d * es : nullptr;
+  m.w_scaled_given = fold_once; m.w_scaled = w_scaled ? w_scaled + (size_t)3 * r * d * es : nullptr;
   group_bwd_seq(c, m, act_g);
 
   // ---- attention side ----
   single_up_bwd(c, b, dh1, d, act_o, ck->z_o, p->w_up_o, g->w_up_o, dz1, accumulate, lax, lx->dz_next_o, lx->dh_prev_o);
   // re-forward q, k, v, o
+  if (!act_once) {
+    const ActLayers aq{{ck->z_qkv}, {lx->h_prev_qkv}, {act_q}, {3 * row}, {}, 1};
+    LAUNCH(c, k_act_layers_bf16(aq, act_kind, c.st));
+  }
   GrpArgs a = qkv_group_args(b);
   a.x = x; a.gamma = p->gamma1; a.w_down_cat = p->w_dn_qkv; a.w_up_stack = p->w_up_qkv; a.y_stack = qkv;
   if (!sv) group_up_seq(c, a, act_q);
@@ -769,7 +776,7 @@ void block_bwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   a.zc = ck->z_qkv; a.statc = ck->s1; a.dy_stack = dqkv; a.dx = dx; a.dres = dh1; a.dres32 = dh1f; a.dgamma = g->gamma1;
   a.dw_down_cat = g->w_dn_qkv; a.dw_up_stack = g->w_up_qkv; a.accumulate = accumulate;
   a.lax = lax; a.dz_next = lx->dz_next_qkv; a.dh_prev = lx->dh_prev_qkv;
-  a.w_scaled = w_scaled;
+  a.w_scaled_given = fold_once; a.w_scaled = w_scaled;
   group_bwd_seq(c, a, act_q);
 }
 

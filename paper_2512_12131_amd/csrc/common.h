@@ -4,6 +4,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <initializer_list>
+
 #include "lrboost.h"
 
 namespace lrb {
@@ -99,8 +101,8 @@ int gemm_bf16_tile(const GemmOp& op);
 // partials: what a unit is depends on op.N alone, not on the tile.
 struct RowParts { int slabs, per_unit, units; };
 RowParts gemm_bf16_rowparts(const GemmOp& op);
-// the most slabs a product of N columns has on any tile (size queries)
-int gemm_bf16_rowpart_slabs_max(int N);
+// the most slabs the product has with any of these epilogues (size queries: they know the shape, not the epilogue)
+int gemm_bf16_rowpart_slabs_max(GemmOp op, std::initializer_list<int> kinds);
 // How `batch` weight gradients (both operands k-major, K = T) run.  Their sum over k is that of gemm_bf16_wgrad_splits()
 // parts, added up by the finishing pass (splitk) or inside the GEMM (k_parts); the other of the two is 1.
 // direct: the output needs no finishing pass when it is not split.

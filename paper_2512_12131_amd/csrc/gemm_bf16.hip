@@ -502,12 +502,11 @@ RowParts gemm_bf16_rowparts(const GemmOp& op) {
   return RowParts{(op.N + bn - 1) / bn * (bn / width), unit / width, (op.N + unit - 1) / unit};
 }
 
-int gemm_bf16_rowpart_slabs_max(int N) {
+int gemm_bf16_rowpart_slabs_max(GemmOp op, std::initializer_list<int> kinds) {
   int most = 0;
-  for (int tile = GEMM_T256; tile <= GEMM_R32; tile++) {
-    if (tile == GEMM_T256X128) continue;                           // two k-major operands only: no row partials
-    GemmOp op;
-    op.N = N; op.tile = tile;
+  op.tile = GEMM_TILE_AUTO;
+  for (int kind : kinds) {
+    op.epi.kind = kind;
     const int s = gemm_bf16_rowparts(op).slabs;
     if (s > most) most = s;
   }

@@ -193,3 +193,16 @@ def test_missing_library_fails_loudly(monkeypatch):
     monkeypatch.setattr(B, "LIB_PATH", "/nonexistent/liblrboost.so")
     with pytest.raises(B.LrError):
         B.lib()
+
+
+# (batch, seq, heads, key / value heads, d_ff, rank, backward) -> bytes that the tensors of the call need: the 7B block's
+# prefill and training step, the TP = 8 shard, the 1B block
+@pytest.mark.parametrize("shape,backward,need", [((1, 777, 32, 8, 11008, 1024), 0, 120812032), ((1, 777, 32, 8, 11008, 1024), 1, 198458624),
+                                                 ((4, 4096, 32, 32, 11008, 1024), 0, 1906311424), ((4, 4096, 32, 32, 11008, 1024), 1, 6929056000),
+                                                 ((4, 4096, 4, 4, 1376, 1024), 1, 1101988096), ((8, 2048, 16, 16, 5461, 512), 1, 2379809024)])
+def test_block_workspace_holds_nothing_twice(shape, backward, need):
+    """Nothing but the row partials' slabs and the weight-gradient partials may vary: 2 %.  (The gamma-folded weights of
+    the prefill, once more than used, are 35 %.)"""
+    Bn, S, H, kv, f, r = shape
+    desc = B.make_block_desc(Bn, S, 128 * H, H, 128, f, (f + 7) // 8 * 8, r, n_kv_heads=kv)
+    assert B.lr_block_workspace_bytes(desc, backward) <= 1.02 * need
