@@ -112,7 +112,7 @@ typedef uint32_t rsrc_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ rsrc_t make_rsrc(const void* base, uint32_t bytes) {
   const uint64_t a = (uint64_t)(uintptr_t)base;
   rsrc_t r = {(uint32_t)a, (uint32_t)(a >> 32) & 0xffffu, bytes, 0x00020000u};
-  return r;
+  return settle_rsrc(r);
 }
 __device__ __forceinline__ rsrc_t tile_rsrc(const uint16_t* base) { return make_rsrc(base, 0x7fffffffu); }
 
@@ -125,9 +125,9 @@ template <int BYTES>
 __device__ __forceinline__ void lds_dma(rsrc_t rs, const unsigned char* lds, uint32_t voff) {
   const uint32_t m0v = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)LRB_LDS_PTR(lds));
   if constexpr (BYTES == 16)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(m0v), "v"(voff), "s"(rs) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(m0v), "v"(voff), "s"(rs) : "m0", "memory");
   else
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(m0v), "v"(voff), "s"(rs) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(m0v), "v"(voff), "s"(rs) : "m0", "memory");
 }
 
 // Per-lane byte offsets (row * ld + logical chunk) of the 16 / NW wavefront loads that a wavefront of
