@@ -623,7 +623,8 @@ int launch_timer_end(lr_launch_record* out, int max_records, int* n_records) {
 
 hipError_t gemm_bf16(const GemmOp& op, hipStream_t st) {
   if (!g_timer.on || op.M <= 0 || op.N <= 0 || op.batch <= 0) return gemm_bf16_untimed(op, st);
-  const int tag = op.splitk > 1 ? (int)EPI_PARTIAL : op.epi.kind;
+  // two k-major operands: a weight gradient, also where it stores bf16 itself
+  const int tag = op.splitk > 1 || (op.transA && op.transB) ? (int)EPI_PARTIAL : op.epi.kind;
   const int slot = launch_timer_open(tag, op.M, op.N, op.K, op.batch, 2.0 * op.M * op.N * (double)op.K * op.batch, st);
   hipError_t e = gemm_bf16_untimed(op, st);
   launch_timer_close(slot, st);

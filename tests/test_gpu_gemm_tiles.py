@@ -130,3 +130,19 @@ def test_block_keeps_to_the_workspace_it_asks_for(accumulate, grad_dt):
     B.lr_block_bwd(desc, packed, x, dy, ck, grads=grads, accumulate=accumulate, ws=wb)
     torch.cuda.synchronize()
     assert bool((wf[nf:] == 0x5A).all()) and bool((wb[nb:] == 0x5A).all())
+
+
+def test_launch_records_name_weight_gradients_as_such():
+    # with bf16 gradients an un-split weight gradient is a plain bf16 store; it is a weight gradient all the same
+    T, d, r, n = 500, 256, 64, 344
+    c = si.linear_case(T, d, r, n, dtype=torch.bfloat16, seed=6)
+    x, wd, wu, dy = (c[k].to(DEV) for k in ("x", "w_down", "w_up", "dy"))
+    z, _ = B.lr_linear_fwd(x, wd, wu)
+    tags = {}
+    for grad_dt in (B.LR_F32, B.LR_BF16):
+        print(f"launch records of a backward, grad_dt={grad_dt}", flush=True)
+        B.lr_launch_timer_begin(16)
+        B.lr_linear_bwd(x, wd, wu, z, dy, grad_dt=grad_dt)
+        tags[grad_dt] = [rec[:5] for rec in B.lr_launch_timer_end()]
+    assert tags[B.LR_BF16] == tags[B.LR_F32]
+    assert sorted(rec[1:4] for rec in tags[B.LR_F32] if rec[0] == 5) == sorted([(n, r, T), (r, d, T)])
