@@ -305,7 +305,7 @@ hipError_t launch_ring(const GemmOp& op, hipStream_t st) {
   const int tiles_m = (op.M + T::BM - 1) / T::BM, tiles_n = (op.N + T::BN - 1) / T::BN;
   int kper = (op.K + op.splitk - 1) / op.splitk;
   kper = (kper + BK - 1) / BK * BK;    // a split ends on a slice boundary; a ragged last stage reads zeros
-  hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n, op.batch * op.splitk), dim3(T::NT), T::LDS_BYTES, st, op, kper, tiles_m, tiles_n);
+  hipLaunchKernelGGL(kern, tile_grid(tiles_m * tiles_n, op.batch * op.splitk), dim3(T::NT), T::LDS_BYTES, st, op, kper, tiles_m, tiles_n);
   return hipGetLastError();
 }
 

@@ -74,6 +74,12 @@ __device__ __forceinline__ void tile_of_block(int bid, int total, int tiles_m, i
   tm = panel * PM + within % pm_eff;
 }
 
+// The launch grid of `tiles` output tiles for each of `members` batch members times k splits.  The kernels number their
+// workgroups through both dimensions, so where the members are more than the second may have, all go into the first.
+inline dim3 tile_grid(int tiles, int members) {
+  return members <= 65535 ? dim3((unsigned)tiles, (unsigned)members) : dim3((unsigned)tiles * (unsigned)members);
+}
+
 #define LRB_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
 
 // ---- epilogue ---------------------------------------------------------------------------------

@@ -118,3 +118,21 @@ def test_attention_gqa_full_shape_sampled_group():
     check("dq", dq[rows, qc], dq_ref, dt, bud["dq"])
     check("dk", dk[rows, kc], dk_ref, dt, bud["dk"])
     check("dv", dv[rows, kc], dv_ref, dt, bud["dv"])
+
+
+def test_more_sequences_times_heads_than_a_grid_dimension_holds():
+    # the dQ product takes all heads of all sequences in one launch: 4100 x 16 of them here, above the 65536 that
+    # the second grid dimension may have
+    Bn, S, H, Hkv, n = 4100, 8, 16, 8, 3
+    print(f"B={Bn} S={S} H={H} Hkv={Hkv}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(8)
+    q, do = (torch.randn((Bn * S, H * 128), generator=g, device=DEV).bfloat16() for _ in range(2))
+    k, v = (torch.randn((Bn * S, Hkv * 128), generator=g, device=DEV).bfloat16() for _ in range(2))
+    o, lse = B.lr_attention_gqa_fwd(q, k, v, Bn, S, H, Hkv, 128)
+    full = B.lr_attention_gqa_bwd(q, k, v, o, do, lse, Bn, S, H, Hkv, 128)
+    torch.cuda.synchronize()
+    for sl, ls in ((slice(0, n * S), slice(0, n)), (slice((Bn - n) * S, Bn * S), slice(Bn - n, Bn))):
+        part = B.lr_attention_gqa_bwd(q[sl], k[sl], v[sl], o[sl], do[sl], lse[ls].contiguous(), n, S, H, Hkv, 128)
+        torch.cuda.synchronize()
+        for a, b in zip(part, full):
+            assert torch.equal(a, b[sl])
