@@ -307,7 +307,7 @@ int lr_attention_gqa_bwd(const void* q, const void* k, const void* v, const void
  * calls from other threads meanwhile.  Used by the benchmark for the per-class GEMM and attention rates
  * (Sec. 5.3 of the paper measures the same quantity per linear layer: kernel time and utilisation).
  * tag: the GEMM's epilogue class (0 store, 1 down-projection: row scale + sigma, 2 / 10 / 11 up-projection
- * + residual, 3 sigma' (+ row statistic), 4 / 12 / 13 RMSNorm backward, 5 split-K weight-gradient partial,
+ * + residual, 3 sigma' (+ row statistic), 4 / 12 / 13 RMSNorm backward, 5 weight gradient,
  * 6 SwiGLU backward, 7 SwiGLU forward, 8 / 9 the LaX forms), or LR_TAG_ATTN_FWD / LR_TAG_ATTN_BWD.
  * flops: 2 M N K batch for a GEMM; causal-halved 2 S^2 hd per (batch, head) and product for attention
  * (2 products forward, 5 backward).                                                               */
@@ -320,6 +320,10 @@ typedef struct {
 } lr_launch_record;
 int lr_launch_timer_begin(int max_launches);
 int lr_launch_timer_end(lr_launch_record* records, int max_records, int* n_records);
+/* Rows and columns of the output tile that a bf16 product of `batch` members C[M, N] over K runs on: form 0 both
+ * operands k-contiguous (activation . weight^T), 1 the second one k-major (gradient . weight), 2 both k-major (weight
+ * gradient, not accumulated, nothing folded in); tag: its epilogue class, as above.  Makes no GPU call.   */
+int lr_gemm_tile(int M, int N, int K, int batch, int form, int tag, int* rows, int* cols);
 /* Sustained rate of the bf16 matrix pipes fed from registers alone (no LDS, no memory traffic):
  * 2048 wavefronts, 8 independent 32x32x16 accumulator tiles each, iters instructions per tile and
  * launch, `launches` timed launches after up to 4 untimed ones, on `stream`; *tflops (HOST pointer)

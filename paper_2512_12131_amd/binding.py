@@ -94,6 +94,7 @@ _SIGS = {
                                     _int, _int, _vp, _sz, _vp]),
     "lr_launch_timer_begin": (_int, [_int]),
     "lr_launch_timer_end": (_int, [_vp, _int, C.POINTER(_int)]),
+    "lr_gemm_tile": (_int, [_int, _int, _int, _int, _int, _int, C.POINTER(_int), C.POINTER(_int)]),
     "lr_mfma_probe": (_int, [_int, _int, _int, C.POINTER(C.c_double), _vp]),
     "lr_rms_stat": (_int, [_vp, _i64, _vp, _i64, _i64, _int, _vp]),
     "lr_rmsnorm_apply": (_int, [_vp, _i64, _vp, _vp, _f32, _vp, _i64, _i64, _i64, _int, _vp]),
@@ -494,6 +495,14 @@ def lr_launch_timer_end():
     n = _int(0)
     _check(lib().lr_launch_timer_end(C.cast(buf, _vp), _timer_cap, C.byref(n)), "lr_launch_timer_end")
     return [(r.tag, r.M, r.N, r.K, r.batch, r.ms, r.flops) for r in buf[:min(n.value, _timer_cap)]]
+
+
+def lr_gemm_tile(M, N, K, batch=1, form=0, tag=0):
+    """(rows, columns) of the output tile a bf16 product runs on; form 0: activation . weight^T, 1: gradient . weight,
+    2: weight gradient; tag: the epilogue class of its launch record."""
+    rows, cols = _int(0), _int(0)
+    _check(lib().lr_gemm_tile(M, N, K, batch, form, tag, C.byref(rows), C.byref(cols)), "lr_gemm_tile")
+    return rows.value, cols.value
 
 
 def lr_mfma_probe(random_operands=True, iters=20000, launches=20):

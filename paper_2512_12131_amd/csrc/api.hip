@@ -1213,6 +1213,16 @@ int lr_launch_timer_end(lr_launch_record* records, int max_records, int* n_recor
   return launch_timer_end(records, max_records, n_records) == 0 ? LR_OK : LR_EINVAL;
 }
 
+int lr_gemm_tile(int M, int N, int K, int batch, int form, int tag, int* rows, int* cols) {
+  if (M <= 0 || N <= 0 || K <= 0 || batch <= 0 || form < 0 || form > 2 || tag < 0 || tag > EPI_NORMBWD_I32 || !rows || !cols)
+    return LR_EINVAL;
+  GemmOp op;
+  op.M = M; op.N = N; op.K = K; op.batch = batch; op.epi.kind = tag;
+  if (form == 1) { op.transB = 1; op.ldb = N; }
+  gemm_bf16_tile_size(form == 2 ? gemm_bf16_plan_wgrad(M, N, K, batch, true).tile : gemm_bf16_tile(op), rows, cols);
+  return LR_OK;
+}
+
 // ---- standalone memory-bound kernels ---------------------------------------------------------
 int lr_rms_stat(const void* x, int64_t ldx, float* stat, int64_t T, int64_t d, int dt, void* stream) {
   TRY(check_dt(dt));

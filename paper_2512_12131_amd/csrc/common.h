@@ -96,6 +96,7 @@ enum GemmTile : int { GEMM_TILE_AUTO = 0, GEMM_T256 = 1, GEMM_T256X128 = 2, GEMM
 
 // The tile gemm_bf16 runs `op` with (op.tile if set, else by estimated time; see gemm_bf16.hip).
 int gemm_bf16_tile(const GemmOp& op);
+void gemm_bf16_tile_size(int tile, int* rows, int* cols);
 // Row partials the bf16 kernel emits with `op`, per batch member: `slabs` columns (rowpart_ld must be >= slabs *
 // batch), each the sum over 64 or 32 output columns.  A row's sum is formed from `units` runs of `per_unit` consecutive
 // partials: what a unit is depends on op.N alone, not on the tile.

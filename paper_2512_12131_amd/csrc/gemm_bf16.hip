@@ -492,6 +492,11 @@ int gemm_bf16_tile(const GemmOp& op) {
   return tile;
 }
 
+void gemm_bf16_tile_size(int tile, int* rows, int* cols) {
+  *rows = kTileCost[tile].bm;
+  *cols = kTileCost[tile].bn;
+}
+
 RowParts gemm_bf16_rowparts(const GemmOp& op) {
   const int tile = gemm_bf16_tile(op), bn = kTileCost[tile].bn;
   const int width = bn <= 64 ? 32 : 64;                            // columns per partial (gemm_tile.h)

@@ -206,3 +206,12 @@ def test_block_workspace_holds_nothing_twice(shape, backward, need):
     Bn, S, H, kv, f, r = shape
     desc = B.make_block_desc(Bn, S, 128 * H, H, 128, f, (f + 7) // 8 * 8, r, n_kv_heads=kv)
     assert B.lr_block_workspace_bytes(desc, backward) <= 1.02 * need
+
+
+def test_gemm_tile_query():
+    assert B.lr_gemm_tile(16, 1024, 4096, 1, 0, 1) == (32, 32)           # a handful of rows
+    assert B.lr_gemm_tile(16384, 11008, 1024, 1, 0, 0) == (256, 256)     # the chip full, k long
+    assert B.lr_gemm_tile(16384, 128, 4096, 1, 0, 1) == (64, 128)        # half of a 256-row tile's columns
+    for bad in ((0, 8, 8, 1, 0, 0), (8, 8, 8, 0, 0, 0), (8, 8, 8, 1, 3, 0), (8, 8, 8, 1, 0, 14), (8, 8, 8, 1, 0, -1)):
+        with pytest.raises(B.LrError):
+            B.lr_gemm_tile(*bad)

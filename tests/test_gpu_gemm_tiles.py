@@ -31,6 +31,67 @@ def test_rows_do_not_depend_on_the_tile(norm):
         assert norm == B.LR_NORM_NONE or torch.equal(s1, s[:t])
 
 
+@pytest.mark.parametrize("norm", [B.LR_NORM_NONE, B.LR_NORM_ONLINE])
+def test_rows_of_a_backward_do_not_depend_on_the_tile(norm):
+    # the weight read k-major in place by the small tiles, a transposed copy by the 256-row one; with a norm also the row dots,
+    # which arrive in partials of 32 or 64 columns (200: several units, the last one not full)
+    T, d, r, n, G = 16384, 1032, 200, 520, 3
+    g = torch.Generator(device=DEV).manual_seed(13)
+    x, z, gamma = (torch.randn(s, generator=g, device=DEV).bfloat16() for s in ((T, d), (T, G * r), (d,)))
+    wd = (torch.randn((G * r, d), generator=g, device=DEV) * d ** -0.5).bfloat16()
+    wu = (torch.randn((G, n, r), generator=g, device=DEV) * r ** -0.5).bfloat16()
+    dy, stat = torch.randn((G, T, n), generator=g, device=DEV).bfloat16(), x.float().square().sum(1)
+    dx = B.lr_group_bwd(x, gamma, 1e-5, norm, wd, wu, z, stat, dy)[0]
+    for t in (1, 63, 129, 777, 2048, 5000):
+        print(f"rows of dx t={t} norm={norm}", flush=True)
+        dx1 = B.lr_group_bwd(x[:t].contiguous(), gamma, 1e-5, norm, wd, wu, z[:t].contiguous(), stat[:t].contiguous(),
+                             dy[:, :t].contiguous())[0]
+        torch.cuda.synchronize()
+        assert torch.equal(dx1, dx[:t])
+
+
+@pytest.mark.parametrize("lax", [False, True])
+def test_sequences_of_a_block_do_not_depend_on_the_batch(lax):
+    # 48, 24, 6 and 1 sequences of 333 tokens: all tiles, every epilogue of the block (the LaX forms among them), both row
+    # statistics.  One sequence runs on tiles that the oracle tests cover, so the others are tied to them.
+    Bn, S, H, f, r = 48, 333, 16, 5000, 520
+    d = 128 * H
+    down, grad = (8, 9) if lax else (1, 3)
+    assert B.lr_gemm_tile(Bn * S, r, d, 1, 0, down) == T256 and B.lr_gemm_tile(Bn * S, r, d, 1, 1, grad) == T256
+    assert B.lr_gemm_tile(24 * S, r, d, 1, 0, down) == R128 and B.lr_gemm_tile(6 * S, r, d, 1, 0, down) == R64X128
+    case = si.block_case(1, S, d, H, 128, f, r, seed=14)
+    p = {k: v.to(DEV) for k, v in si.pack_block_params(case["params"], f, f).items()}
+    g = torch.Generator(device=DEV).manual_seed(15)
+
+    def rand(*shape):
+        return torch.randn(shape, generator=g, device=DEV).bfloat16()
+
+    wide = {"qkv": 3, "o": 1, "gu": 2, "d": 1}
+    x, dy = rand(Bn * S, d), rand(Bn * S, d)
+    h, dz = ({n: rand(Bn * S, w * r) for n, w in wide.items()} for _ in range(2))
+
+    def step(nb):
+        t = nb * S
+        sy = torch.empty((t,), dtype=torch.float32, device=DEV)
+        desc = B.make_block_desc(nb, S, d, H, 128, f, f, r, stat_y_out=sy, act=B.LR_ACT_IDENTITY if lax else B.LR_ACT_SILU)
+        if not lax:
+            y, ck = B.lr_block_fwd(desc, p, x[:t])
+            dx, _ = B.lr_block_bwd(desc, p, x[:t], dy[:t], ck)
+            return {"y": y, "stat_y": sy, "dx": dx, **ck}
+        hp, dn = ({n: a[:t] for n, a in src.items()} for src in (h, dz))
+        y, ck = B.lr_block_lax_fwd(desc, p, x[:t], h_prev=hp)
+        dx, _, dh = B.lr_block_lax_bwd(desc, p, x[:t], dy[:t], ck, h_prev=hp, dz_next=dn)
+        return {"y": y, "stat_y": sy, "dx": dx, **ck, **{"dh_" + n: a for n, a in dh.items()}}
+
+    full = step(Bn)
+    for nb in (24, 6, 1):
+        print(f"{nb} sequences, lax={lax}", flush=True)
+        part = step(nb)
+        torch.cuda.synchronize()
+        off = [n for n, a in part.items() if not torch.equal(a, full[n][:nb * S])]
+        assert not off, f"{nb} sequences: {', '.join(off)}"
+
+
 def test_query_gradient_does_not_depend_on_the_tile():
     # 16, 4 and 1 sequences of 512 tokens, 16 heads: three tiles of the dQ product
     S, H = 512, 16
@@ -87,6 +148,41 @@ def test_linear_at_tile_edges(T, d_in, r, d_out):
     # the accumulating form adds the same sum to what is there
     for a, b in zip(acc, (dwd, dwu)):
         assert float((a - 2 * b).norm() / b.norm()) < 1e-5
+
+
+# Larger layers, no size a multiple of a tile: the tiles that the edges above do not reach.  Which tile runs a product is asserted,
+# so that another choice of tiles cannot take a tile out of the test unseen.
+T256, T256X128, R128, R64X128, R64, R32 = (256, 256), (256, 128), (128, 128), (64, 128), (64, 64), (32, 32)
+LARGE = [(12001, 2056, 776, 1032, dict(z=T256, y=T256, dz=T256, dx=T256, dw_up=T256, dw_down=T256)),
+         (12001, 1032, 264, 520, dict(z=R128, y=R128, dz=R128, dx=R128, dw_up=R128, dw_down=R64X128)),
+         (6001, 2056, 136, 1032, dict(z=R64X128, dz=R64X128, dw_up=R64X128, dw_down=T256X128)),
+         (6001, 520, 72, 520, dict(z=R64, y=R64X128, dz=R64, dx=R64X128, dw_up=R64, dw_down=R64))]
+
+
+@pytest.mark.parametrize("T,d_in,r,d_out,tiles", LARGE)
+def test_linear_at_the_edges_of_the_large_tiles(T, d_in, r, d_out, tiles):
+    print(f"linear T={T} d_in={d_in} r={r} d_out={d_out}", flush=True)
+    run = dict(z=B.lr_gemm_tile(T, r, d_in, 1, 0, 1), y=B.lr_gemm_tile(T, d_out, r, 1, 0, 0), dz=B.lr_gemm_tile(T, r, d_out, 1, 1, 3),
+               dx=B.lr_gemm_tile(T, d_in, r, 1, 1, 0), dw_up=B.lr_gemm_tile(d_out, r, T, 1, 2, 5), dw_down=B.lr_gemm_tile(r, d_in, T, 1, 2, 5))
+    assert {k: run[k] for k in tiles} == tiles
+    c = si.linear_case(T, d_in, r, d_out, dtype=torch.bfloat16, seed=3)
+    x, wd, wu, dy = (c[k].to(DEV) for k in ("x", "w_down", "w_up", "dy"))
+    z, y = B.lr_linear_fwd(x, wd, wu)
+    dx, dwd, dwu = B.lr_linear_bwd(x, wd, wu, z, dy)
+    _, dwd16, dwu16 = B.lr_linear_bwd(x, wd, wu, z, dy, grad_dt=B.LR_BF16)
+    acc = (dwd.clone(), dwu.clone())
+    B.lr_linear_bwd(x, wd, wu, z, dy, grads=acc)
+    torch.cuda.synchronize()
+    # bf16 gradients are the fp32 ones rounded once; added onto themselves they double
+    assert torch.equal(dwd16, dwd.bfloat16()) and torch.equal(dwu16, dwu.bfloat16())
+    assert torch.equal(acc[0], 2 * dwd) and torch.equal(acc[1], 2 * dwu)
+    X, WD, WU, DY = (si.f64(c[k]) for k in ("x", "w_down", "w_up", "dy"))
+    z_ref, _, y_ref = orc.lr_linear_fwd(X, WD, WU, B.LR_ACT_SILU)
+    refs = orc.lr_linear_bwd(X, WD, WU, DY, B.LR_ACT_SILU)
+    ideal = _ideal_bf16_linear(X, WD, WU, DY)
+    for n, got, ref in (("z", z, z_ref), ("y", y, y_ref), ("dx", dx, refs[0]), ("dw_down", dwd, refs[1]), ("dw_up", dwu, refs[2])):
+        check(n, got, ref, torch.bfloat16, (relerr(ideal[n], ref), l2_and_slope(ideal[n], ref)[0]))
+        print(n, "agrees", flush=True)
 
 
 # fp32: odd sizes and leading dimensions (no 16-byte loads), k tails of 1 to 3, four and sixteen wavefronts per

@@ -23,7 +23,7 @@ LIN_CASES = [
     (1, 8, 8, 8, torch.float32),
     (512, 256, 64, 256, torch.bfloat16),
     (600, 320, 72, 264, torch.bfloat16),      # nothing a multiple of the 256 / 128 / 64 tiles
-    (1031, 1024, 256, 768, torch.bfloat16),   # odd T, several k slices, both tile shapes
+    (1031, 1024, 256, 768, torch.bfloat16),   # odd T, several k slices
     (3, 8, 8, 8, torch.bfloat16),
 ]
 
