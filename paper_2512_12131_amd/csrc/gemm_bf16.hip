@@ -1,8 +1,10 @@
 // bf16 MFMA GEMM for gfx950:  C[M,N] = epi( sum_k A[m,k] * B[n,k] ), fp32 accumulate.
 //
-// Two operand forms.  k-contiguous ("NT": the forward projections x.W^T, and the data-gradient GEMMs
-// after the small weight matrices have been transposed once): slices land in LDS as [row][k] and the
-// MFMA operands are plain 16-byte reads.  k-major (weight gradients, which reduce over tokens): slices
+// The 256-row tiles, and the choice between them and the smaller ones of gemm_ring.h.
+//
+// Two operand forms.  k-contiguous ("NT": the forward projections x.W^T, and those data gradients that run on
+// these tiles, on a transposed copy of the weight; the smaller tiles read it in place): slices land in LDS as
+// [row][k] and the MFMA operands are plain 16-byte reads.  k-major (weight gradients, which reduce over tokens): slices
 // land as [k][column] and the operands are gathered with the LDS transpose read.  The k-major form with
 // a plain bf16 store, batched with two-level strides and with the k range of a row tile cut at its last
 // row, also computes the attention's query gradient from the stored score gradient.
@@ -396,10 +398,14 @@ hipError_t dispatch(const GemmOp& op, hipStream_t st) {
 // Estimated microseconds of a launch.  A tile kind runs `slots` workgroups at a time; a round of them takes a
 // fixed time f (pipeline fill), the epilogue g * e + h * e and nk 64-wide k slices of s0 + s1 each, where s1 and g
 // are what the slices and the epilogue lose to each other when every slot is busy (they scale with the share
-// of slots in use) and e is the traffic of the epilogue in units of one bf16 output.  The coefficients are fits to
-// 1770 measured launches (M 64 .. 16384, N 64 .. 11008, K 64 .. 11008, nine epilogue kinds, k-contiguous operands),
-// which they reproduce to 7-11 % rms; always taking the estimated best loses 1 % (geometric mean) against the
-// measured best, where the 256-row tiles alone took 1.93 times as long.  What the lines amount to, with both sides measured (us):
+// of slots in use) and e is the traffic of the epilogue in units of one bf16 output.  The rows of T256, R64, R64X128 and R128
+// are least-squares fits of the relative error over 1770 measured launches with k-contiguous operands (M 64 .. 16384, N 64 ..
+// 11008, K 64 .. 11008, nine epilogue kinds), T256X128's over the plain stores among them; R32's is its measured slice time
+// and start-up, set by hand.  Against 1648 launches of the kernels as they are (888 forward products, M from 16; 400 data
+// gradients; 360 weight gradients), the estimates of tiles within 1.5 times the best are off by 8-16 % rms, R32's by 17-19 %
+// (10-15 % too fast on average).  Taking the estimated best loses 1.7 % (forward) and 1.9 % (data gradients) in the geometric mean
+// against the measured best; the 256-row tiles alone take 2.13 times as long as that over the forward products.  What the
+// lines amount to, with both sides measured (us):
 //   a handful of rows: one chain of k per CU        16 x 1024 x 4096:   T256 67.6   R64    15.0   R32 9.4
 //   few tiles, the loads' latency decides          777 x 1024 x 4096:   T256 68.0   R64    16.1   R32 25.9
 //   half the CUs idle under T256                 16384 x 512 x 2048:   T256 45.6   R128   37.6
@@ -419,7 +425,7 @@ constexpr TileCost kTileCost[] = {
     {64, 128, 512, 2.08f, 1.38f, 0.231f, 0.306f, 1.05f, 0.095f},    // GEMM_R64X128
     {128, 128, 512, 2.48f, 0.80f, 0.479f, 0.451f, 2.42f, 0.142f},   // GEMM_R128
     {32, 32, 512, 2.00f, 1.00f, 0.095f, 0.080f, 0.30f, 0.140f},     // GEMM_R32
-    {128, 128, 256, 2.27f, 1.88f, 0.361f, 0.156f, 0.78f, 0.f},      // GEMM_R128W (causal products only)
+    {128, 128, 256, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f},                  // GEMM_R128W: causal products, chosen by rule below
 };
 // bf16-output equivalents an epilogue moves (reads and writes, secondary outputs included)
 float epi_traffic(int kind) {
@@ -445,8 +451,9 @@ float tile_time(int tile, int M, int N, int nk, int members, float e, float slic
 constexpr float kRingMargin = 1.075f;
 // What a slice costs more with two k-major operands.  The 256-row kernels pay for their transpose reads.  The ring
 // tiles read 128 or 256 bytes per k row where those read 512, which shows when the rows come from HBM (2048 x 512
-// over 16384 tokens: R64x128 in 4 splits 60 us, T256 in 16 splits 45 us plus 6 us more in the finishing pass).
-constexpr float kKMajorSlice[] = {0.f, 1.13f, 1.05f, 1.5f, 1.5f, 1.3f, 1.5f, 1.f};
+// over 16384 tokens: R64x128 in 4 splits 60 us, T256 in 16 splits 45 us plus 6 us more in the finishing pass).  With these
+// factors the estimates of 360 weight gradients (512 .. 16384 tokens) are off by +4, -7, -1, +7, +9 and -12 % on average.
+constexpr float kKMajorSlice[] = {0.f, 1.13f, 1.05f, 1.5f, 1.5f, 1.3f, 1.5f};
 
 }  // namespace
 

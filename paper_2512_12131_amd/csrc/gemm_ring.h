@@ -5,12 +5,12 @@
 // that is set by the latency of its global->LDS loads, not by the matrix pipes.  So the tiles are small (the
 // output spreads over more CUs) and the loads run far ahead: a ring of NS LDS stages, NS - 1 of them in
 // flight, one barrier per stage.  The small tiles read each operand element more often than the 256 x 256
-// tile does, which is why that one keeps the launches that fill the chip (gemm_bf16_route).
+// tile does, which is why that one keeps the launches that fill the chip (gemm_bf16_tile).
 //
 // Every output element is summed by the same MFMA instruction in the same k order, and from the same k slots,
 // as in the 256-row kernel: which of the two kernels runs a product does not change its
 // bits, so a token's result does not depend on how many tokens share the call.  The row statistics keep to that
-// too: k_rowsum_parts adds the narrower row partials of these tiles up in the order a 128-column wavefront does.
+// too: k_rowsum_parts adds the narrower row partials of these tiles up in the order in which a wider wavefront does.
 //
 // Measured (us, this kernel's best tile against the 256-row kernel): 777 x 1024 x 11008 37 / 172, 1031 x 256 x 1024
 // 6.5 / 22, 16384 x 128 x 4096 30 / 72, 512 x 256 x 64 4.2 / 7.2.  A 64 x 64 tile takes 0.21 us per 64-wide slice: a

@@ -83,7 +83,7 @@ inline dim3 tile_grid(int tiles, int members) {
 #define LRB_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
 
 // ---- epilogue ---------------------------------------------------------------------------------
-// Called by every wavefront of a workgroup once its accumulators are final and the main loop's LDS is dead.
+// Called by every wavefront that holds accumulators once they are final and the main loop's LDS is dead.
 // Tile type T: BM rows; WN wavefronts across, each with an FM x FN arrangement of 32x32 MFMA blocks (TM x TN);
 // CS = fp32 row stride of the staging tile.  (m0, n0): first row / column of the output tile, tn its column
 // index, b / (bi, bo) / bz: batch member, its two-level split, batch member times k split.  sStat: the row
