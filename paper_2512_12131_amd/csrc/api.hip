@@ -670,9 +670,12 @@ void block_bwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   // What small blocks wait for are launches, so theirs rebuild all layers' activations in one and fold both norms' gammas in
   // one (8 launches of 2.4 us less at 512 tokens).  Large ones keep to the buffers that the two sides share (67 MB of
   // activations and 25 MB of weights at 16384 tokens of the 7B shape, where a launch is 12 us and more of work).
-  const bool act_once = 7 * T * r * (int64_t)es <= (16 << 20), fold_once = 5 * r * d * (int64_t)es <= (16 << 20);
-  void* act_g = c.take((size_t)T * (act_once ? 2 : 3) * r * es);            // sigma(z_gu)
-  void* act_q = act_once ? c.take((size_t)T * 3 * r * es) : act_g;          // sigma(z_qkv)
+  constexpr int64_t ONCE = 16 << 20;
+  const int64_t row = T * r * (int64_t)es;
+  const bool act_once = 7 * row <= ONCE, fold_once = 5 * r * d * (int64_t)es <= ONCE;
+  // (no less in all than the largest of the small takes: a workspace for more tokens serves for fewer)
+  void* act_g = c.take(act_once ? 2 * row : 3 * row > ONCE / 7 * 5 + 512 ? 3 * row : ONCE / 7 * 5 + 512);   // sigma(z_gu)
+  void* act_q = act_once ? c.take(3 * row) : act_g;                                                       // sigma(z_qkv)
   void* dz1 = c.take((size_t)T * r * es);         // dz_d, later dz_o
   void* h1 = sv ? sv->h1 : c.take((size_t)T * d * es);
   void* dh1 = c.take((size_t)T * d * es);
@@ -702,7 +705,6 @@ void block_bwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   }
 
   // rank-r activations of the layers (z + h_prev in the LaX variant), and the weights with gamma folded in
-  const int64_t row = T * r * (int64_t)es;
   const int act_kind = lax ? (int)LR_ACT_IDENTITY : b.act;
   const ActLayers al{{ck->z_d, ck->z_o, ck->z_gu, ck->z_qkv}, {lx->h_prev_d, lx->h_prev_o, lx->h_prev_gu, lx->h_prev_qkv},
                      {act_d, act_o, act_g, act_q}, {row, row, 2 * row, 3 * row}, {}, act_once ? 4 : 3};

@@ -215,3 +215,14 @@ def test_gemm_tile_query():
     for bad in ((0, 8, 8, 1, 0, 0), (8, 8, 8, 0, 0, 0), (8, 8, 8, 1, 3, 0), (8, 8, 8, 1, 0, 14), (8, 8, 8, 1, 0, -1)):
         with pytest.raises(B.LrError):
             B.lr_gemm_tile(*bad)
+
+
+@pytest.mark.parametrize("shape", [(32, 8, 11008, 1024), (4, 4, 1376, 1024), (8, 8, 2594, 256), (3, 1, 1003, 152)])
+def test_a_block_workspace_for_more_tokens_serves_for_fewer(shape):
+    H, kv, f, r = shape
+    for backward in (0, 1):
+        sizes = []
+        for S in [*range(8, 1500, 8), *range(1536, 16385, 128)]:
+            desc = B.make_block_desc(1, S, 128 * H, H, 128, f, (f + 7) // 8 * 8, r, n_kv_heads=kv)
+            sizes.append(B.lr_block_workspace_bytes(desc, backward))
+        assert sizes == sorted(sizes)
