@@ -112,7 +112,10 @@ typedef uint32_t rsrc_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ rsrc_t make_rsrc(const void* base, uint32_t bytes) {
   const uint64_t a = (uint64_t)(uintptr_t)base;
   rsrc_t r = {(uint32_t)a, (uint32_t)(a >> 32) & 0xffffu, bytes, 0x00020000u};
-  return settle_rsrc(r);
+  // Five wait states have to pass between a vector write of a scalar (v_readfirstlane) and a buffer instruction that reads
+  // it; the compiler does not look for buffer instructions inside lds_dma's assembly.
+  asm volatile("s_nop 4" : "+s"(r));
+  return r;
 }
 __device__ __forceinline__ rsrc_t tile_rsrc(const uint16_t* base) { return make_rsrc(base, 0x7fffffffu); }
 

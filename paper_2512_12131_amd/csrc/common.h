@@ -211,15 +211,6 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-// A buffer descriptor as four scalars, for buffer loads written as inline assembly.  Five wait states have to pass
-// between a vector write of a scalar register (v_readfirstlane) and a buffer instruction that reads it; the compiler keeps
-// them before instructions it knows, this does before the first use inside an assembly block.
-typedef uint32_t rsrc_words __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ rsrc_words settle_rsrc(rsrc_words r) {
-  asm volatile("s_nop 4" : "+s"(r));
-  return r;
-}
-
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t lo16) { return __uint_as_float(lo16 << 16); }
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));

@@ -60,19 +60,22 @@ struct RingTile {
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 
+typedef uint32_t rsrc_words __attribute__((ext_vector_type(4)));
+
 // One 1 KB global -> LDS load of a wavefront: lane L's 16 bytes land at lds + 16 L.  Inline assembly, because
 // through the builtin the compiler makes later LDS reads wait for every load in flight; completion is counted
 // by hand (wait_vmcnt before the barrier that publishes a stage).  No output register is written.  The compiler's hazard
-// pass does not see a memory instruction in here, so the descriptor has to be settled (settle_rsrc) and must not be
-// reloaded from a spill close before: that is another vector write of the scalars that the load reads.
+// pass does not see a memory instruction in here, so the block itself makes the five wait states that have to pass between a
+// vector write of a scalar (the v_readfirstlane of operand_rsrc, the reload of a spill) and a buffer instruction that
+// reads it.  (Waiting once, behind the descriptor, costs the shortest launches more: 16-token layer 15.1 -> 15.6 us.)
 __device__ __forceinline__ void dma16(rsrc_words rs, uint32_t lds, uint32_t voff) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(rs) : "m0", "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(rs) : "m0", "memory");
 }
 __device__ __forceinline__ rsrc_words operand_rsrc(const void* base) {
   const uint64_t a = (uint64_t)(uintptr_t)base;
-  rsrc_words r = {(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a),
+  const rsrc_words r = {(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a),
                         (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(a >> 32) & 0xffffu)), 0x7fffffffu, 0x00020000u};
-  return settle_rsrc(r);
+  return r;
 }
 
 // Swizzle of a k-major stage ([k][W columns], 2 W bytes per k row): the term XORed into the 16-byte chunk index
