@@ -65,11 +65,16 @@ typedef uint32_t rsrc_words __attribute__((ext_vector_type(4)));
 // One 1 KB global -> LDS load of a wavefront: lane L's 16 bytes land at lds + 16 L.  Inline assembly, because
 // through the builtin the compiler makes later LDS reads wait for every load in flight; completion is counted
 // by hand (wait_vmcnt before the barrier that publishes a stage).  No output register is written.  The compiler's hazard
-// pass does not see a memory instruction in here, so the block itself makes the five wait states that have to pass between a
-// vector write of a scalar (the v_readfirstlane of operand_rsrc, the reload of a spill) and a buffer instruction that
-// reads it.  (Waiting once, behind the descriptor, costs the shortest launches more: 16-token layer 15.1 -> 15.6 us.)
+// pass does not see a memory instruction in here, so the loads that follow the making of the descriptors (FIRST) make the five
+// wait states themselves that have to pass between a vector write of a scalar (the v_readfirstlane of operand_rsrc) and a
+// buffer instruction that reads it; a descriptor reloaded from a spill would be another.  (Five in every load: 3-5 % of a
+// launch on 64 x 128 and 128 x 128 tiles; in a block of their own behind the descriptors: 16-token layer 15.2 -> 15.6 us.)
+template <bool FIRST>
 __device__ __forceinline__ void dma16(rsrc_words rs, uint32_t lds, uint32_t voff) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(rs) : "m0", "memory");
+  if constexpr (FIRST)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(rs) : "m0", "memory");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(rs) : "m0", "memory");
 }
 __device__ __forceinline__ rsrc_words operand_rsrc(const void* base) {
   const uint64_t a = (uint64_t)(uintptr_t)base;
@@ -147,7 +152,7 @@ __global__ __launch_bounds__(T::NT) void gemm_ring_kernel(GemmOp op, int kper, i
   // Load I (compile-time, 0 .. LPS - 1) of stage `it` into ring slot `slot`.  k past the end of the range (also
   // whole stages past it) reads as zeros, so the loop needs no tail code and the counts of loads in flight are
   // constants.
-  auto issue_one = [&](int it, int slot, auto I) {
+  auto issue_one = [&](int it, int slot, auto I, auto FIRST) {
     constexpr int s = decltype(I)::value / (T::LA + T::LB), j = decltype(I)::value % (T::LA + T::LB);
     constexpr bool is_a = j < T::LA, km = is_a ? AKM : BKM;
     constexpr int i = is_a ? j : j - T::LA, W = is_a ? T::BM : T::BN, RPL = 512 / W;
@@ -156,7 +161,7 @@ __global__ __launch_bounds__(T::NT) void gemm_ring_kernel(GemmOp op, int kper, i
     const bool in = (k0 + (is_a ? kA : kB) + (km ? i * T::NWL * RPL : 0)) < klen;
     const uint32_t dst = sbase + (uint32_t)(slot * T::STAGE + s * T::SLICE + (is_a ? 0 : T::A_BYTES)) +
                          (uint32_t)(lw + T::NWL * i) * 1024u;
-    dma16(is_a ? rsA : rsB, dst, in ? (is_a ? offA[is_a ? i : 0] : offB[is_a ? 0 : i]) + adv : OOB);   // OOB + adv stays past the resource
+    dma16<decltype(FIRST)::value>(is_a ? rsA : rsB, dst, in ? (is_a ? offA[is_a ? i : 0] : offB[is_a ? 0 : i]) + adv : OOB);   // OOB + adv stays past the resource
   };
 
   // MFMA operands: 32 rows (lane % 32) x 8 consecutive k (k16 step kk, half lane / 32) from either layout
@@ -200,11 +205,24 @@ __global__ __launch_bounds__(T::NT) void gemm_ring_kernel(GemmOp op, int kper, i
 #pragma unroll
       for (int j = 0; j < T::FN; j++) tot[i][j] = acc[i][j];
   }
-  float ssq = 0.f;           // STAT_A: sum of squares of tile row tid / TPR, the same in its TPR threads
+  // STAT_A: sum of squares of tile row tid / TPR, in the first of its TPR threads, and this thread's chunk sums of a stage.
+  // That thread adds the eight chunk sums of a slice, the others' from their registers, in the order they lie in LDS, as the one
+  // thread per row of the 256-row kernel does: same bits whichever tile runs.
+  constexpr int CPT = 8 / T::TPR;
+  float ssq = 0.f, cs[T::SUB * CPT] = {};
+  auto add_chunks = [&] {
+    static_for<T::SUB * 8>([&](auto C) {
+      constexpr int c = decltype(C)::value % 8, j = c / CPT;   // chunk of the slice; the thread of the row that holds it
+      constexpr int ctrl = T::TPR == 4 ? j * 0x55 : 0xF5;      // quad_perm [j,j,j,j] / [1,1,3,3]
+      const float v = cs[decltype(C)::value / 8 * CPT + c % CPT];
+      if constexpr (j == 0) ssq += v;
+      else ssq += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), ctrl, 0xf, 0xf, true));
+    });
+  };
 
 #pragma unroll
   for (int s = 0; s < T::NS - 1; s++)
-    if (lw >= 0) static_for<T::LPS>([&](auto I) { issue_one(s, s, I); });
+    if (lw >= 0) static_for<T::LPS>([&](auto I) { issue_one(s, s, I, std::true_type{}); });
   int rd = 0, wr = T::NS - 1;                            // slots read from and written to
   for (int it = 0; it < nit; it++) {
     // this wavefront's loads of stage `it` have landed (loads retire in order), and its reads of the stage
@@ -215,7 +233,7 @@ __global__ __launch_bounds__(T::NT) void gemm_ring_kernel(GemmOp op, int kper, i
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     if constexpr (T::NL > 0) {
-      if (lw >= 0) static_for<T::LPS>([&](auto I) { issue_one(it + T::NS - 1, wr, I); });
+      if (lw >= 0) static_for<T::LPS>([&](auto I) { issue_one(it + T::NS - 1, wr, I, std::false_type{}); });
     }
     if (T::NL == 0 || lw < 0) {
       // all operand reads of the stage first, then the next stage's loads among the MFMAs: a CU accepts one 1 KB
@@ -248,7 +266,7 @@ __global__ __launch_bounds__(T::NT) void gemm_ring_kernel(GemmOp op, int kper, i
           }
         }
         constexpr int l0 = kk * T::LPS / KSTEPS, l1 = (kk + 1) * T::LPS / KSTEPS;
-        if constexpr (T::NL == 0) static_for<l1 - l0>([&](auto L) { issue_one(it + T::NS - 1, wr, std::integral_constant<int, l0 + decltype(L)::value>{}); });
+        if constexpr (T::NL == 0) static_for<l1 - l0>([&](auto L) { issue_one(it + T::NS - 1, wr, std::integral_constant<int, l0 + decltype(L)::value>{}, std::false_type{}); });
 #pragma unroll
         for (int i = 0; i < T::FM; i++)
 #pragma unroll
@@ -258,21 +276,16 @@ __global__ __launch_bounds__(T::NT) void gemm_ring_kernel(GemmOp op, int kper, i
       });
     }
     if constexpr (STAT_A) {
-      // Each of a row's threads squares its 8 / TPR chunks of a slice; all of them then add the eight chunk sums in the
-      // order they lie in LDS, as the one thread per row of the 256-row kernel does: same bits whichever tile runs.
-      constexpr int CPT = 8 / T::TPR;
+      // Each of a row's threads squares its chunks of the stage; the sums of the stage before are added up meanwhile.
+      if (T::BM * T::TPR == T::NT || tid < T::BM * T::TPR) {
+        uint4 q[T::SUB * CPT];
 #pragma unroll
-      for (int s = 0; s < T::SUB; s++) {
-        if (tid >= T::BM * T::TPR) continue;
-        const unsigned char* sr = smem + rd * T::STAGE + s * T::SLICE + (tid / T::TPR) * 128 + (tid % T::TPR) * (CPT * 16);
-        float cs[CPT];
+        for (int c = 0; c < T::SUB * CPT; c++)
+          q[c] = *reinterpret_cast<const uint4*>(smem + rd * T::STAGE + c / CPT * T::SLICE + (tid / T::TPR) * 128 +
+                                                 ((tid % T::TPR) * CPT + c % CPT) * 16);
+        add_chunks();
 #pragma unroll
-        for (int c = 0; c < CPT; c++) cs[c] = sumsq8(*reinterpret_cast<const uint4*>(sr + c * 16));
-        static_for<8>([&](auto C) {
-          constexpr int j = decltype(C)::value / CPT;    // the thread of the row that holds this chunk
-          constexpr int ctrl = T::TPR == 4 ? j * 0x55 : j == 0 ? 0xA0 : 0xF5;   // quad_perm [j,j,j,j] / [j,j,2+j,2+j]
-          ssq += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(cs[decltype(C)::value % CPT]), ctrl, 0xf, 0xf, false));
-        });
+        for (int c = 0; c < T::SUB * CPT; c++) cs[c] = sumsq8(q[c]);
       }
     }
     rd = rd + 1 == T::NS ? 0 : rd + 1;
@@ -282,6 +295,7 @@ __global__ __launch_bounds__(T::NT) void gemm_ring_kernel(GemmOp op, int kper, i
   __syncthreads();           // the ring is dead from here on
   float* sStat = reinterpret_cast<float*>(smem + T::STAT_OFF);
   if constexpr (STAT_A) {
+    add_chunks();            // of the last stage
     if (tid < T::BM * T::TPR && tid % T::TPR == 0) sStat[tid / T::TPR] = ssq;
     __syncthreads();
   }
