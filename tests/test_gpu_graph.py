@@ -2,6 +2,10 @@
 library launches kernels on the stream it is given and does nothing else: no allocation, no
 synchronisation, no memset nodes), then replayed several times on changing inputs with eager work and
 synchronisations between the replays; every replay must reproduce the eager result bit for bit."""
+import os
+import subprocess
+import sys
+
 import pytest
 import torch
 
@@ -36,7 +40,7 @@ def test_block_step_replays_from_a_graph(rope):
     xs = [si.gaussian(5, f"x{i}", (Bn * S, d), std=1.0, dtype=torch.bfloat16).to(DEV) for i in range(3)]
     dys = [si.gaussian(5, f"dy{i}", (Bn * S, d), std=1.0, dtype=torch.bfloat16).to(DEV) for i in range(3)]
 
-    # eager results (also the warm-up that sets the kernels' one-time attributes before any capture)
+    # eager results
     eager = []
     for x, dy in zip(xs, dys):
         y, ck = B.lr_block_fwd(desc, packed, x)
@@ -67,3 +71,45 @@ def test_block_step_replays_from_a_graph(rope):
         assert torch.equal(ck["z_gu"], zgu_e), f"z_gu, replay of input {rep}"
         for k in g_e:
             assert torch.equal(grads[k], g_e[k]), f"grad {k}, replay of input {rep}"
+
+
+_CHILD = """
+import torch
+import synth_inputs as si
+from paper_2512_12131_amd import binding as B
+Bn, S, H, f, r = 2, 320, 2, 344, 64
+d, f_ld = 128 * H, si.pad_ld(f, 8)
+case = si.block_case(Bn, S, d, H, 128, f, r, seed=5)
+desc = B.make_block_desc(Bn, S, d, H, 128, f, f_ld, r)
+p = {k: v.to("cuda:0") for k, v in si.pack_block_params(case["params"], f, f_ld).items()}
+x, dy = case["x"].to("cuda:0"), case["dy"].to("cuda:0")
+ck = B.alloc_block_ckpt(desc, x.device)
+grads = {n: torch.zeros_like(p[n], dtype=torch.float32) for n in B.PARAM_NAMES}
+ws = [torch.empty(B.lr_block_workspace_bytes(desc, b), dtype=torch.uint8, device=x.device) for b in (0, 1)]
+y, dx = torch.zeros_like(x), torch.zeros_like(x)
+torch.cuda.synchronize()
+graph = torch.cuda.CUDAGraph()
+with torch.cuda.graph(graph):
+    B.lr_block_fwd(desc, p, x, ckpt=ck, ws=ws[0], y=y)
+    B.lr_block_bwd(desc, p, x, dy, ck, grads=grads, ws=ws[1], dx=dx)
+torch.cuda.synchronize()
+y_e, ck_e = B.lr_block_fwd(desc, p, x)
+dx_e, g_e = B.lr_block_bwd(desc, p, x, dy, ck_e)
+for _ in range(3):
+    for t in (y, dx, *grads.values()):
+        t.zero_()
+    torch.cuda.synchronize()
+    graph.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(y, y_e) and torch.equal(dx, dx_e) and all(torch.equal(grads[k], g_e[k]) for k in g_e)
+print("replays equal eager")
+"""
+
+
+def test_capture_needs_no_eager_call_before():
+    # a process of its own whose first library call is the captured one: the kernels' one-time attributes are set
+    # inside the capture
+    print("capture as the first call of a process", flush=True)
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", _CHILD], cwd=root, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and "replays equal eager" in r.stdout, r.stderr[-2000:]
