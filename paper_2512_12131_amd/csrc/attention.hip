@@ -1,9 +1,9 @@
 // Causal multi-head attention, head_dim 128, bf16 in / fp32 softmax, for gfx950.
 //
-// Forward (one workgroup = 4 wavefronts x 32 queries of one (batch, head), for one query block and
+// Forward (one workgroup = 4 or 8 wavefronts x 32 queries of one (batch, head), for one query block and
 // its causal mirror; K/V stream through LDS in 64-key tiles, double buffered):
 //   S^T = K Q^T      MFMA, A = K rows from LDS, B = Q rows kept in registers for the whole kernel
-//   online softmax   per query = per lane column of the S^T accumulators (one cross-half shuffle)
+//   online softmax   per query = per lane column of the S^T accumulators (one exchange of the wavefront's halves)
 //   O^T += V^T P^T   MFMA, B = P^T straight from the softmax registers, A = V^T through the LDS
 //                    transpose read (ds_read_b64_tr_b16), so V is stored as it arrives: [key][h]
 // Working on the transposed problem is what lets the probabilities feed the second MFMA without
@@ -162,6 +162,7 @@ __device__ __forceinline__ void dma_tile(rsrc_t rs, unsigned char* tile, const u
 }
 // s_waitcnt vmcnt(0) alone (gfx9 encoding), and lgkmcnt(0) alone
 __device__ __forceinline__ void wait_vm0() { __builtin_amdgcn_s_waitcnt(0x0f70); }
+__device__ __forceinline__ void wait_lgkm0() { __builtin_amdgcn_s_waitcnt(0xc07f); }
 // s_waitcnt vmcnt(N) alone, N < 64: bits 3:0 and 15:14 hold vmcnt, the other counters stay at "no wait"
 template <int N>
 __device__ __forceinline__ void wait_vm() {
@@ -234,21 +235,63 @@ __device__ __forceinline__ WgCoord wg_coord() {
 
 constexpr int FWD_LDS = 4 * TILE_BYTES;   // K and V, double buffered
 
+// Compile-time loop over std::integral_constant indices: register arrays indexed by them stay in registers.
+template <int N, class F, int I = 0>
+__device__ __forceinline__ void unroll_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    unroll_for<N, F, I + 1>(static_cast<F&&>(f));
+  }
+}
+// Buffer resource of S rows of 256 bytes, ld elements apart: rows at or past S are out of range by themselves.
+__device__ __forceinline__ rsrc_t rows_rsrc(const uint16_t* base, int S, int64_t ld) {
+  return make_rsrc(base, (uint32_t)(S - 1) * (uint32_t)ld * 2u + 256u);
+}
+// The same resource from byte `off` on (scalar arithmetic only); empty, so that loads deliver zeros, where !valid.
+__device__ __forceinline__ rsrc_t rsrc_from(rsrc_t r, uint32_t off, bool valid) {
+  const uint64_t a = (((uint64_t)r.y << 32) | r.x) + (valid ? off : 0u);
+  return rsrc_t{(uint32_t)a, (uint32_t)(a >> 32), valid ? r.z - off : 0u, r.w};
+}
+// lds_dma<16> with the LDS address as a number
+__device__ __forceinline__ void lds_dma_at(rsrc_t rs, uint32_t lds, uint32_t voff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(rs) : "m0", "memory");
+}
+// max / sum of the two lanes l and l + 32
+__device__ __forceinline__ float half_max(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float half_sum(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 // ----------------------------------------------------------------------------------------------
 // forward
 // ----------------------------------------------------------------------------------------------
-template <int MB>
-__global__ __launch_bounds__(256, 2) void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+// Bound: the issue of vector ALU work beside the MFMAs, and in long runs the chip's power.  An iteration works on two key
+// tiles: the scores of tile j + 1 (16 MFMAs) and the output of tile j (16 MFMAs) with the softmax of tile j and the maximum of
+// the new scores threaded between them, one MFMA and a share of the rest per slot, so that a wavefront's matrix and
+// vector work overlap and its LDS operands are read some MFMAs ahead.  (One tile at a time - scores, softmax, output -
+// the phases of the two wavefronts of a SIMD did not overlap enough: matrix pipes 41 % busy, now 53 %.)  One barrier per
+// iteration, in the middle, where the K operands have been read and no V operand yet: each load then has a whole iteration to land.
+// The loop over the unmasked tiles is unrolled by two, its score registers swapping roles; the branches (masks, odd
+// tiles, the end) stay outside, which is what lets the compiler keep every tuple in place (246 registers, no copies).
+// Sustained, one tile at a time -> now (us): 4 x 4096 tokens, 32 heads 627 -> 555; 8 x 2048, 16 heads 175 -> 157;
+// 2 x 2047, 32 / 8 heads 89.9 -> 79; 777 tokens, 32 / 8 heads 23.5 -> 19.9; 4 x 4096, 4 heads 93.8 -> 78.
+constexpr int FWD_D = 4;        // LDS operands are read this many MFMAs ahead (2, 4, 8: within 2 %)
+constexpr int FWD_BAR = 12;     // slot of the barrier: the last operand of the score product has been read
+// elements of the softmax done by the end of slot s: each bf16x8 operand is whole when its MFMAs come (slots 16, 20, 24, 28)
+constexpr int fwd_elems(int s) { return s < 0 ? 0 : s < 16 ? 5 * (s + 1) / 4 : s < 28 ? 5 + s : 32; }
+
+template <int NW>
+__global__ __launch_bounds__(NW * 64, 2) void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                                                        const uint16_t* __restrict__ v, uint16_t* __restrict__ o,
                                                        float* __restrict__ lse, int64_t ld, int64_t ldkv, int grp, int S,
                                                        int H, float scale) {
-  static_assert(MB == 1, "one 32-query block per wavefront");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  constexpr int BQ = 4 * MB * 32;
-  // (here the wavefront index stays a vector value: as a scalar it costs this kernel 13 more spilled
-  // registers; only the LDS destinations of the global->LDS loads use a scalar copy)
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+  constexpr int BQ = NW * 32, NL = 16 / NW;             // queries per block, 1 KB loads per wavefront and tile
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nqb = (S + BQ - 1) / BQ;
   const WgCoord wg = wg_coord();
   const int head = wg.head, b = wg.b;
@@ -256,15 +299,21 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(const uint16_t* __rest
   const uint16_t* qb = q + tok0 * ld + head * HD;
   // grouped-query attention: grp consecutive query heads share key / value head head / grp (rows of ldkv)
   const int kvh = head / grp;
-  const rsrc_t rsK = tile_rsrc(k + tok0 * ldkv + kvh * HD);
-  const rsrc_t rsV = tile_rsrc(v + tok0 * ldkv + kvh * HD);
+  const rsrc_t rsK = rows_rsrc(k + tok0 * ldkv + kvh * HD, S, ldkv);
+  const rsrc_t rsV = rows_rsrc(v + tok0 * ldkv + kvh * HD, S, ldkv);
   const float c = scale * LOG2E;
-  uint32_t offK[4], offV[4];
-  int rowK[4], rowV[4];
-  dma_lane_offsets<SWZ_ROW16, 4>(offK, rowK, ldkv, wave, lane);
-  dma_lane_offsets<SWZ_ROW4, 4>(offV, rowV, ldkv, wave, lane);
-  unsigned char* sK = smem;                              // 2 tiles
-  unsigned char* sV = smem + 2 * TILE_BYTES;             // 2 tiles
+  uint32_t offK[NL], offV[NL];
+  {
+    int row[NL];
+    dma_lane_offsets<SWZ_ROW16, NL>(offK, row, ldkv, wave, lane);
+    dma_lane_offsets<SWZ_ROW4, NL>(offV, row, ldkv, wave, lane);
+  }
+  const uint32_t lds0 = (uint32_t)(uintptr_t)LRB_LDS_PTR(smem) + (uint32_t)wave * 1024u;
+  // load i of key tile t into its slot (K: slots 0, 1, V: slots 2, 3); a tile past the last one: every lane out of range
+  auto dma = [&](bool isV, int t, int ntiles, int i) {
+    lds_dma_at(rsrc_from(isV ? rsV : rsK, (uint32_t)t * (uint32_t)(KT * 2) * (uint32_t)ldkv, t < ntiles),
+               lds0 + (uint32_t)((isV ? 2 : 0) + (t & 1)) * TILE_BYTES + (uint32_t)(i * NW) * 1024u, isV ? offV[i] : offK[i]);
+  };
 
   // Causal work grows linearly with the query block index.  Every workgroup takes one block from the
   // late end and its mirror image from the early end, so that all workgroups of the launch do the
@@ -276,137 +325,212 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(const uint16_t* __rest
   // unpaired launch, or odd block count: the middle block has no mirror
   if (pass == 1 && ((int)gridDim.x == nqb || qblk >= nqb - 1 - wg.x)) break;
   const int q0 = qblk * BQ;
-  const int qw0 = q0 + wave * MB * 32;                   // first query of this wavefront
+  const int qw0 = q0 + wave * 32;                        // first query of this wavefront
+  const int kv_end = min(S, q0 + BQ);                    // causal: keys up to the block's last query
+  const int ntiles = (kv_end + KT - 1) / KT;
+  const int ntw = qw0 < S ? min(ntiles, (qw0 + 31) / KT + 1) : 0;   // ... and up to this wavefront's
 
-  bf16x8 qf[MB][8];
-  load_row_frags<MB>(qf, qb, ld, qw0, S, lane);
+  __syncthreads();                                       // the pass before is done with the slots
+#pragma unroll
+  for (int i = 0; i < NL; i++) dma(false, 0, ntiles, i);
+#pragma unroll
+  for (int i = 0; i < NL; i++) dma(false, 1, ntiles, i);
+#pragma unroll
+  for (int i = 0; i < NL; i++) dma(true, 0, ntiles, i);
+  bf16x8 qf[1][8];
+  load_row_frags<1>(qf, qb, ld, qw0, S, lane);
 
-  f32x16 oacc[4];
-  float mrun = -INFINITY, lrun = 0.f;
+  f32x16 oacc[4], st[2];                                 // st: scores (S^T) of the tile whose softmax comes next
 #pragma unroll
   for (int hb = 0; hb < 4; hb++)
 #pragma unroll
     for (int e = 0; e < 16; e++) oacc[hb][e] = 0.f;
+#pragma unroll
+  for (int nb = 0; nb < 2; nb++)
+#pragma unroll
+    for (int e = 0; e < 16; e++) st[nb][e] = 0.f;
+  float mrun = -INFINITY, lrun = 0.f, alpha = 1.f, mc = 0.f;
+  bf16x8 fr[FWD_D];                                      // operands read ahead, slot s in fr[s % FWD_D]
 
-  const int kv_end = min(S, q0 + BQ);                    // causal: keys up to the block's last query
-  const int ntiles = (kv_end + KT - 1) / KT;
-
-  dma_tile(rsK, sK, offK, rowK, 0, S, ldkv, wave_s);
-  dma_tile(rsV, sV, offV, rowV, 0, S, ldkv, wave_s);
-  wait_vm0();
-  __syncthreads();
-
-  for (int j = 0; j < ntiles; j++) {
-    const int cur = j & 1;
-    if (j + 1 < ntiles) {                                // next tiles land while this one is worked on
-      dma_tile(rsK, sK + (cur ^ 1) * TILE_BYTES, offK, rowK, (j + 1) * KT, S, ldkv, wave_s);
-      dma_tile(rsV, sV + (cur ^ 1) * TILE_BYTES, offV, rowV, (j + 1) * KT, S, ldkv, wave_s);
-    }
-    const int key0 = j * KT;
-    const unsigned char* sKc = sK + cur * TILE_BYTES;
-    const unsigned char* sVc = sV + cur * TILE_BYTES;
-    if (key0 <= qw0 + MB * 32 - 1) {                     // this wavefront still has unmasked keys here
-      // ---- S^T[n][m] for 64 keys x 32 queries: all 16 operand reads are issued up front, so the LDS
-      //      latency is paid once per tile and not once per MFMA pair ----
-      bf16x8 kf[8][2];
-#pragma unroll
-      for (int ks = 0; ks < 8; ks++)
-#pragma unroll
-        for (int nb = 0; nb < 2; nb++) kf[ks][nb] = swz_row_frag(sKc, nb * 32, ks, lane);
-      __builtin_amdgcn_sched_barrier(0);
-      f32x16 st[2];
-#pragma unroll
-      for (int nb = 0; nb < 2; nb++)
-#pragma unroll
-        for (int e = 0; e < 16; e++) st[nb][e] = 0.f;
-#pragma unroll
-      for (int ks = 0; ks < 8; ks++)
-#pragma unroll
-        for (int nb = 0; nb < 2; nb++)
-          st[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks][nb], qf[0][ks], st[nb], 0, 0, 0);
-      // first half of the V^T operands: in flight during the softmax
-      bf16x8 vf[2][4];
-#pragma unroll
-      for (int t = 0; t < 2; t++)
-#pragma unroll
-        for (int hb = 0; hb < 4; hb++) vf[t][hb] = swz_tr_frag(sVc, t * 16, hb * 32, lane);
-      __builtin_amdgcn_sched_barrier(0);
-      if ((key0 + KT - 1 > qw0) || (key0 + KT > S)) {    // wavefront-uniform: diagonal / tail tile
-        asm volatile("" ::: "memory");                   // a real branch: the selects are not to be speculated
-        const int qi = qw0 + (lane & 31);
-#pragma unroll
-        for (int nb = 0; nb < 2; nb++)
-#pragma unroll
-          for (int e = 0; e < 16; e++) {
-            const int key = key0 + nb * 32 + acc_row(e, lane);
-            st[nb][e] = (key > qi || key >= S) ? -INFINITY : st[nb][e];
-          }
-      }
-      float mx = -INFINITY;
-#pragma unroll
-      for (int nb = 0; nb < 2; nb++)
-#pragma unroll
-        for (int e = 0; e < 16; e++) mx = fmaxf(mx, st[nb][e]);
-      mx = fmaxf(mx, __shfl_xor(mx, 32));
-      const float mnew = fmaxf(mrun, mx);                // finite: key 0 is visible to every query
-      const float alpha = fast_exp2((mrun - mnew) * c);
-      mrun = mnew;
-      const float mc = mnew * c;
-      float rs = 0.f;
+  // operand of MFMA slot s: 0..15 scores (k16 step s / 2, key block s % 2), 16..31 output (16 keys each four slots)
+  auto read_frag = [&](auto Sc, const unsigned char* sK, const unsigned char* sV) {
+    constexpr int s = decltype(Sc)::value;
+    if constexpr (s < 16) fr[s % FWD_D] = swz_row_frag(sK, (s & 1) * 32, s >> 1, lane);
+    else fr[s % FWD_D] = swz_tr_frag(sV, ((s - 16) >> 2) * 16, (s & 3) * 32, lane);
+  };
+  // maximum of a tile's scores, mx where no key is masked; else (diagonal / tail tile) masks them first
+  auto masked_max = [&](f32x16 (&x)[2], int key0, float mx) -> float {
+    if ((key0 + KT - 1 > qw0) || (key0 + KT > S)) {      // wavefront-uniform
+      const int lim = min(qw0 + (lane & 31) + 1, S) - key0 - 4 * (lane >> 5);   // first masked key, less the lane's rows
+      mx = -INFINITY;
 #pragma unroll
       for (int nb = 0; nb < 2; nb++)
 #pragma unroll
         for (int e = 0; e < 16; e++) {
-          const float p = fast_exp2(fmaf(st[nb][e], c, -mc));
-          st[nb][e] = p;
-          rs += p;
+          x[nb][e] = nb * 32 + acc_row(e, 0) >= lim ? -INFINITY : x[nb][e];
+          mx = fmaxf(mx, x[nb][e]);
         }
-      lrun = lrun * alpha + rs;
-      // the running maximum settles after the first tiles: skip the rescale when no lane needs it
-      if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) {
-#pragma unroll
-        for (int hb = 0; hb < 4; hb++)
-#pragma unroll
-          for (int e = 0; e < 16; e++) oacc[hb][e] *= alpha;
-      }
-      // ---- O^T += V^T P^T ----
-#pragma unroll
-      for (int nb = 0; nb < 2; nb++) {
-        bf16x8 vn[2][4];
-        if (nb == 0) {                                   // second half of the operands, during the first half's MFMAs
-#pragma unroll
-          for (int t = 0; t < 2; t++)
-#pragma unroll
-            for (int hb = 0; hb < 4; hb++) vn[t][hb] = swz_tr_frag(sVc, 32 + t * 16, hb * 32, lane);
-        }
-#pragma unroll
-        for (int t = 0; t < 2; t++) {
-          const bf16x8 pf = pack_acc_half(st[nb], t);
-#pragma unroll
-          for (int hb = 0; hb < 4; hb++)
-            oacc[hb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[t][hb], pf, oacc[hb], 0, 0, 0);
-        }
-        if (nb == 0) {
-#pragma unroll
-          for (int t = 0; t < 2; t++)
-#pragma unroll
-            for (int hb = 0; hb < 4; hb++) vf[t][hb] = vn[t][hb];
-        }
-      }
     }
+    return mx;
+  };
+  // running maximum over the new scores: the factor of what is there already, and the exponents' common term
+  auto new_max = [&](float mx) {
+    const float mnew = fmaxf(mrun, half_max(mx));        // finite: key 0 is visible to every query
+    alpha = fast_exp2((mrun - mnew) * c);
+    mrun = mnew;
+    mc = mnew * c;
+  };
+
+  wait_vm0();
+  __syncthreads();
+  if (ntw > 0) {                                         // scores of the first tile
+    unroll_for<FWD_D>([&](auto I) { read_frag(I, smem, smem); });
+    unroll_for<16>([&](auto I) {
+      constexpr int s = decltype(I)::value;
+      st[s & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[s % FWD_D], qf[0][s >> 1], st[s & 1], 0, 0, 0);
+      if constexpr (s + FWD_D < 16) read_frag(std::integral_constant<int, s + FWD_D>{}, smem, smem);
+    });
+    float mx = -INFINITY;
+#pragma unroll
+    for (int nb = 0; nb < 2; nb++)
+#pragma unroll
+      for (int e = 0; e < 16; e++) mx = fmaxf(mx, st[nb][e]);
+    new_max(masked_max(st, 0, mx));
+    if (ntw > 1) unroll_for<FWD_D>([&](auto I) { read_frag(I, smem + TILE_BYTES, smem); });
+  }
+  wait_lgkm0();
+  __builtin_amdgcn_s_barrier();                          // nobody reads K's first tile any more
+#pragma unroll
+  for (int i = 0; i < NL; i++) dma(false, 2, ntiles, i);
+
+  // all of this workgroup's reads of K(j + 1) and V(j - 1) are done, K(j + 2) and V(j) have landed
+  auto turn = [&] {
+    wait_lgkm0();
     wait_vm0();
-    __syncthreads();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  auto next_loads = [&](int j, int i) {                  // into the slots just left
+    if (i < NL) dma(true, j + 1, ntiles, i);
+    else dma(false, j + 3, ntiles, i - NL);
+  };
+  // the running maximum settles after the first tiles: skip the rescale when no lane needs it
+  auto rescale = [&] {
+    if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) {
+#pragma unroll
+      for (int hb = 0; hb < 4; hb++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) oacc[hb][e] *= alpha;
+    }
+  };
+  uint32_t pw[16];                                       // the probabilities as bf16 pairs: two operands per key block
+  float rs = 0.f, plow = 0.f;
+  // elements F .. T - 1 of the softmax (key block e / 16, accumulator row e % 16)
+  auto softmax_to = [&](const f32x16 (&x)[2], auto Fc, auto Tc) {
+    constexpr int f = decltype(Fc)::value, t = decltype(Tc)::value;
+    unroll_for<t - f>([&](auto I) {
+      constexpr int e = f + decltype(I)::value;
+      const float p = fast_exp2(fmaf(x[e >> 4][e & 15], c, -mc));
+      rs += p;
+      if constexpr (e & 1) pw[e >> 1] = pack_bf16x2(plow, p);
+      else plow = p;
+    });
+  };
+  auto pv = [&](auto Sc) {                               // output MFMA of slot s
+    constexpr int s = decltype(Sc)::value, kk = (s - 16) >> 2;
+    const bf16x8 pf = __builtin_bit_cast(bf16x8, make_uint4(pw[kk * 4], pw[kk * 4 + 1], pw[kk * 4 + 2], pw[kk * 4 + 3]));
+    oacc[s & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[s % FWD_D], pf, oacc[s & 3], 0, 0, 0);
+  };
+  // softmax and output of tile j (scores sc), scores of tile j + 1 (into sn); par = j % 2.  MASK: tile j + 1 may be the diagonal
+  // or the tail tile (the last one of the wavefront).
+  auto iteration = [&](int j, auto par, auto MASK, f32x16 (&sc)[2], f32x16 (&sn)[2]) {
+    const unsigned char* sK1 = smem + (par ^ 1) * TILE_BYTES;              // K of tile j + 1
+    const unsigned char* sK2 = smem + par * TILE_BYTES;                    // K of tile j + 2
+    const unsigned char* sV = smem + (2 + par) * TILE_BYTES;               // V of tile j
+    rescale();
+    rs = 0.f;
+#pragma unroll
+    for (int nb = 0; nb < 2; nb++)
+#pragma unroll
+      for (int e = 0; e < 16; e++) sn[nb][e] = 0.f;
+    float mx0 = -INFINITY, mx1 = -INFINITY;
+    unroll_for<32>([&](auto Sc) {
+      constexpr int s = decltype(Sc)::value;
+      if constexpr (s < 16)
+        sn[s & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[s % FWD_D], qf[0][s >> 1], sn[s & 1], 0, 0, 0);
+      else pv(Sc);
+      if constexpr (s == FWD_BAR) turn();
+      // operands: V only from behind the barrier, then K of the tile after next
+      unroll_for<32>([&](auto I) {
+        constexpr int t = decltype(I)::value + FWD_D;               // target slot
+        constexpr int at = t - FWD_D < FWD_BAR && t >= 16 ? FWD_BAR : t - FWD_D;
+        if constexpr (at == s) {
+          if constexpr (t < 32) read_frag(std::integral_constant<int, t>{}, sK1, sV);
+          else read_frag(std::integral_constant<int, t - 32>{}, sK2, sV);
+        }
+      });
+      if constexpr (s > FWD_BAR && s <= FWD_BAR + 2 * NL) next_loads(j, s - FWD_BAR - 1);
+      softmax_to(sc, std::integral_constant<int, fwd_elems(s - 1)>{}, std::integral_constant<int, fwd_elems(s)>{});
+      if constexpr (s >= 18 && s < 26) {                            // maximum of the new scores
+        constexpr int e = (s - 18) * 2;
+        mx0 = fmaxf(fmaxf(mx0, sn[0][e]), sn[0][e + 1]);
+        mx1 = fmaxf(fmaxf(mx1, sn[1][e]), sn[1][e + 1]);
+      }
+      // (the sums stay in this block: moved down to their use they would keep every element alive)
+      if constexpr (fwd_elems(s - 1) != fwd_elems(s)) asm volatile("" : "+v"(rs));
+      if constexpr (s == 25) asm volatile("" : "+v"(mx0), "+v"(mx1));
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    lrun = lrun * alpha + rs;
+    float mx = fmaxf(mx0, mx1);
+    if constexpr (decltype(MASK)::value) mx = masked_max(sn, (j + 1) * KT, mx);
+    new_max(mx);
+  };
+  int j = 0;
+  f32x16 s2[2];
+  for (; j + 3 < ntw; j += 2) {
+    iteration(j, std::integral_constant<int, 0>{}, std::false_type{}, st, s2);
+    iteration(j + 1, std::integral_constant<int, 1>{}, std::false_type{}, s2, st);
+  }
+  for (; j + 1 < ntw; j++) {
+    iteration(j, j & 1, std::true_type{}, st, s2);
+#pragma unroll
+    for (int nb = 0; nb < 2; nb++) st[nb] = s2[nb];
+  }
+  if (j < ntw) {                                         // this wavefront's last tile
+    const unsigned char* sV = smem + (2 + (j & 1)) * TILE_BYTES;
+    rescale();
+    rs = 0.f;
+    turn();
+    unroll_for<FWD_D>([&](auto I) { read_frag(std::integral_constant<int, 16 + decltype(I)::value>{}, smem, sV); });
+#pragma unroll
+    for (int i = 0; i < 2 * NL; i++) next_loads(j, i);
+    softmax_to(st, std::integral_constant<int, 0>{}, std::integral_constant<int, 16>{});
+    unroll_for<16>([&](auto I) {
+      constexpr int s = 16 + decltype(I)::value;
+      pv(std::integral_constant<int, s>{});
+      if constexpr (s + FWD_D < 32) read_frag(std::integral_constant<int, s + FWD_D>{}, smem, sV);
+      if constexpr (s < 24) softmax_to(st, std::integral_constant<int, 16 + (s - 16) * 2>{}, std::integral_constant<int, 18 + (s - 16) * 2>{});
+    });
+    lrun = lrun * alpha + rs;
+    j++;
+  }
+  for (; j < ntiles; j++) {                              // nothing left for this wavefront but its share of the loads
+    turn();
+#pragma unroll
+    for (int i = 0; i < 2 * NL; i++) next_loads(j, i);
   }
 
   {
     const int qi = qw0 + (lane & 31);
-    const float l = lrun + __shfl_xor(lrun, 32);
+    const float l = half_sum(lrun);
     if (qi < S) {
       store_acc_T(o + (tok0 + qi) * ld + head * HD, oacc, 1.f / l, lane);
       if (lane < 32) lse[((int64_t)b * H + head) * S + qi] = mrun * scale + logf(l);
     }
   }
   }  // pass
+  wait_vm0();                                            // no load into LDS outlives the workgroup
 }
 
 // ----------------------------------------------------------------------------------------------
@@ -845,19 +969,24 @@ hipError_t attention_gqa_fwd_bf16(const void* q, const void* k, const void* v, v
   const int grp = H / Hkv;
   // 32-bit buffer offsets per (batch, head)
   if ((int64_t)S * ld * 2 >= (int64_t)0x7fffffff || (int64_t)S * ldkv * 2 >= (int64_t)0x7fffffff) return hipErrorNotSupported;
-  constexpr int MB = 1;
-  constexpr int BQ = 4 * MB * 32;
-  // one-time opt-in to more than 64 KB of dynamic LDS (thread-safe static initialisation)
-  static const hipError_t attr_err = set_lds(attn_fwd_kernel<MB>, FWD_LDS);
-  if (attr_err != hipSuccess) return attr_err;
-  const int nqb = (S + BQ - 1) / BQ;
-  // Each workgroup: one query block and its mirror; or one block, where each finds a CU free: the launch then takes
-  // as long as its longest block instead of a pair (2 x 256 tokens, 2 heads: 18.3 -> 12.3 us).  With two
-  // unpaired workgroups per CU the late blocks meet on some CUs (4 x 4096 tokens, 4 heads: 110 -> 135 us).
-  dim3 grid((int64_t)nqb * H * B <= 256 ? nqb : (nqb + 1) / 2, H, B);
-  hipLaunchKernelGGL(attn_fwd_kernel<MB>, grid, dim3(256), FWD_LDS, st, (const uint16_t*)q, (const uint16_t*)k,
-                     (const uint16_t*)v, (uint16_t*)o, lse, ld, ldkv, grp, S, H, 1.f / sqrtf((float)hd));
-  return hipGetLastError();
+  auto launch = [&](auto NWc) {
+    constexpr int NW = decltype(NWc)::value, BQ = NW * 32;
+    // one-time opt-in to more than 64 KB of dynamic LDS (thread-safe static initialisation)
+    static const hipError_t attr_err = set_lds(attn_fwd_kernel<NW>, FWD_LDS);
+    if (attr_err != hipSuccess) return attr_err;
+    const int nqb = (S + BQ - 1) / BQ;
+    // Each workgroup: one query block and its mirror; or one block, where each finds a CU free: the launch then takes
+    // as long as its longest block instead of a pair (2 x 256 tokens, 2 heads: 18.3 -> 12.3 us).  With two
+    // unpaired workgroups per CU the late blocks meet on some CUs (4 x 4096 tokens, 4 heads: 110 -> 135 us).
+    dim3 grid((int64_t)nqb * H * B <= 256 ? nqb : (nqb + 1) / 2, H, B);
+    hipLaunchKernelGGL(attn_fwd_kernel<NW>, grid, dim3(NW * 64), FWD_LDS, st, (const uint16_t*)q, (const uint16_t*)k,
+                       (const uint16_t*)v, (uint16_t*)o, lse, ld, ldkv, grp, S, H, 1.f / sqrtf((float)hd));
+    return hipGetLastError();
+  };
+  // 8 wavefronts fetch a key tile once for 256 queries instead of twice: less work for L2 and memory where the inputs are
+  // cold (2 x 2047 tokens, 32 / 8 heads, three sets of inputs in turn, with the backward: 441 -> 432 us; warm the two are
+  // within 1 %).  They need a launch that still fills the chip.
+  return (int64_t)((S + 255) / 256 + 1) / 2 * H * B >= 256 ? launch(std::integral_constant<int, 8>{}) : launch(std::integral_constant<int, 4>{});
 }
 
 // The backward runs in one of two forms.  With the score gradient kept (S a multiple of 8, and

@@ -1,0 +1,38 @@
+"""Causal attention at the edges of its tiles: 32 queries per wavefront, 64 keys per tile, 128 or 256 queries per block."""
+import pytest
+import torch
+
+from paper_2512_12131_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+HD = 128
+
+
+@pytest.mark.parametrize("S", [1, 31, 32, 33, 63, 64, 65, 97, 127, 128, 129, 191, 193, 255, 256, 257, 321, 385, 513])
+def test_attention_fwd_edges(S):
+    """Blocks of 256 queries (256 heads in a launch) and of 128 (16 heads at a time) give the same bits, and those of one
+    batch element lie within the roundings of p and o of the result in 64 bits.  bf16 keeps 8 significant bits, so
+    rounding to nearest is off by up to 2^-8 of a value: 2^-8 sum p |v| for the probabilities and 2^-8 |o| <= 2^-8 sum p |v| for
+    the output, and 2 % of that for the fp32 arithmetic between."""
+    Bn, H, Hkv = 16, 16, 4
+    print(f"attention edges S={S}", flush=True)
+    g = torch.Generator().manual_seed(S)
+    q = torch.randn(Bn * S, H * HD, generator=g).bfloat16()
+    k, v = (torch.randn(Bn * S, Hkv * HD, generator=g).bfloat16() for _ in range(2))
+    qd, kd, vd = q.to(DEV), k.to(DEV), v.to(DEV)
+    o, lse = B.lr_attention_gqa_fwd(qd, kd, vd, Bn, S, H, Hkv, HD)
+    for b in (0, 7, Bn - 1):
+        r = slice(b * S, (b + 1) * S)
+        o1, lse1 = B.lr_attention_gqa_fwd(qd[r], kd[r], vd[r], 1, S, H, Hkv, HD)
+        assert torch.equal(o[r], o1) and torch.equal(lse.reshape(Bn, -1)[b], lse1.reshape(-1))
+    q64 = q[:S].double().view(S, H, HD).transpose(0, 1)
+    k64, v64 = (t[:S].double().view(S, Hkv, HD).repeat_interleave(H // Hkv, 1).transpose(0, 1).contiguous() for t in (k, v))
+    s = (q64[:, :, None, :] * k64[:, None, :, :]).sum(-1) if S <= 2 else q64 @ k64.transpose(1, 2).contiguous()
+    s = (s / HD ** 0.5).masked_fill(torch.ones(S, S, dtype=torch.bool).triu(1), -torch.inf)
+    p = s.softmax(-1)
+    bound = 2.0 ** -7 * 1.02 * (p @ v64.abs())
+    got = o[:S].cpu().double().view(S, H, HD).transpose(0, 1)
+    worst = ((got - p @ v64).abs() / bound).max().item()
+    assert worst <= 1.0
+    assert (lse.view(Bn, H, S)[0].cpu().double() - s.logsumexp(-1)).abs().max() < 1e-4
