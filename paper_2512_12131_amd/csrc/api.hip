@@ -23,6 +23,9 @@ struct Ctx {
   int gdt = LR_F32;          // dtype of the weight / gamma gradients
   hipStream_t st = nullptr;
   hipError_t err = hipSuccess;
+  // Between hold() and flush(): products that do not depend on each other, to be launched together.
+  GemmOp held[JOINT_MAX];
+  int nheld = -1;            // -1: not holding
 
   void* take(size_t bytes) {
     off = (off + 255) & ~(size_t)255;
@@ -34,6 +37,17 @@ struct Ctx {
   size_t mark() const { return off; }
   void release(size_t m) { off = m; }   // stack discipline: drop everything taken since mark()
   void run(hipError_t e) { if (err == hipSuccess && e != hipSuccess) err = e; }
+  void hold() { nheld = 0; }
+  void flush() {
+    if (!dry && err == hipSuccess && nheld > 0) run(dt == LR_F32 ? gemm_f32_many(held, nheld, st) : gemm_bf16_many(held, nheld, st));
+    nheld = -1;
+  }
+  // launches a product whose operands lie where they stay (nothing of it in scratch that is given back), or holds it
+  void submit(const GemmOp& op) {
+    if (dry || err != hipSuccess) return;
+    if (nheld >= 0 && nheld < JOINT_MAX) held[nheld++] = op;
+    else run(dt == LR_F32 ? gemm_f32(op, st) : gemm_bf16(op, st));
+  }
 };
 
 #define LAUNCH(c, call) do { if (!(c).dry && (c).err == hipSuccess) (c).run(call); } while (0)
@@ -52,13 +66,13 @@ const void* kmajor_to_kcontig(Ctx& c, const void* in, int64_t ld_in, int64_t k_r
 // wants k contiguous, so k-major operands are first copied through a transpose.
 void gemm(Ctx& c, GemmOp op) {
   if (c.dt == LR_F32) {
-    LAUNCH(c, gemm_f32(op, c.st));
+    c.submit(op);
     return;
   }
   // read in place: a weight gradient's two k-major operands, and a k-major weight under the smaller tiles (a size
   // query leaves room for the copy: it does not know the epilogue of the call, which the choice of tile looks at)
   if (gemm_bf16_kmajor_ok(op) || (!c.dry && gemm_bf16_mixed_ok(op))) {
-    LAUNCH(c, gemm_bf16(op, c.st));
+    c.submit(op);
     return;
   }
   // everything below runs k-contiguous on the 256-row tiles; the choice was made with the k-major form in view
@@ -119,14 +133,17 @@ void wgrad(Ctx& c, const void* Aact, int64_t lda, int Mw, const void* Bact, int6
     return;
   }
   if (direct) {
-    op.C = dw; op.ldc = Nw; op.sC = (int64_t)Mw * Nw;
+    op.C = dw; op.ldc = Nw; op.sC = (int64_t)Mw * Nw;   // (nothing in scratch: may be held)
     if (c.gdt == LR_BF16) op.epi.kind = EPI_STORE;   // EPI_PARTIAL stores fp32
     gemm(c, op);
     return;
   }
   float* part = (float*)c.take((size_t)op.splitk * Mw * Nw * sizeof(float));
   op.C = part; op.ldc = Nw;
+  const int held = c.nheld;      // its partials are scratch: not held
+  c.nheld = -1;
   gemm(c, op);
+  c.nheld = held;
   LAUNCH(c, k_wgrad_finish(part, op.splitk, Mw, Nw, dw, colscale, w_for_dgamma, dgamma_part, accumulate, c.dt, c.gdt, c.st));
   c.release(m);
 }
@@ -147,14 +164,16 @@ struct LinArgs {
 
 void linear_fwd_seq(Ctx& c, const LinArgs& a) {
   const size_t es = esize(c.dt);
+  // sigma(z) as a second output of the down-projection; with sigma = identity it is z itself
+  const bool ident = a.act == LR_ACT_IDENTITY;
   void* act = c.take((size_t)a.T * a.r * es);
   GemmOp dn;
   dn.A = a.x; dn.lda = a.ldx; dn.B = a.w_down; dn.ldb = a.d_in; dn.C = a.z; dn.ldc = a.r;
   dn.M = (int)a.T; dn.N = (int)a.r; dn.K = (int)a.d_in;
-  dn.epi.kind = EPI_DOWN; dn.epi.act = a.act; dn.epi.C2 = act; dn.epi.ldc2 = a.r;
+  dn.epi.kind = EPI_DOWN; dn.epi.act = a.act; dn.epi.C2 = ident ? nullptr : act; dn.epi.ldc2 = a.r;
   gemm(c, dn);
   GemmOp up;
-  up.A = act; up.lda = a.r; up.B = a.w_up; up.ldb = a.r; up.C = a.y; up.ldc = a.ldy;
+  up.A = ident ? a.z : act; up.lda = a.r; up.B = a.w_up; up.ldb = a.r; up.C = a.y; up.ldc = a.ldy;
   up.M = (int)a.T; up.N = (int)a.d_out; up.K = (int)a.r;
   up.epi.kind = EPI_STORE;
   gemm(c, up);
@@ -162,17 +181,20 @@ void linear_fwd_seq(Ctx& c, const LinArgs& a) {
 
 void linear_bwd_seq(Ctx& c, const LinArgs& a) {
   const size_t es = esize(c.dt);
-  void* act = c.take((size_t)a.T * a.r * es);
+  const bool ident = a.act == LR_ACT_IDENTITY;
+  void* act_ws = c.take((size_t)a.T * a.r * es);
+  const void* act = ident ? a.zc : act_ws;
   void* dz = c.take((size_t)a.T * a.r * es);
-  LAUNCH(c, k_act_fwd(a.zc, a.r, act, a.r, a.T, a.r, a.act, c.dt, c.st));
-  // dW_up = dy^T . sigma(z)
-  wgrad(c, a.dy, a.lddy, (int)a.d_out, act, a.r, (int)a.r, a.T, a.dw_up, nullptr, nullptr, nullptr, a.accumulate);
-  // dz = (dy . W_up) * sigma'(z)
+  // dz = (dy . W_up) * sigma'(z), and sigma(z), whose z tiles that epilogue holds anyway
   GemmOp da;
   da.A = a.dy; da.lda = a.lddy; da.B = a.w_up; da.ldb = a.r; da.transB = 1; da.C = dz; da.ldc = a.r;
   da.M = (int)a.T; da.N = (int)a.r; da.K = (int)a.d_out;
-  da.epi.kind = EPI_ACTGRAD; da.epi.act = a.act; da.epi.R = a.zc; da.epi.ldr = a.r;
+  da.epi.kind = ident ? EPI_ACTGRAD : EPI_ACTGRAD_A; da.epi.act = a.act; da.epi.R = a.zc; da.epi.ldr = a.r;
+  if (!ident) { da.epi.C2 = act_ws; da.epi.ldc2 = a.r; }
   gemm(c, da);
+  c.hold();   // three products that wait for dz and sigma(z) only
+  // dW_up = dy^T . sigma(z)
+  wgrad(c, a.dy, a.lddy, (int)a.d_out, act, a.r, (int)a.r, a.T, a.dw_up, nullptr, nullptr, nullptr, a.accumulate);
   // dW_down = dz^T . x
   wgrad(c, dz, a.r, (int)a.r, a.x, a.ldx, (int)a.d_in, a.T, a.dw_down, nullptr, nullptr, nullptr, a.accumulate);
   // dx = dz . W_down
@@ -181,6 +203,7 @@ void linear_bwd_seq(Ctx& c, const LinArgs& a) {
   dx.M = (int)a.T; dx.N = (int)a.d_in; dx.K = (int)a.r;
   dx.epi.kind = EPI_STORE;
   gemm(c, dx);
+  c.flush();
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -308,24 +331,29 @@ void group_up_seq(Ctx& c, const GrpArgs& a, const void* act) {
 void group_fwd_seq(Ctx& c, const GrpArgs& a) {
   const size_t es = esize(c.dt);
   void* act = a.act_out ? a.act_out : c.take((size_t)a.T * a.G * a.r * es);
-  group_down_seq(c, a, act);
-  if (a.norm != LR_NORM_SHARD_LOCAL) group_up_seq(c, a, act);
+  const bool ident = !a.act_out && a.act == LR_ACT_IDENTITY;   // sigma(z) is z itself
+  group_down_seq(c, a, ident ? nullptr : act);
+  if (a.norm != LR_NORM_SHARD_LOCAL) group_up_seq(c, a, ident ? a.z_cat : act);
 }
 
-// Backward of the group.  `act` = sigma(z_cat) must already be in place.
-void group_bwd_seq(Ctx& c, const GrpArgs& a, const void* act) {
+// Backward of the group.  `act` = sigma(z_cat): in place already, or (act_new) a buffer that the data gradient's epilogue
+// fills, which holds the z tiles anyway.
+void group_bwd_seq(Ctx& c, const GrpArgs& a, const void* act, bool act_new = false) {
   const size_t es = esize(c.dt);
   const int64_t GR = (int64_t)a.G * a.r;
   const bool normed = a.norm != LR_NORM_NONE;
   GrpRun run[2];
   const int nrun = group_runs(a, run);
   // dW_up[g] = dy_g^T . sigma(z_g)
-  for (int i = 0; i < nrun; i++) {
-    const GrpRun& u = run[i];
-    wgrad(c, (const char*)a.dy_stack + (size_t)u.dy_off * es, u.lddy, (int)u.d_out, (const char*)act + (size_t)u.g0 * a.r * es,
-          GR, (int)a.r, a.T, (char*)a.dw_up_stack + (size_t)u.w_off * esize(c.gdt), nullptr, nullptr, nullptr,
-          a.accumulate, u.n, u.dy_bs, a.r);
-  }
+  auto up_weights = [&] {
+    for (int i = 0; i < nrun; i++) {
+      const GrpRun& u = run[i];
+      wgrad(c, (const char*)a.dy_stack + (size_t)u.dy_off * es, u.lddy, (int)u.d_out, (const char*)act + (size_t)u.g0 * a.r * es,
+            GR, (int)a.r, a.T, (char*)a.dw_up_stack + (size_t)u.w_off * esize(c.gdt), nullptr, nullptr, nullptr,
+            a.accumulate, u.n, u.dy_bs, a.r);
+    }
+  };
+  if (!act_new) up_weights();
   // dp_g = rho * (dy_g . W_up_g) * sigma'(z_g), batched over g, written into the columns of dp_cat;
   // cdot[t] = sum_n dp[t,n] z[t,n] is the RMSNorm-backward statistic, taken at rank r.
   void* dp = c.take((size_t)a.T * GR * es);
@@ -346,6 +374,9 @@ void group_bwd_seq(Ctx& c, const GrpArgs& a, const void* act) {
       da.epi.kind = EPI_LAXGRAD;
       da.epi.R2 = at(a.dz_next, u.g0); da.epi.ldr2 = GR; da.epi.sR2 = a.r;
       da.epi.C2 = (void*)at(a.dh_prev, u.g0); da.epi.ldc2 = GR; da.epi.sC2 = a.r;
+    } else if (act_new) {
+      da.epi.kind = EPI_ACTGRAD_A;
+      da.epi.C2 = (void*)at(act, u.g0); da.epi.ldc2 = GR; da.epi.sC2 = a.r;
     }
     if (normed) {
       da.epi.use_rho = 1; da.epi.rowa = a.statc; da.epi.inv_d = 1.f / (float)a.d_in; da.epi.eps = a.eps;
@@ -355,7 +386,7 @@ void group_bwd_seq(Ctx& c, const GrpArgs& a, const void* act) {
       }
     }
   }
-  if (c.dry && rp.slabs) rp.slabs = gemm_bf16_rowpart_slabs_max(das[0], {EPI_ACTGRAD, EPI_LAXGRAD});
+  if (c.dry && rp.slabs) rp.slabs = gemm_bf16_rowpart_slabs_max(das[0], {EPI_ACTGRAD, EPI_ACTGRAD_A, EPI_LAXGRAD});
   const int nparts = rp.slabs * a.G;
   float* parts = nparts ? (float*)c.take((size_t)a.T * nparts * sizeof(float)) : nullptr;
   for (int i = 0; i < nrun; i++) {
@@ -364,6 +395,7 @@ void group_bwd_seq(Ctx& c, const GrpArgs& a, const void* act) {
     }
     gemm(c, das[i]);
   }
+  if (act_new) up_weights();
   if (nparts) {
     LAUNCH(c, k_rowsum_parts(parts, nparts, a.G, rp, cdot, a.T, c.st));
   } else if (normed) {
@@ -407,8 +439,8 @@ void group_bwd_full_seq(Ctx& c, const GrpArgs& a) {
   const size_t es = esize(c.dt);
   const int64_t GR = (int64_t)a.G * a.r;
   void* act = c.take((size_t)a.T * GR * es);
-  LAUNCH(c, k_act_fwd(a.zc, GR, act, GR, a.T, GR, a.act, c.dt, c.st));
-  group_bwd_seq(c, a, act);
+  if (a.act == LR_ACT_IDENTITY && !c.dry) group_bwd_seq(c, a, a.zc);   // (the order of the other form needs more workspace)
+  else group_bwd_seq(c, a, act, true);
 }
 
 // ---- validation helpers -------------------------------------------------------------------------

@@ -34,11 +34,12 @@ enum EpiKind : int {
   EPI_UP_O32 = 10,
   EPI_UP_I32 = 11,
   EPI_NORMBWD_O32 = 12,
-  EPI_NORMBWD_I32 = 13
+  EPI_NORMBWD_I32 = 13,
+  EPI_ACTGRAD_A = 14   // EPI_ACTGRAD, and C2 = act(R): the rank-r activation that the up-projection's weight gradient reads
 };
 // the formula an epilogue kind applies (the fp32-residual forms share EPI_UP's and EPI_NORMBWD's)
 constexpr int epi_base(int kind) {
-  return (kind == EPI_UP_O32 || kind == EPI_UP_I32) ? (int)EPI_UP
+  return kind == EPI_ACTGRAD_A ? (int)EPI_ACTGRAD : (kind == EPI_UP_O32 || kind == EPI_UP_I32) ? (int)EPI_UP
          : (kind == EPI_NORMBWD_O32 || kind == EPI_NORMBWD_I32) ? (int)EPI_NORMBWD : kind;
 }
 constexpr bool epi_r_is_f32(int kind) { return kind == EPI_UP_I32 || kind == EPI_NORMBWD_I32; }
@@ -110,6 +111,13 @@ int gemm_bf16_rowpart_slabs_max(GemmOp op, std::initializer_list<int> kinds);
 int gemm_bf16_wgrad_splits(int M, int N, int K);
 struct WgradPlan { int tile, splitk, k_parts; };
 WgradPlan gemm_bf16_plan_wgrad(int M, int N, int K, int batch, bool direct);
+// Up to JOINT_MAX products of one launch that do not depend on each other (gemm_joint.hip), on 32 x 32 or 64 x 64 tiles.
+constexpr int JOINT_MAX = 4;
+bool gemm_bf16_joint_ok(const GemmOp& op);
+hipError_t gemm_bf16_joint32(const GemmOp* ops, int n, hipStream_t st);
+hipError_t gemm_bf16_joint64(const GemmOp* ops, int n, hipStream_t st);
+// Runs n independent products, together where that is estimated to be faster.
+hipError_t gemm_bf16_many(const GemmOp* ops, int n, hipStream_t st);
 hipError_t gemm_ring32(const GemmOp& op, hipStream_t st);
 hipError_t gemm_ring64(const GemmOp& op, hipStream_t st);
 hipError_t gemm_ring64x128(const GemmOp& op, hipStream_t st);
@@ -123,6 +131,7 @@ hipError_t gemm_bf16_untimed(const GemmOp& op, hipStream_t st);
 // true when gemm_bf16 can run `op` with both operands k-major (no transposed copies needed)
 bool gemm_bf16_kmajor_ok(const GemmOp& op);
 hipError_t gemm_f32(const GemmOp& op, hipStream_t st);
+hipError_t gemm_f32_many(const GemmOp* ops, int n, hipStream_t st);   // independent products, in one launch where they are small
 int gemm_f32_pick_splitk(int M, int N, int K);   // weight gradients in fp32: K = T
 // Benchmark aid: launches bracketed by HIP events on their stream (every gemm_bf16 launch, tagged with
 // its epilogue kind, and whatever the sequencing code opens and closes itself, tags >= LR_TAG_ATTN_FWD).

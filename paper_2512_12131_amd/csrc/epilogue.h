@@ -66,7 +66,7 @@ struct VecIO<bf16_t, 1> {
 template <int KIND>
 __device__ __forceinline__ bool epi_reads_r(const Epilogue& e) {
   if constexpr (KIND == EPI_UP || KIND == EPI_NORMBWD || KIND == EPI_DOWN_LAX || KIND == EPI_LAXGRAD) return e.R != nullptr;
-  return KIND == EPI_ACTGRAD || KIND == EPI_SWIGLU_BWD || KIND == EPI_SWIGLU_FWD;
+  return epi_base(KIND) == EPI_ACTGRAD || KIND == EPI_SWIGLU_BWD || KIND == EPI_SWIGLU_FWD;
 }
 template <int KIND>
 __device__ __forceinline__ bool epi_reads_r2(const Epilogue& e) {
@@ -75,7 +75,7 @@ __device__ __forceinline__ bool epi_reads_r2(const Epilogue& e) {
 }
 
 // The arithmetic of an epilogue kind on NV consecutive columns of one row.  v[NV]: accumulators in,
-// primary output out; v2[NV]: secondary output (EPI_DOWN with want2, EPI_SWIGLU_BWD); r[NV], r2[NV]:
+// primary output out; v2[NV]: secondary output (EPI_DOWN and EPI_ACTGRAD with want2, EPI_SWIGLU_BWD); r[NV], r2[NV]:
 // the matching entries of the auxiliary tiles (zeros where a kind's tile is absent: adding them is
 // harmless).  rho / rowb: per-row scalars resolved by the caller (rho = 1 when unused).  fp32 throughout;
 // returns this thread's contribution to the row partial (0 if the kind has none).
@@ -102,6 +102,7 @@ __device__ __forceinline__ float epi_math(int act, float inv_d, bool want2, floa
   } else if constexpr (KIND == EPI_ACTGRAD) {
 #pragma unroll
     for (int i = 0; i < NV; i++) {
+      if (want2) v2[i] = act_f(r[i], act);
       v[i] = v[i] * act_prime_f(r[i], act) * rho;
       part += v[i] * r[i];
     }
@@ -144,8 +145,8 @@ __device__ __forceinline__ float epi_compute(const Epilogue& e, void* C, int64_t
   using IO = VecIO<ST, NV>;
   float v2[NV];
   const bool want2 = KIND == EPI_SWIGLU_BWD || KIND == EPI_SWIGLU_FWD || KIND == EPI_DOWN_LAX || KIND == EPI_LAXGRAD ||
-                     (KIND == EPI_DOWN && e.C2 != nullptr);
-  const float part = epi_math<NV, KIND, std::is_same<ST, bf16_t>::value>(e.act, e.inv_d, want2, v, v2, rho, rowb, r, r2);
+                     KIND == EPI_ACTGRAD_A || (KIND == EPI_DOWN && e.C2 != nullptr);
+  const float part = epi_math<NV, epi_base(KIND), std::is_same<ST, bf16_t>::value>(e.act, e.inv_d, want2, v, v2, rho, rowb, r, r2);
   if (KIND != EPI_SWIGLU_FWD || C != nullptr) IO::store(C, (int64_t)b * sC + m * ldc + n, v);
   if (want2 && e.C2 != nullptr) IO::store(e.C2, (int64_t)b * e.sC2 + m * e.ldc2 + n, v2);
   return part;

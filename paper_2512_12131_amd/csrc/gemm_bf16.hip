@@ -379,6 +379,7 @@ hipError_t dispatch(const GemmOp& op, hipStream_t st) {
       return op.epi.stat_from_a ? launch<T, EPI_DOWN, true>(op, st) : launch<T, EPI_DOWN, false>(op, st);
     case EPI_UP: return launch<T, EPI_UP, false>(op, st);
     case EPI_ACTGRAD: return launch<T, EPI_ACTGRAD, false>(op, st);
+    case EPI_ACTGRAD_A: return launch<T, EPI_ACTGRAD_A, false>(op, st);
     case EPI_NORMBWD: return launch<T, EPI_NORMBWD, false>(op, st);
     case EPI_PARTIAL: return launch<T, EPI_PARTIAL, false>(op, st);
     case EPI_SWIGLU_BWD: return launch<T, EPI_SWIGLU_BWD, false>(op, st);
@@ -432,7 +433,8 @@ float epi_traffic(int kind) {
   switch (kind) {
     case EPI_STORE: return 1.f;
     case EPI_DOWN: case EPI_UP: case EPI_ACTGRAD: case EPI_PARTIAL: return 2.f;
-    case EPI_UP_I32: case EPI_NORMBWD: case EPI_SWIGLU_FWD: case EPI_DOWN_LAX: return 3.f;
+    case EPI_UP_I32: case EPI_NORMBWD: case EPI_SWIGLU_FWD: case EPI_DOWN_LAX:
+    case EPI_ACTGRAD_A: return 3.f;
     case EPI_UP_O32: case EPI_NORMBWD_I32: case EPI_SWIGLU_BWD: case EPI_LAXGRAD: return 4.f;
     default: return 5.f;   // EPI_NORMBWD_O32
   }
@@ -447,6 +449,8 @@ float tile_time(int tile, int M, int N, int nk, int members, float e, float slic
   if (u > 0.f) t += c.f + (c.g * u + c.h) * e + (float)nk * slice * (c.s0 + c.s1 * u);
   return t;
 }
+// From the end of one launch to the start of the next.
+constexpr float kLaunchGap = 1.5f;
 // The smaller tiles have to be estimated 7.5 % faster than T256 before they are taken: the estimate's own error.
 constexpr float kRingMargin = 1.075f;
 // What a slice costs more with two k-major operands.  The 256-row kernels pay for their transpose reads.  The ring
@@ -634,12 +638,47 @@ int launch_timer_end(lr_launch_record* out, int max_records, int* n_records) {
 
 hipError_t gemm_bf16(const GemmOp& op, hipStream_t st) {
   if (!g_timer.on || op.M <= 0 || op.N <= 0 || op.batch <= 0) return gemm_bf16_untimed(op, st);
-  // two k-major operands: a weight gradient, also where it stores bf16 itself
-  const int tag = op.splitk > 1 || (op.transA && op.transB) ? (int)EPI_PARTIAL : op.epi.kind;
+  // two k-major operands: a weight gradient, also where it stores bf16 itself; EPI_ACTGRAD_A: the class of EPI_ACTGRAD
+  const int tag = op.splitk > 1 || (op.transA && op.transB) ? (int)EPI_PARTIAL : op.epi.kind == EPI_ACTGRAD_A ? (int)EPI_ACTGRAD : op.epi.kind;
   const int slot = launch_timer_open(tag, op.M, op.N, op.K, op.batch, 2.0 * op.M * op.N * (double)op.K * op.batch, st);
   hipError_t e = gemm_bf16_untimed(op, st);
   launch_timer_close(slot, st);
   return e;
+}
+
+hipError_t gemm_bf16_many(const GemmOp* ops, int n, hipStream_t st) {
+  // Apart, each on its best tile, a launch each; or together on 32 x 32 or 64 x 64 tiles, the workgroups of all
+  // sharing the chip: as long as the longest of them or as all of their work, whichever is more.
+  bool ok = n > 1 && n <= JOINT_MAX && !g_timer.on;
+  float apart = 0.f, joint[2] = {0.f, 0.f};
+  const int tiles[2] = {GEMM_R32, GEMM_R64};
+  for (int i = 0; ok && i < n; i++) ok = gemm_bf16_joint_ok(ops[i]);
+  if (ok) {
+    float longest[2] = {0.f, 0.f};
+    for (int i = 0; i < n; i++) {
+      const GemmOp& op = ops[i];
+      const int nk = (op.K + BK - 1) / BK, best = gemm_bf16_tile(op);
+      const bool km = op.transA && op.transB;
+      const float e = epi_traffic(op.epi.kind);
+      apart += tile_time(best, op.M, op.N, nk, op.batch, e, km ? kKMajorSlice[best] : 1.f) + kLaunchGap;
+      for (int t = 0; t < 2; t++) {
+        const TileCost& c = kTileCost[tiles[t]];
+        const float slice = km ? kKMajorSlice[tiles[t]] : 1.f;
+        const float wgs = (float)((op.M + c.bm - 1) / c.bm) * (float)((op.N + c.bn - 1) / c.bn) * (float)op.batch;
+        const float one = c.f + (c.g + c.h) * e + (float)nk * slice * (c.s0 + c.s1);
+        joint[t] += wgs * one / (float)c.slots;
+        if (one > longest[t]) longest[t] = one;
+      }
+    }
+    for (int t = 0; t < 2; t++) joint[t] = kTileCost[tiles[t]].a + kLaunchGap + (joint[t] > longest[t] ? joint[t] + 0.5f * longest[t] : longest[t]);
+    if (joint[0] <= joint[1] && joint[0] < apart) return gemm_bf16_joint32(ops, n, st);
+    if (joint[1] < apart) return gemm_bf16_joint64(ops, n, st);
+  }
+  for (int i = 0; i < n; i++) {
+    const hipError_t e = gemm_bf16(ops[i], st);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 bool gemm_bf16_kmajor_ok(const GemmOp& op) {

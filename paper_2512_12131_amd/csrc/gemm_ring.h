@@ -93,15 +93,16 @@ __device__ __forceinline__ int kmajor_swz(int k) {
 }
 
 // PARTS: k runs in op.k_parts parts that are summed one by one, as split-K partials are.
+// bid: this workgroup among the `total` of the product.
 template <class T, int KIND, bool STAT_A, bool AKM, bool BKM, bool PARTS>
-__global__ __launch_bounds__(T::NT) void gemm_ring_kernel(GemmOp op, int kper, int tiles_m, int tiles_n) {
+__device__ __forceinline__ void ring_product(const GemmOp& op, int kper, int tiles_m, int tiles_n, int bid, int total) {
   static_assert(!(STAT_A && AKM), "row statistics are gathered from k-contiguous rows");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / T::WN, wn = wave % T::WN;        // (of a multiplying wavefront)
   const int lw = T::NL > 0 ? wave - T::NW : wave;        // index among the loading wavefronts (below 0: not one)
   int tm, tn, bz;
-  tile_of_block(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y, tiles_m, tiles_n, tm, tn, bz);
+  tile_of_block(bid, total, tiles_m, tiles_n, tm, tn, bz);
   if (AKM && BKM && op.causal_k) tm = tiles_m - 1 - tm;   // the longest k ranges of a batch member first
   const int m0 = tm * T::BM, n0 = tn * T::BN;
   const int b = bz / op.splitk, ks = bz % op.splitk;
@@ -311,6 +312,11 @@ __global__ __launch_bounds__(T::NT) void gemm_ring_kernel(GemmOp op, int kper, i
   gemm_epilogue<T, KIND, STAT_A>(op, acc, smem, sStat, wave, lane, m0, n0, tn, tiles_n, b, bi, bo, bz);
 }
 
+template <class T, int KIND, bool STAT_A, bool AKM, bool BKM, bool PARTS>
+__global__ __launch_bounds__(T::NT) void gemm_ring_kernel(GemmOp op, int kper, int tiles_m, int tiles_n) {
+  ring_product<T, KIND, STAT_A, AKM, BKM, PARTS>(op, kper, tiles_m, tiles_n, blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y);
+}
+
 template <class T, int KIND, bool STAT_A, bool AKM, bool BKM, bool PARTS = false>
 hipError_t launch_ring(const GemmOp& op, hipStream_t st) {
   if (!PARTS && op.k_parts != 1) return hipErrorInvalidValue;
@@ -352,6 +358,7 @@ hipError_t dispatch_ring(const GemmOp& op, hipStream_t st) {
       case EPI_STORE: return launch_ring<T, EPI_STORE, false, false, true>(op, st);
       case EPI_UP: return launch_ring<T, EPI_UP, false, false, true>(op, st);
       case EPI_ACTGRAD: return launch_ring<T, EPI_ACTGRAD, false, false, true>(op, st);
+      case EPI_ACTGRAD_A: return launch_ring<T, EPI_ACTGRAD_A, false, false, true>(op, st);
       case EPI_LAXGRAD: return launch_ring<T, EPI_LAXGRAD, false, false, true>(op, st);
       case EPI_NORMBWD: return launch_ring<T, EPI_NORMBWD, false, false, true>(op, st);
       case EPI_NORMBWD_O32: return launch_ring<T, EPI_NORMBWD_O32, false, false, true>(op, st);

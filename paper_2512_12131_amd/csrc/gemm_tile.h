@@ -148,7 +148,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T:
   const uint32_t colC = col_ok ? (uint32_t)coln * (PARTIAL ? 4u : 2u) : EOOB, col2 = col_ok ? (uint32_t)coln * 2u : EOOB;
   const uint32_t col4 = col_ok ? (uint32_t)coln * 4u : EOOB;      // this lane's columns in an fp32 tile
   const bool want2 = KIND == EPI_SWIGLU_BWD || KIND == EPI_SWIGLU_FWD || KIND == EPI_DOWN_LAX || KIND == EPI_LAXGRAD ||
-                     (KIND == EPI_DOWN && e.C2 != nullptr);
+                     KIND == EPI_ACTGRAD_A || (KIND == EPI_DOWN && e.C2 != nullptr);
   const bool use_rho = !PARTIAL && e.use_rho;
   const bool rho_sqrt = e.rho_sqrt != 0;
   // row partials [M, rowpart_ld] and the statistic [M]: one lane per row writes, the others (and rows

@@ -1,0 +1,50 @@
+"""The three products at the end of a layer's backward run in one launch where they are small.  Added to zeros instead of
+written, the weight gradients take their own launches and a finishing pass: every output has to have the same bits."""
+import pytest
+import torch
+
+from paper_2512_12131_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _both(T, d_in, r, d_out, dt, act, grad_dt):
+    g = torch.Generator().manual_seed(T + r)
+    x, wd, wu, dy = (torch.randn(s, generator=g).to(dt).to(DEV) for s in ((T, d_in), (r, d_in), (d_out, r), (T, d_out)))
+    z, y = B.lr_linear_fwd(x, wd, wu, act)
+    plain = B.lr_linear_bwd(x, wd, wu, z, dy, act, grad_dt=grad_dt)
+    gt = torch.float32 if grad_dt == B.LR_F32 else torch.bfloat16
+    zeros = tuple(torch.zeros(w.shape, dtype=gt, device=DEV) for w in (wd, wu))
+    added = B.lr_linear_bwd(x, wd, wu, z, dy, act, grads=zeros, grad_dt=grad_dt)
+    torch.cuda.synchronize()
+    return (x, wd, wu, dy, z), plain, added
+
+
+@pytest.mark.parametrize("grad_dt", [B.LR_F32, B.LR_BF16])
+@pytest.mark.parametrize("act", [B.LR_ACT_SILU, B.LR_ACT_IDENTITY])
+@pytest.mark.parametrize("T,d_in,r,d_out", [(1, 8, 8, 8), (31, 40, 24, 72), (32, 64, 32, 64), (33, 128, 40, 96), (65, 256, 64, 24),
+                                            (513, 264, 72, 520), (1031, 1024, 256, 768), (2050, 512, 128, 512)])
+def test_bf16(T, d_in, r, d_out, act, grad_dt):
+    print(f"joint bf16 T={T} {d_in}->{r}->{d_out} act={act}", flush=True)
+    _, plain, added = _both(T, d_in, r, d_out, torch.bfloat16, act, grad_dt)
+    for a, b in zip(plain, added):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("act", [B.LR_ACT_SILU, B.LR_ACT_IDENTITY])
+@pytest.mark.parametrize("T,d_in,r,d_out", [(1, 1, 1, 1), (31, 33, 5, 7), (64, 32, 32, 96), (129, 127, 33, 65), (512, 256, 64, 256),
+                                            (1023, 511, 127, 509)])
+def test_f32(T, d_in, r, d_out, act):
+    """... and in 32 bits against 64: each gradient is one or two chained sums, and n terms added in 32 bits are off by at most
+    n 2^-24 times the sum of their magnitudes; the tested lengths stay below 2^11, in practice far below the bound."""
+    print(f"joint f32 T={T} {d_in}->{r}->{d_out} act={act}", flush=True)
+    (x, wd, wu, dy, z), plain, added = _both(T, d_in, r, d_out, torch.float32, act, B.LR_F32)
+    for a, b in zip(plain, added):
+        assert torch.equal(a, b)
+    x, wd, wu, dy, z = (t.double().cpu() for t in (x, wd, wu, dy, z))
+    s = torch.sigmoid(z)
+    sig, prime = (z * s, s * (1 + z * (1 - s))) if act == B.LR_ACT_SILU else (z, torch.ones_like(z))
+    dz = (dy @ wu) * prime
+    for got, ref in zip(plain, (dz @ wd, dz.t() @ x, dy.t() @ sig)):
+        assert (got.double().cpu() - ref).norm() <= 2.0 ** 11 * 2.0 ** -24 * ref.norm()
