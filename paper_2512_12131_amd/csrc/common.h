@@ -119,6 +119,8 @@ hipError_t gemm_bf16_joint64(const GemmOp* ops, int n, hipStream_t st);
 // Runs n independent products, together where that is estimated to be faster.
 hipError_t gemm_bf16_many(const GemmOp* ops, int n, hipStream_t st);
 hipError_t gemm_ring32(const GemmOp& op, hipStream_t st);
+bool gemm_rows16_ok(const GemmOp& op);                        // GEMM_R32 as 16 x 16 pieces (gemm_rows16.hip)
+hipError_t gemm_rows16(const GemmOp& op, hipStream_t st);
 hipError_t gemm_ring64(const GemmOp& op, hipStream_t st);
 hipError_t gemm_ring64x128(const GemmOp& op, hipStream_t st);
 hipError_t gemm_ring128(const GemmOp& op, hipStream_t st);

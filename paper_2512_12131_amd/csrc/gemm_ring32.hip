@@ -3,5 +3,8 @@
 #include "gemm_ring.h"
 
 namespace lrb {
-hipError_t gemm_ring32(const GemmOp& op, hipStream_t st) { return dispatch_ring<RingTile<32, 32, 1, 1, 2, 5, 4>>(op, st); }
+hipError_t gemm_ring32(const GemmOp& op, hipStream_t st) {
+  if (gemm_rows16_ok(op)) return gemm_rows16(op, st);
+  return dispatch_ring<RingTile<32, 32, 1, 1, 2, 5, 4>>(op, st);
+}
 }  // namespace lrb
