@@ -38,9 +38,18 @@ struct Ctx {
   void release(size_t m) { off = m; }   // stack discipline: drop everything taken since mark()
   void run(hipError_t e) { if (err == hipSuccess && e != hipSuccess) err = e; }
   void hold() { nheld = 0; }
-  void flush() {
-    if (!dry && err == hipSuccess && nheld > 0) run(dt == LR_F32 ? gemm_f32_many(held, nheld, st) : gemm_bf16_many(held, nheld, st));
+  // tile: the one the held products were found to be faster on together (row partials are laid out for it), or 0
+  void flush(int tile = 0) {
+    if (!dry && err == hipSuccess && nheld > 0)
+      run(tile ? gemm_bf16_joint(tile, held, nheld, st) : dt == LR_F32 ? gemm_f32_many(held, nheld, st) : gemm_bf16_many(held, nheld, st));
     nheld = -1;
+  }
+  // the tile on which the held products and n more would run together, or 0
+  int join_tile(const GemmOp* more, int n) const {
+    if (dry || dt != LR_BF16 || nheld < 0 || nheld + n > JOINT_MAX) return 0;
+    GemmOp all[JOINT_MAX];
+    for (int i = 0; i < nheld + n; i++) all[i] = i < nheld ? held[i] : more[i - nheld];
+    return gemm_bf16_join_tile(all, nheld + n);
   }
   // launches a product whose operands lie where they stay (nothing of it in scratch that is given back), or holds it
   void submit(const GemmOp& op) {
@@ -75,9 +84,14 @@ void gemm(Ctx& c, GemmOp op) {
     c.submit(op);
     return;
   }
+  if (!op.transA && !op.transB) {
+    op.K = (int)rup(op.K, 8);
+    c.submit(op);
+    return;
+  }
   // everything below runs k-contiguous on the 256-row tiles; the choice was made with the k-major form in view
   // and its row partials are laid out for it
-  if (op.transA || op.transB) op.tile = GEMM_T256;
+  op.tile = GEMM_T256;
   const size_t m = c.mark();
   if (op.transA) {
     // only un-batched k-major A operands occur (weight gradients)
@@ -103,17 +117,23 @@ void gemm(Ctx& c, GemmOp op) {
   c.release(m);  // the stream orders later reuse of the transposed copies after this GEMM
 }
 
+// the product of a weight gradient, k-major operands, its output still to be set
+GemmOp wgrad_op(const void* Aact, int64_t lda, int Mw, const void* Bact, int64_t ldb, int Nw, int64_t T, int n, int64_t sA, int64_t sB) {
+  GemmOp op;
+  op.A = Aact; op.lda = lda; op.transA = 1; op.sA = sA;
+  op.B = Bact; op.ldb = ldb; op.transB = 1; op.sB = sB;
+  op.M = Mw; op.N = Nw; op.K = (int)T; op.batch = n;
+  op.epi.kind = EPI_PARTIAL;
+  return op;
+}
+
 // dw[Mw, Nw] (+)= colscale * sum_t Aact[t, Mw] * Bact[t, Nw]    (reduction over tokens, split-K)
 // n > 1: n such products, operands sA / sB elements apart, gradients stacked [n][Mw][Nw].
 void wgrad(Ctx& c, const void* Aact, int64_t lda, int Mw, const void* Bact, int64_t ldb, int Nw, int64_t T, void* dw,
            const void* colscale, const void* w_for_dgamma, float* dgamma_part, int accumulate, int n = 1, int64_t sA = 0,
            int64_t sB = 0) {
   const size_t m = c.mark();
-  GemmOp op;
-  op.A = Aact; op.lda = lda; op.transA = 1; op.sA = sA;
-  op.B = Bact; op.ldb = ldb; op.transB = 1; op.sB = sB;
-  op.M = Mw; op.N = Nw; op.K = (int)T; op.batch = n;
-  op.epi.kind = EPI_PARTIAL;
+  GemmOp op = wgrad_op(Aact, lda, Mw, Bact, ldb, Nw, T, n, sA, sB);
   const bool kmajor = c.dt == LR_F32 || gemm_bf16_kmajor_ok(op);
   // nothing to scale, add to or sum up: an un-split product is the gradient itself, in either output type
   const bool plain = !colscale && !w_for_dgamma && !accumulate && kmajor;
@@ -353,7 +373,10 @@ void group_bwd_seq(Ctx& c, const GrpArgs& a, const void* act, bool act_new = fal
             a.accumulate, u.n, u.dy_bs, a.r);
     }
   };
-  if (!act_new) up_weights();
+  if (!act_new) {
+    c.hold();   // ... beside the data gradient, which does not wait for it
+    up_weights();
+  }
   // dp_g = rho * (dy_g . W_up_g) * sigma'(z_g), batched over g, written into the columns of dp_cat;
   // cdot[t] = sum_n dp[t,n] z[t,n] is the RMSNorm-backward statistic, taken at rank r.
   void* dp = c.take((size_t)a.T * GR * es);
@@ -380,21 +403,36 @@ void group_bwd_seq(Ctx& c, const GrpArgs& a, const void* act, bool act_new = fal
     }
     if (normed) {
       da.epi.use_rho = 1; da.epi.rowa = a.statc; da.epi.inv_d = 1.f / (float)a.d_in; da.epi.eps = a.eps;
-      if (c.dt == LR_BF16) {
-        da.tile = i == 0 ? gemm_bf16_tile(da) : das[0].tile;
-        rp = gemm_bf16_rowparts(da);
-      }
     }
   }
-  if (c.dry && rp.slabs) rp.slabs = gemm_bf16_rowpart_slabs_max(das[0], {EPI_ACTGRAD, EPI_ACTGRAD_A, EPI_LAXGRAD});
+  // Joined with the weight gradients they run on 32- or 64-column tiles, which have the most row partials; a size query leaves
+  // room for those where the products are small enough to be joined at all.
+  const int64_t small_rows = 1024 / ((a.r + 31) / 32 * a.G) * 32;
+  const int join = a.T <= small_rows ? c.join_tile(das, nrun) : 0;
+  for (int i = 0; normed && c.dt == LR_BF16 && i < nrun; i++) {
+    das[i].tile = join ? join : i == 0 ? gemm_bf16_tile(das[0]) : das[0].tile;
+    rp = gemm_bf16_rowparts(das[i]);
+  }
+  int64_t parts_size = 0;
+  if (c.dry && rp.slabs) {
+    rp.slabs = gemm_bf16_rowpart_slabs_max(das[0], {EPI_ACTGRAD, EPI_ACTGRAD_A, EPI_LAXGRAD});
+    for (int t : {GEMM_R32, GEMM_R64}) {   // (for more tokens no less than for fewer)
+      das[0].tile = t;
+      const int64_t need = (a.T < small_rows ? a.T : small_rows) * gemm_bf16_rowparts(das[0]).slabs * a.G;
+      if (need > parts_size) parts_size = need;
+    }
+  }
   const int nparts = rp.slabs * a.G;
-  float* parts = nparts ? (float*)c.take((size_t)a.T * nparts * sizeof(float)) : nullptr;
+  if (a.T * nparts > parts_size) parts_size = a.T * nparts;
+  float* parts = nparts ? (float*)c.take((size_t)parts_size * sizeof(float)) : nullptr;
   for (int i = 0; i < nrun; i++) {
     if (nparts) {
       das[i].epi.rowpart = parts; das[i].epi.rowpart_ld = nparts; das[i].epi.rowpart_off = run[i].g0 * rp.slabs;
     }
-    gemm(c, das[i]);
+    if (join) c.submit(das[i]);
+    else { c.flush(); gemm(c, das[i]); }
   }
+  if (join) c.flush(join);
   if (act_new) up_weights();
   if (nparts) {
     LAUNCH(c, k_rowsum_parts(parts, nparts, a.G, rp, cdot, a.T, c.st));
@@ -403,19 +441,14 @@ void group_bwd_seq(Ctx& c, const GrpArgs& a, const void* act, bool act_new = fal
   }
   // dW_down_cat: with the norm folded in, the GEMM yields the gradient of (w * gamma); the finishing
   // pass scales it by gamma and also produces dgamma[k] = sum_n w[n,k] * dW'[n,k].
-  const void* wB = a.w_down_cat;
-  if (normed) {
-    const int64_t nparts = k_wgrad_dgamma_parts(GR);
-    float* dgp = (float*)c.take((size_t)nparts * a.d_in * sizeof(float));
-    wgrad(c, dp, GR, (int)GR, a.x, a.ldx, (int)a.d_in, a.T, a.dw_down_cat, a.gamma, a.w_down_cat, dgp, a.accumulate);
-    LAUNCH(c, k_colsum_parts(dgp, nparts, a.d_in, a.dgamma, a.accumulate, c.gdt, c.st));
-    wB = scaled_weight(c, a);
-  } else {
-    wgrad(c, dp, GR, (int)GR, a.x, a.ldx, (int)a.d_in, a.T, a.dw_down_cat, nullptr, nullptr, nullptr, a.accumulate);
-  }
+  GemmOp wd = wgrad_op(dp, GR, (int)GR, a.x, a.ldx, (int)a.d_in, a.T, 1, 0, 0);
+  int wd_join = 0;              // dW_down's partials and dx in one launch, on this tile
+  const int64_t dg_parts = normed ? k_wgrad_dgamma_parts(GR) : 0;
+  float* dgp = normed ? (float*)c.take((size_t)dg_parts * a.d_in * sizeof(float)) : nullptr;
+  auto dgamma = [&] { LAUNCH(c, k_colsum_parts(dgp, dg_parts, a.d_in, a.dgamma, a.accumulate, c.gdt, c.st)); };
   // dx = dp_cat . (w*gamma)  - (rho/d) * cdot * x  (+ residual gradient)
   GemmOp dx;
-  dx.A = dp; dx.lda = GR; dx.B = wB; dx.ldb = a.d_in; dx.transB = 1; dx.C = a.dx; dx.ldc = a.lddx;
+  dx.A = dp; dx.lda = GR; dx.B = a.w_down_cat; dx.ldb = a.d_in; dx.transB = 1; dx.C = a.dx; dx.ldc = a.lddx;
   dx.M = (int)a.T; dx.N = (int)a.d_in; dx.K = (int)GR;
   if (normed) {
     dx.epi.kind = EPI_NORMBWD; dx.epi.use_rho = 1; dx.epi.rowa = a.statc; dx.epi.rowb = cdot;
@@ -431,6 +464,31 @@ void group_bwd_seq(Ctx& c, const GrpArgs& a, const void* act, bool act_new = fal
     dx.epi.kind = EPI_UP; dx.epi.R = a.dres; dx.epi.ldr = a.lddres;
   } else {
     dx.epi.kind = EPI_STORE;
+  }
+  // (the folded weight has to be there already: folded here, it and the partials together would need more workspace)
+  if (normed && !c.dry && c.dt == LR_BF16 && a.w_scaled_given && a.w_scaled && gemm_bf16_kmajor_ok(wd)) {
+    const WgradPlan pl = gemm_bf16_plan_wgrad(wd.M, wd.N, wd.K, 1, false);
+    wd.tile = pl.tile; wd.splitk = pl.splitk; wd.k_parts = pl.k_parts;
+    const GemmOp both[2] = {wd, dx};
+    wd_join = gemm_bf16_join_tile(both, 2);
+  }
+  if (wd_join) {
+    const size_t m = c.mark();
+    wd.C = c.take((size_t)wd.splitk * wd.M * wd.N * sizeof(float)); wd.ldc = wd.N;
+    dx.B = a.w_scaled;
+    const GemmOp both[2] = {wd, dx};
+    LAUNCH(c, gemm_bf16_joint(wd_join, both, 2, c.st));
+    LAUNCH(c, k_wgrad_finish((const float*)wd.C, wd.splitk, wd.M, wd.N, a.dw_down_cat, a.gamma, a.w_down_cat, dgp, a.accumulate, c.dt, c.gdt, c.st));
+    dgamma();
+    c.release(m);
+    return;
+  }
+  if (normed) {
+    wgrad(c, dp, GR, (int)GR, a.x, a.ldx, (int)a.d_in, a.T, a.dw_down_cat, a.gamma, a.w_down_cat, dgp, a.accumulate);
+    dgamma();
+    dx.B = scaled_weight(c, a);
+  } else {
+    wgrad(c, dp, GR, (int)GR, a.x, a.ldx, (int)a.d_in, a.T, a.dw_down_cat, nullptr, nullptr, nullptr, a.accumulate);
   }
   gemm(c, dx);
 }
@@ -591,6 +649,7 @@ void mlp_up_swiglu(Ctx& c, const Blk& b, const void* w_up_gu, const void* act, v
   up.M = (int)b.T; up.N = (int)b.f; up.K = (int)b.r;
   up.epi.kind = EPI_STORE;
   gemm(c, up);
+  c.flush();            // (g, and what a caller holds beside it)
   up.A = (const char*)act + (size_t)b.r * es;
   up.B = (const char*)w_up_gu + (size_t)b.f * b.r * es;
   up.C = u;
@@ -744,13 +803,16 @@ void block_bwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   const char* w_scaled = fold_once ? (const char*)scaled_weights(c, b, p) : nullptr;
 
   // ---- MLP side ----
+  c.hold();             // down-D's weight gradient, dz_d, h1 and g wait for nothing but the activations
   single_up_bwd(c, b, dy, d, act_d, ck->z_d, p->w_up_d, g->w_up_d, dz1, accumulate, lax, lx->dz_next_d, lx->dh_prev_d);
   // re-forward from the rank-r checkpoints: h1, then g, u, m
   if (!sv) single_up(c, b, act_o, p->w_up_o, d, x, h1, nullptr);
   GrpArgs m = group_args(b, 2, f);
   m.x = h1; m.gamma = p->gamma2; m.w_down_cat = p->w_dn_gu; m.w_up_stack = p->w_up_gu; m.y_stack = big;
   if (!sv) mlp_up_swiglu(c, b, p->w_up_gu, act_g, big, (char*)big + (size_t)T * f * es, mm);
+  c.flush();
   // down-D backward: dW_dn_d = dz_d^T . m ; dm = dz_d . W_dn_d with the SwiGLU reverse fused in
+  c.hold();
   wgrad(c, dz1, r, (int)r, mm, f, (int)f, T, g->w_dn_d, nullptr, nullptr, nullptr, accumulate);
   {
     GemmOp dm;
@@ -760,6 +822,7 @@ void block_bwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
     dm.epi.ldr2 = f; dm.epi.C2 = (char*)big2 + (size_t)T * f * es; dm.epi.ldc2 = f;
     gemm(c, dm);
   }
+  c.flush();
   // gate/up group backward; dh1 = dy + RMSNorm-2 reverse
   m.zc = ck->z_gu; m.statc = ck->s2; m.dy_stack = big2; m.dx = dh1; m.dx32 = dh1f; m.dres = dy; m.dgamma = g->gamma2;
   m.dw_down_cat = g->w_dn_gu; m.dw_up_stack = g->w_up_gu; m.accumulate = accumulate;
@@ -768,15 +831,17 @@ void block_bwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   group_bwd_seq(c, m, act_g);
 
   // ---- attention side ----
-  single_up_bwd(c, b, dh1, d, act_o, ck->z_o, p->w_up_o, g->w_up_o, dz1, accumulate, lax, lx->dz_next_o, lx->dh_prev_o);
   // re-forward q, k, v, o
   if (!act_once) {
     const ActLayers aq{{ck->z_qkv}, {lx->h_prev_qkv}, {act_q}, {3 * row}, {}, 1};
     LAUNCH(c, k_act_layers_bf16(aq, act_kind, c.st));
   }
+  c.hold();             // q, k, v beside the backward through up-O
+  single_up_bwd(c, b, dh1, d, act_o, ck->z_o, p->w_up_o, g->w_up_o, dz1, accumulate, lax, lx->dz_next_o, lx->dh_prev_o);
   GrpArgs a = qkv_group_args(b);
   a.x = x; a.gamma = p->gamma1; a.w_down_cat = p->w_dn_qkv; a.w_up_stack = p->w_up_qkv; a.y_stack = qkv;
   if (!sv) group_up_seq(c, a, act_q);
+  c.flush();
   if (!sv && b.rope_cos) rope_qk(c, b, qkv, 0);
   const void* q_ = qkv; const void* k_ = (char*)qkv + (size_t)T * d * es; const void* v_ = (char*)qkv + (size_t)T * (d + dkv) * es;
   if (!sv) {
@@ -786,6 +851,7 @@ void block_bwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
     launch_timer_close(slot, c.st);
   }
   // down-O backward
+  c.hold();
   wgrad(c, dz1, r, (int)r, o, d, (int)d, T, g->w_dn_o, nullptr, nullptr, nullptr, accumulate);
   {
     GemmOp dO;
@@ -794,6 +860,7 @@ void block_bwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
     dO.epi.kind = EPI_STORE;
     gemm(c, dO);
   }
+  c.flush();
   {
     const size_t mk = c.mark();
     void* aws = c.take(attention_gqa_bwd_ws_bytes((int)b.B, (int)b.S, (int)b.H, (int)b.Hkv, (int)b.hd));

@@ -114,8 +114,9 @@ WgradPlan gemm_bf16_plan_wgrad(int M, int N, int K, int batch, bool direct);
 // Up to JOINT_MAX products of one launch that do not depend on each other (gemm_joint.hip), on 32 x 32 or 64 x 64 tiles.
 constexpr int JOINT_MAX = 4;
 bool gemm_bf16_joint_ok(const GemmOp& op);
-hipError_t gemm_bf16_joint32(const GemmOp* ops, int n, hipStream_t st);
-hipError_t gemm_bf16_joint64(const GemmOp* ops, int n, hipStream_t st);
+hipError_t gemm_bf16_joint(int tile, const GemmOp* ops, int n, hipStream_t st);   // tile: GEMM_R32 or GEMM_R64
+// The tile on which n independent products are estimated to be faster together than apart, or 0.
+int gemm_bf16_join_tile(const GemmOp* ops, int n);
 // Runs n independent products, together where that is estimated to be faster.
 hipError_t gemm_bf16_many(const GemmOp* ops, int n, hipStream_t st);
 hipError_t gemm_ring32(const GemmOp& op, hipStream_t st);

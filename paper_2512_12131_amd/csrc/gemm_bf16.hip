@@ -646,34 +646,38 @@ hipError_t gemm_bf16(const GemmOp& op, hipStream_t st) {
   return e;
 }
 
-hipError_t gemm_bf16_many(const GemmOp* ops, int n, hipStream_t st) {
+int gemm_bf16_join_tile(const GemmOp* ops, int n) {
   // Apart, each on its best tile, a launch each; or together on 32 x 32 or 64 x 64 tiles, the workgroups of all
   // sharing the chip: as long as the longest of them or as all of their work, whichever is more.
-  bool ok = n > 1 && n <= JOINT_MAX && !g_timer.on;
-  float apart = 0.f, joint[2] = {0.f, 0.f};
+  if (n < 2 || n > JOINT_MAX || g_timer.on) return 0;
+  float apart = 0.f, joint[2] = {0.f, 0.f}, longest[2] = {0.f, 0.f};
   const int tiles[2] = {GEMM_R32, GEMM_R64};
-  for (int i = 0; ok && i < n; i++) ok = gemm_bf16_joint_ok(ops[i]);
-  if (ok) {
-    float longest[2] = {0.f, 0.f};
-    for (int i = 0; i < n; i++) {
-      const GemmOp& op = ops[i];
-      const int nk = (op.K + BK - 1) / BK, best = gemm_bf16_tile(op);
-      const bool km = op.transA && op.transB;
-      const float e = epi_traffic(op.epi.kind);
-      apart += tile_time(best, op.M, op.N, nk, op.batch, e, km ? kKMajorSlice[best] : 1.f) + kLaunchGap;
-      for (int t = 0; t < 2; t++) {
-        const TileCost& c = kTileCost[tiles[t]];
-        const float slice = km ? kKMajorSlice[tiles[t]] : 1.f;
-        const float wgs = (float)((op.M + c.bm - 1) / c.bm) * (float)((op.N + c.bn - 1) / c.bn) * (float)op.batch;
-        const float one = c.f + (c.g + c.h) * e + (float)nk * slice * (c.s0 + c.s1);
-        joint[t] += wgs * one / (float)c.slots;
-        if (one > longest[t]) longest[t] = one;
-      }
+  for (int i = 0; i < n; i++) {
+    const GemmOp& op = ops[i];
+    if (!gemm_bf16_joint_ok(op)) return 0;
+    const int best = op.tile != GEMM_TILE_AUTO ? op.tile : gemm_bf16_tile(op), members = op.batch * op.splitk;
+    const int nk = ((op.K + op.splitk - 1) / op.splitk + BK - 1) / BK;
+    const bool km = op.transA && op.transB;
+    const float e = epi_traffic(op.epi.kind);
+    apart += tile_time(best, op.M, op.N, nk, members, e, km ? kKMajorSlice[best] : 1.f) + kLaunchGap;
+    for (int t = 0; t < 2; t++) {
+      const TileCost& c = kTileCost[tiles[t]];
+      const float slice = km ? kKMajorSlice[tiles[t]] : 1.f;
+      const float wgs = (float)((op.M + c.bm - 1) / c.bm) * (float)((op.N + c.bn - 1) / c.bn) * (float)members;
+      const float one = c.f + (c.g + c.h) * e + (float)nk * slice * (c.s0 + c.s1);
+      joint[t] += wgs * one / (float)c.slots;
+      if (one > longest[t]) longest[t] = one;
     }
-    for (int t = 0; t < 2; t++) joint[t] = kTileCost[tiles[t]].a + kLaunchGap + (joint[t] > longest[t] ? joint[t] + 0.5f * longest[t] : longest[t]);
-    if (joint[0] <= joint[1] && joint[0] < apart) return gemm_bf16_joint32(ops, n, st);
-    if (joint[1] < apart) return gemm_bf16_joint64(ops, n, st);
   }
+  for (int t = 0; t < 2; t++)
+    joint[t] = kTileCost[tiles[t]].a + kLaunchGap + (joint[t] > longest[t] ? joint[t] + 0.5f * longest[t] : longest[t]);
+  const int t = joint[0] <= joint[1] ? 0 : 1;
+  return joint[t] < apart ? tiles[t] : 0;
+}
+
+hipError_t gemm_bf16_many(const GemmOp* ops, int n, hipStream_t st) {
+  const int tile = gemm_bf16_join_tile(ops, n);
+  if (tile) return gemm_bf16_joint(tile, ops, n, st);
   for (int i = 0; i < n; i++) {
     const hipError_t e = gemm_bf16(ops[i], st);
     if (e != hipSuccess) return e;

@@ -48,3 +48,46 @@ def test_f32(T, d_in, r, d_out, act):
     dz = (dy @ wu) * prime
     for got, ref in zip(plain, (dz @ wd, dz.t() @ x, dy.t() @ sig)):
         assert (got.double().cpu() - ref).norm() <= 2.0 ** 11 * 2.0 ** -24 * ref.norm()
+
+
+@pytest.mark.parametrize("Bn,S,H,kv,f,r,lax,grad_dt", [(2, 256, 2, 2, 344, 64, False, B.LR_F32), (1, 33, 1, 1, 200, 40, False, B.LR_BF16),
+                                                       (3, 129, 4, 2, 1003, 136, False, B.LR_F32), (1, 520, 4, 1, 1416, 128, True, B.LR_F32),
+                                                       (2, 500, 8, 8, 2730, 256, False, B.LR_BF16)])
+def test_block(Bn, S, H, kv, f, r, lax, grad_dt):
+    """A block's backward with its independent products joined, and (while launches are being timed) each on its own."""
+    print(f"joint block B={Bn} S={S} H={H}/{kv} f={f} r={r} lax={lax}", flush=True)
+    T, d, dkv, f_ld = Bn * S, 128 * H, 128 * kv, (f + 7) // 8 * 8
+    g = torch.Generator(device=DEV).manual_seed(S)
+
+    def rand(*shape, std=1.0, mean=0.0):
+        return (torch.randn(shape, generator=g, device=DEV) * std + mean).bfloat16()
+
+    p = {"gamma1": rand(d, std=0.1, mean=1.0), "w_dn_qkv": rand(3 * r, d, std=d ** -0.5), "w_up_qkv": rand(d + 2 * dkv, r, std=r ** -0.5),
+         "w_dn_o": rand(r, d, std=d ** -0.5), "w_up_o": rand(d, r, std=r ** -0.5), "gamma2": rand(d, std=0.1, mean=1.0),
+         "w_dn_gu": rand(2 * r, d, std=d ** -0.5), "w_up_gu": rand(2, f_ld, r, std=r ** -0.5), "w_dn_d": rand(r, f_ld, std=f ** -0.5),
+         "w_up_d": rand(d, r, std=r ** -0.5)}
+    p["w_up_gu"][:, f:] = 0
+    p["w_dn_d"][:, f:] = 0
+    desc = B.make_block_desc(Bn, S, d, H, 128, f, f_ld, r, act=B.LR_ACT_IDENTITY if lax else B.LR_ACT_SILU, grad_dt=grad_dt, n_kv_heads=kv)
+    x, dy = rand(T, d), rand(T, d)
+    if lax:
+        wide = {"qkv": 3, "o": 1, "gu": 2, "d": 1}
+        hp, dz = ({n: rand(T, w * r) for n, w in wide.items()} for _ in range(2))
+        _, ck = B.lr_block_lax_fwd(desc, p, x, h_prev=hp)
+
+    def backward():
+        if lax:
+            dx, grads, dh = B.lr_block_lax_bwd(desc, p, x, dy, ck, h_prev=hp, dz_next=dz)
+            return {"dx": dx, **grads, **{"dh_" + n: t for n, t in dh.items()}}
+        dx, grads = B.lr_block_bwd(desc, p, x, dy, ck)
+        return {"dx": dx, **grads}
+
+    if not lax:
+        _, ck = B.lr_block_fwd(desc, p, x)
+    joined = backward()
+    B.lr_launch_timer_begin(200)
+    apart = backward()
+    torch.cuda.synchronize()
+    B.lr_launch_timer_end()
+    off = [n for n, t in joined.items() if not torch.equal(t, apart[n])]
+    assert not off, off
