@@ -256,6 +256,9 @@ __device__ __forceinline__ rsrc_t rsrc_from(rsrc_t r, uint32_t off, bool valid) 
 __device__ __forceinline__ void lds_dma_at(rsrc_t rs, uint32_t lds, uint32_t voff) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(rs) : "m0", "memory");
 }
+__device__ __forceinline__ void lds_dma4_at(rsrc_t rs, uint32_t lds, uint32_t voff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(rs) : "m0", "memory");
+}
 // max / sum of the two lanes l and l + 32
 __device__ __forceinline__ float half_max(float x) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
@@ -597,7 +600,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_kernel(const uint16_t* __rest
   // one query block from the late end and its mirror image from the early end: equal work per workgroup
   for (int pass = 0; pass < 2; pass++) {
   const int qblk = pass == 0 ? nqb - 1 - wg.x : wg.x;
-  if (pass == 1 && qblk >= nqb - 1 - wg.x) break;
+  if (pass == 1 && ((int)gridDim.x == nqb || qblk >= nqb - 1 - wg.x)) break;   // (unpaired launch: see the forward)
   const int q0 = qblk * BQ;
   const int qw0 = q0 + wave * MB * 32;
 
@@ -925,6 +928,258 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(const uint16_t* __res
   }  // pass
 }
 
+// ----------------------------------------------------------------------------------------------
+// The same for long sequences without the score gradient: the elementwise work of a 32-query block threaded between the
+// MFMAs of the next block's S and dP and its own outputs, two MFMAs and a share of it per pair of slots.
+//
+// Bound: instruction issue.  One wavefront per SIMD (its accumulators and K / V operands take 240 registers) issues an
+// instruction every four cycles at best, about 310 of them per block for 32 MFMAs of 32 cycles each; what was lost beside that was the
+// wait for the phases of a block to follow each other.  Four LDS stages, so that a tile's loads have two tiles' time to
+// land; the diagonal tiles, the last one and anything shorter than three full tiles go one block at a time.
+// Backward, us, before -> now: 2 x 2047 tokens, 32 / 8 heads 345 -> 327; 2 x 3333, 16 / 4 heads 484 -> 439; 4 x 1501, 16 heads
+// 260 -> 247; 777, 32 / 8 heads 129.5 -> 125.8; below that it is slower (4 x 300, 8 heads 64 -> 67), and with the score gradient
+// stored as well, where the dQ product waits on memory, the whole backward gained nothing at 2048 tokens (628 / 628).
+// ----------------------------------------------------------------------------------------------
+constexpr int LDKV_MIN_S = 768;
+constexpr int LDKV_NS = 4;                                 // ring of stages: two tiles in use, two on their way
+constexpr int LDKV_LDS = LDKV_NS * DKV_STAGE + KT * 4;     // (and a place for what nobody reads)
+constexpr int DKV_D = 8;        // LDS operands are read this many MFMAs ahead
+constexpr int DKV_BAR = 5;      // slot of the barrier in the stage of a tile's first block
+// elements of P and dS done by the end of slot s: their operands are whole when their MFMAs come (slots 16, 24)
+constexpr int dkv_elems(int s) { return s < 0 ? 0 : s < 16 ? 5 * (s + 1) / 8 : s < 22 ? s - 5 : 16; }
+
+__global__ __launch_bounds__(256) void attn_bwd_dkv_long_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+                                                           const uint16_t* __restrict__ v,
+                                                           const uint16_t* __restrict__ dout,
+                                                           const float* __restrict__ lse2, const float* __restrict__ D,
+                                                           uint16_t* __restrict__ dk, uint16_t* __restrict__ dv,
+                                                           int64_t ld, int64_t ldkv, int64_t lddkv, int grp, int S, int H, float scale) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  constexpr int BN = 128;
+  // the wavefront index as a scalar: everything derived from it (LDS slots, tile rows) is scalar arithmetic
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nkb = (S + BN - 1) / BN;
+  const WgCoord wg = wg_coord();
+  const int head = wg.head, b = wg.b;
+  const int64_t tok0 = (int64_t)b * S;
+  const int64_t hoff = head * HD;
+  const float c = scale * LOG2E;
+  // Q and dO tiles are needed row-wise (S, dP) and transposed (dK^T, dV^T): one LDS copy each, in the
+  // swizzle that serves both reads, written by direct-to-LDS loads.
+  const rsrc_t rsQ = rows_rsrc(q + tok0 * ld + hoff, S, ld);
+  const rsrc_t rsO = rows_rsrc(dout + tok0 * ld + hoff, S, ld);
+  const rsrc_t rsLD = make_rsrc((wave == 0 ? lse2 : D) + ((int64_t)b * H + head) * S, wave < 2 ? (uint32_t)S * 4u : 0u);
+  uint32_t offT[4];
+  {
+    int row[4];
+    dma_lane_offsets<SWZ_BOTH, 4>(offT, row, ld, wave, lane);
+  }
+  const uint32_t lds0 = (uint32_t)(uintptr_t)LRB_LDS_PTR(smem);
+  const int jend = (S + KT - 1) / KT;
+  // Load i of the 9 of 64-query tile j (4 of Q, 4 of dO; the ninth fetches the tile's 64 row scalars: lse2 by wavefront 0, D by
+  // wavefront 1, nothing by the others).  Rows past S, and whole tiles past it, read as zeros: no branches, and every tile
+  // costs every wavefront the same number of loads.
+  auto dma = [&](int slot, int j, int i) {
+    const bool valid = j < jend;
+    const uint32_t p = lds0 + (uint32_t)slot * DKV_STAGE;
+    const uint32_t off = (uint32_t)j * (uint32_t)(KT * 2) * (uint32_t)ld;
+    if (i < 4) lds_dma_at(rsrc_from(rsQ, off, valid), p + (uint32_t)(i * 4 + wave) * 1024u, offT[i]);
+    else if (i < 8) lds_dma_at(rsrc_from(rsO, off, valid), p + TILE_BYTES + (uint32_t)((i - 4) * 4 + wave) * 1024u, offT[i - 4]);
+    else lds_dma4_at(rsLD, wave < 2 ? p + 2 * TILE_BYTES + (uint32_t)wave * (KT * 4) : lds0 + LDKV_NS * DKV_STAGE, (uint32_t)(j * KT + lane) * 4u);
+  };
+
+  // one key block from the early end (most queries) and its mirror image from the late end: equal
+  // work per workgroup
+  for (int pass = 0; pass < 2; pass++) {
+  const int kblk = pass == 0 ? wg.x : nkb - 1 - wg.x;
+  if (pass == 1 && ((int)gridDim.x == nkb || kblk <= wg.x)) break;   // (unpaired launch: see the forward)
+  const int n0 = kblk * BN;
+  const int nw0 = n0 + wave * 32;
+  const int ni = nw0 + (lane & 31);                        // this lane's key
+  __syncthreads();                                         // the pass before is done with the ring
+
+  // K and V rows of this wavefront stay in registers (B operands).
+  bf16x8 kf[1][8], vf[1][8];
+  // (grouped-query attention: the group's shared key / value head, rows of ldkv; dk and dv below are
+  // this query head's contribution, laid out like q)
+  load_row_frags<1>(kf, k + tok0 * ldkv + (head / grp) * HD, ldkv, nw0, S, lane);
+  load_row_frags<1>(vf, v + tok0 * ldkv + (head / grp) * HD, ldkv, nw0, S, lane);
+
+  f32x16 akv[2][4];                                        // [0] = dK^T, [1] = dV^T
+#pragma unroll
+  for (int w = 0; w < 2; w++)
+#pragma unroll
+    for (int hb = 0; hb < 4; hb++)
+#pragma unroll
+      for (int e = 0; e < 16; e++) akv[w][hb][e] = 0.f;
+
+  const int jbeg = n0 / KT;                                // causal: first query tile that sees key n0
+  const int nt = jend - jbeg;
+#pragma unroll
+  for (int t = 0; t < 3; t++)
+#pragma unroll
+    for (int i = 0; i < 9; i++) dma(t, jbeg + t, i);
+  wait_vm<18>();                                           // the first of the three tiles has landed
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+
+  struct Scores { f32x16 s, dp; };                         // rows = queries of a 32-query block, column = key: S and dP, then P and dS
+  Scores sa, sb;                                           // of a tile's first and second block
+#pragma unroll
+  for (int e = 0; e < 16; e++) { sa.s[e] = 0.f; sa.dp[e] = 0.f; sb.s[e] = 0.f; sb.dp[e] = 0.f; }
+  bf16x8 fr[DKV_D];                                        // operands read ahead, slot s in fr[s % DKV_D]
+  float4 slv[4], sdv[4];                                   // lse2 and D of the current block: rows 8 g + 4 (lane / 32) + 0..3
+  uint32_t pw[8], dw[8];                                   // P and dS as bf16 pairs: two operands each
+
+  auto tile = [&](int t) -> const unsigned char* { return smem + (t % LDKV_NS) * DKV_STAGE; };   // t: tile of this pass
+  auto read_scalars = [&](auto Gc, const unsigned char* tp, int rb) {
+    constexpr int g4 = decltype(Gc)::value;
+    const float* sl = reinterpret_cast<const float*>(tp + 2 * TILE_BYTES);
+    if constexpr (g4 < 4) slv[g4] = *reinterpret_cast<const float4*>(sl + rb * 32 + 8 * g4 + 4 * (lane >> 5));
+    else sdv[g4 - 4] = *reinterpret_cast<const float4*>(sl + KT + rb * 32 + 8 * (g4 - 4) + 4 * (lane >> 5));
+  };
+  // operand of slot s: 0..15 the next block's rows (k16 step s / 2, Q then dO), 16..31 the current block's columns
+  // (16 queries each eight slots, 32 columns each two, dO then Q)
+  auto read_frag = [&](auto Sc, const unsigned char* cur, int crb, const unsigned char* nxt, int nrb) {
+    constexpr int s = decltype(Sc)::value;
+    if constexpr (s < 16) fr[s % DKV_D] = both_row_frag(nxt + (s & 1) * TILE_BYTES, nrb * 32, s >> 1, lane);
+    else fr[s % DKV_D] = both_tr_frag(cur + ((s & 1) ^ 1) * TILE_BYTES, crb * 32 + ((s - 16) >> 3) * 16, ((s >> 1) & 3) * 32, lane);
+  };
+  auto mfma = [&](auto Sc, Scores& nx) {
+    constexpr int s = decltype(Sc)::value;
+    const bf16x8 f = fr[s % DKV_D];
+    if constexpr (s < 16) {
+      if constexpr (s & 1) nx.dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, vf[0][s >> 1], nx.dp, 0, 0, 0);
+      else nx.s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, kf[0][s >> 1], nx.s, 0, 0, 0);
+    } else {
+      constexpr int t = (s - 16) >> 3, hb = (s >> 1) & 3, w = (s & 1) ^ 1;
+      const uint32_t* x = w ? pw : dw;
+      const bf16x8 pf = __builtin_bit_cast(bf16x8, make_uint4(x[t * 4], x[t * 4 + 1], x[t * 4 + 2], x[t * 4 + 3]));
+      akv[w][hb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, pf, akv[w][hb], 0, 0, 0);
+    }
+  };
+  auto clear = [&](Scores& x) {
+#pragma unroll
+    for (int e = 0; e < 16; e++) { x.s[e] = 0.f; x.dp[e] = 0.f; }
+  };
+  // elements F .. T - 1 of the current block, whose first query is qb0
+  float plow = 0.f, dlow = 0.f;
+  auto elements = [&](auto Fc, auto Tc, auto MASK, const Scores& x, int qb0) {
+    constexpr int f = decltype(Fc)::value, t = decltype(Tc)::value;
+    unroll_for<t - f>([&](auto I) {
+      constexpr int e = f + decltype(I)::value, g = e >> 2, r = e & 3;
+      const float lv = r == 0 ? slv[g].x : r == 1 ? slv[g].y : r == 2 ? slv[g].z : slv[g].w;
+      const float dvv = r == 0 ? sdv[g].x : r == 1 ? sdv[g].y : r == 2 ? sdv[g].z : sdv[g].w;
+      float p = fast_exp2(fmaf(x.s[e], c, -lv));
+      if constexpr (decltype(MASK)::value) {
+        const int qi = qb0 + acc_row(e, lane);
+        p = (ni > qi || qi >= S) ? 0.f : p;
+      }
+      const float ds = p * (x.dp[e] - dvv);
+      if constexpr (e & 1) {
+        pw[e >> 1] = pack_bf16x2(plow, p);
+        dw[e >> 1] = pack_bf16x2(dlow, ds);
+      } else {
+        plow = p;
+        dlow = ds;
+      }
+    });
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+
+  // Elements and outputs of the current block (of tile t, half crb) with the scores of the next one (half 1 - crb, tile t or
+  // t + 1) between them.  The first operands and the scalars were read by the stage before, and this one reads those of the
+  // stage after; the stage of a tile's first half holds its barrier and the loads of the tile after next but one.
+  auto stage = [&](int t, auto CRB, const Scores& cu, Scores& nx) {
+    constexpr int crb = decltype(CRB)::value;
+    constexpr bool bar = crb == 0;
+    const unsigned char* cur = tile(t);
+    const unsigned char* nxt = crb ? tile(t + 1) : cur;
+    const unsigned char* after = tile(t + 1);              // of the stage after: half 1 of tile t + 1, or half 0 of it
+    const int qb0 = (jbeg + t) * KT + crb * 32;
+    clear(nx);
+    // Slots in pairs, the operand that was asked for last first: one wait serves both.
+    unroll_for<16>([&](auto Uc) {
+      constexpr int u = decltype(Uc)::value, s = 2 * u + 1;
+      mfma(std::integral_constant<int, s>{}, nx);
+      mfma(std::integral_constant<int, s - 1>{}, nx);
+      if constexpr (bar && s == DKV_BAR) {
+        // All loads of tile t + 1 have landed (behind them are the next tile's nine, and loads retire in order).  Everyone
+        // has left tile t - 1, whose slot is loaded anew.
+        wait_vm<9>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+      }
+      unroll_for<2>([&](auto I) {
+        constexpr int r = s - 1 + decltype(I)::value;
+        if constexpr (bar && r > DKV_BAR && r <= DKV_BAR + 9) dma((t + 3) % LDKV_NS, jbeg + t + 3, r - DKV_BAR - 1);
+        if constexpr (r + DKV_D < 32) read_frag(std::integral_constant<int, r + DKV_D>{}, cur, crb, nxt, crb ^ 1);
+        else read_frag(std::integral_constant<int, r + DKV_D - 32>{}, cur, crb, after, crb);
+        if constexpr (r >= 23 && r < 31) read_scalars(std::integral_constant<int, r - 23>{}, nxt, crb ^ 1);
+      });
+      elements(std::integral_constant<int, dkv_elems(s - 2)>{}, std::integral_constant<int, dkv_elems(s)>{}, std::false_type{}, cu, qb0);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  // one block at a time: its scores,
+  auto scores = [&](const unsigned char* tp, int rb, Scores& x) {
+    clear(x);
+    unroll_for<DKV_D>([&](auto I) { read_frag(I, tp, 0, tp, rb); });
+    unroll_for<16>([&](auto Sc) {
+      constexpr int s = decltype(Sc)::value;
+      mfma(Sc, x);
+      if constexpr (s + DKV_D < 16) read_frag(std::integral_constant<int, s + DKV_D>{}, tp, 0, tp, rb);
+    });
+  };
+  // then its elements and outputs
+  auto outputs = [&](const unsigned char* tp, int rb, int qb0, Scores& x) {
+    unroll_for<8>([&](auto G) { read_scalars(G, tp, rb); });
+    unroll_for<DKV_D>([&](auto I) { read_frag(std::integral_constant<int, 16 + decltype(I)::value>{}, tp, rb, tp, 0); });
+    elements(I0{}, std::integral_constant<int, 16>{}, std::true_type{}, x, qb0);
+    unroll_for<16>([&](auto I) {
+      constexpr int s = 16 + decltype(I)::value;
+      mfma(std::integral_constant<int, s>{}, x);
+      if constexpr (s + DKV_D < 32) read_frag(std::integral_constant<int, s + DKV_D>{}, tp, rb, tp, 0);
+    });
+  };
+
+  for (int t = 0; t < nt;) {
+    if (t >= 2 && t + 3 < nt) {
+      // full tiles behind every wavefront's diagonal (three blocks in) and before the last; three of them at least, since the
+      // accumulators change registers on the way in and out
+      scores(tile(t), 0, sa);
+      unroll_for<8>([&](auto G) { read_scalars(G, tile(t), 0); });
+      unroll_for<DKV_D>([&](auto I) { read_frag(I, tile(t), 0, tile(t), 1); });
+      do {
+        stage(t, I0{}, sa, sb);
+        stage(t, I1{}, sb, sa);
+        t++;
+      } while (t + 1 < nt);
+      continue;
+    }
+    wait_vm<9>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < 9; i++) dma((t + 3) % LDKV_NS, jbeg + t + 3, i);
+#pragma unroll 1
+    for (int rb = 0; rb < 2; rb++) {
+      const int qb0 = (jbeg + t) * KT + rb * 32;
+      if (qb0 + 31 < nw0 || qb0 >= S) continue;            // before this wavefront's keys, or not there
+      scores(tile(t), rb, sa);
+      outputs(tile(t), rb, qb0, sa);
+    }
+    t++;
+  }
+  if (ni < S) {
+    store_acc_T(dk + (tok0 + ni) * lddkv + hoff, akv[0], scale, lane);
+    store_acc_T(dv + (tok0 + ni) * lddkv + hoff, akv[1], 1.f, lane);
+  }
+  }  // pass
+  wait_vm0();                                              // no load into LDS outlives the workgroup
+}
+
 // Grouped-query attention: a key / value head's gradient is the sum of the contributions of the grp
 // query heads that share it.  part: two [T, H * HD] bf16 tensors (dK, then dV contributions, one per
 // query head), out: dk / dv [T, ldkv].  One thread adds grp 16-byte vectors in fp32.
@@ -1007,7 +1262,6 @@ size_t attention_gqa_bwd_ws_bytes(int B, int S, int H, int Hkv, int hd) {
   return small + ds_bytes(B, S, H) + (Hkv < H ? 2 * (size_t)B * S * H * HD * 2 : 0);
 }
 
-constexpr int DQ_MB = 2;    // 32-query blocks per wavefront in the dQ kernel
 constexpr int DKV_NB = 1;   // 32-key blocks per wavefront in the dK/dV kernel
 
 hipError_t attention_bwd_bf16(const void* q, const void* k, const void* v, const void* o, const void* dout,
@@ -1025,7 +1279,9 @@ hipError_t attention_gqa_bwd_bf16(const void* q, const void* k, const void* v, c
   // 32-bit buffer offsets per (batch, head)
   if ((int64_t)S * ld * 2 >= (int64_t)0x7fffffff || (int64_t)S * ldkv * 2 >= (int64_t)0x7fffffff) return hipErrorNotSupported;
   static const hipError_t attr_err = [] {
-    hipError_t e = set_lds(attn_bwd_dq_kernel<DQ_MB>, DQ_LDS);
+    hipError_t e = set_lds(attn_bwd_dq_kernel<1>, DQ_LDS);
+    if (e == hipSuccess) e = set_lds(attn_bwd_dq_kernel<2>, DQ_LDS);
+    if (e == hipSuccess) e = set_lds(attn_bwd_dkv_long_kernel, LDKV_LDS);
     if (e == hipSuccess) e = set_lds(attn_bwd_dkv_kernel<DKV_NB, false>, DKV_LDS);
     if (e == hipSuccess) e = set_lds(attn_bwd_dkv_kernel<DKV_NB, true>, DKV_LDS);
     return e;
@@ -1037,7 +1293,7 @@ hipError_t attention_gqa_bwd_bf16(const void* q, const void* k, const void* v, c
   hipLaunchKernelGGL(attn_dot_kernel, dim3((unsigned)((items * 16 + 255) / 256)), dim3(256), 0, st,
                      (const uint16_t*)dout, (const uint16_t*)o, lse, D, lse2, ld, S, H, items);
   const float scale = 1.f / sqrtf((float)hd);
-  const int nkb = (S + DKV_NB * 128 - 1) / (DKV_NB * 128);   // paired or not as in the forward (29.6 -> 18.6 us)
+  const int nkb = (S + 127) / 128;   // paired or not as in the forward (29.6 -> 18.6 us)
   const dim3 kv_grid((int64_t)nkb * H * B <= 256 ? nkb : (nkb + 1) / 2, H, B);
   const size_t small = (2 * (size_t)items * sizeof(float) + 255) / 256 * 256;
   // where the dK / dV kernel writes: the outputs themselves, or (fewer key / value heads than query
@@ -1075,12 +1331,26 @@ hipError_t attention_gqa_bwd_bf16(const void* q, const void* k, const void* v, c
     e = gemm_bf16_untimed(op, st);
     return e != hipSuccess ? e : group_sum();
   }
-  hipLaunchKernelGGL(attn_bwd_dq_kernel<DQ_MB>, dim3(((S + DQ_MB * 128 - 1) / (DQ_MB * 128) + 1) / 2, H, B), dim3(256), DQ_LDS, st, (const uint16_t*)q,
-                     (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout, lse2, D, (uint16_t*)dq, ld, ldkv, grp,
-                     S, H, scale);
-  hipLaunchKernelGGL((attn_bwd_dkv_kernel<DKV_NB, false>), kv_grid, dim3(256), DKV_LDS, st, (const uint16_t*)q,
-                     (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout, lse2, D, dk_w, dv_w,
-                     (uint16_t*)nullptr, ld, ldkv, lddkv, grp, S, H, scale);
+  // dQ: 64 queries per wavefront, a block of 256 and its mirror per workgroup; where that leaves CUs idle a block each, and
+  // of 128 queries where those find a CU each (whole backward, us, pairs only -> now: 1 x 333 tokens, 32 / 8 heads 74.5 -> 45.3;
+  // 1 x 777, 32 / 8 heads 125.8 -> 71.1; 2 x 1031, 16 heads 154.6 -> 118.7; 4 x 1501, 16 heads, paired as before, 247 -> 246).
+  auto dq_launch = [&](auto MBc, bool paired) {
+    constexpr int MB = decltype(MBc)::value;
+    const int n = (S + MB * 128 - 1) / (MB * 128);
+    hipLaunchKernelGGL(attn_bwd_dq_kernel<MB>, dim3(paired ? (n + 1) / 2 : n, H, B), dim3(256), DQ_LDS, st, (const uint16_t*)q,
+                       (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout, lse2, D, (uint16_t*)dq, ld, ldkv, grp,
+                       S, H, scale);
+  };
+  const int64_t heads = (int64_t)H * B;
+  if ((S + 127) / 128 * heads <= 256) dq_launch(std::integral_constant<int, 1>{}, false);
+  else dq_launch(std::integral_constant<int, 2>{}, (S + 255) / 256 * heads > 256);
+  if (S >= LDKV_MIN_S)
+    hipLaunchKernelGGL(attn_bwd_dkv_long_kernel, kv_grid, dim3(256), LDKV_LDS, st, (const uint16_t*)q, (const uint16_t*)k,
+                       (const uint16_t*)v, (const uint16_t*)dout, lse2, D, dk_w, dv_w, ld, ldkv, lddkv, grp, S, H, scale);
+  else
+    hipLaunchKernelGGL((attn_bwd_dkv_kernel<DKV_NB, false>), kv_grid, dim3(256), DKV_LDS, st, (const uint16_t*)q,
+                       (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout, lse2, D, dk_w, dv_w,
+                       (uint16_t*)nullptr, ld, ldkv, lddkv, grp, S, H, scale);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return group_sum();

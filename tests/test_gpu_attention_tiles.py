@@ -2,6 +2,10 @@
 import pytest
 import torch
 
+import bf16_model as M
+import synth_inputs as si
+from oracle import gqa_oracle as gqa
+from parity import check
 from paper_2512_12131_amd import binding as B
 
 pytestmark = pytest.mark.gpu
@@ -36,3 +40,43 @@ def test_attention_fwd_edges(S):
     worst = ((got - p @ v64).abs() / bound).max().item()
     assert worst <= 1.0
     assert (lse.view(Bn, H, S)[0].cpu().double() - s.logsumexp(-1)).abs().max() < 1e-4
+
+
+@pytest.mark.parametrize("S", [65, 129, 255, 257, 513])
+def test_attention_bwd_does_not_depend_on_the_launch(S):
+    """Query blocks of 128 with a workgroup each, of 256 with a workgroup each, and of 256 in pairs: 1, 26 and 64 batch elements
+    of 4 heads (a sequence length that keeps no score gradient)."""
+    H, Hkv, Bn = 4, 2, 64
+    print(f"attention backward launches S={S}", flush=True)
+    g = torch.Generator().manual_seed(S)
+    q, do = (torch.randn(Bn * S, H * HD, generator=g).bfloat16().to(DEV) for _ in range(2))
+    k, v = (torch.randn(Bn * S, Hkv * HD, generator=g).bfloat16().to(DEV) for _ in range(2))
+    o, lse = B.lr_attention_gqa_fwd(q, k, v, Bn, S, H, Hkv, HD)
+    full = B.lr_attention_gqa_bwd(q, k, v, o, do, lse, Bn, S, H, Hkv, HD)
+    for n in (1, 26):
+        t = n * S
+        part = B.lr_attention_gqa_bwd(q[:t], k[:t], v[:t], o[:t], do[:t], lse[:n].contiguous(), n, S, H, Hkv, HD)
+        torch.cuda.synchronize()
+        for a, b in zip(part, full):
+            assert torch.equal(a, b[:t])
+
+
+@pytest.mark.parametrize("S", [767, 769, 801, 833, 897, 1027, 1281])
+def test_attention_bwd_long(S):
+    """The pipelined dK / dV kernel from 768 tokens on, and the other one just below, against the oracle: one to seven tiles in
+    its loop, tails of 1 to 63 queries, key blocks of every remainder.  Tolerances as in test_gpu_attention.py."""
+    H, Hkv = 2, 1
+    print(f"attention backward S={S}", flush=True)
+    dt = torch.bfloat16
+    q, do = (si.gaussian(17, n, (S, H * HD), dtype=dt) for n in ("q", "do"))
+    k, v = (si.gaussian(17, n, (S, Hkv * HD), dtype=dt) for n in ("k", "v"))
+    qd, kd, vd, dod = (t.to(DEV) for t in (q, k, v, do))
+    o, lse = B.lr_attention_gqa_fwd(qd, kd, vd, 1, S, H, Hkv, HD)
+    got = B.lr_attention_gqa_bwd(qd, kd, vd, o, dod, lse, 1, S, H, Hkv, HD)
+    torch.cuda.synchronize()
+    Q, K, V, DO = (si.f64(t) for t in (q, k, v, do))
+    o_ref, _ = gqa.attention_gqa_fwd(Q, K, V, 1, S, H, Hkv, HD)
+    refs = gqa.attention_gqa_bwd(Q, K, V, DO, 1, S, H, Hkv, HD)
+    bud = M.attention_budget(Q, K, V, DO, 1, S, H, Hkv, HD, o_ref, *refs)
+    for n, a, r in zip(("dq", "dk", "dv"), got, refs):
+        check(n, a, r, dt, bud[n])
