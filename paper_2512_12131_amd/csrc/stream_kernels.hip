@@ -176,12 +176,17 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const void* x, int64_t
 // branch, so the loop body is straight-line code and all of a row's loads are in flight together.  (With a
 // bounds test per vector the compiler had put a full wait for memory between the vectors of the
 // second phase: 4.5 instead of the rate below.)
-template <int NIT>
-__global__ __launch_bounds__(256, 2) void rmsnorm_bwd_row_kernel(const uint16_t* x, int64_t ldx, const uint16_t* gamma,
-                                                              const float* stat, float eps, const uint16_t* dxh,
-                                                              int64_t lddxh, const uint16_t* dres, int64_t lddres,
-                                                              uint16_t* dx, int64_t lddx, float* dgpart, int64_t T,
-                                                              int64_t d, int rows_per_wg, int64_t nparts) {
+// What bounds it below one workgroup per CU and on narrow rows is a wavefront's way from one row to the next: 16 rows in a
+// chain, each a wait for memory, then some 20 instructions per column slot.  So NIT follows the width (one kernel of eight
+// slices for every width spent 3 us per row, also on 256 columns), and AHEAD keeps the next row on its way in a second set
+// of registers.  Measured, launch and sum of the partials included, before and after: 49.6 -> 16.2 us (8192 x 512),
+// 101.5 -> 45.7 us (32768 x 1024), 59.7 -> 43.9 us (16384 x 2048: 6.1 TB/s), 58.5 -> 43.9 us (8192 x 3072), 61.2 ->
+// 56.6 us (8192 x 4096).
+template <int NIT, bool AHEAD>
+__global__ __launch_bounds__(256, AHEAD ? 1 : 2) void rmsnorm_bwd_row_kernel(
+    const uint16_t* x, int64_t ldx, const uint16_t* gamma, const float* stat, float eps, const uint16_t* dxh, int64_t lddxh,
+    const uint16_t* dres, int64_t lddres, uint16_t* dx, int64_t lddx, float* dgpart, int64_t T, int64_t d, int rows_per_wg,
+    int64_t nparts) {
   // LDS: gamma (staged once per workgroup: re-reading it here costs no registers and, unlike a global
   // re-read, does not queue behind the row's stores), then each wavefront's column partials of dgamma
   // (kept here rather than in 64 registers per lane, which the row data needs)
@@ -208,26 +213,34 @@ __global__ __launch_bounds__(256, 2) void rmsnorm_bwd_row_kernel(const uint16_t*
   }
   __syncthreads();
   auto u4 = [](const u32x4_t& t) { return make_uint4(t.x, t.y, t.z, t.w); };
-  for (int r = 0; r < rows_per_wg / 4; r++) {
-    const int64_t row = ((int64_t)r * gridDim.x + blockIdx.x) * 4 + wave;
-    if (row >= T) break;
-    const float rho = rsqrtf(stat[row] * inv_d + eps);
-    const __amdgpu_buffer_rsrc_t rsX = row_rsrc(x, row, ldx), rsD = row_rsrc(dxh, row, lddxh),
-                                 rsR = row_rsrc(dres, row, lddres), rsO = row_rsrc(dx, row, lddx);
-    u32x4_t xq[NIT], dq[NIT], rq[NIT];
+  // A row past the last one has empty resources: it loads zeros, adds nothing and stores nothing.
+  struct Row { u32x4_t x[NIT], d[NIT], r[NIT]; float ss; };
+  auto row_at = [&](int r) { return ((int64_t)r * gridDim.x + blockIdx.x) * 4 + wave; };
+  auto fetch = [&](int r, Row& q) {
+    const int64_t row = row_at(r);
+    const bool there = r < rows_per_wg / 4 && row < T;
+    const __amdgpu_buffer_rsrc_t rsX = row_rsrc(there ? x : nullptr, row, ldx),
+                                 rsD = row_rsrc(there ? dxh : nullptr, row, lddxh),
+                                 rsR = row_rsrc(there ? dres : nullptr, row, lddres);
+    q.ss = there ? stat[row] : 1.f;
 #pragma unroll
     for (int it = 0; it < NIT; it++) {
       const int off = (it * 64 + lane) * 16;
-      xq[it] = __builtin_amdgcn_raw_buffer_load_b128(rsX, off, 0, NT_);
-      dq[it] = __builtin_amdgcn_raw_buffer_load_b128(rsD, off, 0, NT_);
+      q.x[it] = __builtin_amdgcn_raw_buffer_load_b128(rsX, off, 0, NT_);
+      q.d[it] = __builtin_amdgcn_raw_buffer_load_b128(rsD, off, 0, NT_);
     }
 #pragma unroll
-    for (int it = 0; it < NIT; it++) rq[it] = __builtin_amdgcn_raw_buffer_load_b128(rsR, (it * 64 + lane) * 16, 0, NT_);
+    for (int it = 0; it < NIT; it++) q.r[it] = __builtin_amdgcn_raw_buffer_load_b128(rsR, (it * 64 + lane) * 16, 0, NT_);
+  };
+  auto work = [&](int r, const Row& q) {
+    const int64_t row = row_at(r);
+    const __amdgpu_buffer_rsrc_t rsO = row_rsrc(row < T ? dx : nullptr, row, lddx);
+    const float rho = rsqrtf(q.ss * inv_d + eps);
     float s = 0.f;
 #pragma unroll
     for (int it = 0; it < NIT; it++) {
       float xv[8], gv[8], dv[8];
-      unpack8(u4(xq[it]), xv); unpack8(sgam[it * 64 + lane], gv); unpack8(u4(dq[it]), dv);
+      unpack8(u4(q.x[it]), xv); unpack8(sgam[it * 64 + lane], gv); unpack8(u4(q.d[it]), dv);
 #pragma unroll
       for (int i = 0; i < 8; i++) s = fmaf(dv[i] * gv[i], xv[i] * rho, s);
       // keeps the compiler from fetching and unpacking every slice's gamma at once (registers)
@@ -238,7 +251,7 @@ __global__ __launch_bounds__(256, 2) void rmsnorm_bwd_row_kernel(const uint16_t*
     for (int it = 0; it < NIT; it++) {
       float xv[8], gv[8], dv[8], rv[8], o[8];
       if (it % 2 == 0) __builtin_amdgcn_sched_barrier(0);
-      unpack8(u4(xq[it]), xv); unpack8(sgam[it * 64 + lane], gv); unpack8(u4(dq[it]), dv); unpack8(u4(rq[it]), rv);
+      unpack8(u4(q.x[it]), xv); unpack8(sgam[it * 64 + lane], gv); unpack8(u4(q.d[it]), dv); unpack8(u4(q.r[it]), rv);
       float4 a0 = myacc[it * 128], a1 = myacc[it * 128 + 1];
       float a[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
 #pragma unroll
@@ -252,6 +265,25 @@ __global__ __launch_bounds__(256, 2) void rmsnorm_bwd_row_kernel(const uint16_t*
       const uint4 ov = pack8(o);
       __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{ov.x, ov.y, ov.z, ov.w}, rsO, (it * 64 + lane) * 16, 0, ST_);
     }
+  };
+  Row qa, qb;
+  if constexpr (AHEAD) {
+    fetch(0, qa);
+    for (int r = 0; r < rows_per_wg / 4; r += 2) {           // (an even number: rows_per_wg is a multiple of NB_RB)
+      if (row_at(r) >= T) break;
+      fetch(r + 1, qb);
+      __builtin_amdgcn_sched_barrier(0);
+      work(r, qa);
+      fetch(r + 2, qa);
+      __builtin_amdgcn_sched_barrier(0);
+      work(r + 1, qb);
+    }
+  } else {
+    for (int r = 0; r < rows_per_wg / 4; r++) {
+      if (row_at(r) >= T) break;
+      fetch(r, qa);
+      work(r, qa);
+    }
   }
   // add the four wavefronts' column partials
   __syncthreads();
@@ -264,7 +296,7 @@ __global__ __launch_bounds__(256, 2) void rmsnorm_bwd_row_kernel(const uint16_t*
     }
   }
 }
-constexpr int RN_ROW_LDS = 8 * 64 * 16 + 4 * 8 * 512 * 4;   // rmsnorm_bwd_row_kernel<8>: gamma + four partial sets
+constexpr int rn_row_lds(int nit) { return nit * 64 * 16 + 4 * nit * 512 * 4; }   // gamma + four sets of partials
 
 // ---- elementwise on [T, n] with leading dimensions -------------------------------------------
 // Each workgroup owns one contiguous run of EW_U x 256 vectors and issues all of its loads before the
@@ -864,10 +896,6 @@ hipError_t k_rmsnorm_bwd(const void* x, int64_t ldx, const void* gamma, const fl
                          float* dgamma_part, int64_t T, int64_t d, int dt, hipStream_t st) {
   if (T <= 0) return hipSuccess;
   if (dt == LR_BF16 && d <= 4096) {   // a row fits a wavefront's registers: single pass over every tensor
-    // one-time opt-in to more than 64 KB of dynamic LDS (thread-safe static initialisation)
-    static const hipError_t attr_err = hipFuncSetAttribute((const void*)rmsnorm_bwd_row_kernel<8>,
-                                                           hipFuncAttributeMaxDynamicSharedMemorySize, RN_ROW_LDS);
-    if (attr_err != hipSuccess) return attr_err;
     // Rows per workgroup: a multiple of NB_RB chosen so that the launch is about one workgroup per CU
     // (measured at T = 32768: 6.1 TB/s with 256 workgroups of 128 rows against 5.8 with 512 of 64; 128
     // workgroups of 256 rows leave half the chip idle, 4.7).  The partial buffer keeps one row per NB_RB
@@ -877,10 +905,29 @@ hipError_t k_rmsnorm_bwd(const void* x, int64_t ldx, const void* gamma, const fl
     if (mult < 1) mult = 1;
     const int rows_per_wg = (int)(mult * NB_RB);
     const unsigned grid = (unsigned)((T + rows_per_wg - 1) / rows_per_wg);
-    hipLaunchKernelGGL(rmsnorm_bwd_row_kernel<8>, dim3(grid), dim3(256), RN_ROW_LDS, st,
-                       (const uint16_t*)x, ldx, (const uint16_t*)gamma, stat, eps, (const uint16_t*)dxhat, lddxh,
-                       (const uint16_t*)dres, lddres, (uint16_t*)dx, lddx, dgamma_part, T, d, rows_per_wg, nparts);
-    return hipGetLastError();
+    const auto launch = [&](auto nit, auto ahead) -> hipError_t {
+      constexpr int NIT = decltype(nit)::value;
+      const auto kernel = rmsnorm_bwd_row_kernel<NIT, decltype(ahead)::value>;
+      // one-time opt-in to more than 64 KB of dynamic LDS (thread-safe static initialisation)
+      static const hipError_t attr_err =
+          hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, rn_row_lds(NIT));
+      if (attr_err != hipSuccess) return attr_err;
+      hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), rn_row_lds(NIT), st, (const uint16_t*)x, ldx,
+                         (const uint16_t*)gamma, stat, eps, (const uint16_t*)dxhat, lddxh, (const uint16_t*)dres, lddres,
+                         (uint16_t*)dx, lddx, dgamma_part, T, d, rows_per_wg, nparts);
+      return hipGetLastError();
+    };
+    // The narrowest kernel that holds the row.  The widest with both sets of rows takes 300 registers, one workgroup per CU:
+    // measured at d = 4096, 56.6 against 61.2 us with 128 workgroups, 92.3 against 91.4 with 256 and 196 against 194 with
+    // more, so there it keeps to one set.
+    const std::true_type ahead;
+    if (d <= 512) return launch(std::integral_constant<int, 1>{}, ahead);
+    if (d <= 1024) return launch(std::integral_constant<int, 2>{}, ahead);
+    if (d <= 1536) return launch(std::integral_constant<int, 3>{}, ahead);
+    if (d <= 2048) return launch(std::integral_constant<int, 4>{}, ahead);
+    if (d <= 3072) return launch(std::integral_constant<int, 6>{}, ahead);
+    return grid < 256 ? launch(std::integral_constant<int, 8>{}, ahead)
+                      : launch(std::integral_constant<int, 8>{}, std::false_type{});
   }
   DISPATCH_DT(dt, rmsnorm_bwd_kernel, dim3(k_rmsnorm_bwd_parts(T)), dim3(256), st, x, ldx, gamma, stat, eps, dxhat,
               lddxh, dres, lddres, dx, lddx, dgamma_part, T, d);

@@ -57,3 +57,48 @@ def test_act_and_swiglu(T, f, dtype):
     check("m", m, orc.silu(Gm) * U, dtype)
     check("dg", dg, DM * U * orc.silu_prime(Gm), dtype)
     check("du", du, DM * orc.silu(Gm), dtype)
+
+
+@pytest.mark.parametrize("d", [504, 520, 1024, 1032, 1536, 1544, 2048, 2056, 3072, 3080, 4096])
+@pytest.mark.parametrize("T", [3, 69, 449])
+def test_rms_bwd_widths(T, d):
+    """Both sides of every width at which the row kernel holds another number of slices, on strided rows.  T = 3: no second
+    row for any wavefront; 69 and 449: rows that end within a workgroup and within a pair of rows."""
+    print(f"rmsnorm backward T={T} d={d}", flush=True)
+    eps = 1e-5
+    x = si.gaussian(7, "x", (T, d + 8), dtype=torch.bfloat16)[:, :d]
+    gamma = si.gaussian(7, "gamma", (d,), std=0.1, mean=1.0, dtype=torch.bfloat16)
+    dxh = si.gaussian(7, "dxh", (T, d + 16), dtype=torch.bfloat16)[:, :d]
+    dres = si.gaussian(7, "dres", (T, d), dtype=torch.bfloat16)
+    big = [torch.full((T, w), float("nan"), dtype=torch.bfloat16, device=DEV) for w in (d + 8, d + 16)]
+    big[0][:, :d], big[1][:, :d] = x.to(DEV), dxh.to(DEV)
+    xd, dxhd, gd, dresd = big[0][:, :d], big[1][:, :d], gamma.to(DEV), dres.to(DEV)
+    stat = B.lr_rms_stat(xd)
+    dx = torch.empty((T, d), dtype=torch.bfloat16, device=DEV)
+    part = torch.empty((B.lib().lr_rmsnorm_bwd_parts(T), d), device=DEV)
+    assert B.lib().lr_rmsnorm_bwd(xd.data_ptr(), d + 8, gd.data_ptr(), stat.data_ptr(), eps, dxhd.data_ptr(), d + 16,
+                                  dresd.data_ptr(), d, dx.data_ptr(), d, part.data_ptr(), T, d, B.LR_BF16,
+                                  torch.cuda.current_stream().cuda_stream) == 0
+    dx_ref, dg_ref = orc.rmsnorm_bwd(si.f64(x), si.f64(gamma), eps, si.f64(dxh))
+    check("dx+dres", dx, dx_ref + si.f64(dres), torch.bfloat16)
+    check("dgamma", part.sum(0), dg_ref, torch.float32, scale=10)
+
+
+@pytest.mark.parametrize("T", [16320, 16321, 16448])
+def test_rms_bwd_rows_do_not_depend_on_their_number(T):
+    """From 256 workgroups on a row of more than 3072 columns is no longer fetched ahead: its results are the same bits."""
+    eps, d, n = 1e-5, 3080, 200
+    g = torch.Generator(device=DEV)
+    g.manual_seed(5)
+    x, dxh, dres = (torch.randn((T, d), generator=g, device=DEV).bfloat16() for _ in range(3))
+    gamma = torch.randn((d,), generator=g, device=DEV).bfloat16()
+    stat = B.lr_rms_stat(x)
+    dx, part = B.lr_rmsnorm_bwd(x, gamma, stat, eps, dxh, dres)
+    for rows in (slice(0, n), slice(T - n, T)):
+        few, _ = B.lr_rmsnorm_bwd(x[rows], gamma, stat[rows], eps, dxh[rows], dres[rows])
+        assert torch.equal(dx[rows].view(torch.int16), few.view(torch.int16))
+    halves = [B.lr_rmsnorm_bwd(x[r], gamma, stat[r], eps, dxh[r], dres[r])[1].sum(0, dtype=torch.float64)
+              for r in (slice(0, T // 2), slice(T // 2, T))]
+    whole = part.sum(0, dtype=torch.float64)
+    # fp32 partials of at most 16 rows per wavefront, each term below max|dxh * n|: a sum of T terms in another order
+    assert (whole - halves[0] - halves[1]).abs().max() <= 2 * 20 * 2.0 ** -24 * T * 25
