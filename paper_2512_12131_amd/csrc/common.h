@@ -195,6 +195,10 @@ hipError_t k_wgrad_finish(const float* part, int nsplit, int64_t rows, int64_t c
                           const void* colscale, const void* w_for_dgamma, float* dgamma_part,
                           int accumulate, int dt, int out_dt, hipStream_t);
 int64_t k_wgrad_dgamma_parts(int64_t rows);
+// The same for up to FINISH_MAX gradients of one call in one launch (bf16 operands, no column scale, no dgamma).
+constexpr int FINISH_MAX = 12;
+struct FinishJob { const float* part; int nsplit; int64_t count; void* dw; };   // count: elements of the gradient
+hipError_t k_wgrad_finish_many(const FinishJob* jobs, int n, int accumulate, int out_dt, hipStream_t);
 // out[c] (+)= sum_p part[p, c]; out has dtype out_dt
 hipError_t k_colsum_parts(const float* part, int64_t nparts, int64_t cols, void* out, int accumulate,
                           int out_dt, hipStream_t);

@@ -821,6 +821,37 @@ __global__ __launch_bounds__(256) void wgrad_finish_narrow_kernel(const float* p
     dgpart[(int64_t)blockIdx.y * cols + c0 + tid] = sclass[tid] + sclass[W + tid] + sclass[2 * W + tid] + sclass[3 * W + tid];
 }
 
+// Several gradients in one launch, one thread per vector as above.  Bound by launches: a gradient of a small or mid-sized
+// block is some hundred KB, whose pass takes 4 us of which most is the way in and out, and a backward has nine.
+struct FinishMany {
+  FinishJob job[FINISH_MAX];
+  int first[FINISH_MAX + 1];    // workgroups [first[i], first[i + 1]) take job i
+};
+template <typename OT>
+__global__ __launch_bounds__(256) void wgrad_finish_many_kernel(FinishMany, int accumulate) {
+  // (read where the dispatch left them: an array indexed by the workgroup's job, not copied to the stack)
+  const FinishMany& a = *(const FinishMany*)__builtin_amdgcn_kernarg_segment_ptr();
+  constexpr int NV = St<LR_BF16>::NV;
+  int j = 0;
+#pragma unroll
+  for (int i = 1; i < FINISH_MAX; i++) j += (int)blockIdx.x >= a.first[i] ? 1 : 0;
+  j = __builtin_amdgcn_readfirstlane(j);
+  const float* part = a.job[j].part;
+  const int nsplit = a.job[j].nsplit;
+  const int64_t count = a.job[j].count, off = ((int64_t)((int)blockIdx.x - a.first[j]) * 256 + threadIdx.x) * NV;
+  if (off >= count) return;
+  float cs[NV], s[NV];
+#pragma unroll
+  for (int i = 0; i < NV; i++) cs[i] = 1.f;
+  switch (nsplit) {
+    case 1: finish_vector<LR_BF16, OT, 1>(part, nsplit, count, off, cs, a.job[j].dw, accumulate, s); break;
+    case 2: finish_vector<LR_BF16, OT, 2>(part, nsplit, count, off, cs, a.job[j].dw, accumulate, s); break;
+    case 3: finish_vector<LR_BF16, OT, 3>(part, nsplit, count, off, cs, a.job[j].dw, accumulate, s); break;
+    case 4: finish_vector<LR_BF16, OT, 4>(part, nsplit, count, off, cs, a.job[j].dw, accumulate, s); break;
+    default: finish_vector<LR_BF16, OT, 0>(part, nsplit, count, off, cs, a.job[j].dw, accumulate, s); break;
+  }
+}
+
 // Column sums of a few hundred partial rows, front to back: 16 columns (a 64-byte run) per workgroup, 16 threads per
 // column that bring every 16th row into LDS, from where one of them adds the column up.  Bound by the latency of
 // the loads: a thread per column walked all rows one after the other from a handful of workgroups (96 x 4096: 26 us).
@@ -1065,6 +1096,21 @@ hipError_t k_wgrad_finish(const float* part, int nsplit, int64_t rows, int64_t c
   else LRB_WF(LR_BF16, bf16_t);
 #undef LRB_WF
 #undef LRB_WF2
+  return hipGetLastError();
+}
+hipError_t k_wgrad_finish_many(const FinishJob* jobs, int n, int accumulate, int out_dt, hipStream_t st) {
+  if (n <= 0) return hipSuccess;
+  if (n > FINISH_MAX) return hipErrorInvalidValue;
+  FinishMany a;
+  int wgs = 0;
+  for (int i = 0; i < FINISH_MAX; i++) {
+    a.first[i] = wgs;
+    a.job[i] = i < n ? jobs[i] : FinishJob{nullptr, 1, 0, nullptr};
+    wgs += (int)((a.job[i].count / St<LR_BF16>::NV + 255) / 256);
+  }
+  a.first[FINISH_MAX] = wgs;
+  if (out_dt == LR_F32) hipLaunchKernelGGL(wgrad_finish_many_kernel<float>, dim3((unsigned)wgs), dim3(256), 0, st, a, accumulate);
+  else hipLaunchKernelGGL(wgrad_finish_many_kernel<bf16_t>, dim3((unsigned)wgs), dim3(256), 0, st, a, accumulate);
   return hipGetLastError();
 }
 hipError_t k_colsum_parts(const float* part, int64_t nparts, int64_t cols, void* out, int accumulate, int out_dt,

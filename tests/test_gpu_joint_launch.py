@@ -91,3 +91,39 @@ def test_block(Bn, S, H, kv, f, r, lax, grad_dt):
     B.lr_launch_timer_end()
     off = [n for n, t in joined.items() if not torch.equal(t, apart[n])]
     assert not off, off
+
+
+@pytest.mark.parametrize("grad_dt", [B.LR_F32, B.LR_BF16])
+@pytest.mark.parametrize("G,T,d_in,r,d_out", [(1, 1024, 64, 32, 72), (1, 1031, 264, 40, 520), (1, 2113, 8, 8, 8), (3, 1700, 256, 64, 256),
+                                              (2, 5120, 256, 64, 616), (14, 1100, 64, 16, 72), (2, 8192, 1024, 512, 1024)])
+def test_gathered_gradients(G, T, d_in, r, d_out, grad_dt):
+    """Split weight gradients summed up in one launch at the end: sizes at and above two splits, that end within a workgroup,
+    more gradients than one launch takes, and partials that do not all fit the region they are gathered in.  sigma = identity,
+    so dW_up is a chained sum of exact products: off by at most T 2^-24 of the sum of their magnitudes, and a bf16 rounding."""
+    print(f"gathered G={G} T={T} {d_in}->{r}->{d_out}", flush=True)
+    g = torch.Generator().manual_seed(T)
+    x, wd, wu, dy = (torch.randn(s, generator=g).bfloat16().to(DEV) for s in ((T, d_in), (G * r, d_in), (G, d_out, r), (G, T, d_out)))
+    gt = torch.float32 if grad_dt == B.LR_F32 else torch.bfloat16
+    base = [torch.randn(s, generator=g).to(gt).to(DEV) for s in ((G * r, d_in), (G, d_out, r))]
+    if G == 1:
+        z, _ = B.lr_linear_fwd(x, wd, wu[0], B.LR_ACT_IDENTITY)
+        run = lambda grads: B.lr_linear_bwd(x, wd, wu[0], z, dy[0], B.LR_ACT_IDENTITY, grads=grads, grad_dt=grad_dt)
+        _, dwd, dwu = run(None)
+        _, awd, awu = run((base[0].clone(), base[1][0].clone()))
+        dwu, awu = dwu[None], awu[None]
+    else:
+        gm = torch.ones(d_in, device=DEV).bfloat16()
+        z, stat, _ = B.lr_group_fwd(x, gm, 1e-5, B.LR_NORM_NONE, wd, wu, B.LR_ACT_IDENTITY)
+        run = lambda grads: B.lr_group_bwd(x, gm, 1e-5, B.LR_NORM_NONE, wd, wu, z, stat, dy, B.LR_ACT_IDENTITY, grads=grads,
+                                           grad_dt=grad_dt)
+        _, _, dwd, dwu = run(None)
+        _, _, awd, awu = run((torch.zeros(d_in, dtype=gt, device=DEV), base[0].clone(), base[1].clone()))
+    for i in range(G):
+        a, b = dy[i].double().cpu(), z[:, i * r:(i + 1) * r].double().cpu()
+        bound = (a.abs().t() @ b.abs()) * (T * 2.0 ** -24)
+        ref = a.t() @ b
+        if grad_dt == B.LR_BF16:
+            bound = bound + (ref.abs() + bound) * 2.0 ** -8
+        assert ((dwu[i].double().cpu() - ref).abs() <= bound).all()
+    if grad_dt == B.LR_F32:   # added to what is there: the same sum and one more rounding
+        assert torch.equal(awd, dwd + base[0]) and torch.equal(awu, dwu + base[1])
