@@ -53,13 +53,14 @@ struct Ctx {
   // way in and out, a backward has nine of them, and its split product may share a launch only if nothing waits to reuse its
   // partials.  Measured, block forward and backward, apart and gathered: 5376 tokens of d = 256, r = 112 423 -> 377 us, 5124 of
   // d = 512, r = 128 488 -> 459, 1912 of d = 512 279 -> 260, 11580 of d = 512, r = 64 973 -> 948.  Of larger ones the partials
-  // leave the caches: with 96 or 256 MiB 0.3 to 1 % slower at d = 2048, 16384 tokens.  So as many gradients as fit GATHER bytes
-  // are, at one split for every eight slices of 64 tokens (the most there are; more tokens never need less room).
+  // leave the caches: with 96 or 256 MiB 0.3 to 1 % slower at d = 2048, 16384 tokens.  So of layers
+  // whose gradients fit half of GATHER bytes (wider ones took the same time either way) as many are as fit it, at one
+  // split for every eight slices of 64 tokens (the most there are; more tokens never need less room).
   static constexpr size_t GATHER = 32 << 20;
   void gather(int64_t weights, int64_t T) {
     const int64_t splits = T / 512 > 1 ? T / 512 : 1;
     const int64_t most = (int64_t)(GATHER / sizeof(float));
-    keep_cap = dt != LR_BF16 ? 0 : (size_t)(weights >= most / splits ? most : weights * splits) * sizeof(float);
+    keep_cap = dt != LR_BF16 || weights > most / 2 ? 0 : (size_t)(weights >= most / splits ? most : weights * splits) * sizeof(float);
     keep = (char*)take(keep_cap);
     keep_off = 0;
     njobs = 0;
