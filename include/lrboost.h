@@ -9,7 +9,10 @@
  *    library never allocates, frees or synchronises: each call validates its arguments on the
  *    host, enqueues kernels on `stream` (a hipStream_t passed as void*, NULL = default
  *    stream) and returns.  Scratch memory comes from the caller through (ws, ws_bytes); the
- *    matching *_workspace_bytes() call gives the size needed.
+ *    matching *_workspace_bytes() call gives the size to hand over.  For the backward of narrow layers
+ *    that is up to 32 MiB more than the call needs (room for the weight gradients' partial sums side by
+ *    side, so that they share launches); a workspace without that part is accepted too and gives the
+ *    same results in more launches.
  *  - Matrices are row-major, activations token-major: x[T, d] with leading dimension ld (in
  *    elements).  Weights use the [out, in] layout: W_down[r, d_in], W_up[d_out, r], dense.
  *  - dt selects the storage type of activations, weights and gradients (LR_F32 or LR_BF16);
@@ -41,7 +44,7 @@ typedef enum {
   LR_OK = 0,
   LR_EINVAL = -1,       /* null pointer, non-positive size, unknown enum value            */
   LR_EUNSUPPORTED = -2, /* valid request the library cannot run (e.g. fp32 block)         */
-  LR_EWORKSPACE = -3,   /* ws is NULL or ws_bytes is smaller than *_workspace_bytes()     */
+  LR_EWORKSPACE = -3,   /* ws is NULL or ws_bytes is smaller than the call needs          */
   LR_EALIGN = -4,       /* pointer / leading-dimension / size alignment rule violated     */
   LR_ELAUNCH = -5       /* a kernel launch was rejected by the runtime                    */
 } lr_status;

@@ -19,6 +19,9 @@ struct Ctx {
   char* base = nullptr;
   size_t cap = 0, off = 0, peak = 0;
   bool dry = false;
+  // The workspace also holds what only makes a call faster (gathered partials, the row partials of a joint launch, sigma(z)
+  // from the data gradient's epilogue).  A query asks for it; a caller whose workspace lacks it gets the same results without.
+  bool roomy = true;
   int dt = LR_BF16;
   int gdt = LR_F32;          // dtype of the weight / gamma gradients
   hipStream_t st = nullptr;
@@ -31,6 +34,7 @@ struct Ctx {
   size_t keep_cap = 0, keep_off = 0;
   FinishJob jobs[FINISH_MAX];
   int njobs = 0;
+  bool keep_full = false;    // (size query) a gradient's partials did not fit
 
   void* take(size_t bytes) {
     off = (off + 255) & ~(size_t)255;
@@ -49,29 +53,33 @@ struct Ctx {
       run(tile ? gemm_bf16_joint(tile, held, nheld, st) : dt == LR_F32 ? gemm_f32_many(held, nheld, st) : gemm_bf16_many(held, nheld, st));
     nheld = -1;
   }
-  // weights: elements of the weights whose gradients over T tokens may be gathered.  A small gradient's finishing pass is 4 us of
-  // way in and out, a backward has nine of them, and its split product may share a launch only if nothing waits to reuse its
-  // partials.  Measured, block forward and backward, apart and gathered: 5376 tokens of d = 256, r = 112 423 -> 377 us, 5124 of
-  // d = 512, r = 128 488 -> 459, 1912 of d = 512 279 -> 260, 11580 of d = 512, r = 64 973 -> 948.  Of larger ones the partials
-  // leave the caches: with 96 or 256 MiB 0.3 to 1 % slower at d = 2048, 16384 tokens.  So of layers
-  // whose gradients fit half of GATHER bytes (wider ones took the same time either way) as many are as fit it, at one
-  // split for every eight slices of 64 tokens (the most there are; more tokens never need less room).
+  // layer: elements of all weights of the call; weights: of those whose gradients over T tokens may be gathered.  A small
+  // gradient's finishing pass is 4 us of way in and out, a backward has nine of them, and its split product may share a launch only
+  // if nothing waits to reuse its partials.  Measured, block forward and backward, apart and gathered: 5376 tokens of d = 256, r = 112
+  // 423 -> 377 us, 5124 of d = 512, r = 128 488 -> 459, 1912 of d = 512 279 -> 260, 11580 of d = 512, r = 64 973 -> 948.  Of
+  // larger ones the partials leave the caches: with 96 or 256 MiB 0.3 to 1 % slower at d = 2048, 16384 tokens.  So of layers
+  // whose gradients fit half of GATHER bytes (wider ones took the same time either way) as many are as fit it, at the most splits
+  // that T tokens have (more tokens never need less room).
   static constexpr size_t GATHER = 32 << 20;
-  void gather(int64_t weights, int64_t T) {
-    const int64_t splits = T / 512 > 1 ? T / 512 : 1;
-    const int64_t most = (int64_t)(GATHER / sizeof(float));
-    keep_cap = dt != LR_BF16 || weights > most / 2 ? 0 : (size_t)(weights >= most / splits ? most : weights * splits) * sizeof(float);
+  void gather(int64_t layer, int64_t weights, int64_t T) {
+    const int64_t splits = gemm_bf16_wgrad_max_splits(T), most = (int64_t)(GATHER / sizeof(float));
+    keep_cap = !roomy || dt != LR_BF16 || layer > most / 2 ? 0 : (size_t)(weights >= most / splits ? most : weights * splits) * sizeof(float);
     keep = (char*)take(keep_cap);
     keep_off = 0;
     njobs = 0;
+    keep_full = false;
   }
-  // room for a gradient's partials until finish(), or null
-  void* gathered(int64_t floats) {
+  // room for a gradient's partials until finish()?  A size query asks with the most splits there are: where one gradient does not fit,
+  // that and all behind it are given room among the ordinary partials, since a call with fewer splits may keep others.
+  bool gathered(int64_t floats, void** p) {
     const size_t bytes = ((size_t)floats * sizeof(float) + 255) & ~(size_t)255;
-    if (dry || njobs == FINISH_MAX || keep_off + bytes > keep_cap) return nullptr;
-    void* p = keep + keep_off;
+    if (keep_full || njobs == FINISH_MAX || keep_off + bytes > keep_cap) {
+      keep_full = dry;
+      return false;
+    }
+    *p = keep + keep_off;
     keep_off += bytes;
-    return p;
+    return true;
   }
   void finish(int accumulate) {
     if (!dry && err == hipSuccess && njobs > 0) run(k_wgrad_finish_many(jobs, njobs, accumulate, gdt, st));
@@ -192,13 +200,13 @@ void wgrad(Ctx& c, const void* Aact, int64_t lda, int Mw, const void* Bact, int6
     gemm(c, op);
     return;
   }
-  if (!colscale && !w_for_dgamma && kmajor)
-    if (void* kept = c.gathered((int64_t)op.splitk * Mw * Nw)) {
-      op.C = kept; op.ldc = Nw;
-      gemm(c, op);
-      c.jobs[c.njobs++] = FinishJob{(const float*)kept, op.splitk, (int64_t)Mw * Nw, dw};
-      return;
-    }
+  void* kept = nullptr;
+  if (!colscale && !w_for_dgamma && kmajor && c.gathered((int64_t)op.splitk * Mw * Nw, &kept)) {
+    op.C = kept; op.ldc = Nw;
+    gemm(c, op);
+    c.jobs[c.njobs++] = FinishJob{(const float*)kept, op.splitk, (int64_t)Mw * Nw, dw};
+    return;
+  }
   float* part = (float*)c.take((size_t)op.splitk * Mw * Nw * sizeof(float));
   op.C = part; op.ldc = Nw;
   const int held = c.nheld;      // its partials are scratch: not held
@@ -253,7 +261,7 @@ void linear_bwd_seq(Ctx& c, const LinArgs& a) {
   da.epi.kind = ident ? EPI_ACTGRAD : EPI_ACTGRAD_A; da.epi.act = a.act; da.epi.R = a.zc; da.epi.ldr = a.r;
   if (!ident) { da.epi.C2 = act_ws; da.epi.ldc2 = a.r; }
   gemm(c, da);
-  c.gather(a.r * (a.d_in + a.d_out), a.T);
+  c.gather(a.r * (a.d_in + a.d_out), a.r * (a.d_in + a.d_out), a.T);
   c.hold();   // three products that wait for dz and sigma(z) only
   // dW_up = dy^T . sigma(z)
   wgrad(c, a.dy, a.lddy, (int)a.d_out, act, a.r, (int)a.r, a.T, a.dw_up, nullptr, nullptr, nullptr, a.accumulate);
@@ -451,15 +459,16 @@ void group_bwd_seq(Ctx& c, const GrpArgs& a, const void* act, bool act_new = fal
   // Joined with the weight gradients they run on 32- or 64-column tiles, which have the most row partials; a size query leaves
   // room for those where the products are small enough to be joined at all.
   const int64_t small_rows = 1024 / ((a.r + 31) / 32 * a.G) * 32;
-  const int join = a.T <= small_rows ? c.join_tile(das, nrun) : 0;
+  const int join = c.roomy && a.T <= small_rows ? c.join_tile(das, nrun) : 0;
   for (int i = 0; normed && c.dt == LR_BF16 && i < nrun; i++) {
     das[i].tile = join ? join : i == 0 ? gemm_bf16_tile(das[0]) : das[0].tile;
     rp = gemm_bf16_rowparts(das[i]);
   }
   int64_t parts_size = 0;
   if (c.dry && rp.slabs) {
-    rp.slabs = gemm_bf16_rowpart_slabs_max(das[0], {EPI_ACTGRAD, EPI_ACTGRAD_A, EPI_LAXGRAD});
+    rp.slabs = gemm_bf16_rowpart_slabs_max(das[0], {EPI_ACTGRAD, act_new ? EPI_ACTGRAD_A : EPI_ACTGRAD, EPI_LAXGRAD});
     for (int t : {GEMM_R32, GEMM_R64}) {   // (for more tokens no less than for fewer)
+      if (!c.roomy) break;
       das[0].tile = t;
       const int64_t need = (a.T < small_rows ? a.T : small_rows) * gemm_bf16_rowparts(das[0]).slabs * a.G;
       if (need > parts_size) parts_size = need;
@@ -544,9 +553,15 @@ void group_bwd_full_seq(Ctx& c, const GrpArgs& a) {
   const size_t es = esize(c.dt);
   const int64_t GR = (int64_t)a.G * a.r;
   void* act = c.take((size_t)a.T * GR * es);
-  c.gather(a.r * a.G * (a.d_in + a.d_out), a.T);
-  if (a.act == LR_ACT_IDENTITY && !c.dry) group_bwd_seq(c, a, a.zc);   // (the order of the other form needs more workspace)
-  else group_bwd_seq(c, a, act, true);
+  c.gather(a.r * a.G * (a.d_in + a.d_out), a.r * a.G * (a.norm == LR_NORM_NONE ? a.d_in + a.d_out : a.d_out), a.T);
+  if (a.act == LR_ACT_IDENTITY && !c.dry) {   // (the order of the other form needs more workspace)
+    group_bwd_seq(c, a, a.zc);
+  } else if (c.roomy) {
+    group_bwd_seq(c, a, act, true);
+  } else {
+    LAUNCH(c, k_act_fwd(a.zc, GR, act, GR, a.T, GR, a.act, c.dt, c.st));
+    group_bwd_seq(c, a, act);
+  }
   c.finish(a.accumulate);
 }
 
@@ -578,6 +593,14 @@ int check_ws(const void* ws, size_t have, size_t need) {
   if (!ws || have < need) return LR_EWORKSPACE;
   if (((uintptr_t)ws & 255) != 0) return LR_EALIGN;
   return LR_OK;
+}
+
+// The same for a call that asks for more than it needs: bytes(true) is its query, bytes(false) what it needs.
+template <class Bytes>
+int check_ws(const void* ws, size_t have, Bytes bytes, bool& roomy) {
+  const size_t all = bytes(true);
+  roomy = have >= all;
+  return check_ws(ws, have, roomy ? all : bytes(false));
 }
 
 int check_sizes_fit_int(std::initializer_list<int64_t> v) {
@@ -805,7 +828,7 @@ void block_bwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   if (!p) p = &np;
   if (!g) g = &np;
   if (!ck) ck = &nck;
-  c.gather(r * (9 * d + 2 * b.dkv + 3 * f), T);
+  c.gather(r * (9 * d + 2 * b.dkv + 3 * f), r * (4 * d + 2 * b.dkv + 3 * f), T);   // (not those behind a norm)
   void* act_d = c.take((size_t)T * r * es);
   void* act_o = c.take((size_t)T * r * es);
   // What small blocks wait for are launches, so theirs rebuild all layers' activations in one and fold both norms' gammas in
@@ -952,13 +975,16 @@ const char* lr_status_string(int status) {
 }
 
 // ---- linear ---------------------------------------------------------------------------------
-size_t lr_linear_workspace_bytes(int64_t T, int64_t d_in, int64_t r, int64_t d_out, int dt, int backward) {
+static size_t linear_bytes(int64_t T, int64_t d_in, int64_t r, int64_t d_out, int dt, int backward, bool roomy) {
   if (check_dt(dt) != LR_OK || T < 0 || check_sizes_fit_int({d_in, r, d_out}) != LR_OK) return 0;
   if (T == 0) return 0;
-  Ctx c; c.dry = true; c.dt = dt;
+  Ctx c; c.dry = true; c.dt = dt; c.roomy = roomy;
   LinArgs a{}; a.T = T; a.d_in = d_in; a.r = r; a.d_out = d_out; a.ldx = d_in; a.ldy = d_out; a.lddy = d_out; a.lddx = d_in;
   if (backward) linear_bwd_seq(c, a); else linear_fwd_seq(c, a);
   return c.peak + 256;
+}
+size_t lr_linear_workspace_bytes(int64_t T, int64_t d_in, int64_t r, int64_t d_out, int dt, int backward) {
+  return linear_bytes(T, d_in, r, d_out, dt, backward, true);
 }
 
 int lr_linear_fwd(const void* x, int64_t ldx, const void* w_down, const void* w_up, void* z, void* y, int64_t ldy,
@@ -992,8 +1018,9 @@ int lr_linear_bwd(const void* x, int64_t ldx, const void* w_down, const void* w_
   if (T == 0) return LR_OK;   // no tokens: gradients are left as they are
   TRY(check_ptrs(dt, {x, w_down, w_up, z, dy, dx}));
   TRY(check_gptrs(grad_dt, {dw_down, dw_up}));
-  TRY(check_ws(ws, ws_bytes, lr_linear_workspace_bytes(T, d_in, r, d_out, dt, 1)));
-  Ctx c; c.base = (char*)ws; c.cap = ws_bytes; c.dt = dt; c.gdt = grad_dt; c.st = (hipStream_t)stream;
+  bool roomy;
+  TRY(check_ws(ws, ws_bytes, [&](bool all) { return linear_bytes(T, d_in, r, d_out, dt, 1, all); }, roomy));
+  Ctx c; c.roomy = roomy; c.base = (char*)ws; c.cap = ws_bytes; c.dt = dt; c.gdt = grad_dt; c.st = (hipStream_t)stream;
   LinArgs a{}; a.x = x; a.w_down = w_down; a.w_up = w_up; a.zc = z; a.dy = dy; a.dx = dx; a.dw_down = dw_down;
   a.dw_up = dw_up; a.ldx = ldx; a.lddy = lddy; a.lddx = lddx; a.T = T; a.d_in = d_in; a.r = r; a.d_out = d_out;
   a.act = act; a.accumulate = accumulate;
@@ -1052,10 +1079,10 @@ int lr_linear_fwd_static(const void* x, int64_t ldx, const void* w_down, const v
 }
 
 // ---- group -----------------------------------------------------------------------------------
-size_t lr_group_workspace_bytes(int G, int64_t T, int64_t d_in, int64_t r, int64_t d_out, int dt, int backward) {
+static size_t group_bytes(int G, int64_t T, int64_t d_in, int64_t r, int64_t d_out, int dt, int backward, bool roomy) {
   if (check_dt(dt) != LR_OK || G <= 0 || G > 64 || T < 0 || check_sizes_fit_int({d_in, r, d_out}) != LR_OK) return 0;
   if (T == 0) return 0;
-  Ctx c; c.dry = true; c.dt = dt;
+  Ctx c; c.dry = true; c.dt = dt; c.roomy = roomy;
   GrpArgs a{}; a.G = G; a.T = T; a.d_in = d_in; a.r = r; a.d_out = d_out; a.ldx = d_in; a.ldy = d_out;
   a.y_bs = T * d_out; a.lddy = d_out; a.dy_bs = T * d_out; a.lddx = d_in;
   size_t peak = 0;
@@ -1067,6 +1094,9 @@ size_t lr_group_workspace_bytes(int G, int64_t T, int64_t d_in, int64_t r, int64
     if (c.peak > peak) peak = c.peak;
   }
   return peak + 256;
+}
+size_t lr_group_workspace_bytes(int G, int64_t T, int64_t d_in, int64_t r, int64_t d_out, int dt, int backward) {
+  return group_bytes(G, T, d_in, r, d_out, dt, backward, true);
 }
 
 int lr_group_fwd(const void* x, int64_t ldx, const void* gamma, float eps, int norm, const void* w_down_cat,
@@ -1124,8 +1154,9 @@ int lr_group_bwd(const void* x, int64_t ldx, const void* gamma, float eps, int n
     if (!stat) return LR_EINVAL;
   }
   if (T == 0) return LR_OK;
-  TRY(check_ws(ws, ws_bytes, lr_group_workspace_bytes(G, T, d_in, r, d_out, dt, 1)));
-  Ctx c; c.base = (char*)ws; c.cap = ws_bytes; c.dt = dt; c.gdt = grad_dt; c.st = (hipStream_t)stream;
+  bool roomy;
+  TRY(check_ws(ws, ws_bytes, [&](bool all) { return group_bytes(G, T, d_in, r, d_out, dt, 1, all); }, roomy));
+  Ctx c; c.roomy = roomy; c.base = (char*)ws; c.cap = ws_bytes; c.dt = dt; c.gdt = grad_dt; c.st = (hipStream_t)stream;
   GrpArgs a{}; a.x = x; a.gamma = gamma; a.w_down_cat = w_down_cat; a.w_up_stack = w_up_stack; a.zc = z_cat;
   a.statc = stat; a.dy_stack = dy_stack; a.dx = dx; a.dgamma = dgamma; a.dw_down_cat = dw_down_cat;
   a.dw_up_stack = dw_up_stack; a.ldx = ldx; a.lddy = lddy; a.dy_bs = dy_batch_stride; a.lddx = lddx; a.T = T;
@@ -1136,14 +1167,16 @@ int lr_group_bwd(const void* x, int64_t ldx, const void* gamma, float eps, int n
 
 
 // ---- block -----------------------------------------------------------------------------------
+static size_t block_bytes(const Blk& b, int backward, const lr_block_saved* sv, bool roomy) {
+  Ctx c; c.dry = true; c.dt = LR_BF16; c.roomy = roomy;
+  lr_block_params np{};
+  if (backward) block_bwd_seq(c, b, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, sv);
+  else block_fwd_seq(c, b, &np, nullptr, nullptr, nullptr, nullptr, sv);
+  return c.peak + 256;
+}
 size_t lr_block_workspace_bytes(const lr_block_desc* desc, int backward) {
   Blk b; int why;
-  if (!block_desc_ok(desc, b, &why)) return 0;
-  Ctx c; c.dry = true; c.dt = LR_BF16;
-  lr_block_params np{};
-  if (backward) block_bwd_seq(c, b, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0);
-  else block_fwd_seq(c, b, &np, nullptr, nullptr, nullptr);
-  return c.peak + 256;
+  return block_desc_ok(desc, b, &why) ? block_bytes(b, backward, nullptr, true) : 0;
 }
 
 size_t lr_block_ckpt_bytes(const lr_block_desc* desc) {
@@ -1183,8 +1216,9 @@ int lr_block_bwd(const lr_block_desc* desc, const lr_block_params* params, const
   if (!block_desc_ok(desc, b, &why)) return why;
   TRY(check_params(params)); TRY(check_params(grads)); TRY(check_ckpt(ckpt));
   TRY(check_ptrs(LR_BF16, {x, dy, dx}));
-  TRY(check_ws(ws, ws_bytes, lr_block_workspace_bytes(desc, 1)));
-  Ctx c; c.base = (char*)ws; c.cap = ws_bytes; c.dt = LR_BF16; c.gdt = b.gdt; c.st = (hipStream_t)stream;
+  bool roomy;
+  TRY(check_ws(ws, ws_bytes, [&](bool all) { return block_bytes(b, 1, nullptr, all); }, roomy));
+  Ctx c; c.roomy = roomy; c.base = (char*)ws; c.cap = ws_bytes; c.dt = LR_BF16; c.gdt = b.gdt; c.st = (hipStream_t)stream;
   block_bwd_seq(c, b, params, x, dy, ckpt, dx, grads, accumulate);
   return c.err == hipErrorNotSupported ? LR_EUNSUPPORTED : status_of(c);
 }
@@ -1192,13 +1226,8 @@ int lr_block_bwd(const lr_block_desc* desc, const lr_block_params* params, const
 // ---- block with every wide activation kept (the store-everything reference of Sec. 4.4 / Table 5) ----
 size_t lr_block_saved_workspace_bytes(const lr_block_desc* desc, int backward) {
   Blk b; int why;
-  if (!block_desc_ok(desc, b, &why)) return 0;
-  Ctx c; c.dry = true; c.dt = LR_BF16;
-  lr_block_params np{};
-  lr_block_saved nsv{};
-  if (backward) block_bwd_seq(c, b, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, &nsv);
-  else block_fwd_seq(c, b, &np, nullptr, nullptr, nullptr, nullptr, &nsv);
-  return c.peak + 256;
+  const lr_block_saved nsv{};
+  return block_desc_ok(desc, b, &why) ? block_bytes(b, backward, &nsv, true) : 0;
 }
 
 static int check_saved(const lr_block_saved* sv) {
@@ -1227,8 +1256,10 @@ int lr_block_bwd_saved(const lr_block_desc* desc, const lr_block_params* params,
   if (!block_desc_ok(desc, b, &why)) return why;
   TRY(check_params(params)); TRY(check_params(grads)); TRY(check_ckpt(ckpt)); TRY(check_saved(saved));
   TRY(check_ptrs(LR_BF16, {x, dy, dx}));
-  TRY(check_ws(ws, ws_bytes, lr_block_saved_workspace_bytes(desc, 1)));
-  Ctx c; c.base = (char*)ws; c.cap = ws_bytes; c.dt = LR_BF16; c.gdt = b.gdt; c.st = (hipStream_t)stream;
+  const lr_block_saved nsv{};
+  bool roomy;
+  TRY(check_ws(ws, ws_bytes, [&](bool all) { return block_bytes(b, 1, &nsv, all); }, roomy));
+  Ctx c; c.roomy = roomy; c.base = (char*)ws; c.cap = ws_bytes; c.dt = LR_BF16; c.gdt = b.gdt; c.st = (hipStream_t)stream;
   block_bwd_seq(c, b, params, x, dy, ckpt, dx, grads, accumulate, nullptr, saved);
   return status_of(c);
 }
@@ -1265,8 +1296,9 @@ int lr_block_lax_bwd(const lr_block_desc* desc, const lr_block_params* params, c
   TRY(check_lax(desc, lax));
   TRY(check_params(params)); TRY(check_params(grads)); TRY(check_ckpt(ckpt));
   TRY(check_ptrs(LR_BF16, {x, dy, dx}));
-  TRY(check_ws(ws, ws_bytes, lr_block_workspace_bytes(desc, 1)));
-  Ctx c; c.base = (char*)ws; c.cap = ws_bytes; c.dt = LR_BF16; c.gdt = b.gdt; c.st = (hipStream_t)stream;
+  bool roomy;
+  TRY(check_ws(ws, ws_bytes, [&](bool all) { return block_bytes(b, 1, nullptr, all); }, roomy));
+  Ctx c; c.roomy = roomy; c.base = (char*)ws; c.cap = ws_bytes; c.dt = LR_BF16; c.gdt = b.gdt; c.st = (hipStream_t)stream;
   block_bwd_seq(c, b, params, x, dy, ckpt, dx, grads, accumulate, lax);
   return c.err == hipErrorNotSupported ? LR_EUNSUPPORTED : status_of(c);
 }

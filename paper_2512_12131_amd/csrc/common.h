@@ -109,6 +109,7 @@ int gemm_bf16_rowpart_slabs_max(GemmOp op, std::initializer_list<int> kinds);
 // parts, added up by the finishing pass (splitk) or inside the GEMM (k_parts); the other of the two is 1.
 // direct: the output needs no finishing pass when it is not split.
 int gemm_bf16_wgrad_splits(int M, int N, int K);
+int gemm_bf16_wgrad_max_splits(int64_t K);       // the most of them that any weight has
 struct WgradPlan { int tile, splitk, k_parts; };
 WgradPlan gemm_bf16_plan_wgrad(int M, int N, int K, int batch, bool direct);
 // Up to JOINT_MAX products of one launch that do not depend on each other (gemm_joint.hip), on 32 x 32 or 64 x 64 tiles.

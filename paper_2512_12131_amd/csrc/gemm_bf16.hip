@@ -528,6 +528,11 @@ int gemm_bf16_rowpart_slabs_max(GemmOp op, std::initializer_list<int> kinds) {
   return most;
 }
 
+int gemm_bf16_wgrad_max_splits(int64_t K) {
+  const int64_t nk = (K + BK - 1) / BK;
+  return nk < 16 ? 1 : nk / 8 < 64 ? (int)(nk / 8) : 64;   // at least 8 slices per split
+}
+
 int gemm_bf16_wgrad_splits(int M, int N, int K) {
   // The splits are part of the result: the fp32 sum over the tokens is their sums added up.  So they follow from the shape
   // alone, whatever tile runs them, whether the gradient is added to and how many equal ones share a launch.
@@ -537,7 +542,7 @@ int gemm_bf16_wgrad_splits(int M, int N, int K) {
   const int bm = 256, bn = N > 128 && (N % 256 == 0 || N > 512) ? 256 : 128;
   const long tiles = (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
   const int nk = (K + BK - 1) / BK;
-  const int maxs = nk >= 16 ? (nk / 8 < 64 ? nk / 8 : 64) : 1;   // at least 8 slices per split
+  const int maxs = gemm_bf16_wgrad_max_splits(K);
   int best = 1;
   long best_cost = -1;
   for (int s = 1; s <= maxs; s++) {

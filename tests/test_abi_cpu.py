@@ -226,3 +226,23 @@ def test_a_block_workspace_for_more_tokens_serves_for_fewer(shape):
             desc = B.make_block_desc(1, S, 128 * H, H, 128, f, (f + 7) // 8 * 8, r, n_kv_heads=kv)
             sizes.append(B.lr_block_workspace_bytes(desc, backward))
         assert sizes == sorted(sizes)
+
+
+# (T, d_in, r, d_out, dtype) -> bytes the backward of a layer needs: sigma(z) and dz, and the larger gradient's partials
+NEEDED_LINEAR = [((16, 1024, 256, 1024, B.LR_BF16), 1065216), ((1031, 1024, 256, 768, B.LR_BF16), 3153152),
+                 ((8192, 1024, 256, 1024, B.LR_BF16), 25166080), ((961, 64, 16, 72, B.LR_BF16), 71424),
+                 ((512, 256, 64, 256, B.LR_F32), 327936)]
+
+
+@pytest.mark.parametrize("shape,need", NEEDED_LINEAR)
+def test_linear_backward_refuses_less_than_it_needs(shape, need):
+    """... and asks for the partials of both gradients side by side (at most 32 MiB) beside sigma(z), dz and a weight, not on top of
+    what it needs without them.  (test_gpu_workspace.py: exactly what it needs is accepted.)"""
+    lib = B.lib()
+    T, d, r, n, dt = shape
+    fake = C.c_void_p(0x10000)
+    assert lib.lr_linear_bwd(fake, d, fake, fake, fake, fake, n, fake, d, fake, fake, T, d, r, n, 1, dt, 0, 0, fake, need - 1, None) == -3
+    splits = max(1, -(-T // 64) // 8)
+    side_by_side = min(32 << 20, splits * r * (d + n) * 4)
+    rest = 2 * T * r * 2 + r * max(d, n) * 2
+    assert need <= B.lr_linear_workspace_bytes(T, d, r, n, dt, 1) <= max(need, side_by_side + rest + 2048)

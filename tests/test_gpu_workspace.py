@@ -1,0 +1,122 @@
+"""A backward that is handed no more workspace than it needs, without the room for gathered partials that its query asks for:
+the same bits, and nothing written behind the end."""
+import ctypes as C
+
+import pytest
+import torch
+
+from paper_2512_12131_amd import binding as B
+from test_abi_cpu import NEEDED_LINEAR
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+GUARD = 64 << 20      # more than any buffer of the calls: an overrun lands in it
+
+
+def _run(call, outs, size):
+    ws = torch.full((size + GUARD,), 0x5A, dtype=torch.uint8, device=DEV)
+    for o in outs:
+        o.fill_(0.5)
+    status = call(ws.data_ptr(), size)
+    torch.cuda.synchronize()
+    assert status == 0, f"{size} bytes: status {status}"
+    assert bool((ws[size:] == 0x5A).all())
+    return [o.clone() for o in outs]
+
+
+def _same(call, outs, need, query):
+    assert need <= query
+    for a, b in zip(_run(call, outs, need), _run(call, outs, query)):
+        assert torch.equal(a, b)
+
+
+def _stream():
+    return torch.cuda.current_stream().cuda_stream
+
+
+@pytest.mark.parametrize("accumulate", [0, 1])
+@pytest.mark.parametrize("act", [B.LR_ACT_SILU, B.LR_ACT_IDENTITY])
+@pytest.mark.parametrize("shape,need", NEEDED_LINEAR)
+def test_linear(shape, need, act, accumulate):
+    T, d, r, n, dt = shape
+    print(f"linear backward in {need} bytes: {shape} act={act} accumulate={accumulate}", flush=True)
+    td = torch.bfloat16 if dt == B.LR_BF16 else torch.float32
+    g = torch.Generator(device=DEV).manual_seed(T)
+    x, wd, wu, dy = (torch.randn(s, generator=g, device=DEV).to(td) for s in ((T, d), (r, d), (n, r), (T, n)))
+    z, _ = B.lr_linear_fwd(x, wd, wu, act)
+    outs = [torch.empty_like(x), torch.empty((r, d), device=DEV), torch.empty((n, r), device=DEV)]
+
+    def call(ws, size):
+        return B.lib().lr_linear_bwd(x.data_ptr(), d, wd.data_ptr(), wu.data_ptr(), z.data_ptr(), dy.data_ptr(), n, outs[0].data_ptr(),
+                                     d, outs[1].data_ptr(), outs[2].data_ptr(), T, d, r, n, act, dt, B.LR_F32, accumulate, ws, size,
+                                     _stream())
+
+    _same(call, outs, need, B.lr_linear_workspace_bytes(T, d, r, n, dt, 1))
+
+
+@pytest.mark.parametrize("act", [B.LR_ACT_SILU, B.LR_ACT_IDENTITY])
+@pytest.mark.parametrize("norm", [B.LR_NORM_NONE, B.LR_NORM_ONLINE])
+@pytest.mark.parametrize("shape,need", [((3, 1031, 264, 40, 520, B.LR_BF16), 782336), ((2, 4, 240, 344, 1480, B.LR_BF16), 2048768),
+                                        ((2, 2048, 16, 592, 1240, B.LR_BF16), 16595200), ((3, 300, 72, 24, 104, B.LR_F32), 196352)])
+def test_group(shape, need, norm, act):
+    G, T, d, r, n, dt = shape
+    print(f"group backward in {need} bytes: {shape} norm={norm} act={act}", flush=True)
+    td = torch.bfloat16 if dt == B.LR_BF16 else torch.float32
+    g = torch.Generator(device=DEV).manual_seed(T)
+    x, wd, wu, dy = (torch.randn(s, generator=g, device=DEV).to(td) for s in ((T, d), (G * r, d), (G, n, r), (G, T, n)))
+    gm = torch.ones(d, device=DEV).to(td)
+    z, stat, _ = B.lr_group_fwd(x, gm, 1e-5, norm, wd, wu, act)
+    outs = [torch.empty_like(x), torch.empty(d, device=DEV), torch.empty((G * r, d), device=DEV), torch.empty((G, n, r), device=DEV)]
+
+    def call(ws, size):
+        return B.lib().lr_group_bwd(x.data_ptr(), d, gm.data_ptr(), 1e-5, norm, wd.data_ptr(), wu.data_ptr(), z.data_ptr(),
+                                    stat.data_ptr(), dy.data_ptr(), n, T * n, outs[0].data_ptr(), d, outs[1].data_ptr(),
+                                    outs[2].data_ptr(), outs[3].data_ptr(), G, T, d, r, n, act, dt, B.LR_F32, 1, ws, size, _stream())
+
+    _same(call, outs, need, B.lr_group_workspace_bytes(G, T, d, r, n, dt, 1))
+
+
+@pytest.mark.parametrize("form", ["plain", "saved", "lax"])
+@pytest.mark.parametrize("shape,need,need_saved", [((2, 256, 2, 2, 344, 64), 6277376, 3905792), ((3, 129, 4, 2, 1003, 136), 9274880, 6135040),
+                                                   ((2, 700, 4, 4, 1416, 128), 32633088, 20716032)])
+def test_block(shape, need, need_saved, form):
+    Bn, S, H, kv, f, r = shape
+    need = need_saved if form == "saved" else need
+    print(f"block backward in {need} bytes: {shape} {form}", flush=True)
+    T, d, dkv, f_ld = Bn * S, 128 * H, 128 * kv, (f + 7) // 8 * 8
+    g = torch.Generator(device=DEV).manual_seed(S)
+
+    def rand(*s, std=1.0, mean=0.0):
+        return (torch.randn(s, generator=g, device=DEV) * std + mean).bfloat16()
+
+    p = {"gamma1": rand(d, std=0.1, mean=1.0), "w_dn_qkv": rand(3 * r, d, std=d ** -0.5), "w_up_qkv": rand(d + 2 * dkv, r, std=r ** -0.5),
+         "w_dn_o": rand(r, d, std=d ** -0.5), "w_up_o": rand(d, r, std=r ** -0.5), "gamma2": rand(d, std=0.1, mean=1.0),
+         "w_dn_gu": rand(2 * r, d, std=d ** -0.5), "w_up_gu": rand(2, f_ld, r, std=r ** -0.5), "w_dn_d": rand(r, f_ld, std=f ** -0.5),
+         "w_up_d": rand(d, r, std=r ** -0.5)}
+    p["w_up_gu"][:, f:] = 0
+    p["w_dn_d"][:, f:] = 0
+    desc = B.make_block_desc(Bn, S, d, H, 128, f, f_ld, r, act=B.LR_ACT_IDENTITY if form == "lax" else B.LR_ACT_SILU, n_kv_heads=kv)
+    x, dy = rand(T, d), rand(T, d)
+    dx = torch.empty_like(x)
+    grads = {n: torch.empty_like(t, dtype=torch.float32) for n, t in p.items()}
+    ps, gs = B._params_struct(p), B._params_struct(grads)
+    saved = B.alloc_block_saved(desc, x.device)
+    if form == "saved":
+        _, ck, saved = B.lr_block_fwd_save(desc, p, x, saved=saved)
+    elif form == "lax":
+        _, ck = B.lr_block_lax_fwd(desc, p, x)
+    else:
+        _, ck = B.lr_block_fwd(desc, p, x)
+    cs, ss, lx = B._ckpt_struct(ck), B._saved_struct(saved), B._lax_struct()
+    lib = B.lib()
+
+    def call(ws, size):
+        a = (C.byref(desc), C.byref(ps), x.data_ptr(), dy.data_ptr(), C.byref(cs))
+        if form == "saved":
+            return lib.lr_block_bwd_saved(*a, C.byref(ss), dx.data_ptr(), C.byref(gs), 1, ws, size, _stream())
+        if form == "lax":
+            return lib.lr_block_lax_bwd(*a, dx.data_ptr(), C.byref(gs), 1, C.byref(lx), ws, size, _stream())
+        return lib.lr_block_bwd(*a, dx.data_ptr(), C.byref(gs), 1, ws, size, _stream())
+
+    query = lib.lr_block_saved_workspace_bytes(C.byref(desc), 1) if form == "saved" else B.lr_block_workspace_bytes(desc, 1)
+    _same(call, [dx, *grads.values()], need, query)
