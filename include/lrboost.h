@@ -12,7 +12,9 @@
  *    matching *_workspace_bytes() call gives the size to hand over.  For the backward of narrow layers
  *    that is up to 32 MiB more than the call needs (room for the weight gradients' partial sums side by
  *    side, so that they share launches); a workspace without that part is accepted too and gives the
- *    same results in more launches.
+ *    same results in more launches.  The queries count dense rows: a backward over x or dy whose rows span
+ *    2 GiB or more in all (T * ld * 2 bytes) needs copies of them on top and returns LR_EWORKSPACE
+ *    without the room.
  *  - Matrices are row-major, activations token-major: x[T, d] with leading dimension ld (in
  *    elements).  Weights use the [out, in] layout: W_down[r, d_in], W_up[d_out, r], dense.
  *  - dt selects the storage type of activations, weights and gradients (LR_F32 or LR_BF16);

@@ -975,16 +975,19 @@ const char* lr_status_string(int status) {
 }
 
 // ---- linear ---------------------------------------------------------------------------------
-static size_t linear_bytes(int64_t T, int64_t d_in, int64_t r, int64_t d_out, int dt, int backward, bool roomy) {
+// ldx, lddy: row strides of x and dy.  A weight gradient reads rows up to 2 GB apart in place and copies others first, which a query
+// for dense rows does not ask for: a call counts what its own strides take.
+static size_t linear_bytes(int64_t T, int64_t d_in, int64_t r, int64_t d_out, int dt, int backward, bool roomy, int64_t ldx,
+                           int64_t lddy) {
   if (check_dt(dt) != LR_OK || T < 0 || check_sizes_fit_int({d_in, r, d_out}) != LR_OK) return 0;
   if (T == 0) return 0;
   Ctx c; c.dry = true; c.dt = dt; c.roomy = roomy;
-  LinArgs a{}; a.T = T; a.d_in = d_in; a.r = r; a.d_out = d_out; a.ldx = d_in; a.ldy = d_out; a.lddy = d_out; a.lddx = d_in;
+  LinArgs a{}; a.T = T; a.d_in = d_in; a.r = r; a.d_out = d_out; a.ldx = ldx; a.ldy = d_out; a.lddy = lddy; a.lddx = d_in;
   if (backward) linear_bwd_seq(c, a); else linear_fwd_seq(c, a);
   return c.peak + 256;
 }
 size_t lr_linear_workspace_bytes(int64_t T, int64_t d_in, int64_t r, int64_t d_out, int dt, int backward) {
-  return linear_bytes(T, d_in, r, d_out, dt, backward, true);
+  return linear_bytes(T, d_in, r, d_out, dt, backward, true, d_in, d_out);
 }
 
 int lr_linear_fwd(const void* x, int64_t ldx, const void* w_down, const void* w_up, void* z, void* y, int64_t ldy,
@@ -1019,7 +1022,7 @@ int lr_linear_bwd(const void* x, int64_t ldx, const void* w_down, const void* w_
   TRY(check_ptrs(dt, {x, w_down, w_up, z, dy, dx}));
   TRY(check_gptrs(grad_dt, {dw_down, dw_up}));
   bool roomy;
-  TRY(check_ws(ws, ws_bytes, [&](bool all) { return linear_bytes(T, d_in, r, d_out, dt, 1, all); }, roomy));
+  TRY(check_ws(ws, ws_bytes, [&](bool all) { return linear_bytes(T, d_in, r, d_out, dt, 1, all, ldx, lddy); }, roomy));
   Ctx c; c.roomy = roomy; c.base = (char*)ws; c.cap = ws_bytes; c.dt = dt; c.gdt = grad_dt; c.st = (hipStream_t)stream;
   LinArgs a{}; a.x = x; a.w_down = w_down; a.w_up = w_up; a.zc = z; a.dy = dy; a.dx = dx; a.dw_down = dw_down;
   a.dw_up = dw_up; a.ldx = ldx; a.lddy = lddy; a.lddx = lddx; a.T = T; a.d_in = d_in; a.r = r; a.d_out = d_out;
@@ -1079,12 +1082,13 @@ int lr_linear_fwd_static(const void* x, int64_t ldx, const void* w_down, const v
 }
 
 // ---- group -----------------------------------------------------------------------------------
-static size_t group_bytes(int G, int64_t T, int64_t d_in, int64_t r, int64_t d_out, int dt, int backward, bool roomy) {
+static size_t group_bytes(int G, int64_t T, int64_t d_in, int64_t r, int64_t d_out, int dt, int backward, bool roomy, int64_t ldx,
+                          int64_t lddy) {
   if (check_dt(dt) != LR_OK || G <= 0 || G > 64 || T < 0 || check_sizes_fit_int({d_in, r, d_out}) != LR_OK) return 0;
   if (T == 0) return 0;
   Ctx c; c.dry = true; c.dt = dt; c.roomy = roomy;
-  GrpArgs a{}; a.G = G; a.T = T; a.d_in = d_in; a.r = r; a.d_out = d_out; a.ldx = d_in; a.ldy = d_out;
-  a.y_bs = T * d_out; a.lddy = d_out; a.dy_bs = T * d_out; a.lddx = d_in;
+  GrpArgs a{}; a.G = G; a.T = T; a.d_in = d_in; a.r = r; a.d_out = d_out; a.ldx = ldx; a.ldy = d_out;
+  a.y_bs = T * d_out; a.lddy = lddy; a.dy_bs = T * d_out; a.lddx = d_in;
   size_t peak = 0;
   // take the larger of the norm variants so one query serves all of them
   for (int norm : {LR_NORM_NONE, LR_NORM_TWO_PASS, LR_NORM_ONLINE, LR_NORM_SHARD_LOCAL}) {
@@ -1096,7 +1100,7 @@ static size_t group_bytes(int G, int64_t T, int64_t d_in, int64_t r, int64_t d_o
   return peak + 256;
 }
 size_t lr_group_workspace_bytes(int G, int64_t T, int64_t d_in, int64_t r, int64_t d_out, int dt, int backward) {
-  return group_bytes(G, T, d_in, r, d_out, dt, backward, true);
+  return group_bytes(G, T, d_in, r, d_out, dt, backward, true, d_in, d_out);
 }
 
 int lr_group_fwd(const void* x, int64_t ldx, const void* gamma, float eps, int norm, const void* w_down_cat,
@@ -1155,7 +1159,7 @@ int lr_group_bwd(const void* x, int64_t ldx, const void* gamma, float eps, int n
   }
   if (T == 0) return LR_OK;
   bool roomy;
-  TRY(check_ws(ws, ws_bytes, [&](bool all) { return group_bytes(G, T, d_in, r, d_out, dt, 1, all); }, roomy));
+  TRY(check_ws(ws, ws_bytes, [&](bool all) { return group_bytes(G, T, d_in, r, d_out, dt, 1, all, ldx, lddy); }, roomy));
   Ctx c; c.roomy = roomy; c.base = (char*)ws; c.cap = ws_bytes; c.dt = dt; c.gdt = grad_dt; c.st = (hipStream_t)stream;
   GrpArgs a{}; a.x = x; a.gamma = gamma; a.w_down_cat = w_down_cat; a.w_up_stack = w_up_stack; a.zc = z_cat;
   a.statc = stat; a.dy_stack = dy_stack; a.dx = dx; a.dgamma = dgamma; a.dw_down_cat = dw_down_cat;

@@ -246,3 +246,22 @@ def test_linear_backward_refuses_less_than_it_needs(shape, need):
     side_by_side = min(32 << 20, splits * r * (d + n) * 4)
     rest = 2 * T * r * 2 + r * max(d, n) * 2
     assert need <= B.lr_linear_workspace_bytes(T, d, r, n, dt, 1) <= max(need, side_by_side + rest + 2048)
+
+
+def test_strided_backward_counts_the_copies_it_makes():
+    """Rows that span 2 GiB or more are copied before the weight gradient: a call without the room for that is refused, instead of
+    copying past the end of its workspace."""
+    lib = B.lib()
+    fake = C.c_void_p(0x10000)
+    T, d, r, n, wide = 65536, 512, 16, 512, 20000           # 65536 rows of 40000 bytes
+    ws = lib.lr_linear_workspace_bytes(T, d, r, n, B.LR_BF16, 1)
+    assert ws < T * (d + r) * 2                             # the copies alone: a wide operand and dz or sigma(z)
+    f = lib.lr_linear_bwd
+    assert f(fake, wide, fake, fake, fake, fake, n, fake, d, fake, fake, T, d, r, n, 1, B.LR_BF16, 0, 0, fake, ws, None) == -3
+    assert f(fake, d, fake, fake, fake, fake, wide, fake, d, fake, fake, T, d, r, n, 1, B.LR_BF16, 0, 0, fake, ws, None) == -3
+    G = 2
+    ws = lib.lr_group_workspace_bytes(G, T, d, r, n, B.LR_BF16, 1)
+    f = lib.lr_group_bwd
+    for ldx, lddy in ((wide, n), (d, wide)):
+        assert f(fake, ldx, fake, 1e-5, B.LR_NORM_ONLINE, fake, fake, fake, fake, fake, lddy, n, fake, d, fake, fake, fake, G, T, d, r, n,
+                 1, B.LR_BF16, 0, 0, fake, ws, None) == -3

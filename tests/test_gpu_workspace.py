@@ -120,3 +120,33 @@ def test_block(shape, need, need_saved, form):
 
     query = lib.lr_block_saved_workspace_bytes(C.byref(desc), 1) if form == "saved" else B.lr_block_workspace_bytes(desc, 1)
     _same(call, [dx, *grads.values()], need, query)
+
+
+def test_rows_that_span_more_than_2_gib():
+    """x and dy as columns of a 2.6 GB tensor: refused in the workspace of dense rows, and with the room for copies the gradients of
+    dense rows.  Each is a chained sum of T exact products in both: off by at most T 2^-24 of the sum of their magnitudes."""
+    T, d, r, n, wide = 65536, 64, 16, 72, 20000
+    print("layer backward over rows that span 2.6 GB", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(1)
+    big = torch.empty((T, wide), dtype=torch.bfloat16, device=DEV)
+    x, dy = big[:, 8:8 + d], big[:, 512:512 + n]
+    x.copy_(torch.randn((T, d), generator=g, device=DEV))
+    dy.copy_(torch.randn((T, n), generator=g, device=DEV))
+    wd, wu = torch.randn((r, d), generator=g, device=DEV).bfloat16(), torch.randn((n, r), generator=g, device=DEV).bfloat16()
+    z, _ = B.lr_linear_fwd(x, wd, wu, B.LR_ACT_IDENTITY)
+    outs = [torch.empty((T, d), dtype=torch.bfloat16, device=DEV), torch.empty((r, d), device=DEV), torch.empty((n, r), device=DEV)]
+
+    def call(ws, size):
+        return B.lib().lr_linear_bwd(x.data_ptr(), wide, wd.data_ptr(), wu.data_ptr(), z.data_ptr(), dy.data_ptr(), wide,
+                                     outs[0].data_ptr(), d, outs[1].data_ptr(), outs[2].data_ptr(), T, d, r, n, B.LR_ACT_IDENTITY,
+                                     B.LR_BF16, B.LR_F32, 0, ws, size, _stream())
+
+    query = B.lr_linear_workspace_bytes(T, d, r, n, B.LR_BF16, 1)
+    ws = torch.empty(query, dtype=torch.uint8, device=DEV)
+    assert call(ws.data_ptr(), query) == -3
+    got = _run(call, outs, query + T * (n + r) * 2 + 4096)
+    dense = B.lr_linear_bwd(x.contiguous(), wd, wu, z, dy.contiguous(), B.LR_ACT_IDENTITY)
+    assert torch.equal(got[0], dense[0])
+    dz = (dy.double() @ wu.double()).bfloat16().double()
+    for a, b, mag in ((got[1], dense[1], dz.abs().t() @ x.double().abs()), (got[2], dense[2], dy.double().abs().t() @ z.double().abs())):
+        assert ((a.double() - b.double()).abs() <= 2 * T * 2.0 ** -24 * 1.01 * mag).all()
