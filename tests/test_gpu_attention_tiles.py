@@ -3,6 +3,7 @@ import pytest
 import torch
 
 import bf16_model as M
+import launches
 import synth_inputs as si
 from oracle import gqa_oracle as gqa
 from parity import check
@@ -15,8 +16,8 @@ HD = 128
 
 @pytest.mark.parametrize("S", [1, 31, 32, 33, 63, 64, 65, 97, 127, 128, 129, 191, 193, 255, 256, 257, 321, 385, 513])
 def test_attention_fwd_edges(S):
-    """Blocks of 256 queries (256 heads in a launch) and of 128 (16 heads at a time) give the same bits, and those of one
-    batch element lie within the roundings of p and o of the result in 64 bits.  bf16 keeps 8 significant bits, so
+    """Query blocks in pairs (256 heads in a launch, from 129 tokens on) and a workgroup each (16 heads at a time) give the same bits, and
+    those of one batch element lie within the roundings of p and o of the result in 64 bits.  bf16 keeps 8 significant bits, so
     rounding to nearest is off by up to 2^-8 of a value: 2^-8 sum p |v| for the probabilities and 2^-8 |o| <= 2^-8 sum p |v| for
     the output, and 2 % of that for the fp32 arithmetic between."""
     Bn, H, Hkv = 16, 16, 4
@@ -80,3 +81,35 @@ def test_attention_bwd_long(S):
     bud = M.attention_budget(Q, K, V, DO, 1, S, H, Hkv, HD, o_ref, *refs)
     for n, a, r in zip(("dq", "dk", "dv"), got, refs):
         check(n, a, r, dt, bud[n])
+
+
+@pytest.mark.parametrize("S", [16, 64, 200, 320, 1100, 2047])
+def test_attention_fwd_blocks_are_of_128_queries(S):
+    """... however many heads a launch has: wider ones leave wavefronts of short sequences idle and wait for their longest."""
+    Bn, H = (24, 16) if S <= 320 else (4, 32)
+    print(f"attention forward launch S={S}", flush=True)
+    q = torch.zeros((Bn * S, H * HD), dtype=torch.bfloat16, device=DEV)
+    blocks = (S + 127) // 128
+    per_wg = 1 if blocks * Bn * H <= 256 else 2
+    assert launches.of(lambda: B.lr_attention_fwd(q, q, q, Bn, S, H, HD)) == [((blocks + per_wg - 1) // per_wg * Bn * H, 256, 65536)]
+
+
+@pytest.mark.parametrize("S", [2049, 2111, 2304])
+def test_attention_fwd_long(S):
+    """Sequences of more blocks than test_attention_fwd_edges has, paired (40 heads) and not (4), on one head against 64 bits; bounds
+    as there."""
+    Bn, H = 5, 8
+    print(f"attention forward S={S}", flush=True)
+    g = torch.Generator().manual_seed(S)
+    q, k, v = (torch.randn(Bn * S, H * HD, generator=g).bfloat16() for _ in range(3))
+    qd, kd, vd = q.to(DEV), k.to(DEV), v.to(DEV)
+    o, lse = B.lr_attention_fwd(qd, kd, vd, Bn, S, H, HD)
+    r = slice((Bn - 1) * S, Bn * S)
+    part = [t[r, 4 * HD:].contiguous() for t in (qd, kd, vd)]
+    o1, lse1 = B.lr_attention_fwd(*part, 1, S, 4, HD)
+    assert torch.equal(o[r, 4 * HD:], o1) and torch.equal(lse.view(Bn, H, S)[-1, 4:], lse1.view(4, S))
+    q64, k64, v64 = (t[:S, :HD].double() for t in (q, k, v))
+    s = (q64 @ k64.t() / HD ** 0.5).masked_fill(torch.ones(S, S, dtype=torch.bool).triu(1), -torch.inf)
+    p = s.softmax(-1)
+    assert ((o[:S, :HD].cpu().double() - p @ v64).abs() <= 2.0 ** -7 * 1.02 * (p @ v64.abs())).all()
+    assert (lse.view(Bn, H, S)[0, 0].cpu().double() - s.logsumexp(-1)).abs().max() < 1e-4
