@@ -952,8 +952,11 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(const uint16_t* __res
 // Backward, us, before -> now: 2 x 2047 tokens, 32 / 8 heads 345 -> 327; 2 x 3333, 16 / 4 heads 484 -> 439; 4 x 1501, 16 heads
 // 260 -> 247; 777, 32 / 8 heads 129.5 -> 125.8; below that it is slower (4 x 300, 8 heads 64 -> 67), and with the score gradient
 // stored as well, where the dQ product waits on memory, the whole backward gained nothing at 2048 tokens (628 / 628).
+// Paired key blocks share a CU's time with others, and there it takes longer sequences to pay (whole backward, this kernel against the
+// other: 8 x 779 tokens, 32 heads +3.3 %, 4 x 923, 32 / 8 heads +2.6, 6 x 1045, 32 / 8 heads -2.5, 8 x 1129, 32 heads -1.7;
+// a workgroup per block: 14 x 774, 1 head -6.3, 14 x 943, 2 heads -6.1).
 // ----------------------------------------------------------------------------------------------
-constexpr int LDKV_MIN_S = 768;
+constexpr int LDKV_MIN_S = 768, LDKV_MIN_S_PAIRED = 1024;
 constexpr int LDKV_NS = 4;                                 // ring of stages: two tiles in use, two on their way
 constexpr int LDKV_LDS = LDKV_NS * DKV_STAGE + KT * 4;     // (and a place for what nobody reads)
 constexpr int DKV_D = 8;        // LDS operands are read this many MFMAs ahead
@@ -1350,7 +1353,7 @@ hipError_t attention_gqa_bwd_bf16(const void* q, const void* k, const void* v, c
   const int64_t heads = (int64_t)H * B;
   if ((S + 127) / 128 * heads <= 256) dq_launch(std::integral_constant<int, 1>{}, false);
   else dq_launch(std::integral_constant<int, 2>{}, (S + 255) / 256 * heads > 256);
-  if (S >= LDKV_MIN_S)
+  if (S >= ((int)kv_grid.x == nkb ? LDKV_MIN_S : LDKV_MIN_S_PAIRED))
     hipLaunchKernelGGL(attn_bwd_dkv_long_kernel, kv_grid, dim3(256), LDKV_LDS, st, (const uint16_t*)q, (const uint16_t*)k,
                        (const uint16_t*)v, (const uint16_t*)dout, lse2, D, dk_w, dv_w, ld, ldkv, lddkv, grp, S, H, scale);
   else

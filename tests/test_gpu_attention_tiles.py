@@ -113,3 +113,38 @@ def test_attention_fwd_long(S):
     p = s.softmax(-1)
     assert ((o[:S, :HD].cpu().double() - p @ v64).abs() <= 2.0 ** -7 * 1.02 * (p @ v64.abs())).all()
     assert (lse.view(Bn, H, S)[0, 0].cpu().double() - s.logsumexp(-1)).abs().max() < 1e-4
+
+
+def _bwd_launches(S, n, H, Hkv):
+    """dQ and dK / dV of a backward over n sequences: (workgroups, threads, LDS) of both"""
+    q, k = (torch.zeros((n * S, h * HD), dtype=torch.bfloat16, device=DEV) for h in (H, Hkv))
+    lse = torch.zeros((n, H, S), device=DEV)
+    return launches.of(lambda: B.lr_attention_gqa_bwd(q, k, k, q, q, lse, n, S, H, Hkv, HD))[1:3]
+
+
+def _compare_parts(S, n, parts, H, Hkv):
+    g = torch.Generator().manual_seed(S)
+    q, do = (torch.randn(n * S, H * HD, generator=g).bfloat16().to(DEV) for _ in range(2))
+    k, v = (torch.randn(n * S, Hkv * HD, generator=g).bfloat16().to(DEV) for _ in range(2))
+    o, lse = B.lr_attention_gqa_fwd(q, k, v, n, S, H, Hkv, HD)
+    full = B.lr_attention_gqa_bwd(q, k, v, o, do, lse, n, S, H, Hkv, HD)
+    for m in parts:
+        r, last = slice((n - m) * S, n * S), slice(n - m, n)     # (the last ones: their blocks are the launch's last)
+        part = B.lr_attention_gqa_bwd(q[r], k[r], v[r], o[r], do[r], lse[last].contiguous(), m, S, H, Hkv, HD)
+        torch.cuda.synchronize()
+        for a, b in zip(part, full):
+            assert torch.equal(a, b[r])
+
+
+@pytest.mark.parametrize("S", [769, 897, 1023, 1025, 1087, 1153, 1283])
+def test_attention_bwd_paired_key_blocks(S):
+    """Launches whose workgroups take two key blocks, the second one with the ring that the first has used: odd and even numbers of
+    blocks (an odd one has a middle block without a mirror), from 1024 tokens on with the pipelined kernel.  The bits of one
+    sequence, a workgroup per block, which test_attention_bwd_long checks against the oracle."""
+    H, Hkv, n = 4, 2, 11
+    print(f"attention backward, paired key blocks S={S}", flush=True)
+    blocks, long_lds = (S + 127) // 128, 4 * (2 * 64 * 256 + 512) + 256
+    many, one = _bwd_launches(S, n, H, Hkv)[1], _bwd_launches(S, 1, H, Hkv)[1]
+    assert many[0] == (blocks + 1) // 2 * H * n and one[0] == blocks * H
+    assert (many[2] == long_lds) == (S >= 1024) and one[2] == long_lds
+    _compare_parts(S, n, (1,), H, Hkv)
