@@ -45,8 +45,9 @@ def test_attention_fwd_edges(S):
 
 @pytest.mark.parametrize("S", [65, 129, 255, 257, 513])
 def test_attention_bwd_does_not_depend_on_the_launch(S):
-    """Query blocks of 128 with a workgroup each, of 256 with a workgroup each, and of 256 in pairs: 1, 26 and 64 batch elements
-    of 4 heads (a sequence length that keeps no score gradient)."""
+    """1, 26 and 64 batch elements of 4 heads (a sequence length that keeps no score gradient).  At 257 tokens that is query blocks of
+    128 with a workgroup each, of 256 with a workgroup each, and of 256 in pairs; every form of every length:
+    test_attention_bwd_forms."""
     H, Hkv, Bn = 4, 2, 64
     print(f"attention backward launches S={S}", flush=True)
     g = torch.Generator().manual_seed(S)
@@ -134,6 +135,20 @@ def _compare_parts(S, n, parts, H, Hkv):
         torch.cuda.synchronize()
         for a, b in zip(part, full):
             assert torch.equal(a, b[r])
+
+
+@pytest.mark.parametrize("S,batches", [(65, (1, 66)), (129, (1, 40, 66)), (255, (1, 40, 66)), (257, (1, 26, 40)), (513, (1, 16, 30))])
+def test_attention_bwd_forms(S, batches):
+    """dQ on blocks of 128 queries, on blocks of 256 and on pairs
+    of those: batches of 4 heads that take one form each, the same bits from all."""
+    H, Hkv = 4, 2
+    print(f"attention backward forms S={S} B={batches}", flush=True)
+    n128, n256 = (S + 127) // 128, (S + 255) // 256
+    grids = [n128 * H * batches[0], *([n256 * H * batches[1]] if len(batches) == 3 else []), (n256 + 1) // 2 * H * batches[-1]]
+    assert [_bwd_launches(S, n, H, Hkv)[0][0] for n in batches] == grids
+    assert n128 * H * batches[0] <= 256 < n256 * H * batches[-1]
+    assert len(batches) == 2 or n256 * H * batches[1] <= 256 < n128 * H * batches[1]
+    _compare_parts(S, batches[-1], batches[:-1], H, Hkv)
 
 
 @pytest.mark.parametrize("S", [769, 897, 1023, 1025, 1087, 1153, 1283])
