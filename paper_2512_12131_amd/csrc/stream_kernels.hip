@@ -181,7 +181,7 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const void* x, int64_t
 // slices for every width spent 3 us per row, also on 256 columns), and AHEAD keeps the next row on its way in a second set
 // of registers.  Measured, launch and sum of the partials included, before and after: 49.6 -> 16.2 us (8192 x 512),
 // 101.5 -> 45.7 us (32768 x 1024), 59.7 -> 43.9 us (16384 x 2048: 6.1 TB/s), 58.5 -> 43.9 us (8192 x 3072), 61.2 ->
-// 56.6 us (8192 x 4096).
+// 56.6 us (8192 x 4096).  A row that is not there is left out, not worked on as zeros (one row of 2176 columns 7.2 -> 5.4 us).
 template <int NIT, bool AHEAD>
 __global__ __launch_bounds__(256, AHEAD ? 1 : 2) void rmsnorm_bwd_row_kernel(
     const uint16_t* x, int64_t ldx, const uint16_t* gamma, const float* stat, float eps, const uint16_t* dxh, int64_t lddxh,
@@ -213,7 +213,7 @@ __global__ __launch_bounds__(256, AHEAD ? 1 : 2) void rmsnorm_bwd_row_kernel(
   }
   __syncthreads();
   auto u4 = [](const u32x4_t& t) { return make_uint4(t.x, t.y, t.z, t.w); };
-  // A row past the last one has empty resources: it loads zeros, adds nothing and stores nothing.
+  // A row past the last one, asked for ahead, has empty resources; nobody works on it.
   struct Row { u32x4_t x[NIT], d[NIT], r[NIT]; float ss; };
   auto row_at = [&](int r) { return ((int64_t)r * gridDim.x + blockIdx.x) * 4 + wave; };
   auto fetch = [&](int r, Row& q) {
@@ -274,6 +274,7 @@ __global__ __launch_bounds__(256, AHEAD ? 1 : 2) void rmsnorm_bwd_row_kernel(
       fetch(r + 1, qb);
       __builtin_amdgcn_sched_barrier(0);
       work(r, qa);
+      if (row_at(r + 1) >= T) break;
       fetch(r + 2, qa);
       __builtin_amdgcn_sched_barrier(0);
       work(r + 1, qb);
@@ -949,16 +950,16 @@ hipError_t k_rmsnorm_bwd(const void* x, int64_t ldx, const void* gamma, const fl
       return hipGetLastError();
     };
     // The narrowest kernel that holds the row.  The widest with both sets of rows takes 300 registers, one workgroup per CU:
-    // measured at d = 4096, 56.6 against 61.2 us with 128 workgroups, 92.3 against 91.4 with 256 and 196 against 194 with
-    // more, so there it keeps to one set.
+    // measured at d = 4096 against one set, 55.9 / 61.8 us with 128 workgroups, 50.2 / 52.2 with 19, 46.4 / 46.0 with 10, 47.0 / 45.3
+    // with one, 92.3 / 91.4 with 256 and 196 / 194 with more, so at both ends it keeps to one set.
     const std::true_type ahead;
     if (d <= 512) return launch(std::integral_constant<int, 1>{}, ahead);
     if (d <= 1024) return launch(std::integral_constant<int, 2>{}, ahead);
     if (d <= 1536) return launch(std::integral_constant<int, 3>{}, ahead);
     if (d <= 2048) return launch(std::integral_constant<int, 4>{}, ahead);
     if (d <= 3072) return launch(std::integral_constant<int, 6>{}, ahead);
-    return grid < 256 ? launch(std::integral_constant<int, 8>{}, ahead)
-                      : launch(std::integral_constant<int, 8>{}, std::false_type{});
+    return grid >= 16 && grid < 256 ? launch(std::integral_constant<int, 8>{}, ahead)
+                                    : launch(std::integral_constant<int, 8>{}, std::false_type{});
   }
   DISPATCH_DT(dt, rmsnorm_bwd_kernel, dim3(k_rmsnorm_bwd_parts(T)), dim3(256), st, x, ldx, gamma, stat, eps, dxhat,
               lddxh, dres, lddres, dx, lddx, dgamma_part, T, d);

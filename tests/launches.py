@@ -24,9 +24,7 @@ def _hip():
     return lib
 
 
-def of(call):
-    """[(workgroups, threads of a workgroup, bytes of dynamic LDS)] in the order of the graph's nodes.  `call` allocates nothing that the
-    caller has not seen before (it is captured, not run)."""
+def _kernels(call):
     hip = _hip()
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph(keep_graph=True)
@@ -36,10 +34,18 @@ def of(call):
     assert hip.hipGraphGetNodes(raw, None, C.byref(count)) == 0
     nodes = (C.c_void_p * count.value)()
     assert hip.hipGraphGetNodes(raw, nodes, C.byref(count)) == 0
-    out = []
     for node in nodes:
         kind, p = C.c_int(-1), _KernelParams()
         assert hip.hipGraphNodeGetType(node, C.byref(kind)) == 0 and kind.value == 0, "not a kernel launch"
         assert hip.hipGraphKernelNodeGetParams(node, C.byref(p)) == 0
-        out.append((p.grid.x * p.grid.y * p.grid.z, p.block.x * p.block.y * p.block.z, p.lds))
-    return out
+        yield p
+
+
+def of(call):
+    """[(workgroups, threads of a workgroup, bytes of dynamic LDS)] in the order of the graph's nodes (captured, not run)."""
+    return [(p.grid.x * p.grid.y * p.grid.z, p.block.x * p.block.y * p.block.z, p.lds) for p in _kernels(call)]
+
+
+def functions(call):
+    """The kernels themselves, as numbers that are equal where two launches run the same one."""
+    return [p.func for p in _kernels(call)]

@@ -3,6 +3,7 @@ import numpy as np
 import pytest
 import torch
 
+import launches
 import synth_inputs as si
 from oracle import lowrank_oracle as orc
 from parity import check
@@ -102,3 +103,29 @@ def test_rms_bwd_rows_do_not_depend_on_their_number(T):
     whole = part.sum(0, dtype=torch.float64)
     # fp32 partials of at most 16 rows per wavefront, each term below max|dxh * n|: a sum of T terms in another order
     assert (whole - halves[0] - halves[1]).abs().max() <= 2 * 20 * 2.0 ** -24 * T * 25
+
+
+def test_rms_bwd_wide_rows_one_at_a_time_where_there_are_few():
+    """More than 3072 columns: the next row is fetched ahead between 16 and 255 workgroups of 64 rows, and rows have the same bits on
+    either side of both ends."""
+    eps, d = 1e-5, 3080
+    g = torch.Generator(device=DEV).manual_seed(6)
+    x, dxh, dres = (torch.randn((961, d), generator=g, device=DEV).bfloat16() for _ in range(3))
+    gamma = torch.randn((d,), generator=g, device=DEV).bfloat16()
+    stat = B.lr_rms_stat(x)
+
+    def kernel(T):
+        big = torch.zeros((T, d), dtype=torch.bfloat16, device=DEV)
+        return launches.functions(lambda: B.lr_rmsnorm_bwd(big, gamma, torch.ones(T, device=DEV), eps, big, big))[-1]
+
+    kinds = {T: kernel(T) for T in (1, 960, 961, 16320, 16321)}
+    assert kinds[1] == kinds[960] == kinds[16321] != kinds[961] == kinds[16320]
+    dx, part = B.lr_rmsnorm_bwd(x, gamma, stat, eps, dxh, dres)
+    few, fpart = B.lr_rmsnorm_bwd(x[:960], gamma, stat[:960], eps, dxh[:960], dres[:960])
+    assert torch.equal(dx[:960].view(torch.int16), few.view(torch.int16))
+    last, lpart = B.lr_rmsnorm_bwd(x[960:], gamma, stat[960:], eps, dxh[960:], dres[960:])
+    assert torch.equal(dx[960:].view(torch.int16), last.view(torch.int16))
+    # the gamma gradient: fp32 partials of the same terms in another order
+    whole, parts = part.sum(0, dtype=torch.float64), fpart.sum(0, dtype=torch.float64) + lpart.sum(0, dtype=torch.float64)
+    n = x.double() * torch.rsqrt(stat.double() / d + eps)[:, None]
+    assert ((whole - parts).abs() <= 2 * 961 * 2.0 ** -24 * (n * dxh.double()).abs().sum(0)).all()
