@@ -132,12 +132,15 @@ hipError_t launch_rows16(const GemmOp& op, hipStream_t st) {
 
 }  // namespace
 
-// Up to two workgroups per CU (what fits): beyond, the 32 x 32 tile's fewer operand bytes decide (200 tokens,
-// 4096 -> 1024 -> 4096: 17.6 us against 23.6 on 16 x 16 pieces; 400 tokens, 512 -> 128 -> 512: 6.8 against 11.3).
+// A CU holds one workgroup (two rings would be all of its LDS), so from 257 pieces on there is a second round, which only long
+// k makes up for.  One product, replayed from a graph, 16 x 16 pieces / 32 x 32 tiles (us): 256 pieces, k = 64 3.2 / 3.4, 1024
+// 3.5 / 4.8, 4096 5.1 / 9.9; 384 and 512 pieces, k = 64 4.7 / 3.5, 1024 5.4 / 4.9, 2048 6.7 / 6.6, 4096 8.7 / 9.9.  With at most 32
+// rows two rounds are a weight of 4096 rows or more, where memory decides (8 x 8192 x 4096: 13.2 / 12.3).
 bool gemm_rows16_ok(const GemmOp& op) {
   const bool kind = op.epi.kind == EPI_STORE || (op.epi.kind == EPI_DOWN && !op.epi.stat_from_a);
+  const int64_t pieces = (int64_t)((op.M + 15) / 16) * ((op.N + 15) / 16) * op.batch;
   return kind && !op.transA && !op.transB && op.splitk == 1 && op.K % 8 == 0 && op.N % 8 == 0 &&
-         (int64_t)((op.M + 15) / 16) * ((op.N + 15) / 16) * op.batch <= 512;
+         (pieces <= 256 || (pieces <= 512 && op.K >= 3072 && op.M > 32));
 }
 hipError_t gemm_rows16(const GemmOp& op, hipStream_t st) {
   return op.epi.kind == EPI_STORE ? launch_rows16<EPI_STORE>(op, st) : launch_rows16<EPI_DOWN>(op, st);

@@ -3,6 +3,7 @@ bits that the larger tiles, with their 32 x 32 x 16 instruction, give it."""
 import pytest
 import torch
 
+import launches
 from paper_2512_12131_amd import binding as B
 
 pytestmark = pytest.mark.gpu
@@ -40,3 +41,21 @@ def test_rows_of_a_group(norm):
     for t in (1, 16, 33, 64):
         z1, _, y1 = B.lr_group_fwd(x[:t].contiguous(), gamma, 1e-5, norm, wd, wu)
         assert torch.equal(z1, z[:t]) and torch.equal(y1, y[:, :t])
+
+
+@pytest.mark.parametrize("t,d_in,r,d_out,pieces", [
+    (16, 4096, 1024, 4096, (True, True)),        # 64 and 256 pieces
+    (417, 120, 232, 184, (False, False)),        # 405 and 324 of short k
+    (141, 208, 512, 456, (False, False)),        # 288 and 261
+    (64, 4096, 2048, 1024, (True, True)),        # 512 of long k, 256
+    (64, 2048, 2048, 512, (False, True)),        # 512 of 2048 k, 128
+    (32, 4096, 4096, 2048, (False, True))])      # 512, but 32 rows of a weight of 4096 rows; 256
+def test_second_round_only_for_long_k(t, d_in, r, d_out, pieces):
+    """A CU holds one workgroup of 16 x 16 pieces: more than 256 of them take a second round, which long k alone makes up for."""
+    x, wd, wu = (torch.zeros(s, dtype=torch.bfloat16, device=DEV) for s in ((t, d_in), (r, d_in), (d_out, r)))
+    z, y = (torch.zeros(s, dtype=torch.bfloat16, device=DEV) for s in ((t, r), (t, d_out)))
+    assert B.lr_gemm_tile(t, r, d_in, 1, 0, 1) == B.lr_gemm_tile(t, d_out, r, 1, 0, 0) == (32, 32)
+    B.lr_linear_fwd_static(x, wd, wu, z, y)      # (its scratch is looked up outside a capture)
+    grids = [g for g, _, _ in launches.of(lambda: B.lr_linear_fwd_static(x, wd, wu, z, y))]
+    side = [16 if small else 32 for small in pieces]
+    assert grids == [-(-t // s) * -(-n // s) for s, n in zip(side, (r, d_out))]
