@@ -405,7 +405,8 @@ hipError_t dispatch(const GemmOp& op, hipStream_t st) {
 // and start-up, set by hand.  Against 1648 launches of the kernels as they are (888 forward products, M from 16; 400 data
 // gradients; 360 weight gradients), the estimates of tiles within 1.5 times the best are off by 8-16 % rms, R32's by 17-19 %
 // (10-15 % too fast on average).  Taking the estimated best loses 1.7 % (forward) and 1.9 % (data gradients) in the geometric mean
-// against the measured best; the 256-row tiles alone take 2.13 times as long as that over the forward products.  What the
+// against the measured best; the 256-row tiles alone take 2.13 times as long as that over the forward products.  Forward products on R32 of up to
+// 256 pieces of 16 x 16 run as those (gemm_rows16.hip): up to twice as fast with long k, which the estimate does not know.  What the
 // lines amount to, with both sides measured (us):
 //   a handful of rows: one chain of k per CU        16 x 1024 x 4096:   T256 67.6   R64    15.0   R32 9.4
 //   few tiles, the loads' latency decides          777 x 1024 x 4096:   T256 68.0   R64    16.1   R32 25.9
@@ -449,7 +450,7 @@ float tile_time(int tile, int M, int N, int nk, int members, float e, float slic
   if (u > 0.f) t += c.f + (c.g * u + c.h) * e + (float)nk * slice * (c.s0 + c.s1 * u);
   return t;
 }
-// From the end of one launch to the start of the next.
+// From the end of one launch to the start of the next (see gemm_bf16_join_tile).
 constexpr float kLaunchGap = 1.5f;
 // The smaller tiles have to be estimated 7.5 % faster than T256 before they are taken: the estimate's own error.
 constexpr float kRingMargin = 1.075f;
@@ -653,7 +654,15 @@ hipError_t gemm_bf16(const GemmOp& op, hipStream_t st) {
 
 int gemm_bf16_join_tile(const GemmOp* ops, int n) {
   // Apart, each on its best tile, a launch each; or together on 32 x 32 or 64 x 64 tiles, the workgroups of all
-  // sharing the chip: as long as the longest of them or as all of their work, whichever is more.
+  // sharing the chip: as long as the longest workgroup or, where all of their work is more, as that and the longest one (they are not
+  // alike: what a slot still holds when the others are empty).
+  // Against 3328 backward calls of a layer or group (1 .. 6000 tokens, weights 16 .. 4096 wide), each measured apart and joined on either
+  // tile: the choice loses 0.75 % to the best of the three in the geometric mean and saves 29.7 % of the call against apart; 17
+  // calls are more than 3 % slower than apart, the worst 12 %.  (With half of the longest 0.76 %, 60 calls, 20 %; with a gap between
+  // launches of 0 or 3 us instead of 1.5 1.15 and 0.78 %, 6 and 58 calls.)  Some of them, us, apart / 32 x 32 / 64 x 64 tiles:
+  //   layer 12 tokens 2872 -> 400 -> 1760: 20.0 / 21.8 / 18.5        439 tokens 3000 -> 288 -> 864: 22.6 / 29.7 / 21.5
+  //         1059 tokens 64 -> 48 -> 288:   19.0 / 10.7 / 12.4        3380 tokens 2088 -> 72 -> 72:  30.1 / 65.7 / 41.1
+  //   group 2 x 82 tokens 240 -> 344 -> 1480: 19.8 / 17.9 / 18.2     1 x 557 tokens 392 -> 184 -> 504: 28.4 / 24.9 / 25.7
   if (n < 2 || n > JOINT_MAX || g_timer.on) return 0;
   float apart = 0.f, joint[2] = {0.f, 0.f}, longest[2] = {0.f, 0.f};
   const int tiles[2] = {GEMM_R32, GEMM_R64};
@@ -675,7 +684,7 @@ int gemm_bf16_join_tile(const GemmOp* ops, int n) {
     }
   }
   for (int t = 0; t < 2; t++)
-    joint[t] = kTileCost[tiles[t]].a + kLaunchGap + (joint[t] > longest[t] ? joint[t] + 0.5f * longest[t] : longest[t]);
+    joint[t] = kTileCost[tiles[t]].a + kLaunchGap + longest[t] + (joint[t] > longest[t] ? joint[t] : 0.f);
   const int t = joint[0] <= joint[1] ? 0 : 1;
   return joint[t] < apart ? tiles[t] : 0;
 }

@@ -3,6 +3,7 @@ written, the weight gradients take their own launches and a finishing pass: ever
 import pytest
 import torch
 
+import launches
 from paper_2512_12131_amd import binding as B
 
 pytestmark = pytest.mark.gpu
@@ -127,3 +128,17 @@ def test_gathered_gradients(G, T, d_in, r, d_out, grad_dt):
         assert ((dwu[i].double().cpu() - ref).abs() <= bound).all()
     if grad_dt == B.LR_F32:   # added to what is there: the same sum and one more rounding
         assert torch.equal(awd, dwd + base[0]) and torch.equal(awu, dwu + base[1])
+
+
+BF, F32 = torch.bfloat16, torch.float32
+
+
+@pytest.mark.parametrize("T,d_in,r,d_out,dt,count", [
+    (16, 1024, 256, 1024, BF, 2), (33, 128, 40, 96, BF, 2), (513, 264, 72, 520, BF, 2), (1031, 1024, 256, 768, BF, 2),   # dz, then the rest
+    (2050, 512, 128, 512, BF, 3),                                                             # ... and a finishing pass
+    (1693, 2208, 16, 88, BF, 5), (3380, 2088, 72, 72, BF, 5),                                 # apart: faster so
+    (33, 128, 40, 96, F32, 2), (512, 256, 64, 256, F32, 2), (513, 264, 72, 520, F32, 2),
+    (16, 1024, 256, 1024, F32, 4), (1031, 1024, 256, 768, F32, 4)])                           # more than 512 tiles
+def test_launches_of_a_layer_backward(T, d_in, r, d_out, dt, count):
+    x, wd, wu, dy, z = (torch.zeros(s, dtype=dt, device=DEV) for s in ((T, d_in), (r, d_in), (d_out, r), (T, d_out), (T, r)))
+    assert len(launches.of(lambda: B.lr_linear_bwd(x, wd, wu, z, dy))) == count
