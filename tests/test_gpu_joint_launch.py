@@ -1,5 +1,6 @@
-"""The three products at the end of a layer's backward run in one launch where they are small.  Added to zeros instead of
-written, the weight gradients take their own launches and a finishing pass: every output has to have the same bits."""
+"""The three products at the end of a layer's backward run in one launch where they are small.  While launches are being timed each
+has its own, and added to zeros instead of written the weight gradients go through a finishing pass: every output has to have the
+same bits."""
 import pytest
 import torch
 
@@ -19,7 +20,12 @@ def _both(T, d_in, r, d_out, dt, act, grad_dt):
     zeros = tuple(torch.zeros(w.shape, dtype=gt, device=DEV) for w in (wd, wu))
     added = B.lr_linear_bwd(x, wd, wu, z, dy, act, grads=zeros, grad_dt=grad_dt)
     torch.cuda.synchronize()
-    return (x, wd, wu, dy, z), plain, added
+    B.lr_launch_timer_begin(16)
+    apart = B.lr_linear_bwd(x, wd, wu, z, dy, act, grad_dt=grad_dt)
+    torch.cuda.synchronize()
+    records = B.lr_launch_timer_end()
+    assert dt == torch.float32 or len(records) == 4      # (the timer sees, and keeps apart, bf16 products)
+    return (x, wd, wu, dy, z), plain, added, apart
 
 
 @pytest.mark.parametrize("grad_dt", [B.LR_F32, B.LR_BF16])
@@ -28,9 +34,9 @@ def _both(T, d_in, r, d_out, dt, act, grad_dt):
                                             (513, 264, 72, 520), (1031, 1024, 256, 768), (2050, 512, 128, 512)])
 def test_bf16(T, d_in, r, d_out, act, grad_dt):
     print(f"joint bf16 T={T} {d_in}->{r}->{d_out} act={act}", flush=True)
-    _, plain, added = _both(T, d_in, r, d_out, torch.bfloat16, act, grad_dt)
-    for a, b in zip(plain, added):
-        assert torch.equal(a, b)
+    _, plain, added, apart = _both(T, d_in, r, d_out, torch.bfloat16, act, grad_dt)
+    for a, b, c in zip(plain, added, apart):
+        assert torch.equal(a, b) and torch.equal(a, c)
 
 
 @pytest.mark.parametrize("act", [B.LR_ACT_SILU, B.LR_ACT_IDENTITY])
@@ -40,7 +46,7 @@ def test_f32(T, d_in, r, d_out, act):
     """... and in 32 bits against 64: each gradient is one or two chained sums, and n terms added in 32 bits are off by at most
     n 2^-24 times the sum of their magnitudes; the tested lengths stay below 2^11, in practice far below the bound."""
     print(f"joint f32 T={T} {d_in}->{r}->{d_out} act={act}", flush=True)
-    (x, wd, wu, dy, z), plain, added = _both(T, d_in, r, d_out, torch.float32, act, B.LR_F32)
+    (x, wd, wu, dy, z), plain, added, _ = _both(T, d_in, r, d_out, torch.float32, act, B.LR_F32)
     for a, b in zip(plain, added):
         assert torch.equal(a, b)
     x, wd, wu, dy, z = (t.double().cpu() for t in (x, wd, wu, dy, z))
@@ -128,6 +134,50 @@ def test_gathered_gradients(G, T, d_in, r, d_out, grad_dt):
         assert ((dwu[i].double().cpu() - ref).abs() <= bound).all()
     if grad_dt == B.LR_F32:   # added to what is there: the same sum and one more rounding
         assert torch.equal(awd, dwd + base[0]) and torch.equal(awu, dwu + base[1])
+
+
+@pytest.mark.parametrize("grad_dt", [B.LR_F32, B.LR_BF16])
+@pytest.mark.parametrize("G,T,d_in,r,d_out", [(1, 1024, 64, 32, 72), (1, 1031, 264, 40, 520), (1, 2113, 8, 8, 8), (3, 1700, 256, 64, 256),
+                                              (2, 5120, 256, 64, 616), (14, 1100, 64, 16, 72), (2, 8192, 1024, 512, 1024)])
+def test_gathered_gradients_against_64_bits(G, T, d_in, r, d_out, grad_dt):
+    """All gradients, written and added.  W_up picks a column of dy for each of dz, which is then exact, so both gradients are chained
+    sums of exact products: off by at most T 2^-24 of the sum of their magnitudes, one more 32-bit rounding where they are added to
+    what is there, and a bf16 rounding."""
+    print(f"gathered, 64 bits G={G} T={T} {d_in}->{r}->{d_out}", flush=True)
+    g = torch.Generator().manual_seed(T + 1)
+    x, wd, dy = (torch.randn(s, generator=g).bfloat16().to(DEV) for s in ((T, d_in), (G * r, d_in), (G, T, d_out)))
+    pick = torch.stack([torch.randperm(d_out, generator=g)[:r] for _ in range(G)])
+    wu = torch.zeros((G, d_out, r), dtype=torch.bfloat16)
+    wu[torch.arange(G)[:, None], pick, torch.arange(r)[None, :]] = 1
+    wu = wu.to(DEV)
+    gt = torch.float32 if grad_dt == B.LR_F32 else torch.bfloat16
+    base = [torch.randn(s, generator=g).to(gt).to(DEV) for s in ((G * r, d_in), (G, d_out, r))]
+    if G == 1:
+        z, _ = B.lr_linear_fwd(x, wd, wu[0], B.LR_ACT_IDENTITY)
+        run = lambda grads: B.lr_linear_bwd(x, wd, wu[0], z, dy[0], B.LR_ACT_IDENTITY, grads=grads, grad_dt=grad_dt)[1:]
+        got = [run(None), run((base[0].clone(), base[1][0].clone()))]
+        got = [(down, up[None]) for down, up in got]
+    else:
+        gm = torch.ones(d_in, device=DEV).bfloat16()
+        z, stat, _ = B.lr_group_fwd(x, gm, 1e-5, B.LR_NORM_NONE, wd, wu, B.LR_ACT_IDENTITY)
+        run = lambda grads: B.lr_group_bwd(x, gm, 1e-5, B.LR_NORM_NONE, wd, wu, z, stat, dy, B.LR_ACT_IDENTITY, grads=grads,
+                                           grad_dt=grad_dt)[2:]
+        got = [run(None), run((torch.zeros(d_in, dtype=gt, device=DEV), base[0].clone(), base[1].clone()))]
+    for i in range(G):
+        dz = dy[i][:, pick[i].to(DEV)]
+        rows = slice(i * r, (i + 1) * r)
+        for a, b, outs in ((dz, x, [(down[rows], add) for (down, _), add in zip(got, (None, base[0][rows]))]),
+                           (dy[i], z[:, rows], [(up[i], add) for (_, up), add in zip(got, (None, base[1][i]))])):
+            a, b = a.double(), b.double()
+            ref, mag = a.t() @ b, a.abs().t() @ b.abs()
+            for out, add in outs:
+                want, bound = ref, mag * (T * 2.0 ** -24)
+                if add is not None:
+                    want = ref + add.double()
+                    bound = bound + (want.abs() + bound) * 2.0 ** -24
+                if grad_dt == B.LR_BF16:
+                    bound = bound + (want.abs() + bound) * 2.0 ** -8
+                assert ((out.double() - want).abs() <= bound).all()
 
 
 BF, F32 = torch.bfloat16, torch.float32

@@ -15,7 +15,8 @@ LANE_READ = re.compile(r"v_(?:readlane|readfirstlane)_b32 s(\d+),")
 
 
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
-@pytest.mark.parametrize("src", ["gemm_ring32.hip", "gemm_ring64.hip", "gemm_ring64x128.hip", "gemm_ring128.hip", "attention.hip"])
+@pytest.mark.parametrize("src", ["gemm_ring32.hip", "gemm_ring64.hip", "gemm_ring64x128.hip", "gemm_ring128.hip", "gemm_joint.hip",
+                                 "gemm_rows16.hip", "attention.hip"])
 def test_descriptors_of_inline_loads_are_settled(src, tmp_path):
     out = tmp_path / "k.s"
     subprocess.run(["hipcc", *bld.FLAGS, "-S", "--offload-device-only", os.path.join(bld.CSRC, src), "-o", str(out)], check=True,
