@@ -1,6 +1,6 @@
 // Causal multi-head attention, head_dim 128, bf16 in / fp32 softmax, for gfx950.
 //
-// Forward (one workgroup = 4 wavefronts x 32 queries of one (batch, head), for one query block and
+// Forward (one workgroup = 4 or 8 wavefronts x 32 queries of one (batch, head), for one query block and
 // its causal mirror; K/V stream through LDS in 64-key tiles, double buffered):
 //   S^T = K Q^T      MFMA, A = K rows from LDS, B = Q rows kept in registers for the whole kernel
 //   online softmax   per query = per lane column of the S^T accumulators (one exchange of the wavefront's halves)
@@ -282,23 +282,20 @@ __device__ __forceinline__ float half_sum(float x) {
 // tiles, the end) stay outside, which is what lets the compiler keep every tuple in place (246 registers, no copies).
 // Sustained, one tile at a time -> now (us): 4 x 4096 tokens, 32 heads 627 -> 555; 8 x 2048, 16 heads 175 -> 157;
 // 2 x 2047, 32 / 8 heads 89.9 -> 79; 777 tokens, 32 / 8 heads 23.5 -> 19.9; 4 x 4096, 4 heads 93.8 -> 78.
-// 4 wavefronts, not 8 that would fetch a key tile once for 256 queries: a block's wavefronts walk its keys together, so those of its
-// first half wait for those of the second, and the chip fills less evenly (us, 4 / 8, inputs warm: 128 x 64 tokens, 16 heads
-// 31.0 / 47.4, 16 x 1024 95 / 103, 7 x 1280, 32 heads 131 / 155, 8 x 2048, 16 heads 155 / 158, 4 x 4096, 32 heads 552 / 568; three sets
-// of inputs in turn: 2 x 2047, 32 / 8 heads 78.7 / 78.4, 4 x 4096 548 / 566; at best, 2 x 3333, 16 / 4 heads, 107 / 104).  A tile
-// past the last one is not asked for where that costs a scalar branch outside the main loop (128 x 64 tokens: 32.7 -> 31.0 us).
-constexpr int FWD_NW = 4;       // wavefronts of a workgroup
+// A tile past the last one is not asked for where that costs a scalar branch outside the main loop (128 x 64 tokens, 16 heads:
+// 32.7 -> 31.0).
 constexpr int FWD_D = 4;        // LDS operands are read this many MFMAs ahead (2, 4, 8: within 2 %)
 constexpr int FWD_BAR = 12;     // slot of the barrier: the last operand of the score product has been read
 // elements of the softmax done by the end of slot s: each bf16x8 operand is whole when its MFMAs come (slots 16, 20, 24, 28)
 constexpr int fwd_elems(int s) { return s < 0 ? 0 : s < 16 ? 5 * (s + 1) / 4 : s < 28 ? 5 + s : 32; }
 
-__global__ __launch_bounds__(FWD_NW * 64, 2) void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+template <int NW>
+__global__ __launch_bounds__(NW * 64, 2) void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                                                        const uint16_t* __restrict__ v, uint16_t* __restrict__ o,
                                                        float* __restrict__ lse, int64_t ld, int64_t ldkv, int grp, int S,
                                                        int H, float scale) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  constexpr int NW = FWD_NW, BQ = NW * 32, NL = 16 / NW; // queries per block, 1 KB loads per wavefront and tile
+  constexpr int BQ = NW * 32, NL = 16 / NW;             // queries per block, 1 KB loads per wavefront and tile
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nqb = (S + BQ - 1) / BQ;
   const WgCoord wg = wg_coord();
@@ -1240,17 +1237,31 @@ hipError_t attention_gqa_fwd_bf16(const void* q, const void* k, const void* v, v
   const int grp = H / Hkv;
   // 32-bit buffer offsets per (batch, head)
   if ((int64_t)S * ld * 2 >= (int64_t)0x7fffffff || (int64_t)S * ldkv * 2 >= (int64_t)0x7fffffff) return hipErrorNotSupported;
-  // one-time opt-in to more than 64 KB of dynamic LDS (thread-safe static initialisation)
-  static const hipError_t attr_err = set_lds(attn_fwd_kernel, FWD_LDS);
-  if (attr_err != hipSuccess) return attr_err;
-  const int nqb = (S + FWD_NW * 32 - 1) / (FWD_NW * 32);
-  // Each workgroup: one query block and its mirror; or one block, where each finds a CU free: the launch then takes
-  // as long as its longest block instead of a pair (2 x 256 tokens, 2 heads: 18.3 -> 12.3 us).  With two
-  // unpaired workgroups per CU the late blocks meet on some CUs (4 x 4096 tokens, 4 heads: 110 -> 135 us).
-  dim3 grid((int64_t)nqb * H * B <= 256 ? nqb : (nqb + 1) / 2, H, B);
-  hipLaunchKernelGGL(attn_fwd_kernel, grid, dim3(FWD_NW * 64), FWD_LDS, st, (const uint16_t*)q, (const uint16_t*)k,
-                     (const uint16_t*)v, (uint16_t*)o, lse, ld, ldkv, grp, S, H, 1.f / sqrtf((float)hd));
-  return hipGetLastError();
+  auto launch = [&](auto NWc) {
+    constexpr int NW = decltype(NWc)::value, BQ = NW * 32;
+    // one-time opt-in to more than 64 KB of dynamic LDS (thread-safe static initialisation)
+    static const hipError_t attr_err = set_lds(attn_fwd_kernel<NW>, FWD_LDS);
+    if (attr_err != hipSuccess) return attr_err;
+    const int nqb = (S + BQ - 1) / BQ;
+    // Each workgroup: one query block and its mirror; or one block, where each finds a CU free: the launch then takes
+    // as long as its longest block instead of a pair (2 x 256 tokens, 2 heads: 18.3 -> 12.3 us).  With two
+    // unpaired workgroups per CU the late blocks meet on some CUs (4 x 4096 tokens, 4 heads: 110 -> 135 us).
+    dim3 grid((int64_t)nqb * H * B <= 256 ? nqb : (nqb + 1) / 2, H, B);
+    hipLaunchKernelGGL(attn_fwd_kernel<NW>, grid, dim3(NW * 64), FWD_LDS, st, (const uint16_t*)q, (const uint16_t*)k,
+                       (const uint16_t*)v, (uint16_t*)o, lse, ld, ldkv, grp, S, H, 1.f / sqrtf((float)hd));
+    return hipGetLastError();
+  };
+  // 4 wavefronts: a block's wavefronts walk its keys together, so in one of 8 those of the first half wait for those of the second, and
+  // the chip fills less evenly (us, 4 / 8, inputs warm: 128 x 64 tokens, 16 heads 31.0 / 47.4, 16 x 1024 95 / 103, 7 x 1280, 32 heads
+  // 131 / 155, 8 x 2048, 16 heads 155 / 158, 4 x 4096, 32 heads 552 / 568).  8 where every CU gets one such pair of blocks and no more,
+  // which is as many wavefronts as two workgroups of 4 but fetches a key tile once for them, not twice: no faster warm (2 x 2047, 32 / 8
+  // heads 83.5 / 82.8, 4 x 2047, 16 heads 81.5 / 83.0), but with the inputs in memory (91.4 / 90.3, 94.0 / 88.9; 1 x 4096, 32
+  // heads 150.6 / 146.2; the first with its backward 431 / 424).  Fewer blocks than 8, or an odd one out: behind in both (us, cold,
+  // 1 x 1600, 64 / 8 heads 66.3 / 71.4, 1 x 2349, 32 / 8 heads 79.1 / 84.2).
+  const int wide = (S + 255) / 256;
+  const int64_t pairs = (int64_t)(wide / 2) * H * B;
+  return wide >= 8 && wide % 2 == 0 && pairs >= 224 && pairs <= 256 ? launch(std::integral_constant<int, 8>{})
+                                                                    : launch(std::integral_constant<int, 4>{});
 }
 
 // The backward runs in one of two forms.  With the score gradient kept (S a multiple of 8, and

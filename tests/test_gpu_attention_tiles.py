@@ -84,31 +84,34 @@ def test_attention_bwd_long(S):
         check(n, a, r, dt, bud[n])
 
 
-@pytest.mark.parametrize("S", [16, 64, 200, 320, 1100, 2047])
-def test_attention_fwd_blocks_are_of_128_queries(S):
-    """... however many heads a launch has: wider ones leave wavefronts of short sequences idle and wait for their longest."""
-    Bn, H = (24, 16) if S <= 320 else (4, 32)
+@pytest.mark.parametrize("S,Bn,H,threads", [(16, 24, 16, 256), (64, 24, 16, 256), (200, 24, 16, 256), (320, 24, 16, 256), (1024, 4, 32, 256),
+                                            (1793, 2, 32, 512), (2047, 2, 32, 512), (2047, 4, 32, 256), (2049, 2, 32, 256),
+                                            (3584, 1, 32, 512)])
+def test_attention_fwd_width_of_a_block(S, Bn, H, threads):
+    """Blocks of 128 queries, and of 256 where a launch is one pair of those for each CU, from eight blocks on: elsewhere wide
+    blocks leave wavefronts waiting."""
     print(f"attention forward launch S={S}", flush=True)
     q = torch.zeros((Bn * S, H * HD), dtype=torch.bfloat16, device=DEV)
-    blocks = (S + 127) // 128
+    blocks = -(-S // (threads // 2))
     per_wg = 1 if blocks * Bn * H <= 256 else 2
-    assert launches.of(lambda: B.lr_attention_fwd(q, q, q, Bn, S, H, HD)) == [((blocks + per_wg - 1) // per_wg * Bn * H, 256, 65536)]
+    assert launches.of(lambda: B.lr_attention_fwd(q, q, q, Bn, S, H, HD)) == [(-(-blocks // per_wg) * Bn * H, threads, 65536)]
 
 
-@pytest.mark.parametrize("S", [2049, 2111, 2304])
+@pytest.mark.parametrize("S", [1793, 1825, 1983, 2015, 2047, 2048, 2049, 2111, 2304])
 def test_attention_fwd_long(S):
-    """Sequences of more blocks than test_attention_fwd_edges has, paired (40 heads) and not (4), on one head against 64 bits; bounds
-    as there."""
-    Bn, H = 5, 8
+    """Sequences of more blocks than test_attention_fwd_edges has: blocks of 256 queries up to 2048 tokens, pairs of blocks of 128 beyond
+    (64 heads), and a workgroup for each block of 128 (4 heads); on one head against 64 bits, bounds as there."""
+    Bn, H = 8, 8
     print(f"attention forward S={S}", flush=True)
     g = torch.Generator().manual_seed(S)
     q, k, v = (torch.randn(Bn * S, H * HD, generator=g).bfloat16() for _ in range(3))
     qd, kd, vd = q.to(DEV), k.to(DEV), v.to(DEV)
     o, lse = B.lr_attention_fwd(qd, kd, vd, Bn, S, H, HD)
-    r = slice((Bn - 1) * S, Bn * S)
-    part = [t[r, 4 * HD:].contiguous() for t in (qd, kd, vd)]
-    o1, lse1 = B.lr_attention_fwd(*part, 1, S, 4, HD)
-    assert torch.equal(o[r, 4 * HD:], o1) and torch.equal(lse.view(Bn, H, S)[-1, 4:], lse1.view(4, S))
+    for b in (0, Bn - 1):
+        r = slice(b * S, (b + 1) * S)
+        part = [t[r, 4 * HD:].contiguous() for t in (qd, kd, vd)]
+        o1, lse1 = B.lr_attention_fwd(*part, 1, S, 4, HD)
+        assert torch.equal(o[r, 4 * HD:], o1) and torch.equal(lse.view(Bn, H, S)[b, 4:], lse1.view(4, S))
     q64, k64, v64 = (t[:S, :HD].double() for t in (q, k, v))
     s = (q64 @ k64.t() / HD ** 0.5).masked_fill(torch.ones(S, S, dtype=torch.bool).triu(1), -torch.inf)
     p = s.softmax(-1)
