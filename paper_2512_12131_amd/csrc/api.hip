@@ -169,16 +169,19 @@ GemmOp wgrad_op(const void* Aact, int64_t lda, int Mw, const void* Bact, int64_t
   return op;
 }
 
-// dw[Mw, Nw] (+)= colscale * sum_t Aact[t, Mw] * Bact[t, Nw]    (reduction over tokens, split-K)
+// What the finishing pass of a gradient behind a norm does besides summing up.  A size query passes one too, of null pointers: such
+// a gradient takes another way through the workspace.
+struct NormFold { const void *colscale, *w_for_dgamma; float* dgamma_part; };
+
+// dw[Mw, Nw] (+)= colscale * sum_t Aact[t, Mw] * Bact[t, Nw]    (reduction over tokens, split-K; colscale: of `fold`, if any)
 // n > 1: n such products, operands sA / sB elements apart, gradients stacked [n][Mw][Nw].
 void wgrad(Ctx& c, const void* Aact, int64_t lda, int Mw, const void* Bact, int64_t ldb, int Nw, int64_t T, void* dw,
-           const void* colscale, const void* w_for_dgamma, float* dgamma_part, int accumulate, int n = 1, int64_t sA = 0,
-           int64_t sB = 0) {
+           const NormFold* fold, int accumulate, int n = 1, int64_t sA = 0, int64_t sB = 0) {
   const size_t m = c.mark();
   GemmOp op = wgrad_op(Aact, lda, Mw, Bact, ldb, Nw, T, n, sA, sB);
   const bool kmajor = c.dt == LR_F32 || gemm_bf16_kmajor_ok(op);
   // nothing to scale, add to or sum up: an un-split product is the gradient itself, in either output type
-  const bool plain = !colscale && !w_for_dgamma && !accumulate && kmajor;
+  const bool plain = !fold && !accumulate && kmajor;
   if (c.dt == LR_F32) {
     op.splitk = gemm_f32_pick_splitk(Mw, Nw, (int)T);
   } else if (kmajor && !c.dry) {
@@ -191,7 +194,7 @@ void wgrad(Ctx& c, const void* Aact, int64_t lda, int Mw, const void* Bact, int6
   if (!direct && n > 1) {   // the finishing pass takes one product at a time
     for (int i = 0; i < n; i++)
       wgrad(c, (const char*)Aact + (size_t)i * sA * esize(c.dt), lda, Mw, (const char*)Bact + (size_t)i * sB * esize(c.dt), ldb,
-            Nw, T, (char*)dw + (size_t)i * Mw * Nw * esize(c.gdt), colscale, w_for_dgamma, dgamma_part, accumulate);
+            Nw, T, (char*)dw + (size_t)i * Mw * Nw * esize(c.gdt), fold, accumulate);
     return;
   }
   if (direct) {
@@ -201,7 +204,7 @@ void wgrad(Ctx& c, const void* Aact, int64_t lda, int Mw, const void* Bact, int6
     return;
   }
   void* kept = nullptr;
-  if (!colscale && !w_for_dgamma && kmajor && c.gathered((int64_t)op.splitk * Mw * Nw, &kept)) {
+  if (!fold && kmajor && c.gathered((int64_t)op.splitk * Mw * Nw, &kept)) {
     op.C = kept; op.ldc = Nw;
     gemm(c, op);
     c.jobs[c.njobs++] = FinishJob{(const float*)kept, op.splitk, (int64_t)Mw * Nw, dw};
@@ -213,7 +216,8 @@ void wgrad(Ctx& c, const void* Aact, int64_t lda, int Mw, const void* Bact, int6
   c.nheld = -1;
   gemm(c, op);
   c.nheld = held;
-  LAUNCH(c, k_wgrad_finish(part, op.splitk, Mw, Nw, dw, colscale, w_for_dgamma, dgamma_part, accumulate, c.dt, c.gdt, c.st));
+  const NormFold f = fold ? *fold : NormFold{};
+  LAUNCH(c, k_wgrad_finish(part, op.splitk, Mw, Nw, dw, f.colscale, f.w_for_dgamma, f.dgamma_part, accumulate, c.dt, c.gdt, c.st));
   c.release(m);
 }
 
@@ -264,9 +268,9 @@ void linear_bwd_seq(Ctx& c, const LinArgs& a) {
   c.gather(a.r * (a.d_in + a.d_out), a.r * (a.d_in + a.d_out), a.T);
   c.hold();   // three products that wait for dz and sigma(z) only
   // dW_up = dy^T . sigma(z)
-  wgrad(c, a.dy, a.lddy, (int)a.d_out, act, a.r, (int)a.r, a.T, a.dw_up, nullptr, nullptr, nullptr, a.accumulate);
+  wgrad(c, a.dy, a.lddy, (int)a.d_out, act, a.r, (int)a.r, a.T, a.dw_up, nullptr, a.accumulate);
   // dW_down = dz^T . x
-  wgrad(c, dz, a.r, (int)a.r, a.x, a.ldx, (int)a.d_in, a.T, a.dw_down, nullptr, nullptr, nullptr, a.accumulate);
+  wgrad(c, dz, a.r, (int)a.r, a.x, a.ldx, (int)a.d_in, a.T, a.dw_down, nullptr, a.accumulate);
   // dx = dz . W_down
   GemmOp dx;
   dx.A = dz; dx.lda = a.r; dx.B = a.w_down; dx.ldb = a.d_in; dx.transB = 1; dx.C = a.dx; dx.ldc = a.lddx;
@@ -420,8 +424,7 @@ void group_bwd_seq(Ctx& c, const GrpArgs& a, const void* act, bool act_new = fal
     for (int i = 0; i < nrun; i++) {
       const GrpRun& u = run[i];
       wgrad(c, (const char*)a.dy_stack + (size_t)u.dy_off * es, u.lddy, (int)u.d_out, (const char*)act + (size_t)u.g0 * a.r * es,
-            GR, (int)a.r, a.T, (char*)a.dw_up_stack + (size_t)u.w_off * esize(c.gdt), nullptr, nullptr, nullptr,
-            a.accumulate, u.n, u.dy_bs, a.r);
+            GR, (int)a.r, a.T, (char*)a.dw_up_stack + (size_t)u.w_off * esize(c.gdt), nullptr, a.accumulate, u.n, u.dy_bs, a.r);
     }
   };
   if (!act_new) {
@@ -540,11 +543,12 @@ void group_bwd_seq(Ctx& c, const GrpArgs& a, const void* act, bool act_new = fal
     return;
   }
   if (normed) {
-    wgrad(c, dp, GR, (int)GR, a.x, a.ldx, (int)a.d_in, a.T, a.dw_down_cat, a.gamma, a.w_down_cat, dgp, a.accumulate);
+    const NormFold fold{a.gamma, a.w_down_cat, dgp};
+    wgrad(c, dp, GR, (int)GR, a.x, a.ldx, (int)a.d_in, a.T, a.dw_down_cat, &fold, a.accumulate);
     dgamma();
     dx.B = scaled_weight(c, a);
   } else {
-    wgrad(c, dp, GR, (int)GR, a.x, a.ldx, (int)a.d_in, a.T, a.dw_down_cat, nullptr, nullptr, nullptr, a.accumulate);
+    wgrad(c, dp, GR, (int)GR, a.x, a.ldx, (int)a.d_in, a.T, a.dw_down_cat, nullptr, a.accumulate);
   }
   gemm(c, dx);
 }
@@ -698,7 +702,7 @@ void single_up(Ctx& c, const Blk& b, const void* act, const void* w_up, int64_t 
 void single_up_bwd(Ctx& c, const Blk& b, const void* dout, int64_t N, const void* act, const void* z, const void* w_up,
                    void* dw_up, void* dz, int accumulate, int lax = 0, const void* dz_next = nullptr,
                    void* dh_prev = nullptr) {
-  wgrad(c, dout, N, (int)N, act, b.r, (int)b.r, b.T, dw_up, nullptr, nullptr, nullptr, accumulate);
+  wgrad(c, dout, N, (int)N, act, b.r, (int)b.r, b.T, dw_up, nullptr, accumulate);
   GemmOp da;
   da.A = dout; da.lda = N; da.B = w_up; da.ldb = b.r; da.transB = 1; da.C = dz; da.ldc = b.r;
   da.M = (int)b.T; da.N = (int)b.r; da.K = (int)N;
@@ -886,7 +890,7 @@ void block_bwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   c.flush();
   // down-D backward: dW_dn_d = dz_d^T . m ; dm = dz_d . W_dn_d with the SwiGLU reverse fused in
   c.hold();
-  wgrad(c, dz1, r, (int)r, mm, f, (int)f, T, g->w_dn_d, nullptr, nullptr, nullptr, accumulate);
+  wgrad(c, dz1, r, (int)r, mm, f, (int)f, T, g->w_dn_d, nullptr, accumulate);
   {
     GemmOp dm;
     dm.A = dz1; dm.lda = r; dm.B = p->w_dn_d; dm.ldb = f; dm.transB = 1; dm.C = big2; dm.ldc = f;
@@ -925,7 +929,7 @@ void block_bwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   }
   // down-O backward
   c.hold();
-  wgrad(c, dz1, r, (int)r, o, d, (int)d, T, g->w_dn_o, nullptr, nullptr, nullptr, accumulate);
+  wgrad(c, dz1, r, (int)r, o, d, (int)d, T, g->w_dn_o, nullptr, accumulate);
   {
     GemmOp dO;
     dO.A = dz1; dO.lda = r; dO.B = p->w_dn_o; dO.ldb = d; dO.transB = 1; dO.C = dout; dO.ldc = d;

@@ -265,3 +265,11 @@ def test_strided_backward_counts_the_copies_it_makes():
     for ldx, lddy in ((wide, n), (d, wide)):
         assert f(fake, ldx, fake, 1e-5, B.LR_NORM_ONLINE, fake, fake, fake, fake, fake, lddy, n, fake, d, fake, fake, fake, G, T, d, r, n,
                  1, B.LR_BF16, 0, 0, fake, ws, None) == -3
+
+
+def test_group_backward_asks_for_the_partials_behind_the_norm():
+    """What is alive at once while dW_down of a group behind a norm is formed: sigma(z), the gathered partials of dW_up (7 splits, the
+    most that the tokens have, or 32 MiB), dp, and its own partials, which are never among the gathered ones."""
+    T, d, r, n = 3844, 264, 488, 2616
+    alive = 2 * T * r * 2 + min(32 << 20, 7 * r * n * 4) + 7 * r * d * 4
+    assert B.lr_group_workspace_bytes(1, T, d, r, n, B.LR_BF16, 1) >= alive

@@ -57,7 +57,8 @@ def test_linear(shape, need, act, accumulate):
 @pytest.mark.parametrize("act", [B.LR_ACT_SILU, B.LR_ACT_IDENTITY])
 @pytest.mark.parametrize("norm", [B.LR_NORM_NONE, B.LR_NORM_ONLINE])
 @pytest.mark.parametrize("shape,need", [((3, 1031, 264, 40, 520, B.LR_BF16), 782336), ((2, 4, 240, 344, 1480, B.LR_BF16), 2048768),
-                                        ((2, 2048, 16, 592, 1240, B.LR_BF16), 16595200), ((3, 300, 72, 24, 104, B.LR_F32), 196352)])
+                                        ((2, 2048, 16, 592, 1240, B.LR_BF16), 16595200), ((3, 300, 72, 24, 104, B.LR_F32), 196352),
+                                        ((1, 3844, 264, 488, 2616, B.LR_BF16), 29284352), ((1, 8550, 16, 40, 272, B.LR_BF16), 1509888)])
 def test_group(shape, need, norm, act):
     G, T, d, r, n, dt = shape
     print(f"group backward in {need} bytes: {shape} norm={norm} act={act}", flush=True)
@@ -78,7 +79,8 @@ def test_group(shape, need, norm, act):
 
 @pytest.mark.parametrize("form", ["plain", "saved", "lax"])
 @pytest.mark.parametrize("shape,need,need_saved", [((2, 256, 2, 2, 344, 64), 6277376, 3905792), ((3, 129, 4, 2, 1003, 136), 9274880, 6135040),
-                                                   ((2, 700, 4, 4, 1416, 128), 32633088, 20716032)])
+                                                   ((2, 700, 4, 4, 1416, 128), 32633088, 20716032),
+                                                   ((8, 770, 1, 1, 2600, 32), 173348608, 77227776)])
 def test_block(shape, need, need_saved, form):
     Bn, S, H, kv, f, r = shape
     need = need_saved if form == "saved" else need
