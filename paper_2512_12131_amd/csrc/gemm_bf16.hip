@@ -654,12 +654,14 @@ hipError_t gemm_bf16(const GemmOp& op, hipStream_t st) {
 
 int gemm_bf16_join_tile(const GemmOp* ops, int n) {
   // Apart, each on its best tile, a launch each; or together on 32 x 32 or 64 x 64 tiles, the workgroups of all
-  // sharing the chip: as long as the longest workgroup or, where all of their work is more, as that and the longest one (they are not
-  // alike: what a slot still holds when the others are empty).
-  // Against 3328 backward calls of a layer or group (1 .. 6000 tokens, weights 16 .. 4096 wide), each measured apart and joined on either
-  // tile: the choice loses 0.75 % to the best of the three in the geometric mean and saves 29.7 % of the call against apart; 17
-  // calls are more than 3 % slower than apart, the worst 12 %.  (With half of the longest 0.76 %, 60 calls, 20 %; with a gap between
-  // launches of 0 or 3 us instead of 1.5 1.15 and 0.78 %, 6 and 58 calls.)  Some of them, us, apart / 32 x 32 / 64 x 64 tiles:
+  // sharing the chip: as long as the longest workgroup or, where all of their work is more, as that and three quarters of the longest
+  // one (they are not alike: what a slot still holds when the others are empty).
+  // Against 11106 backward calls of a layer or group (1 .. 6000 tokens, weights 16 .. 4096 wide, written or added to), each measured
+  // apart and joined on either tile: the choice loses 1.0 % to the best of the three in the geometric mean and saves 31 % of the
+  // call against apart; 165 calls are more than 3 % slower than apart.  (With half of the longest 1.02 %, 229 calls, with all of it
+  // 1.04 %, 98 calls; without the gap between launches 1.06 %, 47 calls, with twice as much 1.11 %, 288.  A linear fit of all
+  // terms loses 0.6 % here but makes small blocks, whose chains of launches these calls do not show, up to 6 % slower.)  Some of
+  // them, us, apart / 32 x 32 / 64 x 64 tiles:
   //   layer 12 tokens 2872 -> 400 -> 1760: 20.0 / 21.8 / 18.5        439 tokens 3000 -> 288 -> 864: 22.6 / 29.7 / 21.5
   //         1059 tokens 64 -> 48 -> 288:   19.0 / 10.7 / 12.4        3380 tokens 2088 -> 72 -> 72:  30.1 / 65.7 / 41.1
   //   group 2 x 82 tokens 240 -> 344 -> 1480: 19.8 / 17.9 / 18.2     1 x 557 tokens 392 -> 184 -> 504: 28.4 / 24.9 / 25.7
@@ -684,7 +686,7 @@ int gemm_bf16_join_tile(const GemmOp* ops, int n) {
     }
   }
   for (int t = 0; t < 2; t++)
-    joint[t] = kTileCost[tiles[t]].a + kLaunchGap + longest[t] + (joint[t] > longest[t] ? joint[t] : 0.f);
+    joint[t] = kTileCost[tiles[t]].a + kLaunchGap + (joint[t] > longest[t] ? joint[t] + 0.75f * longest[t] : longest[t]);
   const int t = joint[0] <= joint[1] ? 0 : 1;
   return joint[t] < apart ? tiles[t] : 0;
 }

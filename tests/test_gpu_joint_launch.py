@@ -186,7 +186,7 @@ BF, F32 = torch.bfloat16, torch.float32
 @pytest.mark.parametrize("T,d_in,r,d_out,dt,count", [
     (16, 1024, 256, 1024, BF, 2), (33, 128, 40, 96, BF, 2), (513, 264, 72, 520, BF, 2), (1031, 1024, 256, 768, BF, 2),   # dz, then the rest
     (2050, 512, 128, 512, BF, 3),                                                             # ... and a finishing pass
-    (1693, 2208, 16, 88, BF, 5), (3380, 2088, 72, 72, BF, 5),                                 # apart: faster so
+    (3380, 2088, 72, 72, BF, 5),                                                              # apart: faster so
     (33, 128, 40, 96, F32, 2), (512, 256, 64, 256, F32, 2), (513, 264, 72, 520, F32, 2),
     (16, 1024, 256, 1024, F32, 4), (1031, 1024, 256, 768, F32, 4)])                           # more than 512 tiles
 def test_launches_of_a_layer_backward(T, d_in, r, d_out, dt, count):
