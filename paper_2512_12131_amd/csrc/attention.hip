@@ -276,7 +276,7 @@ __device__ __forceinline__ float half_sum(float x) {
 // tiles: the scores of tile j + 1 (16 MFMAs) and the output of tile j (16 MFMAs) with the softmax of tile j and the maximum of
 // the new scores threaded between them, one MFMA and a share of the rest per slot, so that a wavefront's matrix and
 // vector work overlap and its LDS operands are read some MFMAs ahead.  (One tile at a time - scores, softmax, output -
-// the phases of the two wavefronts of a SIMD did not overlap enough: matrix pipes 41 % busy, now 53 %.)  One barrier per
+// the phases of the two wavefronts of a SIMD did not overlap enough: matrix pipes 41 % busy, now 52 %.)  One barrier per
 // iteration, in the middle, where the K operands have been read and no V operand yet: each load then has a whole iteration to land.
 // The loop over the unmasked tiles is unrolled by two, its score registers swapping roles; the branches (masks, odd
 // tiles, the end) stay outside, which is what lets the compiler keep every tuple in place (246 registers, no copies).
