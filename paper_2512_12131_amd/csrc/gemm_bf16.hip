@@ -9,7 +9,7 @@
 // a plain bf16 store, batched with two-level strides and with the k range of a row tile cut at its last
 // row, also computes the attention's query gradient from the stored score gradient.
 //
-// Work decomposition: one workgroup owns a BM x BN output tile, WM x WN wavefronts each own a
+// Work decomposition: one workgroup owns a BM x BN output tile at a time, WM x WN wavefronts each own a
 // (BM/WM) x (BN/WN) sub-tile built from 32x32x16 MFMA blocks (256x256 by 8 wavefronts, two per SIMD,
 // or 256x128 by 4).  The k loop moves 64-wide slices straight from global memory into LDS
 // (buffer_load ... lds, no register staging, whole 128-byte cache lines per row) through a ring of
@@ -20,6 +20,19 @@
 // auxiliary tiles it reads, the secondary output) is a row-contiguous 16-byte vector through a per-tile
 // buffer resource, without branches.  Workgroups map to tiles XCD by XCD in compact panels and all walk k front to back, so that
 // the tiles resident in one XCD share operand slices in its L2.
+//
+// A launch has at most one workgroup per CU, and a workgroup walks all its tiles in one stream of slices.  What bounds
+// a launch with k of 512 or 1024 is the time outside the main loop: with a workgroup per tile 9 us of each 33 us (K = 1024,
+// plain store) went into its start, the wait for its first slices and the drain of its stores, with the matrix pipes idle.
+// Now the first two slices of the next tile are under way before the epilogue starts, and the epilogue's stores drain behind
+// the next tile's first slice.  us, a workgroup per tile -> one stream (inside a block step):
+//   16384 x 11008 x 1024, plain store        350 -> 319      same, SwiGLU forward            443 -> 413
+//   16384 x  4096 x 1024, three members      381 -> 350      same, SwiGLU backward           556 -> 526
+//   16384 x  2048 x  512, three members      125 -> 110      11008 x 1024 x 16384 k-major    352 -> 331
+//   16384 x  1024 x 4096 (one tile per CU)   112 -> 111      16384 x 4096 x 4096             424 -> 424
+// The four-kilobyte staging space that this leaves a wavefront gives the epilogue rows of 128 bytes.  Rows of 256 through the free B slot
+// as well, with slice 1 of B loaded behind the epilogue, lost the gain (350 -> 350: its wait includes the stores); rows of 64
+// bytes (one MFMA block at a time) made epilogues that read tiles up to 30 % slower.
 #include <vector>
 
 #include "gemm_tile.h"
@@ -29,6 +42,7 @@ namespace {
 
 constexpr int NSA = 3;          // LDS slots of the A operand's slices: loads get two slices of lead
 constexpr int NSB = 2;          // LDS slots of the B operand's slices: loads get one slice of lead
+constexpr int NCU = 256;        // workgroups of a launch with more tiles than that: one per CU
 
 template <int BM_, int BN_, int WM_, int WN_>
 struct Tile {
@@ -39,16 +53,21 @@ struct Tile {
   static constexpr int A_BYTES = BM * 128, B_BYTES = BN * 128, STAGE = A_BYTES + B_BYTES;
   static constexpr int WLOADS = (BM + BN) / 8 / NW;   // 1 KB wavefront loads (8 rows x 128 B) per wavefront per stage
   static constexpr int WLOADS_A = BM / 8 / NW;        // the first WLOADS_A of them fetch A rows, the rest B rows
-  // fp32 row stride of the epilogue staging tile: = 4 (mod 64), so the 16 rows that one cycle of a
-  // 16-byte-per-lane write touches fall on 16 different groups of four banks
-  static constexpr int CS = TN + 4;
-  static constexpr int EPI_BYTES = NW * 32 * CS * 4;
-  static constexpr int STAT_BYTES = BM * 4;
   static constexpr int MAIN_BYTES = NSA * A_BYTES + NSB * B_BYTES;
-  // The per-row statistic is written after the main loop, into main-loop space the epilogue staging
-  // does not reach (the 256x256 tile uses all 160 KB of LDS for its slices).
-  static constexpr int STAT_OFF = EPI_BYTES;
-  static constexpr int LDS_BYTES = MAIN_BYTES > EPI_BYTES + STAT_BYTES ? MAIN_BYTES : EPI_BYTES + STAT_BYTES;
+  static constexpr int LDS_BYTES = MAIN_BYTES;
+  // The epilogue stages 16 rows x 64 columns per wavefront at a time (rows of a whole cache line of bf16), in four 1 KB pieces of
+  // the free A slot that the wavefront's own global->LDS loads fill: what it has read back it may load over, without a
+  // word to the others.  The XOR spreads what a cycle writes (one chunk of 16 rows) and reads (every second chunk of two
+  // rows) over all banks.
+  static constexpr int SR = 16, SC = 64;
+  struct EpiStage {
+    unsigned char* p;
+    __device__ __forceinline__ unsigned char* at(int row, int chunk) const {
+      return p + (row >> 2) * (NW * 1024) + (row & 3) * 256 + ((chunk ^ row) << 4);
+    }
+  };
+  static constexpr bool STAT_IN_STAGE = true;
+  static_assert(WLOADS_A >= 4, "a wavefront stages 4 KB in pieces of its own");
   static_assert(BM / 8 % NW == 0 && BN / 8 % NW == 0 && FM >= 1 && FN >= 1 && BM <= NT,
                 "tile / wavefront layout mismatch");
 };
@@ -57,29 +76,77 @@ struct Tile {
 // KM = true:  operands k-major,      A[k][m], B[k][n]  (weight gradients: k runs over tokens).  The
 //             slices are stored in LDS as they arrive, [k][m], and the MFMA operands are gathered
 //             with the LDS transpose read, so no transposed copy of an activation is ever written.
+// KM = false: operands k-contiguous, A[m][k], B[n][k].
+// KM = true:  operands k-major,      A[k][m], B[k][n]  (weight gradients: k runs over tokens).  The
+//             slices are stored in LDS as they arrive, [k][m], and the MFMA operands are gathered
+//             with the LDS transpose read, so no transposed copy of an activation is ever written.
+// vector memory instructions that a wavefront's epilogue certainly issues after the loads of the next tile's slices
+template <class T, int KIND>
+constexpr int epilogue_stores() {
+  const int passes = T::TM * T::TN / (64 * 8);
+  return KIND == EPI_PARTIAL ? 2 * passes : passes;
+}
+
+// KM = false: operands k-contiguous, A[m][k], B[n][k].
+// KM = true:  operands k-major,      A[k][m], B[k][n]  (weight gradients: k runs over tokens).  The
+//             slices are stored in LDS as they arrive, [k][m], and the MFMA operands are gathered
+//             with the LDS transpose read, so no transposed copy of an activation is ever written.
 template <class T, int KIND, bool STAT_A, bool KM>
-__global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, int tiles_m, int tiles_n) {
+__global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, int tiles_m, int tiles_n, int total) {
   static_assert(!KM || ((KIND == EPI_PARTIAL || KIND == EPI_STORE) && !STAT_A && T::BM == 256 && T::BN % 128 == 0),
                 "the k-major form serves split-K weight gradients and plain stores");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  float* sStat = reinterpret_cast<float*>(smem + T::STAT_OFF);
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / T::WN, wn = wave % T::WN;
-  int tm, tn, bz;
-  tile_of_block(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y, tiles_m, tiles_n, tm, tn, bz);
-  if (KM && op.causal_k) tm = tiles_m - 1 - tm;   // the longest k ranges of a batch member first
-  const int m0 = tm * T::BM, n0 = tn * T::BN;
-  const int b = bz / op.splitk, ks = bz % op.splitk;
-  const int kbeg = ks * kper;
-  int kend = min(op.K, kbeg + kper);
-  if (KM && op.causal_k) kend = min(kend, m0 + T::BM);
-  // element offsets of this batch entry's operands
-  const int bo = op.batch_inner > 0 ? b / op.batch_inner : 0, bi = op.batch_inner > 0 ? b % op.batch_inner : b;
-  const int nk = kend > kbeg ? (kend - kbeg + BK - 1) / BK : 0;
 
-  const uint16_t* A = (const uint16_t*)op.A + (int64_t)bi * op.sA + (int64_t)bo * op.sAo;
-  const uint16_t* B = (const uint16_t*)op.B + (int64_t)(bi / op.b_group) * op.sB + (int64_t)bo * op.sBo;
+  // ---- tiles of this workgroup -----------------------------------------------------------------
+  // The hardware deals workgroups round-robin to the XCDs; each XCD works through a contiguous range of tiles, its
+  // workgroups side by side.
+  const int bid = blockIdx.x + gridDim.x * blockIdx.y, nwg = gridDim.x * gridDim.y;
+  const int xcd = bid % NXCD;
+  const int step = nwg / NXCD + (xcd < nwg % NXCD ? 1 : 0);             // workgroups on this XCD
+  const int tiles_first = xcd * (total / NXCD) + min(xcd, total % NXCD);
+  const int tiles_end = tiles_first + total / NXCD + (xcd < total % NXCD ? 1 : 0);
+
+  // Where a tile's slices come from.  rec_*: bytes behind base_* that may be read; what lies beyond (rows past the
+  // matrix, or everything for the tile after the last one) arrives as zeros.
+  struct Source {
+    const uint16_t *base_a, *base_b;
+    uint32_t rec_a, rec_b;
+    int klen, nk;                        // k elements, 64-wide slices (at least two)
+    int m0, n0, tn, b, bi, bo, bz;
+  };
+  auto source = [&](int nid) -> Source {
+    Source s;
+    int tm;
+    tile_of_index(nid, tiles_m, tiles_n, tm, s.tn, s.bz);
+    if (KM && op.causal_k) tm = tiles_m - 1 - tm;   // the longest k ranges of a batch member first
+    s.m0 = tm * T::BM;
+    s.n0 = s.tn * T::BN;
+    s.b = s.bz / op.splitk;
+    const int kbeg = s.bz % op.splitk * kper;
+    int kend = min(op.K, kbeg + kper);
+    if (KM && op.causal_k) kend = min(kend, s.m0 + T::BM);
+    s.klen = max(kend - kbeg, 0);
+    s.nk = max((s.klen + BK - 1) / BK, 2);
+    // element offsets of this batch entry's operands
+    s.bo = op.batch_inner > 0 ? s.b / op.batch_inner : 0;
+    s.bi = op.batch_inner > 0 ? s.b % op.batch_inner : s.b;
+    const uint16_t* A = (const uint16_t*)op.A + (int64_t)s.bi * op.sA + (int64_t)s.bo * op.sAo;
+    const uint16_t* B = (const uint16_t*)op.B + (int64_t)(s.bi / op.b_group) * op.sB + (int64_t)s.bo * op.sBo;
+    s.base_a = KM ? A + (int64_t)kbeg * op.lda + s.m0 : A + (int64_t)s.m0 * op.lda + kbeg;
+    s.base_b = KM ? B + (int64_t)kbeg * op.ldb + s.n0 : B + (int64_t)s.n0 * op.ldb + kbeg;
+    // first to last element of the tile's rows, k-contiguous: [rows][klen], k-major: [klen][columns]
+    auto extent = [&](int64_t rows, int64_t cols, int64_t ld) -> uint32_t {
+      return s.klen > 0 ? (uint32_t)min((int64_t)0x7fffffff, ((rows - 1) * ld + cols) * 2) : 0u;
+    };
+    s.rec_a = KM ? extent(s.klen, op.M - s.m0, op.lda) : extent(min(T::BM, op.M - s.m0), s.klen, op.lda);
+    s.rec_b = KM ? extent(s.klen, op.N - s.n0, op.ldb) : extent(min(T::BN, op.N - s.n0), s.klen, op.ldb);
+    return s;
+  };
+  int nid = tiles_first + bid / NXCD;
+  Source cur = source(nid), nxt = cur;
 
   // ---- global -> LDS, without passing through registers ---------------------------------------
   // One buffer_load_dwordx4 ... lds per wavefront moves 8 tile rows x 128 bytes (1 KB, eight whole
@@ -88,11 +155,6 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, i
   // chunk that belongs in its slot; MFMA operand reads (32 rows x one logical chunk) then spread over
   // all banks.  A lane whose chunk lies outside the matrix (row tail, k tail) uses an offset past the
   // resource size: the load returns zeros and zeros are what reaches LDS.
-  constexpr uint32_t OOB = 0x80000000u;
-  const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(KM ? A + (int64_t)kbeg * op.lda + m0 : A + (int64_t)m0 * op.lda + kbeg), 0, 0x7fffffff, 0x00020000);
-  const __amdgpu_buffer_rsrc_t rsB = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(KM ? B + (int64_t)kbeg * op.ldb + n0 : B + (int64_t)n0 * op.ldb + kbeg), 0, 0x7fffffff, 0x00020000);
   // k-contiguous form: 8 rows x 128 B per wavefront load; k-major form: 2 k-rows x 512 B (BM = 256
   // columns) or 4 k-rows x 256 B (128 columns).  In both, the 16-byte chunk index inside a row is
   // XOR-swizzled so that the operand reads spread over the banks.
@@ -101,88 +163,63 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, i
   // with this term the 16 rows that one cycle of a 16-byte-per-lane read touches (16 lanes) fall on
   // 16 different 16-byte bank groups.  The 1 KB group index g = wave + NW * i keeps its parity over i
   // (NW is even), so one swizzle value per lane serves all of its loads.
+  // k-major: rows past k lie behind the resource's end; a column chunk past the matrix reads into the next k-row (or ends with
+  // the resource) and feeds output rows or columns that are not stored.
+  // The offsets below hold for every slice of every tile.
+  constexpr uint32_t OOB = 0x80000000u;
   static_assert(T::NW % 2 == 0 && (T::BM / 8) % 2 == 0, "row parity of a lane must not depend on the load index");
-  const int lrow = KM ? 0 : lane >> 3;
-  const int lchunk = KM ? 0 : (lane & 7) ^ (((wave & 1) << 2) | (lrow >> 1));
+  const int lrow = lane >> 3, lchunk = (lane & 7) ^ (((wave & 1) << 2) | (lrow >> 1));
   uint32_t goff[T::WLOADS];
-  int kml_a = 0, kml_b = 0;          // KM: k-row (inside the slice, modulo the per-load stride) of this lane
 #pragma unroll
   for (int i = 0; i < T::WLOADS; i++) {
-    const int g = wave + T::NW * i;                        // 1 KB group: A groups first, then B
+    const bool isA = i < T::WLOADS_A;
+    const int g = wave + T::NW * i - (isA ? 0 : T::BM / 8);   // 1 KB group of the operand
+    const int64_t ld = isA ? op.lda : op.ldb;
+    int64_t off;
     if constexpr (!KM) {
-      if (i < T::WLOADS_A) {
-        const int row = g * 8 + lrow;
-        goff[i] = (m0 + row) < op.M ? (uint32_t)(row * (int)op.lda + lchunk * 8) * 2u : OOB;
-      } else {
-        const int row = (g - T::BM / 8) * 8 + lrow;
-        goff[i] = (n0 + row) < op.N ? (uint32_t)(row * (int)op.ldb + lchunk * 8) * 2u : OOB;
-      }
+      off = ((g * 8 + lrow) * ld + lchunk * 8) * 2;
     } else {
-      if (i < T::WLOADS_A) {
-        constexpr int CPR = T::BM / 8, RPL = 64 / CPR;       // chunks per k-row, k-rows per wavefront load
-        const int krow = g * RPL + lane / CPR;
-        const int lc = (lane % CPR) ^ ((krow & 7) << 2);
-        goff[i] = (m0 + lc * 8) < op.M ? (uint32_t)(krow * (int)op.lda + lc * 8) * 2u : OOB;
-        if (i == 0) kml_a = krow;
-      } else {
-        constexpr int CPR = T::BN / 8, RPL = 64 / CPR;
-        const int krow = (g - T::BM / 8) * RPL + lane / CPR;
-        const int lc = (lane % CPR) ^ (((krow & 7) << 2) & (CPR - 1));
-        goff[i] = (n0 + lc * 8) < op.N ? (uint32_t)(krow * (int)op.ldb + lc * 8) * 2u : OOB;
-        if (i == T::WLOADS_A) kml_b = krow;
-      }
+      const int CPR = (isA ? T::BM : T::BN) / 8, RPL = 64 / CPR;       // chunks per k-row, k-rows per wavefront load
+      const int krow = g * RPL + lane / CPR;
+      off = (krow * ld + ((lane % CPR) ^ (((krow & 7) << 2) & (CPR - 1))) * 8) * 2;
     }
+    goff[i] = off < (int64_t)OOB ? (uint32_t)off : OOB;
   }
   // Every workgroup walks its k range in the same order, front to back.  The workgroups of an XCD
   // that share A rows or B rows (one panel of tiles) then want the same k slice at about the same time,
   // and all but the first request for it hit in that XCD's L2: walking from staggered starting slices
   // instead multiplied the traffic out of L2 by 3.6 and cost 12-18% of the GEMM rate.  The fixed order
   // also makes the summation order of a token row independent of how sequences are batched.
-  // slot addresses: A slices cycle through NSA slots at the bottom of LDS, B slices through NSB above
-  auto a_slot = [&](int kt) -> unsigned char* { return smem + (kt % NSA) * T::A_BYTES; };
-  auto b_slot = [&](int kt) -> unsigned char* { return smem + NSA * T::A_BYTES + (kt % NSB) * T::B_BYTES; };
+  // Slots: A slices cycle through NSA slots at the bottom of LDS, B slices through NSB above, on from tile to tile.
+  // a0, a1, a2: slots of slices kt, kt + 1, kt + 2 (and of kt - 1); b0, b1 those of kt, kt + 1.
+  uint32_t a0 = 0, a1 = T::A_BYTES, a2 = 2 * T::A_BYTES, b0 = NSA * T::A_BYTES, b1 = b0 + T::B_BYTES;
   constexpr int WLOADS_B = T::WLOADS - T::WLOADS_A;
-  // issue_ab(kt, IS_A, HALF): HALF = 0 / 1 issues the first / second half of the operand's loads of
-  // slice kt, HALF = 2 all of them
-  auto issue_ab = [&](int kt, auto IS_A, auto HALF) {
+  // issue_ab(kt, dst, IS_A, HALF): HALF = 0 / 1 issues the first / second half of the operand's loads of
+  // slice kt of this tile, or past its end of the next one, HALF = 2 all of them
+  auto issue_ab = [&](int kt, uint32_t slot, auto IS_A, auto HALF) {
     constexpr bool isA = decltype(IS_A)::value;
     constexpr int half = decltype(HALF)::value;
-    const int kte = kt;
-    unsigned char* dst = (isA ? a_slot(kt) : b_slot(kt)) + wave * 1024;
+    const bool here = kt < cur.nk;
+    const int ks = here ? kt : kt - cur.nk;
+    const int64_t skip = (int64_t)ks * (KM ? BK * 2 * (isA ? op.lda : op.ldb) : BK * 2);     // bytes before this slice
+    const uint32_t rec = here ? (isA ? cur.rec_a : cur.rec_b) : (isA ? nxt.rec_a : nxt.rec_b);
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        (char*)(here ? (isA ? cur.base_a : cur.base_b) : (isA ? nxt.base_a : nxt.base_b)) + skip, 0,
+        skip < (int64_t)rec ? rec - (uint32_t)skip : 0u, 0x00020000);
+    // k tail of the k-contiguous form: chunks past the end of k read as zeros
+    const uint32_t kmask = KM || ks * BK + lchunk * 8 < (here ? cur.klen : nxt.klen) ? 0u : OOB;
+    unsigned char* dst = smem + slot + wave * 1024;
     constexpr int F0 = isA ? 0 : T::WLOADS_A, F1 = isA ? T::WLOADS_A : T::WLOADS;   // the operand's loads
     constexpr int I0 = half == 1 ? (F0 + F1) / 2 : F0, I1 = half == 0 ? (F0 + F1) / 2 : F1;
-    if constexpr (!KM) {
-      const uint32_t kmask = (kt < nk && (kbeg + kte * BK + lchunk * 8) < kend) ? 0u : OOB;
-      const uint32_t ktoff = (uint32_t)kte * (BK * 2);
 #pragma unroll
-      for (int i = I0; i < I1; i++)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(isA ? rsA : rsB, LRB_LDS_PTR(dst + (i - F0) * (T::NW * 1024)), 16,
-                                                 (int)((goff[i] + ktoff) | kmask), 0, 0, 0);
-    } else {
-      // k-rows of load i: kml + i * (NW * rows-per-load); rows at or past the end of k read as zeros
-      constexpr int RPL = 64 / ((isA ? T::BM : T::BN) / 8);
-      const int krem = kt < nk ? (kend - kbeg) - kte * BK : 0;      // valid k-rows left from this slice's start
-      const uint32_t off = (uint32_t)kte * BK * (uint32_t)(isA ? op.lda : op.ldb) * 2u;
-      const int kml = isA ? kml_a : kml_b;
-#pragma unroll
-      for (int i = I0; i < I1; i++) {
-        const uint32_t km = (kml + (i - F0) * T::NW * RPL) < krem ? 0u : OOB;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(isA ? rsA : rsB, LRB_LDS_PTR(dst + (i - F0) * (T::NW * 1024)), 16,
-                                                 (int)((goff[i] + off) | km), 0, 0, 0);
-      }
-    }
+    for (int i = I0; i < I1; i++)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, LRB_LDS_PTR(dst + (i - F0) * (T::NW * 1024)), 16, (int)(goff[i] | kmask), 0, 0, 0);
   };
   using Half0 = std::integral_constant<int, 0>;
   using Half1 = std::integral_constant<int, 1>;
   using Whole = std::integral_constant<int, 2>;
 
   f32x16 acc[T::FM][T::FN];
-#pragma unroll
-  for (int i = 0; i < T::FM; i++)
-#pragma unroll
-    for (int j = 0; j < T::FN; j++)
-#pragma unroll
-      for (int v = 0; v < 16; v++) acc[i][j][v] = 0.f;
 
   // MFMA operand addressing: row = lane%32 of a 32-row block, logical chunk kk*2 + lane/32
   const int frow = lane & 31, fk = lane >> 5, fsw = (frow >> 1) & 7;
@@ -207,11 +244,11 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, i
 #pragma unroll
     for (int j2 = 0; j2 < T::FN; j2++) troffB[j2] = lane_off(T::BN * 2, wn * T::TN + j2 * 32 + cin, ksw & (T::BN / 8 - 1));
   }
-  auto load_frags = [&](int buf, int kt, auto KKc) {
+  auto load_frags = [&](int buf, uint32_t slot_a, uint32_t slot_b, auto KKc) {
     constexpr int kk = decltype(KKc)::value;
     if constexpr (!KM) {
-      const unsigned char* sa = a_slot(kt) + (wm * T::TM + frow) * 128;
-      const unsigned char* sb = b_slot(kt) + (wn * T::TN + frow) * 128;
+      const unsigned char* sa = smem + slot_a + (wm * T::TM + frow) * 128;
+      const unsigned char* sb = smem + slot_b + (wn * T::TN + frow) * 128;
       const int coff = ((kk * 2 + fk) ^ fsw) << 4;
 #pragma unroll
       for (int i = 0; i < T::FM; i++) af[buf][i] = *reinterpret_cast<const bf16x8*>(sa + i * 32 * 128 + coff);
@@ -226,8 +263,8 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, i
       // two slices of load lead).  The price: the compiler does not wait for their results either, so
       // every k16 step of this form ends with an explicit wait for the LDS counter behind a scheduling
       // barrier (see the main loop).
-      const uint32_t slotA = (uint32_t)(uintptr_t)LRB_LDS_PTR(a_slot(kt));
-      const uint32_t slotB = (uint32_t)(uintptr_t)LRB_LDS_PTR(b_slot(kt));
+      const uint32_t slotA = (uint32_t)(uintptr_t)LRB_LDS_PTR(smem + slot_a);
+      const uint32_t slotB = (uint32_t)(uintptr_t)LRB_LDS_PTR(smem + slot_b);
       auto tr_pair = [&](uint32_t addr, auto PITCH) -> bf16x8 {
         constexpr int o0 = kk * 16 * decltype(PITCH)::value, o1 = o0 + 8 * decltype(PITCH)::value;
         static_assert(o1 < 65536, "LDS instruction offset field");
@@ -243,20 +280,29 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, i
       for (int j = 0; j < T::FN; j++) bf[buf][j] = tr_pair(slotB + troffB[j], std::integral_constant<int, T::BN * 2>{});
     }
   };
-  auto mfma_step = [&](int buf) {
+  // first operands of a tile (the reads of the k-major form are waited for here)
+  auto first_frags = [&]() {
+    load_frags(0, a0, b0, std::integral_constant<int, 0>{});
+    if constexpr (KM) {
+      wait_lgkmcnt0();
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  auto mfma_step = [&](int buf, auto ZERO) {
+    constexpr f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < T::FM; i++)
 #pragma unroll
       for (int j = 0; j < T::FN; j++)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[buf][j], af[buf][i], acc[i][j], 0, 0, 0);
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[buf][j], af[buf][i], decltype(ZERO)::value ? zero : acc[i][j], 0, 0, 0);
   };
   // STAT_A: thread t accumulates the sum of squares of tile row t from the LDS copy, chunk by chunk as they lie there
   // (the ring kernels share a row among threads and add its chunks up in this order)
   float ssq = 0.f;
-  auto stat_row = [&](int kt, int half) {
+  auto stat_row = [&](int half) {
     if constexpr (STAT_A) {
       if (tid < T::BM) {
-        const unsigned char* sr = a_slot(kt) + tid * 128 + half * 64;
+        const unsigned char* sr = smem + a0 + tid * 128 + half * 64;
 #pragma unroll
         for (int c = 0; c < 4; c++) ssq += sumsq8(*reinterpret_cast<const uint4*>(sr + c * 16));
       }
@@ -276,8 +322,10 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, i
   //   step 1, 2: the halves of A(kt+2)    -> the slot A(kt-1) left at the previous barrier
   //   barrier (needs A(kt+1), B(kt+1); loads retire in order, so A(kt+2) alone may stay in flight)
   //   step 3: first half of B(kt+2)       -> the slot B(kt) just left
-  // The loop body is branch free: slices past the end of k are "loaded" with every lane out of range
-  // (zeros into a slot nobody reads again), so the wait counts are compile-time constants.
+  // The loop body is branch free: slices past the end of k are the next tile's, or, after the last tile, "loaded" with
+  // every lane out of range (zeros into a slot nobody reads again), so the wait counts are compile-time constants.
+  // Slices 0 and 1 of the next tile are on their way before this tile's epilogue starts, which stages through the one A
+  // slot that then is free.  They do not wait for its stores either: slice 0 lets those fly.
   // Instruction interleave: a wavefront issues in order, and an MFMA occupies the matrix pipe for
   // 32 cycles during which the same wavefront may issue other work.  The scheduler is therefore
   // told to thread the LDS reads and global->LDS loads between the MFMAs instead of issuing them
@@ -286,27 +334,22 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, i
   constexpr int HLA = T::WLOADS_A / 2, HLB = WLOADS_B / 2; // loads per half slice of A, of B
   constexpr std::true_type OPA{};
   constexpr std::false_type OPB{};
-  issue_ab(0, OPA, Whole{});
-  issue_ab(0, OPB, Whole{});
-  issue_ab(1, OPA, Whole{});
-  issue_ab(1, OPB, Half0{});
-  wait_vmcnt<T::WLOADS_A + HLB>();   // A(0), B(0) landed; A(1) and half of B(1) may fly
-  __builtin_amdgcn_s_barrier();
-  load_frags(0, 0, std::integral_constant<int, 0>{});
-  if constexpr (KM) {
-    wait_lgkmcnt0();
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  for (int kt = 0; kt < nk; kt++) {
+  // vector memory instructions that a wavefront's epilogue certainly issues behind the loads of slice 1 of the next tile
+  constexpr int STORES = T::TM * T::TN / (64 * 8) * (KIND == EPI_PARTIAL ? 2 : 1);
+  static_assert(T::WLOADS_A + STORES < 64, "vmcnt is a 6-bit counter");
+  bool stores_fly = false;          // there was an epilogue
+  // FIRST: slice 0 of a tile.  B(1) is on its way already, the accumulators start at zero.
+  auto slice = [&](int kt, auto FIRST) {
+    constexpr bool first = decltype(FIRST)::value;
     static_for<3>([&](auto KK) {
       constexpr int kk = decltype(KK)::value;
-      load_frags((kk + 1) & 1, kt, std::integral_constant<int, kk + 1>{});
-      if constexpr (kk == 0) issue_ab(kt + 1, OPB, Half1{});
-      if constexpr (kk == 1) issue_ab(kt + 2, OPA, Half0{});
-      if constexpr (kk == 2) issue_ab(kt + 2, OPA, Half1{});
-      if constexpr (kk < 2) stat_row(kt, kk);
-      mfma_step(kk & 1);
-      constexpr int NL = kk == 0 ? HLB : HLA;
+      load_frags((kk + 1) & 1, a0, b0, std::integral_constant<int, kk + 1>{});
+      if constexpr (kk == 0 && !first) issue_ab(kt + 1, b1, OPB, Half1{});
+      if constexpr (kk == 1) issue_ab(kt + 2, a2, OPA, Half0{});
+      if constexpr (kk == 2) issue_ab(kt + 2, a2, OPA, Half1{});
+      if constexpr (kk < 2) stat_row(kk);
+      mfma_step(kk & 1, std::integral_constant<bool, first && kk == 0>{});
+      constexpr int NL = kk > 0 ? HLA : first ? 0 : HLB;
 #pragma unroll
       for (int i = 0; i < T::FM + T::FN; i++) {
         __builtin_amdgcn_sched_group_barrier(0x008, MPR, 0);   // MFMA
@@ -320,13 +363,14 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, i
       }
       __builtin_amdgcn_sched_barrier(0);
     });
-    wait_vmcnt<T::WLOADS_A>();             // A(kt+1), B(kt+1) of this wavefront landed; A(kt+2) may fly
+    if (first && stores_fly) wait_vmcnt<T::WLOADS_A + STORES>();
+    else wait_vmcnt<T::WLOADS_A>();        // A(kt+1), B(kt+1) of this wavefront landed; A(kt+2) may fly
     wait_lgkmcnt0();                       // and its reads of slice kt's slots are complete
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    issue_ab(kt + 2, OPB, Half0{});
-    load_frags(0, kt + 1, std::integral_constant<int, 0>{});
-    mfma_step(1);
+    issue_ab(kt + 2, b0, OPB, Half0{});
+    load_frags(0, a1, b1, std::integral_constant<int, 0>{});
+    mfma_step(1, std::false_type{});
 #pragma unroll
     for (int i = 0; i < T::FM + T::FN; i++) {
       __builtin_amdgcn_sched_group_barrier(0x008, MPR, 0);   // MFMA
@@ -339,16 +383,53 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, i
       wait_lgkmcnt0();
     }
     __builtin_amdgcn_sched_barrier(0);
+    const uint32_t a = a0, b = b0;
+    a0 = a1; a1 = a2; a2 = a;
+    b0 = b1; b1 = b;
+  };
+  issue_ab(0, a0, OPA, Whole{});
+  issue_ab(0, b0, OPB, Whole{});
+  issue_ab(1, a1, OPA, Whole{});
+  issue_ab(1, b1, OPB, Whole{});
+  wait_vmcnt<T::WLOADS>();          // A(0), B(0) landed; A(1) and B(1) may fly
+  __builtin_amdgcn_s_barrier();
+  while (true) {
+    const int nid_next = nid + step;
+    const bool more = nid_next < tiles_end;
+    if (more) {
+      nxt = source(nid_next);
+    } else {
+      nxt.rec_a = 0;
+      nxt.rec_b = 0;
+      nxt.klen = 0;
+    }
+    first_frags();
+    slice(0, std::true_type{});
+    for (int kt = 1; kt < cur.nk; kt++) slice(kt, std::false_type{});
+    issue_ab(cur.nk + 1, b1, OPB, Half1{});
+    __builtin_amdgcn_sched_barrier(0);
+    // ---- epilogue: a2 is the free slot -------------------------------------------------------------
+    if constexpr (STAT_A) {
+      float* sStat = reinterpret_cast<float*>(smem + a2);
+      if (tid < T::BM) sStat[tid] = ssq;
+      ssq = 0.f;
+      wait_lgkmcnt0();
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+    }
+    // (opaque copies: otherwise the epilogue's address arithmetic is moved out of the loop over tiles, and spilled)
+    int elane = lane, ewave = wave;
+    asm volatile("" : "+v"(elane), "+s"(ewave));
+    gemm_epilogue<T, KIND, STAT_A>(op, acc, typename T::EpiStage{smem + a2 + wave * 1024},
+                                   reinterpret_cast<const float*>(smem + a2), ewave, elane, cur.m0, cur.n0, cur.tn, tiles_n, cur.b,
+                                   cur.bi, cur.bo, cur.bz);
+    if (!more) break;
+    stores_fly = true;
+    nid = nid_next;
+    cur = nxt;
   }
-  wait_vmcnt<0>();
-
-  // ---- per-row sum of squares gathered from the A slices ---------------------------------------
-  __syncthreads();  // main-loop LDS is dead from here on
-  if constexpr (STAT_A) {
-    if (tid < T::BM) sStat[tid] = ssq;
-    __syncthreads();
-  }
-  gemm_epilogue<T, KIND, STAT_A>(op, acc, smem, sStat, wave, lane, m0, n0, tn, tiles_n, b, bi, bo, bz);
+  wait_vmcnt<STORES>();          // no load into LDS outlives its workgroup
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -363,7 +444,10 @@ hipError_t launch(const GemmOp& op, hipStream_t st) {
   const int tiles_m = (op.M + T::BM - 1) / T::BM, tiles_n = (op.N + T::BN - 1) / T::BN;
   int kper = (op.K + op.splitk - 1) / op.splitk;
   kper = (kper + BK - 1) / BK * BK;
-  hipLaunchKernelGGL(kern, tile_grid(tiles_m * tiles_n, op.batch * op.splitk), dim3(T::NT), T::LDS_BYTES, st, op, kper, tiles_m, tiles_n);
+  const int64_t total = (int64_t)tiles_m * tiles_n * op.batch * op.splitk;
+  // causal k ranges differ from tile to tile: a workgroup each, dealt out as CUs become free
+  const dim3 grid = op.causal_k || total <= NCU ? tile_grid(tiles_m * tiles_n, op.batch * op.splitk) : dim3(NCU);
+  hipLaunchKernelGGL(kern, grid, dim3(T::NT), T::LDS_BYTES, st, op, kper, tiles_m, tiles_n, (int)total);
   return hipGetLastError();
 }
 

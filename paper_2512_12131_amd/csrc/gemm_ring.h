@@ -45,7 +45,14 @@ struct RingTile {
   static constexpr int LA = BM / 8 / NWL, LB = BN / 8 / NWL;   // 1 KB wavefront loads per wavefront and slice
   static constexpr int LPS = (LA + LB) * SUB;                // ... and stage
   static constexpr int CS = TN + 4;                          // fp32 row stride of the epilogue staging tile
-  static constexpr int EPI_BYTES = NW * 32 * CS * 4;
+  static constexpr int STAGE_BYTES = 32 * CS * 4;            // ... of a wavefront
+  static constexpr int EPI_BYTES = NW * STAGE_BYTES;
+  struct EpiStage {
+    unsigned char* p;
+    __device__ __forceinline__ unsigned char* at(int row, int chunk) const { return p + row * (CS * 4) + chunk * 16; }
+  };
+  static constexpr int SR = 32, SC = TN;
+  static constexpr bool STAT_IN_STAGE = false;
   static constexpr int STAT_OFF = EPI_BYTES;
   static constexpr int MAIN_BYTES = NS * STAGE;
   static constexpr int LDS_BYTES = MAIN_BYTES > EPI_BYTES + BM * 4 ? MAIN_BYTES : EPI_BYTES + BM * 4;
@@ -309,7 +316,7 @@ __device__ __forceinline__ void ring_product(const GemmOp& op, int kper, int til
 #pragma unroll
         for (int v = 0; v < 16; v++) acc[i][j][v] += tot[i][j][v];
   }
-  gemm_epilogue<T, KIND, STAT_A>(op, acc, smem, sStat, wave, lane, m0, n0, tn, tiles_n, b, bi, bo, bz);
+  gemm_epilogue<T, KIND, STAT_A>(op, acc, typename T::EpiStage{smem + wave * T::STAGE_BYTES}, sStat, wave, lane, m0, n0, tn, tiles_n, b, bi, bo, bz);
 }
 
 template <class T, int KIND, bool STAT_A, bool AKM, bool BKM, bool PARTS>

@@ -53,16 +53,9 @@ __device__ __forceinline__ float lane_group_sum(float x) {
   return x;
 }
 
-// Maps the linear workgroup id to an output tile so that (a) the workgroups that the hardware
-// deals round-robin to one XCD form a contiguous range of tiles, and (b) consecutive tiles of that
-// range form compact panels (PM tiles tall), keeping the A rows and B rows they share in that
-// XCD's L2.
-// The range runs over the whole launch, (batch member, k split) slowest: an XCD then works on tiles of
-// one batch member and one k range at a time, which is what lets its workgroups share operand slices.
-__device__ __forceinline__ void tile_of_block(int bid, int total, int tiles_m, int tiles_n, int& tm, int& tn, int& bz) {
-  const int xcd = bid % NXCD, loc = bid / NXCD;
-  const int base = total / NXCD, rem = total % NXCD;
-  const int nid = xcd * base + (xcd < rem ? xcd : rem) + loc;
+// The output tile with index nid of a launch: consecutive indexes form compact panels (PM tiles tall), keeping the A
+// rows and B rows they share in one L2; (batch member, k split) slowest.
+__device__ __forceinline__ void tile_of_index(int nid, int tiles_m, int tiles_n, int& tm, int& tn, int& bz) {
   const int tiles = tiles_m * tiles_n;
   bz = nid / tiles;
   const int tid_ = nid % tiles;
@@ -74,6 +67,16 @@ __device__ __forceinline__ void tile_of_block(int bid, int total, int tiles_m, i
   tm = panel * PM + within % pm_eff;
 }
 
+// Maps the linear workgroup id to an output tile so that the workgroups that the hardware deals round-robin to one
+// XCD form a contiguous range of tiles.
+// The range runs over the whole launch: an XCD then works on tiles of one batch member and one k range at a time,
+// which is what lets its workgroups share operand slices.
+__device__ __forceinline__ void tile_of_block(int bid, int total, int tiles_m, int tiles_n, int& tm, int& tn, int& bz) {
+  const int xcd = bid % NXCD, loc = bid / NXCD;
+  const int base = total / NXCD, rem = total % NXCD;
+  tile_of_index(xcd * base + (xcd < rem ? xcd : rem) + loc, tiles_m, tiles_n, tm, tn, bz);
+}
+
 // The launch grid of `tiles` output tiles for each of `members` batch members times k splits.  The kernels number their
 // workgroups through both dimensions, so where the members are more than the second may have, all go into the first.
 inline dim3 tile_grid(int tiles, int members) {
@@ -83,17 +86,18 @@ inline dim3 tile_grid(int tiles, int members) {
 #define LRB_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
 
 // ---- epilogue ---------------------------------------------------------------------------------
-// Called by every wavefront that holds accumulators once they are final and the main loop's LDS is dead.
-// Tile type T: BM rows; WN wavefronts across, each with an FM x FN arrangement of 32x32 MFMA blocks (TM x TN);
-// CS = fp32 row stride of the staging tile.  (m0, n0): first row / column of the output tile, tn its column
+// Called by every wavefront that holds accumulators once they are final and its staging space is free.
+// Tile type T: BM rows; WN wavefronts across, each with an FM x FN arrangement of 32x32 MFMA blocks (TM x TN), of
+// which SR rows of SC columns are staged at a time: 32 of all columns, or 16 of 64.  stage.at(row, chunk): where 16-byte
+// chunk `chunk` of staged row `row` lies.  (m0, n0): first row / column of the output tile, tn its column
 // index, b / (bi, bo) / bz: batch member, its two-level split, batch member times k split.  sStat: the row
-// statistics gathered in the main loop (STAT_A).
-template <class T, int KIND, bool STAT_A>
-__device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T::FM][T::FN], unsigned char* smem,
+// statistics gathered in the main loop (STAT_A); STAT_IN_STAGE: they lie in the staging space.
+template <class T, int KIND, bool STAT_A, class Stage>
+__device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T::FM][T::FN], const Stage& stage,
                                               const float* sStat, int wave, int lane, int m0, int n0, int tn,
                                               int tiles_n, int b, int bi, int bo, int bz) {
   const int wm = wave / T::WN, wn = wave % T::WN;
-  // The wavefront's sub-tile leaves in FM x (32/RPP) passes of RPP rows.  Everything the passes touch
+  // The wavefront's sub-tile leaves in passes of RPP rows and SC columns.  Everything the passes touch
   // in global memory goes through buffer resources that start at the tile's first row and end after
   // its last valid row: rows past M (and, by an out-of-range offset, columns past N) read as zeros and
   // are dropped on store, an absent auxiliary tile is a resource of size zero.  The pass code is
@@ -101,11 +105,13 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T:
   // auxiliary tiles an epilogue reads (residual, z, x, g, u) are fetched PF passes ahead into a small
   // register ring, and each pass waits only for its own.
   const Epilogue& e = op.epi;
-  float* sC = reinterpret_cast<float*>(smem) + wave * (32 * T::CS);
-  constexpr int LPR = T::TN / 8;            // lanes per output row
+  constexpr int LPR = T::SC / 8;            // lanes per output row
   constexpr int RPP = 64 / LPR;             // rows per pass
-  constexpr int PPB = 32 / RPP;             // passes per 32-row block
-  constexpr int NQ = T::FM * PPB;           // passes per wavefront
+  constexpr int PPS = T::SR / RPP;          // passes per staged piece
+  constexpr int NJ = T::TN / T::SC;         // pieces side by side
+  constexpr int NH = 32 / T::SR;            // pieces of an MFMA block's rows
+  constexpr int NQ = T::FM * NH * NJ * PPS; // passes per wavefront
+  static_assert(T::SR == 32 ? NJ == 1 : T::SR == 16 && T::SC == 64, "staging forms");
   // which auxiliary tiles a kind can read at all, and the prefetch distance in passes: kinds with one
   // auxiliary tile keep eight of its 16-byte vectors in flight per lane, kinds with two keep four of each
   // BASE: the formula; R_F32: the R tile is fp32 (two 16-byte vectors per lane and pass); O32: the primary
@@ -119,8 +125,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T:
   constexpr uint32_t EOOB = 0x80000000u;
   const int cg = lane % LPR, rsub = lane / LPR;
   const int rows_valid = min(T::BM, op.M - m0);
-  const int coln = n0 + wn * T::TN + cg * 8;                         // first of this lane's 8 columns
-  const bool col_ok = coln < op.N;
+  const int coln = n0 + wn * T::TN + cg * 8;                         // first of this lane's 8 columns (leftmost piece)
   auto tile_rsrc = [&](const void* base, int64_t batch_off, int64_t ld, int esz) {
     const char* p = base ? (const char*)base + (batch_off + (int64_t)m0 * ld) * esz : nullptr;
     return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, base ? (uint32_t)rows_valid * (uint32_t)ld * (uint32_t)esz : 0u,
@@ -145,8 +150,10 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T:
   const __amdgpu_buffer_rsrc_t rsRowB = row_rsrc(!PARTIAL ? e.rowb : nullptr);
   const int ldC = PARTIAL ? op.N * 4 : (int)op.ldc * 2;               // row pitches in bytes
   const int ldC2 = (int)e.ldc2 * 2, ldR = (int)e.ldr * (R_F32 ? 4 : 2), ldR2 = (int)e.ldr2 * 2, ldC32 = (int)e.ldc32 * 4;
-  const uint32_t colC = col_ok ? (uint32_t)coln * (PARTIAL ? 4u : 2u) : EOOB, col2 = col_ok ? (uint32_t)coln * 2u : EOOB;
-  const uint32_t col4 = col_ok ? (uint32_t)coln * 4u : EOOB;      // this lane's columns in an fp32 tile
+  // byte offset inside a row of this lane's columns of piece jj, for elements of es bytes
+  auto col_off = [&](int jj, uint32_t es) -> uint32_t {
+    return coln + jj * T::SC < op.N ? (uint32_t)(coln + jj * T::SC) * es : EOOB;
+  };
   const bool want2 = KIND == EPI_SWIGLU_BWD || KIND == EPI_SWIGLU_FWD || KIND == EPI_DOWN_LAX || KIND == EPI_LAXGRAD ||
                      KIND == EPI_ACTGRAD_A || (KIND == EPI_DOWN && e.C2 != nullptr);
   const bool use_rho = !PARTIAL && e.use_rho;
@@ -159,7 +166,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T:
       (ROWPART && e.rowpart) ? (uint32_t)rows_valid * (uint32_t)e.rowpart_ld * 4u : 0u, 0x00020000);
   const int ldPart = ROWPART ? (int)e.rowpart_ld * 4 : 0;
   // one partial per 64 columns (32 where the wavefront's sub-tile has no more): SPW of them per wavefront and row
-  constexpr int LPP = T::TN < 64 ? T::TN / 8 : 8, SPW = LPR / LPP;
+  constexpr int LPP = T::TN < 64 ? T::TN / 8 : 8, SPW = T::TN / (LPP * 8);
   const uint32_t colPart =
       cg % LPP == 0 ? (uint32_t)(e.rowpart_off + ((b * tiles_n + tn) * T::WN + wn) * SPW + cg / LPP) * 4u : EOOB;
   const bool write_stat = STAT_A && e.stat_out && tn == 0 && wn == 0 && b == 0;
@@ -169,64 +176,90 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T:
   const float inv_d = e.inv_d, eps = e.eps;
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   u32x4 auxr[PF], auxr2[PF], auxr3[R_F32 ? PF : 1];   // auxr3: columns 4..7 of an fp32 R tile
-  auto row_of = [&](int q) { return wm * T::TM + (q / PPB) * 32 + (q % PPB) * RPP + rsub; };   // row inside the tile
-  auto fetch = [&](int q, u32x4& ar, u32x4& ar2, u32x4& ar3) {
+  // pass q: MFMA block row i, piece h of its rows, piece jj across, p-th run of RPP rows
+  auto row_of = [&](int q) {                                       // row inside the tile
+    return wm * T::TM + (q / (NH * NJ * PPS)) * 32 + (q / (NJ * PPS) % NH) * T::SR + (q % PPS) * RPP + rsub;
+  };
+  auto across = [](int q) { return q / PPS % NJ; };
+  float ssv[STAT_A ? NQ : PF], rbv[PF];               // per-row scalars, fetched with the auxiliary tiles
+  constexpr bool ROWS = !PARTIAL && !STAT_A && BASE != EPI_STORE && BASE != EPI_UP && BASE != EPI_SWIGLU_BWD && BASE != EPI_SWIGLU_FWD;
+  auto fetch = [&](int q, u32x4& ar, u32x4& ar2, u32x4& ar3, float& ss, float& rb) {
     const int lm = row_of(q);
-    if constexpr (R_F32) {
-      ar = __builtin_amdgcn_raw_buffer_load_b128(rsR, (int)((uint32_t)(lm * ldR) + col4), 0, 0);
-      ar3 = __builtin_amdgcn_raw_buffer_load_b128(rsR, (int)((uint32_t)(lm * ldR) + col4 + 16u), 0, 0);
-    } else if constexpr (HAS_R) {
-      ar = __builtin_amdgcn_raw_buffer_load_b128(rsR, (int)((uint32_t)(lm * ldR) + col2), 0, 0);
+    if constexpr (ROWS) {
+      if (use_rho) ss = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsRowA, lm * 4, 0, 0));
     }
-    if constexpr (HAS_R2) ar2 = __builtin_amdgcn_raw_buffer_load_b128(rsR2, (int)((uint32_t)(lm * ldR2) + col2), 0, 0);
+    if constexpr (BASE == EPI_NORMBWD) rb = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsRowB, lm * 4, 0, 0));
+    if constexpr (R_F32) {
+      const uint32_t off = (uint32_t)(lm * ldR) + col_off(across(q), 4u);
+      ar = __builtin_amdgcn_raw_buffer_load_b128(rsR, (int)off, 0, 0);
+      ar3 = __builtin_amdgcn_raw_buffer_load_b128(rsR, (int)(off + 16u), 0, 0);
+    } else if constexpr (HAS_R) {
+      ar = __builtin_amdgcn_raw_buffer_load_b128(rsR, (int)((uint32_t)(lm * ldR) + col_off(across(q), 2u)), 0, 0);
+    }
+    if constexpr (HAS_R2) ar2 = __builtin_amdgcn_raw_buffer_load_b128(rsR2, (int)((uint32_t)(lm * ldR2) + col_off(across(q), 2u)), 0, 0);
   };
   static_for<PF>([&](auto Q) {
     constexpr int q = decltype(Q)::value;
     auxr[q] = u32x4{0u, 0u, 0u, 0u};
     auxr2[q] = u32x4{0u, 0u, 0u, 0u};
     if constexpr (R_F32) auxr3[q] = u32x4{0u, 0u, 0u, 0u};
-    if constexpr (q < NQ) fetch(q, auxr[q], auxr2[q], auxr3[R_F32 ? q : 0]);
-  });
-  // per-row scalars of all passes, requested before the first pass
-  float ssv[NQ], rbv[NQ];
-  static_for<NQ>([&](auto Q) {
-    constexpr int q = decltype(Q)::value;
-    ssv[q] = 0.f;
+    if constexpr (!STAT_A) ssv[q] = 0.f;
     rbv[q] = 0.f;
-    if constexpr (!PARTIAL && !STAT_A) {
-      if (use_rho) ssv[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsRowA, row_of(q) * 4, 0, 0));
-    }
-    if constexpr (BASE == EPI_NORMBWD)
-      rbv[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsRowB, row_of(q) * 4, 0, 0));
+    if constexpr (q < NQ) fetch(q, auxr[q], auxr2[q], auxr3[R_F32 ? q : 0], ssv[q], rbv[q]);
   });
+  if constexpr (STAT_A)
+    static_for<NQ>([&](auto Q) { ssv[decltype(Q)::value] = sStat[row_of(decltype(Q)::value)]; });
+  if constexpr (STAT_A && T::STAT_IN_STAGE) {   // read by all before anyone writes there
+    wait_lgkmcnt0();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  }
   static_for<NQ>([&](auto Q) {
     constexpr int q = decltype(Q)::value;
-    constexpr int i = q / PPB, p = q % PPB;
-    if constexpr (p == 0) {
-      static_for<T::FN>([&](auto J) {
+    constexpr int i = q / (NH * NJ * PPS), h = q / (NJ * PPS) % NH, jj = q / PPS % NJ, p = q % PPS;
+    // the accumulators hold the transposed 32x32 block (the MFMA is issued with its operands
+    // exchanged): lane -> row lane%32, registers 4g..4g+3 -> columns 8g + 4*(lane/32) + 0..3, so a lane
+    // stages four consecutive columns with one 16-byte write.
+    // No barrier: the staging region belongs to this wavefront alone and a wavefront's LDS
+    // operations complete in order.
+    if constexpr (T::SR == 16 && h == 0 && jj == 0 && p == 0) {
+      // Rows 0..15 of two neighbouring MFMA blocks come together: lanes 16..31 and 48..63 of the left block (its rows
+      // 16..31) change places with lanes 0..15 and 32..47 of the right one.  Then lane -> row lane%16, block (lane/16)%2.
+      static_for<T::FN / 2>([&](auto J) {
         constexpr int j = decltype(J)::value;
-        // the accumulators hold the transposed 32x32 block (the MFMA is issued with its operands
-        // exchanged): lane -> row lane%32, registers 4g..4g+3 -> columns 8g + 4*(lane/32) + 0..3, so a lane
-        // stages four consecutive columns with one 16-byte write
+#pragma unroll
+        for (int v = 0; v < 16; v++) {
+          const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[i][2 * j][v]), __float_as_uint(acc[i][2 * j + 1][v]),
+                                                           false, false);
+          acc[i][2 * j][v] = __uint_as_float(sw[0]);
+          acc[i][2 * j + 1][v] = __uint_as_float(sw[1]);
+        }
+      });
+    }
+    if constexpr (p == 0) {
+      auto put = [&](int row, int chunk, const f32x16& a) {
 #pragma unroll
         for (int g = 0; g < 4; g++)
-          *reinterpret_cast<float4*>(sC + (lane & 31) * T::CS + j * 32 + 8 * g + 4 * (lane >> 5)) =
-              make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
-      });
-      // No barrier: the staging region belongs to this wavefront alone and a wavefront's LDS
-      // operations complete in order.
+          *reinterpret_cast<f32x4*>(stage.at(row, chunk + 2 * g)) = f32x4{a[4 * g], a[4 * g + 1], a[4 * g + 2], a[4 * g + 3]};
+      };
+      if constexpr (T::SR == 32)
+        static_for<T::FN>([&](auto J) { put(lane & 31, decltype(J)::value * 8 + (lane >> 5), acc[i][decltype(J)::value]); });
+      else
+        put(lane & 15, (lane >> 4 & 1) * 8 + (lane >> 5), acc[i][2 * jj + h]);
     }
-    const int rl = p * RPP + rsub;
-    const int lm = wm * T::TM + i * 32 + rl;      // row inside the block tile
+    const int rl = p * RPP + rsub;                // row inside the piece
+    const int lm = row_of(q);                     // row inside the block tile
     float v[8];
     {
-      const float4 lo = *reinterpret_cast<const float4*>(sC + rl * T::CS + cg * 8);
-      const float4 hi = *reinterpret_cast<const float4*>(sC + rl * T::CS + cg * 8 + 4);
+      // (vector types: of a struct's member accesses the compiler would make each wait for the LDS loads in flight)
+      const f32x4 lo = *reinterpret_cast<const f32x4*>(stage.at(rl, 2 * cg));
+      const f32x4 hi = *reinterpret_cast<const f32x4*>(stage.at(rl, 2 * cg + 1));
       v[0] = lo.x; v[1] = lo.y; v[2] = lo.z; v[3] = lo.w;
       v[4] = hi.x; v[5] = hi.y; v[6] = hi.z; v[7] = hi.w;
     }
     if constexpr (PARTIAL) {
-      const uint32_t off = (uint32_t)(lm * ldC) + colC;
+      const uint32_t off = (uint32_t)(lm * ldC) + col_off(jj, 4u);
       const u32x4 lo = {__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])};
       const u32x4 hi = {__float_as_uint(v[4]), __float_as_uint(v[5]), __float_as_uint(v[6]), __float_as_uint(v[7])};
       __builtin_amdgcn_raw_buffer_store_b128(lo, rsC, (int)off, 0, 0);
@@ -234,12 +267,10 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T:
     } else {
       float rho = 1.f, rowb = 0.f;
       if (use_rho) {
-        float ss;
-        if constexpr (STAT_A) ss = sStat[lm];
-        else ss = ssv[q];
+        const float ss = ssv[STAT_A ? q : q % PF];
         rho = rho_sqrt ? sqrtf(ss * inv_d + eps) : rsqrtf(ss * inv_d + eps);
       }
-      if constexpr (BASE == EPI_NORMBWD) rowb = rbv[q];
+      if constexpr (BASE == EPI_NORMBWD) rowb = rbv[q % PF];
       float r[8], r2[8], v2[8];
       if constexpr (R_F32) {
         const u32x4 a0 = auxr[q % PF], a1 = auxr3[q % PF];
@@ -253,27 +284,27 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T:
       if constexpr (O32) {
         const u32x4 lo = {__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])};
         const u32x4 hi = {__float_as_uint(v[4]), __float_as_uint(v[5]), __float_as_uint(v[6]), __float_as_uint(v[7])};
-        const uint32_t off = (uint32_t)(lm * ldC32) + col4;
+        const uint32_t off = (uint32_t)(lm * ldC32) + col_off(jj, 4u);
         __builtin_amdgcn_raw_buffer_store_b128(lo, rsC32, (int)off, 0, 0);
         __builtin_amdgcn_raw_buffer_store_b128(hi, rsC32, (int)(off + 16u), 0, 0);
       }
       {
         const uint4 o = pack8(v);
         const u32x4 ov = {o.x, o.y, o.z, o.w};
-        __builtin_amdgcn_raw_buffer_store_b128(ov, rsC, (int)((uint32_t)(lm * ldC) + colC), 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(ov, rsC, (int)((uint32_t)(lm * ldC) + col_off(jj, 2u)), 0, 0);
       }
       if (want2) {
         const uint4 o = pack8(v2);
         const u32x4 ov = {o.x, o.y, o.z, o.w};
-        __builtin_amdgcn_raw_buffer_store_b128(ov, rsC2, (int)((uint32_t)(lm * ldC2) + col2), 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(ov, rsC2, (int)((uint32_t)(lm * ldC2) + col_off(jj, 2u)), 0, 0);
       }
-      if constexpr (q + PF < NQ) fetch(q + PF, auxr[q % PF], auxr2[q % PF], auxr3[R_F32 ? q % PF : 0]);
+      if constexpr (q + PF < NQ) fetch(q + PF, auxr[q % PF], auxr2[q % PF], auxr3[R_F32 ? q % PF : 0], ssv[q % PF], rbv[q % PF]);
       if constexpr (ROWPART) {
         part = lane_group_sum<LPP>(part);
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(part), rsPart, (int)((uint32_t)(lm * ldPart) + colPart), 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(part), rsPart, (int)((uint32_t)(lm * ldPart) + colPart + jj * (T::SC / (LPP * 8)) * 4), 0, 0);
       }
-      if constexpr (STAT_A)
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(sStat[lm]), rsStat, (int)((uint32_t)(lm * 4) + colStat), 0, 0);
+      if constexpr (STAT_A && jj == 0)
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ssv[q]), rsStat, (int)((uint32_t)(lm * 4) + colStat), 0, 0);
     }
   });
 }

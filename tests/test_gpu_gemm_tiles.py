@@ -108,6 +108,30 @@ def test_query_gradient_does_not_depend_on_the_tile():
             assert torch.equal(a, b[:t])
 
 
+# more tiles than CUs, so that a workgroup streams through several: a last round of few tiles, remainders of rows, columns and
+# k, tiles of other batch members, the shortest k that runs there
+@pytest.mark.parametrize("T,d,r,n,G", [(16385, 64, 1032, 4104, 1), (16640, 64, 520, 2568, 2), (33000, 72, 328, 2560, 3)])
+def test_stream_of_tiles(T, d, r, n, G):
+    print(f"stream T={T} r={r} n={n} G={G}", flush=True)
+    assert B.lr_gemm_tile(T, n, r, G, 0, 0) == T256 and -(-T // 256) * -(-n // 256) * G > 256
+    g = torch.Generator(device=DEV).manual_seed(21)
+    x, dy = torch.randn((T, d), generator=g, device=DEV).bfloat16(), torch.randn((G, T, n), generator=g, device=DEV).bfloat16()
+    wd = (torch.randn((G * r, d), generator=g, device=DEV) * d ** -0.5).bfloat16()
+    wu = (torch.randn((G, n, r), generator=g, device=DEV) * r ** -0.5).bfloat16()
+    gamma = torch.ones((d,), device=DEV).bfloat16()
+    z, s, y = B.lr_group_fwd(x, gamma, 1e-5, B.LR_NORM_NONE, wd, wu)
+    for rows in (slice(0, 300), slice(T // 2, T // 2 + 300), slice(T - 300, T)):      # on the small tiles
+        z1, _, y1 = B.lr_group_fwd(x[rows].contiguous(), gamma, 1e-5, B.LR_NORM_NONE, wd, wu)
+        assert torch.equal(z1, z[rows]) and torch.equal(y1, y[:, rows])
+    dwu = B.lr_group_bwd(x, gamma, 1e-5, B.LR_NORM_NONE, wd, wu, z, s, dy)[3]
+    for i in range(G):
+        act = z[:, i * r:(i + 1) * r].double()
+        ref = dy[i].double().T @ (act * torch.sigmoid(act)).bfloat16().double()
+        # sigma rounds to bf16 the other way for single entries (2^-9 of them relative, one in a thousand: below 1e-4 in the norm),
+        # fp32 sums over T tokens give sqrt(T) 2^-24 = 1e-5
+        assert float((dwu[i].double() - ref).norm() / ref.norm()) < 2e-4
+
+
 # one tile exactly, one row / column chunk more, remainders in every dimension, k shorter than a slice, several
 # splits of the token reduction, wide and narrow outputs
 EDGES = [(64, 64, 64, 64), (65, 72, 8, 136), (129, 264, 120, 520), (255, 1032, 200, 328), (2, 2048, 64, 2048),
