@@ -22,6 +22,10 @@ struct Ctx {
   // The workspace also holds what only makes a call faster (gathered partials, the row partials of a joint launch, sigma(z)
   // from the data gradient's epilogue).  A query asks for it; a caller whose workspace lacks it gets the same results without.
   bool roomy = true;
+  // Likewise: a block's d_ff wide rows in it start on cache lines (128 bytes), where that adds no more than a 64th to them.  The
+  // 256-row tiles' epilogues touch 128 bytes of a row at a time: two lines each where rows start anywhere.  16384 tokens, d_ff
+  // 5464 of d = 2048, us: SwiGLU forward with u stored 216 -> 207, SwiGLU backward 257 -> 220, the block's step 4170 -> 4094.
+  bool lines = true;
   int dt = LR_BF16;
   int gdt = LR_F32;          // dtype of the weight / gamma gradients
   hipStream_t st = nullptr;
@@ -43,6 +47,7 @@ struct Ctx {
     if (off > peak) peak = off;
     return p;
   }
+  int64_t wide_ld(int64_t f) const { return lines && (rup(f, 64) - f) * 64 <= f ? rup(f, 64) : f; }
   size_t mark() const { return off; }
   void release(size_t m) { off = m; }   // stack discipline: drop everything taken since mark()
   void run(hipError_t e) { if (err == hipSuccess && e != hipSuccess) err = e; }
@@ -662,10 +667,10 @@ double attn_unit_flops(const Blk& b) { return 2.0 * (double)b.B * b.H * (double)
 
 // z = in . w_dn^T (no norm), act = sigma(z)
 // (LaX: act = z + h_prev, identity gate)
-void single_down(Ctx& c, const Blk& b, const void* in, int64_t K, const void* w_dn, void* z, void* act, int lax = 0,
+void single_down(Ctx& c, const Blk& b, const void* in, int64_t ld, int64_t K, const void* w_dn, void* z, void* act, int lax = 0,
                  const void* h_prev = nullptr) {
   GemmOp dn;
-  dn.A = in; dn.lda = K; dn.B = w_dn; dn.ldb = K; dn.C = z; dn.ldc = b.r;
+  dn.A = in; dn.lda = ld; dn.B = w_dn; dn.ldb = K; dn.C = z; dn.ldc = b.r;
   dn.M = (int)b.T; dn.N = (int)b.r; dn.K = (int)K;
   dn.epi.kind = EPI_DOWN; dn.epi.act = b.act; dn.epi.C2 = act; dn.epi.ldc2 = b.r;
   if (lax) { dn.epi.kind = EPI_DOWN_LAX; dn.epi.R = h_prev; dn.epi.ldr = b.r; }
@@ -717,11 +722,11 @@ void single_up_bwd(Ctx& c, const Blk& b, const void* dout, int64_t N, const void
 // The gate / up pair of the MLP: g = act_g . W_up_g^T, then u = act_u . W_up_u^T whose epilogue forms
 // m = SiLU(g) * u from its fp32 accumulators and the g tile just written (the SwiGLU gate never
 // runs as a pass of its own).  u itself is stored only where a buffer is given: the forward has no use
-// for it, the backward's re-forward does.
-void mlp_up_swiglu(Ctx& c, const Blk& b, const void* w_up_gu, const void* act, void* g, void* u, void* m) {
+// for it, the backward's re-forward does.  ld: row stride of all three
+void mlp_up_swiglu(Ctx& c, const Blk& b, const void* w_up_gu, const void* act, void* g, void* u, void* m, int64_t ld) {
   const size_t es = 2;
   GemmOp up;
-  up.A = act; up.lda = 2 * b.r; up.B = w_up_gu; up.ldb = b.r; up.C = g; up.ldc = b.f;
+  up.A = act; up.lda = 2 * b.r; up.B = w_up_gu; up.ldb = b.r; up.C = g; up.ldc = ld;
   up.M = (int)b.T; up.N = (int)b.f; up.K = (int)b.r;
   up.epi.kind = EPI_STORE;
   gemm(c, up);
@@ -729,7 +734,7 @@ void mlp_up_swiglu(Ctx& c, const Blk& b, const void* w_up_gu, const void* act, v
   up.A = (const char*)act + (size_t)b.r * es;
   up.B = (const char*)w_up_gu + (size_t)b.f * b.r * es;
   up.C = u;
-  up.epi.kind = EPI_SWIGLU_FWD; up.epi.R = g; up.epi.ldr = b.f; up.epi.C2 = m; up.epi.ldc2 = b.f;
+  up.epi.kind = EPI_SWIGLU_FWD; up.epi.R = g; up.epi.ldr = ld; up.epi.C2 = m; up.epi.ldc2 = ld;
   gemm(c, up);
 }
 
@@ -769,13 +774,18 @@ void rope_qk(Ctx& c, const Blk& b, void* qkv, int inverse) {
                            inverse, c.st));
 }
 
+// The stride of d_ff wide rows that have room for `room` elements each.  Past 2 GB of rows a product that reduces over tokens
+// reads transposed copies: wider rows are not to bring that about.
+int64_t wide_stride(int64_t T, int64_t f, int64_t room) { return T * room * 2 < 0x7fffffffLL ? room : f; }
+
 // sv: optional; the wide activations then land in the caller's buffers (to be kept for a backward that
 // does not re-forward) instead of the workspace
 void block_fwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x, void* y, const lr_block_ckpt* ck,
                    const lr_block_lax* lx = nullptr, const lr_block_saved* sv = nullptr) {
   const int lax = lx != nullptr;
   const size_t es = 2;
-  const int64_t T = b.T, d = b.d, r = b.r, f = b.f;
+  const int64_t T = b.T, d = b.d, r = b.r, f = b.f, rowf = c.wide_ld(f);
+  const int64_t ldf = sv ? f : wide_stride(T, f, rowf);     // row stride of g, u and m
   const int64_t dkv = b.dkv;
   void* qkv = sv ? sv->qkv : c.take((size_t)T * (d + 2 * dkv) * es);     // q [T, d], k [T, dkv], v [T, dkv]
   void* o = sv ? sv->o : c.take((size_t)T * d * es);
@@ -783,9 +793,9 @@ void block_fwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   float* h1f = (float*)c.take((size_t)T * d * sizeof(float));   // h1 before rounding: the residual of y
   float* lse = sv ? sv->lse : (float*)c.take((size_t)b.B * b.H * b.S * sizeof(float));
   void* act = c.take((size_t)T * 3 * r * es);     // sigma(z) of whichever projection group is live
-  void* gg = sv ? sv->gu : c.take((size_t)T * f * es);
+  void* gg = sv ? sv->gu : c.take((size_t)T * rowf * es);
   void* uu = sv ? (void*)((char*)sv->gu + (size_t)T * f * es) : nullptr;   // u itself is kept only when saving
-  void* mm = sv ? sv->m : c.take((size_t)T * f * es);
+  void* mm = sv ? sv->m : c.take((size_t)T * rowf * es);
   // attention side
   GrpArgs a = qkv_group_args(b);
   a.x = x; a.gamma = p->gamma1; a.w_down_cat = p->w_dn_qkv; a.w_up_stack = p->w_up_qkv;
@@ -803,7 +813,7 @@ void block_fwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
                                      d, dkv, (int)b.B, (int)b.S, (int)b.H, (int)b.Hkv, (int)b.hd, b.causal, c.st));
     launch_timer_close(slot, c.st);
   }
-  single_down(c, b, o, d, p->w_dn_o, ck ? ck->z_o : nullptr, act, lax, lax ? lx->h_prev_o : nullptr);
+  single_down(c, b, o, d, d, p->w_dn_o, ck ? ck->z_o : nullptr, act, lax, lax ? lx->h_prev_o : nullptr);
   single_up(c, b, act, p->w_up_o, d, x, h1, ck ? ck->s2 : nullptr, h1f);   // h1 = x + ..., s2 = sum h1^2 from the epilogue
   // MLP side
   GrpArgs m = group_args(b, 2, f);
@@ -812,8 +822,8 @@ void block_fwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   m.lax = lax; m.h_prev = lax ? lx->h_prev_gu : nullptr;
   m.w_scaled_given = scaled; m.w_scaled = w_scaled ? w_scaled + (size_t)3 * r * d * es : nullptr;
   group_down_seq(c, m, act);
-  mlp_up_swiglu(c, b, p->w_up_gu, act, gg, uu, mm);
-  single_down(c, b, mm, f, p->w_dn_d, ck ? ck->z_d : nullptr, act, lax, lax ? lx->h_prev_d : nullptr);
+  mlp_up_swiglu(c, b, p->w_up_gu, act, gg, uu, mm, ldf);
+  single_down(c, b, mm, ldf, f, p->w_dn_d, ck ? ck->z_d : nullptr, act, lax, lax ? lx->h_prev_d : nullptr);
   single_up(c, b, act, p->w_up_d, d, nullptr, y, b.stat_y_out, nullptr, h1f);   // optionally sum y^2 for the block above
 }
 
@@ -826,7 +836,8 @@ void block_bwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   const lr_block_lax nlx{};
   if (!lx) lx = &nlx;
   const size_t es = 2;
-  const int64_t T = b.T, d = b.d, r = b.r, f = b.f;
+  const int64_t T = b.T, d = b.d, r = b.r, f = b.f, rowf = c.wide_ld(f);
+  const int64_t ldf = sv ? f : wide_stride(T, f, rowf);     // row stride of g, u, m, dg and du
   const lr_block_params np{};  // dry runs have no parameter structs
   const lr_block_ckpt nck{};
   if (!p) p = &np;
@@ -848,9 +859,9 @@ void block_bwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   void* h1 = sv ? sv->h1 : c.take((size_t)T * d * es);
   void* dh1 = c.take((size_t)T * d * es);
   float* dh1f = (float*)c.take((size_t)T * d * sizeof(float));   // dh1 before rounding: the residual of dx
-  void* big = sv ? sv->gu : c.take((size_t)2 * T * f * es);     // g,u  (later q,k,v: needs 3*T*d <= 2*T*f checked below)
-  void* big2 = c.take((size_t)2 * T * f * es);    // dg,du (later dq,dk,dv)
-  void* mm = sv ? sv->m : c.take((size_t)T * f * es);          // m, later o and do
+  void* big = sv ? sv->gu : c.take((size_t)2 * T * rowf * es);     // g,u  (later q,k,v: needs 3*T*d <= 2*T*f checked below)
+  void* big2 = c.take((size_t)2 * T * rowf * es);    // dg,du (later dq,dk,dv)
+  void* mm = sv ? sv->m : c.take((size_t)T * rowf * es);          // m, later o and do
   float* lse = sv ? sv->lse : (float*)c.take((size_t)b.B * b.H * b.S * sizeof(float));
   const int64_t dkv = b.dkv;
   void* qkv = big;
@@ -886,17 +897,18 @@ void block_bwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   if (!sv) single_up(c, b, act_o, p->w_up_o, d, x, h1, nullptr);
   GrpArgs m = group_args(b, 2, f);
   m.x = h1; m.gamma = p->gamma2; m.w_down_cat = p->w_dn_gu; m.w_up_stack = p->w_up_gu; m.y_stack = big;
-  if (!sv) mlp_up_swiglu(c, b, p->w_up_gu, act_g, big, (char*)big + (size_t)T * f * es, mm);
+  m.lddy = ldf; m.dy_bs = T * ldf;
+  if (!sv) mlp_up_swiglu(c, b, p->w_up_gu, act_g, big, (char*)big + (size_t)T * ldf * es, mm, ldf);
   c.flush();
   // down-D backward: dW_dn_d = dz_d^T . m ; dm = dz_d . W_dn_d with the SwiGLU reverse fused in
   c.hold();
-  wgrad(c, dz1, r, (int)r, mm, f, (int)f, T, g->w_dn_d, nullptr, accumulate);
+  wgrad(c, dz1, r, (int)r, mm, ldf, (int)f, T, g->w_dn_d, nullptr, accumulate);
   {
     GemmOp dm;
-    dm.A = dz1; dm.lda = r; dm.B = p->w_dn_d; dm.ldb = f; dm.transB = 1; dm.C = big2; dm.ldc = f;
+    dm.A = dz1; dm.lda = r; dm.B = p->w_dn_d; dm.ldb = f; dm.transB = 1; dm.C = big2; dm.ldc = ldf;
     dm.M = (int)T; dm.N = (int)f; dm.K = (int)r;
-    dm.epi.kind = EPI_SWIGLU_BWD; dm.epi.R = big; dm.epi.ldr = f; dm.epi.R2 = (char*)big + (size_t)T * f * es;
-    dm.epi.ldr2 = f; dm.epi.C2 = (char*)big2 + (size_t)T * f * es; dm.epi.ldc2 = f;
+    dm.epi.kind = EPI_SWIGLU_BWD; dm.epi.R = big; dm.epi.ldr = ldf; dm.epi.R2 = (char*)big + (size_t)T * ldf * es;
+    dm.epi.ldr2 = ldf; dm.epi.C2 = (char*)big2 + (size_t)T * ldf * es; dm.epi.ldc2 = ldf;
     gemm(c, dm);
   }
   c.flush();
@@ -1175,16 +1187,24 @@ int lr_group_bwd(const void* x, int64_t ldx, const void* gamma, float eps, int n
 
 
 // ---- block -----------------------------------------------------------------------------------
-static size_t block_bytes(const Blk& b, int backward, const lr_block_saved* sv, bool roomy) {
-  Ctx c; c.dry = true; c.dt = LR_BF16; c.roomy = roomy;
+static size_t block_bytes(const Blk& b, int backward, const lr_block_saved* sv, bool roomy = true, bool lines = true) {
+  Ctx c; c.dry = true; c.dt = LR_BF16; c.roomy = roomy; c.lines = lines;
   lr_block_params np{};
   if (backward) block_bwd_seq(c, b, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, sv);
   else block_fwd_seq(c, b, &np, nullptr, nullptr, nullptr, nullptr, sv);
   return c.peak + 256;
 }
+// A workspace of the query's size, or less: without rows on cache lines, then also without the rest of what a call can do without.
+static int check_block_ws(Ctx& c, const Blk& b, int backward, const lr_block_saved* sv, void* ws, size_t have) {
+  c.base = (char*)ws; c.cap = have; c.dt = LR_BF16; c.gdt = b.gdt;
+  size_t need = block_bytes(b, backward, sv);
+  if (have < need && c.wide_ld(b.f) != b.f) need = block_bytes(b, backward, sv, true, c.lines = false);
+  if (have < need && backward) need = block_bytes(b, backward, sv, c.roomy = false, c.lines = false);
+  return check_ws(ws, have, need);
+}
 size_t lr_block_workspace_bytes(const lr_block_desc* desc, int backward) {
   Blk b; int why;
-  return block_desc_ok(desc, b, &why) ? block_bytes(b, backward, nullptr, true) : 0;
+  return block_desc_ok(desc, b, &why) ? block_bytes(b, backward, nullptr) : 0;
 }
 
 size_t lr_block_ckpt_bytes(const lr_block_desc* desc) {
@@ -1211,8 +1231,8 @@ int lr_block_fwd(const lr_block_desc* desc, const lr_block_params* params, const
   if (!block_desc_ok(desc, b, &why)) return why;
   TRY(check_params(params)); TRY(check_ckpt(ckpt));
   TRY(check_ptrs(LR_BF16, {x, y}));
-  TRY(check_ws(ws, ws_bytes, lr_block_workspace_bytes(desc, 0)));
-  Ctx c; c.base = (char*)ws; c.cap = ws_bytes; c.dt = LR_BF16; c.st = (hipStream_t)stream;
+  Ctx c; c.st = (hipStream_t)stream;
+  TRY(check_block_ws(c, b, 0, nullptr, ws, ws_bytes));
   block_fwd_seq(c, b, params, x, y, ckpt);
   return c.err == hipErrorNotSupported ? LR_EUNSUPPORTED : status_of(c);
 }
@@ -1224,9 +1244,8 @@ int lr_block_bwd(const lr_block_desc* desc, const lr_block_params* params, const
   if (!block_desc_ok(desc, b, &why)) return why;
   TRY(check_params(params)); TRY(check_params(grads)); TRY(check_ckpt(ckpt));
   TRY(check_ptrs(LR_BF16, {x, dy, dx}));
-  bool roomy;
-  TRY(check_ws(ws, ws_bytes, [&](bool all) { return block_bytes(b, 1, nullptr, all); }, roomy));
-  Ctx c; c.roomy = roomy; c.base = (char*)ws; c.cap = ws_bytes; c.dt = LR_BF16; c.gdt = b.gdt; c.st = (hipStream_t)stream;
+  Ctx c; c.st = (hipStream_t)stream;
+  TRY(check_block_ws(c, b, 1, nullptr, ws, ws_bytes));
   block_bwd_seq(c, b, params, x, dy, ckpt, dx, grads, accumulate);
   return c.err == hipErrorNotSupported ? LR_EUNSUPPORTED : status_of(c);
 }
@@ -1235,7 +1254,7 @@ int lr_block_bwd(const lr_block_desc* desc, const lr_block_params* params, const
 size_t lr_block_saved_workspace_bytes(const lr_block_desc* desc, int backward) {
   Blk b; int why;
   const lr_block_saved nsv{};
-  return block_desc_ok(desc, b, &why) ? block_bytes(b, backward, &nsv, true) : 0;
+  return block_desc_ok(desc, b, &why) ? block_bytes(b, backward, &nsv) : 0;
 }
 
 static int check_saved(const lr_block_saved* sv) {
@@ -1251,8 +1270,8 @@ int lr_block_fwd_save(const lr_block_desc* desc, const lr_block_params* params, 
   if (!block_desc_ok(desc, b, &why)) return why;
   TRY(check_params(params)); TRY(check_ckpt(ckpt)); TRY(check_saved(saved));
   TRY(check_ptrs(LR_BF16, {x, y}));
-  TRY(check_ws(ws, ws_bytes, lr_block_saved_workspace_bytes(desc, 0)));
-  Ctx c; c.base = (char*)ws; c.cap = ws_bytes; c.dt = LR_BF16; c.st = (hipStream_t)stream;
+  Ctx c; c.st = (hipStream_t)stream;
+  TRY(check_block_ws(c, b, 0, saved, ws, ws_bytes));
   block_fwd_seq(c, b, params, x, y, ckpt, nullptr, saved);
   return status_of(c);
 }
@@ -1264,10 +1283,8 @@ int lr_block_bwd_saved(const lr_block_desc* desc, const lr_block_params* params,
   if (!block_desc_ok(desc, b, &why)) return why;
   TRY(check_params(params)); TRY(check_params(grads)); TRY(check_ckpt(ckpt)); TRY(check_saved(saved));
   TRY(check_ptrs(LR_BF16, {x, dy, dx}));
-  const lr_block_saved nsv{};
-  bool roomy;
-  TRY(check_ws(ws, ws_bytes, [&](bool all) { return block_bytes(b, 1, &nsv, all); }, roomy));
-  Ctx c; c.roomy = roomy; c.base = (char*)ws; c.cap = ws_bytes; c.dt = LR_BF16; c.gdt = b.gdt; c.st = (hipStream_t)stream;
+  Ctx c; c.st = (hipStream_t)stream;
+  TRY(check_block_ws(c, b, 1, saved, ws, ws_bytes));
   block_bwd_seq(c, b, params, x, dy, ckpt, dx, grads, accumulate, nullptr, saved);
   return status_of(c);
 }
@@ -1290,8 +1307,8 @@ int lr_block_lax_fwd(const lr_block_desc* desc, const lr_block_params* params, c
   TRY(check_lax(desc, lax));
   TRY(check_params(params)); TRY(check_ckpt(ckpt));
   TRY(check_ptrs(LR_BF16, {x, y}));
-  TRY(check_ws(ws, ws_bytes, lr_block_workspace_bytes(desc, 0)));
-  Ctx c; c.base = (char*)ws; c.cap = ws_bytes; c.dt = LR_BF16; c.st = (hipStream_t)stream;
+  Ctx c; c.st = (hipStream_t)stream;
+  TRY(check_block_ws(c, b, 0, nullptr, ws, ws_bytes));
   block_fwd_seq(c, b, params, x, y, ckpt, lax);
   return c.err == hipErrorNotSupported ? LR_EUNSUPPORTED : status_of(c);
 }
@@ -1304,9 +1321,8 @@ int lr_block_lax_bwd(const lr_block_desc* desc, const lr_block_params* params, c
   TRY(check_lax(desc, lax));
   TRY(check_params(params)); TRY(check_params(grads)); TRY(check_ckpt(ckpt));
   TRY(check_ptrs(LR_BF16, {x, dy, dx}));
-  bool roomy;
-  TRY(check_ws(ws, ws_bytes, [&](bool all) { return block_bytes(b, 1, nullptr, all); }, roomy));
-  Ctx c; c.roomy = roomy; c.base = (char*)ws; c.cap = ws_bytes; c.dt = LR_BF16; c.gdt = b.gdt; c.st = (hipStream_t)stream;
+  Ctx c; c.st = (hipStream_t)stream;
+  TRY(check_block_ws(c, b, 1, nullptr, ws, ws_bytes));
   block_bwd_seq(c, b, params, x, dy, ckpt, dx, grads, accumulate, lax);
   return c.err == hipErrorNotSupported ? LR_EUNSUPPORTED : status_of(c);
 }

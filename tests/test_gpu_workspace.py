@@ -124,6 +124,34 @@ def test_block(shape, need, need_saved, form):
     _same(call, [dx, *grads.values()], need, query)
 
 
+@pytest.mark.parametrize("f", [2600, 2624, 1376])     # rows that get room up to a cache line, that end on one, that would grow by 2 %
+def test_block_without_room_for_rows_on_cache_lines(f):
+    """Forward and backward in the query's size less the ends of g, u, m, dg and du: accepted, the same bits, nothing past the end."""
+    Bn, S, H, r = 2, 640, 4, 136
+    T, d, pad = Bn * S, 128 * H, 24 if f == 2600 else 0
+    print(f"block in the room of unpadded rows, f={f}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(f)
+    shapes = {"gamma1": (d,), "w_dn_qkv": (3 * r, d), "w_up_qkv": (3, d, r), "w_dn_o": (r, d), "w_up_o": (d, r), "gamma2": (d,),
+              "w_dn_gu": (2 * r, d), "w_up_gu": (2, f, r), "w_dn_d": (r, f), "w_up_d": (d, r)}
+    p = {n: (torch.randn(s, generator=g, device=DEV) * s[-1] ** -0.5).bfloat16() for n, s in shapes.items()}
+    x, dy = (torch.randn((T, d), generator=g, device=DEV).bfloat16() for _ in range(2))
+    desc = B.make_block_desc(Bn, S, d, H, 128, f, f, r)
+    lib, ps, ck, y, dx = B.lib(), B._params_struct(p), B.alloc_block_ckpt(desc, x.device), torch.empty_like(x), torch.empty_like(x)
+    grads = {n: torch.empty_like(t, dtype=torch.float32) for n, t in p.items()}
+    cs, gs = B._ckpt_struct(ck), B._params_struct(grads)
+
+    def fwd(ws, size):
+        return lib.lr_block_fwd(C.byref(desc), C.byref(ps), x.data_ptr(), y.data_ptr(), C.byref(cs), ws, size, _stream())
+
+    def bwd(ws, size):
+        return lib.lr_block_bwd(C.byref(desc), C.byref(ps), x.data_ptr(), dy.data_ptr(), C.byref(cs), dx.data_ptr(), C.byref(gs), 1, ws, size,
+                                _stream())
+
+    for call, outs, rows in ((fwd, [y, *ck.values()], 2), (bwd, [dx, *grads.values()], 5)):
+        query = B.lr_block_workspace_bytes(desc, int(call is bwd))
+        _same(call, outs, query - rows * T * pad * 2, query)
+
+
 def test_rows_that_span_more_than_2_gib():
     """x and dy as columns of a 2.6 GB tensor: refused in the workspace of dense rows, and with the room for copies the gradients of
     dense rows.  Each is a chained sum of T exact products in both: off by at most T 2^-24 of the sum of their magnitudes."""
