@@ -92,7 +92,7 @@ constexpr int epilogue_stores() {
 //             slices are stored in LDS as they arrive, [k][m], and the MFMA operands are gathered
 //             with the LDS transpose read, so no transposed copy of an activation is ever written.
 template <class T, int KIND, bool STAT_A, bool KM>
-__global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, int tiles_m, int tiles_n, int total) {
+__global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, int tiles_m, int tiles_n, int total, int stagger) {
   static_assert(!KM || ((KIND == EPI_PARTIAL || KIND == EPI_STORE) && !STAT_A && T::BM == 256 && T::BN % 128 == 0),
                 "the k-major form serves split-K weight gradients and plain stores");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -106,6 +106,8 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, i
   const int bid = blockIdx.x + gridDim.x * blockIdx.y, nwg = gridDim.x * gridDim.y;
   const int xcd = bid % NXCD;
   const int step = nwg / NXCD + (xcd < nwg % NXCD ? 1 : 0);             // workgroups on this XCD
+  // (see launch)
+  for (int i = 0; i < xcd * stagger; i++) __builtin_amdgcn_s_sleep(16);
   const int tiles_first = xcd * (total / NXCD) + min(xcd, total % NXCD);
   const int tiles_end = tiles_first + total / NXCD + (xcd < total % NXCD ? 1 : 0);
 
@@ -447,7 +449,16 @@ hipError_t launch(const GemmOp& op, hipStream_t st) {
   const int64_t total = (int64_t)tiles_m * tiles_n * op.batch * op.splitk;
   // causal k ranges differ from tile to tile: a workgroup each, dealt out as CUs become free
   const dim3 grid = op.causal_k || total <= NCU ? tile_grid(tiles_m * tiles_n, op.batch * op.splitk) : dim3(NCU);
-  hipLaunchKernelGGL(kern, grid, dim3(T::NT), T::LDS_BYTES, st, op, kper, tiles_m, tiles_n, (int)total);
+  // SwiGLU epilogues move up to 512 KB per tile, 134 MB of a round of 256 tiles, 25 of its 48 us at k = 1024, with the matrix pipes
+  // idle; then all main loops leave memory idle.  The XCDs start 3/4 of a slice's cycles per slice of k apart (units of 1024
+  // cycles), and one's epilogues run beside the others' main loops: about 6 us off a round for a start that is 2.3 us per
+  // slice longer.  us, together -> apart: 16384 x 11008 x 1024 SwiGLU forward 425 -> 406, with u stored 507 -> 481, backward
+  // 530 -> 501; 16384 x 5464 x 512 163 -> 160, 209 -> 199, 222 -> 211.  Of other kinds and fewer rounds the start costs more
+  // (16384 x 4096 x 2048, norm's reverse 341 -> 350, plain stores of k = 1024 320 -> 340).
+  const int nk = kper / BK;
+  const bool swiglu = KIND == EPI_SWIGLU_FWD || KIND == EPI_SWIGLU_BWD;
+  const int stagger = swiglu && grid.y == 1 && total / NCU * 16 >= nk * 9 ? nk * 3 / 4 : 0;
+  hipLaunchKernelGGL(kern, grid, dim3(T::NT), T::LDS_BYTES, st, op, kper, tiles_m, tiles_n, (int)total, stagger);
   return hipGetLastError();
 }
 
