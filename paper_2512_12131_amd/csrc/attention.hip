@@ -1193,6 +1193,248 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_long_kernel(const uint16_t* 
   wait_vm0();                                              // no load into LDS outlives the workgroup
 }
 
+// ----------------------------------------------------------------------------------------------
+// backward, dK and dV of 256 keys where the score gradient is not kept and there is work for the chip (dkv_pairs below): pairs of
+// wavefronts share 64 keys and walk 32-query blocks together, one forming S, P and dV, the other dP, dS and dK
+//
+// Bound: what one wavefront of a SIMD does while the other's MFMAs run.  A wavefront that does all of a key block's work holds dK,
+// dV, K and V of 32 keys (192 registers): it is alone on its SIMD, its MFMAs and its vector arithmetic follow each other (matrix pipes
+// 35 % busy in the kernel above), and each MFMA needs an operand of its own from LDS.  Split by what is formed, a wavefront holds one
+// of dK and dV and one of K and V, and that of 64 keys (192 registers again): every operand read from LDS feeds two MFMAs, and the
+// wavefronts w and w + 4 of a pair sit on one SIMD.  What passes between them is P, as the fp32 values that dS is formed
+// from (8 KB per block, twice buffered): one barrier per block.  The sums over queries and over h are those of the other
+// dK / dV kernels, in the same order: the same bits.
+// Whole backward, us, the other kernels -> this one: 2 x 2047 tokens, 32 / 8 heads 338 -> 308; 2 x 1501, 32 heads 245 -> 224; 4 x 4095, 8
+// heads 524 -> 497; 1 x 12001, 8 heads 1237 -> 1147; 16 x 300, 16 heads 115 -> 101; 16 x 500, 32 heads 327 -> 316.
+// With the score gradient stored as well the stores were what it waited for (8 x 2048, 16 heads 621 -> 634): not done there.
+// ----------------------------------------------------------------------------------------------
+constexpr int PAIR_NS = 5;                                       // ring of 32-query blocks: one or two in use, three on their way
+constexpr int PAIR_BLOCK = 2 * 32 * HD * 2 + 512;                // Q rows, dO rows, lse2, D (64 entries each, 32 used)
+constexpr int PAIR_X = PAIR_NS * PAIR_BLOCK;                     // P of the four pairs, two blocks
+constexpr int PAIR_NONE = PAIR_X + 2 * 4 * 8192;                 // a place for what nobody reads
+constexpr int PAIR_LDS = PAIR_NONE + 256;
+constexpr int PAIR_D = 2;                                        // LDS operands are read this many pairs of MFMAs ahead
+static_assert(PAIR_BLOCK % 256 == 0 && PAIR_LDS <= 160 * 1024, "LDS of a CU");
+
+__global__ __launch_bounds__(512) void attn_bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+                                                                const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
+                                                                const float* __restrict__ lse2, const float* __restrict__ D,
+                                                                uint16_t* __restrict__ dk, uint16_t* __restrict__ dv,
+                                                                int64_t ld, int64_t ldkv, int64_t lddkv, int grp, int S, int H,
+                                                                float scale) {
+  extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
+  constexpr int BN = 256;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int pair = wave & 3;
+  const bool second = wave >= 4;                           // dP, dS, dK; otherwise S, P, dV
+  const int nkb = (S + BN - 1) / BN;
+  const WgCoord wg = wg_coord();
+  const int head = wg.head, b = wg.b;
+  const int64_t tok0 = (int64_t)b * S, hoff = head * HD, kvoff = (head / grp) * HD;
+  const float c = scale * LOG2E;
+  const rsrc_t rsQ = rows_rsrc(q + tok0 * ld + hoff, S, ld);
+  const rsrc_t rsO = rows_rsrc(dout + tok0 * ld + hoff, S, ld);
+  const rsrc_t rsLD = make_rsrc((wave == 0 ? lse2 : D) + ((int64_t)b * H + head) * S, (wave & 3) == 0 ? (uint32_t)S * 4u : 0u);
+  uint32_t offT[2];
+  {
+    int row[2];
+    dma_lane_offsets<SWZ_BOTH, 2>(offT, row, ld, wave, lane);
+  }
+  const uint32_t lds0 = (uint32_t)(uintptr_t)LRB_LDS_PTR(smem);
+  const int qblocks = (S + 31) / 32;
+  // The three loads of a wavefront for 32-query block qb (of the sequence): four rows of Q, four of dO, the scalars or nothing.
+  // Rows past S, and whole blocks past it, read as zeros.
+  auto dma = [&](int slot, int qb) {
+    const bool valid = qb < qblocks;
+    const uint32_t p = lds0 + (uint32_t)slot * PAIR_BLOCK, off = (uint32_t)qb * 64u * (uint32_t)ld;
+    lds_dma_at(rsrc_from(rsQ, off, valid), p + (uint32_t)wave * 1024u, offT[0]);
+    lds_dma_at(rsrc_from(rsO, off, valid), p + 8192u + (uint32_t)wave * 1024u, offT[0]);
+    lds_dma4_at(rsLD, (wave & 3) == 0 ? p + 16384u + (uint32_t)(wave >> 2) * 256u : lds0 + PAIR_NONE, (uint32_t)(qb * 32 + lane) * 4u);
+  };
+  uint32_t rowl, trl;
+  {
+    const int l31 = lane & 31, f = ((l31 & 3) << 2) | ((l31 >> 2) & 3), g = lane >> 4, s = lane & 15;
+    rowl = (uint32_t)(l31 * 256 + (((lane >> 5) ^ f) << 4));
+    trl = (uint32_t)(((g >> 1) * 4 + (s >> 2)) * 256 + ((((g & 1) * 2 + ((s & 3) >> 1)) ^ (((s >> 2) << 2) | (g >> 1))) << 4) + (s & 1) * 8);
+  }
+  // one key block from the early end (most queries) and its mirror image from the late end: equal work per workgroup
+  for (int pass = 0; pass < 2; pass++) {
+    const int kblk = pass == 0 ? wg.x : nkb - 1 - wg.x;
+    if (pass == 1 && ((int)gridDim.x == nkb || kblk <= wg.x)) break;   // (unpaired launch: see the forward)
+    const int n0 = kblk * BN, nw0 = n0 + pair * 64;
+    wait_vm0();                                            // the pass before: its last loads, and everyone done with the ring
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    // K or V rows of the pair's keys stay in registers (B operands); rows past S read as zeros.
+    bf16x8 kv[2][8];
+    {
+      const __amdgpu_buffer_rsrc_t rsKV = __builtin_amdgcn_make_buffer_rsrc(
+          (void*)((second ? v : k) + tok0 * ldkv + kvoff), 0, (uint32_t)(S - 1) * (uint32_t)ldkv * 2u + 256u, 0x00020000);
+      const uint32_t off = (uint32_t)(nw0 + (lane & 31)) * (uint32_t)ldkv * 2u + (uint32_t)(lane >> 5) * 16u;
+#pragma unroll
+      for (int nb = 0; nb < 2; nb++)
+#pragma unroll
+        for (int ks = 0; ks < 8; ks++)
+          kv[nb][ks] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
+              rsKV, (int)(off + (uint32_t)(nb * 32) * (uint32_t)ldkv * 2u + (uint32_t)ks * 32u), 0, 0));
+    }
+    f32x16 acc[2][4];                                      // dK^T or dV^T
+#pragma unroll
+    for (int nb = 0; nb < 2; nb++)
+#pragma unroll
+      for (int hb = 0; hb < 4; hb++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) acc[nb][hb][e] = 0.f;
+    const int qb0 = n0 / 32, n = qblocks - qb0;            // causal: the first block that sees key n0, how many there are
+    for (int i = 0; i < PAIR_NS - 1; i++) dma(i, qb0 + i);
+    wait_vm<9>();                                          // block 0 has landed
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    int slot = 0, spare = PAIR_NS - 1;                     // of block i, and where block i + 4 goes
+
+    // Operand addresses inside a SWZ_BOTH block (both_row_frag, both_tr_frag): the lane's part, from which the k16 step or the
+    // 32 columns differ by an XOR.  (Blocks are multiples of 256 bytes; with the block added first nothing but the lane's part
+    // is kept over the loop.)
+    auto row_frag = [&](uint32_t blk, int ks) -> bf16x8 { return lds_b128(smem + ((blk + rowl) ^ (uint32_t)(ks << 5))); };
+    auto tr_frag = [&](uint32_t blk, int t, int hb) -> bf16x8 {
+      typedef short s16x8 __attribute__((ext_vector_type(8)));
+      const uint32_t at = (blk + trl) ^ (uint32_t)(hb << 6);
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(smem + at + t * 4096));
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(smem + (at ^ 32u) + t * 4096 + 2048));
+      const s16x8 r = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+      return __builtin_bit_cast(bf16x8, r);
+    };
+    // scores of the block at blk (its Q or dO rows): 32 queries x 32 NB keys
+    auto scores = [&](uint32_t blk, f32x16 (&x)[2], auto NB) {
+#pragma unroll
+      for (int nb = 0; nb < decltype(NB)::value; nb++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) x[nb][e] = 0.f;
+      bf16x8 f[PAIR_D + 1];
+      unroll_for<PAIR_D>([&](auto I) { f[decltype(I)::value] = row_frag(blk, decltype(I)::value); });
+      unroll_for<8>([&](auto I) {
+        constexpr int ks = decltype(I)::value;
+        if constexpr (ks + PAIR_D < 8) f[(ks + PAIR_D) % (PAIR_D + 1)] = row_frag(blk, ks + PAIR_D);
+#pragma unroll
+        for (int nb = 0; nb < decltype(NB)::value; nb++)
+          x[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[ks % (PAIR_D + 1)], kv[nb][ks], x[nb], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    };
+    // acc += columns of the block at blk (its dO or Q rows) times what was made of the scores
+    auto outputs = [&](uint32_t blk, const bf16x8 (&w)[2][2], auto NB) {
+      bf16x8 f[PAIR_D + 1];
+      unroll_for<PAIR_D>([&](auto I) { f[decltype(I)::value] = tr_frag(blk, 0, decltype(I)::value); });
+      unroll_for<8>([&](auto I) {
+        constexpr int s = decltype(I)::value, a = s + PAIR_D;
+        if constexpr (a < 8) f[a % (PAIR_D + 1)] = tr_frag(blk, a >> 2, a & 3);
+#pragma unroll
+        for (int nb = 0; nb < decltype(NB)::value; nb++)
+          acc[nb][s & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[s % (PAIR_D + 1)], w[nb][s >> 2], acc[nb][s & 3], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    };
+    // Between the first and the second half of block i: this wavefront's loads of block i + 1 have landed, everyone is done
+    // with block i - 1.  Behind those loads lie the ones of two more blocks.
+    auto meet = [&](int i) {
+      wait_lgkm0();
+      wait_vm<6>();
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      dma(spare, qb0 + i + PAIR_NS - 1);
+    };
+    auto next = [&]() {
+      spare = slot;
+      slot = slot + 1 == PAIR_NS ? 0 : slot + 1;
+    };
+    // Blocks of this pass: those before the pair's keys, the one that sees the first 32 of them (and only those: what the other 32
+    // would add is 0 times it, NaN where it is not finite), the one with the other 32 keys' diagonal, whole ones, perhaps one with
+    // the last queries.  Loops of their own: a branch around part of a block's work would have the accumulators change registers.
+    const int skip = min(pair * 2, n), half = min(skip + 1, n), diag = min(skip + 2, n), whole = max(diag, S / 32 - qb0);
+    constexpr std::integral_constant<int, 1> one{};
+    constexpr std::integral_constant<int, 2> two{};
+    int i = 0;
+    for (; i < skip; i++) {
+      meet(i);
+      next();
+    }
+    if (!second) {
+      auto block = [&](auto MASKED, auto NB) {
+        const uint32_t blk = (uint32_t)slot * PAIR_BLOCK;
+        f32x16 x[2];
+        scores(blk, x, NB);
+        const float* sl = reinterpret_cast<const float*>(smem + blk + 16384);
+        unsigned char* xp = smem + PAIR_X + (i & 1) * 32768 + pair * 8192 + lane * 16;
+        bf16x8 w[2][2];
+        unroll_for<4>([&](auto G) {
+          constexpr int g = decltype(G)::value;
+          const f32x4 lv = *reinterpret_cast<const f32x4*>(sl + 8 * g + 4 * (lane >> 5));
+#pragma unroll
+          for (int nb = 0; nb < decltype(NB)::value; nb++) {
+            f32x4 p;
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+              p[r] = fast_exp2(fmaf(x[nb][4 * g + r], c, -lv[r]));
+              if constexpr (decltype(MASKED)::value) {
+                const int qi = (qb0 + i) * 32 + acc_row(4 * g + r, lane), ni = nw0 + nb * 32 + (lane & 31);
+                p[r] = (ni > qi || qi >= S) ? 0.f : p[r];
+              }
+            }
+            *reinterpret_cast<f32x4*>(xp + (nb * 4 + g) * 1024) = p;
+#pragma unroll
+            for (int r = 0; r < 4; r++) x[nb][4 * g + r] = p[r];
+          }
+          if constexpr (g & 1)
+#pragma unroll
+            for (int nb = 0; nb < decltype(NB)::value; nb++) w[nb][g >> 1] = pack_acc_half(x[nb], g >> 1);
+          __builtin_amdgcn_sched_barrier(0);
+        });
+        meet(i);
+        outputs(blk + 8192, w, NB);
+        next();
+      };
+      for (; i < half; i++) block(std::true_type{}, one);
+      for (; i < diag; i++) block(std::true_type{}, two);
+      for (; i < whole; i++) block(std::false_type{}, two);
+      for (; i < n; i++) block(std::true_type{}, two);
+    } else {
+      auto block = [&](auto NB) {
+        const uint32_t blk = (uint32_t)slot * PAIR_BLOCK;
+        f32x16 x[2];
+        scores(blk + 8192, x, NB);
+        meet(i);
+        const float* sd = reinterpret_cast<const float*>(smem + blk + 16384 + 256);
+        const unsigned char* xp = smem + PAIR_X + (i & 1) * 32768 + pair * 8192 + lane * 16;
+        bf16x8 w[2][2];
+        unroll_for<4>([&](auto G) {
+          constexpr int g = decltype(G)::value;
+          const f32x4 dvv = *reinterpret_cast<const f32x4*>(sd + 8 * g + 4 * (lane >> 5));
+#pragma unroll
+          for (int nb = 0; nb < decltype(NB)::value; nb++) {
+            const f32x4 p = *reinterpret_cast<const f32x4*>(xp + (nb * 4 + g) * 1024);
+#pragma unroll
+            for (int r = 0; r < 4; r++) x[nb][4 * g + r] = p[r] * (x[nb][4 * g + r] - dvv[r]);   // dS
+          }
+          if constexpr (g & 1)
+#pragma unroll
+            for (int nb = 0; nb < decltype(NB)::value; nb++) w[nb][g >> 1] = pack_acc_half(x[nb], g >> 1);
+          __builtin_amdgcn_sched_barrier(0);
+        });
+        outputs(blk, w, NB);
+        next();
+      };
+      for (; i < half; i++) block(one);
+      for (; i < n; i++) block(two);
+    }
+#pragma unroll
+    for (int nb = 0; nb < 2; nb++) {
+      const int ni = nw0 + nb * 32 + (lane & 31);
+      if (ni < S) store_acc_T((second ? dk : dv) + (tok0 + ni) * lddkv + hoff, acc[nb], second ? scale : 1.f, lane);
+    }
+  }  // pass
+  wait_vm0();                                              // no load into LDS outlives the workgroup
+}
+
 // Grouped-query attention: a key / value head's gradient is the sum of the contributions of the grp
 // query heads that share it.  part: two [T, H * HD] bf16 tensors (dK, then dV contributions, one per
 // query head), out: dk / dv [T, ldkv].  One thread adds grp 16-byte vectors in fp32.
@@ -1284,6 +1526,17 @@ size_t attention_gqa_bwd_ws_bytes(int B, int S, int H, int Hkv, int hd) {
 
 constexpr int DKV_NB = 1;   // 32-key blocks per wavefront in the dK/dV kernel
 
+// 256 keys per workgroup, in pairs of blocks, or 128: a workgroup of twice the keys takes 0.91 to 0.97 of two workgroups' time, so it
+// pays where the launch is half as many rounds of the chip or fewer, and from 144 workgroups on (fewer were not measured).  Whole
+// backward, this kernel against the others, % (rounds, this one's first): 2 x 2047 tokens, 32 heads -8.9 (1, 2), 2 x 2999, 12 heads -8.5
+// (1, 2), 16 x 259, 32 heads -9.3 (2, 4), 7 x 1283, 32 heads -6.2 (3, 6); 8 x 1129, 32 heads -3.8 (3, 5), 20 x 1001, 16 heads -1.8 (3, 5),
+// 3 x 1801, 32 heads +1.4 (2, 3), 16 x 700, 16 heads +3.9 (2, 3), 1 x 6001, 24 heads +7.1 (2, 3), 13 x 641, 32 heads +8.8 (4, 5), 1 x 3333,
+// 16 heads, a block per workgroup, +17 (1, 1).
+static bool dkv_pairs(int S, int64_t heads) {
+  const int64_t wide = (S + 255) / 256, wgs = (wide + 1) / 2 * heads, other = ((S + 127) / 128 + 1) / 2 * heads;
+  return wide * heads > 256 && wgs >= 144 && 2 * ((wgs + 255) / 256) <= (other + 255) / 256;
+}
+
 hipError_t attention_bwd_bf16(const void* q, const void* k, const void* v, const void* o, const void* dout,
                               const float* lse, void* dq, void* dk, void* dv, int64_t ld, int B, int S, int H, int hd,
                               int causal, void* ws, hipStream_t st) {
@@ -1302,6 +1555,7 @@ hipError_t attention_gqa_bwd_bf16(const void* q, const void* k, const void* v, c
     hipError_t e = set_lds(attn_bwd_dq_kernel<1>, DQ_LDS);
     if (e == hipSuccess) e = set_lds(attn_bwd_dq_kernel<2>, DQ_LDS);
     if (e == hipSuccess) e = set_lds(attn_bwd_dkv_long_kernel, LDKV_LDS);
+    if (e == hipSuccess) e = set_lds(attn_bwd_dkv_pair_kernel, PAIR_LDS);
     if (e == hipSuccess) e = set_lds(attn_bwd_dkv_kernel<DKV_NB, false>, DKV_LDS);
     if (e == hipSuccess) e = set_lds(attn_bwd_dkv_kernel<DKV_NB, true>, DKV_LDS);
     return e;
@@ -1364,7 +1618,11 @@ hipError_t attention_gqa_bwd_bf16(const void* q, const void* k, const void* v, c
   const int64_t heads = (int64_t)H * B;
   if ((S + 127) / 128 * heads <= 256) dq_launch(std::integral_constant<int, 1>{}, false);
   else dq_launch(std::integral_constant<int, 2>{}, (S + 255) / 256 * heads > 256);
-  if (S >= ((int)kv_grid.x == nkb ? LDKV_MIN_S : LDKV_MIN_S_PAIRED))
+  if (dkv_pairs(S, heads))
+    hipLaunchKernelGGL(attn_bwd_dkv_pair_kernel, dim3(((S + 255) / 256 + 1) / 2, H, B), dim3(512), PAIR_LDS, st, (const uint16_t*)q,
+                       (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout, lse2, D, dk_w, dv_w, ld, ldkv, lddkv, grp, S, H,
+                       scale);
+  else if (S >= ((int)kv_grid.x == nkb ? LDKV_MIN_S : LDKV_MIN_S_PAIRED))
     hipLaunchKernelGGL(attn_bwd_dkv_long_kernel, kv_grid, dim3(256), LDKV_LDS, st, (const uint16_t*)q, (const uint16_t*)k,
                        (const uint16_t*)v, (const uint16_t*)dout, lse2, D, dk_w, dv_w, ld, ldkv, lddkv, grp, S, H, scale);
   else

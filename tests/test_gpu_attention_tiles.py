@@ -166,3 +166,23 @@ def test_attention_bwd_paired_key_blocks(S):
     assert many[0] == (blocks + 1) // 2 * H * n and one[0] == blocks * H
     assert (many[2] == long_lds) == (S >= 1024) and one[2] == long_lds
     _compare_parts(S, n, (1,), H, Hkv)
+
+
+@pytest.mark.parametrize("S,n", [(257, 40), (289, 40), (383, 40), (511, 36), (513, 22), (1025, 13), (1283, 12), (1799, 9)])
+def test_attention_bwd_pairs_of_wavefronts(S, n):
+    """256 keys per workgroup, in pairs of blocks: the bits of the other kernels, which one sequence takes; also of what an infinite
+    gradient reaches (the keys that its query sees, and those of its 32 x 32 block)."""
+    H, Hkv = 4, 2
+    print(f"attention backward, pairs of wavefronts S={S} B={n}", flush=True)
+    many, one = _bwd_launches(S, n, H, Hkv)[1], _bwd_launches(S, 1, H, Hkv)[1]
+    assert many[:2] == (((S + 255) // 256 + 1) // 2 * H * n, 512) and one[1] == 256
+    _compare_parts(S, n, (1,), H, Hkv)
+    g = torch.Generator().manual_seed(S)
+    q, do = (torch.randn(n * S, H * HD, generator=g).bfloat16().to(DEV) for _ in range(2))
+    k, v = (torch.randn(n * S, Hkv * HD, generator=g).bfloat16().to(DEV) for _ in range(2))
+    do[torch.tensor([5, 70, S - 1]) - S, torch.tensor([3, HD + 9, 3 * HD])] = torch.inf    # a query of three heads of the last sequence
+    o, lse = B.lr_attention_gqa_fwd(q, k, v, n, S, H, Hkv, HD)
+    full = B.lr_attention_gqa_bwd(q, k, v, o, do, lse, n, S, H, Hkv, HD)
+    part = B.lr_attention_gqa_bwd(*(t[-S:] for t in (q, k, v, o, do)), lse[n - 1:].contiguous(), 1, S, H, Hkv, HD)
+    for a, b in zip(part, full):
+        assert a.isnan().any() and torch.equal(a.nan_to_num(nan=7.0), b[-S:].nan_to_num(nan=7.0))
