@@ -165,13 +165,15 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, i
   // with this term the 16 rows that one cycle of a 16-byte-per-lane read touches (16 lanes) fall on
   // 16 different 16-byte bank groups.  The 1 KB group index g = wave + NW * i keeps its parity over i
   // (NW is even), so one swizzle value per lane serves all of its loads.
-  // k-major: rows past k lie behind the resource's end; a column chunk past the matrix reads into the next k-row (or ends with
-  // the resource) and feeds output rows or columns that are not stored.
+  // k-major: rows past k lie behind the resource's end; a column chunk past the matrix is left out (read into the next k-row it
+  // would only feed rows or columns that are not stored, but it costs its bytes: dQ of 9 x 1032 tokens, 32 heads, 8 of the last
+  // tile's 256 rows in the matrix, 149 us against 133).  A lane's columns are the same in all its loads: NW * RPL is a multiple of 8.
   // The offsets below hold for every slice of every tile.
   constexpr uint32_t OOB = 0x80000000u;
   static_assert(T::NW % 2 == 0 && (T::BM / 8) % 2 == 0, "row parity of a lane must not depend on the load index");
   const int lrow = lane >> 3, lchunk = (lane & 7) ^ (((wave & 1) << 2) | (lrow >> 1));
   uint32_t goff[T::WLOADS];
+  int kcol_a = 0, kcol_b = 0;                            // first column of this lane's chunks (k-major)
 #pragma unroll
   for (int i = 0; i < T::WLOADS; i++) {
     const bool isA = i < T::WLOADS_A;
@@ -183,7 +185,9 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, i
     } else {
       const int CPR = (isA ? T::BM : T::BN) / 8, RPL = 64 / CPR;       // chunks per k-row, k-rows per wavefront load
       const int krow = g * RPL + lane / CPR;
-      off = (krow * ld + ((lane % CPR) ^ (((krow & 7) << 2) & (CPR - 1))) * 8) * 2;
+      const int col = ((lane % CPR) ^ (((krow & 7) << 2) & (CPR - 1))) * 8;
+      (isA ? kcol_a : kcol_b) = col;
+      off = (krow * ld + col) * 2;
     }
     goff[i] = off < (int64_t)OOB ? (uint32_t)off : OOB;
   }
@@ -208,14 +212,17 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, i
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
         (char*)(here ? (isA ? cur.base_a : cur.base_b) : (isA ? nxt.base_a : nxt.base_b)) + skip, 0,
         skip < (int64_t)rec ? rec - (uint32_t)skip : 0u, 0x00020000);
-    // k tail of the k-contiguous form: chunks past the end of k read as zeros
-    const uint32_t kmask = KM || ks * BK + lchunk * 8 < (here ? cur.klen : nxt.klen) ? 0u : OOB;
+    // chunks past the end of k (k-contiguous form) or of the columns read as zeros
+    bool inside;
+    if constexpr (KM) inside = (isA ? kcol_a + (here ? cur.m0 : nxt.m0) : kcol_b + (here ? cur.n0 : nxt.n0)) < (isA ? op.M : op.N);
+    else inside = ks * BK + lchunk * 8 < (here ? cur.klen : nxt.klen);
+    const uint32_t mask = inside ? 0u : OOB;
     unsigned char* dst = smem + slot + wave * 1024;
     constexpr int F0 = isA ? 0 : T::WLOADS_A, F1 = isA ? T::WLOADS_A : T::WLOADS;   // the operand's loads
     constexpr int I0 = half == 1 ? (F0 + F1) / 2 : F0, I1 = half == 0 ? (F0 + F1) / 2 : F1;
 #pragma unroll
     for (int i = I0; i < I1; i++)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, LRB_LDS_PTR(dst + (i - F0) * (T::NW * 1024)), 16, (int)(goff[i] | kmask), 0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, LRB_LDS_PTR(dst + (i - F0) * (T::NW * 1024)), 16, (int)(goff[i] | mask), 0, 0, 0);
   };
   using Half0 = std::integral_constant<int, 0>;
   using Half1 = std::integral_constant<int, 1>;
