@@ -72,14 +72,6 @@ struct Tile {
                 "tile / wavefront layout mismatch");
 };
 
-// KM = false: operands k-contiguous, A[m][k], B[n][k].
-// KM = true:  operands k-major,      A[k][m], B[k][n]  (weight gradients: k runs over tokens).  The
-//             slices are stored in LDS as they arrive, [k][m], and the MFMA operands are gathered
-//             with the LDS transpose read, so no transposed copy of an activation is ever written.
-// KM = false: operands k-contiguous, A[m][k], B[n][k].
-// KM = true:  operands k-major,      A[k][m], B[k][n]  (weight gradients: k runs over tokens).  The
-//             slices are stored in LDS as they arrive, [k][m], and the MFMA operands are gathered
-//             with the LDS transpose read, so no transposed copy of an activation is ever written.
 // vector memory instructions that a wavefront's epilogue certainly issues after the loads of the next tile's slices
 template <class T, int KIND>
 constexpr int epilogue_stores() {
@@ -506,7 +498,8 @@ hipError_t dispatch(const GemmOp& op, hipStream_t st) {
 // 11008, K 64 .. 11008, nine epilogue kinds), T256X128's over the plain stores among them; R32's is its measured slice time
 // and start-up, set by hand.  Against 1648 launches of the kernels as they are (888 forward products, M from 16; 400 data
 // gradients; 360 weight gradients), the estimates of tiles within 1.5 times the best are off by 8-16 % rms, R32's by 17-19 %
-// (10-15 % too fast on average).  Taking the estimated best loses 1.7 % (forward) and 1.9 % (data gradients) in the geometric mean
+// (10-15 % too fast on average).  (Those of the 256-row tiles were taken with a workgroup per tile; as a stream, launches of more
+// than 256 tiles are 2 to 7 % faster than the estimate has them.)  Taking the estimated best loses 1.7 % (forward) and 1.9 % (data gradients) in the geometric mean
 // against the measured best; the 256-row tiles alone take 2.13 times as long as that over the forward products.  Forward products on R32 of up to
 // 256 pieces of 16 x 16 run as those (gemm_rows16.hip): up to twice as fast with long k, which the estimate does not know.  What the
 // lines amount to, with both sides measured (us):
