@@ -160,7 +160,10 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, i
   // k-major: rows past k lie behind the resource's end; a column chunk past the matrix is left out (read into the next k-row it
   // would only feed rows or columns that are not stored, but it costs its bytes: dQ of 9 x 1032 tokens, 32 heads, 8 of the last
   // tile's 256 rows in the matrix, 149 us against 133).  A lane's columns are the same in all its loads: NW * RPL is a multiple of 8.
-  // The offsets below hold for every slice of every tile.
+  // The offsets below hold for every slice of every tile; a slice's own offset is added per lane.  (Advancing the resource's base
+  // instead saves a vector addition per load, but its chains of scalar instructions stand between a slice's barrier and its first
+  // MFMA: 90 scalar instructions per slice against 65, 2 % of a launch.  us, base advanced -> offset added: 1000 x 11008 x 1024
+  // 28.1 -> 27.3, 16384 x 11008 x 1024 in a block step 311 -> 306, 16384 x 1024 x 4096 109.9 -> 107.1.)
   constexpr uint32_t OOB = 0x80000000u;
   static_assert(T::NW % 2 == 0 && (T::BM / 8) % 2 == 0, "row parity of a lane must not depend on the load index");
   const int lrow = lane >> 3, lchunk = (lane & 7) ^ (((wave & 1) << 2) | (lrow >> 1));
@@ -198,23 +201,26 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, i
     constexpr bool isA = decltype(IS_A)::value;
     constexpr int half = decltype(HALF)::value;
     const bool here = kt < cur.nk;
-    const int ks = here ? kt : kt - cur.nk;
-    const int64_t skip = (int64_t)ks * (KM ? BK * 2 * (isA ? op.lda : op.ldb) : BK * 2);     // bytes before this slice
+    const int ks = here ? kt : kt - cur.nk, klen = here ? cur.klen : nxt.klen;
+    const uint32_t skip = (uint32_t)ks * (uint32_t)(KM ? BK * 2 * (isA ? op.lda : op.ldb) : BK * 2);     // bytes before this slice
     const uint32_t rec = here ? (isA ? cur.rec_a : cur.rec_b) : (isA ? nxt.rec_a : nxt.rec_b);
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        (char*)(here ? (isA ? cur.base_a : cur.base_b) : (isA ? nxt.base_a : nxt.base_b)) + skip, 0,
-        skip < (int64_t)rec ? rec - (uint32_t)skip : 0u, 0x00020000);
-    // chunks past the end of k (k-contiguous form) or of the columns read as zeros
+        (void*)(here ? (isA ? cur.base_a : cur.base_b) : (isA ? nxt.base_a : nxt.base_b)), 0, rec, 0x00020000);
+    // chunks past the end of k or of the columns (k-major form) read as zeros.  (k-major, whole slices past the end of k: skip may
+    // have wrapped.  Elsewhere offset and skip are each below 2 GB or OOB, and their sum is past the resource or right.)
     bool inside;
-    if constexpr (KM) inside = (isA ? kcol_a + (here ? cur.m0 : nxt.m0) : kcol_b + (here ? cur.n0 : nxt.n0)) < (isA ? op.M : op.N);
-    else inside = ks * BK + lchunk * 8 < (here ? cur.klen : nxt.klen);
+    if constexpr (KM)
+      inside = ks * BK < klen && (isA ? kcol_a + (here ? cur.m0 : nxt.m0) : kcol_b + (here ? cur.n0 : nxt.n0)) < (isA ? op.M : op.N);
+    else
+      inside = ks * BK + lchunk * 8 < klen;
     const uint32_t mask = inside ? 0u : OOB;
     unsigned char* dst = smem + slot + wave * 1024;
     constexpr int F0 = isA ? 0 : T::WLOADS_A, F1 = isA ? T::WLOADS_A : T::WLOADS;   // the operand's loads
     constexpr int I0 = half == 1 ? (F0 + F1) / 2 : F0, I1 = half == 0 ? (F0 + F1) / 2 : F1;
 #pragma unroll
     for (int i = I0; i < I1; i++)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, LRB_LDS_PTR(dst + (i - F0) * (T::NW * 1024)), 16, (int)(goff[i] | mask), 0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, LRB_LDS_PTR(dst + (i - F0) * (T::NW * 1024)), 16,
+                                               (int)((goff[i] + skip) | mask), 0, 0, 0);
   };
   using Half0 = std::integral_constant<int, 0>;
   using Half1 = std::integral_constant<int, 1>;

@@ -37,3 +37,27 @@ def test_descriptors_of_inline_loads_are_settled(src, tmp_path):
             if states > 5:
                 break
     assert loads > 0
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+def test_slices_of_the_256_row_tiles_need_few_scalar_instructions(tmp_path):
+    """The loop over 64-wide slices (32 MFMAs of a 256 x 256 tile's wavefront).  Scalar instructions issue in order and 9 cycles apart where
+    they depend on each other: with 79 to 90 of them per slice (descriptors whose base advances) launches were 2 % slower than with 54 to 74."""
+    out = tmp_path / "k.s"
+    subprocess.run(["hipcc", *bld.FLAGS, "-S", "--offload-device-only", os.path.join(bld.CSRC, "gemm_bf16.hip"), "-o", str(out)], check=True,
+                   capture_output=True)
+    loops = 0
+    for kernel in re.finditer(r"^(_ZN\S*gemm_bf16_kernel\S*):\s.*?^\.Lfunc_end\d+:", out.read_text(), re.S | re.M):
+        body = kernel[0].split("\n")
+        labels = {m[1]: i for i, ln in enumerate(body) if (m := re.match(r"(\.LBB\S+):", ln))}
+        for i, ln in enumerate(body):
+            m = re.match(r"\ts_c?branch\S*\s+(\.LBB\S+)", ln)
+            if not m or labels.get(m[1], i) >= i:
+                continue
+            ops = [b.split()[0] for b in body[labels[m[1]]:i] if re.match(r"\t[vsdgb][a-z]*_", b)]
+            if sum(op.startswith("v_mfma") for op in ops) != 32:
+                continue
+            loops += 1
+            scalar = [op for op in ops if op.startswith("s_") and op not in ("s_waitcnt", "s_barrier", "s_nop")]
+            assert len(scalar) <= 76, f"{kernel[1]}: {len(scalar)}"
+    assert loops >= 20
