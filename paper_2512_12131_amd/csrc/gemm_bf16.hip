@@ -108,9 +108,12 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, i
   struct Source {
     const uint16_t *base_a, *base_b;
     uint32_t rec_a, rec_b;
-    int klen, nk;                        // k elements, 64-wide slices (at least two)
+    int klen, nk;                        // k elements, 64-wide slices
     int m0, n0, tn, b, bi, bo, bz;
   };
+  // At least one slice, and two where a tile follows another: two slices of the next tile are under way before an epilogue, and may not
+  // reach into a third.  (Two for all, us: 1024 x 12288 x 64 12.1 -> 13.2, 4096 x 4096 x 40 13.6 -> 14.6.)
+  const int nk_min = total > nwg ? 2 : 1;
   auto source = [&](int nid) -> Source {
     Source s;
     int tm;
@@ -123,7 +126,7 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, i
     int kend = min(op.K, kbeg + kper);
     if (KM && op.causal_k) kend = min(kend, s.m0 + T::BM);
     s.klen = max(kend - kbeg, 0);
-    s.nk = max((s.klen + BK - 1) / BK, 2);
+    s.nk = max((s.klen + BK - 1) / BK, nk_min);
     // element offsets of this batch entry's operands
     s.bo = op.batch_inner > 0 ? s.b / op.batch_inner : 0;
     s.bi = op.batch_inner > 0 ? s.b % op.batch_inner : s.b;

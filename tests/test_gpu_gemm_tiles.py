@@ -132,6 +132,22 @@ def test_stream_of_tiles(T, d, r, n, G):
         assert float((dwu[i].double() - ref).norm() / ref.norm()) < 2e-4
 
 
+# one 256-row tile per CU or fewer: a k of one slice, of less than one, of one and a remainder
+@pytest.mark.parametrize("k", [8, 40, 64, 72])
+@pytest.mark.parametrize("T,n", [(1024, 12288), (4000, 4072)])
+def test_short_k_of_a_tile_per_cu(T, n, k):
+    print(f"short k T={T} n={n} k={k}", flush=True)
+    assert B.lr_gemm_tile(T, n, k, 1, 0, 0) == T256 and -(-T // 256) * -(-n // 256) <= 256 and B.lr_gemm_tile(300, n, k, 1, 0, 0) != T256
+    g = torch.Generator(device=DEV).manual_seed(k)
+    x = torch.randn((T, 64), generator=g, device=DEV).bfloat16()
+    wd = (torch.randn((k, 64), generator=g, device=DEV) * 64 ** -0.5).bfloat16()
+    wu = (torch.randn((n, k), generator=g, device=DEV) * k ** -0.5).bfloat16()
+    z, y = B.lr_linear_fwd(x, wd, wu)
+    for rows in (slice(0, 300), slice(T - 300, T)):      # on the small tiles
+        z1, y1 = B.lr_linear_fwd(x[rows].contiguous(), wd, wu)
+        assert torch.equal(z1, z[rows]) and torch.equal(y1, y[rows])
+
+
 # one tile exactly, one row / column chunk more, remainders in every dimension, k shorter than a slice, several
 # splits of the token reduction, wide and narrow outputs
 EDGES = [(64, 64, 64, 64), (65, 72, 8, 136), (129, 264, 120, 520), (255, 1032, 200, 328), (2, 2048, 64, 2048),
