@@ -59,14 +59,24 @@ struct Tile {
   // the free A slot that the wavefront's own global->LDS loads fill: what it has read back it may load over, without a
   // word to the others.  The XOR spreads what a cycle writes (one chunk of 16 rows) and reads (every second chunk of two
   // rows) over all banks.
-  static constexpr int SR = 16, SC = 64;
   struct EpiStage {
+    static constexpr int SR = 16, SC = 64;
+    static constexpr bool STAT_IN_STAGE = true;
     unsigned char* p;
     __device__ __forceinline__ unsigned char* at(int row, int chunk) const {
       return p + (row >> 2) * (NW * 1024) + (row & 3) * 256 + ((chunk ^ row) << 4);
     }
   };
-  static constexpr bool STAT_IN_STAGE = true;
+  // Behind the last tile all of LDS is free: whole rows of the wavefront's sub-tile.  The fp32 row stride is = 4 (mod 64), so the
+  // 16 rows that one cycle of a 16-byte-per-lane write touches fall on 16 different groups of four banks.
+  static constexpr int LAST_CS = TN + 4, LAST_BYTES = 32 * LAST_CS * 4;
+  struct LastStage {
+    static constexpr int SR = 32, SC = TN;
+    static constexpr bool STAT_IN_STAGE = false;
+    unsigned char* p;
+    __device__ __forceinline__ unsigned char* at(int row, int chunk) const { return p + row * (LAST_CS * 4) + chunk * 16; }
+  };
+  static_assert(NW * LAST_BYTES <= LDS_BYTES, "staging of the last tile");
   static_assert(WLOADS_A >= 4, "a wavefront stages 4 KB in pieces of its own");
   static_assert(BM / 8 % NW == 0 && BN / 8 % NW == 0 && FM >= 1 && FN >= 1 && BM <= NT,
                 "tile / wavefront layout mismatch");
@@ -416,6 +426,22 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, i
     first_frags();
     slice(0, std::true_type{});
     for (int kt = 1; kt < cur.nk; kt++) slice(kt, std::false_type{});
+    // (opaque copies: otherwise the epilogue's address arithmetic is moved out of the loop over tiles, and spilled)
+    int elane = lane, ewave = wave;
+    asm volatile("" : "+v"(elane), "+s"(ewave));
+    // Of the kinds only EPI_UP_O32 gains by whole rows for its last tile: its fp32 copy then leaves in runs of 512 bytes.  us, a
+    // workgroup per tile / pieces of 64 columns / whole rows last: 8192 x 2048 x 512 49.2 / 51.6 / 49.7, 8192 x 4096 x 1024 119.6 /
+    // 123.3 / 119.4, 16384 x 4096 x 1024 235.3 / 239.1 / 235.7.  Others, pieces / whole rows: plain stores 1000 x 11008 x 1024
+    // 33.1 / 33.3, EPI_DOWN 16384 x 1024 x 2048 70.1 / 71.1, EPI_NORMBWD_O32 8192 x 2048 x 1024 63.0 / 65.7.
+    if (KIND == EPI_UP_O32 && !more) {
+      wait_vmcnt<0>();             // this wavefront's loads past the last tile have written their zeros, then everyone's
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      gemm_epilogue<T, KIND, STAT_A>(op, acc, typename T::LastStage{smem + wave * T::LAST_BYTES}, nullptr, ewave, elane, cur.m0, cur.n0,
+                                     cur.tn, tiles_n, cur.b, cur.bi, cur.bo, cur.bz);
+      return;
+    }
     issue_ab(cur.nk + 1, b1, OPB, Half1{});
     __builtin_amdgcn_sched_barrier(0);
     // ---- epilogue: a2 is the free slot -------------------------------------------------------------
@@ -428,9 +454,6 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_kernel(GemmOp op, int kper, i
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
     }
-    // (opaque copies: otherwise the epilogue's address arithmetic is moved out of the loop over tiles, and spilled)
-    int elane = lane, ewave = wave;
-    asm volatile("" : "+v"(elane), "+s"(ewave));
     gemm_epilogue<T, KIND, STAT_A>(op, acc, typename T::EpiStage{smem + a2 + wave * 1024},
                                    reinterpret_cast<const float*>(smem + a2), ewave, elane, cur.m0, cur.n0, cur.tn, tiles_n, cur.b,
                                    cur.bi, cur.bo, cur.bz);

@@ -48,11 +48,11 @@ struct RingTile {
   static constexpr int STAGE_BYTES = 32 * CS * 4;            // ... of a wavefront
   static constexpr int EPI_BYTES = NW * STAGE_BYTES;
   struct EpiStage {
+    static constexpr int SR = 32, SC = TN;
+    static constexpr bool STAT_IN_STAGE = false;
     unsigned char* p;
     __device__ __forceinline__ unsigned char* at(int row, int chunk) const { return p + row * (CS * 4) + chunk * 16; }
   };
-  static constexpr int SR = 32, SC = TN;
-  static constexpr bool STAT_IN_STAGE = false;
   static constexpr int STAT_OFF = EPI_BYTES;
   static constexpr int MAIN_BYTES = NS * STAGE;
   static constexpr int LDS_BYTES = MAIN_BYTES > EPI_BYTES + BM * 4 ? MAIN_BYTES : EPI_BYTES + BM * 4;

@@ -88,8 +88,8 @@ inline dim3 tile_grid(int tiles, int members) {
 // ---- epilogue ---------------------------------------------------------------------------------
 // Called by every wavefront that holds accumulators once they are final and its staging space is free.
 // Tile type T: BM rows; WN wavefronts across, each with an FM x FN arrangement of 32x32 MFMA blocks (TM x TN), of
-// which SR rows of SC columns are staged at a time: 32 of all columns, or 16 of 64.  stage.at(row, chunk): where 16-byte
-// chunk `chunk` of staged row `row` lies.  (m0, n0): first row / column of the output tile, tn its column
+// which Stage::SR rows of Stage::SC columns are staged at a time: 32 of all columns, or 16 of 64.  stage.at(row, chunk): where
+// 16-byte chunk `chunk` of staged row `row` lies.  (m0, n0): first row / column of the output tile, tn its column
 // index, b / (bi, bo) / bz: batch member, its two-level split, batch member times k split.  sStat: the row
 // statistics gathered in the main loop (STAT_A); STAT_IN_STAGE: they lie in the staging space.
 template <class T, int KIND, bool STAT_A, class Stage>
@@ -105,13 +105,13 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T:
   // auxiliary tiles an epilogue reads (residual, z, x, g, u) are fetched PF passes ahead into a small
   // register ring, and each pass waits only for its own.
   const Epilogue& e = op.epi;
-  constexpr int LPR = T::SC / 8;            // lanes per output row
+  constexpr int LPR = Stage::SC / 8;            // lanes per output row
   constexpr int RPP = 64 / LPR;             // rows per pass
-  constexpr int PPS = T::SR / RPP;          // passes per staged piece
-  constexpr int NJ = T::TN / T::SC;         // pieces side by side
-  constexpr int NH = 32 / T::SR;            // pieces of an MFMA block's rows
+  constexpr int PPS = Stage::SR / RPP;          // passes per staged piece
+  constexpr int NJ = T::TN / Stage::SC;         // pieces side by side
+  constexpr int NH = 32 / Stage::SR;            // pieces of an MFMA block's rows
   constexpr int NQ = T::FM * NH * NJ * PPS; // passes per wavefront
-  static_assert(T::SR == 32 ? NJ == 1 : T::SR == 16 && T::SC == 64, "staging forms");
+  static_assert(Stage::SR == 32 ? NJ == 1 : Stage::SR == 16 && Stage::SC == 64, "staging forms");
   // which auxiliary tiles a kind can read at all, and the prefetch distance in passes: kinds with one
   // auxiliary tile keep eight of its 16-byte vectors in flight per lane, kinds with two keep four of each
   // BASE: the formula; R_F32: the R tile is fp32 (two 16-byte vectors per lane and pass); O32: the primary
@@ -152,7 +152,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T:
   const int ldC2 = (int)e.ldc2 * 2, ldR = (int)e.ldr * (R_F32 ? 4 : 2), ldR2 = (int)e.ldr2 * 2, ldC32 = (int)e.ldc32 * 4;
   // byte offset inside a row of this lane's columns of piece jj, for elements of es bytes
   auto col_off = [&](int jj, uint32_t es) -> uint32_t {
-    return coln + jj * T::SC < op.N ? (uint32_t)(coln + jj * T::SC) * es : EOOB;
+    return coln + jj * Stage::SC < op.N ? (uint32_t)(coln + jj * Stage::SC) * es : EOOB;
   };
   const bool want2 = KIND == EPI_SWIGLU_BWD || KIND == EPI_SWIGLU_FWD || KIND == EPI_DOWN_LAX || KIND == EPI_LAXGRAD ||
                      KIND == EPI_ACTGRAD_A || (KIND == EPI_DOWN && e.C2 != nullptr);
@@ -178,7 +178,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T:
   u32x4 auxr[PF], auxr2[PF], auxr3[R_F32 ? PF : 1];   // auxr3: columns 4..7 of an fp32 R tile
   // pass q: MFMA block row i, piece h of its rows, piece jj across, p-th run of RPP rows
   auto row_of = [&](int q) {                                       // row inside the tile
-    return wm * T::TM + (q / (NH * NJ * PPS)) * 32 + (q / (NJ * PPS) % NH) * T::SR + (q % PPS) * RPP + rsub;
+    return wm * T::TM + (q / (NH * NJ * PPS)) * 32 + (q / (NJ * PPS) % NH) * Stage::SR + (q % PPS) * RPP + rsub;
   };
   auto across = [](int q) { return q / PPS % NJ; };
   float ssv[STAT_A ? NQ : PF], rbv[PF];               // per-row scalars, fetched with the auxiliary tiles
@@ -209,7 +209,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T:
   });
   if constexpr (STAT_A)
     static_for<NQ>([&](auto Q) { ssv[decltype(Q)::value] = sStat[row_of(decltype(Q)::value)]; });
-  if constexpr (STAT_A && T::STAT_IN_STAGE) {   // read by all before anyone writes there
+  if constexpr (STAT_A && Stage::STAT_IN_STAGE) {   // read by all before anyone writes there
     wait_lgkmcnt0();
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
@@ -223,7 +223,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T:
     // stages four consecutive columns with one 16-byte write.
     // No barrier: the staging region belongs to this wavefront alone and a wavefront's LDS
     // operations complete in order.
-    if constexpr (T::SR == 16 && h == 0 && jj == 0 && p == 0) {
+    if constexpr (Stage::SR == 16 && h == 0 && jj == 0 && p == 0) {
       // Rows 0..15 of two neighbouring MFMA blocks come together: lanes 16..31 and 48..63 of the left block (its rows
       // 16..31) change places with lanes 0..15 and 32..47 of the right one.  Then lane -> row lane%16, block (lane/16)%2.
       static_for<T::FN / 2>([&](auto J) {
@@ -243,7 +243,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T:
         for (int g = 0; g < 4; g++)
           *reinterpret_cast<f32x4*>(stage.at(row, chunk + 2 * g)) = f32x4{a[4 * g], a[4 * g + 1], a[4 * g + 2], a[4 * g + 3]};
       };
-      if constexpr (T::SR == 32)
+      if constexpr (Stage::SR == 32)
         static_for<T::FN>([&](auto J) { put(lane & 31, decltype(J)::value * 8 + (lane >> 5), acc[i][decltype(J)::value]); });
       else
         put(lane & 15, (lane >> 4 & 1) * 8 + (lane >> 5), acc[i][2 * jj + h]);
@@ -301,7 +301,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T:
       if constexpr (q + PF < NQ) fetch(q + PF, auxr[q % PF], auxr2[q % PF], auxr3[R_F32 ? q % PF : 0], ssv[q % PF], rbv[q % PF]);
       if constexpr (ROWPART) {
         part = lane_group_sum<LPP>(part);
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(part), rsPart, (int)((uint32_t)(lm * ldPart) + colPart + jj * (T::SC / (LPP * 8)) * 4), 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(part), rsPart, (int)((uint32_t)(lm * ldPart) + colPart + jj * (Stage::SC / (LPP * 8)) * 4), 0, 0);
       }
       if constexpr (STAT_A && jj == 0)
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ssv[q]), rsStat, (int)((uint32_t)(lm * 4) + colStat), 0, 0);

@@ -92,6 +92,29 @@ def test_sequences_of_a_block_do_not_depend_on_the_batch(lax):
         assert not off, f"{nb} sequences: {', '.join(off)}"
 
 
+# the residual sum that is stored twice (bf16 and fp32) stages a workgroup's last tile another way than those before it: one tile each,
+# one or two, remainders of rows and of columns.  What follows from it: s2, the MLP's checkpoints and y.
+@pytest.mark.parametrize("Bn,tiles", [(37, 245), (70, 460)])
+def test_last_tile_of_the_residual_sum(Bn, tiles):
+    S, H, f, r = 333, 9, 1032, 520
+    d = 128 * H
+    print(f"residual sum of {Bn} sequences, {tiles} tiles", flush=True)
+    assert B.lr_gemm_tile(Bn * S, d, r, 1, 0, 10) == T256 and -(-Bn * S // 256) * -(-d // 256) == tiles
+    assert B.lr_gemm_tile(S, d, r, 1, 0, 10) != T256
+    p = {k: v.to(DEV) for k, v in si.pack_block_params(si.block_case(1, S, d, H, 128, f, r, seed=14)["params"], f, f).items()}
+    x = torch.randn((Bn * S, d), generator=torch.Generator(device=DEV).manual_seed(16), device=DEV).bfloat16()
+
+    def forward(rows, nb):
+        y, ck = B.lr_block_fwd(B.make_block_desc(nb, S, d, H, 128, f, f, r), p, x[rows])
+        return {"y": y, **ck}
+
+    full = forward(slice(0, Bn * S), Bn)
+    for i in (0, Bn // 2, Bn - 1):
+        rows = slice(i * S, (i + 1) * S)
+        off = [n for n, t in forward(rows, 1).items() if not torch.equal(t, full[n][rows])]
+        assert not off, f"sequence {i}: {', '.join(off)}"
+
+
 def test_query_gradient_does_not_depend_on_the_tile():
     # 16, 4 and 1 sequences of 512 tokens, 16 heads: three tiles of the dQ product
     S, H = 512, 16
