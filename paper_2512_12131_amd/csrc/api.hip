@@ -837,7 +837,7 @@ void block_bwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   if (!lx) lx = &nlx;
   const size_t es = 2;
   const int64_t T = b.T, d = b.d, r = b.r, f = b.f, rowf = c.wide_ld(f);
-  const int64_t ldf = sv ? f : wide_stride(T, f, rowf);     // row stride of g, u, m, dg and du
+  const int64_t ldw = wide_stride(T, f, rowf), ldf = sv ? f : ldw;     // row strides of dg and du, of g, u and m
   const lr_block_params np{};  // dry runs have no parameter structs
   const lr_block_ckpt nck{};
   if (!p) p = &np;
@@ -897,7 +897,7 @@ void block_bwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   if (!sv) single_up(c, b, act_o, p->w_up_o, d, x, h1, nullptr);
   GrpArgs m = group_args(b, 2, f);
   m.x = h1; m.gamma = p->gamma2; m.w_down_cat = p->w_dn_gu; m.w_up_stack = p->w_up_gu; m.y_stack = big;
-  m.lddy = ldf; m.dy_bs = T * ldf;
+  m.lddy = ldw; m.dy_bs = T * ldw;
   if (!sv) mlp_up_swiglu(c, b, p->w_up_gu, act_g, big, (char*)big + (size_t)T * ldf * es, mm, ldf);
   c.flush();
   // down-D backward: dW_dn_d = dz_d^T . m ; dm = dz_d . W_dn_d with the SwiGLU reverse fused in
@@ -905,10 +905,10 @@ void block_bwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   wgrad(c, dz1, r, (int)r, mm, ldf, (int)f, T, g->w_dn_d, nullptr, accumulate);
   {
     GemmOp dm;
-    dm.A = dz1; dm.lda = r; dm.B = p->w_dn_d; dm.ldb = f; dm.transB = 1; dm.C = big2; dm.ldc = ldf;
+    dm.A = dz1; dm.lda = r; dm.B = p->w_dn_d; dm.ldb = f; dm.transB = 1; dm.C = big2; dm.ldc = ldw;
     dm.M = (int)T; dm.N = (int)f; dm.K = (int)r;
     dm.epi.kind = EPI_SWIGLU_BWD; dm.epi.R = big; dm.epi.ldr = ldf; dm.epi.R2 = (char*)big + (size_t)T * ldf * es;
-    dm.epi.ldr2 = ldf; dm.epi.C2 = (char*)big2 + (size_t)T * ldf * es; dm.epi.ldc2 = ldf;
+    dm.epi.ldr2 = ldf; dm.epi.C2 = (char*)big2 + (size_t)T * ldw * es; dm.epi.ldc2 = ldw;
     gemm(c, dm);
   }
   c.flush();

@@ -152,6 +152,34 @@ def test_block_without_room_for_rows_on_cache_lines(f):
         _same(call, outs, query - rows * T * pad * 2, query)
 
 
+def test_saved_backward_uses_the_room_for_rows_on_cache_lines():
+    """What the query asks for the ends of dg's and du's rows is taken up by them: no more whole 64 bytes stay untouched than without."""
+    Bn, S, H, f, r = 8, 770, 1, 2600, 344
+    T, d, pad = Bn * S, 128 * H, 24
+    print(f"kept-activation backward, what it leaves untouched, f={f}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(f)
+    shapes = {"gamma1": (d,), "w_dn_qkv": (3 * r, d), "w_up_qkv": (3, d, r), "w_dn_o": (r, d), "w_up_o": (d, r), "gamma2": (d,),
+              "w_dn_gu": (2 * r, d), "w_up_gu": (2, f, r), "w_dn_d": (r, f), "w_up_d": (d, r)}
+    p = {n: (torch.randn(s, generator=g, device=DEV) * s[-1] ** -0.5).bfloat16() for n, s in shapes.items()}
+    x, dy = (torch.randn((T, d), generator=g, device=DEV).bfloat16() for _ in range(2))
+    desc = B.make_block_desc(Bn, S, d, H, 128, f, f, r)
+    _, ck, saved = B.lr_block_fwd_save(desc, p, x)
+    query = B.lib().lr_block_saved_workspace_bytes(C.byref(desc), 1)
+    outs, untouched = [], []
+    for size in (query, query - 2 * T * pad * 2):
+        ws = torch.full((size,), 0x55, dtype=torch.uint8, device=DEV)
+        dx, grads = torch.empty_like(x), {n: torch.empty_like(t, dtype=torch.float32) for n, t in p.items()}
+        status = B.lib().lr_block_bwd_saved(C.byref(desc), C.byref(B._params_struct(p)), x.data_ptr(), dy.data_ptr(),
+                                            C.byref(B._ckpt_struct(ck)), C.byref(B._saved_struct(saved)), dx.data_ptr(),
+                                            C.byref(B._params_struct(grads)), 0, ws.data_ptr(), size, _stream())
+        torch.cuda.synchronize()
+        assert status == 0
+        outs.append([dx, *grads.values()])
+        untouched.append(64 * int((ws[:size // 64 * 64].view(-1, 64) == 0x55).all(1).sum()))
+    assert all(torch.equal(a, b) for a, b in zip(*outs))
+    assert untouched[0] - untouched[1] < T * pad * 2, untouched
+
+
 def test_rows_that_span_more_than_2_gib():
     """x and dy as columns of a 2.6 GB tensor: refused in the workspace of dense rows, and with the room for copies the gradients of
     dense rows.  Each is a chained sum of T exact products in both: off by at most T 2^-24 of the sum of their magnitudes."""
