@@ -481,14 +481,20 @@ hipError_t launch(const GemmOp& op, hipStream_t st) {
   // causal k ranges differ from tile to tile: a workgroup each, dealt out as CUs become free
   const dim3 grid = op.causal_k || total <= NCU ? tile_grid(tiles_m * tiles_n, op.batch * op.splitk) : dim3(NCU);
   // SwiGLU epilogues move up to 512 KB per tile, 134 MB of a round of 256 tiles, 25 of its 48 us at k = 1024, with the matrix pipes
-  // idle; then all main loops leave memory idle.  The XCDs start 3/4 of a slice's cycles per slice of k apart (units of 1024
-  // cycles), and one's epilogues run beside the others' main loops: about 6 us off a round for a start that is 2.3 us per
-  // slice longer.  us, together -> apart: 16384 x 11008 x 1024 SwiGLU forward 425 -> 406, with u stored 507 -> 481, backward
-  // 530 -> 501; 16384 x 5464 x 512 163 -> 160, 209 -> 199, 222 -> 211.  Of other kinds and fewer rounds the start costs more
-  // (16384 x 4096 x 2048, norm's reverse 341 -> 350, plain stores of k = 1024 320 -> 340).
+  // idle; then all main loops leave memory idle.  The XCDs start 768 cycles per slice of k apart (in units of 1024), 3/8 of the matrix
+  // time of a slice, and one's epilogues run beside the others' main loops: up to 6 us off a round, for a last XCD that starts 7 x 768
+  // cycles per slice of k late (36 us at k = 1024).  So it takes rounds enough, and more of them for longer k.  Against starting together,
+  // 311 launches of 8192 to 16384 tokens x 2752 .. 16384 over k of 256 .. 2048: of the 145 under the rule none is more than 1.2 % slower,
+  // on average the forward is 2.1 % faster and the reverse, which moves more, 1.7 %.  us, together -> apart, forward: five rounds 8192 x
+  // 10240 x 512 129 -> 138, six 12288 x 8192 x 512 149 -> 154, seven 16384 x 7168 x 512 181 -> 178, eight 16384 x 8192 x 512 222 -> 213, with
+  // u stored 278 -> 263; reverse: five 8192 x 10240 x 512 180 -> 184, six 8192 x 12264 x 512 242 -> 231.  The rounds for a k: 16384 x 8192 x 1024 (half
+  // a round per slice) 303 -> 297, 8192 x 11008 x 1024 (0.31) 214 -> 222, 16384 x 11008 x 2048 (0.31) 637 -> 681; the line is at 9/16.
+  // Half and a quarter of the delay gain less (16384 x 8192 x 512 222 -> 220, 223).  Of other kinds the start costs more than it
+  // gives (16384 x 4096 x 2048, norm's reverse 341 -> 350, plain stores of k = 1024 320 -> 340).
   const int nk = kper / BK;
-  const bool swiglu = KIND == EPI_SWIGLU_FWD || KIND == EPI_SWIGLU_BWD;
-  const int stagger = swiglu && grid.y == 1 && total / NCU * 16 >= nk * 9 ? nk * 3 / 4 : 0;
+  const int64_t rounds = total / NCU;
+  const bool enough = KIND == EPI_SWIGLU_FWD ? rounds >= 7 : KIND == EPI_SWIGLU_BWD && rounds >= 6;
+  const int stagger = enough && grid.y == 1 && rounds * 16 >= nk * 9 ? nk * 3 / 4 : 0;
   hipLaunchKernelGGL(kern, grid, dim3(T::NT), T::LDS_BYTES, st, op, kper, tiles_m, tiles_n, (int)total, stagger);
   return hipGetLastError();
 }
