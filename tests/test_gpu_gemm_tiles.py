@@ -155,6 +155,46 @@ def test_stream_of_tiles(T, d, r, n, G):
         assert float((dwu[i].double() - ref).norm() / ref.norm()) < 2e-4
 
 
+# the norm's statistic gathered from the A slices by workgroups that stream through several tiles: it starts anew with each tile, and
+# lies in the slot that the epilogue then stages through
+def test_gathered_statistic_over_a_stream_of_tiles():
+    T, d, r, n, G = 16385, 1032, 520, 264, 3
+    print(f"gathered statistic T={T} N={G * r}", flush=True)
+    assert B.lr_gemm_tile(T, G * r, d, 1, 0, 1) == T256 and -(-T // 256) * -(-G * r // 256) > 256
+    assert B.lr_gemm_tile(300, G * r, d, 1, 0, 1) != T256
+    g = torch.Generator(device=DEV).manual_seed(22)
+    x, gamma = torch.randn((T, d), generator=g, device=DEV).bfloat16(), torch.randn((d,), generator=g, device=DEV).bfloat16()
+    wd = (torch.randn((G * r, d), generator=g, device=DEV) * d ** -0.5).bfloat16()
+    wu = (torch.randn((G, n, r), generator=g, device=DEV) * r ** -0.5).bfloat16()
+    z, s, y = B.lr_group_fwd(x, gamma, 1e-5, B.LR_NORM_ONLINE_GATHER, wd, wu)
+    for rows in (slice(0, 300), slice(8192, 8492), slice(16080, T)):      # on the small tiles; the order of a row's sum has a period of 16 rows
+        z1, s1, y1 = B.lr_group_fwd(x[rows].contiguous(), gamma, 1e-5, B.LR_NORM_ONLINE_GATHER, wd, wu)
+        assert torch.equal(s1, s[rows]) and torch.equal(z1, z[rows]) and torch.equal(y1, y[:, rows])
+
+
+def test_gathered_statistic_over_a_stream_of_tiles_lax():
+    Bn, S, H, f, r = 50, 336, 9, 1032, 520
+    T, d = Bn * S, 128 * H
+    print(f"gathered statistic, LaX, T={T} N={3 * r}", flush=True)
+    assert B.lr_gemm_tile(T, 3 * r, d, 1, 0, 8) == T256 and -(-T // 256) * -(-3 * r // 256) > 256
+    assert B.lr_gemm_tile(S, 3 * r, d, 1, 0, 8) != T256
+    p = {k: v.to(DEV) for k, v in si.pack_block_params(si.block_case(1, S, d, H, 128, f, r, seed=14)["params"], f, f).items()}
+    g = torch.Generator(device=DEV).manual_seed(23)
+    x = torch.randn((T, d), generator=g, device=DEV).bfloat16()
+    h = {n: torch.randn((T, w * r), generator=g, device=DEV).bfloat16() for n, w in {"qkv": 3, "o": 1, "gu": 2, "d": 1}.items()}
+
+    def forward(rows, nb):
+        desc = B.make_block_desc(nb, S, d, H, 128, f, f, r, act=B.LR_ACT_IDENTITY, norm=B.LR_NORM_ONLINE_GATHER)
+        y, ck = B.lr_block_lax_fwd(desc, p, x[rows], h_prev={n: t[rows] for n, t in h.items()})
+        return {"y": y, **ck}
+
+    full = forward(slice(0, T), Bn)
+    for i in (0, Bn // 2, Bn - 1):
+        rows = slice(i * S, (i + 1) * S)
+        off = [n for n, t in forward(rows, 1).items() if not torch.equal(t, full[n][rows])]
+        assert not off, f"sequence {i}: {', '.join(off)}"
+
+
 # one 256-row tile per CU or fewer: a k of one slice, of less than one, of one and a remainder
 @pytest.mark.parametrize("k", [8, 40, 64, 72])
 @pytest.mark.parametrize("T,n", [(1024, 12288), (4000, 4072)])
