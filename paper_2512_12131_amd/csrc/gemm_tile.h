@@ -181,14 +181,20 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T:
     return wm * T::TM + (q / (NH * NJ * PPS)) * 32 + (q / (NJ * PPS) % NH) * Stage::SR + (q % PPS) * RPP + rsub;
   };
   auto across = [](int q) { return q / PPS % NJ; };
-  float ssv[STAT_A ? NQ : PF], rbv[PF];               // per-row scalars, fetched with the auxiliary tiles
+  // per-row scalars, fetched with the auxiliary tiles; where there is none, all before the first pass: behind stores that a branch
+  // may leave out, the compiler cannot count, and their waits were for everything, the next tile's slices included (EPI_DOWN)
+  constexpr int PR = STAT_A || !HAS_R ? NQ : PF;
+  float ssv[PR], rbv[PR];
   constexpr bool ROWS = !PARTIAL && !STAT_A && BASE != EPI_STORE && BASE != EPI_UP && BASE != EPI_SWIGLU_BWD && BASE != EPI_SWIGLU_FWD;
-  auto fetch = [&](int q, u32x4& ar, u32x4& ar2, u32x4& ar3, float& ss, float& rb) {
+  auto fetch_row = [&](int q, float& ss, float& rb) {
     const int lm = row_of(q);
     if constexpr (ROWS) {
       if (use_rho) ss = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsRowA, lm * 4, 0, 0));
     }
     if constexpr (BASE == EPI_NORMBWD) rb = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsRowB, lm * 4, 0, 0));
+  };
+  auto fetch = [&](int q, u32x4& ar, u32x4& ar2, u32x4& ar3) {
+    const int lm = row_of(q);
     if constexpr (R_F32) {
       const uint32_t off = (uint32_t)(lm * ldR) + col_off(across(q), 4u);
       ar = __builtin_amdgcn_raw_buffer_load_b128(rsR, (int)off, 0, 0);
@@ -203,9 +209,13 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T:
     auxr[q] = u32x4{0u, 0u, 0u, 0u};
     auxr2[q] = u32x4{0u, 0u, 0u, 0u};
     if constexpr (R_F32) auxr3[q] = u32x4{0u, 0u, 0u, 0u};
-    if constexpr (!STAT_A) ssv[q] = 0.f;
+    if constexpr (q < NQ) fetch(q, auxr[q], auxr2[q], auxr3[R_F32 ? q : 0]);
+  });
+  static_for<(PR < NQ ? PR : NQ)>([&](auto Q) {
+    constexpr int q = decltype(Q)::value;
+    ssv[q] = 0.f;
     rbv[q] = 0.f;
-    if constexpr (q < NQ) fetch(q, auxr[q], auxr2[q], auxr3[R_F32 ? q : 0], ssv[q], rbv[q]);
+    fetch_row(q, ssv[q], rbv[q]);
   });
   if constexpr (STAT_A)
     static_for<NQ>([&](auto Q) { ssv[decltype(Q)::value] = sStat[row_of(decltype(Q)::value)]; });
@@ -267,10 +277,10 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T:
     } else {
       float rho = 1.f, rowb = 0.f;
       if (use_rho) {
-        const float ss = ssv[STAT_A ? q : q % PF];
+        const float ss = ssv[q % PR];
         rho = rho_sqrt ? sqrtf(ss * inv_d + eps) : rsqrtf(ss * inv_d + eps);
       }
-      if constexpr (BASE == EPI_NORMBWD) rowb = rbv[q % PF];
+      if constexpr (BASE == EPI_NORMBWD) rowb = rbv[q % PR];
       float r[8], r2[8], v2[8];
       if constexpr (R_F32) {
         const u32x4 a0 = auxr[q % PF], a1 = auxr3[q % PF];
@@ -298,7 +308,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T:
         const u32x4 ov = {o.x, o.y, o.z, o.w};
         __builtin_amdgcn_raw_buffer_store_b128(ov, rsC2, (int)((uint32_t)(lm * ldC2) + col_off(jj, 2u)), 0, 0);
       }
-      if constexpr (q + PF < NQ) fetch(q + PF, auxr[q % PF], auxr2[q % PF], auxr3[R_F32 ? q % PF : 0], ssv[q % PF], rbv[q % PF]);
+      if constexpr (q + PR < NQ) fetch_row(q + PR, ssv[q % PR], rbv[q % PR]);
+      if constexpr (q + PF < NQ) fetch(q + PF, auxr[q % PF], auxr2[q % PF], auxr3[R_F32 ? q % PF : 0]);
       if constexpr (ROWPART) {
         part = lane_group_sum<LPP>(part);
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(part), rsPart, (int)((uint32_t)(lm * ldPart) + colPart + jj * (Stage::SC / (LPP * 8)) * 4), 0, 0);
