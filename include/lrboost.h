@@ -8,11 +8,14 @@
  *  - Every pointer is a DEVICE pointer owned by the caller unless a comment says "host".  The
  *    library never allocates, frees or synchronises: each call validates its arguments on the
  *    host, enqueues kernels on `stream` (a hipStream_t passed as void*, NULL = default
- *    stream) and returns.  Scratch memory comes from the caller through (ws, ws_bytes); the
- *    matching *_workspace_bytes() call gives the size to hand over.  For the backward of narrow layers
- *    that is up to 32 MiB more than the call needs (room for the weight gradients' partial sums side by
- *    side, so that they share launches); a workspace without that part is accepted too and gives the
- *    same results in more launches.  The queries count dense rows: a backward over x or dy whose rows span
+ *    stream) and returns.  A large product keeps every CU until its launch ends (up to 0.5 ms at
+ *    16384 tokens): what another stream enqueues meanwhile waits for that.  Scratch memory comes
+ *    from the caller through (ws, ws_bytes); the matching *_workspace_bytes() call gives the size to
+ *    hand over.  That may be more than the call needs, and a workspace without what is on top is
+ *    accepted too, with the same results, slower: for the backward of narrow layers up to 32 MiB
+ *    (room for the weight gradients' partial sums side by side, so that they share launches), for a
+ *    block, forward or backward, up to a 64th of its d_ff wide activations (their rows then start
+ *    on cache lines).  The queries count dense rows: a backward over x or dy whose rows span
  *    2 GiB or more in all (T * ld * 2 bytes) needs copies of them on top and returns LR_EWORKSPACE
  *    without the room.
  *  - Matrices are row-major, activations token-major: x[T, d] with leading dimension ld (in

@@ -21,18 +21,24 @@
 // buffer resource, without branches.  Workgroups map to tiles XCD by XCD in compact panels and all walk k front to back, so that
 // the tiles resident in one XCD share operand slices in its L2.
 //
-// A launch has at most one workgroup per CU, and a workgroup walks all its tiles in one stream of slices.  What bounds
+// A launch has at most one workgroup per CU, and a workgroup walks all its tiles in one stream of slices.  (The causal product of
+// the attention keeps a workgroup per tile: see launch.)  What bounds
 // a launch with k of 512 or 1024 is the time outside the main loop: with a workgroup per tile 9 us of each 33 us (K = 1024,
 // plain store) went into its start, the wait for its first slices and the drain of its stores, with the matrix pipes idle.
 // Now the first two slices of the next tile are under way before the epilogue starts, and the epilogue's stores drain behind
 // the next tile's first slice.  us, a workgroup per tile -> one stream (inside a block step):
-//   16384 x 11008 x 1024, plain store        350 -> 319      same, SwiGLU forward            443 -> 413
-//   16384 x  4096 x 1024, three members      381 -> 350      same, SwiGLU backward           556 -> 526
-//   16384 x  2048 x  512, three members      125 -> 110      11008 x 1024 x 16384 k-major    352 -> 331
-//   16384 x  1024 x 4096 (one tile per CU)   112 -> 111      16384 x 4096 x 4096             424 -> 424
+//   16384 x 11008 x 1024, plain store        352 -> 314      same, SwiGLU forward            449 -> 396
+//   16384 x  4096 x 1024, three members      379 -> 344      same, SwiGLU backward           555 -> 490
+//   16384 x  2048 x  512, three members      123 -> 108      11008 x 1024 x 16384 k-major    353 -> 341
+// Launches of one tile per CU have nothing to stream to and take what they took: 16384 x 1024 x 4096 112.0 -> 109.5, 777 x 11008 x 1024 29.3 ->
+// 29.0, k of one slice 1024 x 12288 x 64 12.2 -> 11.8; up to 5 % longer is the residual sum over a short k (16384 x 1024 x 256 26.6 -> 28.0).
 // The four-kilobyte staging space that this leaves a wavefront gives the epilogue rows of 128 bytes.  Rows of 256 through the free B slot
 // as well, with slice 1 of B loaded behind the epilogue, lost the gain (350 -> 350: its wait includes the stores); rows of 64
-// bytes (one MFMA block at a time) made epilogues that read tiles up to 30 % slower.
+// bytes (one MFMA block at a time) made epilogues that read tiles up to 30 % slower.  Where rows start between cache lines a piece spans
+// two of them: SwiGLU with u stored, 16384 x 5464 x 512 into a caller's dense rows, 213 -> 218 (in a workspace rows start on lines).
+// A workgroup's share of tiles is fixed, and a CU is not free for another stream's workgroups before the launch ends (up to 500 us; with
+// a workgroup per tile, a tile's time).  Beside a chain of attention forwards (4096 tokens, 4 heads) a group forward of 16384 tokens
+// takes 1155 -> 949 us and each of them 105 -> 125; beside a kernel that holds 64 CUs for 0.5 ms at a time 1910 -> 1815.
 #include <vector>
 
 #include "gemm_tile.h"
@@ -81,13 +87,6 @@ struct Tile {
   static_assert(BM / 8 % NW == 0 && BN / 8 % NW == 0 && FM >= 1 && FN >= 1 && BM <= NT,
                 "tile / wavefront layout mismatch");
 };
-
-// vector memory instructions that a wavefront's epilogue certainly issues after the loads of the next tile's slices
-template <class T, int KIND>
-constexpr int epilogue_stores() {
-  const int passes = T::TM * T::TN / (64 * 8);
-  return KIND == EPI_PARTIAL ? 2 * passes : passes;
-}
 
 // KM = false: operands k-contiguous, A[m][k], B[n][k].
 // KM = true:  operands k-major,      A[k][m], B[k][n]  (weight gradients: k runs over tokens).  The
@@ -486,9 +485,10 @@ hipError_t launch(const GemmOp& op, hipStream_t st) {
   // cycles per slice of k late (36 us at k = 1024).  So it takes rounds enough, and more of them for longer k.  Against starting together,
   // 311 launches of 8192 to 16384 tokens x 2752 .. 16384 over k of 256 .. 2048: of the 145 under the rule none is more than 1.2 % slower,
   // on average the forward is 2.1 % faster and the reverse, which moves more, 1.7 %.  us, together -> apart, forward: five rounds 8192 x
-  // 10240 x 512 129 -> 138, six 12288 x 8192 x 512 149 -> 154, seven 16384 x 7168 x 512 181 -> 178, eight 16384 x 8192 x 512 222 -> 213, with
-  // u stored 278 -> 263; reverse: five 8192 x 10240 x 512 180 -> 184, six 8192 x 12264 x 512 242 -> 231.  The rounds for a k: 16384 x 8192 x 1024 (half
-  // a round per slice) 303 -> 297, 8192 x 11008 x 1024 (0.31) 214 -> 222, 16384 x 11008 x 2048 (0.31) 637 -> 681; the line is at 9/16.
+  // 10240 x 512 129 -> 138, six 12288 x 8192 x 512 149 -> 154, seven 16384 x 7168 x 512 181 -> 178, eight 16384 x 8192 x 512 222 -> 213,
+  // with u stored 278 -> 263; reverse: five 8192 x 10240 x 512 180 -> 184, six 8192 x 12264 x 512 242 -> 231.  The rounds for a k: 16384 x
+  // 8192 x 1024 (half a round per slice) 303 -> 297, 8192 x 11008 x 1024 (0.31) 214 -> 222, 16384 x 11008 x 2048 (0.31) 637 -> 681; the
+  // line is at 9/16.
   // Half and a quarter of the delay gain less (16384 x 8192 x 512 222 -> 220, 223).  Of other kinds the start costs more than it
   // gives (16384 x 4096 x 2048, norm's reverse 341 -> 350, plain stores of k = 1024 320 -> 340).
   const int nk = kper / BK;
@@ -536,18 +536,21 @@ hipError_t dispatch(const GemmOp& op, hipStream_t st) {
 // 11008, K 64 .. 11008, nine epilogue kinds), T256X128's over the plain stores among them; R32's is its measured slice time
 // and start-up, set by hand.  Against 1648 launches of the kernels as they are (888 forward products, M from 16; 400 data
 // gradients; 360 weight gradients), the estimates of tiles within 1.5 times the best are off by 8-16 % rms, R32's by 17-19 %
-// (10-15 % too fast on average).  (Those of the 256-row tiles were taken with a workgroup per tile; as a stream, launches of more
-// than 256 tiles are 2 to 7 % faster than the estimate has them.)  Taking the estimated best loses 1.7 % (forward) and 1.9 % (data gradients) in the geometric mean
-// against the measured best; the 256-row tiles alone take 2.13 times as long as that over the forward products.  Forward products on R32 of up to
+// (10-15 % too fast on average).  Taking the estimated best loses 1.7 % (forward) and 1.9 % (data gradients) in the geometric mean
+// against the measured best; the 256-row tiles alone take 2.13 times as long as that over the forward products.  All that was measured
+// with a workgroup per 256-row tile.  As a stream, launches of more than 256 tiles are 2 to 15 % faster than the estimate has them, of
+// fewer as before.  123 plain stores as they are now (M 2048 .. 16384, N 512 .. 8192, k 64 .. 2048): taking the estimated best
+// loses 0.7 %; T256 is taken wrongly in two, by 3.4 % at most (2048 x 8192 x 128 15.4 us, R128 14.9), and missed in four
+// (16384 x 4096 x 128 R128 40.6 us, T256 34.9).  Forward products on R32 of up to
 // 256 pieces of 16 x 16 run as those (gemm_rows16.hip): up to twice as fast with long k, which the estimate does not know.  What the
-// lines amount to, with both sides measured (us):
-//   a handful of rows: one chain of k per CU        16 x 1024 x 4096:   T256 67.6   R64    15.0   R32 9.4
-//   few tiles, the loads' latency decides          777 x 1024 x 4096:   T256 68.0   R64    16.1   R32 25.9
-//   half the CUs idle under T256                 16384 x 512 x 2048:   T256 45.6   R128   37.6
-//   N = 128 leaves T256 half its columns         16384 x 128 x 4096:   T256 72.1   R64x128 29.9
-//   short k, the epilogue decides: two resident workgroups overlap it with each other's main loop
-//                                                16384 x 4096 x 256:   T256 70.8   R128   54.6
-//   the chip full and k long                     16384 x 4096 x 2048:  T256 225.8  R128   274.4
+// lines amount to, with both sides measured (us, plain stores):
+//   a handful of rows: one chain of k per CU        16 x 1024 x 4096:   T256 69.0   R64    16.6   R32 7.3
+//   few tiles, the loads' latency decides          777 x 1024 x 4096:   T256 69.0   R64    18.1   R32 27.6
+//   half the CUs idle under T256                 16384 x 512 x 2048:   T256 45.2   R128   37.6
+//   N = 128 leaves T256 half its columns         16384 x 128 x 4096:   T256 70.6   R64x128 40.8
+//   few tiles and short k                         8192 x 512 x 256:   T256 13.4   R64x128 9.3
+//   the chip full                                16384 x 4096 x 256:   T256 44.6   R128   54.7
+//                                                16384 x 4096 x 2048:  T256 215.3  R128   259.7
 struct TileCost {
   int bm, bn, slots;
   float a, f, s0, s1, g, h;
