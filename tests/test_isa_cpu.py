@@ -81,3 +81,12 @@ def test_down_epilogue_waits_for_none_of_the_next_tile(kernels_256):
         assert waits and min(waits) >= 7, waits
         found += 1
     assert found == 1
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+def test_256_row_tiles_ask_for_all_lines_of_their_arguments_at_once(kernels_256):
+    """Six cache lines of arguments; each that is asked for later is a wait of its own before a workgroup's first loads."""
+    for name, body in kernels_256.items():
+        first = next(i for i, ln in enumerate(body) if re.match(r"\ts_waitcnt.*lgkmcnt", ln))
+        lines = {int(m[1], 16) // 64 for ln in body[:first] if (m := re.match(r"\ts_load_dword\S* \S+, s\[0:1\], (0x[0-9a-f]+)", ln))}
+        assert lines == set(range(6)), f"{name}: {sorted(lines)}"
