@@ -27,11 +27,12 @@
 // plain store) went into its start, the wait for its first slices and the drain of its stores, with the matrix pipes idle.
 // Now the first two slices of the next tile are under way before the epilogue starts, and the epilogue's stores drain behind
 // the next tile's first slice.  us, a workgroup per tile -> one stream (inside a block step):
-//   16384 x 11008 x 1024, plain store        352 -> 314      same, SwiGLU forward            449 -> 396
-//   16384 x  4096 x 1024, three members      379 -> 344      same, SwiGLU backward           555 -> 490
-//   16384 x  2048 x  512, three members      123 -> 108      11008 x 1024 x 16384 k-major    353 -> 341
-// Launches of one tile per CU have nothing to stream to and take what they took: 16384 x 1024 x 4096 112.0 -> 109.5, 777 x 11008 x 1024 29.3 ->
-// 29.0, k of one slice 1024 x 12288 x 64 12.2 -> 11.8; up to 5 % longer is the residual sum over a short k (16384 x 1024 x 256 26.6 -> 28.0).
+//   16384 x 11008 x 1024, plain store        341 -> 304      same, SwiGLU forward            442 -> 385
+//   16384 x  4096 x 1024, three members      366 -> 342      same, SwiGLU backward           543 -> 478
+//   16384 x  2048 x  512, three members      113 -> 106      11008 x 1024 x 16384 k-major    349 -> 337
+// Launches of one tile per CU have nothing to stream to and take what they took: 16384 x 1024 x 4096 111.1 -> 108.7, 777 x 11008 x 1024 27.8 ->
+// 27.6, k of one slice 1024 x 12288 x 64 12.2 -> 11.8; up to 5 % longer is the re-forward's residual sum over a short k (16384 x 1024 x 256
+// 25.2 -> 26.4).
 // The four-kilobyte staging space that this leaves a wavefront gives the epilogue rows of 128 bytes.  Rows of 256 through the free B slot
 // as well, with slice 1 of B loaded behind the epilogue, lost the gain (350 -> 350: its wait includes the stores); rows of 64
 // bytes (one MFMA block at a time) made epilogues that read tiles up to 30 % slower.  Where rows start between cache lines a piece spans
