@@ -14,12 +14,13 @@
 // lse * log2(e) from a small preprocessing kernel:
 //   dkv kernel - workgroup owns 128 keys, streams 64-query tiles from the diagonal on:
 //                S = Q K^T, dP = dO V^T, dV^T += dO^T P, dK^T += Q^T dS;
-//                in its usual form it also stores scale * dS^T (bf16, [key][query] per (batch, head)),
-//                and dQ = (scale dS^T)^T K is then one causal k-major GEMM (gemm_bf16.hip): the scores
-//                are formed once, 5 GEMM units in all
-//   dq kernel  - the form without that workspace (S not a multiple of 8, or too large): same walk as the
-//                forward (workgroup owns queries, streams keys): S^T, dP^T = V dO^T,
-//                dS^T = P^T*(dP^T - D), dQ^T += K^T dS^T; 7 units together with the dkv kernel
+//                in launches that leave CUs idle it also stores scale * dS^T (bf16, [key][query] per
+//                (batch, head)), and dQ = (scale dS^T)^T K is then one causal k-major GEMM
+//                (gemm_bf16.hip): the scores are formed once, 5 GEMM units in all
+//   dq kernel  - the form without that workspace (work for the whole chip; S not a multiple of 8, or
+//                too large): same walk as the forward (workgroup owns queries, streams keys): S^T,
+//                dP^T = V dO^T, dS^T = P^T*(dP^T - D), dQ^T += K^T dS^T; 7 units together with the
+//                dkv kernel
 //
 // Grouped-query form (fewer key / value heads than query heads, H / Hkv consecutive query heads per
 // key / value head): the same kernels with K and V addressed by head / group and their own row stride.
@@ -580,146 +581,229 @@ __global__ __launch_bounds__(256) void attn_dot_kernel(const uint16_t* __restric
 }
 
 // ----------------------------------------------------------------------------------------------
-// backward, dQ: workgroup owns 4 x 32 queries, streams 64-key tiles of K and V
+// backward, dQ: workgroup owns NW x 32 queries, streams 64-key tiles of K and V
+//
+// Bound: instruction issue beside the MFMAs, and the LDS port (every operand read feeds one MFMA, as in the forward).  With 32
+// queries a wavefront holds Q, dO, dQ and the scores of two 32-key blocks in 250 registers, so two of them share a SIMD, and the
+// elements of one block are threaded between the MFMAs of the next block's S and dP and its own outputs (the kernels above do the
+// same).  Four LDS stages: a tile's loads have two tiles' time to land; one barrier per tile.
+// Only a wavefront's last block lies on the diagonal; it is the only one that is masked, outside the loop.
+// Whole backward, us, 64 queries per wavefront, one wavefront per SIMD and one block after the other -> now: 2 x 2047 tokens, 32 / 8
+// heads 315 -> 275 (this kernel 173 -> 125); 1 x 777, 32 / 8 heads 71.6 -> 63.5; 4 x 4095, 8 heads 502 -> 449; 13 x 641, 32 heads
+// 496 -> 400; 1 x 3333, 16 heads 281 -> 195; 1 x 333, 32 / 8 heads 45.4 -> 41.4.
 // ----------------------------------------------------------------------------------------------
-template <int MB>
-__global__ __launch_bounds__(256) void attn_bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+constexpr int DQ_NS = 4;                                   // ring of key tiles: two in use, two on their way
+constexpr int DQ_LDS = DQ_NS * 2 * TILE_BYTES;
+
+constexpr int DQ_BAR = 5;       // slot of the barrier in the stage of a tile's first block
+// elements of dS done by the end of slot s: their operands are whole when their MFMAs come (slots 16, 20)
+constexpr int dq_elems(int s) { return s < 0 ? 0 : s < 20 ? 4 * (s + 1) / 5 : 16; }
+
+// SCALED: dS is scaled before it is rounded, as where it is stored (attn_bwd_dkv_kernel): dQ then has the bits of the product that
+// reads it there, whose order over the keys is this one.
+template <int NW, bool SCALED>
+__global__ __launch_bounds__(NW * 64, NW / 4) void attn_bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                                                           const uint16_t* __restrict__ v,
                                                           const uint16_t* __restrict__ dout,
                                                           const float* __restrict__ lse2, const float* __restrict__ D,
                                                           uint16_t* __restrict__ dq, int64_t ld, int64_t ldkv, int grp, int S, int H,
                                                           float scale) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  constexpr int BQ = 4 * MB * 32;
+  constexpr int BQ = NW * 32, NL = 16 / NW;                // queries per block, 1 KB loads per wavefront, tile and operand
+  constexpr int DQ_D = NW == 8 ? 4 : 8;                    // LDS operands are read this many MFMAs ahead (8 of 8 wavefronts: spills)
   // the wavefront index as a scalar: everything derived from it (LDS slots, tile rows) is scalar arithmetic
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nqb = (S + BQ - 1) / BQ;
   const WgCoord wg = wg_coord();
   const int head = wg.head, b = wg.b;
   const int64_t tok0 = (int64_t)b * S;
-  const int64_t hoff = head * HD;
+  const int64_t hoff = head * HD, kvoff = (head / grp) * HD;   // the key / value head this query head's group shares
   const float c = scale * LOG2E;
   // K is needed row-wise (S^T) and transposed (dQ^T), V row-wise (dP^T): one LDS copy each, in the
   // swizzle that serves both reads, written by direct-to-LDS loads.
-  const int64_t kvoff = (head / grp) * HD;     // the key / value head this query head's group shares
-  const rsrc_t rsK = tile_rsrc(k + tok0 * ldkv + kvoff);
-  const rsrc_t rsV = tile_rsrc(v + tok0 * ldkv + kvoff);
-  uint32_t offT[4];
-  int rowT[4];
-  dma_lane_offsets<SWZ_BOTH, 4>(offT, rowT, ldkv, wave, lane);
+  const rsrc_t rsK = rows_rsrc(k + tok0 * ldkv + kvoff, S, ldkv);
+  const rsrc_t rsV = rows_rsrc(v + tok0 * ldkv + kvoff, S, ldkv);
+  uint32_t offT[NL];
+  {
+    int row[NL];
+    dma_lane_offsets<SWZ_BOTH, NL>(offT, row, ldkv, wave, lane);
+  }
+  const uint32_t lds0 = (uint32_t)(uintptr_t)LRB_LDS_PTR(smem) + (uint32_t)wave * 1024u;
+  // Operand addresses inside a SWZ_BOTH tile (both_row_frag, both_tr_frag): the lane's part, from which the k16 step or the 32
+  // columns differ by an XOR, and rows by a constant.
+  uint32_t rowl, trl;
+  {
+    const int l31 = lane & 31, f = ((l31 & 3) << 2) | ((l31 >> 2) & 3), g = lane >> 4, s = lane & 15;
+    rowl = (uint32_t)(l31 * 256 + (((lane >> 5) ^ f) << 4));
+    trl = (uint32_t)(((g >> 1) * 4 + (s >> 2)) * 256 + ((((g & 1) * 2 + ((s & 3) >> 1)) ^ (((s >> 2) << 2) | (g >> 1))) << 4) + (s & 1) * 8);
+  }
   // one query block from the late end and its mirror image from the early end: equal work per workgroup
   for (int pass = 0; pass < 2; pass++) {
   const int qblk = pass == 0 ? nqb - 1 - wg.x : wg.x;
   if (pass == 1 && ((int)gridDim.x == nqb || qblk >= nqb - 1 - wg.x)) break;   // (unpaired launch: see the forward)
   const int q0 = qblk * BQ;
-  const int qw0 = q0 + wave * MB * 32;
+  const int qw0 = q0 + wave * 32;
+  const int ntiles = (min(S, q0 + BQ) + KT - 1) / KT;      // causal: keys up to the block's last query
+  const int nb = qw0 < S ? qw0 / 32 + 1 : 0;               // 32-key blocks up to this wavefront's diagonal
+  // load i of the 2 NL of key tile t (K, then V); a tile past the last one: every lane out of range, so that every tile costs
+  // every wavefront the same number of loads
+  auto dma = [&](int t, int i) {
+    lds_dma_at(rsrc_from(i < NL ? rsK : rsV, (uint32_t)t * (uint32_t)(KT * 2) * (uint32_t)ldkv, t < ntiles),
+               lds0 + (uint32_t)(t % DQ_NS) * (2 * TILE_BYTES) + (uint32_t)((i / NL) * TILE_BYTES + (i % NL) * NW * 1024), offT[i % NL]);
+  };
+  __syncthreads();                                         // the pass before is done with the ring
 
-  // Q and dO rows of this wavefront stay in registers (B operands); every K / V fragment read from
-  // LDS then feeds MB MFMAs.
-  bf16x8 qf[MB][8], dof[MB][8];
-  load_row_frags<MB>(qf, q + tok0 * ld + hoff, ld, qw0, S, lane);
-  load_row_frags<MB>(dof, dout + tok0 * ld + hoff, ld, qw0, S, lane);
-  float lsq[MB], Dq[MB];
+  // Q and dO rows of this wavefront stay in registers (B operands).
+  bf16x8 qf[1][8], dof[1][8];
+  load_row_frags<1>(qf, q + tok0 * ld + hoff, ld, qw0, S, lane);
+  load_row_frags<1>(dof, dout + tok0 * ld + hoff, ld, qw0, S, lane);
+  const int qi = qw0 + (lane & 31);                        // this lane's query
+  const int64_t sidx = ((int64_t)b * H + head) * S + min(qi, S - 1);
+  float lsq = lse2[sidx], Dq = D[sidx];
 #pragma unroll
-  for (int mb = 0; mb < MB; mb++) {
-    const int qi = qw0 + mb * 32 + (lane & 31);
-    const int64_t sidx = ((int64_t)b * H + head) * S + min(qi, S - 1);
-    lsq[mb] = lse2[sidx];
-    Dq[mb] = D[sidx];
-  }
+  for (int t = 0; t < 3; t++)
+#pragma unroll
+    for (int i = 0; i < 2 * NL; i++) dma(t, i);
 
-  f32x16 acc[MB][4];
+  f32x16 acc[4];                                           // dQ^T
 #pragma unroll
-  for (int mb = 0; mb < MB; mb++)
+  for (int hb = 0; hb < 4; hb++)
 #pragma unroll
-    for (int hb = 0; hb < 4; hb++)
-#pragma unroll
-      for (int e = 0; e < 16; e++) acc[mb][hb][e] = 0.f;
+    for (int e = 0; e < 16; e++) acc[hb][e] = 0.f;
+  wait_vm<4 * NL>();                                       // the first of the three tiles has landed
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" : "+v"(lsq), "+v"(Dq) : : "memory");     // (used here, so that no wait for them stays in the loop)
 
-  constexpr int STAGE = 2 * TILE_BYTES;                  // K, V
-  const int kv_end = min(S, q0 + BQ);
-  const int ntiles = (kv_end + KT - 1) / KT;
-  dma_tile<4>(rsK, smem, offT, rowT, 0, S, ldkv, wave);
-  dma_tile<4>(rsV, smem + TILE_BYTES, offT, rowT, 0, S, ldkv, wave);
-  wait_vm0();
-  __syncthreads();
-
-  for (int j = 0; j < ntiles; j++) {
-    const int cur = j & 1;
-    if (j + 1 < ntiles) {                                // lands while this tile is worked on
-      dma_tile<4>(rsK, smem + (cur ^ 1) * STAGE, offT, rowT, (j + 1) * KT, S, ldkv, wave);
-      dma_tile<4>(rsV, smem + (cur ^ 1) * STAGE + TILE_BYTES, offT, rowT, (j + 1) * KT, S, ldkv, wave);
+  struct Scores { f32x16 s, dp; };                         // rows = keys of a 32-key block, column = query: S^T and dP^T
+  Scores sa, sb;                                           // of a tile's first and second block
+  bf16x8 fr[DQ_D];                                         // operands read ahead, slot s in fr[s % DQ_D]
+  uint32_t dw[8];                                          // dS as bf16 pairs: two operands
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  auto tile = [&](int t) -> uint32_t { return (uint32_t)(t % DQ_NS) * (2 * TILE_BYTES); };
+  // operand of slot s: 0..15 the next block's rows (k16 step s / 2, K then V), 16..23 the current block's columns of K (16 keys
+  // each four slots)
+  auto read_frag = [&](auto Sc, uint32_t cur, auto CRB, uint32_t nxt, auto NRB) {
+    constexpr int s = decltype(Sc)::value;
+    if constexpr (s < 16) {
+      fr[s % DQ_D] = lds_b128(smem + ((nxt + rowl) ^ (uint32_t)((s >> 1) << 5)) + (s & 1) * TILE_BYTES + decltype(NRB)::value * 8192);
+    } else {
+      typedef short s16x8 __attribute__((ext_vector_type(8)));
+      constexpr int off = decltype(CRB)::value * 8192 + ((s - 16) >> 2) * 4096;
+      const uint32_t at = (cur + trl) ^ (uint32_t)((s & 3) << 6);
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(smem + at + off));
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(smem + (at ^ 32u) + off + 2048));
+      const s16x8 r = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+      fr[s % DQ_D] = __builtin_bit_cast(bf16x8, r);
     }
-    const unsigned char* sK = smem + cur * STAGE;
-    const unsigned char* sVb = sK + TILE_BYTES;
-    const int key0 = j * KT;
-    // one 32-key block at a time; blocks entirely after this wavefront's queries are skipped
-#pragma unroll 1
-    for (int nb = 0; nb < 2; nb++) {
-      const int kb0 = key0 + nb * 32;
-      if (kb0 > qw0 + MB * 32 - 1 || kb0 >= S) continue;
-      f32x16 st[MB], dp[MB];
-#pragma unroll
-      for (int mb = 0; mb < MB; mb++)
-#pragma unroll
-        for (int e = 0; e < 16; e++) { st[mb][e] = 0.f; dp[mb][e] = 0.f; }
-#pragma unroll
-      for (int ks = 0; ks < 8; ks++) {
-        const bf16x8 kfr = both_row_frag(sK, nb * 32, ks, lane), vfr = both_row_frag(sVb, nb * 32, ks, lane);
-#pragma unroll
-        for (int mb = 0; mb < MB; mb++) {
-          st[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr, qf[mb][ks], st[mb], 0, 0, 0);
-          dp[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfr, dof[mb][ks], dp[mb], 0, 0, 0);
-        }
-      }
-      // dS^T = P^T * (dP^T - D), masked on the diagonal / tail blocks only
-      const bool need_mask = (kb0 + 31 > qw0) || (kb0 + 32 > S);
-      auto elements = [&](auto MASKED) {   // one wavefront-uniform branch around two copies of the loop
-#pragma unroll
-        for (int mb = 0; mb < MB; mb++) {
-          const int qi = qw0 + mb * 32 + (lane & 31);
-#pragma unroll
-          for (int e = 0; e < 16; e++) {
-            float p = fast_exp2(fmaf(st[mb][e], c, -lsq[mb]));
-            if constexpr (decltype(MASKED)::value) {
-              const int key = kb0 + acc_row(e, lane);
-              p = (key > qi || key >= S) ? 0.f : p;
-            }
-            st[mb][e] = p * (dp[mb][e] - Dq[mb]);
-          }
-        }
-      };
-      if (need_mask) {
-        asm volatile("" ::: "memory");
-        elements(std::true_type{});
-      } else {
-        elements(std::false_type{});
-      }
-#pragma unroll
-      for (int t = 0; t < 2; t++) {
-        bf16x8 dsf[MB];
-#pragma unroll
-        for (int mb = 0; mb < MB; mb++) dsf[mb] = pack_acc_half(st[mb], t);
-#pragma unroll
-        for (int hb = 0; hb < 4; hb++) {
-          const bf16x8 ktf = both_tr_frag(sK, nb * 32 + t * 16, hb * 32, lane);
-#pragma unroll
-          for (int mb = 0; mb < MB; mb++)
-            acc[mb][hb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ktf, dsf[mb], acc[mb][hb], 0, 0, 0);
-        }
-      }
+  };
+  auto mfma = [&](auto Sc, Scores& nx) {
+    constexpr int s = decltype(Sc)::value;
+    constexpr f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    const bf16x8 f = fr[s % DQ_D];
+    if constexpr (s < 16) {
+      if constexpr (s & 1) nx.dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, dof[0][s >> 1], s < 2 ? zero : nx.dp, 0, 0, 0);
+      else nx.s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, qf[0][s >> 1], s < 2 ? zero : nx.s, 0, 0, 0);
+    } else {
+      constexpr int t = (s - 16) >> 2, hb = s & 3;
+      const bf16x8 x = __builtin_bit_cast(bf16x8, make_uint4(dw[t * 4], dw[t * 4 + 1], dw[t * 4 + 2], dw[t * 4 + 3]));
+      acc[hb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, x, acc[hb], 0, 0, 0);
     }
-    wait_vm0();
-    __syncthreads();
-  }
+  };
+  // elements F .. T - 1 of dS^T = P^T * (dP^T - D) of the current block, whose first key is kb0
+  float dlow = 0.f;
+  auto elements = [&](auto Fc, auto Tc, auto MASK, const Scores& x, int kb0) {
+    constexpr int f = decltype(Fc)::value, t = decltype(Tc)::value;
+    unroll_for<t - f>([&](auto I) {
+      constexpr int e = f + decltype(I)::value;
+      float p = fast_exp2(fmaf(x.s[e], c, -lsq));
+      if constexpr (decltype(MASK)::value) p = kb0 + acc_row(e, lane) > qi ? 0.f : p;
+      const float ds = (SCALED ? p * scale : p) * (x.dp[e] - Dq);
+      if constexpr (e & 1) dw[e >> 1] = pack_bf16x2(dlow, ds);
+      else dlow = ds;
+    });
+  };
+  // this wavefront's loads of tile t + 1 have landed (behind them are the next tile's, and loads retire in order), then
+  // everyone's, and everyone has left tile t - 1, whose slot is loaded anew
+  auto meet = [&] {
+    wait_vm<2 * NL>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  // Elements and outputs of the current block (half CRB of tile t) with the scores of the next one (half 1 - CRB, tile t or
+  // t + 1) between them.  The first operands were read by the stage before, and this one reads those of the stage after.
+  auto stage = [&](int t, auto CRB, const Scores& cu, Scores& nx) {
+    constexpr int crb = decltype(CRB)::value;
+    using Other = std::integral_constant<int, crb ^ 1>;
+    const uint32_t cur = tile(t), after = tile(t + 1);     // after: of the stage after, half 1 of tile t + 1, or half 0 of it
+    const uint32_t nxt = crb ? after : cur;
+    // Slots in pairs, the operand that was asked for last first: one wait serves both.
+    unroll_for<12>([&](auto Uc) {
+      constexpr int u = decltype(Uc)::value, s = 2 * u + 1;
+      mfma(std::integral_constant<int, s>{}, nx);
+      mfma(std::integral_constant<int, s - 1>{}, nx);
+      if constexpr (crb == 0 && s == DQ_BAR) meet();
+      unroll_for<2>([&](auto I) {
+        constexpr int r = s - 1 + decltype(I)::value;
+        if constexpr (crb == 0 && r > DQ_BAR && r <= DQ_BAR + 2 * NL) dma(t + 3, r - DQ_BAR - 1);
+        if constexpr (r + DQ_D < 24) read_frag(std::integral_constant<int, r + DQ_D>{}, cur, CRB, nxt, Other{});
+        else read_frag(std::integral_constant<int, r + DQ_D - 24>{}, cur, CRB, after, CRB);
+      });
+      elements(std::integral_constant<int, dq_elems(s - 2)>{}, std::integral_constant<int, dq_elems(s)>{}, std::false_type{}, cu, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  // the diagonal block, at cur and from key kb0 on, whose scores are there
+  auto last = [&](uint32_t cur, int kb0, const Scores& x) {
+    Scores none;
+    unroll_for<DQ_D>([&](auto I) { read_frag(std::integral_constant<int, 16 + decltype(I)::value>{}, cur, I0{}, cur, I0{}); });
+    elements(I0{}, std::integral_constant<int, 8>{}, std::true_type{}, x, kb0);
+    __builtin_amdgcn_sched_barrier(0);
+    elements(std::integral_constant<int, 8>{}, std::integral_constant<int, 16>{}, std::true_type{}, x, kb0);
+    __builtin_amdgcn_sched_barrier(0);
+    unroll_for<8>([&](auto I) {
+      constexpr int s = 16 + decltype(I)::value;
+      mfma(std::integral_constant<int, s>{}, none);
+      if constexpr (s + DQ_D < 24) read_frag(std::integral_constant<int, s + DQ_D>{}, cur, I0{}, cur, I0{});
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+
+  int t = 0;
+  if (nb > 0) {
+    unroll_for<DQ_D>([&](auto I) { read_frag(I, 0, I0{}, 0, I0{}); });    // scores of the first block
+    unroll_for<16>([&](auto Sc) {
+      constexpr int s = decltype(Sc)::value;
+      mfma(Sc, sa);
+      if constexpr (s + DQ_D < 16) read_frag(std::integral_constant<int, s + DQ_D>{}, 0, I0{}, 0, I0{});
+    });
+    unroll_for<DQ_D>([&](auto I) { read_frag(I, 0, I0{}, 0, I1{}); });    // (unused where there is no second block)
+    for (; 2 * t + 2 < nb; t++) {
+      stage(t, I0{}, sa, sb);
+      stage(t, I1{}, sb, sa);
+    }
+    const int odd = 2 * t + 1 < nb;                        // one more block before the diagonal
+    if (odd) {
+      stage(t, I0{}, sa, sb);
+      sa = sb;
+    } else {
+      meet();
 #pragma unroll
-  for (int mb = 0; mb < MB; mb++) {
-    const int qi = qw0 + mb * 32 + (lane & 31);
-    if (qi < S) store_acc_T(dq + (tok0 + qi) * ld + hoff, acc[mb], scale, lane);
+      for (int i = 0; i < 2 * NL; i++) dma(t + 3, i);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    last(tile(t) + (uint32_t)odd * 8192u, t * KT + odd * 32, sa);
+    t++;
   }
+  for (; t < ntiles; t++) {                                // nothing left for this wavefront but its share of the loads
+    meet();
+#pragma unroll
+    for (int i = 0; i < 2 * NL; i++) dma(t + 3, i);
+  }
+  if (qi < S) store_acc_T(dq + (tok0 + qi) * ld + hoff, acc, SCALED ? 1.f : scale, lane);
   }  // pass
+  wait_vm0();                                              // no load into LDS outlives the workgroup
 }
-constexpr int DQ_LDS = 4 * TILE_BYTES;   // K and V, double buffered
 
 // ----------------------------------------------------------------------------------------------
 // backward, dK and dV: workgroup owns 4 x 32 keys, streams 64-query tiles of Q and dO
@@ -1206,7 +1290,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_long_kernel(const uint16_t* 
 // dK / dV kernels, in the same order: the same bits.
 // Whole backward, us, the other kernels -> this one: 2 x 2047 tokens, 32 / 8 heads 338 -> 308; 2 x 1501, 32 heads 245 -> 224; 4 x 4095, 8
 // heads 524 -> 497; 1 x 12001, 8 heads 1237 -> 1147; 16 x 300, 16 heads 115 -> 101; 16 x 500, 32 heads 327 -> 316.
-// With the score gradient stored as well the stores were what it waited for (8 x 2048, 16 heads 621 -> 634): not done there.
+// With the score gradient stored as well the stores were what it waited for (8 x 2048, 16 heads 621 -> 634): not done.
 // ----------------------------------------------------------------------------------------------
 constexpr int PAIR_NS = 5;                                       // ring of 32-query blocks: one or two in use, three on their way
 constexpr int PAIR_BLOCK = 2 * 32 * HD * 2 + 512;                // Q rows, dO rows, lse2, D (64 entries each, 32 used)
@@ -1216,6 +1300,7 @@ constexpr int PAIR_LDS = PAIR_NONE + 256;
 constexpr int PAIR_D = 2;                                        // LDS operands are read this many pairs of MFMAs ahead
 static_assert(PAIR_BLOCK % 256 == 0 && PAIR_LDS <= 160 * 1024, "LDS of a CU");
 
+template <bool SCALED>
 __global__ __launch_bounds__(512) void attn_bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                                                                 const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
                                                                 const float* __restrict__ lse2, const float* __restrict__ D,
@@ -1413,7 +1498,7 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_pair_kernel(const uint16_t* 
           for (int nb = 0; nb < decltype(NB)::value; nb++) {
             const f32x4 p = *reinterpret_cast<const f32x4*>(xp + (nb * 4 + g) * 1024);
 #pragma unroll
-            for (int r = 0; r < 4; r++) x[nb][4 * g + r] = p[r] * (x[nb][4 * g + r] - dvv[r]);   // dS
+            for (int r = 0; r < 4; r++) x[nb][4 * g + r] = (SCALED ? p[r] * scale : p[r]) * (x[nb][4 * g + r] - dvv[r]);   // dS
           }
           if constexpr (g & 1)
 #pragma unroll
@@ -1429,7 +1514,7 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_pair_kernel(const uint16_t* 
 #pragma unroll
     for (int nb = 0; nb < 2; nb++) {
       const int ni = nw0 + nb * 32 + (lane & 31);
-      if (ni < S) store_acc_T((second ? dk : dv) + (tok0 + ni) * lddkv + hoff, acc[nb], second ? scale : 1.f, lane);
+      if (ni < S) store_acc_T((second ? dk : dv) + (tok0 + ni) * lddkv + hoff, acc[nb], second && !SCALED ? scale : 1.f, lane);
     }
   }  // pass
   wait_vm0();                                              // no load into LDS outlives the workgroup
@@ -1509,7 +1594,12 @@ hipError_t attention_gqa_fwd_bf16(const void* q, const void* k, const void* v, v
 // The backward runs in one of two forms.  With the score gradient kept (S a multiple of 8, and
 // B * H * S^2 bf16 values within the cap below): the dK / dV kernel also writes scale * dS^T and dQ is
 // one k-major GEMM over it, 5 GEMM units in all.  Otherwise: a second kernel recomputes S, dP and dS for
-// dQ, 7 units and no large workspace.
+// dQ, 7 units and no large workspace.  Where the pairs of wavefronts find work for the whole chip (dkv_pairs), forming the
+// score gradient twice is faster than the way through memory, and the kernels round it where the first form does: the same
+// bits.  Whole backward, us, kept -> formed twice: 4 x 4096 tokens, 32 heads 2098 -> 1841; 8 x 2048, 16 heads 644 -> 542; 1 x 8192, 16 heads
+// 980 -> 853; 8 x 1024, 16 heads 204 -> 178; 16 x 264, 32 heads 157 -> 152; elsewhere 2 x 1536, 16 heads 106 / 115; 1 x 2048, 8 heads 99 / 104,
+// 128 x 128, 16 heads 243 / 280.
+// (The size query counts the first form wherever S allows it: a workspace for more tokens serves for fewer.)
 constexpr size_t DS_WS_CAP = (size_t)24 << 30;
 static bool keep_ds(int B, int S, int H) {
   return S % 8 == 0 && (int64_t)S * S * 2 < (int64_t)0x7fffffff && (size_t)B * H * S * S * 2 <= DS_WS_CAP;
@@ -1552,10 +1642,12 @@ hipError_t attention_gqa_bwd_bf16(const void* q, const void* k, const void* v, c
   // 32-bit buffer offsets per (batch, head)
   if ((int64_t)S * ld * 2 >= (int64_t)0x7fffffff || (int64_t)S * ldkv * 2 >= (int64_t)0x7fffffff) return hipErrorNotSupported;
   static const hipError_t attr_err = [] {
-    hipError_t e = set_lds(attn_bwd_dq_kernel<1>, DQ_LDS);
-    if (e == hipSuccess) e = set_lds(attn_bwd_dq_kernel<2>, DQ_LDS);
+    hipError_t e = set_lds(attn_bwd_dq_kernel<4, false>, DQ_LDS);
+    if (e == hipSuccess) e = set_lds(attn_bwd_dq_kernel<8, false>, DQ_LDS);
+    if (e == hipSuccess) e = set_lds(attn_bwd_dq_kernel<8, true>, DQ_LDS);
     if (e == hipSuccess) e = set_lds(attn_bwd_dkv_long_kernel, LDKV_LDS);
-    if (e == hipSuccess) e = set_lds(attn_bwd_dkv_pair_kernel, PAIR_LDS);
+    if (e == hipSuccess) e = set_lds(attn_bwd_dkv_pair_kernel<false>, PAIR_LDS);
+    if (e == hipSuccess) e = set_lds(attn_bwd_dkv_pair_kernel<true>, PAIR_LDS);
     if (e == hipSuccess) e = set_lds(attn_bwd_dkv_kernel<DKV_NB, false>, DKV_LDS);
     if (e == hipSuccess) e = set_lds(attn_bwd_dkv_kernel<DKV_NB, true>, DKV_LDS);
     return e;
@@ -1584,7 +1676,9 @@ hipError_t attention_gqa_bwd_bf16(const void* q, const void* k, const void* v, c
                        part_elems, (uint16_t*)dk, (uint16_t*)dv, ldkv, grp, H, T);
     return hipGetLastError();
   };
-  if (keep_ds(B, S, H)) {
+  const int64_t heads = (int64_t)H * B;
+  const bool pairs = dkv_pairs(S, heads), kept = keep_ds(B, S, H);
+  if (kept && !pairs) {
     uint16_t* dst = (uint16_t*)((char*)ws + small);
     hipLaunchKernelGGL((attn_bwd_dkv_kernel<DKV_NB, true>), kv_grid, dim3(256), DKV_LDS, st, (const uint16_t*)q,
                        (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout, lse2, D, dk_w, dv_w, dst, ld, ldkv,
@@ -1605,23 +1699,30 @@ hipError_t attention_gqa_bwd_bf16(const void* q, const void* k, const void* v, c
     e = gemm_bf16_untimed(op, st);
     return e != hipSuccess ? e : group_sum();
   }
-  // dQ: 64 queries per wavefront, a block of 256 and its mirror per workgroup; where that leaves CUs idle a block each, and
-  // of 128 queries where those find a CU each (whole backward, us, pairs only -> now: 1 x 333 tokens, 32 / 8 heads 74.5 -> 45.3;
-  // 1 x 777, 32 / 8 heads 125.8 -> 71.1; 2 x 1031, 16 heads 154.6 -> 118.7; 4 x 1501, 16 heads, paired as before, 247 -> 246).
-  auto dq_launch = [&](auto MBc, bool paired) {
-    constexpr int MB = decltype(MBc)::value;
-    const int n = (S + MB * 128 - 1) / (MB * 128);
-    hipLaunchKernelGGL(attn_bwd_dq_kernel<MB>, dim3(paired ? (n + 1) / 2 : n, H, B), dim3(256), DQ_LDS, st, (const uint16_t*)q,
-                       (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout, lse2, D, (uint16_t*)dq, ld, ldkv, grp,
-                       S, H, scale);
+  // dQ: a block of 256 queries and its mirror per workgroup; where that leaves CUs idle a block each, and of 128 queries where
+  // those find a CU each.  Of few long blocks of 256 the last ones decide, so from 1024 tokens on they are halved and paired
+  // (whole backward, us, a block of 256 each / 128 and its mirror: 4 x 4095 tokens, 4 heads 279 / 253, 1 x 3333, 16 heads 216 / 195,
+  // 4 x 1501, 8 heads 121 / 112, 2 x 1031, 16 heads 95.1 / 93.3; 4 x 700, 12 heads 76 / 78).
+  auto dq_launch = [&](auto NWc, auto SCALED, bool paired) {
+    constexpr int NW = decltype(NWc)::value;
+    const int n = (S + NW * 32 - 1) / (NW * 32);
+    hipLaunchKernelGGL((attn_bwd_dq_kernel<NW, decltype(SCALED)::value>), dim3(paired ? (n + 1) / 2 : n, H, B), dim3(NW * 64), DQ_LDS, st,
+                       (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout, lse2, D, (uint16_t*)dq, ld,
+                       ldkv, grp, S, H, scale);
   };
-  const int64_t heads = (int64_t)H * B;
-  if ((S + 127) / 128 * heads <= 256) dq_launch(std::integral_constant<int, 1>{}, false);
-  else dq_launch(std::integral_constant<int, 2>{}, (S + 255) / 256 * heads > 256);
-  if (dkv_pairs(S, heads))
-    hipLaunchKernelGGL(attn_bwd_dkv_pair_kernel, dim3(((S + 255) / 256 + 1) / 2, H, B), dim3(512), PAIR_LDS, st, (const uint16_t*)q,
-                       (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout, lse2, D, dk_w, dv_w, ld, ldkv, lddkv, grp, S, H,
-                       scale);
+  using Four = std::integral_constant<int, 4>;
+  using Eight = std::integral_constant<int, 8>;
+  if (pairs && kept) dq_launch(Eight{}, std::true_type{}, true);   // (pairs: more than 256 blocks of 256)
+  else if ((S + 127) / 128 * heads <= 256) dq_launch(Four{}, std::false_type{}, false);
+  else if (S >= 1024 && (S + 255) / 256 * heads <= 256) dq_launch(Four{}, std::false_type{}, true);
+  else dq_launch(Eight{}, std::false_type{}, (S + 255) / 256 * heads > 256);
+  auto pair_launch = [&](auto SCALED) {
+    hipLaunchKernelGGL(attn_bwd_dkv_pair_kernel<decltype(SCALED)::value>, dim3(((S + 255) / 256 + 1) / 2, H, B), dim3(512), PAIR_LDS, st,
+                       (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout, lse2, D, dk_w, dv_w, ld, ldkv,
+                       lddkv, grp, S, H, scale);
+  };
+  if (pairs && kept) pair_launch(std::true_type{});
+  else if (pairs) pair_launch(std::false_type{});
   else if (S >= ((int)kv_grid.x == nkb ? LDKV_MIN_S : LDKV_MIN_S_PAIRED))
     hipLaunchKernelGGL(attn_bwd_dkv_long_kernel, kv_grid, dim3(256), LDKV_LDS, st, (const uint16_t*)q, (const uint16_t*)k,
                        (const uint16_t*)v, (const uint16_t*)dout, lse2, D, dk_w, dv_w, ld, ldkv, lddkv, grp, S, H, scale);

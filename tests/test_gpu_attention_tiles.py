@@ -186,3 +186,26 @@ def test_attention_bwd_pairs_of_wavefronts(S, n):
     part = B.lr_attention_gqa_bwd(*(t[-S:] for t in (q, k, v, o, do)), lse[n - 1:].contiguous(), 1, S, H, Hkv, HD)
     for a, b in zip(part, full):
         assert a.isnan().any() and torch.equal(a.nan_to_num(nan=7.0), b[-S:].nan_to_num(nan=7.0))
+
+
+@pytest.mark.parametrize("S,n", [(1025, 10), (1281, 9), (2047, 6)])
+def test_attention_bwd_paired_query_blocks(S, n):
+    """dQ on blocks of 128 queries and their mirrors, where blocks of 256 are no more than CUs: odd and even numbers of blocks; the
+    bits of one sequence, a workgroup per block."""
+    H, Hkv = 4, 2
+    print(f"attention backward, paired query blocks S={S} B={n}", flush=True)
+    n128, n256 = (S + 127) // 128, (S + 255) // 256
+    assert n256 * H * n <= 256 < n128 * H * n
+    assert [_bwd_launches(S, m, H, Hkv)[0][:2] for m in (n, 1)] == [((n128 + 1) // 2 * H * n, 256), (n128 * H, 256)]
+    _compare_parts(S, n, (1,), H, Hkv)
+
+
+@pytest.mark.parametrize("S,n", [(264, 40), (288, 40), (512, 36), (776, 18), (1280, 13), (2048, 9)])
+def test_attention_bwd_score_gradient_kept_or_formed_twice(S, n):
+    """Multiples of 8 tokens: one sequence stores the score gradient for dQ's product, enough of them form it twice; the same bits."""
+    H, Hkv = 4, 2
+    print(f"attention backward, score gradient kept or not S={S} B={n}", flush=True)
+    pairs = ((S + 255) // 256 + 1) // 2 * H * n
+    many, one = _bwd_launches(S, n, H, Hkv), _bwd_launches(S, 1, H, Hkv)
+    assert [k[:2] for k in many] == [(pairs, 512)] * 2 and one[0][:2] == ((S + 127) // 128 * H, 256)
+    _compare_parts(S, n, (1,), H, Hkv)
