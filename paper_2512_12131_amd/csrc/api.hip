@@ -721,13 +721,21 @@ void single_up_bwd(Ctx& c, const Blk& b, const void* dout, int64_t N, const void
 
 // The gate / up pair of the MLP: g = act_g . W_up_g^T, then u = act_u . W_up_u^T whose epilogue forms
 // m = SiLU(g) * u from its fp32 accumulators and the g tile just written (the SwiGLU gate never
-// runs as a pass of its own).  u itself is stored only where a buffer is given: the forward has no use
-// for it, the backward's re-forward does.  ld: row stride of all three
-void mlp_up_swiglu(Ctx& c, const Blk& b, const void* w_up_gu, const void* act, void* g, void* u, void* m, int64_t ld) {
+// runs as a pass of its own); or one launch that forms both tiles and m from them.  g and u themselves are wanted only by the
+// backward's re-forward and a caller that keeps them (g_wanted; u null): the forward has no use for them.  ld: row stride of all three
+void mlp_up_swiglu(Ctx& c, const Blk& b, const void* w_up_gu, const void* act, void* g, bool g_wanted, void* u, void* m, int64_t ld) {
   const size_t es = 2;
   GemmOp up;
   up.A = act; up.lda = 2 * b.r; up.B = w_up_gu; up.ldb = b.r; up.C = g; up.ldc = ld;
   up.M = (int)b.T; up.N = (int)b.f; up.K = (int)b.r;
+  GemmOp both = up;
+  both.sA = b.r; both.sB = b.f * b.r; both.C = u;
+  both.epi.kind = EPI_SWIGLU_DUAL; both.epi.R = g_wanted ? g : nullptr; both.epi.ldr = ld; both.epi.C2 = m; both.epi.ldc2 = ld;
+  if (!c.dry && gemm_bf16_dual_tile(both)) {
+    c.submit(both);
+    c.flush();          // (and what a caller holds beside it)
+    return;
+  }
   up.epi.kind = EPI_STORE;
   gemm(c, up);
   c.flush();            // (g, and what a caller holds beside it)
@@ -822,7 +830,7 @@ void block_fwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   m.lax = lax; m.h_prev = lax ? lx->h_prev_gu : nullptr;
   m.w_scaled_given = scaled; m.w_scaled = w_scaled ? w_scaled + (size_t)3 * r * d * es : nullptr;
   group_down_seq(c, m, act);
-  mlp_up_swiglu(c, b, p->w_up_gu, act, gg, uu, mm, ldf);
+  mlp_up_swiglu(c, b, p->w_up_gu, act, gg, sv != nullptr, uu, mm, ldf);
   single_down(c, b, mm, ldf, f, p->w_dn_d, ck ? ck->z_d : nullptr, act, lax, lax ? lx->h_prev_d : nullptr);
   single_up(c, b, act, p->w_up_d, d, nullptr, y, b.stat_y_out, nullptr, h1f);   // optionally sum y^2 for the block above
 }
@@ -898,7 +906,7 @@ void block_bwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   GrpArgs m = group_args(b, 2, f);
   m.x = h1; m.gamma = p->gamma2; m.w_down_cat = p->w_dn_gu; m.w_up_stack = p->w_up_gu; m.y_stack = big;
   m.lddy = ldw; m.dy_bs = T * ldw;
-  if (!sv) mlp_up_swiglu(c, b, p->w_up_gu, act_g, big, (char*)big + (size_t)T * ldf * es, mm, ldf);
+  if (!sv) mlp_up_swiglu(c, b, p->w_up_gu, act_g, big, true, (char*)big + (size_t)T * ldf * es, mm, ldf);
   c.flush();
   // down-D backward: dW_dn_d = dz_d^T . m ; dm = dz_d . W_dn_d with the SwiGLU reverse fused in
   c.hold();

@@ -35,12 +35,16 @@ enum EpiKind : int {
   EPI_UP_I32 = 11,
   EPI_NORMBWD_O32 = 12,
   EPI_NORMBWD_I32 = 13,
-  EPI_ACTGRAD_A = 14   // EPI_ACTGRAD, and C2 = act(R): the rank-r activation that the up-projection's weight gradient reads
+  EPI_ACTGRAD_A = 14,  // EPI_ACTGRAD, and C2 = act(R): the rank-r activation that the up-projection's weight gradient reads
+  // Two products in one launch (ring tiles): g = A B^T, then u = A' B'^T with A' = A + sA, B' = B + sB.  R (written here, if given) = g;
+  // C = u (skipped when null), C2 = silu(g as stored) * u
+  EPI_SWIGLU_DUAL = 15
 };
 // the formula an epilogue kind applies (the fp32-residual forms share EPI_UP's and EPI_NORMBWD's)
 constexpr int epi_base(int kind) {
   return kind == EPI_ACTGRAD_A ? (int)EPI_ACTGRAD : (kind == EPI_UP_O32 || kind == EPI_UP_I32) ? (int)EPI_UP
-         : (kind == EPI_NORMBWD_O32 || kind == EPI_NORMBWD_I32) ? (int)EPI_NORMBWD : kind;
+         : (kind == EPI_NORMBWD_O32 || kind == EPI_NORMBWD_I32) ? (int)EPI_NORMBWD
+         : kind == EPI_SWIGLU_DUAL ? (int)EPI_SWIGLU_FWD : kind;
 }
 constexpr bool epi_r_is_f32(int kind) { return kind == EPI_UP_I32 || kind == EPI_NORMBWD_I32; }
 constexpr bool epi_writes_f32(int kind) { return kind == EPI_UP_O32 || kind == EPI_NORMBWD_O32; }
@@ -130,6 +134,8 @@ hipError_t gemm_ring128w(const GemmOp& op, hipStream_t st);   // two k-major ope
 // true when gemm_bf16 reads a k-major B operand beside a k-contiguous A in place (no transposed copy)
 bool gemm_bf16_mixed_ok(const GemmOp& op);
 hipError_t gemm_bf16(const GemmOp& op, hipStream_t st);
+// The tile on which EPI_SWIGLU_DUAL is estimated to be faster than its two products apart (EPI_STORE, then EPI_SWIGLU_FWD), or 0.
+int gemm_bf16_dual_tile(const GemmOp& op);
 // the same launch, never counted by the benchmark timer below (launches that are not projection GEMMs)
 hipError_t gemm_bf16_untimed(const GemmOp& op, hipStream_t st);
 // true when gemm_bf16 can run `op` with both operands k-major (no transposed copies needed)

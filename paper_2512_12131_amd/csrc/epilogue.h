@@ -66,7 +66,7 @@ struct VecIO<bf16_t, 1> {
 template <int KIND>
 __device__ __forceinline__ bool epi_reads_r(const Epilogue& e) {
   if constexpr (KIND == EPI_UP || KIND == EPI_NORMBWD || KIND == EPI_DOWN_LAX || KIND == EPI_LAXGRAD) return e.R != nullptr;
-  return epi_base(KIND) == EPI_ACTGRAD || KIND == EPI_SWIGLU_BWD || KIND == EPI_SWIGLU_FWD;
+  return epi_base(KIND) == EPI_ACTGRAD || KIND == EPI_SWIGLU_BWD || KIND == EPI_SWIGLU_FWD;   // (a gate of its own: written, never read)
 }
 template <int KIND>
 __device__ __forceinline__ bool epi_reads_r2(const Epilogue& e) {

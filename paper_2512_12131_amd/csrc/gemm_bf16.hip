@@ -587,6 +587,14 @@ float epi_traffic(int kind) {
     default: return 5.f;   // EPI_NORMBWD_O32
   }
 }
+float epi_traffic(const GemmOp& op) {
+  if (op.epi.kind == EPI_SWIGLU_DUAL) return 1.f + (op.epi.R ? 1.f : 0.f) + (op.C ? 1.f : 0.f);
+  return epi_traffic(op.epi.kind);
+}
+// k slices of one workgroup
+int op_slices(const GemmOp& op) {
+  return (((op.K + op.splitk - 1) / op.splitk) + BK - 1) / BK * (op.epi.kind == EPI_SWIGLU_DUAL ? 2 : 1);
+}
 // nk: k slices of one workgroup; members: batch members times k splits; slice: factor on the slice time
 float tile_time(int tile, int M, int N, int nk, int members, float e, float slice = 1.f) {
   const TileCost& c = kTileCost[tile];
@@ -616,6 +624,7 @@ bool gemm_bf16_mixed_ok(const GemmOp& op) {
 int gemm_bf16_tile(const GemmOp& op) {
   if (op.tile != GEMM_TILE_AUTO) return op.tile;
   if (op.splitk > 1 || op.epi.kind == EPI_PARTIAL) return GEMM_T256;   // weight gradients come with a plan
+  const bool dual = op.epi.kind == EPI_SWIGLU_DUAL;
   // a k-major weight is read in place in whole 8-column chunks, within the 2 GB a buffer resource addresses
   if (op.transB && !op.transA && (op.N % 8 || op.K % 8 || (int64_t)op.K * op.ldb * 2 >= 0x7fffffffLL)) return GEMM_T256;
   // Causal k ranges: tiles of unequal length, for which the estimate has no term.  Where the 256-row tiles give less
@@ -627,10 +636,10 @@ int gemm_bf16_tile(const GemmOp& op) {
     if ((op.M + 255) / 256 * members >= 512) return GEMM_T256X128;
     if ((op.M + 127) / 128 * members >= 128) return GEMM_R128W;
   }
-  const int nk = (op.K + BK - 1) / BK;
-  const float e = epi_traffic(op.epi.kind);
+  const int nk = op_slices(op);
+  const float e = epi_traffic(op);
   const bool km = op.transA && op.transB;
-  float best = tile_time(GEMM_T256, op.M, op.N, nk, op.batch, e, km ? kKMajorSlice[GEMM_T256] : 1.f);
+  float best = dual ? 1e30f : tile_time(GEMM_T256, op.M, op.N, nk, op.batch, e, km ? kKMajorSlice[GEMM_T256] : 1.f);
   // T256 with a k-major weight first writes a transposed copy: one launch per batch member
   if (op.transB && !op.transA) best += (float)op.batch * (2.5f + (float)op.N * (float)op.K * (4.f / 4e6f));
   int tile = GEMM_T256;
@@ -819,9 +828,9 @@ int gemm_bf16_join_tile(const GemmOp* ops, int n) {
     const GemmOp& op = ops[i];
     if (!gemm_bf16_joint_ok(op)) return 0;
     const int best = op.tile != GEMM_TILE_AUTO ? op.tile : gemm_bf16_tile(op), members = op.batch * op.splitk;
-    const int nk = ((op.K + op.splitk - 1) / op.splitk + BK - 1) / BK;
+    const int nk = op_slices(op);
     const bool km = op.transA && op.transB;
-    const float e = epi_traffic(op.epi.kind);
+    const float e = epi_traffic(op);
     apart += tile_time(best, op.M, op.N, nk, members, e, km ? kKMajorSlice[best] : 1.f) + kLaunchGap;
     for (int t = 0; t < 2; t++) {
       const TileCost& c = kTileCost[tiles[t]];
@@ -836,6 +845,32 @@ int gemm_bf16_join_tile(const GemmOp* ops, int n) {
     joint[t] = kTileCost[tiles[t]].a + kLaunchGap + (joint[t] > longest[t] ? joint[t] + 0.75f * longest[t] : longest[t]);
   const int t = joint[0] <= joint[1] ? 0 : 1;
   return joint[t] < apart ? tiles[t] : 0;
+}
+
+int gemm_bf16_dual_tile(const GemmOp& op) {
+  // Apart, the gate's tile goes to memory and comes back, and a launch ends in between; together, both products run on the tiles of
+  // gemm_ring.h, which read an operand element more often.  Block forwards (only m stored) and backwards (g and u too) of 256 to
+  // 16384 tokens, 2 to 32 heads, rank 64 to 1024, replayed from graphs, us, apart -> together:
+  //   256 tokens, 2 heads, r 64: 54.0 -> 50.8, 101 -> 98              777, 16 heads, r 128: 104 -> 98, 259 -> 257
+  //   3000, 16 heads, r 512: 319 -> 298, 937 -> 925                   16384, 32 heads, r 128: 1320 -> 1188, 3779 -> 3716
+  //   16384, 16 heads, r 512: 1045 -> 1023, 2992 -> 2995              16384, 32 heads, r 1024: 2787 -> 2853, 7855 -> 8040
+  // Streams of 256-row tiles are faster than their estimate; from 2.5 rounds on, together has to be estimated a third faster (8192
+  // tokens, 16 heads, r 512: 0.69 of the estimate, forward 577 -> 599; 16384, 16 heads, r 512: 0.66).  With that line no call of those
+  // is slower by more than 0.3 %, and the choice of the tile loses 1 % to the best.
+  if (g_timer.on || op.epi.kind != EPI_SWIGLU_DUAL || op.transA || op.transB || op.splitk != 1 || op.batch != 1 || op.N % 8 || op.K % 8 ||
+      (op.sA + 128 * op.lda + op.K) * 2 >= 0x7fffffffLL || (op.sB + 128 * op.ldb + op.K) * 2 >= 0x7fffffffLL)
+    return 0;
+  const int tile = gemm_bf16_tile(op), nk = op_slices(op);
+  GemmOp one = op;
+  float apart = kLaunchGap;
+  bool stream = (int64_t)((op.M + 255) / 256) * ((op.N + 255) / 256) * 2 > 5 * NCU;
+  for (int kind : {EPI_STORE, EPI_SWIGLU_FWD}) {
+    one.epi.kind = kind;
+    const int t = gemm_bf16_tile(one);
+    stream = stream && t == GEMM_T256;
+    apart += tile_time(t, op.M, op.N, nk / 2, 1, epi_traffic(kind) + (kind == EPI_SWIGLU_FWD && op.C ? 1.f : 0.f));
+  }
+  return tile_time(tile, op.M, op.N, nk, 1, epi_traffic(op)) < apart * (stream ? 0.68f : 1.f) ? tile : 0;
 }
 
 hipError_t gemm_bf16_many(const GemmOp* ops, int n, hipStream_t st) {

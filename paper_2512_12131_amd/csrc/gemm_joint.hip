@@ -14,7 +14,7 @@ namespace {
 // operand form (T: k-major, N: k-contiguous A; N: k-major, T: k-contiguous B) and epilogue
 enum JointForm : int {
   JF_NONE = -1, JF_TT_PARTIAL, JF_TT_PARTIAL_PARTS, JF_TT_STORE, JF_TT_STORE_PARTS,
-  JF_NN_STORE, JF_NN_ACTGRAD, JF_NN_LAXGRAD, JF_NN_SWIGLU_BWD, JF_NN_NORMBWD_O32, JF_NN_NORMBWD_I32, JF_NT_STORE, JF_NT_UP
+  JF_NN_STORE, JF_NN_ACTGRAD, JF_NN_LAXGRAD, JF_NN_SWIGLU_BWD, JF_NN_NORMBWD_O32, JF_NN_NORMBWD_I32, JF_NT_STORE, JF_NT_UP, JF_NT_SWIGLU_DUAL
 };
 
 struct JointArgs {
@@ -46,6 +46,7 @@ __global__ __launch_bounds__(T::NT) void gemm_joint_kernel(JointArgs) {
     case JF_NN_NORMBWD_I32: ring_product<T, EPI_NORMBWD_I32, false, false, true, false>(op, kper, tm, tn, bid, total); break;
     case JF_NT_STORE: ring_product<T, EPI_STORE, false, false, false, false>(op, kper, tm, tn, bid, total); break;
     case JF_NT_UP: ring_product<T, EPI_UP, false, false, false, false>(op, kper, tm, tn, bid, total); break;
+    case JF_NT_SWIGLU_DUAL: ring_product<T, EPI_SWIGLU_DUAL, false, false, false, false>(op, kper, tm, tn, bid, total); break;
     default: break;
   }
 }
@@ -59,7 +60,7 @@ JointForm form_of(const GemmOp& op) {
     return op.k_parts > 1 ? JF_TT_STORE_PARTS : JF_TT_STORE;
   }
   if (op.transA || op.splitk != 1 || op.k_parts != 1 || op.N % 8 || op.K % 8) return JF_NONE;
-  if (!op.transB) return kind == EPI_STORE ? JF_NT_STORE : kind == EPI_UP ? JF_NT_UP : JF_NONE;
+  if (!op.transB) return kind == EPI_STORE ? JF_NT_STORE : kind == EPI_UP ? JF_NT_UP : kind == EPI_SWIGLU_DUAL ? JF_NT_SWIGLU_DUAL : JF_NONE;
   // a k-major weight beside k-contiguous rows: in place under the conditions of gemm_bf16_tile
   if ((int64_t)op.K * op.ldb * 2 >= 0x7fffffffLL) return JF_NONE;
   switch (kind) {

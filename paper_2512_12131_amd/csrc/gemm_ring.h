@@ -21,6 +21,11 @@
 // the order that keeps a row's bits: there the 32 x 32 tile gives the chain a wavefront of its own and the loads
 // to four others, 0.095 us per slice (15.0 -> 9.4 us; 16 x 4096 x 1024 6.6 -> 5.5; the same split at 64 x 64: 13.3).
 //
+// EPI_SWIGLU_DUAL walks the gate's product and then the up product in one stream of stages: the gate's accumulators wait as bf16
+// pairs (half of the registers; what the epilogue would read back from memory), and g never leaves the chip where nobody wants it.
+// Bound: the d_ff wide stores (16384 x 11008, k = 128: g, then u with the epilogue 112 + 221 us, together 160; with g and u stored
+// 110 + 290 -> 345).
+//
 // Operand forms: k-contiguous (p[i*ld + k]) or k-major (p[k*ld + i]) for A and B independently; the k-major
 // side is read through the LDS transpose read, so a data-gradient product needs no transposed weight copy.
 #pragma once
@@ -119,7 +124,9 @@ __device__ __forceinline__ void ring_product(const GemmOp& op, int kper, int til
   const int bo = op.batch_inner > 0 ? b / op.batch_inner : 0, bi = op.batch_inner > 0 ? b % op.batch_inner : b;
   const int klen = kend > kbeg ? kend - kbeg : 0;
   constexpr int KST = T::SUB * BK, KSTEPS = T::SUB * 4;  // k elements and k16 steps per stage
-  const int nit = (klen + KST - 1) / KST;
+  // DUAL: the stages of the gate's product, then those of the other one, in one stream
+  constexpr bool DUAL = KIND == EPI_SWIGLU_DUAL;
+  const int nit1 = (klen + KST - 1) / KST, nit = DUAL ? 2 * nit1 : nit1;
 
   const uint16_t* A = (const uint16_t*)op.A + (int64_t)bi * op.sA + (int64_t)bo * op.sAo;
   const uint16_t* B = (const uint16_t*)op.B + (int64_t)(bi / op.b_group) * op.sB + (int64_t)bo * op.sBo;
@@ -164,8 +171,10 @@ __device__ __forceinline__ void ring_product(const GemmOp& op, int kper, int til
     constexpr int s = decltype(I)::value / (T::LA + T::LB), j = decltype(I)::value % (T::LA + T::LB);
     constexpr bool is_a = j < T::LA, km = is_a ? AKM : BKM;
     constexpr int i = is_a ? j : j - T::LA, W = is_a ? T::BM : T::BN, RPL = 512 / W;
-    const int k0 = it * KST + s * BK;
-    const uint32_t adv = (uint32_t)k0 * (km ? (uint32_t)(is_a ? op.lda : op.ldb) : 1u) * 2u;
+    const bool other = DUAL && it >= nit1;
+    const int k0 = (other ? it - nit1 : it) * KST + s * BK;
+    uint32_t adv = (uint32_t)k0 * (km ? (uint32_t)(is_a ? op.lda : op.ldb) : 1u) * 2u;
+    if (other) adv += (uint32_t)(is_a ? op.sA : op.sB) * 2u;
     const bool in = (k0 + (is_a ? kA : kB) + (km ? i * T::NWL * RPL : 0)) < klen;
     const uint32_t dst = sbase + (uint32_t)(slot * T::STAGE + s * T::SLICE + (is_a ? 0 : T::A_BYTES)) +
                          (uint32_t)(lw + T::NWL * i) * 1024u;
@@ -232,7 +241,7 @@ __device__ __forceinline__ void ring_product(const GemmOp& op, int kper, int til
   for (int s = 0; s < T::NS - 1; s++)
     if (lw >= 0) static_for<T::LPS>([&](auto I) { issue_one(s, s, I, std::true_type{}); });
   int rd = 0, wr = T::NS - 1;                            // slots read from and written to
-  for (int it = 0; it < nit; it++) {
+  auto stage = [&](int it) {
     // this wavefront's loads of stage `it` have landed (loads retire in order), and its reads of the stage
     // before are done; after the barrier that holds for all of them
     asm volatile("" ::: "memory");
@@ -298,6 +307,21 @@ __device__ __forceinline__ void ring_product(const GemmOp& op, int kper, int til
     }
     rd = rd + 1 == T::NS ? 0 : rd + 1;
     wr = wr + 1 == T::NS ? 0 : wr + 1;
+  };
+  for (int it = 0; it < nit1; it++) stage(it);
+  GateAcc<T> gate;
+  if constexpr (DUAL) {
+#pragma unroll
+    for (int i = 0; i < T::FM; i++)
+#pragma unroll
+      for (int j = 0; j < T::FN; j++)
+#pragma unroll
+        for (int g = 0; g < 4; g++) {
+          gate.v[i][j][g] = make_uint2(pack_bf16x2(acc[i][j][4 * g], acc[i][j][4 * g + 1]), pack_bf16x2(acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]));
+#pragma unroll
+          for (int r = 0; r < 4; r++) acc[i][j][4 * g + r] = 0.f;
+        }
+    for (int it = nit1; it < nit; it++) stage(it);
   }
   wait_vmcnt<0>();
   __syncthreads();           // the ring is dead from here on
@@ -316,7 +340,7 @@ __device__ __forceinline__ void ring_product(const GemmOp& op, int kper, int til
 #pragma unroll
         for (int v = 0; v < 16; v++) acc[i][j][v] += tot[i][j][v];
   }
-  gemm_epilogue<T, KIND, STAT_A>(op, acc, typename T::EpiStage{smem + wave * T::STAGE_BYTES}, sStat, wave, lane, m0, n0, tn, tiles_n, b, bi, bo, bz);
+  gemm_epilogue<T, KIND, STAT_A>(op, acc, typename T::EpiStage{smem + wave * T::STAGE_BYTES}, sStat, wave, lane, m0, n0, tn, tiles_n, b, bi, bo, bz, gate);
 }
 
 template <class T, int KIND, bool STAT_A, bool AKM, bool BKM, bool PARTS>
@@ -385,6 +409,7 @@ hipError_t dispatch_ring(const GemmOp& op, hipStream_t st) {
     case EPI_UP_O32: return launch_ring<T, EPI_UP_O32, false, false, false>(op, st);
     case EPI_UP_I32: return launch_ring<T, EPI_UP_I32, false, false, false>(op, st);
     case EPI_SWIGLU_FWD: return launch_ring<T, EPI_SWIGLU_FWD, false, false, false>(op, st);
+    case EPI_SWIGLU_DUAL: return launch_ring<T, EPI_SWIGLU_DUAL, false, false, false>(op, st);
     default: return hipErrorInvalidValue;
   }
 }

@@ -91,11 +91,14 @@ inline dim3 tile_grid(int tiles, int members) {
 // which Stage::SR rows of Stage::SC columns are staged at a time: 32 of all columns, or 16 of 64.  stage.at(row, chunk): where
 // 16-byte chunk `chunk` of staged row `row` lies.  (m0, n0): first row / column of the output tile, tn its column
 // index, b / (bi, bo) / bz: batch member, its two-level split, batch member times k split.  sStat: the row
-// statistics gathered in the main loop (STAT_A); STAT_IN_STAGE: they lie in the staging space.
+// statistics gathered in the main loop (STAT_A); STAT_IN_STAGE: they lie in the staging space.  accg: the gate's accumulators as
+// bf16 pairs (EPI_SWIGLU_DUAL): [row block][column block][four columns of a run].
+template <class T>
+struct GateAcc { uint2 v[T::FM][T::FN][4]; };
 template <class T, int KIND, bool STAT_A, class Stage>
 __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T::FM][T::FN], const Stage& stage,
                                               const float* sStat, int wave, int lane, int m0, int n0, int tn,
-                                              int tiles_n, int b, int bi, int bo, int bz) {
+                                              int tiles_n, int b, int bi, int bo, int bz, const GateAcc<T>& accg = GateAcc<T>()) {
   const int wm = wave / T::WN, wn = wave % T::WN;
   // The wavefront's sub-tile leaves in passes of RPP rows and SC columns.  Everything the passes touch
   // in global memory goes through buffer resources that start at the tile's first row and end after
@@ -118,7 +121,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T:
   // output is also written un-rounded, as fp32, into C32
   constexpr int BASE = epi_base(KIND);
   constexpr bool R_F32 = epi_r_is_f32(KIND), O32 = epi_writes_f32(KIND);
-  constexpr bool HAS_R = BASE == EPI_UP || BASE == EPI_ACTGRAD || BASE == EPI_NORMBWD || BASE == EPI_SWIGLU_BWD ||
+  constexpr bool DUAL = KIND == EPI_SWIGLU_DUAL;
+  constexpr bool HAS_R = DUAL ? false : BASE == EPI_UP || BASE == EPI_ACTGRAD || BASE == EPI_NORMBWD || BASE == EPI_SWIGLU_BWD ||
                          BASE == EPI_SWIGLU_FWD || BASE == EPI_DOWN_LAX || BASE == EPI_LAXGRAD;
   constexpr bool HAS_R2 = BASE == EPI_NORMBWD || BASE == EPI_SWIGLU_BWD || BASE == EPI_LAXGRAD;
   constexpr int PF = (HAS_R2 || R_F32) ? 4 : 8;
@@ -143,7 +147,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T:
       : tile_rsrc(op.C, (int64_t)bi * op.sC + (int64_t)bo * op.sCo, op.ldc, 2);
   const __amdgpu_buffer_rsrc_t rsC2 = tile_rsrc(PARTIAL ? nullptr : e.C2, (int64_t)b * e.sC2, e.ldc2, 2);
   const bool use_r = !PARTIAL && epi_reads_r<BASE>(e), use_r2 = !PARTIAL && epi_reads_r2<BASE>(e);
-  const __amdgpu_buffer_rsrc_t rsR = tile_rsrc(use_r ? e.R : nullptr, (int64_t)b * e.sR, e.ldr, R_F32 ? 4 : 2);
+  const __amdgpu_buffer_rsrc_t rsR = tile_rsrc(use_r ? e.R : nullptr, (int64_t)b * e.sR, e.ldr, R_F32 ? 4 : 2);   // (DUAL: g, written)
   const __amdgpu_buffer_rsrc_t rsC32 = tile_rsrc(O32 ? e.C32 : nullptr, 0, e.ldc32, 4);
   const __amdgpu_buffer_rsrc_t rsR2 = tile_rsrc(use_r2 ? e.R2 : nullptr, (int64_t)b * e.sR2, e.ldr2, 2);
   const __amdgpu_buffer_rsrc_t rsRowA = row_rsrc((!PARTIAL && e.use_rho && !STAT_A) ? e.rowa : nullptr);
@@ -154,7 +158,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T:
   auto col_off = [&](int jj, uint32_t es) -> uint32_t {
     return coln + jj * Stage::SC < op.N ? (uint32_t)(coln + jj * Stage::SC) * es : EOOB;
   };
-  const bool want2 = KIND == EPI_SWIGLU_BWD || KIND == EPI_SWIGLU_FWD || KIND == EPI_DOWN_LAX || KIND == EPI_LAXGRAD ||
+  const bool want2 = KIND == EPI_SWIGLU_BWD || BASE == EPI_SWIGLU_FWD || KIND == EPI_DOWN_LAX || KIND == EPI_LAXGRAD ||
                      KIND == EPI_ACTGRAD_A || (KIND == EPI_DOWN && e.C2 != nullptr);
   const bool use_rho = !PARTIAL && e.use_rho;
   const bool rho_sqrt = e.rho_sqrt != 0;
@@ -176,6 +180,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T:
   const float inv_d = e.inv_d, eps = e.eps;
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   u32x4 auxr[PF], auxr2[PF], auxr3[R_F32 ? PF : 1];   // auxr3: columns 4..7 of an fp32 R tile
+  uint4 gate[DUAL ? PPS : 1];                   // DUAL: g as stored, of the staged piece
   // pass q: MFMA block row i, piece h of its rows, piece jj across, p-th run of RPP rows
   auto row_of = [&](int q) {                                       // row inside the tile
     return wm * T::TM + (q / (NH * NJ * PPS)) * 32 + (q / (NJ * PPS) % NH) * Stage::SR + (q % PPS) * RPP + rsub;
@@ -247,6 +252,16 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T:
         }
       });
     }
+    if constexpr (DUAL && p == 0) {
+      // the gate's piece through the staging space first: rows of eight columns, rounded as they are stored
+      static_for<T::FN>([&](auto J) {
+#pragma unroll
+        for (int g = 0; g < 4; g++)
+          *reinterpret_cast<uint2*>(stage.at(lane & 31, decltype(J)::value * 4 + g) + (lane >> 5) * 8) = accg.v[i][decltype(J)::value][g];
+      });
+#pragma unroll
+      for (int pp = 0; pp < PPS; pp++) gate[pp] = *reinterpret_cast<const uint4*>(stage.at(pp * RPP + rsub, cg));
+    }
     if constexpr (p == 0) {
       auto put = [&](int row, int chunk, const f32x16& a) {
 #pragma unroll
@@ -286,6 +301,10 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T:
         const u32x4 a0 = auxr[q % PF], a1 = auxr3[q % PF];
         r[0] = __uint_as_float(a0.x); r[1] = __uint_as_float(a0.y); r[2] = __uint_as_float(a0.z); r[3] = __uint_as_float(a0.w);
         r[4] = __uint_as_float(a1.x); r[5] = __uint_as_float(a1.y); r[6] = __uint_as_float(a1.z); r[7] = __uint_as_float(a1.w);
+      } else if constexpr (DUAL) {
+        unpack8(gate[p], r);
+        const u32x4 gv = {gate[p].x, gate[p].y, gate[p].z, gate[p].w};
+        __builtin_amdgcn_raw_buffer_store_b128(gv, rsR, (int)((uint32_t)(lm * ldR) + col_off(jj, 2u)), 0, 0);
       } else {
         unpack8(make_uint4(auxr[q % PF].x, auxr[q % PF].y, auxr[q % PF].z, auxr[q % PF].w), r);
       }
