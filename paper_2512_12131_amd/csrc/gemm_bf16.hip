@@ -854,23 +854,25 @@ int gemm_bf16_dual_tile(const GemmOp& op) {
   //   256 tokens, 2 heads, r 64: 54.0 -> 50.8, 101 -> 98              777, 16 heads, r 128: 104 -> 98, 259 -> 257
   //   3000, 16 heads, r 512: 319 -> 298, 937 -> 925                   16384, 32 heads, r 128: 1320 -> 1188, 3779 -> 3716
   //   16384, 16 heads, r 512: 1045 -> 1023, 2992 -> 2995              16384, 32 heads, r 1024: 2787 -> 2853, 7855 -> 8040
-  // Streams of 256-row tiles are faster than their estimate; from 2.5 rounds on, together has to be estimated a third faster (8192
-  // tokens, 16 heads, r 512: 0.69 of the estimate, forward 577 -> 599; 16384, 16 heads, r 512: 0.66).  With that line no call of those
-  // is slower by more than 0.3 %, and the choice of the tile loses 1 % to the best.
+  // 256-row tiles read less, which shows when the weights come from memory: where they run both products, together has to be estimated a
+  // quarter faster (777 tokens, 32 heads, r 1024: 0.78 of the estimate, warm 285 / 285, weights cold 298 -> 303; 5000, 16 heads, r 512:
+  // 0.69, 409 -> 395).  As streams of 2.5 rounds and more they are also faster than their estimate: a third (8192, 16 heads, r 512:
+  // 0.69, forward 577 -> 599; 16384, 16 heads, r 512: 0.66).
   if (g_timer.on || op.epi.kind != EPI_SWIGLU_DUAL || op.transA || op.transB || op.splitk != 1 || op.batch != 1 || op.N % 8 || op.K % 8 ||
       (op.sA + 128 * op.lda + op.K) * 2 >= 0x7fffffffLL || (op.sB + 128 * op.ldb + op.K) * 2 >= 0x7fffffffLL)
     return 0;
   const int tile = gemm_bf16_tile(op), nk = op_slices(op);
   GemmOp one = op;
   float apart = kLaunchGap;
-  bool stream = (int64_t)((op.M + 255) / 256) * ((op.N + 255) / 256) * 2 > 5 * NCU;
+  bool t256 = true;
   for (int kind : {EPI_STORE, EPI_SWIGLU_FWD}) {
     one.epi.kind = kind;
     const int t = gemm_bf16_tile(one);
-    stream = stream && t == GEMM_T256;
+    t256 = t256 && t == GEMM_T256;
     apart += tile_time(t, op.M, op.N, nk / 2, 1, epi_traffic(kind) + (kind == EPI_SWIGLU_FWD && op.C ? 1.f : 0.f));
   }
-  return tile_time(tile, op.M, op.N, nk, 1, epi_traffic(op)) < apart * (stream ? 0.68f : 1.f) ? tile : 0;
+  const bool rounds = (int64_t)((op.M + 255) / 256) * ((op.N + 255) / 256) * 2 > 5 * NCU;
+  return tile_time(tile, op.M, op.N, nk, 1, epi_traffic(op)) < apart * (!t256 ? 1.f : rounds ? 0.68f : 0.75f) ? tile : 0;
 }
 
 hipError_t gemm_bf16_many(const GemmOp* ops, int n, hipStream_t st) {

@@ -104,6 +104,69 @@ __device__ __forceinline__ int kmajor_swz(int k) {
   return W >= 128 ? (k & 3) << 2 : W == 64 ? ((k >> 1) & 1) << 2 : 0;
 }
 
+constexpr uint32_t RING_OOB = 0x80000000u;               // beyond every resource: the load delivers zeros
+
+// A wavefront's loads of one slice of an operand: group g = lw + NWL * i covers 8 rows x 128 B
+// (k-contiguous; chunk index XORed by (row / 2) % 8) or 512 / W k rows x 2 W bytes (k-major).
+// i0, lim: first row (k-contiguous) or column (k-major) of the tile, and where the matrix ends.
+template <class T, bool KM, int W, int NI>
+__device__ __forceinline__ void lane_offsets(uint32_t (&off)[NI], int& k_of_lane, int64_t ld, int i0, int lim, int lw, int lane) {
+  static_assert(NI == W / 8 / T::NWL, "loads of a wavefront");
+#pragma unroll
+  for (int i = 0; i < NI; i++) {
+    const int g = lw + T::NWL * i;
+    if constexpr (!KM) {
+      const int row = g * 8 + (lane >> 3);
+      const int lc = (lane & 7) ^ ((row >> 1) & 7);
+      if (i == 0) k_of_lane = lc * 8;                  // the same for every i: NWL * 8 rows apart, NWL even
+      off[i] = (i0 + row) < lim ? (uint32_t)(row * (int)ld + lc * 8) * 2u : RING_OOB;
+    } else {
+      constexpr int CPR = W / 8, RPL = 64 / CPR;
+      const int krow = g * RPL + lane / CPR;
+      const int lc = (lane % CPR) ^ kmajor_swz<W>(krow);
+      if (i == 0) k_of_lane = krow;                    // load i: NWL * RPL rows further
+      off[i] = (i0 + lc * 8) < lim ? (uint32_t)(krow * (int)ld + lc * 8) * 2u : RING_OOB;
+    }
+  }
+}
+
+// MFMA operands: 32 rows (lane % 32) x 8 consecutive k (k16 step kk, half lane / 32) from either layout.  BOTH: both operands are k-major.
+template <bool KM, int W, bool BOTH>
+__device__ __forceinline__ bf16x8 ring_frag(const unsigned char* base, int r0, int kk, int lane) {
+  const int frow = lane & 31, fhalf = lane >> 5, fsw = (frow >> 1) & 7;
+  if constexpr (!KM) {
+    return *reinterpret_cast<const bf16x8*>(base + (r0 + frow) * 128 + (((kk * 2 + fhalf) ^ fsw) << 4));
+  } else {
+    // Inside 16 lanes, lane s supplies the address of 4 columns of k row s / 4 and receives column s.  Beside a
+    // k-contiguous operand the lane's slots are its half's 8 consecutive k.  With two k-major operands they are
+    // the two runs of four of the 256-row kernel's k-major form (k = (e / 4) * 8 + half * 4 + e % 4): the order of
+    // the sum, and so the bits of the attention's query gradient, must not depend on which of the two runs.
+    const int g = lane >> 4, s = lane & 15;
+    const int krow = fhalf * (BOTH ? 4 : 8) + (s >> 2);
+    const int col = r0 + (g & 1) * 16 + (s & 3) * 4;
+    const unsigned char* p = base + (kk * 16 + krow) * (2 * W) + (((col >> 3) ^ kmajor_swz<W>(krow)) << 4) + (col & 7) * 2;
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p + (BOTH ? 8 : 4) * 2 * W));
+    const s16x8 r = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(bf16x8, r);
+  }
+}
+
+// The gate's accumulators put away, and cleared for the other product.
+template <class T>
+__device__ __forceinline__ void gate_from(GateAcc<T>& gate, f32x16 (&acc)[T::FM][T::FN]) {
+#pragma unroll
+  for (int i = 0; i < T::FM; i++)
+#pragma unroll
+    for (int j = 0; j < T::FN; j++)
+#pragma unroll
+      for (int g = 0; g < 4; g++) {
+        gate.v[i][j][g] = make_uint2(pack_bf16x2(acc[i][j][4 * g], acc[i][j][4 * g + 1]), pack_bf16x2(acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]));
+#pragma unroll
+        for (int r = 0; r < 4; r++) acc[i][j][4 * g + r] = 0.f;
+      }
+}
+
 // PARTS: k runs in op.k_parts parts that are summed one by one, as split-K partials are.
 // bid: this workgroup among the `total` of the product.
 template <class T, int KIND, bool STAT_A, bool AKM, bool BKM, bool PARTS>
@@ -130,39 +193,15 @@ __device__ __forceinline__ void ring_product(const GemmOp& op, int kper, int til
 
   const uint16_t* A = (const uint16_t*)op.A + (int64_t)bi * op.sA + (int64_t)bo * op.sAo;
   const uint16_t* B = (const uint16_t*)op.B + (int64_t)(bi / op.b_group) * op.sB + (int64_t)bo * op.sBo;
-  constexpr uint32_t OOB = 0x80000000u;                  // beyond every resource: the load delivers zeros
+  constexpr uint32_t OOB = RING_OOB;
   const rsrc_words rsA = operand_rsrc(AKM ? A + (int64_t)kbeg * op.lda + m0 : A + (int64_t)m0 * op.lda + kbeg);
   const rsrc_words rsB = operand_rsrc(BKM ? B + (int64_t)kbeg * op.ldb + n0 : B + (int64_t)n0 * op.ldb + kbeg);
   const uint32_t sbase = (uint32_t)(uintptr_t)LRB_LDS_PTR(smem);
 
-  // A wavefront's loads of one slice of an operand: group g = lw + NWL * i covers 8 rows x 128 B
-  // (k-contiguous; chunk index XORed by (row / 2) % 8) or 512 / W k rows x 2 W bytes (k-major).
   uint32_t offA[T::LA], offB[T::LB];
   int kA = 0, kB = 0;        // this lane's first k inside the slice: of its chunk (k-contiguous) or its row (k-major)
-  auto lane_offsets = [&](auto KM, auto Wc, auto& off, int& k_of_lane, int64_t ld, int i0, int lim) {
-    constexpr bool km = decltype(KM)::value;
-    constexpr int W = decltype(Wc)::value, NI = W / 8 / T::NWL;
-#pragma unroll
-    for (int i = 0; i < NI; i++) {
-      const int g = lw + T::NWL * i;
-      if constexpr (!km) {
-        const int row = g * 8 + (lane >> 3);
-        const int lc = (lane & 7) ^ ((row >> 1) & 7);
-        if (i == 0) k_of_lane = lc * 8;                  // the same for every i: NWL * 8 rows apart, NWL even
-        off[i] = (i0 + row) < lim ? (uint32_t)(row * (int)ld + lc * 8) * 2u : OOB;
-      } else {
-        constexpr int CPR = W / 8, RPL = 64 / CPR;
-        const int krow = g * RPL + lane / CPR;
-        const int lc = (lane % CPR) ^ kmajor_swz<W>(krow);
-        if (i == 0) k_of_lane = krow;                    // load i: NWL * RPL rows further
-        off[i] = (i0 + lc * 8) < lim ? (uint32_t)(krow * (int)ld + lc * 8) * 2u : OOB;
-      }
-    }
-  };
-  using WA = std::integral_constant<int, T::BM>;
-  using WB = std::integral_constant<int, T::BN>;
-  lane_offsets(std::integral_constant<bool, AKM>{}, WA{}, offA, kA, op.lda, m0, op.M);
-  lane_offsets(std::integral_constant<bool, BKM>{}, WB{}, offB, kB, op.ldb, n0, op.N);
+  lane_offsets<T, AKM, T::BM>(offA, kA, op.lda, m0, op.M, lw, lane);
+  lane_offsets<T, BKM, T::BN>(offB, kB, op.ldb, n0, op.N, lw, lane);
 
   // Load I (compile-time, 0 .. LPS - 1) of stage `it` into ring slot `slot`.  k past the end of the range (also
   // whole stages past it) reads as zeros, so the loop needs no tail code and the counts of loads in flight are
@@ -179,30 +218,6 @@ __device__ __forceinline__ void ring_product(const GemmOp& op, int kper, int til
     const uint32_t dst = sbase + (uint32_t)(slot * T::STAGE + s * T::SLICE + (is_a ? 0 : T::A_BYTES)) +
                          (uint32_t)(lw + T::NWL * i) * 1024u;
     dma16<decltype(FIRST)::value>(is_a ? rsA : rsB, dst, in ? (is_a ? offA[is_a ? i : 0] : offB[is_a ? 0 : i]) + adv : OOB);   // OOB + adv stays past the resource
-  };
-
-  // MFMA operands: 32 rows (lane % 32) x 8 consecutive k (k16 step kk, half lane / 32) from either layout
-  const int frow = lane & 31, fhalf = lane >> 5, fsw = (frow >> 1) & 7;
-  auto frag = [&](auto KM, auto Wc, const unsigned char* base, int r0, int kk) -> bf16x8 {
-    constexpr bool km = decltype(KM)::value;
-    constexpr int W = decltype(Wc)::value;
-    if constexpr (!km) {
-      return *reinterpret_cast<const bf16x8*>(base + (r0 + frow) * 128 + (((kk * 2 + fhalf) ^ fsw) << 4));
-    } else {
-      // Inside 16 lanes, lane s supplies the address of 4 columns of k row s / 4 and receives column s.  Beside a
-      // k-contiguous operand the lane's slots are its half's 8 consecutive k.  With two k-major operands they are
-      // the two runs of four of the 256-row kernel's k-major form (k = (e / 4) * 8 + half * 4 + e % 4): the order of
-      // the sum, and so the bits of the attention's query gradient, must not depend on which of the two runs.
-      constexpr bool both = AKM && BKM;
-      const int g = lane >> 4, s = lane & 15;
-      const int krow = fhalf * (both ? 4 : 8) + (s >> 2);
-      const int col = r0 + (g & 1) * 16 + (s & 3) * 4;
-      const unsigned char* p = base + (kk * 16 + krow) * (2 * W) + (((col >> 3) ^ kmajor_swz<W>(krow)) << 4) + (col & 7) * 2;
-      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p));
-      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p + (both ? 8 : 4) * 2 * W));
-      const s16x8 r = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-      return __builtin_bit_cast(bf16x8, r);
-    }
   };
 
   f32x16 acc[T::FM][T::FN];
@@ -260,10 +275,10 @@ __device__ __forceinline__ void ring_product(const GemmOp& op, int kper, int til
       for (int kk = 0; kk < KSTEPS; kk++) {
         const unsigned char* sa = smem + rd * T::STAGE + (kk / 4) * T::SLICE;
 #pragma unroll
-        for (int i = 0; i < T::FM; i++) af[kk][i] = frag(std::integral_constant<bool, AKM>{}, WA{}, sa, wm * T::TM + i * 32, kk % 4);
+        for (int i = 0; i < T::FM; i++) af[kk][i] = ring_frag<AKM, T::BM, AKM && BKM>(sa, wm * T::TM + i * 32, kk % 4, lane);
 #pragma unroll
         for (int j = 0; j < T::FN; j++)
-          bf[kk][j] = frag(std::integral_constant<bool, BKM>{}, WB{}, sa + T::A_BYTES, wn * T::TN + j * 32, kk % 4);
+          bf[kk][j] = ring_frag<BKM, T::BN, AKM && BKM>(sa + T::A_BYTES, wn * T::TN + j * 32, kk % 4, lane);
       }
       asm volatile("" ::: "memory");
       static_for<KSTEPS>([&](auto KK) {
@@ -311,16 +326,7 @@ __device__ __forceinline__ void ring_product(const GemmOp& op, int kper, int til
   for (int it = 0; it < nit1; it++) stage(it);
   GateAcc<T> gate;
   if constexpr (DUAL) {
-#pragma unroll
-    for (int i = 0; i < T::FM; i++)
-#pragma unroll
-      for (int j = 0; j < T::FN; j++)
-#pragma unroll
-        for (int g = 0; g < 4; g++) {
-          gate.v[i][j][g] = make_uint2(pack_bf16x2(acc[i][j][4 * g], acc[i][j][4 * g + 1]), pack_bf16x2(acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]));
-#pragma unroll
-          for (int r = 0; r < 4; r++) acc[i][j][4 * g + r] = 0.f;
-        }
+    gate_from(gate, acc);
     for (int it = nit1; it < nit; it++) stage(it);
   }
   wait_vmcnt<0>();

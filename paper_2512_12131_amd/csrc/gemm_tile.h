@@ -254,11 +254,21 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp& op, f32x16 (&acc)[T:
     }
     if constexpr (DUAL && p == 0) {
       // the gate's piece through the staging space first: rows of eight columns, rounded as they are stored
-      static_for<T::FN>([&](auto J) {
+      if constexpr (Stage::SR == 32) {
+        static_for<T::FN>([&](auto J) {
 #pragma unroll
-        for (int g = 0; g < 4; g++)
-          *reinterpret_cast<uint2*>(stage.at(lane & 31, decltype(J)::value * 4 + g) + (lane >> 5) * 8) = accg.v[i][decltype(J)::value][g];
-      });
+          for (int g = 0; g < 4; g++)
+            *reinterpret_cast<uint2*>(stage.at(lane & 31, decltype(J)::value * 4 + g) + (lane >> 5) * 8) = accg.v[i][decltype(J)::value][g];
+        });
+      } else {
+#pragma unroll
+        for (int g = 0; g < 4; g++) {
+          // (as below: rows 0..15 of two neighbouring blocks, then their rows 16..31)
+          const uint2 l = accg.v[i][2 * jj][g], r = accg.v[i][2 * jj + 1][g];
+          const auto sx = __builtin_amdgcn_permlane16_swap(l.x, r.x, false, false), sy = __builtin_amdgcn_permlane16_swap(l.y, r.y, false, false);
+          *reinterpret_cast<uint2*>(stage.at(lane & 15, (lane >> 4 & 1) * 4 + g) + (lane >> 5) * 8) = make_uint2(sx[h], sy[h]);
+        }
+      }
 #pragma unroll
       for (int pp = 0; pp < PPS; pp++) gate[pp] = *reinterpret_cast<const uint4*>(stage.at(pp * RPP + rsub, cg));
     }
