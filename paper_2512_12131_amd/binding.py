@@ -1,4 +1,5 @@
-"""ctypes binding of liblrboost.so: argument marshalling only.
+"""Binding of liblrboost.so: argument marshalling only, by ctypes, and in native code (csrc/marshal.cpp) where calls are small and made
+often: the layer, group, attention and streaming entry points.
 
 Every function takes torch tensors that already live on the GPU, passes their device pointers,
 sizes and leading dimensions through the C ABI of include/lrboost.h and returns the output
@@ -9,6 +10,8 @@ library is missing or a call fails, an exception is raised.
 from __future__ import annotations
 
 import ctypes as C
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
@@ -20,6 +23,7 @@ LR_NORM_NONE, LR_NORM_TWO_PASS, LR_NORM_ONLINE, LR_NORM_SHARD_LOCAL, LR_NORM_ONL
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "liblrboost.so")
 _lib = None
+_marshal = None
 
 _vp, _i64, _int, _f32, _sz = C.c_void_p, C.c_int64, C.c_int, C.c_float, C.c_size_t
 
@@ -109,8 +113,8 @@ EXPORTS = tuple(_SIGS)
 
 
 def lib():
-    """Loads liblrboost.so on first use.  Raises if it has not been built."""
-    global _lib
+    """Loads liblrboost.so, and the native marshalling linked against it, on first use.  Raises if they have not been built."""
+    global _lib, _marshal
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise LrError(f"{LIB_PATH} is missing: run `python -c 'import __graft_entry__ as g; g.build()'` "
@@ -119,8 +123,22 @@ def lib():
         for name, (res, args) in _SIGS.items():
             fn = getattr(L, name)
             fn.restype, fn.argtypes = res, args
+        path = os.path.join(os.path.dirname(LIB_PATH), "_marshal.so")
+        if not os.path.exists(path):
+            raise LrError(f"{path} is missing: run `python -c 'import __graft_entry__ as g; g.build()'` (there is no fallback path)")
+        loader = importlib.machinery.ExtensionFileLoader("_marshal", path)
+        m = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_marshal", path, loader=loader))
+        loader.exec_module(m)
+        m.set_error(LrError)
+        _marshal = m
         _lib = L
     return _lib
+
+
+def _native():
+    if _lib is None:
+        lib()
+    return _marshal
 
 
 def _check(status: int, what: str):
@@ -136,9 +154,8 @@ def _dt(t: torch.Tensor) -> int:
     raise LrError(f"unsupported dtype {t.dtype}")
 
 
-# The small calls are bound by the host (a launch costs it 3.3 us), so the marshalling keeps to what it needs: plain integers
-# for pointers (the argument types make void* of them) and the current stream's handle without a Stream object around it
-# (3.2 -> 0.2 us a call; one layer of 16 tokens 13.8 -> 10.1 us of host time).
+# Plain integers for pointers (the argument types make void* of them) and the current stream's handle without a Stream object around
+# it (3.2 -> 0.2 us a call).
 def _p(t):
     return None if t is None else t.data_ptr()
 
@@ -163,27 +180,13 @@ def lr_linear_workspace_bytes(T, d_in, r, d_out, dt, backward):
 
 def lr_linear_fwd(x, w_down, w_up, act=LR_ACT_SILU):
     """Returns (z[T, r], y[T, d_out])."""
-    T, d_in = x.shape
-    r, d_out = w_down.shape[0], w_up.shape[0]
-    dt = _dt(x)
-    z = torch.empty((T, r), dtype=x.dtype, device=x.device)
-    y = torch.empty((T, d_out), dtype=x.dtype, device=x.device)
-    nb = lr_linear_workspace_bytes(T, d_in, r, d_out, dt, 0)
-    ws = _ws(nb, x.device)
-    _check(lib().lr_linear_fwd(_p(x), _rowmajor(x), _p(w_down), _p(w_up), _p(z), _p(y), d_out, T, d_in, r, d_out, act,
-                               dt, _p(ws), nb, _stream()), "lr_linear_fwd")
-    return z, y
+    return _native().linear_fwd(x, w_down, w_up, act)
 
 
 def lr_linear_fwd_static(x, w_down, w_up, z, y, act=LR_ACT_SILU):
     """The forward of one bottleneck layer through the entry point that allocates nothing: the caller
     passes the outputs z[T, r] and y[T, d_out]; the library's scratch is a device array of its own."""
-    T, d_in = x.shape
-    r, d_out = w_down.shape[0], w_up.shape[0]
-    assert z.shape == (T, r) and y.shape == (T, d_out) and z.is_contiguous() and y.is_contiguous()
-    _check(lib().lr_linear_fwd_static(_p(x), _rowmajor(x), _p(w_down), _p(w_up), _p(z), _p(y), d_out, T, d_in, r, d_out,
-                                      act, _dt(x), _stream()), "lr_linear_fwd_static")
-    return z, y
+    return _native().linear_fwd_static(x, w_down, w_up, z, y, act)
 
 
 def _tdt(dt):
@@ -192,19 +195,8 @@ def _tdt(dt):
 
 def lr_linear_bwd(x, w_down, w_up, z, dy, act=LR_ACT_SILU, grads=None, grad_dt=LR_F32):
     """Returns (dx, dw_down, dw_up).  With grads=(dw_down, dw_up) the weight grads are accumulated."""
-    T, d_in = x.shape
-    r, d_out = w_down.shape[0], w_up.shape[0]
-    dt = _dt(x)
-    dx = torch.empty((T, d_in), dtype=x.dtype, device=x.device)
-    acc = grads is not None
-    dwd, dwu = grads if acc else (torch.empty_like(w_down, dtype=_tdt(grad_dt)),
-                                  torch.empty_like(w_up, dtype=_tdt(grad_dt)))
-    nb = lr_linear_workspace_bytes(T, d_in, r, d_out, dt, 1)
-    ws = _ws(nb, x.device)
-    _check(lib().lr_linear_bwd(_p(x), _rowmajor(x), _p(w_down), _p(w_up), _p(z), _p(dy), _rowmajor(dy), _p(dx), d_in,
-                               _p(dwd), _p(dwu), T, d_in, r, d_out, act, dt, grad_dt, int(acc), _p(ws), nb, _stream()),
-           "lr_linear_bwd")
-    return dx, dwd, dwu
+    dwd, dwu = (None, None) if grads is None else grads
+    return _native().linear_bwd(x, w_down, w_up, z, dy, act, dwd, dwu, grad_dt)
 
 
 # ---- G projections sharing one input ---------------------------------------------------------
@@ -214,40 +206,14 @@ def lr_group_workspace_bytes(G, T, d_in, r, d_out, dt, backward):
 
 def lr_group_fwd(x, gamma, eps, norm, w_down_cat, w_up_stack, act=LR_ACT_SILU):
     """Returns (z_cat[T, G*r], stat[T] fp32, y_stack[G, T, d_out])."""
-    T, d_in = x.shape
-    G, d_out, r = w_up_stack.shape
-    dt = _dt(x)
-    z = torch.empty((T, G * r), dtype=x.dtype, device=x.device)
-    stat = torch.empty((T,), dtype=torch.float32, device=x.device)
-    y = torch.empty((G, T, d_out), dtype=x.dtype, device=x.device)
-    nb = lr_group_workspace_bytes(G, T, d_in, r, d_out, dt, 0)
-    ws = _ws(nb, x.device)
-    _check(lib().lr_group_fwd(_p(x), _rowmajor(x), _p(gamma), eps, norm, _p(w_down_cat), _p(w_up_stack), _p(z),
-                              _p(stat), _p(y), d_out, T * d_out, G, T, d_in, r, d_out, act, dt, _p(ws), nb, _stream()),
-           "lr_group_fwd")
-    return z, stat, y
+    return _native().group_fwd(x, gamma, eps, norm, w_down_cat, w_up_stack, act)
 
 
 def lr_group_bwd(x, gamma, eps, norm, w_down_cat, w_up_stack, z_cat, stat, dy_stack, act=LR_ACT_SILU, grads=None,
                  grad_dt=LR_F32):
     """Returns (dx, dgamma, dw_down_cat, dw_up_stack)."""
-    T, d_in = x.shape
-    G, d_out, r = w_up_stack.shape
-    dt = _dt(x)
-    dx = torch.empty((T, d_in), dtype=x.dtype, device=x.device)
-    acc = grads is not None
-    if acc:
-        dgamma, dwd, dwu = grads
-    else:
-        gt = _tdt(grad_dt)
-        dgamma = torch.empty((d_in,), dtype=gt, device=x.device)
-        dwd, dwu = torch.empty_like(w_down_cat, dtype=gt), torch.empty_like(w_up_stack, dtype=gt)
-    nb = lr_group_workspace_bytes(G, T, d_in, r, d_out, dt, 1)
-    ws = _ws(nb, x.device)
-    _check(lib().lr_group_bwd(_p(x), _rowmajor(x), _p(gamma), eps, norm, _p(w_down_cat), _p(w_up_stack), _p(z_cat),
-                              _p(stat), _p(dy_stack), d_out, T * d_out, _p(dx), d_in, _p(dgamma), _p(dwd), _p(dwu), G,
-                              T, d_in, r, d_out, act, dt, grad_dt, int(acc), _p(ws), nb, _stream()), "lr_group_bwd")
-    return dx, dgamma, dwd, dwu
+    dgamma, dwd, dwu = (None, None, None) if grads is None else grads
+    return _native().group_bwd(x, gamma, eps, norm, w_down_cat, w_up_stack, z_cat, stat, dy_stack, act, grads is not None, dgamma, dwd, dwu, grad_dt)
 
 
 # ---- the decoder block -----------------------------------------------------------------------
@@ -456,24 +422,11 @@ def lr_attention_bwd(q, k, v, o, dout, lse, B, S, H, hd, causal=True):
 
 def lr_attention_gqa_fwd(q, k, v, B, S, H, Hkv, hd, causal=True):
     """q [B*S, >= H*hd], k and v [B*S, >= Hkv*hd] (k and v with the same row stride)."""
-    o = torch.empty_like(q)
-    lse = torch.empty((B, H, S), dtype=torch.float32, device=q.device)
-    assert _rowmajor(k) == _rowmajor(v)
-    _check(lib().lr_attention_gqa_fwd(_p(q), _p(k), _p(v), _p(o), _p(lse), _rowmajor(q), _rowmajor(k), B, S, H, Hkv, hd,
-                                      int(causal), _dt(q), _stream()), "lr_attention_gqa_fwd")
-    return o, lse
+    return _native().attention_fwd(q, k, v, B, S, H, Hkv, hd, int(causal))
 
 
 def lr_attention_gqa_bwd(q, k, v, o, dout, lse, B, S, H, Hkv, hd, causal=True):
-    assert _rowmajor(k) == _rowmajor(v)
-    dq = torch.empty_like(q)
-    dk, dv = (torch.empty_strided(k.shape, k.stride(), dtype=k.dtype, device=k.device) for _ in range(2))   # rows of ldkv
-    nb = lib().lr_attention_gqa_bwd_workspace_bytes(B, S, H, Hkv, hd)
-    ws = _ws(nb, q.device)
-    _check(lib().lr_attention_gqa_bwd(_p(q), _p(k), _p(v), _p(o), _p(dout), _p(lse), _p(dq), _p(dk), _p(dv), _rowmajor(q),
-                                      _rowmajor(k), B, S, H, Hkv, hd, int(causal), _dt(q), _p(ws), ws.numel(), _stream()),
-           "lr_attention_gqa_bwd")
-    return dq, dk, dv
+    return _native().attention_bwd(q, k, v, o, dout, lse, B, S, H, Hkv, hd, int(causal))
 
 
 # ---- measurement aid -----------------------------------------------------------------------
@@ -517,18 +470,11 @@ def lr_mfma_probe(random_operands=True, iters=20000, launches=20):
 
 # ---- standalone memory-bound kernels ---------------------------------------------------------
 def lr_rms_stat(x):
-    T, d = x.shape
-    stat = torch.empty((T,), dtype=torch.float32, device=x.device)
-    _check(lib().lr_rms_stat(_p(x), _rowmajor(x), _p(stat), T, d, _dt(x), _stream()), "lr_rms_stat")
-    return stat
+    return _native().rms_stat(x)
 
 
 def lr_rmsnorm_apply(x, gamma, stat, eps):
-    T, d = x.shape
-    out = torch.empty_like(x)
-    _check(lib().lr_rmsnorm_apply(_p(x), _rowmajor(x), _p(gamma), _p(stat), eps, _p(out), d, T, d, _dt(x), _stream()),
-           "lr_rmsnorm_apply")
-    return out
+    return _native().rmsnorm_apply(x, gamma, stat, eps)
 
 
 def lr_shard_down_fwd(x_shard, gamma_shard, eps, w_down_cat_shard):
@@ -557,14 +503,7 @@ def lr_online_rmsnorm_finish(h_sum, stat_sum, d_total, eps):
 
 def lr_rmsnorm_bwd(x, gamma, stat, eps, dxhat, dres=None):
     """Returns (dx, dgamma_part[nparts, d] fp32)."""
-    T, d = x.shape
-    dx = torch.empty_like(x)
-    nparts = lib().lr_rmsnorm_bwd_parts(T)
-    part = torch.empty((max(nparts, 1), d), dtype=torch.float32, device=x.device)
-    _check(lib().lr_rmsnorm_bwd(_p(x), _rowmajor(x), _p(gamma), _p(stat), eps, _p(dxhat), _rowmajor(dxhat), _p(dres),
-                                _rowmajor(dres) if dres is not None else 0, _p(dx), d, _p(part), T, d, _dt(x),
-                                _stream()), "lr_rmsnorm_bwd")
-    return dx, part
+    return _native().rmsnorm_bwd(x, gamma, stat, eps, dxhat, dres)
 
 
 def lr_act_fwd(z, act=LR_ACT_SILU):
@@ -575,15 +514,9 @@ def lr_act_fwd(z, act=LR_ACT_SILU):
 
 
 def lr_swiglu_fwd(g, u):
-    T, f = g.shape
-    m = torch.empty_like(g)
-    _check(lib().lr_swiglu_fwd(_p(g), _p(u), _p(m), _rowmajor(g), T, f, _dt(g), _stream()), "lr_swiglu_fwd")
-    return m
+    return _native().swiglu_fwd(g, u)
 
 
 def lr_swiglu_bwd(g, u, dm):
-    T, f = g.shape
-    dg, du = torch.empty_like(g), torch.empty_like(u)
-    _check(lib().lr_swiglu_bwd(_p(g), _p(u), _p(dm), _p(dg), _p(du), _rowmajor(g), T, f, _dt(g), _stream()),
-           "lr_swiglu_bwd")
-    return dg, du
+    """Returns (dg, du)."""
+    return _native().swiglu_bwd(g, u, dm)
