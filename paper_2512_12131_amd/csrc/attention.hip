@@ -1278,8 +1278,9 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_long_kernel(const uint16_t* 
 }
 
 // ----------------------------------------------------------------------------------------------
-// backward, dK and dV of 256 keys where the score gradient is not kept and there is work for the chip (dkv_pairs below): pairs of
-// wavefronts share 64 keys and walk 32-query blocks together, one forming S, P and dV, the other dP, dS and dK
+// backward, dK and dV by pairs of wavefronts that share 32 KB keys and walk 32-query blocks together, one forming S, P and dV, the
+// other dP, dS and dK: 256 keys per workgroup where the score gradient is formed twice and there is work for the chip (dkv_pairs
+// below), 128 where it is stored and a workgroup has a CU to itself
 //
 // Bound: what one wavefront of a SIMD does while the other's MFMAs run.  A wavefront that does all of a key block's work holds dK,
 // dV, K and V of 32 keys (192 registers): it is alone on its SIMD, its MFMAs and its vector arithmetic follow each other (matrix pipes
@@ -1290,25 +1291,28 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_long_kernel(const uint16_t* 
 // dK / dV kernels, in the same order: the same bits.
 // Whole backward, us, the other kernels -> this one: 2 x 2047 tokens, 32 / 8 heads 338 -> 308; 2 x 1501, 32 heads 245 -> 224; 4 x 4095, 8
 // heads 524 -> 497; 1 x 12001, 8 heads 1237 -> 1147; 16 x 300, 16 heads 115 -> 101; 16 x 500, 32 heads 327 -> 316.
-// With the score gradient stored as well the stores were what it waited for (8 x 2048, 16 heads 621 -> 634): not done.
+// With the score gradient stored as well the stores were what 256 keys waited for (8 x 2048, 16 heads 621 -> 634): not done.  128
+// keys leave registers for a read-ahead of six operands (of two: 1 x 4096 tokens, 4 heads 166 -> 169) and wait for the stores of
+// three blocks before only.
 // ----------------------------------------------------------------------------------------------
 constexpr int PAIR_NS = 5;                                       // ring of 32-query blocks: one or two in use, three on their way
 constexpr int PAIR_BLOCK = 2 * 32 * HD * 2 + 512;                // Q rows, dO rows, lse2, D (64 entries each, 32 used)
 constexpr int PAIR_X = PAIR_NS * PAIR_BLOCK;                     // P of the four pairs, two blocks
 constexpr int PAIR_NONE = PAIR_X + 2 * 4 * 8192;                 // a place for what nobody reads
 constexpr int PAIR_LDS = PAIR_NONE + 256;
-constexpr int PAIR_D = 2;                                        // LDS operands are read this many pairs of MFMAs ahead
 static_assert(PAIR_BLOCK % 256 == 0 && PAIR_LDS <= 160 * 1024, "LDS of a CU");
 
-template <bool SCALED>
+template <int KB, bool SCALED, bool WRITE_DS>
 __global__ __launch_bounds__(512) void attn_bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                                                                 const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
                                                                 const float* __restrict__ lse2, const float* __restrict__ D,
                                                                 uint16_t* __restrict__ dk, uint16_t* __restrict__ dv,
-                                                                int64_t ld, int64_t ldkv, int64_t lddkv, int grp, int S, int H,
+                                                                uint16_t* __restrict__ dst, int64_t ld, int64_t ldkv, int64_t lddkv, int grp, int S, int H,
                                                                 float scale) {
   extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
-  constexpr int BN = 256;
+  static_assert(!WRITE_DS || SCALED, "what is stored is scaled");
+  constexpr int BN = 128 * KB;
+  constexpr int PAIR_D = KB == 2 ? 2 : 6;                  // LDS operands are read this many groups of KB MFMAs ahead
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int pair = wave & 3;
   const bool second = wave >= 4;                           // dP, dS, dK; otherwise S, P, dV
@@ -1336,6 +1340,19 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_pair_kernel(const uint16_t* 
     lds_dma_at(rsrc_from(rsO, off, valid), p + 8192u + (uint32_t)wave * 1024u, offT[0]);
     lds_dma4_at(rsLD, (wave & 3) == 0 ? p + 16384u + (uint32_t)(wave >> 2) * 256u : lds0 + PAIR_NONE, (uint32_t)(qb * 32 + lane) * 4u);
   };
+  // dS^T of this (batch, head), see attn_bwd_dkv_kernel
+  const __amdgpu_buffer_rsrc_t rsS = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(WRITE_DS ? dst + ((int64_t)b * H + head) * S * S : nullptr), 0, WRITE_DS ? (uint32_t)S * (uint32_t)S * 2u : 0u, 0x00020000);
+  auto store_ds = [&](const bf16x8& f, int key, int q16) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const uint4 w = __builtin_bit_cast(uint4, f);
+    const auto sx = __builtin_amdgcn_permlane32_swap(w.x, w.z, false, false);
+    const auto sy = __builtin_amdgcn_permlane32_swap(w.y, w.w, false, false);
+    const int q0 = q16 + 8 * (lane >> 5);
+    const uint32_t o = q0 < S ? (uint32_t)key * (uint32_t)S * 2u + (uint32_t)q0 * 2u : DMA_OOB;
+    __builtin_amdgcn_raw_buffer_store_b128(u32x4{sx[0], sy[0], sx[1], sy[1]}, rsS, (int)o, 0, 0);
+  };
+  const bf16x8 zero_frag = __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0));
   uint32_t rowl, trl;
   {
     const int l31 = lane & 31, f = ((l31 & 3) << 2) | ((l31 >> 2) & 3), g = lane >> 4, s = lane & 15;
@@ -1346,26 +1363,31 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_pair_kernel(const uint16_t* 
   for (int pass = 0; pass < 2; pass++) {
     const int kblk = pass == 0 ? wg.x : nkb - 1 - wg.x;
     if (pass == 1 && ((int)gridDim.x == nkb || kblk <= wg.x)) break;   // (unpaired launch: see the forward)
-    const int n0 = kblk * BN, nw0 = n0 + pair * 64;
+    const int n0 = kblk * BN, nw0 = n0 + pair * 32 * KB;
     wait_vm0();                                            // the pass before: its last loads, and everyone done with the ring
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
+    // what the dQ product reads of queries before this key block: zeros
+    if (WRITE_DS && second)
+      for (int qz = n0 / 256 * 256; qz < n0; qz += 16)
+#pragma unroll
+        for (int nb = 0; nb < KB; nb++) store_ds(zero_frag, nw0 + nb * 32 + (lane & 31), qz);
     // K or V rows of the pair's keys stay in registers (B operands); rows past S read as zeros.
-    bf16x8 kv[2][8];
+    bf16x8 kv[KB][8];
     {
       const __amdgpu_buffer_rsrc_t rsKV = __builtin_amdgcn_make_buffer_rsrc(
           (void*)((second ? v : k) + tok0 * ldkv + kvoff), 0, (uint32_t)(S - 1) * (uint32_t)ldkv * 2u + 256u, 0x00020000);
       const uint32_t off = (uint32_t)(nw0 + (lane & 31)) * (uint32_t)ldkv * 2u + (uint32_t)(lane >> 5) * 16u;
 #pragma unroll
-      for (int nb = 0; nb < 2; nb++)
+      for (int nb = 0; nb < KB; nb++)
 #pragma unroll
         for (int ks = 0; ks < 8; ks++)
           kv[nb][ks] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
               rsKV, (int)(off + (uint32_t)(nb * 32) * (uint32_t)ldkv * 2u + (uint32_t)ks * 32u), 0, 0));
     }
-    f32x16 acc[2][4];                                      // dK^T or dV^T
+    f32x16 acc[KB][4];                                     // dK^T or dV^T
 #pragma unroll
-    for (int nb = 0; nb < 2; nb++)
+    for (int nb = 0; nb < KB; nb++)
 #pragma unroll
       for (int hb = 0; hb < 4; hb++)
 #pragma unroll
@@ -1390,7 +1412,7 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_pair_kernel(const uint16_t* 
       return __builtin_bit_cast(bf16x8, r);
     };
     // scores of the block at blk (its Q or dO rows): 32 queries x 32 NB keys
-    auto scores = [&](uint32_t blk, f32x16 (&x)[2], auto NB) {
+    auto scores = [&](uint32_t blk, f32x16 (&x)[KB], auto NB) {
 #pragma unroll
       for (int nb = 0; nb < decltype(NB)::value; nb++)
 #pragma unroll
@@ -1407,9 +1429,9 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_pair_kernel(const uint16_t* 
       });
     };
     // acc += columns of the block at blk (its dO or Q rows) times what was made of the scores
-    auto outputs = [&](uint32_t blk, const bf16x8 (&w)[2][2], auto NB) {
+    auto outputs = [&](uint32_t blk, const bf16x8 (&w)[KB][2], auto NB) {
       bf16x8 f[PAIR_D + 1];
-      unroll_for<PAIR_D>([&](auto I) { f[decltype(I)::value] = tr_frag(blk, 0, decltype(I)::value); });
+      unroll_for<PAIR_D>([&](auto I) { f[decltype(I)::value] = tr_frag(blk, decltype(I)::value >> 2, decltype(I)::value & 3); });
       unroll_for<8>([&](auto I) {
         constexpr int s = decltype(I)::value, a = s + PAIR_D;
         if constexpr (a < 8) f[a % (PAIR_D + 1)] = tr_frag(blk, a >> 2, a & 3);
@@ -1420,10 +1442,11 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_pair_kernel(const uint16_t* 
       });
     };
     // Between the first and the second half of block i: this wavefront's loads of block i + 1 have landed, everyone is done
-    // with block i - 1.  Behind those loads lie the ones of two more blocks.
-    auto meet = [&](int i) {
+    // with block i - 1.  Behind those loads lie the ones of two more blocks, and from block 3 on (STORES) what three blocks stored.
+    auto meet = [&](int i, auto STORES) {
       wait_lgkm0();
-      wait_vm<6>();
+      if (decltype(STORES)::value && i >= 3) wait_vm<6 + 3 * 2 * KB>();
+      else wait_vm<6>();
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
       dma(spare, qb0 + i + PAIR_NS - 1);
@@ -1435,22 +1458,32 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_pair_kernel(const uint16_t* 
     // Blocks of this pass: those before the pair's keys, the one that sees the first 32 of them (and only those: what the other 32
     // would add is 0 times it, NaN where it is not finite), the one with the other 32 keys' diagonal, whole ones, perhaps one with
     // the last queries.  Loops of their own: a branch around part of a block's work would have the accumulators change registers.
-    const int skip = min(pair * 2, n), half = min(skip + 1, n), diag = min(skip + 2, n), whole = max(diag, S / 32 - qb0);
+    const int skip = min(pair * KB, n), half = KB == 2 ? min(skip + 1, n) : skip, diag = min(skip + KB, n), whole = max(diag, S / 32 - qb0);
     constexpr std::integral_constant<int, 1> one{};
-    constexpr std::integral_constant<int, 2> two{};
+    constexpr std::integral_constant<int, KB> all{};
+    constexpr std::false_type none{};
+    constexpr std::integral_constant<bool, WRITE_DS> stores{};
     int i = 0;
     for (; i < skip; i++) {
-      meet(i);
+      if (second) meet(i, stores);
+      else meet(i, none);
+      if constexpr (WRITE_DS) {
+        if (second)
+#pragma unroll
+          for (int t = 0; t < 2; t++)
+#pragma unroll
+            for (int nb = 0; nb < KB; nb++) store_ds(zero_frag, nw0 + nb * 32 + (lane & 31), (qb0 + i) * 32 + t * 16);
+      }
       next();
     }
     if (!second) {
       auto block = [&](auto MASKED, auto NB) {
         const uint32_t blk = (uint32_t)slot * PAIR_BLOCK;
-        f32x16 x[2];
+        f32x16 x[KB];
         scores(blk, x, NB);
         const float* sl = reinterpret_cast<const float*>(smem + blk + 16384);
         unsigned char* xp = smem + PAIR_X + (i & 1) * 32768 + pair * 8192 + lane * 16;
-        bf16x8 w[2][2];
+        bf16x8 w[KB][2];
         unroll_for<4>([&](auto G) {
           constexpr int g = decltype(G)::value;
           const f32x4 lv = *reinterpret_cast<const f32x4*>(sl + 8 * g + 4 * (lane >> 5));
@@ -1474,23 +1507,24 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_pair_kernel(const uint16_t* 
             for (int nb = 0; nb < decltype(NB)::value; nb++) w[nb][g >> 1] = pack_acc_half(x[nb], g >> 1);
           __builtin_amdgcn_sched_barrier(0);
         });
-        meet(i);
+        meet(i, none);
         outputs(blk + 8192, w, NB);
         next();
       };
-      for (; i < half; i++) block(std::true_type{}, one);
-      for (; i < diag; i++) block(std::true_type{}, two);
-      for (; i < whole; i++) block(std::false_type{}, two);
-      for (; i < n; i++) block(std::true_type{}, two);
+      if constexpr (KB == 2)
+        for (; i < half; i++) block(std::true_type{}, one);
+      for (; i < diag; i++) block(std::true_type{}, all);
+      for (; i < whole; i++) block(std::false_type{}, all);
+      for (; i < n; i++) block(std::true_type{}, all);
     } else {
       auto block = [&](auto NB) {
         const uint32_t blk = (uint32_t)slot * PAIR_BLOCK;
-        f32x16 x[2];
+        f32x16 x[KB];
         scores(blk + 8192, x, NB);
-        meet(i);
+        meet(i, stores);
         const float* sd = reinterpret_cast<const float*>(smem + blk + 16384 + 256);
         const unsigned char* xp = smem + PAIR_X + (i & 1) * 32768 + pair * 8192 + lane * 16;
-        bf16x8 w[2][2];
+        bf16x8 w[KB][2];
         unroll_for<4>([&](auto G) {
           constexpr int g = decltype(G)::value;
           const f32x4 dvv = *reinterpret_cast<const f32x4*>(sd + 8 * g + 4 * (lane >> 5));
@@ -1505,14 +1539,20 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_pair_kernel(const uint16_t* 
             for (int nb = 0; nb < decltype(NB)::value; nb++) w[nb][g >> 1] = pack_acc_half(x[nb], g >> 1);
           __builtin_amdgcn_sched_barrier(0);
         });
+        if constexpr (WRITE_DS) {   // (as many stores for every block: the waits above count them)
+          static_assert(KB == 1, "a block with the first 32 keys alone stores less");
+#pragma unroll
+          for (int t = 0; t < 2; t++) store_ds(w[0][t], nw0 + (lane & 31), (qb0 + i) * 32 + t * 16);
+        }
         outputs(blk, w, NB);
         next();
       };
-      for (; i < half; i++) block(one);
-      for (; i < n; i++) block(two);
+      if constexpr (KB == 2)
+        for (; i < half; i++) block(one);
+      for (; i < n; i++) block(all);
     }
 #pragma unroll
-    for (int nb = 0; nb < 2; nb++) {
+    for (int nb = 0; nb < KB; nb++) {
       const int ni = nw0 + nb * 32 + (lane & 31);
       if (ni < S) store_acc_T((second ? dk : dv) + (tok0 + ni) * lddkv + hoff, acc[nb], second && !SCALED ? scale : 1.f, lane);
     }
@@ -1646,8 +1686,9 @@ hipError_t attention_gqa_bwd_bf16(const void* q, const void* k, const void* v, c
     if (e == hipSuccess) e = set_lds(attn_bwd_dq_kernel<8, false>, DQ_LDS);
     if (e == hipSuccess) e = set_lds(attn_bwd_dq_kernel<8, true>, DQ_LDS);
     if (e == hipSuccess) e = set_lds(attn_bwd_dkv_long_kernel, LDKV_LDS);
-    if (e == hipSuccess) e = set_lds(attn_bwd_dkv_pair_kernel<false>, PAIR_LDS);
-    if (e == hipSuccess) e = set_lds(attn_bwd_dkv_pair_kernel<true>, PAIR_LDS);
+    if (e == hipSuccess) e = set_lds(attn_bwd_dkv_pair_kernel<2, false, false>, PAIR_LDS);
+    if (e == hipSuccess) e = set_lds(attn_bwd_dkv_pair_kernel<2, true, false>, PAIR_LDS);
+    if (e == hipSuccess) e = set_lds(attn_bwd_dkv_pair_kernel<1, true, true>, PAIR_LDS);
     if (e == hipSuccess) e = set_lds(attn_bwd_dkv_kernel<DKV_NB, false>, DKV_LDS);
     if (e == hipSuccess) e = set_lds(attn_bwd_dkv_kernel<DKV_NB, true>, DKV_LDS);
     return e;
@@ -1680,9 +1721,18 @@ hipError_t attention_gqa_bwd_bf16(const void* q, const void* k, const void* v, c
   const bool pairs = dkv_pairs(S, heads), kept = keep_ds(B, S, H);
   if (kept && !pairs) {
     uint16_t* dst = (uint16_t*)((char*)ws + small);
-    hipLaunchKernelGGL((attn_bwd_dkv_kernel<DKV_NB, true>), kv_grid, dim3(256), DKV_LDS, st, (const uint16_t*)q,
-                       (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout, lse2, D, dk_w, dv_w, dst, ld, ldkv,
-                       lddkv, grp, S, H, scale);
+    // Pairs of wavefronts put two on a SIMD where a workgroup has a CU to itself (whole backward, us, four wavefronts / four pairs:
+    // 1 x 2048 tokens, 8 heads 100 / 92.3, 1 x 4096, 4 heads 181 / 165.8, 1 x 776, 32 heads 58.6 / 55.4, 2 x 1536, 16 heads
+    // 107.8 / 100.8, 4 x 1024, 16 heads 92.9 / 90.1).  They lose where two workgroups of four fit beside each other (8 x 1280, 16
+    // heads 315 / 322), and on few long sequences that fill the chip (4 x 4096, 4 heads 258.8 / 276.1; 2 x 2048, 16 heads 152 / 161).
+    if (nkb * heads <= 256 || (nkb * heads <= 512 && S <= 1536))
+      hipLaunchKernelGGL((attn_bwd_dkv_pair_kernel<1, true, true>), kv_grid, dim3(512), PAIR_LDS, st, (const uint16_t*)q,
+                         (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout, lse2, D, dk_w, dv_w, dst, ld, ldkv,
+                         lddkv, grp, S, H, scale);
+    else
+      hipLaunchKernelGGL((attn_bwd_dkv_kernel<DKV_NB, true>), kv_grid, dim3(256), DKV_LDS, st, (const uint16_t*)q,
+                         (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout, lse2, D, dk_w, dv_w, dst, ld, ldkv,
+                         lddkv, grp, S, H, scale);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     // dQ[q, :] = sum_key (scale dS^T)[key, q] * K[key, :], per (batch, head): both operands k-major, the
@@ -1717,9 +1767,9 @@ hipError_t attention_gqa_bwd_bf16(const void* q, const void* k, const void* v, c
   else if (S >= 1024 && (S + 255) / 256 * heads <= 256) dq_launch(Four{}, std::false_type{}, true);
   else dq_launch(Eight{}, std::false_type{}, (S + 255) / 256 * heads > 256);
   auto pair_launch = [&](auto SCALED) {
-    hipLaunchKernelGGL(attn_bwd_dkv_pair_kernel<decltype(SCALED)::value>, dim3(((S + 255) / 256 + 1) / 2, H, B), dim3(512), PAIR_LDS, st,
-                       (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout, lse2, D, dk_w, dv_w, ld, ldkv,
-                       lddkv, grp, S, H, scale);
+    hipLaunchKernelGGL((attn_bwd_dkv_pair_kernel<2, decltype(SCALED)::value, false>), dim3(((S + 255) / 256 + 1) / 2, H, B), dim3(512),
+                       PAIR_LDS, st, (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout, lse2, D, dk_w, dv_w,
+                       (uint16_t*)nullptr, ld, ldkv, lddkv, grp, S, H, scale);
   };
   if (pairs && kept) pair_launch(std::true_type{});
   else if (pairs) pair_launch(std::false_type{});

@@ -207,5 +207,19 @@ def test_attention_bwd_score_gradient_kept_or_formed_twice(S, n):
     print(f"attention backward, score gradient kept or not S={S} B={n}", flush=True)
     pairs = ((S + 255) // 256 + 1) // 2 * H * n
     many, one = _bwd_launches(S, n, H, Hkv), _bwd_launches(S, 1, H, Hkv)
-    assert [k[:2] for k in many] == [(pairs, 512)] * 2 and one[0][:2] == ((S + 127) // 128 * H, 256)
+    assert [k[:2] for k in many] == [(pairs, 512)] * 2 and one[0][:2] == ((S + 127) // 128 * H, 512)
     _compare_parts(S, n, (1,), H, Hkv)
+
+
+@pytest.mark.parametrize("S,n", [(8, 80), (136, 40), (136, 70), (520, 21), (1536, 10), (1536, 11), (1544, 9), (2056, 7)])
+def test_attention_bwd_key_blocks_of_pairs_or_of_wavefronts(S, n):
+    """Multiples of 8 tokens whose score gradient is stored: by four pairs of wavefronts where a workgroup has a CU, by four
+    wavefronts where it has not; the same bits."""
+    H, Hkv = 4, 2
+    print(f"attention backward, key blocks S={S} B={n}", flush=True)
+    nkb = (S + 127) // 128
+    for m in (1, n):
+        wide = nkb * H * m <= 256 or (nkb * H * m <= 512 and S <= 1536)
+        blocks = (nkb if nkb * H * m <= 256 else (nkb + 1) // 2) * H * m
+        assert _bwd_launches(S, m, H, Hkv)[0][:2] == (blocks, 512 if wide else 256)
+    _compare_parts(S, n, (1, n // 2), H, Hkv)
