@@ -176,7 +176,7 @@ GemmOp wgrad_op(const void* Aact, int64_t lda, int Mw, const void* Bact, int64_t
 
 // What the finishing pass of a gradient behind a norm does besides summing up.  A size query passes one too, of null pointers: such
 // a gradient takes another way through the workspace.
-struct NormFold { const void *colscale, *w_for_dgamma; float* dgamma_part; };
+struct NormFold { const void *colscale, *w_for_dgamma; float* dgamma_part; void* dgamma; };
 
 // dw[Mw, Nw] (+)= colscale * sum_t Aact[t, Mw] * Bact[t, Nw]    (reduction over tokens, split-K; colscale: of `fold`, if any)
 // n > 1: n such products, operands sA / sB elements apart, gradients stacked [n][Mw][Nw].
@@ -222,7 +222,8 @@ void wgrad(Ctx& c, const void* Aact, int64_t lda, int Mw, const void* Bact, int6
   gemm(c, op);
   c.nheld = held;
   const NormFold f = fold ? *fold : NormFold{};
-  LAUNCH(c, k_wgrad_finish(part, op.splitk, Mw, Nw, dw, f.colscale, f.w_for_dgamma, f.dgamma_part, accumulate, c.dt, c.gdt, c.st));
+  LAUNCH(c, k_wgrad_finish(part, op.splitk, Mw, Nw, dw, f.colscale, f.w_for_dgamma, f.dgamma_part, f.dgamma, accumulate, c.dt,
+                           c.gdt, c.st));
   c.release(m);
 }
 
@@ -335,13 +336,26 @@ int group_runs(const GrpArgs& a, GrpRun (&run)[2]) {
   return 2;
 }
 
-// w_down_cat with gamma folded into its columns
-const void* scaled_weight(Ctx& c, const GrpArgs& a) {
-  if (a.w_scaled_given) return a.w_scaled;
-  const int64_t GR = (int64_t)a.G * a.r;
-  void* wg = c.take((size_t)GR * a.d_in * esize(c.dt));
-  LAUNCH(c, k_scale_cols(a.w_down_cat, a.gamma, wg, GR, a.d_in, c.dt, c.st));
-  return wg;
+// w_down_cat with gamma folded into its columns; stat: and the row statistic of x
+const void* scaled_weight(Ctx& c, const GrpArgs& a, bool stat = false) {
+  if (a.w_scaled_given) {
+    if (stat) LAUNCH(c, k_rms_stat(a.x, a.ldx, a.stat, a.T, a.d_in, c.dt, c.st));
+    return a.w_scaled;
+  }
+  ScaleCols f;
+  f.w0 = a.w_down_cat; f.gamma0 = a.gamma; f.rows0 = (int64_t)a.G * a.r; f.cols = a.d_in;
+  f.out0 = c.take((size_t)f.rows0 * a.d_in * esize(c.dt));
+  if (stat) LAUNCH(c, k_scale_cols_rms_stat(f, a.x, a.ldx, a.stat, a.T, a.d_in, c.dt, c.st));
+  else LAUNCH(c, k_scale_cols(f, c.dt, c.st));
+  return f.out0;
+}
+
+// Sum of squares gathered from the A tiles inside the GEMM.  Every column tile of a row panel repeats the gather, so this pays only
+// while the output is one or two tiles wide; beyond that a separate pass over x (Alg. 1 line 1 as its own step) is faster (0.80
+// against 0.89 ms for the Q/K/V group of the 7B shape), and LR_NORM_ONLINE takes it.  LR_NORM_ONLINE_GATHER asks for the gather at
+// any width.
+bool stat_in_gemm(const Ctx& c, const GrpArgs& a) {
+  return c.dt == LR_BF16 && ((int64_t)a.G * a.r <= 512 || a.norm == LR_NORM_ONLINE_GATHER);
 }
 
 // z_cat = RMSNorm(x) . w_down_cat^T (+ sigma(z_cat) into `act`)
@@ -354,19 +368,12 @@ void group_down_seq(Ctx& c, const GrpArgs& a, void* act) {
   dn.epi.kind = EPI_DOWN; dn.epi.act = a.act; dn.epi.C2 = act; dn.epi.ldc2 = GR;
   if (a.lax) { dn.epi.kind = EPI_DOWN_LAX; dn.epi.R = a.h_prev; dn.epi.ldr = GR; }
   if (a.norm == LR_NORM_ONLINE || a.norm == LR_NORM_ONLINE_GATHER) {
-    dn.B = scaled_weight(c, a);
+    const bool gather = !a.stat_ready && stat_in_gemm(c, a);
+    dn.B = scaled_weight(c, a, !a.stat_ready && !gather);
     dn.epi.use_rho = 1; dn.epi.inv_d = 1.f / (float)a.d_in; dn.epi.eps = a.eps;
-    if (a.stat_ready) {
-      dn.epi.rowa = a.stat;
-    } else if (c.dt == LR_BF16 && (GR <= 512 || a.norm == LR_NORM_ONLINE_GATHER)) {
-      // sum of squares gathered from the A tiles inside the GEMM.  Every column tile of a row panel
-      // repeats the gather, so this pays only while the output is one or two tiles wide; beyond that a
-      // separate pass over x (Alg. 1 line 1 as its own step) is faster (0.80 against 0.89 ms for the
-      // Q/K/V group of the 7B shape), and LR_NORM_ONLINE takes it.  LR_NORM_ONLINE_GATHER asks for the
-      // gather at any width.
+    if (gather) {
       dn.epi.stat_from_a = 1; dn.epi.stat_out = a.stat;
     } else {
-      LAUNCH(c, k_rms_stat(a.x, a.ldx, a.stat, a.T, a.d_in, c.dt, c.st));
       dn.epi.rowa = a.stat;
     }
   } else if (a.norm == LR_NORM_TWO_PASS) {
@@ -509,7 +516,6 @@ void group_bwd_seq(Ctx& c, const GrpArgs& a, const void* act, bool act_new = fal
   int wd_join = 0;              // dW_down's partials and dx in one launch, on this tile
   const int64_t dg_parts = normed ? k_wgrad_dgamma_parts(GR) : 0;
   float* dgp = normed ? (float*)c.take((size_t)dg_parts * a.d_in * sizeof(float)) : nullptr;
-  auto dgamma = [&] { LAUNCH(c, k_colsum_parts(dgp, dg_parts, a.d_in, a.dgamma, a.accumulate, c.gdt, c.st)); };
   // dx = dp_cat . (w*gamma)  - (rho/d) * cdot * x  (+ residual gradient)
   GemmOp dx;
   dx.A = dp; dx.lda = GR; dx.B = a.w_down_cat; dx.ldb = a.d_in; dx.transB = 1; dx.C = a.dx; dx.ldc = a.lddx;
@@ -542,15 +548,14 @@ void group_bwd_seq(Ctx& c, const GrpArgs& a, const void* act, bool act_new = fal
     dx.B = a.w_scaled;
     const GemmOp both[2] = {wd, dx};
     LAUNCH(c, gemm_bf16_joint(wd_join, both, 2, c.st));
-    LAUNCH(c, k_wgrad_finish((const float*)wd.C, wd.splitk, wd.M, wd.N, a.dw_down_cat, a.gamma, a.w_down_cat, dgp, a.accumulate, c.dt, c.gdt, c.st));
-    dgamma();
+    LAUNCH(c, k_wgrad_finish((const float*)wd.C, wd.splitk, wd.M, wd.N, a.dw_down_cat, a.gamma, a.w_down_cat, dgp, a.dgamma, a.accumulate,
+                             c.dt, c.gdt, c.st));
     c.release(m);
     return;
   }
   if (normed) {
-    const NormFold fold{a.gamma, a.w_down_cat, dgp};
+    const NormFold fold{a.gamma, a.w_down_cat, dgp, a.dgamma};
     wgrad(c, dp, GR, (int)GR, a.x, a.ldx, (int)a.d_in, a.T, a.dw_down_cat, &fold, a.accumulate);
-    dgamma();
     dx.B = scaled_weight(c, a);
   } else {
     wgrad(c, dp, GR, (int)GR, a.x, a.ldx, (int)a.d_in, a.T, a.dw_down_cat, nullptr, a.accumulate);
@@ -765,21 +770,18 @@ GrpArgs group_args(const Blk& b, int G, int64_t d_out) {
 }
 
 // the down-projection weights of both norms' groups with gamma folded in: qkv [3r, d], then gate / up [2r, d]
-void* scaled_weights(Ctx& c, const Blk& b, const lr_block_params* p) {
-  void* w = c.take((size_t)5 * b.r * b.d * 2);
-  LAUNCH(c, k_scale_cols2(p->w_dn_qkv, p->gamma1, w, 3 * b.r, p->w_dn_gu, p->gamma2, (char*)w + (size_t)3 * b.r * b.d * 2, 2 * b.r,
-                          b.d, LR_BF16, c.st));
-  return w;
+ScaleCols folded_weights(Ctx& c, const Blk& b, const lr_block_params* p) {
+  char* w = (char*)c.take((size_t)5 * b.r * b.d * 2);
+  ScaleCols f;
+  f.w0 = p->w_dn_qkv; f.gamma0 = p->gamma1; f.out0 = w; f.rows0 = 3 * b.r;
+  f.w1 = p->w_dn_gu; f.gamma1 = p->gamma2; f.out1 = w + (size_t)3 * b.r * b.d * 2; f.rows1 = 2 * b.r;
+  f.cols = b.d;
+  return f;
 }
 
 void rope_qk(Ctx& c, const Blk& b, void* qkv, int inverse) {
-  if (b.dkv == b.d) {   // q and k are two [T, d] tensors back to back: one pass over both
-    LAUNCH(c, k_rope128_bf16(qkv, b.d, b.rope_cos, b.rope_sin, 2 * b.T, (int)b.S, (int)b.H, inverse, c.st));
-    return;
-  }
-  LAUNCH(c, k_rope128_bf16(qkv, b.d, b.rope_cos, b.rope_sin, b.T, (int)b.S, (int)b.H, inverse, c.st));
-  LAUNCH(c, k_rope128_bf16((char*)qkv + (size_t)b.T * b.d * 2, b.dkv, b.rope_cos, b.rope_sin, b.T, (int)b.S, (int)b.Hkv,
-                           inverse, c.st));
+  LAUNCH(c, k_rope128_bf16(qkv, b.d, (int)b.H, (char*)qkv + (size_t)b.T * b.d * 2, b.dkv, (int)b.Hkv, b.rope_cos, b.rope_sin, b.T,
+                           (int)b.S, inverse, c.st));
 }
 
 // The stride of d_ff wide rows that have room for `room` elements each.  Past 2 GB of rows a product that reduces over tokens
@@ -811,7 +813,17 @@ void block_fwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   a.stat_ready = b.stat_x_ready;
   a.lax = lax; a.h_prev = lax ? lx->h_prev_qkv : nullptr;
   const bool scaled = b.norm != LR_NORM_TWO_PASS;
-  const char* w_scaled = scaled ? (const char*)scaled_weights(c, b, p) : nullptr;
+  const char* w_scaled = nullptr;
+  if (scaled) {
+    const ScaleCols fold = folded_weights(c, b, p);
+    w_scaled = (const char*)fold.out0;
+    if (a.stat_ready || stat_in_gemm(c, a)) {
+      LAUNCH(c, k_scale_cols(fold, LR_BF16, c.st));
+    } else {
+      LAUNCH(c, k_scale_cols_rms_stat(fold, x, a.ldx, a.stat, T, d, LR_BF16, c.st));
+      a.stat_ready = 1;
+    }
+  }
   a.w_scaled_given = scaled; a.w_scaled = w_scaled;
   group_fwd_seq(c, a);
   if (b.rope_cos) rope_qk(c, b, qkv, 0);
@@ -895,8 +907,9 @@ void block_bwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   const int act_kind = lax ? (int)LR_ACT_IDENTITY : b.act;
   const ActLayers al{{ck->z_d, ck->z_o, ck->z_gu, ck->z_qkv}, {lx->h_prev_d, lx->h_prev_o, lx->h_prev_gu, lx->h_prev_qkv},
                      {act_d, act_o, act_g, act_q}, {row, row, 2 * row, 3 * row}, {}, act_once ? 4 : 3};
-  LAUNCH(c, k_act_layers_bf16(al, act_kind, c.st));
-  const char* w_scaled = fold_once ? (const char*)scaled_weights(c, b, p) : nullptr;
+  const ScaleCols fold = fold_once ? folded_weights(c, b, p) : ScaleCols{};
+  const char* w_scaled = (const char*)fold.out0;
+  LAUNCH(c, k_act_layers_bf16(al, act_kind, fold_once ? &fold : nullptr, c.st));
 
   // ---- MLP side ----
   c.hold();             // down-D's weight gradient, dz_d, h1 and g wait for nothing but the activations
@@ -931,7 +944,7 @@ void block_bwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   // re-forward q, k, v, o
   if (!act_once) {
     const ActLayers aq{{ck->z_qkv}, {lx->h_prev_qkv}, {act_q}, {3 * row}, {}, 1};
-    LAUNCH(c, k_act_layers_bf16(aq, act_kind, c.st));
+    LAUNCH(c, k_act_layers_bf16(aq, act_kind, nullptr, c.st));
   }
   c.hold();             // q, k, v beside the backward through up-O
   single_up_bwd(c, b, dh1, d, act_o, ck->z_o, p->w_up_o, g->w_up_o, dz1, accumulate, lax, lx->dz_next_o, lx->dh_prev_o);
@@ -1419,7 +1432,7 @@ int lr_rope(void* x, int64_t ldx, const float* cos_tab, const float* sin_tab, in
   if (!cos_tab || !sin_tab) return LR_EINVAL;
   TRY(check_ptrs(LR_BF16, {x, cos_tab, sin_tab}));
   if (ldx % 8) return LR_EALIGN;
-  hipError_t e = k_rope128_bf16(x, ldx, cos_tab, sin_tab, B * S, (int)S, (int)H, inverse, (hipStream_t)stream);
+  hipError_t e = k_rope128_bf16(x, ldx, (int)H, nullptr, 0, 0, cos_tab, sin_tab, B * S, (int)S, inverse, (hipStream_t)stream);
   return e == hipSuccess ? LR_OK : LR_ELAUNCH;
 }
 

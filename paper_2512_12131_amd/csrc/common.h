@@ -152,6 +152,18 @@ int launch_timer_end(lr_launch_record* out, int max_records, int* n_records);
 
 // ---- streaming kernels (stream_kernels.hip) ---------------------------------------------------
 hipError_t k_rms_stat(const void* x, int64_t ldx, float* stat, int64_t T, int64_t d, int dt, hipStream_t);
+// out[n, k] = w[n, k] * gamma[k] for one or two (rows1 > 0) matrices of equal width
+struct ScaleCols {
+  const void *w0 = nullptr, *gamma0 = nullptr;
+  void* out0 = nullptr;
+  int64_t rows0 = 0;
+  const void *w1 = nullptr, *gamma1 = nullptr;
+  void* out1 = nullptr;
+  int64_t rows1 = 0, cols = 0;
+};
+hipError_t k_scale_cols(const ScaleCols& p, int dt, hipStream_t);
+// both in one launch
+hipError_t k_scale_cols_rms_stat(const ScaleCols& p, const void* x, int64_t ldx, float* stat, int64_t T, int64_t d, int dt, hipStream_t);
 hipError_t k_rmsnorm_apply(const void* x, int64_t ldx, const void* gamma, const float* stat, float eps,
                            void* xhat, int64_t ldo, int64_t T, int64_t d, int dt, hipStream_t);
 // out[t, j] = h[t, j] * rsqrt(stat[t] / d_total + eps), j < n  (the global rescale of a sharded projection)
@@ -166,9 +178,9 @@ hipError_t k_act_fwd(const void* z, int64_t ldz, void* a, int64_t lda, int64_t T
 hipError_t k_swiglu_fwd(const void* g, const void* u, void* m, int64_t ld, int64_t T, int64_t f, int dt,
                         hipStream_t);
 // rotary embedding in place on x[rows, ld] (bf16, H heads of 128 from column 0, position = row % S);
-// cos / sin tables [S, 64] fp32; inverse = the transposed rotation
-hipError_t k_rope128_bf16(void* x, int64_t ld, const float* cos_tab, const float* sin_tab, int64_t rows, int S, int H,
-                          int inverse, hipStream_t);
+// cos / sin tables [S, 64] fp32; inverse = the transposed rotation.  And on x1[rows, ld1] with H1 heads (0: no such tensor).
+hipError_t k_rope128_bf16(void* x, int64_t ld, int H, void* x1, int64_t ld1, int H1, const float* cos_tab, const float* sin_tab,
+                          int64_t rows, int S, int inverse, hipStream_t);
 // a[i] = act(z[i]), or z[i] + h[i] where h[i] is given: up to four dense bf16 tensors of bytes[i] (a multiple of 16)
 struct ActLayers {
   const void *z[4], *h[4];
@@ -177,7 +189,8 @@ struct ActLayers {
   int first[4];      // filled in by the launch
   int n;
 };
-hipError_t k_act_layers_bf16(ActLayers p, int act, hipStream_t);
+// fold: optional, in the same launch (bf16)
+hipError_t k_act_layers_bf16(ActLayers p, int act, const ScaleCols* fold, hipStream_t);
 hipError_t k_swiglu_bwd(const void* g, const void* u, const void* dm, void* dg, void* du, int64_t ld,
                         int64_t T, int64_t f, int dt, hipStream_t);
 // out[r, c] = in[c, r] for in[rows, cols] (ld_in) -> out[cols, rows] (ld_out)
@@ -188,18 +201,12 @@ hipError_t k_rowsum_parts(const float* part, int64_t ld, int members, const RowP
 // out[m] = sum_n a[m,n] * b[m,n]
 hipError_t k_rowdot(const void* a, int64_t lda, const void* b, int64_t ldb, float* out, int64_t M,
                     int64_t N, int dt, hipStream_t);
-// wout[n, k] = w[n, k] * gamma[k]
-hipError_t k_scale_cols(const void* w, const void* gamma, void* wout, int64_t rows, int64_t cols, int dt,
-                        hipStream_t);
-// the same for two matrices of equal width
-hipError_t k_scale_cols2(const void* w0, const void* gamma0, void* out0, int64_t rows0, const void* w1, const void* gamma1,
-                         void* out1, int64_t rows1, int64_t cols, int dt, hipStream_t);
 // Sum `nsplit` fp32 partials [nsplit][count] (batch-major outside) and write / accumulate into dw.
 //   dw[i] (+)= colscale[i % cols] * sum_s part[s][i]      (colscale optional)
-// With wg_for_dgamma (the un-scaled weight) also emits dgamma_part[k_wgrad_dgamma_parts()][cols] partial sums of
-// w * sum_s part (dgamma = sum over all rows).
+// With w_for_dgamma (the un-scaled weight) also dgamma (+)= the column sums of w * sum_s part, through
+// dgamma_part[k_wgrad_dgamma_parts()][cols].
 hipError_t k_wgrad_finish(const float* part, int nsplit, int64_t rows, int64_t cols, void* dw,
-                          const void* colscale, const void* w_for_dgamma, float* dgamma_part,
+                          const void* colscale, const void* w_for_dgamma, float* dgamma_part, void* dgamma,
                           int accumulate, int dt, int out_dt, hipStream_t);
 int64_t k_wgrad_dgamma_parts(int64_t rows);
 // The same for up to FINISH_MAX gradients of one call in one launch (bf16 operands, no column scale, no dgamma).

@@ -24,11 +24,11 @@ __device__ __forceinline__ float wave_sum(float v) {
 // ---- S[t] = sum_j x[t,j]^2 : one wavefront per row ---------------------------------------------
 // (Many short wavefronts read faster here than fewer wavefronts with more rows or vectors each.)
 template <int DT>
-__global__ __launch_bounds__(256) void rms_stat_kernel(const void* x, int64_t ldx, float* stat, int64_t T, int64_t d) {
+__device__ __forceinline__ void rms_stat_rows(int block, const void* x, int64_t ldx, float* stat, int64_t T, int64_t d) {
   using S = St<DT>;
   using IO = VecIO<typename S::T, S::NV>;
   const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int64_t row = (int64_t)block * 4 + (threadIdx.x >> 6);
   if (row >= T) return;
   float s = 0.f;
   // four vectors per lane in flight before the arithmetic
@@ -51,6 +51,42 @@ __global__ __launch_bounds__(256) void rms_stat_kernel(const void* x, int64_t ld
   }
   s = wave_sum(s);
   if (lane == 0) stat[row] = s;
+}
+template <int DT>
+__global__ __launch_bounds__(256) void rms_stat_kernel(const void* x, int64_t ldx, float* stat, int64_t T, int64_t d) {
+  rms_stat_rows<DT>((int)blockIdx.x, x, ldx, stat, T, d);
+}
+
+// Columns scaled by gamma, of one or two matrices of equal width (rows1 = 0: one): a block folds both of its norms' gammas in one
+// launch.  Workgroup `block` of `blocks`.
+template <int DT>
+__device__ __forceinline__ void scale_cols_part(const ScaleCols& p, int block, int blocks) {
+  using S = St<DT>;
+  using IO = VecIO<typename S::T, S::NV>;
+  const int64_t cpr = p.cols / S::NV, total0 = p.rows0 * cpr, total = total0 + p.rows1 * cpr;
+  for (int64_t j = (int64_t)block * 256 + threadIdx.x; j < total; j += (int64_t)blocks * 256) {
+    const bool second = j >= total0;
+    const int64_t i = second ? j - total0 : j;
+    const int64_t c = (i % cpr) * S::NV, off = (i / cpr) * p.cols + c;
+    float wv[S::NV], gv[S::NV];
+    IO::load(second ? p.w1 : p.w0, off, wv);
+    IO::load(second ? p.gamma1 : p.gamma0, c, gv);
+#pragma unroll
+    for (int k = 0; k < S::NV; k++) wv[k] *= gv[k];
+    IO::store(second ? p.out1 : p.out0, off, wv);
+  }
+}
+template <int DT>
+__global__ __launch_bounds__(256) void scale_cols_kernel(ScaleCols p) {
+  scale_cols_part<DT>(p, (int)blockIdx.x, (int)gridDim.x);
+}
+// A normed group folds its gamma and takes the rows' statistic: neither waits for the other (777 rows of 4096 beside 5120 x 4096
+// weights 14.5 + 6.3 -> 15.4 us, 16384 rows of 2048 beside 1536 x 2048 5.7 + 12.0 -> 14.6, and one way in and out less).
+template <int DT>
+__global__ __launch_bounds__(256) void scale_cols_rms_stat_kernel(ScaleCols p, int stat_blocks, const void* x, int64_t ldx, float* stat,
+                                                                  int64_t T, int64_t d) {
+  if ((int)blockIdx.x < stat_blocks) rms_stat_rows<DT>((int)blockIdx.x, x, ldx, stat, T, d);
+  else scale_cols_part<DT>(p, (int)blockIdx.x - stat_blocks, (int)gridDim.x - stat_blocks);
 }
 
 template <int DT>
@@ -433,9 +469,14 @@ __global__ __launch_bounds__(256) void act_fwd_dense_kernel(const void* z, void*
 
 // The rank-r activations of a block's layers, rebuilt from the checkpoints in one launch (a launch per layer is
 // what a small block waits for: four of 2.4 us at 512 tokens): sigma(z), or z + h_{i-1} where the LaX variant
-// hands an h.  Workgroups [first[i], first[i + 1]) take segment i.
+// hands an h.  Workgroups [first[i], first[i + 1]) take segment i; those from `act_blocks` on fold the norms' gammas into the
+// weights of the call (512 tokens, rank 64, 256 features: 4.2 + 2.4 -> 3.9 us).
 template <int U>
-__global__ __launch_bounds__(256) void act_layers_kernel(ActLayers p, int act) {
+__global__ __launch_bounds__(256) void act_layers_kernel(ActLayers p, int act, int act_blocks, ScaleCols fold) {
+  if ((int)blockIdx.x >= act_blocks) {
+    scale_cols_part<LR_BF16>(fold, (int)blockIdx.x - act_blocks, (int)gridDim.x - act_blocks);
+    return;
+  }
   constexpr int64_t CHUNK = 256 * U * 16;
   int i = 0;
   while (i + 1 < p.n && (int)blockIdx.x >= p.first[i + 1]) i++;
@@ -527,11 +568,17 @@ __global__ __launch_bounds__(256) void swiglu_bwd_dense_kernel(const void* g, co
 // x[rows, ld], head h in columns 128 h ..; the pair (v[i], v[i + 64]) of the row at position p = row % S
 // is turned by the angle whose cosine and sine the caller tabulated as cs[p, i], sn[p, i] ([S, 64] fp32).
 // One lane owns 8 consecutive i of one head: two 16-byte loads, two 16-byte stores.  sgn = -1 applies the
-// transpose (the backward of the rotation).
-__global__ __launch_bounds__(256) void rope128_kernel(uint16_t* x, int64_t ld, const float* __restrict__ cs,
-                                                      const float* __restrict__ sn, int64_t rows, int S, int H, float sgn) {
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= rows * H * 8) return;
+// transpose (the backward of the rotation).  x1, ld1, H1: a second tensor of as many rows, the keys beside the queries (H1 = 0: none;
+// 777 rows, 32 and 8 heads: 5.1 + 4.6 -> 5.6 us).
+__global__ __launch_bounds__(256) void rope128_kernel(uint16_t* x, int64_t ld, int H, uint16_t* x1, int64_t ld1, int H1,
+                                                      const float* __restrict__ cs, const float* __restrict__ sn, int64_t rows, int S,
+                                                      float sgn) {
+  int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (idx >= rows * H * 8) {
+    idx -= rows * H * 8;
+    x = x1; ld = ld1; H = H1;
+    if (idx >= rows * H * 8) return;
+  }
   const int c8 = (int)(idx & 7) * 8;
   const int64_t rh = idx >> 3;
   const int h = (int)(rh % H);
@@ -656,26 +703,6 @@ __global__ __launch_bounds__(256) void rowdot_kernel(const void* a, int64_t lda,
   }
   s = wave_sum(s);
   if (lane == 0) out[row] = s;
-}
-
-// One or two matrices of equal width (rows1 = 0: one): a block folds both of its norms' gammas in one launch.
-template <int DT>
-__global__ __launch_bounds__(256) void scale_cols_kernel(const void* w0, const void* gamma0, void* out0, int64_t rows0, const void* w1,
-                                                         const void* gamma1, void* out1, int64_t rows1, int64_t cols) {
-  using S = St<DT>;
-  using IO = VecIO<typename S::T, S::NV>;
-  const int64_t cpr = cols / S::NV, total0 = rows0 * cpr, total = total0 + rows1 * cpr;
-  for (int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x; j < total; j += (int64_t)gridDim.x * 256) {
-    const bool second = j >= total0;
-    const int64_t i = second ? j - total0 : j;
-    const int64_t c = (i % cpr) * S::NV, off = (i / cpr) * cols + c;
-    float wv[S::NV], gv[S::NV];
-    IO::load(second ? w1 : w0, off, wv);
-    IO::load(second ? gamma1 : gamma0, c, gv);
-#pragma unroll
-    for (int k = 0; k < S::NV; k++) wv[k] *= gv[k];
-    IO::store(second ? out1 : out0, off, wv);
-  }
 }
 
 // ---- finish a split-K weight gradient ------------------------------------------------------------
@@ -822,6 +849,69 @@ __global__ __launch_bounds__(256) void wgrad_finish_narrow_kernel(const float* p
     dgpart[(int64_t)blockIdx.y * cols + c0 + tid] = sclass[tid] + sclass[W + tid] + sclass[2 * W + tid] + sclass[3 * W + tid];
 }
 
+// The whole pass behind a norm, dgamma included, where a gradient has few rows: a workgroup takes 32 columns of all of them, the
+// partials of 32 rows stay in LDS and are added up there, in the order of the two kernels that otherwise share the work.  Bound by its
+// way in and out like those, of which it saves one (128 x 256 and its dgamma 4.1 + 2.6 -> 4.7 us, 192 x 1024 1 us less; but 504 x 512,
+// whose rows follow each other in 16 workgroups, 5 us more).
+constexpr int WHOLE_ROWS = 256, WHOLE_COLS = 1024;
+template <int DT, typename OT>
+__global__ __launch_bounds__(256) void wgrad_finish_whole_kernel(const float* part, int nsplit, int64_t rows, int64_t cols, void* dw,
+                                                                 const void* colscale, const void* wdg, void* dgamma, int accumulate) {
+  constexpr int NV = St<DT>::NV, W = 32, VS = W / NV, CH = 128;
+  using IO = VecIO<typename St<DT>::T, NV>;
+  using OIO = VecIO<OT, 1>;
+  __shared__ float ssum[CH * W], sw[CH * W], sclass[CH / WF_RB * 4 * W], spart[WHOLE_ROWS / WF_RB * W];
+  const int tid = threadIdx.x, v = tid % VS;
+  const int64_t count = rows * cols, c0 = (int64_t)blockIdx.x * W, c = c0 + v * NV;
+  float cs[NV];
+#pragma unroll
+  for (int i = 0; i < NV; i++) cs[i] = 1.f;
+  if (c < cols && colscale) IO::load(colscale, c, cs);
+  for (int r0 = 0; r0 < (int)rows; r0 += CH) {
+    const int nrows = min(CH, (int)rows - r0);
+    if (c < cols)
+      for (int rr = tid / VS; rr < nrows; rr += 256 / VS) {
+        const int64_t off = (int64_t)(r0 + rr) * cols + c;
+        float s[NV], wv[NV];
+        IO::load(wdg, off, wv);
+        switch (nsplit) {
+          case 1: finish_vector<DT, OT, 1>(part, nsplit, count, off, cs, dw, accumulate, s); break;
+          case 2: finish_vector<DT, OT, 2>(part, nsplit, count, off, cs, dw, accumulate, s); break;
+          case 4: finish_vector<DT, OT, 4>(part, nsplit, count, off, cs, dw, accumulate, s); break;
+          default: finish_vector<DT, OT, 0>(part, nsplit, count, off, cs, dw, accumulate, s); break;
+        }
+#pragma unroll
+        for (int i = 0; i < NV; i++) {
+          ssum[rr * W + v * NV + i] = s[i];
+          sw[rr * W + v * NV + i] = wv[i];
+        }
+      }
+    __syncthreads();
+    for (int i = tid; i < CH / WF_RB * 4 * W; i += 256) {
+      const int col = i % W, first = i / (4 * W) * WF_RB, last = min(nrows, first + WF_RB);
+      float dg = 0.f;
+      if (c0 + col < cols)
+        for (int rr = first + i / W % 4; rr < last; rr += 4) dg = fmaf(sw[rr * W + col], ssum[rr * W + col], dg);
+      sclass[i] = dg;
+    }
+    __syncthreads();
+    for (int i = tid; i < CH / WF_RB * W; i += 256) {
+      const float* q = sclass + i / W * 4 * W + i % W;
+      if (r0 / WF_RB + i / W < WHOLE_ROWS / WF_RB) spart[r0 / WF_RB * W + i] = q[0] + q[W] + q[2 * W] + q[3 * W];
+    }
+  }
+  __syncthreads();
+  if (tid >= W || c0 + tid >= cols) return;
+  float s = 0.f;
+  for (int p = 0; p < (int)((rows + WF_RB - 1) / WF_RB); p++) s += spart[p * W + tid];
+  if (accumulate) {
+    float o;
+    OIO::load(dgamma, c0 + tid, &o);
+    s += o;
+  }
+  OIO::store(dgamma, c0 + tid, &s);
+}
+
 // Several gradients in one launch, one thread per vector as above.  Bound by launches: a gradient of a small or mid-sized
 // block is some hundred KB, whose pass takes 4 us of which most is the way in and out, and a backward has nine.
 struct FinishMany {
@@ -896,6 +986,10 @@ inline int grid1d(int64_t total, int cap = 256 * 32) {
   if (g > cap) g = cap;
   if (g < 1) g = 1;
   return (int)g;
+}
+inline unsigned scale_blocks(const ScaleCols& p, int dt) {
+  if (p.rows0 + p.rows1 <= 0 || p.cols <= 0) return 0;
+  return (unsigned)grid1d((p.rows0 + p.rows1) * (p.cols / (dt == LR_BF16 ? 8 : 1)));
 }
 
 }  // namespace
@@ -975,22 +1069,24 @@ hipError_t k_act_fwd(const void* z, int64_t ldz, void* a, int64_t lda, int64_t T
   const int nv = dt == LR_BF16 ? 8 : 1;
   DISPATCH_DT(dt, act_fwd_kernel, dim3(grid_chunks(T * (n / nv), 256 * EW_U)), dim3(256), st, z, ldz, a, lda, T, n, act);
 }
-hipError_t k_rope128_bf16(void* x, int64_t ld, const float* cos_tab, const float* sin_tab, int64_t rows, int S, int H,
-                          int inverse, hipStream_t st) {
+hipError_t k_rope128_bf16(void* x, int64_t ld, int H, void* x1, int64_t ld1, int H1, const float* cos_tab, const float* sin_tab,
+                          int64_t rows, int S, int inverse, hipStream_t st) {
   if (rows <= 0 || H <= 0) return hipSuccess;
-  const int64_t items = rows * H * 8;
-  hipLaunchKernelGGL(rope128_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, (uint16_t*)x, ld, cos_tab,
-                     sin_tab, rows, S, H, inverse ? -1.f : 1.f);
+  const int64_t items = rows * (H + H1) * 8;
+  hipLaunchKernelGGL(rope128_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, (uint16_t*)x, ld, H, (uint16_t*)x1, ld1, H1,
+                     cos_tab, sin_tab, rows, S, inverse ? -1.f : 1.f);
   return hipGetLastError();
 }
-hipError_t k_act_layers_bf16(ActLayers p, int act, hipStream_t st) {
+hipError_t k_act_layers_bf16(ActLayers p, int act, const ScaleCols* fold, hipStream_t st) {
   unsigned grid = 0;
   for (int i = 0; i < p.n; i++) {
     p.first[i] = (int)grid;
     grid += grid_chunks(p.bytes[i] / 16, 256 * DENSE_U);
   }
+  const int act_blocks = (int)grid;
+  if (fold) grid += scale_blocks(*fold, LR_BF16);
   if (grid == 0) return hipSuccess;
-  hipLaunchKernelGGL(act_layers_kernel<DENSE_U>, dim3(grid), dim3(256), 0, st, p, act);
+  hipLaunchKernelGGL(act_layers_kernel<DENSE_U>, dim3(grid), dim3(256), 0, st, p, act, act_blocks, fold ? *fold : ScaleCols{});
   return hipGetLastError();
 }
 hipError_t k_swiglu_fwd(const void* g, const void* u, void* m, int64_t ld, int64_t T, int64_t f, int dt,
@@ -1044,24 +1140,37 @@ hipError_t k_rowdot(const void* a, int64_t lda, const void* b, int64_t ldb, floa
   if (M <= 0) return hipSuccess;
   DISPATCH_DT(dt, rowdot_kernel, dim3((M + 3) / 4), dim3(256), st, a, lda, b, ldb, out, M, N);
 }
-hipError_t k_scale_cols(const void* w, const void* gamma, void* wout, int64_t rows, int64_t cols, int dt,
-                        hipStream_t st) {
-  return k_scale_cols2(w, gamma, wout, rows, nullptr, nullptr, nullptr, 0, cols, dt, st);
+hipError_t k_scale_cols(const ScaleCols& p, int dt, hipStream_t st) {
+  const unsigned blocks = scale_blocks(p, dt);
+  if (!blocks) return hipSuccess;
+  DISPATCH_DT(dt, scale_cols_kernel, dim3(blocks), dim3(256), st, p);
 }
-hipError_t k_scale_cols2(const void* w0, const void* gamma0, void* out0, int64_t rows0, const void* w1, const void* gamma1,
-                         void* out1, int64_t rows1, int64_t cols, int dt, hipStream_t st) {
-  if (rows0 + rows1 <= 0 || cols <= 0) return hipSuccess;
-  const int nv = dt == LR_BF16 ? 8 : 1;
-  DISPATCH_DT(dt, scale_cols_kernel, dim3(grid1d((rows0 + rows1) * (cols / nv))), dim3(256), st, w0, gamma0, out0, rows0, w1, gamma1,
-              out1, rows1, cols);
+hipError_t k_scale_cols_rms_stat(const ScaleCols& p, const void* x, int64_t ldx, float* stat, int64_t T, int64_t d, int dt, hipStream_t st) {
+  const unsigned blocks = scale_blocks(p, dt), stat_blocks = T > 0 ? (unsigned)((T + 3) / 4) : 0;
+  if (!blocks || !stat_blocks) {
+    const hipError_t e = k_scale_cols(p, dt, st);
+    return e != hipSuccess ? e : k_rms_stat(x, ldx, stat, T, d, dt, st);
+  }
+  DISPATCH_DT(dt, scale_cols_rms_stat_kernel, dim3(stat_blocks + blocks), dim3(256), st, p, (int)stat_blocks, x, ldx, stat, T, d);
 }
 int64_t k_wgrad_dgamma_parts(int64_t rows) { return (rows + WF_RB - 1) / WF_RB; }
 hipError_t k_wgrad_finish(const float* part, int nsplit, int64_t rows, int64_t cols, void* dw, const void* colscale,
-                          const void* w_for_dgamma, float* dgamma_part, int accumulate, int dt, int out_dt,
+                          const void* w_for_dgamma, float* dgamma_part, void* dgamma, int accumulate, int dt, int out_dt,
                           hipStream_t st) {
   if (rows <= 0 || cols <= 0) return hipSuccess;
   const int nv = dt == LR_BF16 ? 8 : 1;
   const bool dg = w_for_dgamma != nullptr && dgamma_part != nullptr;
+  if (dg && rows <= WHOLE_ROWS && cols <= WHOLE_COLS && (dt == LR_BF16 || out_dt == LR_F32)) {
+    const dim3 grid((unsigned)((cols + 31) / 32));
+#define LRB_WHOLE(DT_, OT_)                                                                                                         \
+  hipLaunchKernelGGL((wgrad_finish_whole_kernel<DT_, OT_>), grid, dim3(256), 0, st, part, nsplit, rows, cols, dw, colscale, w_for_dgamma, \
+                     dgamma, accumulate)
+    if (dt == LR_F32) LRB_WHOLE(LR_F32, float);
+    else if (out_dt == LR_F32) LRB_WHOLE(LR_BF16, float);
+    else LRB_WHOLE(LR_BF16, bf16_t);
+#undef LRB_WHOLE
+    return hipGetLastError();
+  }
   const int64_t blocks = (rows + WF_RB - 1) / WF_RB;
   // narrow strips where 64-vector ones would leave CUs without two workgroups (3072 x 512, five splits: 96 workgroups
   // took 20 us; 3072 x 4096: 768 workgroups read at 5.4 TB/s)
@@ -1097,7 +1206,8 @@ hipError_t k_wgrad_finish(const float* part, int nsplit, int64_t rows, int64_t c
   else LRB_WF(LR_BF16, bf16_t);
 #undef LRB_WF
 #undef LRB_WF2
-  return hipGetLastError();
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess || !dg ? e : k_colsum_parts(dgamma_part, blocks, cols, dgamma, accumulate, out_dt, st);
 }
 hipError_t k_wgrad_finish_many(const FinishJob* jobs, int n, int accumulate, int out_dt, hipStream_t st) {
   if (n <= 0) return hipSuccess;
