@@ -114,7 +114,7 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 const void* kmajor_to_kcontig(Ctx& c, const void* in, int64_t ld_in, int64_t k_rows, int64_t n_cols, int64_t& ld_out) {
   ld_out = rup(k_rows, 8);
   void* out = c.take((size_t)n_cols * ld_out * esize(c.dt));
-  LAUNCH(c, k_transpose(in, ld_in, out, ld_out, k_rows, n_cols, c.dt, c.st));
+  LAUNCH(c, k_transpose(in, ld_in, 0, out, ld_out, 0, k_rows, n_cols, 1, c.dt, c.st));
   return out;
 }
 
@@ -151,9 +151,7 @@ void gemm(Ctx& c, GemmOp op) {
   if (op.transB) {
     int64_t ld = rup(op.K, 8);
     void* out = c.take((size_t)op.batch * op.N * ld * esize(c.dt));
-    for (int b = 0; b < op.batch; b++)
-      LAUNCH(c, k_transpose((const char*)op.B + (size_t)b * op.sB * esize(c.dt), op.ldb,
-                            (char*)out + (size_t)b * op.N * ld * esize(c.dt), ld, op.K, op.N, c.dt, c.st));
+    LAUNCH(c, k_transpose(op.B, op.ldb, op.sB, out, ld, (int64_t)op.N * ld, op.K, op.N, op.batch, c.dt, c.st));
     op.B = out;
     op.ldb = ld;
     op.sB = (int64_t)op.N * ld;

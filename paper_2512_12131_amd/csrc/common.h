@@ -193,9 +193,9 @@ struct ActLayers {
 hipError_t k_act_layers_bf16(ActLayers p, int act, const ScaleCols* fold, hipStream_t);
 hipError_t k_swiglu_bwd(const void* g, const void* u, const void* dm, void* dg, void* du, int64_t ld,
                         int64_t T, int64_t f, int dt, hipStream_t);
-// out[r, c] = in[c, r] for in[rows, cols] (ld_in) -> out[cols, rows] (ld_out)
-hipError_t k_transpose(const void* in, int64_t ld_in, void* out, int64_t ld_out, int64_t rows,
-                       int64_t cols, int dt, hipStream_t);
+// out[r, c] = in[c, r] for n matrices in[rows, cols] (ld_in) -> out[cols, rows] (ld_out), s_in and s_out elements apart
+hipError_t k_transpose(const void* in, int64_t ld_in, int64_t s_in, void* out, int64_t ld_out, int64_t s_out, int64_t rows, int64_t cols,
+                       int n, int dt, hipStream_t);
 // out[m] = sum of the row partials of `members` batch members (each rp.slabs columns of part[m, :])
 hipError_t k_rowsum_parts(const float* part, int64_t ld, int members, const RowParts& rp, float* out, int64_t M, hipStream_t);
 // out[m] = sum_n a[m,n] * b[m,n]

@@ -640,7 +640,9 @@ int gemm_bf16_tile(const GemmOp& op) {
   const float e = epi_traffic(op);
   const bool km = op.transA && op.transB;
   float best = dual ? 1e30f : tile_time(GEMM_T256, op.M, op.N, nk, op.batch, e, km ? kKMajorSlice[GEMM_T256] : 1.f);
-  // T256 with a k-major weight first writes a transposed copy: one launch per batch member
+  // T256 with a k-major weight first writes a transposed copy, of all batch members in one launch (three of 1024 x 512: 14.4 us as
+  // three, 5.0 as one).  Its price is that of a launch per member: without it three of 512 x 2048 under 16384 tokens came out even
+  // (157 us with the copy, 157 on R128) for a launch more.
   if (op.transB && !op.transA) best += (float)op.batch * (2.5f + (float)op.N * (float)op.K * (4.f / 4e6f));
   int tile = GEMM_T256;
   if (km) {

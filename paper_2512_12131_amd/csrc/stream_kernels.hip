@@ -608,9 +608,10 @@ __global__ __launch_bounds__(256) void rope128_kernel(uint16_t* x, int64_t ld, i
 // are written as zeros, so a transposed activation can serve as a k-contiguous GEMM operand whose
 // k extent is rounded up to the 16-byte vector.
 template <typename E>
-__global__ __launch_bounds__(256) void transpose_kernel(const E* in, int64_t ld_in, E* out, int64_t ld_out,
+__global__ __launch_bounds__(256) void transpose_kernel(const E* in, int64_t ld_in, int64_t s_in, E* out, int64_t ld_out, int64_t s_out,
                                                         int64_t rows, int64_t cols, int64_t pad_to) {
   __shared__ E tile[64][64 + 2];
+  in += blockIdx.z * s_in; out += blockIdx.z * s_out;
   const int64_t r0 = (int64_t)blockIdx.y * 64, c0 = (int64_t)blockIdx.x * 64;
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
   for (int i = ty; i < 64; i += 4) {
@@ -630,9 +631,10 @@ __global__ __launch_bounds__(256) void transpose_kernel(const E* in, int64_t ld_
 // 16-bit elements, all extents and pitches multiples of 8: global accesses are 16-byte vectors on both
 // sides (a 2-byte-per-lane access moves 128 bytes per wavefront instruction, a 16-byte one 1 KB); the
 // element shuffle happens between LDS and registers.  Tile: 64 input rows x 64 input columns.
-__global__ __launch_bounds__(256) void transpose16_vec_kernel(const uint16_t* in, int64_t ld_in, uint16_t* out,
-                                                              int64_t ld_out, int64_t rows, int64_t cols, int64_t pad_to) {
+__global__ __launch_bounds__(256) void transpose16_vec_kernel(const uint16_t* in, int64_t ld_in, int64_t s_in, uint16_t* out, int64_t ld_out,
+                                                              int64_t s_out, int64_t rows, int64_t cols, int64_t pad_to) {
   __shared__ uint16_t tile[64][64 + 8];   // pitch 144 bytes: 16-byte aligned rows, column walks spread over banks
+  in += blockIdx.z * s_in; out += blockIdx.z * s_out;
   const int64_t r0 = (int64_t)blockIdx.y * 64, c0 = (int64_t)blockIdx.x * 64;
   const int t = threadIdx.x;
 #pragma unroll
@@ -1111,21 +1113,21 @@ hipError_t k_swiglu_bwd(const void* g, const void* u, const void* dm, void* dg, 
   const int nv = dt == LR_BF16 ? 8 : 1;
   DISPATCH_DT(dt, swiglu_bwd_kernel, dim3(grid_chunks(T * (f / nv), 256 * EW_U3)), dim3(256), st, g, u, dm, dg, du, ld, T, f);
 }
-hipError_t k_transpose(const void* in, int64_t ld_in, void* out, int64_t ld_out, int64_t rows, int64_t cols, int dt,
-                       hipStream_t st) {
-  if (rows <= 0 || cols <= 0) return hipSuccess;
+hipError_t k_transpose(const void* in, int64_t ld_in, int64_t s_in, void* out, int64_t ld_out, int64_t s_out, int64_t rows, int64_t cols,
+                       int n, int dt, hipStream_t st) {
+  if (rows <= 0 || cols <= 0 || n <= 0) return hipSuccess;
   const int64_t pad_to = ld_out;  // the whole output row is owned by the destination buffer
-  dim3 grid((cols + 63) / 64, (pad_to + 63) / 64);
+  dim3 grid((cols + 63) / 64, (pad_to + 63) / 64, n);
   if (dt == LR_F32)
-    hipLaunchKernelGGL(transpose_kernel<float>, grid, dim3(256), 0, st, (const float*)in, ld_in, (float*)out, ld_out,
+    hipLaunchKernelGGL(transpose_kernel<float>, grid, dim3(256), 0, st, (const float*)in, ld_in, s_in, (float*)out, ld_out, s_out,
                        rows, cols, pad_to);
   else if (rows % 8 == 0 && cols % 8 == 0 && ld_in % 8 == 0 && ld_out % 8 == 0 && ((uintptr_t)in & 15) == 0 &&
-           ((uintptr_t)out & 15) == 0)
-    hipLaunchKernelGGL(transpose16_vec_kernel, grid, dim3(256), 0, st, (const uint16_t*)in, ld_in, (uint16_t*)out, ld_out,
+           ((uintptr_t)out & 15) == 0 && (n == 1 || (s_in % 8 == 0 && s_out % 8 == 0)))
+    hipLaunchKernelGGL(transpose16_vec_kernel, grid, dim3(256), 0, st, (const uint16_t*)in, ld_in, s_in, (uint16_t*)out, ld_out, s_out,
                        rows, cols, pad_to);
   else
-    hipLaunchKernelGGL(transpose_kernel<uint16_t>, grid, dim3(256), 0, st, (const uint16_t*)in, ld_in, (uint16_t*)out,
-                       ld_out, rows, cols, pad_to);
+    hipLaunchKernelGGL(transpose_kernel<uint16_t>, grid, dim3(256), 0, st, (const uint16_t*)in, ld_in, s_in, (uint16_t*)out, ld_out, s_out,
+                       rows, cols, pad_to);
   return hipGetLastError();
 }
 hipError_t k_rowsum_parts(const float* part, int64_t ld, int members, const RowParts& rp, float* out, int64_t M,
