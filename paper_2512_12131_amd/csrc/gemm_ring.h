@@ -23,8 +23,8 @@
 //
 // EPI_SWIGLU_DUAL walks the gate's product and then the up product in one stream of stages: the gate's accumulators wait as bf16
 // pairs (half of the registers; what the epilogue would read back from memory), and g never leaves the chip where nobody wants it.
-// Bound: the d_ff wide stores (16384 x 11008, k = 128: g, then u with the epilogue 112 + 221 us, together 160; with g and u stored
-// 110 + 290 -> 345).
+// Bound: the d_ff wide stores and the epilogue (16384 x 11008, k = 128, inside a block: g, then u with the epilogue 113 + 216 us,
+// together 219, and 197 as a stream of tiles; with g and u stored 111 + 287 -> 292).
 //
 // Operand forms: k-contiguous (p[i*ld + k]) or k-major (p[k*ld + i]) for A and B independently; the k-major
 // side is read through the LDS transpose read, so a data-gradient product needs no transposed weight copy.
