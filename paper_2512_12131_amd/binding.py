@@ -173,6 +173,18 @@ def _rowmajor(t: torch.Tensor):
     return t.stride(0)
 
 
+def _rowmajor_all(t: torch.Tensor, *others):
+    """The row stride of t, passed for the others too (of a single row any will do)."""
+    ld = _rowmajor(t)
+    assert all(_rowmajor(o) == ld or t.shape[0] <= 1 >= o.shape[0] for o in others), "operands with the same row stride expected"
+    return ld
+
+
+def _rows_like(t: torch.Tensor):
+    """An output that is written with the row stride of t."""
+    return torch.empty_strided(t.shape, t.stride(), dtype=t.dtype, device=t.device)
+
+
 # ---- one bottleneck layer ------------------------------------------------------------------
 def lr_linear_workspace_bytes(T, d_in, r, d_out, dt, backward):
     return lib().lr_linear_workspace_bytes(T, d_in, r, d_out, dt, int(backward))
@@ -404,18 +416,20 @@ def lr_rope(x, cos, sin, B, S, H, hd, inverse=False):
 
 # ---- attention -----------------------------------------------------------------------------
 def lr_attention_fwd(q, k, v, B, S, H, hd, causal=True):
-    o = torch.empty_like(q)
+    ld = _rowmajor_all(q, k, v)
+    o = _rows_like(q)
     lse = torch.empty((B, H, S), dtype=torch.float32, device=q.device)
-    _check(lib().lr_attention_fwd(_p(q), _p(k), _p(v), _p(o), _p(lse), _rowmajor(q), B, S, H, hd, int(causal), _dt(q),
+    _check(lib().lr_attention_fwd(_p(q), _p(k), _p(v), _p(o), _p(lse), ld, B, S, H, hd, int(causal), _dt(q),
                                   _stream()), "lr_attention_fwd")
     return o, lse
 
 
 def lr_attention_bwd(q, k, v, o, dout, lse, B, S, H, hd, causal=True):
-    dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
+    ld = _rowmajor_all(q, k, v, o, dout)
+    dq, dk, dv = _rows_like(q), _rows_like(k), _rows_like(v)
     nb = lib().lr_attention_bwd_workspace_bytes(B, S, H, hd)
     ws = _ws(nb, q.device)
-    _check(lib().lr_attention_bwd(_p(q), _p(k), _p(v), _p(o), _p(dout), _p(lse), _p(dq), _p(dk), _p(dv), _rowmajor(q),
+    _check(lib().lr_attention_bwd(_p(q), _p(k), _p(v), _p(o), _p(dout), _p(lse), _p(dq), _p(dk), _p(dv), ld,
                                   B, S, H, hd, int(causal), _dt(q), _p(ws), ws.numel(), _stream()), "lr_attention_bwd")
     return dq, dk, dv
 

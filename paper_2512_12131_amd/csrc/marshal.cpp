@@ -70,6 +70,13 @@ int64_t stride_of(const at::Tensor& t) {
   if (t.dim() != 2 || t.stride(1) != 1) fail(PyExc_AssertionError, "row-major 2-D tensor expected");
   return t.stride(0);
 }
+// The row stride of t, passed for the others too (of a single row any will do).
+int64_t stride_of_all(const at::Tensor& t, std::initializer_list<const at::Tensor*> others) {
+  const int64_t ld = stride_of(t);
+  for (const at::Tensor* o : others)
+    if (stride_of(*o) != ld && (t.size(0) > 1 || o->size(0) > 1)) fail(PyExc_AssertionError, "operands with the same row stride expected");
+  return ld;
+}
 int64_t size_of(const at::Tensor& t, int64_t i) {
   if (t.dim() <= i) fail(PyExc_IndexError, "tuple index out of range");
   return t.size(i);
@@ -78,6 +85,8 @@ void* ptr(const at::Tensor& t) { return t.defined() ? t.data_ptr() : nullptr; }
 at::Tensor fresh(at::IntArrayRef sizes, at::ScalarType dt, const at::Tensor& like) {
   return at::empty(sizes, at::TensorOptions().dtype(dt).device(like.device()));
 }
+// an output that is written with the row stride of t
+at::Tensor rows_like(const at::Tensor& t) { return at::empty_strided(t.sizes(), t.strides(), t.options()); }
 at::Tensor workspace(size_t bytes, const at::Tensor& like) {
   return fresh({(int64_t)(bytes < 256 ? 256 : bytes)}, at::kByte, like);
 }
@@ -216,11 +225,9 @@ PyObject* attention_fwd(Args& a) {
   const at::Tensor &q = a.tensor(), &k = a.tensor(), &v = a.tensor();
   const int64_t B = a.integer(), S = a.integer(), H = a.integer(), Hkv = a.integer(), hd = a.integer();
   const int causal = a.enumerator();
-  const at::Tensor o = at::empty_like(q), lse = fresh({B, H, S}, at::kFloat, q);
-  const int64_t ldkv = stride_of(k);
-  if (ldkv != stride_of(v)) fail(PyExc_AssertionError, "k and v with the same row stride expected");
-  const int64_t ld = stride_of(q);
+  const int64_t ld = stride_of(q), ldkv = stride_of_all(k, {&v});
   const int dt = dt_of(q);
+  const at::Tensor o = rows_like(q), lse = fresh({B, H, S}, at::kFloat, q);
   void *pq = ptr(q), *pk = ptr(k), *pv = ptr(v), *po = ptr(o), *pl = ptr(lse), *st = stream();
   call("lr_attention_gqa_fwd", [&] { return lr_attention_gqa_fwd(pq, pk, pv, po, (float*)pl, ld, ldkv, B, S, H, Hkv, hd, causal, dt, st); });
   return tuple(o, lse);
@@ -230,12 +237,9 @@ PyObject* attention_bwd(Args& a) {
   const at::Tensor &q = a.tensor(), &k = a.tensor(), &v = a.tensor(), &o = a.tensor(), &dout = a.tensor(), &lse = a.tensor();
   const int64_t B = a.integer(), S = a.integer(), H = a.integer(), Hkv = a.integer(), hd = a.integer();
   const int causal = a.enumerator();
-  const int64_t ldkv = stride_of(k);
-  if (ldkv != stride_of(v)) fail(PyExc_AssertionError, "k and v with the same row stride expected");
-  const at::Tensor dq = at::empty_like(q), dk = at::empty_strided(k.sizes(), k.strides(), k.options()),
-                   dv = at::empty_strided(k.sizes(), k.strides(), k.options());   // rows of ldkv
+  const int64_t ld = stride_of_all(q, {&o, &dout}), ldkv = stride_of_all(k, {&v});
+  const at::Tensor dq = rows_like(q), dk = rows_like(k), dv = rows_like(k);
   const at::Tensor ws = workspace(lr_attention_gqa_bwd_workspace_bytes(B, S, H, Hkv, hd), q);
-  const int64_t ld = stride_of(q);
   const size_t nb = (size_t)ws.numel();
   const int dt = dt_of(q);
   void *pq = ptr(q), *pk = ptr(k), *pv = ptr(v), *po = ptr(o), *pdo = ptr(dout), *pl = ptr(lse), *gq = ptr(dq), *gk = ptr(dk), *gv = ptr(dv),
@@ -289,8 +293,8 @@ PyObject* rmsnorm_bwd(Args& a) {
 PyObject* swiglu_fwd(Args& a) {
   const at::Tensor &g = a.tensor(), &u = a.tensor();
   const int64_t T = rows_of(g), f = g.size(1);
-  const at::Tensor m = at::empty_like(g);
-  const int64_t ld = stride_of(g);
+  const int64_t ld = stride_of_all(g, {&u});
+  const at::Tensor m = rows_like(g);
   const int dt = dt_of(g);
   void *pg = ptr(g), *pu = ptr(u), *pm = ptr(m), *st = stream();
   call("lr_swiglu_fwd", [&] { return lr_swiglu_fwd(pg, pu, pm, ld, T, f, dt, st); });
@@ -300,8 +304,8 @@ PyObject* swiglu_fwd(Args& a) {
 PyObject* swiglu_bwd(Args& a) {
   const at::Tensor &g = a.tensor(), &u = a.tensor(), &dm = a.tensor();
   const int64_t T = rows_of(g), f = g.size(1);
-  const at::Tensor dg = at::empty_like(g), du = at::empty_like(u);
-  const int64_t ld = stride_of(g);
+  const int64_t ld = stride_of_all(g, {&u, &dm});
+  const at::Tensor dg = rows_like(g), du = rows_like(u);
   const int dt = dt_of(g);
   void *pg = ptr(g), *pu = ptr(u), *pm = ptr(dm), *gg = ptr(dg), *gu = ptr(du), *st = stream();
   call("lr_swiglu_bwd", [&] { return lr_swiglu_bwd(pg, pu, pm, gg, gu, ld, T, f, dt, st); });

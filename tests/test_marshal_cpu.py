@@ -5,6 +5,7 @@ import torch
 from paper_2512_12131_amd import binding as B
 
 X, WD, WU = torch.zeros(4, 16), torch.zeros(8, 16), torch.zeros(24, 8)
+WIDE = torch.zeros(4, 48)[:, :16]      # rows 48 apart
 
 
 @pytest.mark.parametrize("error,call", [
@@ -20,6 +21,19 @@ X, WD, WU = torch.zeros(4, 16), torch.zeros(8, 16), torch.zeros(24, 8)
 ])
 def test_refused(error, call):
     with pytest.raises(error):
+        call()
+
+
+# One row stride is passed for these operands: rows of any other distance would be read, or written, at wrong places.
+@pytest.mark.parametrize("call", [
+    lambda: B.lr_attention_fwd(X, WIDE, X, 1, 4, 1, 16), lambda: B.lr_attention_fwd(X, X, WIDE, 1, 4, 1, 16),
+    lambda: B.lr_attention_bwd(X, X, X, WIDE, X, X, 1, 4, 1, 16), lambda: B.lr_attention_bwd(X, X, X, X, WIDE, X, 1, 4, 1, 16),
+    lambda: B.lr_attention_gqa_fwd(X, X, WIDE, 1, 4, 1, 1, 16),
+    lambda: B.lr_attention_gqa_bwd(WIDE, X, X, X, WIDE, X, 1, 4, 1, 1, 16), lambda: B.lr_attention_gqa_bwd(WIDE, X, X, WIDE, X, X, 1, 4, 1, 1, 16),
+    lambda: B.lr_swiglu_fwd(WIDE, X), lambda: B.lr_swiglu_bwd(X, WIDE, X), lambda: B.lr_swiglu_bwd(WIDE, WIDE, X),
+])
+def test_operands_of_one_row_stride(call):
+    with pytest.raises(AssertionError):
         call()
 
 
