@@ -160,6 +160,14 @@ def _p(t):
     return None if t is None else t.data_ptr()
 
 
+# of an operand that no stride is passed for
+def _dense(t):
+    if t is None:
+        return None
+    assert t.is_contiguous(), "contiguous tensor expected"
+    return t.data_ptr()
+
+
 def _stream():
     return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
@@ -238,16 +246,16 @@ def make_block_desc(batch, seq, d_model, n_heads, head_dim, ffn, ffn_ld, rank, e
     addresses only: keep the tensors alive while the descriptor is in use (desc._keep does)."""
     cos_p = sin_p = None
     if rope is not None:
-        cos_p, sin_p = rope[0].data_ptr(), rope[1].data_ptr()
+        cos_p, sin_p = _dense(rope[0]), _dense(rope[1])
     desc = BlockDesc(batch, seq, d_model, n_heads, head_dim, ffn, ffn_ld, rank, eps, act, norm, dt, grad_dt, causal,
-                     cos_p, sin_p, int(bool(stat_x_ready)), None if stat_y_out is None else stat_y_out.data_ptr(),
+                     cos_p, sin_p, int(bool(stat_x_ready)), _dense(stat_y_out),
                      int(n_kv_heads))
     desc._keep = (rope, stat_y_out)
     return desc
 
 
 def _params_struct(params: dict):
-    return BlockParams(*[C.c_void_p(params[n].data_ptr()) for n in PARAM_NAMES])
+    return BlockParams(*[C.c_void_p(_dense(params[n])) for n in PARAM_NAMES])
 
 
 def lr_block_workspace_bytes(desc, backward):
@@ -272,7 +280,7 @@ def alloc_block_ckpt(desc, device):
 
 
 def _ckpt_struct(ck: dict):
-    return BlockCkpt(*[C.c_void_p(ck[n].data_ptr()) for n, _ in BlockCkpt._fields_])
+    return BlockCkpt(*[C.c_void_p(_dense(ck[n])) for n, _ in BlockCkpt._fields_])
 
 
 def lr_block_fwd(desc, params: dict, x, ckpt: dict = None, ws=None, y=None):
@@ -287,7 +295,7 @@ def lr_block_fwd(desc, params: dict, x, ckpt: dict = None, ws=None, y=None):
     if ws is None:
         ws = _ws(nb, x.device)
     ps, cs = _params_struct(params), _ckpt_struct(ckpt)
-    _check(lib().lr_block_fwd(C.byref(desc), C.byref(ps), _p(x), _p(y), C.byref(cs), _p(ws), ws.numel(), _stream()),
+    _check(lib().lr_block_fwd(C.byref(desc), C.byref(ps), _dense(x), _dense(y), C.byref(cs), _p(ws), ws.numel(), _stream()),
            "lr_block_fwd")
     return y, ckpt
 
@@ -304,7 +312,7 @@ def lr_block_bwd(desc, params: dict, x, dy, ckpt: dict, grads: dict = None, accu
     if ws is None:
         ws = _ws(nb, x.device)
     ps, cs, gs = _params_struct(params), _ckpt_struct(ckpt), _params_struct(grads)
-    _check(lib().lr_block_bwd(C.byref(desc), C.byref(ps), _p(x), _p(dy), C.byref(cs), _p(dx), C.byref(gs),
+    _check(lib().lr_block_bwd(C.byref(desc), C.byref(ps), _dense(x), _dense(dy), C.byref(cs), _dense(dx), C.byref(gs),
                               int(accumulate), _p(ws), ws.numel(), _stream()), "lr_block_bwd")
     return dx, grads
 
@@ -323,7 +331,7 @@ def alloc_block_saved(desc, device):
 
 
 def _saved_struct(sv: dict):
-    return BlockSaved(*[C.c_void_p(sv[n].data_ptr()) for n, _ in BlockSaved._fields_])
+    return BlockSaved(*[C.c_void_p(_dense(sv[n])) for n, _ in BlockSaved._fields_])
 
 
 def lr_block_fwd_save(desc, params: dict, x, ckpt: dict = None, saved: dict = None, ws=None, y=None):
@@ -336,7 +344,7 @@ def lr_block_fwd_save(desc, params: dict, x, ckpt: dict = None, saved: dict = No
         raise LrError("lr_block_saved_workspace_bytes: invalid or unsupported block descriptor")
     ws = _ws(nb, x.device) if ws is None else ws
     ps, cs, ss = _params_struct(params), _ckpt_struct(ckpt), _saved_struct(saved)
-    _check(lib().lr_block_fwd_save(C.byref(desc), C.byref(ps), _p(x), _p(y), C.byref(cs), C.byref(ss), _p(ws),
+    _check(lib().lr_block_fwd_save(C.byref(desc), C.byref(ps), _dense(x), _dense(y), C.byref(cs), C.byref(ss), _p(ws),
                                    ws.numel(), _stream()), "lr_block_fwd_save")
     return y, ckpt, saved
 
@@ -352,7 +360,7 @@ def lr_block_bwd_saved(desc, params: dict, x, dy, ckpt: dict, saved: dict, grads
         raise LrError("lr_block_saved_workspace_bytes: invalid or unsupported block descriptor")
     ws = _ws(nb, x.device) if ws is None else ws
     ps, cs, gs, ss = _params_struct(params), _ckpt_struct(ckpt), _params_struct(grads), _saved_struct(saved)
-    _check(lib().lr_block_bwd_saved(C.byref(desc), C.byref(ps), _p(x), _p(dy), C.byref(cs), C.byref(ss), _p(dx),
+    _check(lib().lr_block_bwd_saved(C.byref(desc), C.byref(ps), _dense(x), _dense(dy), C.byref(cs), C.byref(ss), _dense(dx),
                                     C.byref(gs), int(accumulate), _p(ws), ws.numel(), _stream()), "lr_block_bwd_saved")
     return dx, grads
 
@@ -363,8 +371,7 @@ def _lax_struct(h_prev=None, dz_next=None, dh_prev=None):
     vals = []
     for d in (h_prev, dz_next, dh_prev):
         for n in LAX_PARTS:
-            t = None if d is None else d.get(n)
-            vals.append(C.c_void_p(None if t is None else t.data_ptr()))
+            vals.append(C.c_void_p(None if d is None else _dense(d.get(n))))
     return BlockLax(*vals)
 
 
@@ -380,7 +387,7 @@ def lr_block_lax_fwd(desc, params: dict, x, h_prev: dict = None, ckpt: dict = No
     if ws is None:
         ws = _ws(nb, x.device)
     ps, cs, lx = _params_struct(params), _ckpt_struct(ckpt), _lax_struct(h_prev)
-    _check(lib().lr_block_lax_fwd(C.byref(desc), C.byref(ps), _p(x), _p(y), C.byref(cs), C.byref(lx), _p(ws),
+    _check(lib().lr_block_lax_fwd(C.byref(desc), C.byref(ps), _dense(x), _dense(y), C.byref(cs), C.byref(lx), _p(ws),
                                   ws.numel(), _stream()), "lr_block_lax_fwd")
     return y, ckpt
 
@@ -402,7 +409,7 @@ def lr_block_lax_bwd(desc, params: dict, x, dy, ckpt: dict, h_prev: dict = None,
         ws = _ws(nb, x.device)
     ps, cs, gs = _params_struct(params), _ckpt_struct(ckpt), _params_struct(grads)
     lx = _lax_struct(h_prev, dz_next, dh)
-    _check(lib().lr_block_lax_bwd(C.byref(desc), C.byref(ps), _p(x), _p(dy), C.byref(cs), _p(dx), C.byref(gs),
+    _check(lib().lr_block_lax_bwd(C.byref(desc), C.byref(ps), _dense(x), _dense(dy), C.byref(cs), _dense(dx), C.byref(gs),
                                   int(accumulate), C.byref(lx), _p(ws), ws.numel(), _stream()), "lr_block_lax_bwd")
     return dx, grads, dh
 
@@ -410,7 +417,7 @@ def lr_block_lax_bwd(desc, params: dict, x, dy, ckpt: dict, h_prev: dict = None,
 # ---- rotary position embedding ----------------------------------------------------------------
 def lr_rope(x, cos, sin, B, S, H, hd, inverse=False):
     """In place on x [B*S, >= H*hd] bf16; cos, sin [S, hd/2] fp32 device tensors.  Returns x."""
-    _check(lib().lr_rope(_p(x), _rowmajor(x), _p(cos), _p(sin), B, S, H, hd, int(inverse), _dt(x), _stream()), "lr_rope")
+    _check(lib().lr_rope(_p(x), _rowmajor(x), _dense(cos), _dense(sin), B, S, H, hd, int(inverse), _dt(x), _stream()), "lr_rope")
     return x
 
 
@@ -429,7 +436,7 @@ def lr_attention_bwd(q, k, v, o, dout, lse, B, S, H, hd, causal=True):
     dq, dk, dv = _rows_like(q), _rows_like(k), _rows_like(v)
     nb = lib().lr_attention_bwd_workspace_bytes(B, S, H, hd)
     ws = _ws(nb, q.device)
-    _check(lib().lr_attention_bwd(_p(q), _p(k), _p(v), _p(o), _p(dout), _p(lse), _p(dq), _p(dk), _p(dv), ld,
+    _check(lib().lr_attention_bwd(_p(q), _p(k), _p(v), _p(o), _p(dout), _dense(lse), _p(dq), _p(dk), _p(dv), ld,
                                   B, S, H, hd, int(causal), _dt(q), _p(ws), ws.numel(), _stream()), "lr_attention_bwd")
     return dq, dk, dv
 
@@ -501,8 +508,8 @@ def lr_shard_down_fwd(x_shard, gamma_shard, eps, w_down_cat_shard):
     stat = torch.empty((T,), dtype=torch.float32, device=x_shard.device)
     nb = lr_group_workspace_bytes(1, T, d_in, GR, 8, dt, 0)
     ws = _ws(nb, x_shard.device)
-    _check(lib().lr_group_fwd(_p(x_shard), _rowmajor(x_shard), _p(gamma_shard), eps, LR_NORM_SHARD_LOCAL,
-                              _p(w_down_cat_shard), None, _p(h), _p(stat), None, 0, 0, 1, T, d_in, GR, 8, LR_ACT_IDENTITY,
+    _check(lib().lr_group_fwd(_p(x_shard), _rowmajor(x_shard), _dense(gamma_shard), eps, LR_NORM_SHARD_LOCAL,
+                              _dense(w_down_cat_shard), None, _p(h), _p(stat), None, 0, 0, 1, T, d_in, GR, 8, LR_ACT_IDENTITY,
                               dt, _p(ws), nb, _stream()), "lr_group_fwd (shard-local)")
     return h, stat
 
@@ -510,7 +517,7 @@ def lr_shard_down_fwd(x_shard, gamma_shard, eps, w_down_cat_shard):
 def lr_online_rmsnorm_finish(h_sum, stat_sum, d_total, eps):
     T, n = h_sum.shape
     z = torch.empty_like(h_sum)
-    _check(lib().lr_online_rmsnorm_finish(_p(h_sum), _rowmajor(h_sum), _p(stat_sum), d_total, eps, _p(z), n, T, n,
+    _check(lib().lr_online_rmsnorm_finish(_p(h_sum), _rowmajor(h_sum), _dense(stat_sum), d_total, eps, _p(z), n, T, n,
                                           _dt(h_sum), _stream()), "lr_online_rmsnorm_finish")
     return z
 

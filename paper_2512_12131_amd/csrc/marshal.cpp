@@ -82,6 +82,11 @@ int64_t size_of(const at::Tensor& t, int64_t i) {
   return t.size(i);
 }
 void* ptr(const at::Tensor& t) { return t.defined() ? t.data_ptr() : nullptr; }
+// of an operand that no stride is passed for
+void* dense(const at::Tensor& t) {
+  if (t.defined() && !t.is_contiguous()) fail(PyExc_AssertionError, "contiguous tensor expected");
+  return ptr(t);
+}
 at::Tensor fresh(at::IntArrayRef sizes, at::ScalarType dt, const at::Tensor& like) {
   return at::empty(sizes, at::TensorOptions().dtype(dt).device(like.device()));
 }
@@ -130,7 +135,7 @@ PyObject* linear_fwd(Args& a) {
   const size_t nb = lr_linear_workspace_bytes(T, d, r, n, dt, 0);
   const at::Tensor ws = workspace(nb, x);
   const int64_t ldx = stride_of(x);
-  void *px = ptr(x), *pd = ptr(wd), *pu = ptr(wu), *pz = ptr(z), *py = ptr(y), *pw = ptr(ws), *st = stream();
+  void *px = ptr(x), *pd = dense(wd), *pu = dense(wu), *pz = ptr(z), *py = ptr(y), *pw = ptr(ws), *st = stream();
   call("lr_linear_fwd", [&] { return lr_linear_fwd(px, ldx, pd, pu, pz, py, n, T, d, r, n, act, dt, pw, nb, st); });
   return tuple(z, y);
 }
@@ -144,7 +149,7 @@ PyObject* linear_fwd_static(Args& a) {
     fail(PyExc_AssertionError, "contiguous z [T, r] and y [T, d_out] expected");
   const int64_t ldx = stride_of(x);
   const int dt = dt_of(x);
-  void *px = ptr(x), *pd = ptr(wd), *pu = ptr(wu), *pz = ptr(z), *py = ptr(y), *st = stream();
+  void *px = ptr(x), *pd = dense(wd), *pu = dense(wu), *pz = ptr(z), *py = ptr(y), *st = stream();
   call("lr_linear_fwd_static", [&] { return lr_linear_fwd_static(px, ldx, pd, pu, pz, py, n, T, d, r, n, act, dt, st); });
   return tuple(z, y);
 }
@@ -163,7 +168,7 @@ PyObject* linear_bwd(Args& a) {
   const size_t nb = lr_linear_workspace_bytes(T, d, r, n, dt, 1);
   const at::Tensor ws = workspace(nb, x);
   const int64_t ldx = stride_of(x), lddy = stride_of(dy);
-  void *px = ptr(x), *pd = ptr(wd), *pu = ptr(wu), *pz = ptr(z), *py = ptr(dy), *pdx = ptr(dx), *gd = ptr(dwd), *gu = ptr(dwu),
+  void *px = ptr(x), *pd = dense(wd), *pu = dense(wu), *pz = dense(z), *py = ptr(dy), *pdx = ptr(dx), *gd = dense(dwd), *gu = dense(dwu),
        *pw = ptr(ws), *st = stream();
   call("lr_linear_bwd", [&] { return lr_linear_bwd(px, ldx, pd, pu, pz, py, lddy, pdx, d, gd, gu, T, d, r, n, act, dt, gdt, acc, pw, nb, st); });
   return tuple(dx, dwd, dwu);
@@ -182,7 +187,7 @@ PyObject* group_fwd(Args& a) {
   const size_t nb = lr_group_workspace_bytes((int)G, T, d, r, n, dt, 0);
   const at::Tensor ws = workspace(nb, x);
   const int64_t ldx = stride_of(x);
-  void *px = ptr(x), *pg = ptr(gamma), *pd = ptr(wd), *pu = ptr(wu), *pz = ptr(z), *ps = ptr(stat), *py = ptr(y), *pw = ptr(ws), *st = stream();
+  void *px = ptr(x), *pg = dense(gamma), *pd = dense(wd), *pu = dense(wu), *pz = ptr(z), *ps = dense(stat), *py = ptr(y), *pw = ptr(ws), *st = stream();
   call("lr_group_fwd", [&] {
     return lr_group_fwd(px, ldx, pg, eps, norm, pd, pu, pz, (float*)ps, py, n, T * n, (int)G, T, d, r, n, act, dt, pw, nb, st);
   });
@@ -211,8 +216,8 @@ PyObject* group_bwd(Args& a) {
   const size_t nb = lr_group_workspace_bytes((int)G, T, d, r, n, dt, 1);
   const at::Tensor ws = workspace(nb, x);
   const int64_t ldx = stride_of(x);
-  void *px = ptr(x), *pg = ptr(gamma), *pd = ptr(wd), *pu = ptr(wu), *pz = ptr(z), *ps = ptr(stat), *py = ptr(dy), *pdx = ptr(dx),
-       *gg = ptr(dgamma), *gd = ptr(dwd), *gu = ptr(dwu), *pw = ptr(ws), *st = stream();
+  void *px = ptr(x), *pg = dense(gamma), *pd = dense(wd), *pu = dense(wu), *pz = dense(z), *ps = dense(stat), *py = dense(dy), *pdx = ptr(dx),
+       *gg = dense(dgamma), *gd = dense(dwd), *gu = dense(dwu), *pw = ptr(ws), *st = stream();
   call("lr_group_bwd", [&] {
     return lr_group_bwd(px, ldx, pg, eps, norm, pd, pu, pz, (const float*)ps, py, n, T * n, pdx, d, gg, gd, gu, (int)G, T, d, r, n, act, dt, gdt,
                         acc, pw, nb, st);
@@ -228,7 +233,7 @@ PyObject* attention_fwd(Args& a) {
   const int64_t ld = stride_of(q), ldkv = stride_of_all(k, {&v});
   const int dt = dt_of(q);
   const at::Tensor o = rows_like(q), lse = fresh({B, H, S}, at::kFloat, q);
-  void *pq = ptr(q), *pk = ptr(k), *pv = ptr(v), *po = ptr(o), *pl = ptr(lse), *st = stream();
+  void *pq = ptr(q), *pk = ptr(k), *pv = ptr(v), *po = ptr(o), *pl = dense(lse), *st = stream();
   call("lr_attention_gqa_fwd", [&] { return lr_attention_gqa_fwd(pq, pk, pv, po, (float*)pl, ld, ldkv, B, S, H, Hkv, hd, causal, dt, st); });
   return tuple(o, lse);
 }
@@ -242,7 +247,7 @@ PyObject* attention_bwd(Args& a) {
   const at::Tensor ws = workspace(lr_attention_gqa_bwd_workspace_bytes(B, S, H, Hkv, hd), q);
   const size_t nb = (size_t)ws.numel();
   const int dt = dt_of(q);
-  void *pq = ptr(q), *pk = ptr(k), *pv = ptr(v), *po = ptr(o), *pdo = ptr(dout), *pl = ptr(lse), *gq = ptr(dq), *gk = ptr(dk), *gv = ptr(dv),
+  void *pq = ptr(q), *pk = ptr(k), *pv = ptr(v), *po = ptr(o), *pdo = ptr(dout), *pl = dense(lse), *gq = ptr(dq), *gk = ptr(dk), *gv = ptr(dv),
        *pw = ptr(ws), *st = stream();
   call("lr_attention_gqa_bwd", [&] {
     return lr_attention_gqa_bwd(pq, pk, pv, po, pdo, (const float*)pl, gq, gk, gv, ld, ldkv, B, S, H, Hkv, hd, causal, dt, pw, nb, st);
@@ -257,7 +262,7 @@ PyObject* rms_stat(Args& a) {
   const at::Tensor stat = fresh({T}, at::kFloat, x);
   const int64_t ldx = stride_of(x);
   const int dt = dt_of(x);
-  void *px = ptr(x), *ps = ptr(stat), *st = stream();
+  void *px = ptr(x), *ps = dense(stat), *st = stream();
   call("lr_rms_stat", [&] { return lr_rms_stat(px, ldx, (float*)ps, T, d, dt, st); });
   return wrap(stat);
 }
@@ -269,7 +274,7 @@ PyObject* rmsnorm_apply(Args& a) {
   const at::Tensor out = at::empty_like(x);
   const int64_t ldx = stride_of(x);
   const int dt = dt_of(x);
-  void *px = ptr(x), *pg = ptr(gamma), *ps = ptr(stat), *po = ptr(out), *st = stream();
+  void *px = ptr(x), *pg = dense(gamma), *ps = dense(stat), *po = ptr(out), *st = stream();
   call("lr_rmsnorm_apply", [&] { return lr_rmsnorm_apply(px, ldx, pg, (const float*)ps, eps, po, d, T, d, dt, st); });
   return wrap(out);
 }
@@ -285,7 +290,7 @@ PyObject* rmsnorm_bwd(Args& a) {
   const at::Tensor part = fresh({parts < 1 ? 1 : parts, d}, at::kFloat, x);
   const int64_t ldx = stride_of(x), lddxh = stride_of(dxhat), lddres = dres.defined() ? stride_of(dres) : 0;
   const int dt = dt_of(x);
-  void *px = ptr(x), *pg = ptr(gamma), *ps = ptr(stat), *ph = ptr(dxhat), *pr = ptr(dres), *pdx = ptr(dx), *pp = ptr(part), *st = stream();
+  void *px = ptr(x), *pg = dense(gamma), *ps = dense(stat), *ph = ptr(dxhat), *pr = ptr(dres), *pdx = ptr(dx), *pp = ptr(part), *st = stream();
   call("lr_rmsnorm_bwd", [&] { return lr_rmsnorm_bwd(px, ldx, pg, (const float*)ps, eps, ph, lddxh, pr, lddres, pdx, d, (float*)pp, T, d, dt, st); });
   return tuple(dx, part);
 }

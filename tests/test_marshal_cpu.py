@@ -37,6 +37,36 @@ def test_operands_of_one_row_stride(call):
         call()
 
 
+# No stride is passed for these: of anything but dense memory other elements would be read or written, of a broadcast tensor (the
+# gradient of a sum, say) elements past its end.
+ONE, G2 = torch.zeros(()), torch.zeros(2, 24, 8)
+DY, DESC = ONE.expand(2, 4, 24), B.make_block_desc(1, 4, 128, 1, 128, 256, 256, 32)
+Z, Z2, GAMMA, STAT, T128 = torch.zeros(4, 8), torch.zeros(4, 16), torch.zeros(16), torch.zeros(4), torch.zeros(4, 128)
+PARAMS = {n: torch.zeros(8) for n in B.PARAM_NAMES}
+CKPT, SAVED = ({n: torch.zeros(8) for n, _ in c._fields_} for c in (B.BlockCkpt, B.BlockSaved))
+
+
+@pytest.mark.parametrize("call", [
+    lambda: B.lr_linear_fwd(X, WD.t().contiguous().t(), WU), lambda: B.lr_linear_fwd(X, WD, ONE.expand(24, 8)),
+    lambda: B.lr_linear_bwd(X, WD, WU, Z2[:, :8], torch.zeros(4, 24)),
+    lambda: B.lr_linear_bwd(X, WD, WU, Z, torch.zeros(4, 24), grads=(torch.zeros(8, 32)[:, :16], WU)),
+    lambda: B.lr_group_fwd(X, ONE.expand(16), 1e-5, B.LR_NORM_ONLINE, torch.zeros(16, 16), G2),
+    lambda: B.lr_group_bwd(X, None, 1e-5, B.LR_NORM_NONE, torch.zeros(16, 16), G2, Z2, None, DY),
+    lambda: B.lr_group_bwd(X, None, 1e-5, B.LR_NORM_NONE, torch.zeros(16, 16), G2, Z2, None, DY.contiguous(), grads=(None, X, G2.transpose(1, 2))),
+    lambda: B.lr_attention_gqa_bwd(X, X, X, X, X, ONE.expand(1, 1, 4), 1, 4, 1, 1, 16),
+    lambda: B.lr_attention_bwd(X, X, X, X, X, ONE.expand(1, 1, 4), 1, 4, 1, 16),
+    lambda: B.lr_rmsnorm_apply(X, GAMMA, ONE.expand(4), 1e-5), lambda: B.lr_rmsnorm_bwd(X, ONE.expand(16), STAT, 1e-5, X),
+    lambda: B.lr_block_fwd(DESC, PARAMS, ONE.expand(4, 128)), lambda: B.lr_block_bwd(DESC, PARAMS, T128, ONE.expand(4, 128), CKPT),
+    lambda: B.lr_block_bwd_saved(DESC, PARAMS, T128, ONE.expand(4, 128), CKPT, SAVED),
+    lambda: B.lr_block_lax_bwd(DESC, PARAMS, T128, ONE.expand(4, 128), CKPT), lambda: B.lr_block_lax_fwd(DESC, PARAMS, ONE.expand(4, 128)),
+    lambda: B.lr_block_fwd_save(DESC, PARAMS, ONE.expand(4, 128)), lambda: B.lr_block_fwd(DESC, {**PARAMS, "w_up_d": G2[:, :, 0]}, T128),
+    lambda: B.make_block_desc(1, 4, 128, 1, 128, 256, 256, 32, rope=(torch.zeros(4, 128)[:, :64], torch.zeros(4, 64))),
+])
+def test_operands_without_a_stride_are_dense(call):
+    with pytest.raises(AssertionError):
+        call()
+
+
 def test_missing_marshalling_fails_loudly(monkeypatch, tmp_path):
     import shutil
     B.lib()
