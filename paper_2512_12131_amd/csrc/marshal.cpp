@@ -4,6 +4,7 @@
 // Bound: host time.  A layer's forward and backward on a few hundred tokens are four launches of 3 us of host time each; the same
 // marshalling through ctypes and torch's Python functions took another 18 us (1.7 us for each of seven tensors, 2-3 us for each
 // call's twenty arguments), more than the GPU needs for the kernels.
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <ATen/ATen.h>
@@ -317,21 +318,18 @@ PyObject* swiglu_bwd(Args& a) {
   return tuple(dg, du);
 }
 
-// No C++ exception leaves an entry.
+// No C++ exception leaves an entry; torch's own become the Python exceptions that they are elsewhere (out of memory, a device's error,
+// an interpreter's exception that crossed torch).
 template <PyObject* (*F)(Args&)>
 PyObject* entry(PyObject*, PyObject* const* v, Py_ssize_t n) {
+  HANDLE_TH_ERRORS
   try {
     Args a{v, n};
     return F(a);
   } catch (const PyError&) {
-  } catch (const python_error&) {        // (an interpreter's exception that crossed torch: it is set again)
-    if (!PyErr_Occurred()) PyErr_SetString(PyExc_RuntimeError, "error in a Python callback");
-  } catch (const c10::Error& e) {
-    PyErr_SetString(PyExc_RuntimeError, e.what_without_backtrace());
-  } catch (const std::exception& e) {
-    PyErr_SetString(PyExc_RuntimeError, e.what());
+    return nullptr;
   }
-  return nullptr;
+  END_HANDLE_TH_ERRORS
 }
 
 PyObject* set_error(PyObject*, PyObject* type) {

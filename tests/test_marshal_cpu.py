@@ -67,6 +67,12 @@ def test_operands_without_a_stride_are_dense(call):
         call()
 
 
+@pytest.mark.skipif(torch.cuda.is_available(), reason="an error of a device that is not there")
+def test_errors_of_torch_keep_their_types():
+    with pytest.raises(torch.AcceleratorError):
+        B.lr_linear_fwd(X, WD, WU)
+
+
 def test_missing_marshalling_fails_loudly(monkeypatch, tmp_path):
     import shutil
     B.lib()
