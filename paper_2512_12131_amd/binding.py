@@ -216,7 +216,7 @@ def _tdt(dt):
 def lr_linear_bwd(x, w_down, w_up, z, dy, act=LR_ACT_SILU, grads=None, grad_dt=LR_F32):
     """Returns (dx, dw_down, dw_up).  With grads=(dw_down, dw_up) the weight grads are accumulated."""
     dwd, dwu = (None, None) if grads is None else grads
-    return _native().linear_bwd(x, w_down, w_up, z, dy, act, dwd, dwu, grad_dt)
+    return _native().linear_bwd(x, w_down, w_up, z, dy, act, grads is not None, dwd, dwu, grad_dt)
 
 
 # ---- G projections sharing one input ---------------------------------------------------------

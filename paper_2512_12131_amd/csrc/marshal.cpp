@@ -158,8 +158,9 @@ PyObject* linear_fwd_static(Args& a) {
 PyObject* linear_bwd(Args& a) {
   const at::Tensor &x = a.tensor(), &wd = a.tensor(), &wu = a.tensor(), &z = a.tensor(), &dy = a.tensor();
   const int act = a.enumerator();
-  at::Tensor dwd = a.optional(), dwu = a.optional();     // given: added to
-  const int gdt = a.enumerator(), acc = dwd.defined(), dt = dt_of(x);
+  const int acc = a.enumerator();
+  at::Tensor dwd = a.optional(), dwu = a.optional();     // acc: added to
+  const int gdt = a.enumerator(), dt = dt_of(x);
   const int64_t T = rows_of(x), d = x.size(1), r = size_of(wd, 0), n = size_of(wu, 0);
   const at::Tensor dx = fresh({T, d}, x.scalar_type(), x);
   if (!acc) {
