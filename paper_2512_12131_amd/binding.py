@@ -113,32 +113,36 @@ EXPORTS = tuple(_SIGS)
 
 
 def lib():
-    """Loads liblrboost.so, and the native marshalling linked against it, on first use.  Raises if they have not been built."""
+    """Loads liblrboost.so on first use.  Raises if it has not been built."""
     global _lib, _marshal
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
-            raise LrError(f"{LIB_PATH} is missing: run `python -c 'import __graft_entry__ as g; g.build()'` "
-                          "(there is no fallback path)")
-        L = C.CDLL(LIB_PATH)
+        L = C.CDLL(_built(LIB_PATH))
         for name, (res, args) in _SIGS.items():
             fn = getattr(L, name)
             fn.restype, fn.argtypes = res, args
-        path = os.path.join(os.path.dirname(LIB_PATH), "_marshal.so")
-        if not os.path.exists(path):
-            raise LrError(f"{path} is missing: run `python -c 'import __graft_entry__ as g; g.build()'` (there is no fallback path)")
-        loader = importlib.machinery.ExtensionFileLoader("_marshal", path)
-        m = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_marshal", path, loader=loader))
-        loader.exec_module(m)
-        m.set_error(LrError)
-        _marshal = m
+        _marshal = None      # (is linked against the library beside it)
         _lib = L
     return _lib
 
 
 def _native():
-    if _lib is None:
+    """Loads the native marshalling, which needs the torch it was built against, on first use: the calls through ctypes do without it."""
+    global _marshal
+    if _lib is None or _marshal is None:
         lib()
+        path = _built(os.path.join(os.path.dirname(LIB_PATH), "_marshal.so"))
+        loader = importlib.machinery.ExtensionFileLoader("_marshal", path)
+        m = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_marshal", path, loader=loader))
+        loader.exec_module(m)
+        m.set_error(LrError)
+        _marshal = m
     return _marshal
+
+
+def _built(path: str) -> str:
+    if not os.path.exists(path):
+        raise LrError(f"{path} is missing: run `python -c 'import __graft_entry__ as g; g.build()'` (there is no fallback path)")
+    return path
 
 
 def _check(status: int, what: str):

@@ -54,8 +54,8 @@ def build_library(verbose: bool = True) -> str:
     with ThreadPoolExecutor(max_workers=min(len(SOURCES) + 1, os.cpu_count() or 4)) as ex:
         marshal = ex.submit(_compile_marshal)
         objs = list(ex.map(_compile, SOURCES))
-        obj, options = marshal.result()
     _run("link", ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs])
+    obj, options = marshal.result()      # (the library is there whether or not this compiled)
     _run("link of the marshalling", ["g++", "-shared", "-fPIC", "-o", MARSHAL, obj, *options])
     if verbose:
         print(f"built {LIB}", file=sys.stderr)

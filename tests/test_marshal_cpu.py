@@ -3,6 +3,7 @@ import pytest
 import torch
 
 from paper_2512_12131_amd import binding as B
+from paper_2512_12131_amd import build
 
 X, WD, WU = torch.zeros(4, 16), torch.zeros(8, 16), torch.zeros(24, 8)
 WIDE = torch.zeros(4, 48)[:, :16]      # rows 48 apart
@@ -81,3 +82,25 @@ def test_missing_marshalling_fails_loudly(monkeypatch, tmp_path):
     monkeypatch.setattr(B, "LIB_PATH", str(tmp_path / "liblrboost.so"))
     with pytest.raises(B.LrError):
         B.lr_rms_stat(X)
+    # what goes through ctypes does without
+    assert B.lr_block_workspace_bytes(DESC, 1) > 0
+    with pytest.raises(B.LrError, match="LR_EUNSUPPORTED"):
+        B._check(B.lib().lr_rope(16, 128, 16, 16, 1, 4, 1, 128, 0, B.LR_F32, None), "lr_rope")
+    monkeypatch.undo()
+    with pytest.raises(ValueError):
+        B.lr_rms_stat(X[0])
+
+
+def test_library_is_built_without_the_marshalling(monkeypatch):
+    """A torch that the marshalling does not compile against fails the build, after the library has been linked."""
+    done = []
+
+    def fail():
+        raise RuntimeError("no torch headers")
+
+    monkeypatch.setattr(build, "_compile", lambda src: src)
+    monkeypatch.setattr(build, "_run", lambda what, cmd: done.append(what))
+    monkeypatch.setattr(build, "_compile_marshal", fail)
+    with pytest.raises(RuntimeError, match="no torch headers"):
+        build.build_library(verbose=False)
+    assert done == ["link"]
