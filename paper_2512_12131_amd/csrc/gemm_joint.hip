@@ -107,11 +107,12 @@ bool gemm_bf16_joint_ok(const GemmOp& op) { return form_of(op) != JF_NONE; }
 hipError_t gemm_bf16_joint(int tile, const GemmOp* in, int n, hipStream_t st) {
   if (n <= 0 || n > JOINT_MAX) return hipErrorInvalidValue;
   // The longest workgroups first: started last they run alone behind the others (4 tokens, two members 328 -> 464 -> 3408, a
-  // data gradient of 54 slices beside weight gradients of one: 27.9 us, apart 20).
+  // data gradient of 54 slices beside weight gradients of one: 27.9 us, apart 20).  A gate's and up pair walks k twice.
+  auto walk = [](const GemmOp& op) { return (int64_t)op.K * (op.epi.kind == EPI_SWIGLU_DUAL ? 2 : 1); };
   GemmOp ops[JOINT_MAX];
   for (int i = 0; i < n; i++) {
     int j = i;
-    for (; j > 0 && (int64_t)ops[j - 1].K * in[i].splitk < (int64_t)in[i].K * ops[j - 1].splitk; j--) ops[j] = ops[j - 1];
+    for (; j > 0 && walk(ops[j - 1]) * in[i].splitk < walk(in[i]) * ops[j - 1].splitk; j--) ops[j] = ops[j - 1];
     ops[j] = in[i];
   }
   if (tile == GEMM_R32) return launch_joint<RingTile<32, 32, 1, 1, 2, 5, 4>>(ops, n, st);

@@ -49,3 +49,11 @@ def of(call):
 def functions(call):
     """The kernels themselves, as numbers that are equal where two launches run the same one."""
     return [p.func for p in _kernels(call)]
+
+
+def arguments(call, kernel, words):
+    """The first `words` 32-bit words of the first argument of every launch of a kernel with `kernel` in its name."""
+    hip = _hip()
+    hip.hipKernelNameRefByPtr.restype, hip.hipKernelNameRefByPtr.argtypes = C.c_char_p, [C.c_void_p, C.c_void_p]
+    return [list((C.c_int32 * words).from_address((C.c_void_p * 1).from_address(p.params)[0])) for p in _kernels(call)
+            if kernel in hip.hipKernelNameRefByPtr(p.func, None).decode()]

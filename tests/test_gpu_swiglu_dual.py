@@ -38,3 +38,18 @@ def test_forward_and_backward(T, H, f, r):
     B.lr_launch_timer_end()
     for a, b in zip(together, apart):
         assert torch.equal(a, b)
+
+
+def test_longest_first_in_a_joint_launch():
+    """Beside products whose k lies between its own and twice that, the pair is the one that takes longest: its workgroups start first."""
+    T, H, f, r = 128, 1, 344, 120
+    print(f"gate and up first in a joint launch T={T} H={H} f={f} r={r}", flush=True)
+    d = 128 * H
+    case = si.block_case(1, T, d, H, 128, f, r, seed=6)
+    p = {k: v.to(DEV) for k, v in si.pack_block_params(case["params"], f, f).items()}
+    x, dy = case["x"].to(DEV), case["dy"].to(DEV)
+    desc = B.make_block_desc(1, T, d, H, 128, f, f, r)
+    y, ck = B.lr_block_fwd(desc, p, x)
+    # (a product's sizes M, N, K lie among its first words)
+    firsts = [w[20:23] for w in launches.arguments(lambda: B.lr_block_bwd(desc, p, x, dy, ck), "gemm_joint_kernel", 24)]
+    assert [T, f, r] in firsts
