@@ -851,11 +851,21 @@ __global__ __launch_bounds__(256) void wgrad_finish_narrow_kernel(const float* p
     dgpart[(int64_t)blockIdx.y * cols + c0 + tid] = sclass[tid] + sclass[W + tid] + sclass[2 * W + tid] + sclass[3 * W + tid];
 }
 
-// The whole pass behind a norm, dgamma included, where a gradient has few rows: a workgroup takes 32 columns of all of them, the
-// partials of 32 rows stay in LDS and are added up there, in the order of the two kernels that otherwise share the work.  Bound by its
-// way in and out like those, of which it saves one (128 x 256 and its dgamma 4.1 + 2.6 -> 4.7 us, 192 x 1024 1 us less; but 504 x 512,
-// whose rows follow each other in 16 workgroups, 5 us more).
-constexpr int WHOLE_ROWS = 256, WHOLE_COLS = 1024;
+// The whole pass behind a norm, dgamma included, where a gradient has few rows and partials: a workgroup takes 32 columns of all rows, the
+// sums of 32 rows stay in LDS and are added up there, in the order of the two kernels that otherwise share the work.  Bound by its way
+// in and out like those, of which it saves one; a thread takes every 64th row (bf16; fp32, one column per thread: every 8th) and its
+// partials one after the other, on as many workgroups as there are strips of 32 columns, which costs more than the launch where there are
+// several such rows or many partials.  us, two launches / this one, by rows (256 columns; 64 to 1024 differ by 0.7 at most) and
+// partials, right behind what writes them:
+//   bf16   64: 1 5.2 / 3.0, 32 10.5 / 8.0      128: 1 5.3 / 3.8, 12 7.5 / 7.2, 16 8.1 / 8.6, 32 11.0 / 13.3
+//         160: 1 5.2 / 5.0, 4 5.8 / 6.1        192: 1 5.4 / 5.0, 2 5.4 / 5.6, 16 8.5 / 12.5       256: 1 5.4 / 5.7, 32 12.7 / 25.3
+//   fp32   16: 1 3.8 / 2.6, 16 4.6 / 4.2        32: 1 4.3 / 3.4, 4 4.4 / 4.0, 8 4.5 / 5.0          64: 1 4.4 / 4.9, 16 5.9 / 9.1
+constexpr int WHOLE_ROWS = 192, WHOLE_COLS = 1024;
+inline bool finish_whole(int64_t rows, int64_t cols, int nsplit, int dt) {
+  if (cols > WHOLE_COLS) return false;
+  if (dt == LR_F32) return nsplit <= (rows <= 16 ? 16 : rows <= 32 ? 4 : 0);
+  return rows <= 64 || nsplit <= (rows <= 128 ? 12 : rows <= WHOLE_ROWS ? 1 : 0);
+}
 template <int DT, typename OT>
 __global__ __launch_bounds__(256) void wgrad_finish_whole_kernel(const float* part, int nsplit, int64_t rows, int64_t cols, void* dw,
                                                                  const void* colscale, const void* wdg, void* dgamma, int accumulate) {
@@ -1162,7 +1172,7 @@ hipError_t k_wgrad_finish(const float* part, int nsplit, int64_t rows, int64_t c
   if (rows <= 0 || cols <= 0) return hipSuccess;
   const int nv = dt == LR_BF16 ? 8 : 1;
   const bool dg = w_for_dgamma != nullptr && dgamma_part != nullptr;
-  if (dg && rows <= WHOLE_ROWS && cols <= WHOLE_COLS && (dt == LR_BF16 || out_dt == LR_F32)) {
+  if (dg && finish_whole(rows, cols, nsplit, dt) && (dt == LR_BF16 || out_dt == LR_F32)) {
     const dim3 grid((unsigned)((cols + 31) / 32));
 #define LRB_WHOLE(DT_, OT_)                                                                                                         \
   hipLaunchKernelGGL((wgrad_finish_whole_kernel<DT_, OT_>), grid, dim3(256), 0, st, part, nsplit, rows, cols, dw, colscale, w_for_dgamma, \

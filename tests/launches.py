@@ -51,9 +51,16 @@ def functions(call):
     return [p.func for p in _kernels(call)]
 
 
-def arguments(call, kernel, words):
-    """The first `words` 32-bit words of the first argument of every launch of a kernel with `kernel` in its name."""
+def named(call, kernel):
+    """(name, addresses of its arguments) of every launch of a kernel with `kernel` in its name, while its graph is there."""
     hip = _hip()
     hip.hipKernelNameRefByPtr.restype, hip.hipKernelNameRefByPtr.argtypes = C.c_char_p, [C.c_void_p, C.c_void_p]
-    return [list((C.c_int32 * words).from_address((C.c_void_p * 1).from_address(p.params)[0])) for p in _kernels(call)
-            if kernel in hip.hipKernelNameRefByPtr(p.func, None).decode()]
+    for p in _kernels(call):
+        name = hip.hipKernelNameRefByPtr(p.func, None).decode()
+        if kernel in name:
+            yield name, C.cast(p.params, C.POINTER(C.c_void_p))
+
+
+def words(address, n):
+    """n 32-bit integers from there (no more than the argument has)."""
+    return list((C.c_int32 * n).from_address(address))

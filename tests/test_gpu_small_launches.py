@@ -41,6 +41,29 @@ def test_dgamma_of_few_rows(d, r, G, dtype):
     assert torch.equal(more[0], dg + 0.5) and torch.equal(more[1], dwd + 0.5)
 
 
+# rows and partials on both sides of each line: all of one turn of a workgroup, of two up to 12 partials, of three with one; in fp32, whose
+# turns have 8 rows, up to 16 rows, up to 32 with 4 partials
+@pytest.mark.parametrize("dtype,rows,T,partials,whole", [
+    (torch.bfloat16, 64, 10000, 18, True), (torch.bfloat16, 72, 6144, 12, True), (torch.bfloat16, 128, 6144, 12, True),
+    (torch.bfloat16, 72, 6656, 13, False), (torch.bfloat16, 128, 16384, 32, False), (torch.bfloat16, 136, 512, 1, True),
+    (torch.bfloat16, 192, 512, 1, True), (torch.bfloat16, 192, 2048, 4, False), (torch.bfloat16, 200, 512, 1, False),
+    (torch.float32, 16, 8200, 4, True), (torch.float32, 17, 8200, 4, True), (torch.float32, 32, 512, 1, True),
+    (torch.float32, 32, 16400, 8, False), (torch.float32, 33, 512, 1, False), (torch.float32, 192, 512, 1, False)])
+def test_one_launch_for_few_rows_and_partials(dtype, rows, T, partials, whole):
+    d, n = 136, 72
+    print(f"finishing pass {dtype} rows={rows} T={T}", flush=True)
+    x, gamma, wd, wu, dy = _group(T, d, rows, n, 1, dtype, rows)
+    z, stat, _ = B.lr_group_fwd(x, gamma, 1e-5, B.LR_NORM_ONLINE, wd, wu)
+    back = lambda: B.lr_group_bwd(x, gamma, 1e-5, B.LR_NORM_ONLINE, wd, wu, z, stat, dy)
+    _, dg, dwd, _ = back()
+    torch.cuda.synchronize()
+    terms = wd.double() * (dwd.double() / gamma.double())
+    assert ((dg.double() - terms.sum(0)).abs() <= (12 + rows / 32) * 2.0 ** -24 * terms.abs().sum(0)).all()      # (as above)
+    # (the pass behind the norm comes after the others, which have no dgamma; its second argument is the number of partials)
+    name, count = [(name, launches.words(args[1], 1)[0]) for name, args in launches.named(back, "wgrad_finish") if "many" not in name][-1]
+    assert (count, "whole" in name) == (partials, whole)
+
+
 # rows that don't fill a workgroup, and more weight vectors than a workgroup's
 @pytest.mark.parametrize("T,d,r,G", [(1, 64, 520, 1), (7, 2056, 264, 2), (1031, 520, 176, 3)])
 def test_fold_beside_the_row_statistic(T, d, r, G):

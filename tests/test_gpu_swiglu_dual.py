@@ -51,5 +51,5 @@ def test_longest_first_in_a_joint_launch():
     desc = B.make_block_desc(1, T, d, H, 128, f, f, r)
     y, ck = B.lr_block_fwd(desc, p, x)
     # (a product's sizes M, N, K lie among its first words)
-    firsts = [w[20:23] for w in launches.arguments(lambda: B.lr_block_bwd(desc, p, x, dy, ck), "gemm_joint_kernel", 24)]
+    firsts = [launches.words(args[0], 24)[20:23] for _, args in launches.named(lambda: B.lr_block_bwd(desc, p, x, dy, ck), "gemm_joint_kernel")]
     assert [T, f, r] in firsts
