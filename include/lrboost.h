@@ -275,10 +275,12 @@ int lr_rope(void* x, int64_t ldx, const float* cos_tab, const float* sin_tab, in
 /* q, k, v, o: [B*S, H*hd] token-major, head h in columns h*hd..; lse[B, H, S] fp32.
  * bf16 only, hd = 128, and S * ld * 2 < 2^31 bytes (the kernels address one batch element with
  * 32-bit buffer offsets); otherwise LR_EUNSUPPORTED.  The backward workspace holds two [B, H, S]
- * fp32 arrays (sum_h dO*O and lse * log2(e)) and, when S is a multiple of 8 and it stays under
- * 24 GiB, the score gradient scale * dS^T as bf16 [B, H, S, S] (4.3 GB at B 4, H 32, S 4096):
- * the key / value gradient kernel writes it and the query gradient is one GEMM over it, which
- * saves recomputing the scores a second time.  Other shapes take the recomputing form.        */
+ * fp32 arrays (sum_h dO*O and lse * log2(e)) and, where S is a multiple of 8, room for the score
+ * gradient scale * dS^T as bf16 [B, H, S, S].  Where the work leaves CUs idle the key / value gradient
+ * kernel writes it and the query gradient is one GEMM over it; where there is work for the whole chip,
+ * S is not a multiple of 8 or the room would be over 24 GiB, it is formed a second time instead.  The
+ * same bits either way.  The room is that of the calls of H heads on up to B sequences of up to S
+ * tokens that store it (0.5 GB at B 4, H 4, S 4096; 3.3 GB at B 4, H 32, S 4096, for S 3584).        */
 int lr_attention_fwd(const void* q, const void* k, const void* v, void* o, float* lse,
                      int64_t ld, int64_t B, int64_t S, int64_t H, int64_t hd, int causal,
                      int dt, void* stream);

@@ -1639,22 +1639,10 @@ hipError_t attention_gqa_fwd_bf16(const void* q, const void* k, const void* v, v
 // bits.  Whole backward, us, kept -> formed twice: 4 x 4096 tokens, 32 heads 2098 -> 1841; 8 x 2048, 16 heads 644 -> 542; 1 x 8192, 16 heads
 // 980 -> 853; 8 x 1024, 16 heads 204 -> 178; 16 x 264, 32 heads 157 -> 152; elsewhere 2 x 1536, 16 heads 106 / 115; 1 x 2048, 8 heads 99 / 104,
 // 128 x 128, 16 heads 243 / 280.
-// (The size query counts the first form wherever S allows it: a workspace for more tokens serves for fewer.)
 constexpr size_t DS_WS_CAP = (size_t)24 << 30;
 static bool keep_ds(int B, int S, int H) {
   return S % 8 == 0 && (int64_t)S * S * 2 < (int64_t)0x7fffffff && (size_t)B * H * S * S * 2 <= DS_WS_CAP;
 }
-// D and the base-2 exponent offsets lse * log2(e), both [B, H, S] fp32; then dS^T [B, H, S, S] bf16
-size_t attention_bwd_ws_bytes(int B, int S, int H, int hd) { return attention_gqa_bwd_ws_bytes(B, S, H, H, hd); }
-// ... and, with fewer key / value heads than query heads, the per-query-head contributions to dK and dV
-// (two [B * S, H * hd] bf16 tensors) that a last kernel adds up group by group
-static size_t ds_bytes(int B, int S, int H) { return keep_ds(B, S, H) ? ((size_t)B * H * S * S * 2 + 255) / 256 * 256 : 0; }
-size_t attention_gqa_bwd_ws_bytes(int B, int S, int H, int Hkv, int hd) {
-  const size_t small = (2 * (size_t)B * H * S * sizeof(float) + 255) / 256 * 256;
-  return small + ds_bytes(B, S, H) + (Hkv < H ? 2 * (size_t)B * S * H * HD * 2 : 0);
-}
-
-constexpr int DKV_NB = 1;   // 32-key blocks per wavefront in the dK/dV kernel
 
 // 256 keys per workgroup, in pairs of blocks, or 128: a workgroup of twice the keys takes 0.91 to 0.97 of two workgroups' time, so it
 // pays where the launch is half as many rounds of the chip or fewer, and from 144 workgroups on (fewer were not measured).  Whole
@@ -1666,6 +1654,32 @@ static bool dkv_pairs(int S, int64_t heads) {
   const int64_t wide = (S + 255) / 256, wgs = (wide + 1) / 2 * heads, other = ((S + 127) / 128 + 1) / 2 * heads;
   return wide * heads > 256 && wgs >= 144 && 2 * ((wgs + 255) / 256) <= (other + 255) / 256;
 }
+
+// The room for the score gradient: the most that a call of as many heads stores for up to B sequences of up to S tokens, so that a
+// workspace for more tokens serves for fewer, which may store it where more form it twice (4 x 4096 tokens, 32 heads: 3.3 GB, for
+// 3584 tokens, where its own would be 4.3).  dkv_pairs sees of S only the number of 256-key blocks: of those with as many the
+// longest sequence counts.
+static size_t ds_bytes(int B, int S, int H) {
+  if (!keep_ds(B, S, H)) return 0;
+  size_t most = 0;
+  for (int wide = (S + 255) / 256; wide > 0; wide--) {
+    const size_t s = (size_t)(S < wide * 256 ? S : wide * 256), one = s * s * 2 * H;
+    for (int b = B; b > 0 && (size_t)b * one > most; b--)
+      if (!dkv_pairs((int)s, (int64_t)b * H)) most = (size_t)b * one;
+    if ((size_t)B * one <= most) break;
+  }
+  return (most + 255) / 256 * 256;
+}
+// D and the base-2 exponent offsets lse * log2(e), both [B, H, S] fp32; then dS^T [B, H, S, S] bf16
+size_t attention_bwd_ws_bytes(int B, int S, int H, int hd) { return attention_gqa_bwd_ws_bytes(B, S, H, H, hd); }
+// ... and, with fewer key / value heads than query heads, the per-query-head contributions to dK and dV
+// (two [B * S, H * hd] bf16 tensors) that a last kernel adds up group by group
+size_t attention_gqa_bwd_ws_bytes(int B, int S, int H, int Hkv, int hd) {
+  const size_t small = (2 * (size_t)B * H * S * sizeof(float) + 255) / 256 * 256;
+  return small + ds_bytes(B, S, H) + (Hkv < H ? 2 * (size_t)B * S * H * HD * 2 : 0);
+}
+
+constexpr int DKV_NB = 1;   // 32-key blocks per wavefront in the dK/dV kernel
 
 hipError_t attention_bwd_bf16(const void* q, const void* k, const void* v, const void* o, const void* dout,
                               const float* lse, void* dq, void* dk, void* dv, int64_t ld, int B, int S, int H, int hd,

@@ -273,3 +273,34 @@ def test_group_backward_asks_for_the_partials_behind_the_norm():
     T, d, r, n = 3844, 264, 488, 2616
     alive = 2 * T * r * 2 + min(32 << 20, 7 * r * n * 4) + 7 * r * d * 4
     assert B.lr_group_workspace_bytes(1, T, d, r, n, B.LR_BF16, 1) >= alive
+
+
+def _stores_score_gradient(Bn, S, H):
+    """Whether a backward call keeps the score gradient: S in whole vectors, unless it has work for the whole chip in pairs of 256-key blocks."""
+    ceil = lambda a, b: -(-a // b)
+    heads, wide = Bn * H, ceil(S, 256)
+    wgs, other = ceil(wide, 2) * heads, ceil(ceil(S, 128), 2) * heads
+    return S % 8 == 0 and not (wide * heads > 256 and wgs >= 144 and 2 * ceil(wgs, 256) <= ceil(other, 256))
+
+
+def test_attention_backward_holds_no_score_gradient_that_no_call_stores():
+    """4 x 4096 tokens of 32 heads form the score gradient twice; what is kept for shorter sequences is at most theirs."""
+    query = B.lib().lr_attention_bwd_workspace_bytes
+    assert query(4, 4096, 32, 128) < 3.4e9 and query(1, 8192, 16, 128) < 0.6e9
+    for S in (1, 200, 264, 1024, 2056, 4096, 8184):
+        for H in (1, 4, 12, 32):
+            for Bn in (1, 3, 8, 40):
+                D_lse2 = 2 * Bn * H * S * 4
+                most = Bn * H * S * S * 2 if S % 8 == 0 and Bn * H * S * S * 2 <= 24 << 30 else 0
+                assert D_lse2 + (most if _stores_score_gradient(Bn, S, H) else 0) <= query(Bn, S, H, 128) <= D_lse2 + most + 1024
+
+
+@pytest.mark.parametrize("H", [1, 2, 6, 12, 16, 32, 40])
+def test_an_attention_workspace_for_more_tokens_serves_for_fewer(H):
+    query = lambda Bn, S: B.lib().lr_attention_bwd_workspace_bytes(Bn, S, H, 128)
+    for Bn in (1, 4, 9):
+        sizes = [query(Bn, S) for S in range(8, 4097, 8)]
+        assert sizes == sorted(sizes)
+    for S in (136, 512, 1536, 2304, 4096):
+        sizes = [query(Bn, S) for Bn in range(1, 20)]
+        assert sizes == sorted(sizes)

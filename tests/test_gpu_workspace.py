@@ -208,3 +208,24 @@ def test_rows_that_span_more_than_2_gib():
     dz = (dy.double() @ wu.double()).bfloat16().double()
     for a, b, mag in ((got[1], dense[1], dz.abs().t() @ x.double().abs()), (got[2], dense[2], dy.double().abs().t() @ z.double().abs())):
         assert ((a.double() - b.double()).abs() <= 2 * T * 2.0 ** -24 * 1.01 * mag).all()
+
+
+# the score gradient formed twice (no room for it in the workspace) and stored, key / value heads of groups behind it
+@pytest.mark.parametrize("Bn,S,H,Hkv", [(8, 264, 20, 20), (9, 264, 20, 10), (3, 264, 20, 10), (1, 520, 4, 2), (2, 333, 4, 4)])
+def test_attention(Bn, S, H, Hkv):
+    print(f"attention backward in the bytes of its query B={Bn} S={S} H={H} Hkv={Hkv}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(S)
+    q, dout = (torch.randn((Bn * S, H * 128), generator=g, device=DEV).bfloat16() for _ in range(2))
+    k, v = (torch.randn((Bn * S, Hkv * 128), generator=g, device=DEV).bfloat16() for _ in range(2))
+    o, lse = B.lr_attention_gqa_fwd(q, k, v, Bn, S, H, Hkv, 128)
+    outs = [torch.empty_like(t) for t in (q, k, v)]
+
+    def call(ws, size):
+        return B.lib().lr_attention_gqa_bwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), dout.data_ptr(), lse.data_ptr(),
+                                            *(t.data_ptr() for t in outs), H * 128, Hkv * 128, Bn, S, H, Hkv, 128, 1, B.LR_BF16, ws, size,
+                                            _stream())
+
+    need = B.lib().lr_attention_gqa_bwd_workspace_bytes(Bn, S, H, Hkv, 128)
+    _same(call, outs, need, need + Bn * H * S * S * 2)
+    for a, b in zip(outs, B.lr_attention_gqa_bwd(q, k, v, o, dout, lse, Bn, S, H, Hkv, 128)):
+        assert torch.equal(a, b)
