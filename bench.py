@@ -68,8 +68,8 @@ def block_flops(B, S, d, H, f, r, dkv=None):
     model = 3.0 * lin_fwd + 3.5 * attn_fwd                       # bwd: 2x linear, 2.5x attention
     recompute_lin = 2.0 * T * r * (2 * d + 2 * dkv + 2 * f)      # six of the seven up-projections
     gemm_exec = 3.0 * lin_fwd + recompute_lin
-    # attention as executed here: fwd, re-fwd, and a backward of 5 GEMM units against the 2 of the forward
-    # (S, dP, dV, dK in one kernel that also leaves dS; dQ as one GEMM over it)
+    # attention: fwd, re-fwd, and a backward of 5 GEMM units against the 2 of the forward (S, dP, dV, dK, dQ; large launches
+    # form S and dP a second time for dQ, which is not counted)
     attn_exec = attn_fwd * (1.0 + 1.0 + 2.5)
     return {"model": model, "gemm_exec": gemm_exec, "attn_exec": attn_exec, "exec": gemm_exec + attn_exec,
             "lin_fwd": lin_fwd, "attn_fwd": attn_fwd}

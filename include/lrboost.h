@@ -316,11 +316,13 @@ int lr_attention_gqa_bwd(const void* q, const void* k, const void* v, const void
  * objects, and only on request.  Process-global and not thread-safe: one measuring thread, no compute
  * calls from other threads meanwhile.  Used by the benchmark for the per-class GEMM and attention rates
  * (Sec. 5.3 of the paper measures the same quantity per linear layer: kernel time and utilisation).
+ * Products that otherwise share a launch (small independent ones; the MLP's gate and up pair, where that
+ * is faster) each have their own meanwhile: same results, but not the launches of an untimed call.
  * tag: the GEMM's epilogue class (0 store, 1 down-projection: row scale + sigma, 2 / 10 / 11 up-projection
  * + residual, 3 sigma' (+ row statistic), 4 / 12 / 13 RMSNorm backward, 5 weight gradient,
  * 6 SwiGLU backward, 7 SwiGLU forward, 8 / 9 the LaX forms), or LR_TAG_ATTN_FWD / LR_TAG_ATTN_BWD.
  * flops: 2 M N K batch for a GEMM; causal-halved 2 S^2 hd per (batch, head) and product for attention
- * (2 products forward, 5 backward).                                                               */
+ * (2 products forward, 5 backward: S, dP, dV, dK, dQ, also where S and dP are formed twice).       */
 #define LR_TAG_ATTN_FWD 32
 #define LR_TAG_ATTN_BWD 33
 typedef struct {

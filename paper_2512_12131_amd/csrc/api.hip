@@ -334,12 +334,9 @@ int group_runs(const GrpArgs& a, GrpRun (&run)[2]) {
   return 2;
 }
 
-// w_down_cat with gamma folded into its columns; stat: and the row statistic of x
+// w_down_cat with gamma folded into its columns; stat: and the row statistic of x (a block that folds beforehand has taken it then)
 const void* scaled_weight(Ctx& c, const GrpArgs& a, bool stat = false) {
-  if (a.w_scaled_given) {
-    if (stat) LAUNCH(c, k_rms_stat(a.x, a.ldx, a.stat, a.T, a.d_in, c.dt, c.st));
-    return a.w_scaled;
-  }
+  if (a.w_scaled_given) return a.w_scaled;
   ScaleCols f;
   f.w0 = a.w_down_cat; f.gamma0 = a.gamma; f.rows0 = (int64_t)a.G * a.r; f.cols = a.d_in;
   f.out0 = c.take((size_t)f.rows0 * a.d_in * esize(c.dt));
@@ -972,7 +969,7 @@ void block_bwd_seq(Ctx& c, const Blk& b, const lr_block_params* p, const void* x
   {
     const size_t mk = c.mark();
     void* aws = c.take(attention_gqa_bwd_ws_bytes((int)b.B, (int)b.S, (int)b.H, (int)b.Hkv, (int)b.hd));
-    // five GEMM units (S, dP, dV, dK in one kernel, dQ over the stored score gradient) against the forward's two
+    // five GEMM units (S, dP, dV, dK, dQ) against the forward's two, also where S and dP are formed a second time for dQ
     const int slot = c.dry ? -1 : launch_timer_open(LR_TAG_ATTN_BWD, (int)T, (int)d, (int)b.S, 1, attn_unit_flops(b) * 5.0, c.st);
     LAUNCH(c, attention_gqa_bwd_bf16(q_, k_, v_, o, dout, lse, dqkv, (char*)dqkv + (size_t)T * d * es,
                                      (char*)dqkv + (size_t)T * (d + dkv) * es, d, dkv, (int)b.B, (int)b.S, (int)b.H,
