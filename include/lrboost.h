@@ -279,8 +279,8 @@ int lr_rope(void* x, int64_t ldx, const float* cos_tab, const float* sin_tab, in
  * gradient scale * dS^T as bf16 [B, H, S, S].  Where the work leaves CUs idle the key / value gradient
  * kernel writes it and the query gradient is one GEMM over it; where there is work for the whole chip,
  * S is not a multiple of 8 or the room would be over 24 GiB, it is formed a second time instead.  The
- * same bits either way.  The room is that of the calls of H heads on up to B sequences of up to S
- * tokens that store it (0.5 GB at B 4, H 4, S 4096; 3.3 GB at B 4, H 32, S 4096, for S 3584).        */
+ * same bits either way.  The room is that of the calls of H heads on up to B * S tokens in sequences
+ * of up to S that store it (0.5 GB at B 4, H 4, S 4096; 3.4 GB at B 4, H 32, S 4096, for B 5, S 3272). */
 int lr_attention_fwd(const void* q, const void* k, const void* v, void* o, float* lse,
                      int64_t ld, int64_t B, int64_t S, int64_t H, int64_t hd, int causal,
                      int dt, void* stream);

@@ -1655,18 +1655,22 @@ static bool dkv_pairs(int S, int64_t heads) {
   return wide * heads > 256 && wgs >= 144 && 2 * ((wgs + 255) / 256) <= (other + 255) / 256;
 }
 
-// The room for the score gradient: the most that a call of as many heads stores for up to B sequences of up to S tokens, so that a
-// workspace for more tokens serves for fewer, which may store it where more form it twice (4 x 4096 tokens, 32 heads: 3.3 GB, for
-// 3584 tokens, where its own would be 4.3).  dkv_pairs sees of S only the number of 256-key blocks: of those with as many the
-// longest sequence counts.
+// The room for the score gradient: the most that a call of as many heads stores for up to B * S tokens in sequences of up to S, so that
+// a workspace for more tokens serves for fewer, which may store it where more form it twice (4 x 4096 tokens, 32 heads: 3.4 GB, for
+// 5 x 3272; its own would be 4.3).  dkv_pairs sees of S only the number of 256-key blocks, so of those with as
+// many the longest sequence counts: `longest` while b of them fit, then what the tokens leave to each.
 static size_t ds_bytes(int B, int S, int H) {
   if (!keep_ds(B, S, H)) return 0;
+  const int64_t tokens = (int64_t)B * S;
   size_t most = 0;
+  auto one = [&](int64_t b, int64_t s) { return (size_t)b * H * s * s * 2; };
   for (int wide = (S + 255) / 256; wide > 0; wide--) {
-    const size_t s = (size_t)(S < wide * 256 ? S : wide * 256), one = s * s * 2 * H;
-    for (int b = B; b > 0 && (size_t)b * one > most; b--)
-      if (!dkv_pairs((int)s, (int64_t)b * H)) most = (size_t)b * one;
-    if ((size_t)B * one <= most) break;
+    const int64_t longest = S < wide * 256 ? S : wide * 256, fit = tokens / longest;
+    if ((size_t)tokens * H * longest * 2 <= most) break;
+    for (int64_t b = fit; b > 0 && one(b, longest) > most; b--)
+      if (!dkv_pairs((int)longest, b * H)) most = one(b, longest);
+    for (int64_t b = fit + 1; tokens / b > (wide - 1) * 256 && one(b, tokens / b) > most; b++)
+      if (!dkv_pairs((int)longest, b * H)) most = one(b, tokens / b);
   }
   return (most + 255) / 256 * 256;
 }
