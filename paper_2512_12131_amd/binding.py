@@ -128,7 +128,8 @@ def lib():
 def _native():
     """Loads the native marshalling, which needs the torch it was built against, on first use: the calls through ctypes do without it."""
     global _marshal
-    if _lib is None or _marshal is None:
+    m = _marshal             # (another thread's first lib() clears it)
+    if _lib is None or m is None:
         lib()
         path = _built(os.path.join(os.path.dirname(LIB_PATH), "_marshal.so"))
         loader = importlib.machinery.ExtensionFileLoader("_marshal", path)
@@ -136,7 +137,7 @@ def _native():
         loader.exec_module(m)
         m.set_error(LrError)
         _marshal = m
-    return _marshal
+    return m
 
 
 def _built(path: str) -> str:

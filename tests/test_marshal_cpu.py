@@ -91,6 +91,29 @@ def test_missing_marshalling_fails_loudly(monkeypatch, tmp_path):
         B.lr_rms_stat(X[0])
 
 
+def test_first_calls_of_two_threads(monkeypatch):
+    """One thread's first load of the library, ending while the other's marshalling is there already, does not take it away."""
+    import sys
+    monkeypatch.setattr(B, "_lib", None)
+    monkeypatch.setattr(B, "_marshal", None)
+
+    def between_lines(frame, event, arg):
+        if frame.f_code is B._native.__code__ and B._marshal is not None:
+            B._lib = B._marshal = None      # as the other thread begins
+            B.lib()                         # ... and ends
+        return between_lines
+
+    before = sys.gettrace()
+    sys.settrace(between_lines)
+    try:
+        m = B._native()
+    finally:
+        sys.settrace(before)
+    assert m is not None
+    with pytest.raises(ValueError):
+        m.rms_stat(X[0])
+
+
 def test_library_is_built_without_the_marshalling(monkeypatch):
     """A torch that the marshalling does not compile against fails the build, after the library has been linked."""
     done = []
