@@ -187,9 +187,12 @@ def _rowmajor(t: torch.Tensor):
 
 
 def _rowmajor_all(t: torch.Tensor, *others):
-    """The row stride of t, passed for the others too (of a single row any will do)."""
+    """The row stride of t, passed for the others too (of a single row any will do; beside a dense t, dense others of as many elements are
+    the same rows in any shape)."""
     ld = _rowmajor(t)
-    assert all(_rowmajor(o) == ld or t.shape[0] <= 1 >= o.shape[0] for o in others), "operands with the same row stride expected"
+    for o in others:
+        if not ((ld == t.shape[1] or t.shape[0] <= 1) and o.is_contiguous() and o.numel() == t.numel()):
+            assert _rowmajor(o) == ld or t.shape[0] <= 1 >= o.shape[0], "operands with the same row stride expected"
     return ld
 
 

@@ -71,11 +71,14 @@ int64_t stride_of(const at::Tensor& t) {
   if (t.dim() != 2 || t.stride(1) != 1) fail(PyExc_AssertionError, "row-major 2-D tensor expected");
   return t.stride(0);
 }
-// The row stride of t, passed for the others too (of a single row any will do).
+// The row stride of t, passed for the others too (of a single row any will do; beside a dense t, dense others of as many elements are the
+// same rows in any shape).
 int64_t stride_of_all(const at::Tensor& t, std::initializer_list<const at::Tensor*> others) {
   const int64_t ld = stride_of(t);
-  for (const at::Tensor* o : others)
+  for (const at::Tensor* o : others) {
+    if ((ld == t.size(1) || t.size(0) <= 1) && o->is_contiguous() && o->numel() == t.numel()) continue;
     if (stride_of(*o) != ld && (t.size(0) > 1 || o->size(0) > 1)) fail(PyExc_AssertionError, "operands with the same row stride expected");
+  }
   return ld;
 }
 int64_t size_of(const at::Tensor& t, int64_t i) {
@@ -228,11 +231,17 @@ PyObject* group_bwd(Args& a) {
 }
 
 // ---- attention -----------------------------------------------------------------------------
+int64_t stride_of_kv(const at::Tensor& k, const at::Tensor& v) {
+  const int64_t ldkv = stride_of(k);
+  if (ldkv != stride_of(v)) fail(PyExc_AssertionError, "k and v with the same row stride expected");
+  return ldkv;
+}
+
 PyObject* attention_fwd(Args& a) {
   const at::Tensor &q = a.tensor(), &k = a.tensor(), &v = a.tensor();
   const int64_t B = a.integer(), S = a.integer(), H = a.integer(), Hkv = a.integer(), hd = a.integer();
   const int causal = a.enumerator();
-  const int64_t ld = stride_of(q), ldkv = stride_of_all(k, {&v});
+  const int64_t ld = stride_of(q), ldkv = stride_of_kv(k, v);
   const int dt = dt_of(q);
   const at::Tensor o = rows_like(q), lse = fresh({B, H, S}, at::kFloat, q);
   void *pq = ptr(q), *pk = ptr(k), *pv = ptr(v), *po = ptr(o), *pl = dense(lse), *st = stream();
@@ -244,7 +253,7 @@ PyObject* attention_bwd(Args& a) {
   const at::Tensor &q = a.tensor(), &k = a.tensor(), &v = a.tensor(), &o = a.tensor(), &dout = a.tensor(), &lse = a.tensor();
   const int64_t B = a.integer(), S = a.integer(), H = a.integer(), Hkv = a.integer(), hd = a.integer();
   const int causal = a.enumerator();
-  const int64_t ld = stride_of_all(q, {&o, &dout}), ldkv = stride_of_all(k, {&v});
+  const int64_t ld = stride_of_all(q, {&o, &dout}), ldkv = stride_of_kv(k, v);
   const at::Tensor dq = rows_like(q), dk = rows_like(k), dv = rows_like(k);
   const at::Tensor ws = workspace(lr_attention_gqa_bwd_workspace_bytes(B, S, H, Hkv, hd), q);
   const size_t nb = (size_t)ws.numel();

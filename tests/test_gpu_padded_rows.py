@@ -51,3 +51,21 @@ def test_swiglu(T, f):
     dense = [t.contiguous() for t in (g, u, dm)]
     _check([B.lr_swiglu_fwd(g, u)], [B.lr_swiglu_fwd(*dense[:2])])
     _check(B.lr_swiglu_bwd(g, u, dm), B.lr_swiglu_bwd(*dense))
+
+
+def test_dense_operands_of_other_shapes():
+    """[B, S, H, 128], or the rows of all heads one after the other, is the memory of dense [B * S, H * 128]."""
+    Bn, S, H = 2, 40, 3
+    print(f"operands by sequences and heads B={Bn} S={S} H={H}", flush=True)
+    q, k, v, dout = (t.contiguous() for t in _slices(Bn * S, [H * 128] * 4, S))
+    heads, rows = (lambda t: t.view(Bn, S, H, 128)), (lambda t: t.view(Bn * S * H, 128))
+    o, lse = B.lr_attention_fwd(q, k, v, Bn, S, H, 128)
+    _check(B.lr_attention_fwd(q, heads(k), rows(v), Bn, S, H, 128), [o, lse])
+    want = B.lr_attention_gqa_bwd(q, k, v, o, dout, lse, Bn, S, H, H, 128)
+    _check(B.lr_attention_gqa_bwd(q, k, v, heads(o), rows(dout), lse, Bn, S, H, H, 128), want)
+    dq, dk, dv = B.lr_attention_bwd(q, heads(k), rows(v), rows(o), heads(dout), lse, Bn, S, H, 128)
+    _check([dq, dk, dv], [want[0], heads(want[1]), rows(want[2])])
+    _check([B.lr_swiglu_fwd(q, heads(k))], [B.lr_swiglu_fwd(q, k)])
+    dg, du = B.lr_swiglu_bwd(q, heads(k), rows(dout))
+    want = B.lr_swiglu_bwd(q, k, dout)
+    _check([dg, du], [want[0], heads(want[1])])

@@ -38,6 +38,31 @@ def test_operands_of_one_row_stride(call):
         call()
 
 
+# ... but dense memory of as many elements is the same rows whatever its shape.
+@pytest.mark.skipif(torch.cuda.is_available(), reason="goes on to a device that is not there")
+@pytest.mark.parametrize("call", [
+    lambda: B.lr_attention_bwd(X, X.view(2, 2, 16), X.view(8, 8), X.view(2, 2, 1, 16), X.view(-1), X, 1, 4, 1, 16),
+    lambda: B.lr_attention_gqa_bwd(X, X, X, X.view(2, 2, 1, 16), X.view(8, 8), X, 1, 4, 1, 1, 16),
+    lambda: B.lr_swiglu_fwd(X, X.view(2, 2, 16)), lambda: B.lr_swiglu_bwd(X, X.view(64), X.view(2, 2, 16)),
+    lambda: B.lr_swiglu_fwd(WIDE[:1], X[:1].view(1, 1, 16)),
+])
+def test_dense_operands_of_other_shapes(call):
+    with pytest.raises((RuntimeError, B.LrError)):      # (not an AssertionError)
+        call()
+
+
+@pytest.mark.parametrize("call", [
+    lambda: B.lr_attention_bwd(X, X, X, X.view(2, 2, 16)[:, :, :8], X, X, 1, 4, 1, 16), lambda: B.lr_swiglu_fwd(X, torch.zeros(4, 32)),
+    lambda: B.lr_swiglu_fwd(X, torch.zeros(2, 4, 16)), lambda: B.lr_swiglu_fwd(WIDE, X.view(2, 2, 16)),
+    lambda: B.lr_attention_fwd(X, X, X.t().contiguous().t(), 1, 4, 1, 16),
+    lambda: B.lr_attention_gqa_fwd(X, X, X.view(2, 2, 16), 1, 4, 1, 1, 16), lambda: B.lr_attention_gqa_bwd(X, X, X.view(2, 2, 16), X, X, X, 1, 4, 1, 1, 16),
+    lambda: B.lr_attention_gqa_fwd(X[:1], X[:1], WIDE[:1], 1, 1, 1, 1, 16),
+])
+def test_other_shapes_of_other_memory(call):
+    with pytest.raises(AssertionError):
+        call()
+
+
 # No stride is passed for these: of anything but dense memory other elements would be read or written, of a broadcast tensor (the
 # gradient of a sum, say) elements past its end.
 ONE, G2 = torch.zeros(()), torch.zeros(2, 24, 8)
