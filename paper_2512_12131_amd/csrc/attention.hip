@@ -1278,8 +1278,8 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_long_kernel(const uint16_t* 
 }
 
 // ----------------------------------------------------------------------------------------------
-// backward, dK and dV by pairs of wavefronts that share 32 KB keys and walk 32-query blocks together, one forming S, P and dV, the
-// other dP, dS and dK: 256 keys per workgroup where the score gradient is formed twice and there is work for the chip (dkv_pairs
+// backward, dK and dV by pairs of wavefronts that share KB blocks of 32 keys and walk 32-query blocks together, one forming S, P and dV,
+// the other dP, dS and dK: 256 keys per workgroup where the score gradient is formed twice and there is work for the chip (dkv_pairs
 // below), 128 where it is stored and a workgroup has a CU to itself
 //
 // Bound: what one wavefront of a SIMD does while the other's MFMAs run.  A wavefront that does all of a key block's work holds dK,

@@ -543,25 +543,24 @@ hipError_t dispatch(const GemmOp& op, hipStream_t st) {
 // fixed time f (pipeline fill), the epilogue g * e + h * e and nk 64-wide k slices of s0 + s1 each, where s1 and g
 // are what the slices and the epilogue lose to each other when every slot is busy (they scale with the share
 // of slots in use) and e is the traffic of the epilogue in units of one bf16 output.  The rows of T256, R64, R64X128 and R128
-// are least-squares fits of the relative error over 1770 measured launches with k-contiguous operands (M 64 .. 16384, N 64 ..
+// are least-squares fits of the relative error over 1770 launches with k-contiguous operands (M 64 .. 16384, N 64 ..
 // 11008, K 64 .. 11008, nine epilogue kinds), T256X128's over the plain stores among them; R32's is its measured slice time
-// and start-up, set by hand.  Against 1648 launches of the kernels as they are (888 forward products, M from 16; 400 data
-// gradients; 360 weight gradients), the estimates of tiles within 1.5 times the best are off by 8-16 % rms, R32's by 17-19 %
-// (10-15 % too fast on average).  Taking the estimated best loses 1.7 % (forward) and 1.9 % (data gradients) in the geometric mean
-// against the measured best; the 256-row tiles alone take 2.13 times as long as that over the forward products.  All that was measured
-// with a workgroup per 256-row tile.  As a stream, launches of more than 256 tiles are 2 to 15 % faster than the estimate has them, of
-// fewer as before.  123 plain stores as they are now (M 2048 .. 16384, N 512 .. 8192, k 64 .. 2048): taking the estimated best
-// loses 0.7 %; T256 is taken wrongly in two, by 3.4 % at most (2048 x 8192 x 128 15.4 us, R128 14.9), and missed in four
-// (16384 x 4096 x 128 R128 40.6 us, T256 34.9).  Forward products on R32 of up to
-// 256 pieces of 16 x 16 run as those (gemm_rows16.hip): up to twice as fast with long k, which the estimate does not know.  What the
-// lines amount to, with both sides measured (us, plain stores):
-//   a handful of rows: one chain of k per CU        16 x 1024 x 4096:   T256 69.0   R64    16.6   R32 7.3
-//   few tiles, the loads' latency decides          777 x 1024 x 4096:   T256 69.0   R64    18.1   R32 27.6
-//   half the CUs idle under T256                 16384 x 512 x 2048:   T256 45.2   R128   37.6
-//   N = 128 leaves T256 half its columns         16384 x 128 x 4096:   T256 70.6   R64x128 40.8
-//   few tiles and short k                         8192 x 512 x 256:   T256 13.4   R64x128 9.3
-//   the chip full                                16384 x 4096 x 256:   T256 44.6   R128   54.7
-//                                                16384 x 4096 x 2048:  T256 215.3  R128   259.7
+// and start-up, set by hand.  All of these ran a workgroup per tile.  Against 1648 launches of the kernels as they are, T256 and R128 as
+// streams among them (888 forward products, M from 16; 400 data gradients; 360 weight gradients), the estimates of tiles within 1.5 times
+// the best are off by 7-17 % rms, 2-8 % too slow on average (data gradients on ring tiles 6 % too fast to 2 % too slow).  R128 as a stream
+// is 10 % (forward) and 4 % (data gradients) faster than its estimate, T256 as one 2 to 15 %.  Taking the estimated best loses 0.9 %
+// (forward) and 1.4 % (data gradients) in the geometric mean against the measured best, 28 % in the worst launch (16384 x 4096 x 256
+// with the fp32 copy of the output: T256 184 us, R128 143), 13-23 % for weights 11008 wide on 256 and 1024 rows (R64X128 taken, R128
+// faster); the 256-row tiles alone take 2.27 times as long as that over the forward products.  Forward products on R32 of up to
+// 256 pieces of 16 x 16 run as those (gemm_rows16.hip): up to twice as fast with long k, which the estimate does not know (off by 32 %
+// rms there).  What the lines amount to, with both sides measured (us, plain stores):
+//   a handful of rows: one chain of k per CU        16 x 1024 x 4096:   T256 67.1   R64    14.6   R32 5.1
+//   few tiles, the loads' latency decides          777 x 1024 x 4096:   T256 67.2   R64    16.4   R32 25.7
+//   half the CUs idle under T256                 16384 x 512 x 2048:   T256 43.4   R128   35.1
+//   N = 128 leaves T256 half its columns         16384 x 128 x 4096:   T256 70.0   R64x128 28.2
+//   few tiles and short k                         8192 x 512 x 256:   T256 10.6   R64x128 6.8
+//   the chip full                                16384 x 4096 x 256:   T256 46.2   R128   51.5
+//                                                16384 x 4096 x 2048:  T256 214.4  R128   263.7
 struct TileCost {
   int bm, bn, slots;
   float a, f, s0, s1, g, h;
@@ -612,7 +611,7 @@ constexpr float kRingMargin = 1.075f;
 // What a slice costs more with two k-major operands.  The 256-row kernels pay for their transpose reads.  The ring
 // tiles read 128 or 256 bytes per k row where those read 512, which shows when the rows come from HBM (2048 x 512
 // over 16384 tokens: R64x128 in 4 splits 60 us, T256 in 16 splits 45 us plus 6 us more in the finishing pass).  With these
-// factors the estimates of 360 weight gradients (512 .. 16384 tokens) are off by +4, -7, -1, +7, +9 and -12 % on average.
+// factors the estimates of 360 weight gradients (512 .. 16384 tokens) are 8, 0, 11, 10, 11 and 5 % too slow on average.
 constexpr float kKMajorSlice[] = {0.f, 1.13f, 1.05f, 1.5f, 1.5f, 1.3f, 1.5f};
 
 }  // namespace
